@@ -13,8 +13,8 @@ namespace mlmc {
 mlmc_status topk_zero(const mlmc_plan_t* pl, void* ws, int32_t* dev_status, hipStream_t st);
 mlmc_status topk_select(const mlmc_plan_t* pl, const TopkArgs& a, bool sums, bool vec, hipStream_t st);
 mlmc_status topk_compact(const mlmc_plan_t* pl, const TopkArgs& a, bool vec, hipStream_t st);
-mlmc_status bits_compress(const mlmc_plan_t* pl, const BitsArgs& a, bool vec, hipStream_t st);
-mlmc_status rtn_compress(const mlmc_plan_t* pl, const BitsArgs& a, bool vec, bool message, hipStream_t st);
+mlmc_status bits_compress(const mlmc_plan_t* pl, const BitsArgs& a, hipStream_t st);
+mlmc_status rtn_compress(const mlmc_plan_t* pl, const BitsArgs& a, bool message, hipStream_t st);
 mlmc_status agg_bits(const mlmc_plan_t* pl, const BitsArgs& b, const int32_t* level, const int32_t* scale_exp,
                      const uint64_t* planes, float alpha, float* out, float eta, float* x, hipStream_t st);
 mlmc_status agg_sparse(const mlmc_plan_t* pl, const int64_t* row_off, const uint32_t* idx, const float* val, int64_t capacity,
@@ -500,7 +500,7 @@ mlmc_status mlmc_level_norms(const mlmc_plan_t* plan, const void* g, int64_t ld,
         BitsArgs b;
         fill_bits_args(plan, b, g, ld, ws, dev_status);
         b.norms_user = norms;
-        return rtn_compress(plan, b, vec_ok(plan, g, ld), false, st);
+        return rtn_compress(plan, b, false, st);
     }
     if (plan->kind == MLMC_STOPK) {
         StopkArgs sa;
@@ -587,7 +587,7 @@ mlmc_status mlmc_compress_bits(const mlmc_plan_t* plan, const void* g, int64_t l
     b.planes = planes;
     b.seed = seed;
     b.step = step;
-    return bits_compress(plan, b, vec_ok(plan, g, ld), st);
+    return bits_compress(plan, b, st);
 }
 
 mlmc_status mlmc_compress_rtn(const mlmc_plan_t* plan, const void* g, int64_t ld, uint64_t seed, uint64_t step, int32_t* level,
@@ -602,7 +602,7 @@ mlmc_status mlmc_compress_rtn(const mlmc_plan_t* plan, const void* g, int64_t ld
     b.norms_user = norms_out;
     b.seed = seed;
     b.step = step;
-    return rtn_compress(plan, b, vec_ok(plan, g, ld), true, (hipStream_t)hip_stream);
+    return rtn_compress(plan, b, true, (hipStream_t)hip_stream);
 }
 
 mlmc_status mlmc_compress_bits_static(const mlmc_plan_t* plan, const void* g, int64_t ld, uint64_t seed, uint64_t step,

@@ -9,7 +9,7 @@
 //   k_tileoff       (fallback) per-tile offsets of index-sorted sparse rows by binary search
 //   k_agg_sparse    atomic-free segmented scatter-add: one workgroup owns one dense tile
 //   k_message_bits  bits on the wire of every row's message
-// The ladder of |g| / max|g| and the Round-to-Nearest ladder are launched from mlmc_vrtn.hip.
+// The Round-to-Nearest ladder is launched from mlmc_vrtn.hip.
 #include "mlmc_extract.h"
 
 namespace mlmc {
@@ -399,38 +399,23 @@ mlmc_status message_bits(const mlmc_plan_t* pl, const int32_t* level, unsigned l
 }
 
 // ---------------------------------------------------------------------------------------------------
-mlmc_status vbits_extract(const mlmc_plan_t* pl, const BitsArgs& a, bool vec, dim3 egrid, hipStream_t st);   // mlmc_vrtn.hip
-
-mlmc_status bits_compress(const mlmc_plan_t* pl, const BitsArgs& a0, bool vec, hipStream_t st) {
+mlmc_status bits_compress(const mlmc_plan_t* pl, const BitsArgs& a0, hipStream_t st) {
     BitsArgs a = a0;
     if (a.flt) MLMC_LAUNCH(K_DRAW, st, k_bits_prep<<<1, 1024, 0, st>>>(a));
-    // a wave takes about four tiles (its loads run ahead across tiles); at least some 2048 waves in all
-    int64_t ntiles = pl->ntiles;
-    int gx = (int)((ntiles + 15) / 16);
-    if ((int64_t)gx * pl->M < 512) gx = (int)((ntiles + 3) / 4);
-    int cap = 4096 / pl->M > 0 ? 4096 / pl->M : 1;
-    if (gx > cap) gx = cap;
-    if (gx < 1) gx = 1;
-    dim3 egrid(gx, pl->M);
-#define MLMC_EXTRACT_V(ID, DT, VEC, REDO, KIND, SMALL, BIG)                                                              \
+    const dim3 egrid = extract_grid(pl);
+#define MLMC_EXTRACT_B(ID, DT, REDO, KIND)                                                                               \
     do {                                                                                                                \
-        if (small) MLMC_LAUNCH(ID, st, k_bits_extract<DT, VEC, REDO, SMALL, KIND><<<egrid, 256, 0, st>>>(a));            \
-        else MLMC_LAUNCH(ID, st, k_bits_extract<DT, VEC, REDO, BIG, KIND><<<egrid, 256, 0, st>>>(a));                    \
+        if (a.F[0] == 0) MLMC_LAUNCH(ID, st, k_bits_extract<DT, REDO, KIND, false><<<egrid, EX_THREADS, 0, st>>>(a));    \
+        else MLMC_LAUNCH(ID, st, k_bits_extract<DT, REDO, KIND, true><<<egrid, EX_THREADS, 0, st>>>(a));                 \
     } while (0)
-#define MLMC_EXTRACT(ID, REDO, KIND, SMALL, BIG)                                                                         \
+#define MLMC_EXTRACT(ID, REDO, KIND)                                                                                     \
     do {                                                                                                                \
-        if (pl->dtype == MLMC_F32) {                                                                                    \
-            if (vec) MLMC_EXTRACT_V(ID, MLMC_F32, true, REDO, KIND, SMALL, BIG);                                         \
-            else MLMC_EXTRACT_V(ID, MLMC_F32, false, REDO, KIND, SMALL, BIG);                                            \
-        } else {                                                                                                        \
-            if (vec) MLMC_EXTRACT_V(ID, MLMC_BF16, true, REDO, KIND, SMALL, BIG);                                        \
-            else MLMC_EXTRACT_V(ID, MLMC_BF16, false, REDO, KIND, SMALL, BIG);                                           \
-        }                                                                                                               \
+        if (pl->dtype == MLMC_F32) MLMC_EXTRACT_B(ID, MLMC_F32, REDO, KIND);                                             \
+        else MLMC_EXTRACT_B(ID, MLMC_BF16, REDO, KIND);                                                                  \
     } while (0)
     if (a.flt) {
         // floating-point ladder (App. B): no scale, so nothing to find before the one read
-        const bool small = pl->nplanes <= 11;
-        MLMC_EXTRACT(K_BITS_EXTRACT, false, 1, 11, MAX_FPLANES);
+        MLMC_EXTRACT(K_BITS_EXTRACT, false, 1);
         return MLMC_OK;
     }
     // sampled (or, for short rows, exact) row maxima
@@ -444,19 +429,16 @@ mlmc_status bits_compress(const mlmc_plan_t* pl, const BitsArgs& a0, bool vec, h
     // the first launch of the call: its workgroups leave one maximum each (nothing to clear beforehand) and draw the levels
     static_assert(1024 <= SMAX_PARTS_MAX, "sw is at most 1024");
     a.smax_parts = (int32_t)sw;
-    if (pl->dtype == MLMC_F32) {
-        if (vec) MLMC_LAUNCH(K_BITS_MAX, st, k_bits_smax<MLMC_F32, true, true><<<sgrid, SMAX_THREADS, 0, st>>>(a));
-        else MLMC_LAUNCH(K_BITS_MAX, st, k_bits_smax<MLMC_F32, false, true><<<sgrid, SMAX_THREADS, 0, st>>>(a));
-    } else {
-        if (vec) MLMC_LAUNCH(K_BITS_MAX, st, k_bits_smax<MLMC_BF16, true, true><<<sgrid, SMAX_THREADS, 0, st>>>(a));
-        else MLMC_LAUNCH(K_BITS_MAX, st, k_bits_smax<MLMC_BF16, false, true><<<sgrid, SMAX_THREADS, 0, st>>>(a));
+    if (pl->dtype == MLMC_F32) MLMC_LAUNCH(K_BITS_MAX, st, k_bits_smax<MLMC_F32, true><<<sgrid, SMAX_THREADS, 0, st>>>(a));
+    else MLMC_LAUNCH(K_BITS_MAX, st, k_bits_smax<MLMC_BF16, true><<<sgrid, SMAX_THREADS, 0, st>>>(a));
+    if (a.vmx) {   // the maxima above are exact (every block was read): one extraction
+        MLMC_EXTRACT(K_BITS_EXTRACT, false, 2);
+        return MLMC_OK;
     }
-    const bool small = pl->nplanes <= 9;
-    if (a.vmx) return vbits_extract(pl, a, vec, egrid, st);   // the maxima above are exact (every block was read): one extraction
-    MLMC_EXTRACT(K_BITS_EXTRACT, false, 0, 9, MAX_PLANES);
-    if (a.sample_shift > 0) MLMC_EXTRACT(K_BITS_REDO, true, 0, 9, MAX_PLANES);   // rows whose sampled maximum fell short (returns at once for the others)
-#undef MLMC_EXTRACT_V
+    MLMC_EXTRACT(K_BITS_EXTRACT, false, 0);
+    if (a.sample_shift > 0) MLMC_EXTRACT(K_BITS_REDO, true, 0);   // rows whose sampled maximum fell short (returns at once for the others)
 #undef MLMC_EXTRACT
+#undef MLMC_EXTRACT_B
     return MLMC_OK;
 }
 

@@ -111,7 +111,11 @@ __device__ __forceinline__ uint64_t sig_square(uint32_t key) {
 }
 
 // ---- row loaders: four consecutive elements starting at j (j % 4 == 0), as fp32 bit patterns -------
-// DT = MLMC_F32 / MLMC_BF16.  VEC: the row start and ld allow one aligned 16-byte (8-byte for bf16) load.
+// DT = MLMC_F32 / MLMC_BF16.  VEC: one 16-byte (8-byte for bf16) load for the four; it needs the alignment of an element
+// only (the memory system takes unaligned wide loads: the maximum of 8 rows of 11,689,513 fp32 elements takes 62 us, as that of
+// aligned rows does, and took 68 us with single-element loads).
+typedef uint32_t u32x4_f32 __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32x2_bf16 __attribute__((ext_vector_type(2), aligned(2)));
 template <int DT, bool VEC>
 struct RowLoader {
     const void* row;
@@ -129,7 +133,7 @@ struct RowLoader {
         if (DT == MLMC_F32) {
             const uint32_t* p = (const uint32_t*)row + j;
             if (VEC && nv == 4) {
-                uint4 v = *(const uint4*)p;
+                const u32x4_f32 v = *(const u32x4_f32*)p;
                 b[0] = v.x; b[1] = v.y; b[2] = v.z; b[3] = v.w;
             } else {
 #pragma unroll
@@ -138,7 +142,7 @@ struct RowLoader {
         } else {
             const uint16_t* p = (const uint16_t*)row + j;
             if (VEC && nv == 4) {
-                uint2 v = *(const uint2*)p;
+                const u32x2_bf16 v = *(const u32x2_bf16*)p;
                 b[0] = v.x << 16; b[1] = v.x & 0xFFFF0000u; b[2] = v.y << 16; b[3] = v.y & 0xFFFF0000u;
             } else {
 #pragma unroll
@@ -153,7 +157,7 @@ struct RowLoader {
         if (DT == MLMC_F32) {
             const uint32_t* p = (const uint32_t*)row + j;
             if (VEC) {
-                uint4 v = *(const uint4*)p;
+                const u32x4_f32 v = *(const u32x4_f32*)p;
                 b[0] = v.x; b[1] = v.y; b[2] = v.z; b[3] = v.w;
             } else {
 #pragma unroll
@@ -162,7 +166,7 @@ struct RowLoader {
         } else {
             const uint16_t* p = (const uint16_t*)row + j;
             if (VEC) {
-                uint2 v = *(const uint2*)p;
+                const u32x2_bf16 v = *(const u32x2_bf16*)p;
                 b[0] = v.x << 16; b[1] = v.x & 0xFFFF0000u; b[2] = v.y << 16; b[3] = v.y & 0xFFFF0000u;
             } else {
 #pragma unroll
@@ -173,13 +177,11 @@ struct RowLoader {
     // load4_full for a row that is streamed through once: a non-temporal load, so that the row does not push
     // what the kernel writes and reads back soon after (its staged lists) out of the L2
     __device__ __forceinline__ void load4_stream(int64_t j, uint32_t (&b)[4]) const {
-        typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-        typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
         if (DT == MLMC_F32 && VEC) {
-            const u32x4 v = __builtin_nontemporal_load((const u32x4*)((const uint32_t*)row + j));
+            const u32x4_f32 v = __builtin_nontemporal_load((const u32x4_f32*)((const uint32_t*)row + j));
             b[0] = v.x; b[1] = v.y; b[2] = v.z; b[3] = v.w;
         } else if (DT != MLMC_F32 && VEC) {
-            const u32x2 v = __builtin_nontemporal_load((const u32x2*)((const uint16_t*)row + j));
+            const u32x2_bf16 v = __builtin_nontemporal_load((const u32x2_bf16*)((const uint16_t*)row + j));
             b[0] = v.x << 16; b[1] = v.x & 0xFFFF0000u; b[2] = v.y << 16; b[3] = v.y & 0xFFFF0000u;
         } else {
             load4_full(j, b);

@@ -1,27 +1,7 @@
-// Fixed-point ladder of |g| / max|g| (Sec. 3.1 as written) and Round-to-Nearest MLMC (Sec. 3.3, App. G.2) on gfx950:
-// the launches that need the exact largest entry of a row before the extraction.
+// Round-to-Nearest MLMC (Sec. 3.3, App. G.2) on gfx950.
 #include "mlmc_extract.h"
 
 namespace mlmc {
-
-// The extraction of the largest-entry ladder: the maxima are exact (every block was read), one launch.
-mlmc_status vbits_extract(const mlmc_plan_t* pl, const BitsArgs& a, bool vec, dim3 egrid, hipStream_t st) {
-    const bool small = pl->nplanes <= 9;
-#define MLMC_VEXTRACT(DT, VEC)                                                                                           \
-    do {                                                                                                                \
-        if (small) MLMC_LAUNCH(K_BITS_EXTRACT, st, k_bits_extract<DT, VEC, false, 9, 2><<<egrid, 256, 0, st>>>(a));       \
-        else MLMC_LAUNCH(K_BITS_EXTRACT, st, k_bits_extract<DT, VEC, false, MAX_PLANES, 2><<<egrid, 256, 0, st>>>(a));   \
-    } while (0)
-    if (pl->dtype == MLMC_F32) {
-        if (vec) MLMC_VEXTRACT(MLMC_F32, true);
-        else MLMC_VEXTRACT(MLMC_F32, false);
-    } else {
-        if (vec) MLMC_VEXTRACT(MLMC_BF16, true);
-        else MLMC_VEXTRACT(MLMC_BF16, false);
-    }
-#undef MLMC_VEXTRACT
-    return MLMC_OK;
-}
 
 // ---------------------------------------------------------------------------------------------------
 // Round-to-Nearest MLMC.  k_rtn_prep clears the per-row state; k_bits_smax (every block) finds c; k_rtn_norms sums
@@ -37,13 +17,13 @@ __global__ __launch_bounds__(256) void k_rtn_prep(BitsArgs a) {
     if (t < a.M * a.L * 2) a.rtn_sums[t] = 0ull;
 }
 
-template <int DT, bool VEC>
+template <int DT>
 __global__ __launch_bounds__(256) void k_rtn_norms(BitsArgs a) {
     const int row = blockIdx.y;
     const uint32_t ckey = a.racc[row].smpmax_key;
     if (ckey == 0u) return;   // a zero row: every residual is zero
     const double c = key_to_double(ckey), den = 2.0 * c, inv_den = __ddiv_rn(1.0, den);
-    RowLoader<DT, VEC> ld(a.g, a.ld, a.d, row);
+    RowLoader<DT, true> ld(a.g, a.ld, a.d, row);
     const int L = a.L;
     // Everything below is fp64 arithmetic on integers that fp64 holds exactly: |g| D has 40 bits, a code 16, a residual
     // integer k fewer than 18, k^2 fewer than 36, and a thread adds far fewer than 2^17 of them per level.
@@ -174,28 +154,117 @@ __global__ __launch_bounds__(64) void k_rtn_draw(BitsArgs a, int norms_only) {
     a.scale_exp[2 * row + 1] = (int32_t)__float_as_uint(pl == 0.0 ? 0.0f : (float)__ddiv_rn(f, pl));
 }
 
-template <int DT, bool VEC>
-__global__ __launch_bounds__(256) void k_rtn_extract(BitsArgs a) {
-    __shared__ __align__(16) uint32_t s_tr[4][1024];
-    uint32_t* slds = s_tr[threadIdx.x >> 6];
+struct RtnPlaneCode {    // one of the (up to three) codes of a row's message
+    double mul_in, mul_out;   // D / 2c, moved towards and away from zero
+    RtnCode code;
+    int32_t at;               // its first plane
+};
+// Code planes of the drawn message.  A code n = rne(a D / 2c) comes from one fused multiply-add: a * fl(D / 2c) plus
+// 1.5 2^52 leaves the rounded integer, sign included, in the low word.  Rounding the multiplier can only matter at an
+// exact half-integer (the exact quotient is otherwise at least 2^-40 of itself away from one: its numerator is an
+// integer below 2^40), so the product is formed twice, with the multiplier moved 2^-44 towards and away from zero:
+// where the two agree the code is exact; a block where they differ anywhere (a tie; always at the largest entry itself,
+// whose code is cut) and a row of non-finite numbers have their codes computed the long way.
+// A block's elements stay in LDS and are read once per code, so that the codes in the making are all the registers hold.
+template <int DT>
+__global__ __launch_bounds__(EX_THREADS, 4) void k_rtn_extract(BitsArgs a) {
+    typedef BlockLoader<DT> Loader;
+    __shared__ __align__(16) unsigned char s_buf[EX_THREADS / 64][EX_ELEMS * 4];
+    __shared__ RtnPlaneCode s_code[3];
     const int row = blockIdx.y;
     const int level = a.rinfo[row].level;
-    RtnRow rr;
-    rr.c = key_to_double(a.racc[row].smpmax_key);
-    rr.den = 2.0 * rr.c;
-    rr.inv_den = rr.c > 0.0 ? __ddiv_rn(1.0, rr.den) : 0.0;
-    rr.code[0] = rtn_code_of(a.F[0]);
-    rr.code[1] = rtn_code_of(level > 1 ? a.F[level - 1] : 0);
-    rr.code[2] = rtn_code_of(a.F[level]);
-    const int np = rr.code[0].b + rr.code[1].b + rr.code[2].b;
-    uint32_t maxkey = 0;
-    if (np <= 8) bits_extract_tiles<DT, VEC, 8, 5>(a, row, 1, level, np, maxkey, slds, 0.0, 0.0, &rr);
-    else if (np <= 16) bits_extract_tiles<DT, VEC, 16, 5>(a, row, 1, level, np, maxkey, slds, 0.0, 0.0, &rr);
-    else bits_extract_tiles<DT, VEC, MAX_FPLANES, 5>(a, row, 1, level, np, maxkey, slds, 0.0, 0.0, &rr);
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = lane_id();
+    const int64_t nblk = (a.d + EX_ELEMS - 1) / EX_ELEMS, nwhole = a.d / EX_ELEMS;
+    const int64_t stride = (int64_t)gridDim.x * (EX_THREADS / 64);
+    int64_t blk = (int64_t)blockIdx.x * (EX_THREADS / 64) + wave;
+    const Loader ld(a.g, a.ld, a.d, row);
+    const uint32_t ckey = a.racc[row].smpmax_key;
+    const double c = key_to_double(ckey), den = 2.0 * c;
+    // the codes of the message in plane order: the base's (b_0 > 0), the previous level's (l > 1), the drawn level's
+    const int b0 = a.F[0], b1 = level > 1 ? a.F[level - 1] : 0, b2 = a.F[level];
+    const int nc = (b0 > 0 ? 1 : 0) + (b1 > 0 ? 1 : 0) + 1, np = b0 + b1 + b2;
+    if (threadIdx.x < 3) {
+        const int b = threadIdx.x == 0 ? b0 : threadIdx.x == 1 ? b1 : b2;
+        if (b > 0) {
+            RtnPlaneCode& k = s_code[threadIdx.x == 0 ? 0 : threadIdx.x == 1 ? nc - 2 : nc - 1];
+            k.code = rtn_code_of(b);
+            const double mul = c > 0.0 ? __ddiv_rn(k.code.D, den) : 0.0;   // a zero row has only zero codes
+            k.mul_in = __dmul_rn(mul, 1.0 - 0x1p-44);
+            k.mul_out = __dmul_rn(mul, 1.0 + 0x1p-44);
+            k.at = threadIdx.x == 0 ? 0 : threadIdx.x == 1 ? b0 : b0 + b1;
+        }
+    }
+    __syncthreads();
+    unsigned char* buf = s_buf[wave];
+    for_blocks(ld, buf, blk, stride, nblk, nwhole, [&](int64_t at_blk) {
+        uint32_t x[32], tie = ckey >= 0x7F800000u ? 1u : 0u;
+#pragma unroll
+        for (int i = 0; i < 32; ++i) x[i] = 0;
+#pragma unroll 1
+        for (int k = 0; k < nc; ++k) {
+            const double mul_in = s_code[k].mul_in, mul_out = s_code[k].mul_out;
+            const uint32_t mask = (1u << s_code[k].code.b) - 1u, at = (uint32_t)s_code[k].at;
+            wave_lds_sync();   // the elements are read again for every code (kept, their doubles would take 64 registers)
+            const uint32_t from = ld.take_at(wave * (EX_ELEMS * 4));
+#pragma unroll
+            for (int h = 0; h < Loader::CPL; ++h) {
+                uint32_t b[Loader::EPC];
+                ld.take_chunk(&s_buf[0][0], from, h, b);
+#pragma unroll
+                for (int i = 0; i < Loader::EPC; ++i) {
+                    const double av = (double)__uint_as_float(b[i]);
+                    const int n = __double2loint(__fma_rn(av, mul_in, 0x1.8p52)), m = __double2loint(__fma_rn(av, mul_out, 0x1.8p52));
+                    tie |= (uint32_t)(n ^ m);
+                    x[h * Loader::EPC + i] |= ((uint32_t)n & mask) << at;
+                }
+            }
+        }
+        if (__builtin_expect(__ballot(tie != 0u) != 0ull, 0)) {
+            RowLoader<DT, false> ld1(a.g, a.ld, a.d, row);
+            const int64_t j0 = at_blk * EX_ELEMS + 32 * (int64_t)lane;
+            const double inv_den = c > 0.0 ? __ddiv_rn(1.0, den) : 0.0;
+            wave_lds_sync();   // every lane has read its elements: their place takes the codes
+            uint32_t* mine = (uint32_t*)buf + 32 * lane;
+#pragma unroll 1
+            for (int i = 0; i < 32; ++i) {
+                uint32_t v = 0;
+                const uint32_t bits = j0 + i < a.d ? ld1.load1(j0 + i) : 0u;
+#pragma unroll 1
+                for (int k = 0; k < nc; ++k) {
+                    const RtnCode kc = s_code[k].code;
+                    int32_t n = c > 0.0 ? rtn_code_abs(key_to_double(key_of_bits(bits)), kc, c, den, inv_den) : 0;
+                    n = (int32_t)bits < 0 ? -n : n;
+                    v |= ((uint32_t)n & ((1u << kc.b) - 1u)) << s_code[k].at;
+                }
+                mine[i] = v;
+            }
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const uint4 v = ((const uint4*)mine)[i];
+                x[4 * i] = v.x; x[4 * i + 1] = v.y; x[4 * i + 2] = v.z; x[4 * i + 3] = v.w;
+            }
+        }
+        if (at_blk * 64 + lane < a.nwords * 2) {   // a plane's half words end inside the row's last block
+            PlaneWriter w(a, row, at_blk);
+            uint32_t r[8];
+            auto put = [&](auto byte) {
+                constexpr int B = decltype(byte)::value;
+                gather_bytes<B>(x, r);
+                transpose8(r);
+#pragma unroll
+                for (int p = 0; p < 8; ++p)
+                    if (8 * B + p < np) w.put(r[p]);   // uniform
+            };
+            put(std::integral_constant<int, 0>{});
+            if (np > 8) put(std::integral_constant<int, 1>{});
+            if (np > 16) put(std::integral_constant<int, 2>{});
+            if (np > 24) put(std::integral_constant<int, 3>{});
+        }
+    });
 }
 
 // Round-to-Nearest MLMC: largest entry, residual sums, draw, codes.  message == false: norms only.
-mlmc_status rtn_compress(const mlmc_plan_t* pl, const BitsArgs& a, bool vec, bool message, hipStream_t st) {
+mlmc_status rtn_compress(const mlmc_plan_t* pl, const BitsArgs& a, bool message, hipStream_t st) {
     const int M = pl->M;
     int pb = (M * pl->L * 2 + 255) / 256;
     if (pb < (M + 255) / 256) pb = (M + 255) / 256;
@@ -213,29 +282,18 @@ mlmc_status rtn_compress(const mlmc_plan_t* pl, const BitsArgs& a, bool vec, boo
     if (nw < nmin) nw = nmin;
     if (nw < 1) nw = 1;
     const dim3 ngrid((unsigned)nw, M);
-    int64_t ntiles = pl->ntiles;
-    int gx = (int)((ntiles + 15) / 16);
-    if ((int64_t)gx * M < 512) gx = (int)((ntiles + 3) / 4);
-    const int cap = 4096 / M > 0 ? 4096 / M : 1;
-    if (gx > cap) gx = cap;
-    if (gx < 1) gx = 1;
-    const dim3 egrid(gx, M);
+    const dim3 egrid = extract_grid(pl);
     // with the plan's own probabilities the draw needs no norms: that read of the input is made only when they are asked for
     const bool need_norms = pl->adaptive || !message || a.norms_user != nullptr;
-#define MLMC_RTN_STEPS(DT, VEC)                                                                                          \
+#define MLMC_RTN_STEPS(DT)                                                                                               \
     do {                                                                                                                \
-        MLMC_LAUNCH(K_BITS_MAX, st, k_bits_smax<DT, VEC, false><<<sgrid, SMAX_THREADS, 0, st>>>(a));                            \
-        if (need_norms) MLMC_LAUNCH(K_RTN_NORMS, st, k_rtn_norms<DT, VEC><<<ngrid, 256, 0, st>>>(a));                     \
+        MLMC_LAUNCH(K_BITS_MAX, st, k_bits_smax<DT, false><<<sgrid, SMAX_THREADS, 0, st>>>(a));                            \
+        if (need_norms) MLMC_LAUNCH(K_RTN_NORMS, st, k_rtn_norms<DT><<<ngrid, 256, 0, st>>>(a));                     \
         MLMC_LAUNCH(K_RTN_DRAW, st, k_rtn_draw<<<(M + 63) / 64, 64, 0, st>>>(a, message ? 0 : 1));                        \
-        if (message) MLMC_LAUNCH(K_BITS_EXTRACT, st, k_rtn_extract<DT, VEC><<<egrid, 256, 0, st>>>(a));                  \
+        if (message) MLMC_LAUNCH(K_BITS_EXTRACT, st, k_rtn_extract<DT><<<egrid, EX_THREADS, 0, st>>>(a));                  \
     } while (0)
-    if (pl->dtype == MLMC_F32) {
-        if (vec) MLMC_RTN_STEPS(MLMC_F32, true);
-        else MLMC_RTN_STEPS(MLMC_F32, false);
-    } else {
-        if (vec) MLMC_RTN_STEPS(MLMC_BF16, true);
-        else MLMC_RTN_STEPS(MLMC_BF16, false);
-    }
+    if (pl->dtype == MLMC_F32) MLMC_RTN_STEPS(MLMC_F32);
+    else MLMC_RTN_STEPS(MLMC_BF16);
 #undef MLMC_RTN_STEPS
     return MLMC_OK;
 }

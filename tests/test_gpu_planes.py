@@ -1,0 +1,91 @@
+"""GPU parity of the plane packing itself: blocks of 2048 elements dealt to lanes of 32, at the edges of lanes, words and
+blocks, for rows that start at any element, both input types and every plane count class, bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+import mlmc_workloads as W
+import paper_2507_05508_amd as P
+from oracle import mlmc as O
+from gpu_util import to_device
+
+pytestmark = pytest.mark.gpu
+
+KINDS = {  # kind, ladders (with and without a base field; one, two and three bytes of level planes), oracle
+    "bits": (P.MLMC_BITS, [[0, 1, 2, 4, 8, 16], [3, 24], [0, 24]], O.compress_bits, O.aggregate_bits),
+    "vbits": (P.MLMC_VBITS, [[0, 1, 2, 4, 8, 16], [3, 24], [0, 24]], O.compress_vbits, O.aggregate_vbits),
+    "fbits": (P.MLMC_FBITS, [[0, 1, 2, 3, 5, 8, 23], [9, 16, 23], [2, 7, 15]], O.compress_fbits, O.aggregate_fbits),
+    "rtn": (P.MLMC_RTN, [[0, 2, 4, 8, 16], [5, 9, 16], [0, 1]], O.compress_rtn, O.aggregate_rtn),
+}
+
+
+def _one(kind, F, G, g, step, alpha, tag):
+    code, _, compress, aggregate = KINDS[kind]
+    M, d = G.shape
+    G32 = W.bf16_bits_to_f32(G) if G.dtype == np.uint16 else G
+    p = O.geometric_p(len(F) - 1)
+    plan = P.Plan(code, M, d, P.MLMC_BF16 if G.dtype == np.uint16 else P.MLMC_F32, F, p)
+    print(f"planes {kind} F={F} M={M} d={d} {G.dtype} {tag} step={step}", flush=True)
+    msg = P.mlmc_compress_rtn(plan, g, 4, step) if kind == "rtn" else P.mlmc_compress_bits(plan, g, 4, step)
+    out = P.mlmc_aggregate(plan, msg, alpha)
+    torch.cuda.synchronize()
+    assert plan.status() == 0
+    want = compress(G32, F, p, 4, step)
+    planes = msg.planes.cpu().numpy().view(np.uint64)
+    for i in range(M):
+        n = want[i]["planes"].shape[0]
+        assert int(msg.level[i]) == want[i]["level"]
+        assert np.array_equal(planes[i, :n], want[i]["planes"]), f"row {i}"
+    assert np.array_equal(out.cpu().numpy().view(np.uint32), aggregate(want, F, d, alpha).view(np.uint32))
+
+
+@pytest.mark.parametrize("kind", list(KINDS))
+@pytest.mark.parametrize("bf16", [False, True])
+def test_planes_at_the_edges_of_lanes_words_and_blocks(kind, bf16):
+    rng = np.random.default_rng(9)
+    for n, d in enumerate([1, 31, 32, 33, 64, 65, 2047, 2048, 2049, 4 * 2048 + 2016, 9 * 2048 + 1]):
+        G = (rng.standard_normal((2, d)) * np.exp(rng.uniform(-6, 3, size=(2, d)))).astype(np.float32)
+        if bf16:
+            G = W.f32_to_bf16_bits(G)
+        base = to_device(G, ld=d + 5 + n % 3)
+        M = base.shape[0]
+        buf = torch.zeros(M * (d + 11) + 8, dtype=base.dtype, device="cuda")
+        for off in (0, 1, 3):   # rows that start at any element
+            ld = d + 11 if off else d + 5
+            g = torch.as_strided(buf, (M, d), (ld, 1), off)
+            g.copy_(base)
+            for F in KINDS[kind][1]:
+                _one(kind, F, G, g, n + off, 0.5, f"offset {off} ld {ld}")
+
+
+@pytest.mark.parametrize("kind", ["bits", "vbits"])
+def test_planes_of_rows_with_non_finite_entries(kind):
+    """A row that holds Inf or NaN takes its scale from the largest bit pattern, read as a number: digits by integer arithmetic."""
+    d, F = 4096 + 77, [0, 3, 8]
+    rng = np.random.default_rng(3)
+    G = (rng.standard_normal((2, d)) * np.exp(rng.uniform(-80, 88, size=(2, d)))).astype(np.float32)
+    G[0, 5] = np.inf
+    G[1, 9] = -np.inf
+    G[1, 4000] = np.nan
+    p = O.geometric_p(2)
+    plan = P.Plan(KINDS[kind][0], 2, d, P.MLMC_F32, F, p)
+    for step in range(3):
+        print(f"non-finite {kind} step={step}", flush=True)
+        msg = P.mlmc_compress_bits(plan, to_device(G), 4, step)
+        torch.cuda.synchronize()
+        assert plan.status() == P.MLMC_DEV_NONFINITE
+        planes = msg.planes.cpu().numpy().view(np.uint64)
+        for i in range(2):
+            key = (G[i].view(np.uint32) & np.uint32(0x7FFFFFFF)).astype(np.int64)
+            E = np.maximum(key >> 23, 1)
+            sig = np.where(key >> 23, (key & 0x7FFFFF) | 0x800000, key)
+            k = int(np.argmax(key))
+            if kind == "bits":
+                m = [int(s) >> (24 - 8 + 255 - int(e)) for s, e in zip(sig, E)]
+            else:
+                m = [min((int(s) << 8) * 2 ** int(e) // (int(sig[k]) * 2 ** int(E[k])), 255) for s, e in zip(sig, E)]
+            level = int(msg.level[i])
+            field = (np.array(m) >> (8 - F[level])) & ((1 << (F[level] - F[level - 1])) - 1)
+            assert np.array_equal(planes[i, 0], O.pack_plane((G[i].view(np.uint32) >> 31).astype(np.uint8)))
+            for b in range(F[level] - F[level - 1]):
+                assert np.array_equal(planes[i, 1 + b], O.pack_plane(((field >> b) & 1).astype(np.uint8))), (i, b)
