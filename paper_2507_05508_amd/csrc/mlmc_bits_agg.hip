@@ -5,7 +5,7 @@
 //   k_bits_extract  the one full read: digits floor(|g_j| / s * 2^F), sign plane + field planes packed by wave      [mlmc_extract.h]
 //                   ballot, and the true row maximum; a row whose true maximum has a larger exponent than the
 //                   sampled one is extracted again by a second launch (which returns at once for every other row)
-//   k_agg_bits      out = alpha * sum_i decode_i, rows added in worker order (all plane messages, Round-to-Nearest included)
+//   k_agg_planes    out = alpha * sum_i decode_i, rows added in worker order (all plane messages, Round-to-Nearest included)
 //   k_tileoff       (fallback) per-tile offsets of index-sorted sparse rows by binary search
 //   k_agg_sparse    atomic-free segmented scatter-add: one workgroup owns one dense tile
 //   k_message_bits  bits on the wire of every row's message
@@ -52,183 +52,302 @@ struct AggBitsArgs {
     float alpha, eta;
 };
 
-// out[j] = alpha * sum over rows (worker order) of sign * (f0 * c0 + f * cl): Alg. 2 "Server aggregates".
-// A wave owns eight consecutive words of every plane, i.e. 512 consecutive elements; lane = element within a word.
-// The eight words of a (row, plane) are one 64-byte scalar load: a plane word is wave-uniform data, and as a
-// scalar register pair it is at once the lane mask "this element's bit is set".  A row whose level field is a
-// single bit (the most likely levels) costs two selects and one add per element.
-struct Words8 {
-    uint64_t w[8];
+// out[j] = alpha * sum over rows (worker order) of the decoded messages: Alg. 2 "Server aggregates".
+//
+// The extraction's packing run backwards: a wave owns a block of EX_ELEMS elements, a lane 32 of them (half a word of every
+// plane) and their sums in registers.  Eight planes of a row transposed (transpose8) are the low bytes of the lane's 32 values, so
+// that a value costs an instruction or two to assemble whatever its width.  8 rows of 1.17e7 elements: 33 us at two or three planes
+// (wave latency: a wave's rows come one after the other), 40 us at ten (0.16 GB, 4 TB/s), 44 us for Round-to-Nearest codes; with plane
+// words as wave-wide lane masks, one conditional add per plane, it took 48, 136 and 114 us.
+// The next row's first planes (the low eight of both codes for Round-to-Nearest) are in flight while a row is decoded.  The sums leave through LDS in the order of the
+// loads of the extraction, so that the dense vector is read and written 1 KB at a time.
+// PK 0: fixed point (both scales), 1: floating point, 2: Round-to-Nearest.  BASE: the ladder has a base field (F_0 > 0).
+struct AggRow {          // per row, in LDS
+    float c0, cl;
+    int32_t np;          // planes of the message
+    int32_t w, fl;       // fixed point: width of the level field; floating point: and digits of the level; codes: width of the drawn and of the previous code
 };
-__device__ __forceinline__ Words8 load_words8(const uint64_t* __restrict__ p, int nvalid) {
-    Words8 r;
-    if (nvalid >= 8) {   // uniform
-        r = *(const Words8*)p;
-    } else {             // the last words of a plane: nothing is read past the plane's end
-#pragma unroll
-        for (int k = 0; k < 8; ++k) r.w[k] = k < nvalid ? p[k] : 0ull;
-    }
-    return r;
+
+// The values of w <= 24 planes, v[0] the least significant, as numbers: u[e] for the lane's 32 elements.  G: groups of eight planes.
+template <int G>
+__device__ __forceinline__ uint32_t assemble(const uint32_t (&r)[3][8], int i, int k) {
+    if (G == 1) return (r[0][i] >> (8 * k)) & 0xFFu;
+    const uint32_t lo = __builtin_amdgcn_perm(r[1][i], r[0][i], 0x0C0C0400u + 0x0101u * (uint32_t)k);
+    if (G == 2) return lo;
+    return __builtin_amdgcn_perm(r[2][i], lo, 0x0C040100u + 0x010000u * (uint32_t)k);
 }
 
-__global__ __launch_bounds__(256) void k_agg_bits(AggBitsArgs a, const uint64_t* __restrict__ planes, float* __restrict__ out,
-                                                  float* __restrict__ x) {
-    __shared__ float s_c0[MLMC_MAX_WORKERS], s_cl[MLMC_MAX_WORKERS];
-    __shared__ uint8_t s_w[MLMC_MAX_WORKERS], s_fl[MLMC_MAX_WORKERS];
+template <int PK, bool BASE>
+__global__ __launch_bounds__(EX_THREADS, 4) void k_agg_planes(AggBitsArgs a, const uint64_t* __restrict__ planes, float* __restrict__ out,
+                                                              float* __restrict__ x) {
+    extern __shared__ __align__(16) unsigned char s_dyn_planes[];   // the waves' blocks of sums on their way out, then the rows' records
+    AggRow* s_row = (AggRow*)(s_dyn_planes + (EX_THREADS / 64) * EX_ELEMS * 4);
     const BitsArgs& b = a.b;
-    const int F0 = b.F[0];
-    for (int r = threadIdx.x; r < b.M; r += 256) {
+    const int F0 = BASE ? b.F[0] : 0;
+    for (int r = threadIdx.x; r < b.M; r += EX_THREADS) {
         int lev = a.level[r];
         lev = lev < 1 ? 1 : (lev > b.L ? b.L : lev);
-        double pl = b.p_fixed[lev - 1];
-        if (b.rtn) {   // Round-to-Nearest: c_0 = fp32(2c / D_0); the coefficient comes with the message
+        const double pl = b.p_fixed[lev - 1];
+        AggRow q;
+        q.c0 = 0.0f;
+        q.w = b.F[lev] - b.F[lev - 1];
+        q.fl = b.F[lev];
+        if (PK == 2) {          // c_0 = fp32(2c / D_0); the coefficient comes with the message
             const double c = key_to_double((uint32_t)a.scale_exp[2 * r] & 0x7FFFFFFFu);
-            s_c0[r] = F0 > 0 ? (float)__ddiv_rn(__dmul_rn(2.0, c), (double)((1 << F0) - 1)) : 0.0f;
-            s_cl[r] = __uint_as_float((uint32_t)a.scale_exp[2 * r + 1]);
-            s_w[r] = (uint8_t)b.F[lev];                          // width of the drawn level's code
-            s_fl[r] = (uint8_t)(lev > 1 ? b.F[lev - 1] : 0);     // width of the previous level's code when it is sent
-            continue;
-        }
-        if (b.flt) {   // the level's weight fp32(1 / p_l)
-            s_c0[r] = 0.0f;
-            s_cl[r] = pl == 0.0 ? 0.0f : (float)__ddiv_rn(1.0, pl);
-        } else if (b.vmx) {   // the scale field carries the largest entry v: c_0 = fp32(v 2^-F_0), c_l = fp32(v 2^-F_l / p_l)
-            const uint32_t vkey = (uint32_t)a.scale_exp[r] & 0x7FFFFFFFu, vE = vkey >> 23;
-            const double vd = ldexp((double)(vE ? (vkey & 0x7FFFFFu) | 0x800000u : vkey), (int)(vE ? vE : 1u) - 150);
-            s_c0[r] = (float)ldexp(vd, -F0);
-            s_cl[r] = pl == 0.0 ? 0.0f : (float)__ddiv_rn(ldexp(vd, -b.F[lev]), pl);
+            if (BASE) q.c0 = (float)__ddiv_rn(__dmul_rn(2.0, c), (double)((1 << F0) - 1));
+            q.cl = __uint_as_float((uint32_t)a.scale_exp[2 * r + 1]);
+            q.w = b.F[lev];                          // width of the drawn level's code
+            q.fl = lev > 1 ? b.F[lev - 1] : 0;       // width of the previous level's code when it is sent
+            q.np = F0 + q.fl + q.w;
+        } else if (PK == 1) {   // the level's weight fp32(1 / p_l)
+            q.cl = pl == 0.0 ? 0.0f : (float)__ddiv_rn(1.0, pl);
+            q.np = 9 + F0 + q.w;
         } else {
-            int e = a.scale_exp[r];
-            s_c0[r] = (float)ldexp(1.0, e - F0);
-            s_cl[r] = pl == 0.0 ? 0.0f : (float)__ddiv_rn(ldexp(1.0, e - b.F[lev]), pl);
+            if (b.vmx) {        // the scale field carries the largest entry v: c_0 = fp32(v 2^-F_0), c_l = fp32(v 2^-F_l / p_l)
+                const double vd = key_to_double((uint32_t)a.scale_exp[r] & 0x7FFFFFFFu);
+                if (BASE) q.c0 = (float)ldexp(vd, -F0);
+                q.cl = pl == 0.0 ? 0.0f : (float)__ddiv_rn(ldexp(vd, -b.F[lev]), pl);
+            } else {
+                const int e = a.scale_exp[r];
+                if (BASE) q.c0 = (float)ldexp(1.0, e - F0);
+                q.cl = pl == 0.0 ? 0.0f : (float)__ddiv_rn(ldexp(1.0, e - b.F[lev]), pl);
+            }
+            q.np = 1 + F0 + q.w;
         }
-        s_w[r] = (uint8_t)(b.F[lev] - b.F[lev - 1]);
-        s_fl[r] = (uint8_t)b.F[lev];
+        s_row[r] = q;
     }
     __syncthreads();
-    const uint32_t lane = lane_id();
-    const int64_t nw = b.nwords;
-    const int64_t nblk = (nw + 7) / 8;
-    const int64_t wave_global = __builtin_amdgcn_readfirstlane((int)(((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6));
-    const int64_t nwaves = ((int64_t)gridDim.x * 256) >> 6;
-    for (int64_t blk = wave_global; blk < nblk; blk += nwaves) {
-        const int64_t w0 = blk * 8;
-        const int nvalid = nw - w0 < 8 ? (int)(nw - w0) : 8;
-        float acc[8];
+    const uint32_t lane = lane_id(), wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t blk = (int64_t)blockIdx.x * (EX_THREADS / 64) + wave;
+    const int64_t nw2 = b.nwords * 2, h0 = blk * 64;   // half words of a plane; the block's first
+    if (h0 >= nw2) return;
+    const uint32_t last = nw2 - h0 < 64 ? (uint32_t)(nw2 - h0) - 1u : 63u;   // lanes past a plane's end read its last half word again
+    const uint32_t off = (lane < last ? lane : last) * 4u;
+    typedef const __attribute__((address_space(1))) char* GlobalBytes;
+    const size_t step = (size_t)b.nwords * 8;
+    const GlobalBytes base = (GlobalBytes)planes + h0 * 4;
+    auto plane = [&](GlobalBytes row, int p) -> uint32_t { return *(const __attribute__((address_space(1))) uint32_t*)(row + (size_t)p * step + off); };
+    auto uni = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
+    auto funi = [](float v) { return __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(v))); };
+
+    float acc[32];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) acc[k] = 0.0f;
-        for (int r = 0; r < b.M; ++r) {   // rows in worker order
-            const int wd = __builtin_amdgcn_readfirstlane((int)s_w[r]);
-            const float cl = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(s_cl[r])));
-            const uint64_t* rp = planes + (size_t)r * b.nplanes * nw + w0;
-            const Words8 sg = load_words8(rp, nvalid);
-            if (b.rtn) {
-                // codes n_{b_0} (if any), n_{b_{l-1}} (if sent) and n_{b_l} from their planes, sign-extended; the residual
-                // integer k = n_cur D' - n_prev D; value = fp32(n_0) c_0 + fp32(k) coefficient
-                const int bp = __builtin_amdgcn_readfirstlane((int)s_fl[r]);
-                const float c0 = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(s_c0[r])));
-                const int bprev = bp > 0 ? bp : F0;               // level 1: the previous code is the base code
-                const int D = (1 << wd) - 1, Dp = bprev > 0 ? (1 << bprev) - 1 : 1;
-                uint32_t u0[8], u1[8], u2[8];
+    for (int e = 0; e < 32; ++e) acc[e] = 0.0f;
+    constexpr int AHEAD = PK == 2 ? 16 : PK == 1 ? 10 : 9;
+    uint32_t ahead[AHEAD];
+    auto look_ahead = [&](int r) {   // no branch between the loads: past the message's end its last plane is read again
+        const GlobalBytes row = base + (size_t)r * b.nplanes * step;
+        const int np = uni(s_row[r].np);
+        if (PK == 2) {
+            const int at = np - uni(s_row[r].w), pw = uni(s_row[r].fl);
 #pragma unroll
-                for (int k = 0; k < 8; ++k) { u0[k] = 0; u1[k] = 0; u2[k] = 0; }
-                for (int q = 0; q < F0; ++q) {
-                    const Words8 pw = q == 0 ? sg : load_words8(rp + (size_t)q * nw, nvalid);
-                    const uint32_t bit = 1u << q;
+            for (int p = 0; p < 8; ++p) ahead[p] = plane(row, at + p < np ? at + p : np - 1);
+            if (pw > 0) {
 #pragma unroll
-                    for (int k = 0; k < 8; ++k) u0[k] |= __builtin_amdgcn_inverse_ballot_w64(pw.w[k]) ? bit : 0u;
-                }
-                for (int q = 0; q < bp; ++q) {
-                    const Words8 pw = load_words8(rp + (size_t)(F0 + q) * nw, nvalid);
-                    const uint32_t bit = 1u << q;
+                for (int p = 0; p < 8; ++p) ahead[8 + p] = plane(row, F0 + (p < pw ? p : pw - 1));
+            }
+        } else {
 #pragma unroll
-                    for (int k = 0; k < 8; ++k) u1[k] |= __builtin_amdgcn_inverse_ballot_w64(pw.w[k]) ? bit : 0u;
-                }
-                for (int q = 0; q < wd; ++q) {
-                    const Words8 pw = load_words8(rp + (size_t)(F0 + bp + q) * nw, nvalid);
-                    const uint32_t bit = 1u << q;
+            for (int p = 0; p < AHEAD; ++p) ahead[p] = plane(row, p < np ? p : np - 1);
+        }
+    };
 #pragma unroll
-                    for (int k = 0; k < 8; ++k) u2[k] |= __builtin_amdgcn_inverse_ballot_w64(pw.w[k]) ? bit : 0u;
-                }
+    for (int p = 0; p < AHEAD; ++p) ahead[p] = 0;
+    look_ahead(0);
+    for (int r = 0; r < b.M; ++r) {   // rows in worker order
+        const GlobalBytes row = base + (size_t)r * b.nplanes * step;
+        const int np = uni(s_row[r].np), w = uni(s_row[r].w), fl = uni(s_row[r].fl);
+        const float cl = funi(s_row[r].cl), c0 = BASE ? funi(s_row[r].c0) : 0.0f;
+        uint32_t cur[AHEAD];
 #pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    const int32_t n0 = F0 > 0 ? (int32_t)(u0[k] << (32 - F0)) >> (32 - F0) : 0;
-                    const int32_t np_ = bp > 0 ? (int32_t)(u1[k] << (32 - bp)) >> (32 - bp) : n0;
-                    const int32_t nc = (int32_t)(u2[k] << (32 - wd)) >> (32 - wd);
-                    float v = __fmul_rn((float)(nc * Dp - np_ * D), cl);
-                    if (F0 > 0) v = __fadd_rn(__fmul_rn((float)n0, c0), v);
-                    acc[k] = __fadd_rn(acc[k], v);
-                }
-            } else if (b.flt) {
-                // App. B: sign, exponent field and base digits give C^{F_0}; the level digits, placed under the same
-                // sign and exponent, minus the bare power of two give the residual (exact); weight, then one add
-                const int Fl = __builtin_amdgcn_readfirstlane((int)s_fl[r]);
-                uint32_t ev[8], f[8], f0[8];
+        for (int p = 0; p < AHEAD; ++p) cur[p] = ahead[p];
+        if (r + 1 < b.M) look_ahead(r + 1);
+        // planes p0 .. p0 + n - 1 (at most eight of them) of the row into r8, the rest of it zero, transposed
+        auto group = [&](int p0, int n, uint32_t (&r8)[8]) {
 #pragma unroll
-                for (int k = 0; k < 8; ++k) { ev[k] = 0; f[k] = 0; f0[k] = 0; }
-                for (int q = 0; q < 8; ++q) {
-                    const Words8 pw = load_words8(rp + (size_t)(1 + q) * nw, nvalid);
-                    const uint32_t bit = 1u << (23 + q);
+            for (int q = 0; q < 8; ++q) r8[q] = 0;
 #pragma unroll
-                    for (int k = 0; k < 8; ++k) ev[k] |= __builtin_amdgcn_inverse_ballot_w64(pw.w[k]) ? bit : 0u;
-                }
-                for (int q = 0; q < F0; ++q) {
-                    const Words8 pw = load_words8(rp + (size_t)(9 + q) * nw, nvalid);
-                    const uint32_t bit = 1u << (23 - F0 + q);
+            for (int q = 0; q < 8; ++q) if (q < n) r8[q] = plane(row, p0 + q);   // uniform
+            transpose8(r8);
+        };
+        if (PK == 0) {
+            const uint32_t sg = cur[0];
+            auto add = [&](int e, float v) {   // v >= 0, its sign from the sign plane
+                v = __uint_as_float(((sg << (31 - e)) & 0x80000000u) | __float_as_uint(v));
+                acc[e] = __fadd_rn(acc[e], v);
+            };
+            if (!BASE && w == 1) {
+                // f is 0 or 1: the entry is +-cl or absent (adding 0 of either sign leaves the sum as it is)
+                const uint32_t fw = cur[1];
 #pragma unroll
-                    for (int k = 0; k < 8; ++k) f0[k] |= __builtin_amdgcn_inverse_ballot_w64(pw.w[k]) ? bit : 0u;
-                }
-                for (int q = 0; q < wd; ++q) {
-                    const Words8 pw = load_words8(rp + (size_t)(9 + F0 + q) * nw, nvalid);
-                    const uint32_t bit = 1u << (23 - Fl + q);
-#pragma unroll
-                    for (int k = 0; k < 8; ++k) f[k] |= __builtin_amdgcn_inverse_ballot_w64(pw.w[k]) ? bit : 0u;
-                }
-#pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    const uint32_t se = ev[k] | (__builtin_amdgcn_inverse_ballot_w64(sg.w[k]) ? 0x80000000u : 0u);
-                    const float res = __fsub_rn(__uint_as_float(se | f[k]), __uint_as_float(se));
-                    const float v = __fadd_rn(__uint_as_float(se | f0[k]), __fmul_rn(res, cl));
-                    acc[k] = __fadd_rn(acc[k], v);
-                }
-            } else if (F0 == 0 && wd == 1) {
-                // f is 0 or 1: the entry is +-cl or absent (adding +0 leaves the sum as it is)
-                const Words8 fw = load_words8(rp + nw, nvalid);
-#pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    float v = __builtin_amdgcn_inverse_ballot_w64(fw.w[k] & ~sg.w[k]) ? cl : 0.0f;
-                    v = __builtin_amdgcn_inverse_ballot_w64(fw.w[k] & sg.w[k]) ? -cl : v;
-                    acc[k] = __fadd_rn(acc[k], v);
-                }
+                for (int e = 0; e < 32; ++e)
+                    acc[e] = __fadd_rn(acc[e], __uint_as_float((((sg << (31 - e)) & 0x80000000u) | __float_as_uint(cl)) & (uint32_t)__builtin_amdgcn_sbfe((int)fw, e, 1)));
             } else {
-                const float c0 = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(s_c0[r])));
-                uint32_t f[8], f0[8];
+                uint32_t r8[3][8];
 #pragma unroll
-                for (int k = 0; k < 8; ++k) { f[k] = 0; f0[k] = 0; }
-                for (int q = 0; q < F0; ++q) {
-                    const Words8 pw = load_words8(rp + (size_t)(1 + q) * nw, nvalid);
-                    const uint32_t bit = 1u << q;
+                for (int q = 0; q < 8; ++q) r8[0][q] = 1 + q < np ? cur[1 + q] : 0u;
+                transpose8(r8[0]);
+                auto all = [&](auto groups) {
+                    constexpr int G = decltype(groups)::value;
 #pragma unroll
-                    for (int k = 0; k < 8; ++k) f0[k] |= __builtin_amdgcn_inverse_ballot_w64(pw.w[k]) ? bit : 0u;
-                }
-                for (int q = 0; q < wd; ++q) {
-                    const Words8 pw = load_words8(rp + (size_t)(1 + F0 + q) * nw, nvalid);
-                    const uint32_t bit = 1u << q;
+                    for (int k = 0; k < 4; ++k)
 #pragma unroll
-                    for (int k = 0; k < 8; ++k) f[k] |= __builtin_amdgcn_inverse_ballot_w64(pw.w[k]) ? bit : 0u;
-                }
-#pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    float v = __fmul_rn((float)f[k], cl);
-                    if (F0 > 0) v = __fadd_rn(__fmul_rn((float)f0[k], c0), v);
-                    acc[k] = __fadd_rn(acc[k], __builtin_amdgcn_inverse_ballot_w64(sg.w[k]) ? -v : v);
+                        for (int i = 0; i < 8; ++i) {
+                            const uint32_t u = assemble<G>(r8, i, k);
+                            float v;
+                            if (!BASE) v = __fmul_rn((float)u, cl);
+                            else v = __fadd_rn(__fmul_rn((float)(u & ((1u << F0) - 1u)), c0), __fmul_rn((float)(u >> F0), cl));
+                            add(8 * k + i, v);
+                        }
+                };
+                if (np <= 9) {
+                    all(std::integral_constant<int, 1>{});
+                } else {
+                    group(9, np - 9, r8[1]);
+                    if (np <= 17) {
+                        all(std::integral_constant<int, 2>{});
+                    } else {
+                        group(17, np - 17, r8[2]);
+                        all(std::integral_constant<int, 3>{});
+                    }
                 }
             }
+        } else if (PK == 1) {
+            // App. B: sign, exponent field and base digits give C^{F_0}; the level digits, placed under the same sign and
+            // exponent, minus the bare power of two give the residual (exact); weight, then one add
+            uint32_t t[8];   // bits 24 .. 31 of the lane's fp32 words: the exponent's upper seven and the sign
+#pragma unroll
+            for (int q = 0; q < 7; ++q) t[q] = cur[2 + q];
+            t[7] = cur[0];
+            transpose8(t);
+            const uint32_t e0 = cur[1];   // the exponent's lowest bit
+            auto head = [&](int i, int k) -> uint32_t {   // sign and exponent of element 8 k + i
+                const uint32_t hi = __builtin_amdgcn_perm(t[i], 0u, 0x040C0C0Cu + 0x01000000u * (uint32_t)k);
+                return hi | (((e0 >> (8 * k + i)) & 1u) << 23);
+            };
+            auto finish = [&](int i, int k, uint32_t base_digits, uint32_t level_digits) {
+                const uint32_t se = head(i, k);
+                const float res = __fsub_rn(__uint_as_float(se | level_digits), __uint_as_float(se));
+                const float v = __fadd_rn(__uint_as_float(se | base_digits), __fmul_rn(res, cl));
+                acc[8 * k + i] = __fadd_rn(acc[8 * k + i], v);
+            };
+            const int pos = 23 - fl;
+            if (!BASE && w == 1) {
+                const uint32_t fw = cur[9];
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) finish(i, k, 0u, ((fw >> (8 * k + i)) & 1u) << pos);
+            } else {
+                uint32_t f8[3][8], b8[3][8];
+                const int p0 = 9 + F0;
+                group(p0, w, f8[0]);
+                group(p0 + 8, w - 8, f8[1]);
+                group(p0 + 16, w - 16, f8[2]);
+                if (BASE) {
+                    group(9, F0, b8[0]);
+                    group(17, F0 - 8, b8[1]);
+                    group(25, F0 - 16, b8[2]);
+                }
+                const int bpos = 23 - F0;
+                // (a group past the field's end is zero; a base field of more than 8 or 16 digits ends inside its groups)
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        const uint32_t fd = assemble<3>(f8, i, k) << pos;
+                        uint32_t bd = 0;
+                        if (BASE) bd = (assemble<3>(b8, i, k) & ((1u << F0) - 1u)) << bpos;
+                        finish(i, k, bd, fd);
+                    }
+            }
+        } else {
+            // codes n_{b_0} (if any), n_{b_{l-1}} (if sent) and n_{b_l}, sign-extended; the residual integer k = n_cur D' - n_prev D;
+            // value = fp32(n_0) c_0 + fp32(k) coefficient
+            const int bp = fl;
+            const int bprev = bp > 0 ? bp : F0;               // level 1: the previous code is the base code
+            const int D = (1 << w) - 1, Dp = bprev > 0 ? (1 << bprev) - 1 : 1;
+            uint32_t n8[3][8], p8[3][8], z8[3][8];
+            if (BASE) {
+                group(0, F0, z8[0]);
+                if (F0 > 8) group(8, F0 - 8, z8[1]);
+            }
+            auto low = [&](int at, int width, uint32_t (&r8)[8]) {   // the low eight planes of a code, from `cur`
+#pragma unroll
+                for (int q = 0; q < 8; ++q) r8[q] = q < width ? cur[at + q] : 0u;
+                transpose8(r8);
+            };
+            if (w > 8) group(F0 + bp + 8, w - 8, n8[1]);
+            if (bp > 8) group(F0 + 8, bp - 8, p8[1]);
+            low(0, w, n8[0]);
+            if (bp > 0) low(8, bp, p8[0]);
+            auto all = [&](auto cg, auto pg) {
+                constexpr int PG = decltype(pg)::value;   // bytes of the previous code (0: none sent)
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        auto value = [&](auto bytes, const uint32_t (&v)[3][8], int width) -> int {
+                            constexpr int G = decltype(bytes)::value;
+                            if (G == 1) return __builtin_amdgcn_sbfe((int)v[0][i], 8 * k, width);
+                            return __builtin_amdgcn_sbfe((int)assemble<2>(v, i, k), 0, width);
+                        };
+                        const int nc = value(cg, n8, w);
+                        int n0 = 0;
+                        if (BASE) n0 = F0 > 8 ? value(std::integral_constant<int, 2>{}, z8, F0) : value(std::integral_constant<int, 1>{}, z8, F0);
+                        const int prev = PG > 0 ? value(std::integral_constant<int, PG == 0 ? 1 : PG>{}, p8, bp) : n0;
+                        float v = __fmul_rn((float)(__mul24(nc, Dp) + (PG > 0 || BASE ? __mul24(prev, -D) : 0)), cl);
+                        if (BASE) v = __fadd_rn(__fmul_rn((float)n0, c0), v);
+                        acc[8 * k + i] = __fadd_rn(acc[8 * k + i], v);
+                    }
+            };
+            using I0 = std::integral_constant<int, 0>;
+            using I1 = std::integral_constant<int, 1>;
+            using I2 = std::integral_constant<int, 2>;
+            if (w <= 8) {
+                if (bp == 0) all(I1{}, I0{});
+                else all(I1{}, I1{});
+            } else {
+                if (bp == 0) all(I2{}, I0{});
+                else if (bp <= 8) all(I2{}, I1{});
+                else all(I2{}, I2{});
+            }
         }
+    }
+    // the lane's 32 sums into the wave's buffer, out of it 16 bytes at a time: chunk c of lane l in slot c ^ (l & 7)
+    float* buf = (float*)(s_dyn_planes + wave * (EX_ELEMS * 4));
+#pragma unroll
+    for (int c = 0; c < 8; ++c)
+        *(float4*)(buf + (lane * 8u + ((uint32_t)c ^ (lane & 7u))) * 4u) = make_float4(acc[4 * c], acc[4 * c + 1], acc[4 * c + 2], acc[4 * c + 3]);
+    wave_lds_sync();
+    const int64_t j0 = blk * EX_ELEMS;
+    const uint32_t goff = (lane & ~7u) * 4u + ((lane & 7u) ^ ((lane >> 3) & 7u)) * 4u;   // element of this lane's first chunk
+    typedef float f32x4_el __attribute__((ext_vector_type(4), aligned(4)));
+    if (j0 + EX_ELEMS <= b.d) {   // uniform
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
-            const int64_t j = (w0 + k) * 64 + lane;
-            if (j < b.d) finish_entry(a.alpha, acc[k], out, a.eta, x, j);
+            const float4 s4 = *(const float4*)(buf + (64 * k + lane) * 4u);
+            const int64_t j = j0 + k * 256 + goff;
+            f32x4_el gt;
+            gt.x = __fmul_rn(a.alpha, s4.x);
+            gt.y = __fmul_rn(a.alpha, s4.y);
+            gt.z = __fmul_rn(a.alpha, s4.z);
+            gt.w = __fmul_rn(a.alpha, s4.w);
+            if (out) __builtin_nontemporal_store(gt, (f32x4_el*)(out + j));   // written once, read by the caller later
+            if (x) {
+                f32x4_el xv = *(const f32x4_el*)(x + j);
+                xv.x = __fsub_rn(xv.x, __fmul_rn(a.eta, gt.x));
+                xv.y = __fsub_rn(xv.y, __fmul_rn(a.eta, gt.y));
+                xv.z = __fsub_rn(xv.z, __fmul_rn(a.eta, gt.z));
+                xv.w = __fsub_rn(xv.w, __fmul_rn(a.eta, gt.w));
+                *(f32x4_el*)(x + j) = xv;
+            }
+        }
+    } else {
+#pragma unroll 1
+        for (uint32_t e = lane; e < EX_ELEMS && j0 + e < b.d; e += 64) {
+            const uint32_t owner = e >> 5, c = (e & 31u) >> 2;
+            finish_entry(a.alpha, buf[(owner * 8u + (c ^ (owner & 7u))) * 4u + (e & 3u)], out, a.eta, x, j0 + e);
         }
     }
 }
@@ -450,11 +569,18 @@ mlmc_status agg_bits(const mlmc_plan_t* pl, const BitsArgs& b, const int32_t* le
     a.scale_exp = scale_exp;
     a.alpha = alpha;
     a.eta = eta;
-    int64_t waves = (b.nwords + 7) / 8;   // a wave takes eight words at a time
-    int blocks = (int)((waves + 3) / 4);
-    if (blocks > 8192) blocks = 8192;
-    if (blocks < 1) blocks = 1;
-    MLMC_LAUNCH(K_AGG_BITS, st, k_agg_bits<<<blocks, 256, 0, st>>>(a, planes, out, x));
+    const int64_t nblk = (b.d + EX_ELEMS - 1) / EX_ELEMS;
+    const unsigned grid = (unsigned)((nblk + EX_THREADS / 64 - 1) / (EX_THREADS / 64));
+    const size_t lds = (size_t)(EX_THREADS / 64) * EX_ELEMS * 4 + sizeof(AggRow) * (size_t)b.M;
+#define MLMC_AGG(PK)                                                                                                     \
+    do {                                                                                                                \
+        if (b.F[0] == 0) MLMC_LAUNCH(K_AGG_BITS, st, k_agg_planes<PK, false><<<grid, EX_THREADS, lds, st>>>(a, planes, out, x)); \
+        else MLMC_LAUNCH(K_AGG_BITS, st, k_agg_planes<PK, true><<<grid, EX_THREADS, lds, st>>>(a, planes, out, x));       \
+    } while (0)
+    if (b.rtn) MLMC_AGG(2);
+    else if (b.flt) MLMC_AGG(1);
+    else MLMC_AGG(0);
+#undef MLMC_AGG
     return MLMC_OK;
 }
 
