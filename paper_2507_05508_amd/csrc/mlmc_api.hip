@@ -52,7 +52,8 @@ bool g_prof_on = false;
 static const char* const k_names[K_NUM] = {
     "k_zero", "k_hist", "k_scan", "k_main", "k_fhist", "k_finish", "k_finish_rank", "redo_pass", "k_norms", "k_bits_prep", "k_msgplan", "k_filter", "k_write",
     "k_bits_smax", "k_bits_extract", "k_bits_redo", "k_agg_bits", "k_tileoff", "k_agg_sparse", "k_message_bits", "k_rtn_norms", "k_rtn_draw",
-    "k_rs_hist", "k_rs_scan", "k_rs_scatter", "k_sb_norms", "k_sb_draw", "k_sb_mark", "k_sb_offsets", "k_sb_write"};
+    "k_rs_hist", "k_rs_scan", "k_rs_scatter", "k_sb_norms", "k_sb_draw", "k_sb_mark", "k_sb_offsets", "k_sb_write", "k_se_count", "k_se_scan",
+    "k_se_split", "k_se_zone"};
 struct ProfPair { int id; hipEvent_t e0, e1; };
 static std::vector<ProfPair> g_pending;
 static std::vector<ProfPair> g_free;
@@ -244,6 +245,43 @@ static mlmc_status plan_stopk(mlmc_plan_t** plan, int M, int64_t d, int in_dtype
     pl->nblk = (int)((d + 4096 - 1) / 4096);   // sort blocks: RS_TILE elements
     pl->bm_words = ((d + 31) / 32 + 3) / 4 * 4;   // whole 16-byte groups per row
     size_t off = 0;
+    auto take = [&](size_t bytes) { const size_t at = off; off = align_up(off + bytes, 256); return at; };
+    const bool bins = L <= SE_LMAX;   // more levels: a boundary in every few bins, most entries would be zone entries
+    if (bins) {
+        pl->se_rep = L <= 1024 ? 2 : (L <= 2304 ? 1 : 0);   // (L + 256) << se_rep sums fill 40 KB of LDS
+        while (pl->se_shift < 4 && (d >> (pl->se_shift + 1)) >= (1 << 20)) ++pl->se_shift;
+        // One workgroup per CU in one round.  A group's 64-bit sum has room for 2^16 squares: a band has at most s entries, a
+        // copy gets its even share of the slice, so one of the two has to be that small.
+        int64_t wgs = 256 / M > 0 ? 256 / M : 1;
+        if (wgs > (d + 8191) / 8192) wgs = (d + 8191) / 8192;
+        if (s > 65536) {
+            const int64_t least = (d + (65536ll << pl->se_rep) - 1) / (65536ll << pl->se_rep);
+            if (wgs < least) {
+                const int64_t rounds = (least * M + 255) / 256;
+                wgs = rounds * 256 / M > least ? rounds * 256 / M : least;
+            }
+        }
+        pl->se_slice = ((d + wgs - 1) / wgs + 1023) / 1024 * 1024;
+        if (s > 65536 && pl->se_slice > (65536ll << pl->se_rep)) pl->se_slice = 65536ll << pl->se_rep;
+        pl->se_wgs = (int)((d + pl->se_slice - 1) / pl->se_slice);
+        pl->off_se_coarse = take(sizeof(uint32_t) * 8192 * (size_t)M);
+        pl->off_se_big = take(sizeof(uint64_t) * SE_WORDS * (size_t)L * M);
+        pl->off_se_nz = take(sizeof(uint32_t) * 2 * (size_t)M);
+        pl->off_se_end = off;
+        pl->off_se_bsum = take(sizeof(uint32_t) * ((SE_BINS + 255) / 256) * (size_t)M);
+        pl->off_se_map = take(sizeof(uint32_t) * 8192 * (size_t)M);
+        pl->off_se_info = take(sizeof(uint2) * SE_BINS * (size_t)M);
+        pl->off_se_nbins = take(sizeof(uint32_t) * (size_t)M);
+        pl->off_se_part = take(sizeof(uint32_t) * SE_BINS * (size_t)pl->se_wgs * M);
+        pl->off_se_total = take(sizeof(uint32_t) * SE_BINS * (size_t)M);
+        pl->off_se_class = take(sizeof(uint16_t) * SE_BINS * (size_t)M);
+        pl->off_se_gtab = take(sizeof(uint32_t) * (SE_LMAX + 256) * (size_t)M);
+        pl->off_se_thr = take(sizeof(uint2) * (size_t)(L + 1) * M);
+        pl->off_se_zone = take(sizeof(SZone) * SE_LMAX * (size_t)M);
+        pl->off_se_list = take(sizeof(uint32_t) * (size_t)d * M);
+        pl->off_se_list2 = take(sizeof(uint32_t) * (size_t)d * M);
+        pl->off_se_tie = take(sizeof(uint2) * (size_t)pl->ntiles * M);
+    }
     pl->off_bitmap = off;
     off = align_up(off + sizeof(uint32_t) * (size_t)pl->bm_words * M + 16, 256);
     pl->off_tilecnt = off;
@@ -251,18 +289,16 @@ static mlmc_status plan_stopk(mlmc_plan_t** plan, int M, int64_t d, int in_dtype
     pl->off_clear_end = off;
     pl->off_srow = off;
     off = align_up(off + sizeof(SRow) * (size_t)M, 256);
-    pl->off_counts = off;
-    off = align_up(off + sizeof(uint32_t) * 256 * (size_t)pl->nblk * M, 256);
-    pl->off_bintot = off;
-    off = align_up(off + sizeof(uint32_t) * 256 * (size_t)M, 256);
     pl->off_tileoff = off;
     off = align_up(off + sizeof(uint32_t) * (size_t)(pl->ntiles + 1) * M, 256);
     pl->off_norms = off;
     off = align_up(off + sizeof(double) * (size_t)L * M, 256);
-    pl->off_pa = off;
-    off = align_up(off + sizeof(uint2) * (size_t)d * M, 256);
-    pl->off_pb = off;
-    off = align_up(off + sizeof(uint2) * (size_t)d * M, 256);
+    if (!bins) {
+        pl->off_counts = take(sizeof(uint32_t) * 256 * (size_t)pl->nblk * M);
+        pl->off_bintot = take(sizeof(uint32_t) * 256 * (size_t)M);
+        pl->off_pa = take(sizeof(uint2) * (size_t)d * M);
+        pl->off_pb = take(sizeof(uint2) * (size_t)d * M);
+    }
     pl->ws_bytes = off;
     if (workspace_bytes) *workspace_bytes = off;
     if (sparse_capacity_worst) *sparse_capacity_worst = (int64_t)M * (s < d ? s : d);
@@ -289,6 +325,30 @@ static void fill_stopk_args(const mlmc_plan_t* pl, StopkArgs& a, const void* g, 
     a.bitmap = (uint32_t*)(w + pl->off_bitmap);
     a.tile_cnt = (uint32_t*)(w + pl->off_tilecnt);
     a.clear_bytes = pl->off_clear_end - pl->off_bitmap;
+    if (pl->off_se_end) {
+        a.clear_bytes = pl->off_se_end - pl->off_se_coarse;
+        a.bf16 = pl->dtype == MLMC_BF16 ? 1 : 0;
+        a.se_shift = pl->se_shift;
+        a.se_wgs = pl->se_wgs;
+        a.se_rep = pl->se_rep;
+        a.se_slice = pl->se_slice;
+        a.se_coarse = (uint32_t*)(w + pl->off_se_coarse);
+        a.se_big = (unsigned long long*)(w + pl->off_se_big);
+        a.se_map = (uint32_t*)(w + pl->off_se_map);
+        a.se_info = (uint2*)(w + pl->off_se_info);
+        a.se_nbins = (uint32_t*)(w + pl->off_se_nbins);
+        a.se_part = (uint32_t*)(w + pl->off_se_part);
+        a.se_total = (uint32_t*)(w + pl->off_se_total);
+        a.se_class = (uint16_t*)(w + pl->off_se_class);
+        a.se_gtab = (uint32_t*)(w + pl->off_se_gtab);
+        a.se_thr = (uint2*)(w + pl->off_se_thr);
+        a.se_zone = (SZone*)(w + pl->off_se_zone);
+        a.se_bsum = (uint32_t*)(w + pl->off_se_bsum);
+        a.se_nz = (uint32_t*)(w + pl->off_se_nz);
+        a.se_list = (uint32_t*)(w + pl->off_se_list);
+        a.se_list2 = (uint32_t*)(w + pl->off_se_list2);
+        a.se_tie = (uint2*)(w + pl->off_se_tie);
+    }
     a.tile_off = (uint32_t*)(w + pl->off_tileoff);
     a.norms = (double*)(w + pl->off_norms);
     a.srow = (SRow*)(w + pl->off_srow);

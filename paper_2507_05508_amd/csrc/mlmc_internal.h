@@ -190,6 +190,17 @@ struct SRow {           // per row: the drawn segment
     float weight;
     int64_t lo, count;  // its positions in the sorted row: [lo, lo + count)
 };
+// The way without a sort (ladders of up to SE_LMAX levels)
+constexpr int SE_LMAX = 4096;
+constexpr int SE_BINS = 32000;          // bins of a row's exact histogram: with the coarse map they fill a CU's LDS
+constexpr int SE_WORDS = 20;            // 32-bit words of a band's sum of squares (2^-298 units), each in a 64-bit counter
+constexpr uint32_t SE_ALL = 0xFFFFFFFFu;  // threshold {key, SE_ALL}: every entry equal to the key is inside
+struct SZone {          // a bin that holds band boundaries
+    uint32_t cum, n;        // entries of the row above it, entries in it
+    uint32_t lo, shift;     // its keys: lo .. lo + 2^shift - 1
+    uint32_t t0, nb;        // boundaries t0 .. t0 + nb - 1 lie strictly inside
+    uint32_t off, bin;      // its list of keys, its bin
+};
 struct StopkArgs {
     const void* g;
     int64_t ld, d;
@@ -215,13 +226,34 @@ struct StopkArgs {
     int64_t capacity;
     int32_t* dev_status;
     uint64_t seed, step;
+    // the way without a sort
+    int32_t bf16;
+    int32_t se_shift;        // one block of 1024 entries out of 2^se_shift is sampled for the map
+    int32_t se_wgs, se_rep;  // workgroups per row of the two reads that fill LDS; log2 of the copies of a group's sum
+    int64_t se_slice;        // entries of such a workgroup
+    uint32_t* se_coarse;     // [M][8192] sampled histogram (cleared per call)
+    unsigned long long* se_big;  // [M][L][SE_WORDS] sums of squares of the bands (cleared per call)
+    uint32_t* se_map;        // [M][8192] coarse bucket -> first bin | shift << 16
+    uint2* se_info;          // [M][SE_BINS] {lowest key, shift} of a bin
+    uint32_t* se_nbins;      // [M]
+    uint32_t* se_part;       // [M][se_wgs][SE_BINS] counts of a workgroup, then those of the workgroups before it
+    uint32_t* se_total;      // [M][SE_BINS]
+    uint16_t* se_class;      // [M][SE_BINS]
+    uint32_t* se_gtab;       // [M][SE_LMAX + 256] exponent << 16 | band of a sum group
+    uint2* se_thr;           // [M][L + 1] thresholds of the boundaries: {key, how many of its equals are inside}
+    SZone* se_zone;          // [M][SE_LMAX]
+    uint32_t* se_nz;         // [M][2] zones, their entries (cleared per call)
+    uint32_t* se_bsum;       // [M][SE_BINS / 256] totals of 256 bins each
+    uint32_t* se_list;       // [M][d] keys of the zones
+    uint32_t* se_list2;      // [M][d]
+    uint2* se_tie;           // [M][ntiles] entries equal to the two thresholds of the drawn segment, where they are split
 };
 
 // ---- optional per-kernel timing with HIP events (host side, see mlmc_profile_* in mlmc.h) ----------
 enum KernelId {
     K_ZERO = 0, K_HIST, K_SCAN, K_MAIN, K_FHIST, K_FINISH, K_FINISH1, K_REDO, K_NORMS, K_DRAW, K_MSGPLAN, K_FILTER, K_WRITE,
     K_BITS_MAX, K_BITS_EXTRACT, K_BITS_REDO, K_AGG_BITS, K_TILEOFF, K_AGG_SPARSE, K_MSGBITS, K_RTN_NORMS, K_RTN_DRAW,
-    K_RS_HIST, K_RS_SCAN, K_RS_SCATTER, K_SB_NORMS, K_SB_DRAW, K_SB_MARK, K_SB_OFFSETS, K_SB_WRITE, K_NUM
+    K_RS_HIST, K_RS_SCAN, K_RS_SCATTER, K_SB_NORMS, K_SB_DRAW, K_SB_MARK, K_SB_OFFSETS, K_SB_WRITE, K_SE_COUNT, K_SE_SCAN, K_SE_SPLIT, K_SE_ZONE, K_NUM
 };
 extern bool g_prof_on;
 void prof_begin(int id, hipStream_t st);
@@ -260,6 +292,10 @@ struct mlmc_plan_s {
     int nblk;
     int64_t bm_words;
     size_t off_pa, off_pb, off_counts, off_bitmap, off_tilecnt, off_clear_end, off_srow, off_bintot;
+    size_t off_se_coarse, off_se_big, off_se_end, off_se_map, off_se_info, off_se_nbins, off_se_part, off_se_total, off_se_class, off_se_gtab, off_se_thr,
+        off_se_zone, off_se_nz, off_se_list, off_se_list2, off_se_tie, off_se_bsum;   // off_se_end: end of what is cleared per call (0: the plan sorts)
+    int se_shift, se_wgs, se_rep;
+    int64_t se_slice;
     size_t off_rtn_sums;   // Round-to-Nearest plans
     // Side stream of the message step (MLMC_TOPK): the second read of the rows whose band was not staged runs beside the
     // assembly of the other rows' messages from the staged lists.  Created at the first call that uses it, on the device

@@ -1,6 +1,7 @@
 // s-segmented Top-k MLMC on gfx950 (Sec. 2.2 "s-Top-k", Sec. 3.2, Lemma 3.4, App. D): the ladder k_l = min(s l, d),
 // l = 0..L = ceil(d / s), g^0 = 0, adaptive level probabilities over all L bands.  The residual of level l is the
-// l-th segment of the row sorted by magnitude, so the whole row is sorted once:
+// l-th segment of the row sorted by magnitude.  Ladders of up to SE_LMAX levels are handled without a sort (second half of this
+// file); longer ones, whose segments are a few entries, sort the whole row once:
 //
 //   k_rs_hist / k_rs_scan / k_rs_scatter   stable least-significant-digit radix sort of {inverted |g| key, index} pairs,
 //                 8 bits per pass (4 passes for fp32, 2 for bf16 inputs whose keys have 16 significant bits); the
@@ -245,7 +246,17 @@ __global__ __launch_bounds__(1024) void k_sb_draw(StopkArgs a) {
         __syncthreads();
         for (int i = tid; i < n; i += 1024) s_n[i] = nr[c0 + i];
         __syncthreads();
-        if (tid == 0) for (int i = 0; i < n; ++i) tot = __dadd_rn(tot, s_n[i]);
+        if (tid == 0) {
+            int i = 0;
+            for (; i + 16 <= n; i += 16) {   // the reads of sixteen together: a read per addition would cost its latency each time
+                double v[16];
+#pragma unroll
+                for (int u = 0; u < 16; ++u) v[u] = s_n[i + u];
+#pragma unroll
+                for (int u = 0; u < 16; ++u) tot = __dadd_rn(tot, v[u]);
+            }
+            for (; i < n; ++i) tot = __dadd_rn(tot, s_n[i]);
+        }
     }
     if (tid == 0) { s_tot = tot; s_found = 0x7FFFFFFF; }
     __syncthreads();
@@ -260,7 +271,17 @@ __global__ __launch_bounds__(1024) void k_sb_draw(StopkArgs a) {
         for (int i = tid; i < n; i += 1024) s_n[i] = tot == 0.0 ? uni : __ddiv_rn(nr[c0 + i], tot);
         __syncthreads();
         if (tid == 0) {
-            for (int i = 0; i < n; ++i) {
+            int i = 0;
+            for (; i + 16 <= n; i += 16) {
+                double v[16];
+#pragma unroll
+                for (int u = 0; u < 16; ++u) v[u] = s_n[i + u];
+#pragma unroll
+                for (int u = 0; u < 16; ++u) { c = __dadd_rn(c, v[u]); v[u] = c; }
+#pragma unroll
+                for (int u = 0; u < 16; ++u) s_cdf[i + u] = v[u];
+            }
+            for (; i < n; ++i) {
                 c = __dadd_rn(c, s_n[i]);
                 s_cdf[i] = c;
             }
@@ -426,7 +447,832 @@ static mlmc_status launch_stopk(const mlmc_plan_t* pl, const StopkArgs& a, bool 
     return MLMC_OK;
 }
 
+// ---------------------------------------------------------------------------------------------------
+// The way without a sort, for ladders of up to SE_LMAX levels.  What the norms need is, per band, the exact sum of its
+// squares, and what the message needs is two thresholds; neither needs an order among the entries of a band.  So:
+//   k_se_coarse / k_se_map   a histogram of sampled blocks (13 bits of the key) gives a monotone map key -> one of at most
+//                 SE_BINS bins of about equal occupancy, every bin inside one exponent, zero in a bin of its own
+//   k_se_count / k_se_reduce exact counts of the bins (first read of the rows), per workgroup, then summed over the workgroups
+//   k_se_scan     ranks of the bins: a bin whose ranks lie inside one band is a REGION of that band, one that holds band
+//                 boundaries a ZONE (for L = 1000 and the occupancies met here about 5 % of the entries), unless all its
+//                 entries have one key, in which case the boundaries' parts follow from the counts
+//   k_se_split    second read: squares of region entries are added per (band, exponent) in LDS, keys of zone entries go to
+//                 their zones' lists, whose places are exact (the counts are)
+//   k_se_zone     per zone: keys in order, thresholds of its boundaries (key, how many of the equal keys are inside), sums of
+//                 its parts
+//   k_se_norms / k_sb_draw   Delta_l, level
+//   k_se_mark / k_se_offsets / k_se_write   third read: bitmap of the drawn segment and its message; entries equal to a
+//                 threshold whose equal keys are split are told apart by their rank in index order
+// Three reads of the rows and about 10 bytes per entry of other traffic against 4 x 24 bytes and more for the sort of pairs:
+// 8 rows of 1.17e7 fp32 entries at 1000 levels, compress + aggregate: 2788 -> 583 us.  The line at SE_LMAX levels is where the
+// class of a bin and the list cursors of a zone per boundary still fit LDS beside the map and the sums.
+constexpr int SE_CB = 8192;             // coarse buckets: key >> SE_CSHIFT
+constexpr int SE_CSHIFT = 18;
+constexpr int SE_THREADS = 1024;
+constexpr int SE_WAVES = SE_THREADS / 64;
+constexpr uint32_t SE_ZONE = 0x8000u;   // class of a bin: sum group, or SE_ZONE | zone
+constexpr int SE_ZCAP = 2048;           // keys that a zone's workgroup puts in order in LDS
+static_assert(SE_LMAX <= 0x8000 && SE_LMAX + 256 < 0x8000, "class field");
+
+__device__ __forceinline__ uint32_t se_bin(uint32_t entry, uint32_t key) {   // entry: of the key's coarse bucket, base | shift << 16
+    return (entry & 0xFFFFu) + ((key & ((1u << SE_CSHIFT) - 1u)) >> (entry >> 16)) + (key ? 1u : 0u);
+}
+
+// [i0, i1) of a row by the waves of a workgroup, 1024 elements at a time with the next 1024 in flight; i0 is a multiple of
+// 1024.  f(keys of four times four consecutive elements of every lane, how many of each four are there).  f gets all sixteen
+// at once so that it waits for its loads before it stores anything: the waits count loads and stores alike but can only
+// rely on the loads, so a store between them would cut the loads in flight short.
+template <int DT, class F>
+__device__ __forceinline__ void se_stream(const RowLoader<DT, true>& ld, int64_t i0, int64_t i1, uint32_t wave, uint32_t lane, F f) {
+    const int n = (int)((i1 - i0) >> 10);
+    uint32_t b0[4][4], b1[4][4];
+    auto fetch = [&](int p, uint32_t (&b)[4][4]) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) ld.load4_full(i0 + (int64_t)p * 1024 + q * 256 + lane * 4, b[q]);
+    };
+    auto use = [&](uint32_t (&b)[4][4]) {
+        const int nv[4] = {4, 4, 4, 4};
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) b[q][c] = key_of_bits(b[q][c]);
+        f(b, nv);
+    };
+    int p = (int)wave;
+    if (p < n) {
+        fetch(p, b0);
+        while (true) {   // uniform
+            const bool more1 = p + SE_WAVES < n;
+            if (more1) fetch(p + SE_WAVES, b1);
+            use(b0);
+            if (!more1) break;
+            p += SE_WAVES;
+            const bool more0 = p + SE_WAVES < n;
+            if (more0) fetch(p + SE_WAVES, b0);
+            use(b1);
+            if (!more0) break;
+            p += SE_WAVES;
+        }
+    }
+    if ((int)wave == n % SE_WAVES && i0 + (int64_t)n * 1024 < i1) {   // the ragged rest
+        int nv[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int64_t j = i0 + (int64_t)n * 1024 + q * 256 + lane * 4;
+            nv[q] = j < i1 ? ld.load4(j, b0[q]) : 0;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) b0[q][c] = c < nv[q] ? key_of_bits(b0[q][c]) : 0u;
+        }
+        f(b0, nv);
+    }
+}
+
+// Coarse histogram of the sampled blocks of 1024 entries (block b is sampled when b % 2^shift == 2^shift / 2).
+template <int DT>
+__global__ __launch_bounds__(512) void k_se_coarse(StopkArgs a) {
+    __shared__ uint32_t s_h[SE_CB];
+    const int row = blockIdx.y, tid = threadIdx.x;
+    const int64_t nblk = (a.d + 1023) >> 10, first = ((int64_t)1 << a.se_shift) >> 1;
+    for (int i = tid; i < SE_CB; i += 512) s_h[i] = 0;
+    __syncthreads();
+    RowLoader<DT, true> ld(a.g, a.ld, a.d, row);
+    const uint32_t lane = lane_id(), wave = (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6);
+    for (int64_t i = (int64_t)blockIdx.x * 8 + wave; (i << a.se_shift) + first < nblk; i += (int64_t)gridDim.x * 8) {
+        const int64_t base = ((i << a.se_shift) + first) * 1024;
+        uint32_t b[4][4];
+        int nv[4] = {4, 4, 4, 4};
+        if (base + 1024 <= a.d) {   // uniform
+#pragma unroll
+            for (int q = 0; q < 4; ++q) ld.load4_full(base + q * 256 + lane * 4, b[q]);
+        } else {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) nv[q] = ld.load4(base + q * 256 + lane * 4, b[q]);
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if (c < nv[q]) atomicAdd(&s_h[key_of_bits(b[q][c]) >> SE_CSHIFT], 1u);
+    }
+    __syncthreads();
+    uint32_t* h = a.se_coarse + (size_t)row * SE_CB;
+    for (int i = tid; i < SE_CB; i += 512)
+        if (s_h[i]) atomicAdd(&h[i], s_h[i]);
+}
+
+// Per row: the map.  A sampled bucket gets a power of two of bins in proportion to its count, any other one; the share is
+// the largest of five that fit.  16-bit inputs: a bucket has four keys, it gets a bin for each.
+template <int DT>
+__global__ __launch_bounds__(1024) void k_se_map(StopkArgs a) {
+    __shared__ uint32_t s_map[SE_CB];
+    __shared__ uint32_t s_scan[1024 / 64 + 1];
+    constexpr int PER = SE_CB / 1024;
+    constexpr uint32_t ROOM = SE_BINS - 1;          // zero has a bin of its own
+    constexpr uint32_t SHARE = ROOM - SE_CB;
+    const int row = blockIdx.x, tid = threadIdx.x;
+    uint32_t c[PER], sum = 0;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) { c[i] = a.se_coarse[(size_t)row * SE_CB + tid * PER + i]; sum += c[i]; }
+    uint32_t ns;
+    block_excl_scan<1024>(sum, s_scan, ns);
+    uint32_t kb[PER], before = 0, nbins = 0;
+    bool done = false;
+    for (uint32_t m = DT == MLMC_BF16 ? 9u : 8u; !done; --m) {   // uniform; m = 4 always fits
+        uint32_t need = 0;
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            kb[i] = 0;
+            if (c[i]) {
+                if (DT == MLMC_BF16) {
+                    kb[i] = m == 9u ? 2u : 0u;
+                } else {
+                    const unsigned long long v = (unsigned long long)c[i] * (SHARE * m / 4u) / ns;
+                    kb[i] = v ? 31u - (uint32_t)__clz((int)(uint32_t)v) : 0u;
+                    if (kb[i] > (uint32_t)SE_CSHIFT) kb[i] = SE_CSHIFT;
+                }
+            }
+            need += 1u << kb[i];
+        }
+        before = block_excl_scan<1024>(need, s_scan, nbins);
+        done = nbins <= ROOM || m <= 4u;
+    }
+    uint2* info = a.se_info + (size_t)row * SE_BINS;   // {lowest key, shift}
+    uint32_t* map = a.se_map + (size_t)row * SE_CB;
+    uint32_t base = before;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const uint32_t e = base | ((uint32_t)SE_CSHIFT - kb[i]) << 16;
+        s_map[tid * PER + i] = e;
+        map[tid * PER + i] = e;
+        base += 1u << kb[i];
+    }
+    if (tid == 0) {
+        info[0] = make_uint2(0u, 0u);
+        a.se_nbins[row] = nbins + 1;
+    }
+    __syncthreads();
+    const uint32_t lane = lane_id();
+    for (uint32_t b0 = tid & ~63u; b0 < (uint32_t)SE_CB; b0 += 1024) {   // a wave takes 64 buckets: small ones a lane each, large ones together
+        const uint32_t e = s_map[b0 + lane], sh = e >> 16, n = 1u << (SE_CSHIFT - sh);
+        if (n <= 8u)
+            for (uint32_t i = 0; i < n; ++i) info[1 + (e & 0xFFFFu) + i] = make_uint2(((b0 + lane) << SE_CSHIFT) + (i << sh), sh);
+        uint64_t big = __ballot(n > 8u);
+        while (big) {   // uniform
+            const int l = __builtin_ctzll(big);
+            big &= big - 1;
+            const uint32_t eb = (uint32_t)__builtin_amdgcn_readlane((int)e, l), shb = eb >> 16, nb = 1u << (SE_CSHIFT - shb);
+            for (uint32_t i = lane; i < nb; i += 64) info[1 + (eb & 0xFFFFu) + i] = make_uint2(((b0 + (uint32_t)l) << SE_CSHIFT) + (i << shb), shb);
+        }
+    }
+}
+
+// Exact counts of a workgroup's slice of a row.
+template <int DT>
+__global__ __launch_bounds__(SE_THREADS) void k_se_count(StopkArgs a) {
+    __shared__ __align__(16) uint32_t s_map[SE_CB];
+    __shared__ __align__(16) uint32_t s_cnt[SE_BINS];
+    const int row = blockIdx.y, tid = threadIdx.x;
+    const uint32_t lane = lane_id(), wave = (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6);
+    for (int i = tid; i < SE_CB / 4; i += SE_THREADS) ((uint4*)s_map)[i] = ((const uint4*)(a.se_map + (size_t)row * SE_CB))[i];
+    for (int i = tid; i < SE_BINS / 4; i += SE_THREADS) ((uint4*)s_cnt)[i] = make_uint4(0, 0, 0, 0);
+    __syncthreads();
+    RowLoader<DT, true> ld(a.g, a.ld, a.d, row);
+    const int64_t i0 = (int64_t)blockIdx.x * a.se_slice, i1 = i0 + a.se_slice < a.d ? i0 + a.se_slice : a.d;
+    uint32_t maxkey = 0;
+    se_stream<DT>(ld, i0, i1, wave, lane, [&](const uint32_t (&k)[4][4], const int (&nv)[4]) {
+        uint32_t e[4][4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) e[q][c] = s_map[k[q][c] >> SE_CSHIFT];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if (c < nv[q]) {
+                    atomicAdd(&s_cnt[se_bin(e[q][c], k[q][c])], 1u);
+                    maxkey = k[q][c] > maxkey ? k[q][c] : maxkey;
+                }
+    });
+    if (__ballot(maxkey >= 0x7F800000u) && lane == 0) atomicOr(a.dev_status, MLMC_DEV_NONFINITE);
+    __syncthreads();
+    uint4* part = (uint4*)(a.se_part + ((size_t)row * gridDim.x + blockIdx.x) * SE_BINS);
+    const int n4 = ((int)a.se_nbins[row] + 3) / 4;
+    for (int i = tid; i < n4; i += SE_THREADS) part[i] = ((const uint4*)s_cnt)[i];
+}
+
+// Per bin: exclusive prefix over the workgroups, in place, and the total; the total of every 256 bins.
+constexpr int SE_BLOCKS = (SE_BINS + 255) / 256;
+__global__ __launch_bounds__(256) void k_se_reduce(StopkArgs a) {
+    __shared__ uint32_t s_scan[256 / 64 + 1];
+    const int row = blockIdx.y;
+    const uint32_t bin = blockIdx.x * 256 + threadIdx.x;
+    const uint32_t nbins = a.se_nbins[row];
+    if (blockIdx.x * 256 >= nbins) return;
+    uint32_t* p = a.se_part + (size_t)row * a.se_wgs * SE_BINS + bin;
+    uint32_t run = 0;
+    int g = bin < nbins ? 0 : a.se_wgs;
+    for (; g + 8 <= a.se_wgs; g += 8) {
+        uint32_t v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = p[(size_t)(g + u) * SE_BINS];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) { p[(size_t)(g + u) * SE_BINS] = run; run += v[u]; }
+    }
+    for (; g < a.se_wgs; ++g) {
+        const uint32_t v = p[(size_t)g * SE_BINS];
+        p[(size_t)g * SE_BINS] = run;
+        run += v;
+    }
+    if (bin < nbins) a.se_total[(size_t)row * SE_BINS + bin] = run;
+    uint32_t all;
+    block_excl_scan<256>(run, s_scan, all);
+    if (threadIdx.x == 0) a.se_bsum[row * SE_BLOCKS + blockIdx.x] = all;
+}
+
+// value * 2^shift (in units of 2^-298) into the 64-bit word counters of a band
+__device__ __forceinline__ void se_add(unsigned long long* wide, uint64_t v, int shift) {
+    if (!v) return;
+    const int wi = shift >> 5, bs = shift & 31;
+    const uint32_t p0 = (uint32_t)(v << bs);
+    const uint32_t p1 = (uint32_t)(bs ? v >> (32 - bs) : v >> 32);
+    const uint32_t p2 = bs ? (uint32_t)(v >> (64 - bs)) : 0u;
+    if (p0 && wi < SE_WORDS) atomicAdd(&wide[wi], (unsigned long long)p0);
+    if (p1 && wi + 1 < SE_WORDS) atomicAdd(&wide[wi + 1], (unsigned long long)p1);
+    if (p2 && wi + 2 < SE_WORDS) atomicAdd(&wide[wi + 2], (unsigned long long)p2);
+}
+__device__ __forceinline__ int se_exp_shift(uint32_t key) {   // of the square of a significand
+    const uint32_t E = key >> 23;
+    return 2 * ((int)(E ? E : 1u) - 1);
+}
+
+// Per 256 bins: their ranks in descending order of their keys, classes, zones, thresholds that fall on bin edges.
+__global__ __launch_bounds__(256) void k_se_scan(StopkArgs a) {
+    __shared__ uint32_t s_scan[256 / 64 + 1];
+    __shared__ uint32_t s_z0, s_off0;
+    const int row = blockIdx.y, blk = blockIdx.x, tid = threadIdx.x;
+    const int nbins = (int)a.se_nbins[row], nblk = (nbins + 255) / 256;
+    if (blk >= nblk) return;
+    const uint32_t s = (uint32_t)(a.s < a.d ? a.s : a.d), last_t = (uint32_t)a.L - 1u;   // boundaries 1 .. L - 1 at ranks t s
+    const int bin = blk * 256 + 255 - tid;
+    const uint32_t n = bin < nbins ? a.se_total[(size_t)row * SE_BINS + bin] : 0u;
+    const uint2 in = bin < nbins ? a.se_info[(size_t)row * SE_BINS + bin] : make_uint2(0u, 0u);
+    uint32_t above, mine;
+    static_assert(SE_BLOCKS <= 256, "a thread takes a block's total");
+    block_excl_scan<256>(tid > blk && tid < nblk ? a.se_bsum[row * SE_BLOCKS + tid] : 0u, s_scan, above);
+    const uint32_t cum = above + block_excl_scan<256>(n, s_scan, mine);
+    if (blk == 0 && tid == 0 && (int64_t)above + mine != a.d) atomicOr(a.dev_status, MLMC_DEV_INTERNAL);
+    // boundaries strictly inside ranks [cum, cum + n): t0 .. t0 + nb - 1
+    const uint32_t t0 = cum / s + 1u;
+    uint32_t t1 = n ? (cum + n - 1u) / s : 0u;
+    if (t1 > last_t) t1 = last_t;
+    const uint32_t nb = t1 >= t0 ? t1 - t0 + 1u : 0u;
+    const bool one_key = in.y == 0u || (a.bf16 && in.y <= 16u);
+    const bool zone = nb && !one_key;
+    uint32_t zones, zents;   // zones are numbered, and their lists placed, in any order
+    const uint32_t z = block_excl_scan<256>(zone ? 1u : 0u, s_scan, zones);
+    const uint32_t zoff = block_excl_scan<256>(zone ? n : 0u, s_scan, zents);
+    if (tid == 0 && zones) {
+        s_z0 = atomicAdd(&a.se_nz[2 * row], zones);
+        s_off0 = atomicAdd(&a.se_nz[2 * row + 1], zents);
+    }
+    __syncthreads();
+    uint2* thr = a.se_thr + (size_t)row * (a.L + 1);
+    uint32_t code = (uint32_t)a.L + 255u;   // sums nobody reads: an empty bin, or one key with boundaries inside
+    if (n && nb == 0) {
+        // (255 - exponent) + band: one step at least whenever the exponent or the band changes
+        code = 255u - (in.x >> 23) + (t0 - 1u);
+        a.se_gtab[(size_t)row * (SE_LMAX + 256) + code] = (in.x >> 23) << 16 | (t0 - 1u);   // exponent, band (from 0)
+    } else if (zone) {
+        code = SE_ZONE | (s_z0 + z);   // a zone holds a boundary: fewer than L <= SE_LMAX zones
+        SZone zr;
+        zr.cum = cum;
+        zr.n = n;
+        zr.lo = in.x;
+        zr.shift = in.y;
+        zr.t0 = t0;
+        zr.nb = nb;
+        zr.off = s_off0 + zoff;
+        zr.bin = (uint32_t)bin;
+        a.se_zone[(size_t)row * SE_LMAX + s_z0 + z] = zr;
+    } else if (nb) {
+        // the first t s - cum of the equal keys (by index) are inside boundary t
+        const uint64_t sq = sig_square(in.x);
+        const int sh = se_exp_shift(in.x);
+        uint32_t r0 = 0;
+        for (uint32_t u = 0; u <= nb; ++u) {
+            const uint32_t r1 = u < nb ? (t0 + u) * s - cum : n;
+            unsigned long long* wide = a.se_big + ((size_t)row * a.L + (t0 + u - 1u)) * SE_WORDS;
+            se_add(wide, (sq & 0xFFFFFFFFull) * (r1 - r0), sh);
+            se_add(wide, (sq >> 32) * (r1 - r0), sh + 32);
+            if (u < nb) thr[t0 + u] = make_uint2(in.x, r1);
+            r0 = r1;
+        }
+    }
+    if (n && (cum + n) % s == 0u && (cum + n) / s <= last_t) thr[(cum + n) / s] = make_uint2(in.x, SE_ALL);   // a boundary at the bin's lower edge
+    if (bin < nbins) a.se_class[(size_t)row * SE_BINS + bin] = (uint16_t)code;
+    if (blk == 0 && tid == 0) {
+        thr[0] = make_uint2(0xFFFFFFFFu, 0u);
+        thr[a.L] = make_uint2(0u, SE_ALL);
+    }
+}
+
+// Second read: sums of the regions, lists of the zones.
+constexpr int SE_SUMS_BYTES = 40960;   // sums of L + 256 groups, in 1, 2 or 4 lane-interleaved copies
+template <int DT>
+__global__ __launch_bounds__(SE_THREADS) void k_se_split(StopkArgs a) {
+    __shared__ __align__(16) uint32_t s_map[SE_CB];
+    __shared__ __align__(16) uint16_t s_class[SE_BINS];
+    __shared__ uint32_t s_cur[SE_LMAX];
+    __shared__ __align__(16) unsigned long long s_sum[SE_SUMS_BYTES / 8];
+    const int row = blockIdx.y, tid = threadIdx.x;
+    const uint32_t lane = lane_id(), wave = (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6);
+    for (int i = tid; i < SE_CB / 4; i += SE_THREADS) ((uint4*)s_map)[i] = ((const uint4*)(a.se_map + (size_t)row * SE_CB))[i];
+    for (int i = tid; i < SE_BINS / 8; i += SE_THREADS) ((uint4*)s_class)[i] = ((const uint4*)(a.se_class + (size_t)row * SE_BINS))[i];
+    for (int i = tid; i < SE_SUMS_BYTES / 8; i += SE_THREADS) s_sum[i] = 0ull;
+    {
+        const int nz = (int)a.se_nz[2 * row];
+        const uint32_t* part = a.se_part + ((size_t)row * a.se_wgs + blockIdx.x) * SE_BINS;
+        const SZone* zr = a.se_zone + (size_t)row * SE_LMAX;
+        for (int z = tid; z < nz; z += SE_THREADS) s_cur[z] = zr[z].off + part[zr[z].bin];
+    }
+    __syncthreads();
+    RowLoader<DT, true> ld(a.g, a.ld, a.d, row);
+    const int64_t i0 = (int64_t)blockIdx.x * a.se_slice, i1 = i0 + a.se_slice < a.d ? i0 + a.se_slice : a.d;
+    uint32_t* list = a.se_list + (size_t)row * a.d;
+    const int rs = a.se_rep;
+    const uint32_t rlane = lane & ((1u << rs) - 1u), nobody = (uint32_t)a.L + 255u;
+    se_stream<DT>(ld, i0, i1, wave, lane, [&](const uint32_t (&k)[4][4], const int (&nv)[4]) {
+        uint32_t cl[4][4], pos[4][4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) cl[q][c] = s_map[k[q][c] >> SE_CSHIFT];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                cl[q][c] = s_class[se_bin(cl[q][c], k[q][c])];
+                if (c >= nv[q]) cl[q][c] = nobody;
+            }
+        // the places of zone entries are asked for first; they come back while the sums are added
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if (cl[q][c] >= SE_ZONE) pos[q][c] = atomicAdd(&s_cur[cl[q][c] & (SE_ZONE - 1u)], 1u);
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if (cl[q][c] < SE_ZONE) atomicAdd(&s_sum[(cl[q][c] << rs) | rlane], (unsigned long long)sig_square(k[q][c]));
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if (cl[q][c] >= SE_ZONE) list[pos[q][c]] = k[q][c];
+    });
+    __syncthreads();
+    const uint32_t* gtab = a.se_gtab + (size_t)row * (SE_LMAX + 256);
+    for (int g = tid; g < a.L + 255; g += SE_THREADS) {
+        unsigned long long lo = 0, hi = 0;
+        for (int r = 0; r < (1 << rs); ++r) {
+            const unsigned long long v = s_sum[(g << rs) + r];
+            lo += v & 0xFFFFFFFFull;
+            hi += v >> 32;
+        }
+        if (lo | hi) {
+            const uint32_t t = gtab[g];
+            const int sh = se_exp_shift((t >> 16) << 23);
+            unsigned long long* wide = a.se_big + ((size_t)row * a.L + (t & 0xFFFFu)) * SE_WORDS;
+            se_add(wide, lo, sh);
+            se_add(wide, hi, sh + 32);
+        }
+    }
+}
+
+// One workgroup per zone.  Keys of a zone differ in their low `shift` bits only.  Up to SE_ZCAP keys are put in order in LDS:
+// 256 buckets of the zone's key range, then a thread orders its bucket by insertion (a few keys); where a bucket holds many,
+// all keys by a bitonic sort, which takes three times as long.  More keys are ordered by a radix sort between the two lists in memory (a row that the sample misjudged: linear in the number of
+// keys, one workgroup), unless they are all the same.
+constexpr int SZ_THREADS = 256;
+constexpr uint32_t SZ_FEW = 32;
+__global__ __launch_bounds__(SZ_THREADS) void k_se_zone(StopkArgs a) {
+    __shared__ uint32_t s_k[SE_ZCAP];
+    __shared__ uint32_t s_h[256];
+    __shared__ uint32_t s_scan[SZ_THREADS / 64 + 1];
+    __shared__ uint32_t s_min, s_max;
+    const int row = blockIdx.y, tid = threadIdx.x;
+    if (blockIdx.x >= a.se_nz[2 * row]) return;
+    const uint32_t lane = lane_id(), wave = (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6);
+    const SZone zn = a.se_zone[(size_t)row * SE_LMAX + blockIdx.x];
+    const uint32_t n = zn.n;
+    uint32_t* src = a.se_list + (size_t)row * a.d + zn.off;
+    const uint32_t* sorted = nullptr;   // descending; null: in s_k
+    bool equal = false;
+    if (n <= (uint32_t)SE_ZCAP) {
+        constexpr int PER = SE_ZCAP / SZ_THREADS;
+        const uint32_t dsh = zn.shift > 8u ? zn.shift - 8u : 0u;
+        auto digit = [&](uint32_t k) -> uint32_t { return 255u - ((k - zn.lo) >> dsh); };
+        uint32_t my[PER];
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const uint32_t at = (uint32_t)(tid + i * SZ_THREADS);
+            my[i] = at < n ? src[at] : 0u;   // a zone holds no zeros
+        }
+        s_h[tid] = 0;
+        if (tid == 0) s_max = 0;
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < PER; ++i)
+            if (my[i]) atomicAdd(&s_h[digit(my[i])], 1u);
+        __syncthreads();
+        const uint32_t c = s_h[tid];
+        uint32_t all;
+        const uint32_t start = block_excl_scan<SZ_THREADS>(c, s_scan, all);
+        s_h[tid] = start;
+        if (c > SZ_FEW) s_max = 1u;
+        __syncthreads();
+        if (s_max == 0u) {   // uniform
+#pragma unroll
+            for (int i = 0; i < PER; ++i)
+                if (my[i]) s_k[atomicAdd(&s_h[digit(my[i])], 1u)] = my[i];
+            __syncthreads();
+            for (uint32_t i = 1; i < c; ++i) {
+                const uint32_t x = s_k[start + i];
+                uint32_t j = i;
+                for (; j > 0 && s_k[start + j - 1u] < x; --j) s_k[start + j] = s_k[start + j - 1u];
+                s_k[start + j] = x;
+            }
+            __syncthreads();
+        } else {
+        uint32_t np2 = 64;
+        while (np2 < n) np2 <<= 1;
+#pragma unroll
+        for (int i = 0; i < PER; ++i)
+            if ((uint32_t)(tid + i * SZ_THREADS) < np2) s_k[tid + i * SZ_THREADS] = my[i];
+        __syncthreads();
+        for (uint32_t k = 2; k <= np2; k <<= 1) {
+            for (uint32_t j = k >> 1; j > 0; j >>= 1) {
+                for (uint32_t p = tid; p < (np2 >> 1); p += SZ_THREADS) {
+                    const uint32_t i = ((p & ~(j - 1u)) << 1) | (p & (j - 1u)), l = i | j;
+                    const uint32_t x = s_k[i], y = s_k[l];
+                    if ((x < y) == ((i & k) == 0u)) { s_k[i] = y; s_k[l] = x; }
+                }
+                __syncthreads();
+            }
+        }
+        }
+    } else {
+        uint32_t mn = 0xFFFFFFFFu, mx = 0;
+        for (uint32_t i = tid; i < n; i += SZ_THREADS) {
+            const uint32_t k = src[i];
+            mn = k < mn ? k : mn;
+            mx = k > mx ? k : mx;
+        }
+        if (tid == 0) { s_min = 0xFFFFFFFFu; s_max = 0; }
+        __syncthreads();
+        atomicMin(&s_min, mn);
+        atomicMax(&s_max, mx);
+        __syncthreads();
+        equal = s_min == s_max;
+        sorted = src;
+        if (!equal) {
+            // stable passes of eight bits, descending; wave w owns a quarter of the list, in order
+            uint32_t (*h)[256] = (uint32_t (*)[256])s_k;   // [4 waves][256]: counts, then places
+            uint32_t* in = src;
+            uint32_t* out = a.se_list2 + (size_t)row * a.d + zn.off;
+            const uint32_t per = (n + SZ_THREADS - 1) / SZ_THREADS * 64;   // whole groups of 64 per wave
+            const uint32_t w0 = wave * per < n ? wave * per : n, w1 = w0 + per < n ? w0 + per : n;
+            for (uint32_t sh = 0; sh < zn.shift; sh += 8) {
+                __syncthreads();   // the keys a wave reads were written by others
+                for (int i = tid; i < 4 * 256; i += SZ_THREADS) s_k[i] = 0;
+                __syncthreads();
+                for (uint32_t i = w0 + lane; i < w1; i += 64) atomicAdd(&h[wave][255u - ((in[i] >> sh) & 255u)], 1u);
+                __syncthreads();
+                uint32_t mine = 0, all;
+                for (int w = 0; w < 4; ++w) mine += h[w][tid];
+                uint32_t run = block_excl_scan<SZ_THREADS>(mine, s_scan, all);
+                for (int w = 0; w < 4; ++w) {
+                    const uint32_t c = h[w][tid];
+                    h[w][tid] = run;
+                    run += c;
+                }
+                __syncthreads();
+                for (uint32_t i0 = w0; i0 < w1; i0 += 64) {   // uniform over the wave
+                    const bool valid = i0 + lane < w1;
+                    const uint32_t k = in[valid ? i0 + lane : w1 - 1u];
+                    const uint32_t digit = 255u - ((k >> sh) & 255u);
+                    uint64_t peers = __ballot(valid);
+#pragma unroll
+                    for (int b = 0; b < 8; ++b) {
+                        const uint64_t m = __ballot(valid && ((digit >> b) & 1u));
+                        peers &= ((digit >> b) & 1u) ? m : ~m;
+                    }
+                    const uint32_t rank = mbcnt(peers);
+                    const uint32_t base = h[wave][digit];
+                    wave_lds_sync();
+                    if (valid && rank == 0) h[wave][digit] = base + (uint32_t)__popcll(peers);
+                    wave_lds_sync();
+                    if (valid) out[base + rank] = k;
+                }
+                uint32_t* t = in;
+                in = out;
+                out = t;
+                __threadfence_block();
+            }
+            __syncthreads();
+            sorted = in;
+        }
+    }
+    auto key_at = [&](uint32_t i) -> uint32_t { return sorted ? sorted[i] : s_k[i]; };
+    const uint32_t s = (uint32_t)(a.s < a.d ? a.s : a.d);
+    const int esh = se_exp_shift(zn.lo);
+    for (uint32_t u = tid; u < zn.nb; u += SZ_THREADS) {
+        const uint32_t r = (zn.t0 + u) * s - zn.cum;   // 1 .. n - 1 keys of the zone are inside
+        const uint32_t tau = key_at(r - 1u);
+        uint32_t q = SE_ALL;
+        if (key_at(r) == tau) {   // its equal keys are split: how many are inside
+            uint32_t lo = 0, hi = r - 1u;   // first position with a key <= tau
+            while (lo < hi) {
+                const uint32_t mid = (lo + hi) >> 1;
+                if (key_at(mid) > tau) lo = mid + 1u;
+                else hi = mid;
+            }
+            q = r - lo;
+        }
+        a.se_thr[(size_t)row * (a.L + 1) + zn.t0 + u] = make_uint2(tau, q);
+    }
+    for (uint32_t u = wave; u <= zn.nb; u += SZ_THREADS / 64) {   // part u lies in band t0 + u (from 1)
+        const uint32_t r0 = u ? (zn.t0 + u - 1u) * s - zn.cum : 0u, r1 = u < zn.nb ? (zn.t0 + u) * s - zn.cum : n;
+        uint64_t lo = 0, hi = 0;
+        if (equal) {
+            const uint64_t sq = sig_square(s_min);
+            if (lane == 0) { lo = (sq & 0xFFFFFFFFull) * (r1 - r0); hi = (sq >> 32) * (r1 - r0); }
+        } else {
+            for (uint32_t i = r0 + lane; i < r1; i += 64) {
+                const uint64_t sq = sig_square(key_at(i));
+                lo += sq & 0xFFFFFFFFull;
+                hi += sq >> 32;
+            }
+        }
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) {
+            lo += (uint64_t)__shfl_xor((unsigned long long)lo, o, 64);
+            hi += (uint64_t)__shfl_xor((unsigned long long)hi, o, 64);
+        }
+        if (lane == 0) {
+            unsigned long long* wide = a.se_big + ((size_t)row * a.L + (zn.t0 + u - 1u)) * SE_WORDS;
+            se_add(wide, lo, esh);
+            se_add(wide, hi, esh + 32);
+        }
+    }
+}
+
+// Delta_l of every band: carries, one rounding to fp64, sqrt.
+__global__ __launch_bounds__(64) void k_se_norms(StopkArgs a) {
+    __shared__ uint32_t s_big[64][SE_WORDS + 1];
+    const int row = blockIdx.y;
+    const int band = (int)(blockIdx.x * 64 + threadIdx.x);
+    if (band >= a.L) return;
+    const unsigned long long* wide = a.se_big + ((size_t)row * a.L + band) * SE_WORDS;
+    unsigned long long carry = 0, w[SE_WORDS];
+#pragma unroll
+    for (int i = 0; i < SE_WORDS; ++i) w[i] = wide[i];
+#pragma unroll
+    for (int i = 0; i < SE_WORDS; ++i) {
+        const unsigned long long t = w[i] + carry;
+        s_big[threadIdx.x][i] = (uint32_t)t;
+        carry = t >> 32;
+    }
+    BigAcc acc;
+    acc.w = s_big[threadIdx.x];
+    const double nrm = __dsqrt_rn(acc.to_double());
+    a.norms[(size_t)row * a.L + band] = nrm;
+    if (a.norms_user) a.norms_user[(size_t)row * a.L + band] = nrm;
+}
+
+// The drawn segment between its two boundaries: hi (boundary l - 1, its inside excluded) and lo (boundary l).
+struct SegTest {
+    uint32_t tau_hi, tau_lo, q_hi, q_lo;
+    bool cut_hi, cut_lo, same;   // equal keys split at a boundary; both boundaries at one key
+    __device__ __forceinline__ SegTest(const StopkArgs& a, int row) {
+        const int l = a.srow[row].level;
+        const uint2* thr = a.se_thr + (size_t)row * (a.L + 1);
+        const uint2 h = thr[l - 1], o = thr[l];
+        tau_hi = h.x; q_hi = h.y; tau_lo = o.x; q_lo = o.y;
+        same = tau_hi == tau_lo;
+        cut_hi = l > 1 && q_hi != SE_ALL;
+        cut_lo = q_lo != SE_ALL && !same;
+    }
+    // 0: outside, 1: member, 2: equal to tau_hi and decided by rank, 3: equal to tau_lo and decided by rank
+    __device__ __forceinline__ int kind(uint32_t key) const {
+        if (key < tau_hi) return key > tau_lo || (key == tau_lo && !cut_lo) ? 1 : (key == tau_lo ? 3 : 0);
+        return key == tau_hi && cut_hi ? 2 : 0;
+    }
+    __device__ __forceinline__ bool in_hi(uint32_t rank) const { return rank >= q_hi && (!same || q_lo == SE_ALL || rank < q_lo); }
+    __device__ __forceinline__ bool in_lo(uint32_t rank) const { return rank < q_lo; }
+    // how many of the equal keys of ranks [t, t + n) are members
+    __device__ __forceinline__ uint32_t count_hi(uint32_t t, uint32_t n) const {
+        const uint32_t top = same && q_lo != SE_ALL && q_lo < t + n ? q_lo : t + n, bot = q_hi > t ? q_hi : t;
+        return top > bot ? top - bot : 0u;
+    }
+    __device__ __forceinline__ uint32_t count_lo(uint32_t t, uint32_t n) const { return q_lo > t ? (q_lo - t < n ? q_lo - t : n) : 0u; }
+};
+
+// Third read: a wave takes a tile of 4096 entries; its bitmap (members, and entries that a rank decides) and its counts.
+template <int DT>
+__global__ __launch_bounds__(256) void k_se_mark(StopkArgs a) {
+    __shared__ uint32_t s_bm[4][TILE / 32];
+    const int row = blockIdx.y;
+    const uint32_t lane = lane_id(), wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t tile = (int64_t)blockIdx.x * 4 + wave;
+    if (tile >= a.ntiles) return;
+    const SegTest st(a, row);
+    RowLoader<DT, true> ld(a.g, a.ld, a.d, row);
+    ((uint2*)s_bm[wave])[lane] = make_uint2(0u, 0u);
+    wave_lds_sync();
+    const int64_t j0 = tile * TILE;
+    uint32_t n1 = 0, n2 = 0, n3 = 0;
+    auto test = [&](const uint32_t (&b)[4], int q, int nv) {
+        int kd[4];
+        int any = 0;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            kd[c] = c < nv ? st.kind(key_of_bits(b[c])) : 0;
+            any |= kd[c];
+        }
+        if (any) {
+            uint32_t nib = 0;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                nib |= (kd[c] ? 1u : 0u) << c;
+                n1 += kd[c] == 1;
+                n2 += kd[c] == 2;
+                n3 += kd[c] == 3;
+            }
+            const uint32_t rel = (uint32_t)q * 256u + lane * 4u;
+            atomicOr(&s_bm[wave][rel >> 5], nib << (rel & 31u));
+        }
+    };
+    if (j0 + TILE <= a.d) {   // uniform
+        uint32_t b[16][4];
+#pragma unroll
+        for (int q = 0; q < 16; ++q) ld.load4_full(j0 + q * 256 + lane * 4, b[q]);
+#pragma unroll
+        for (int q = 0; q < 16; ++q) test(b[q], q, 4);
+    } else {
+        for (int q = 0; q < 16; ++q) {
+            uint32_t b[4];
+            const int nv = ld.load4(j0 + q * 256 + lane * 4, b);
+            test(b, q, nv);
+        }
+    }
+    wave_lds_sync();
+    const int64_t w0 = tile * (TILE / 32) + lane * 2;
+    uint32_t* bm = a.bitmap + (size_t)row * a.bm_words;
+    if (w0 < a.bm_words) *(uint2*)(bm + w0) = ((const uint2*)s_bm[wave])[lane];   // bm_words is a multiple of 4
+    n1 = wave_sum(n1);
+    n2 = wave_sum(n2);
+    n3 = wave_sum(n3);
+    if (lane == 0) {
+        const size_t at = (size_t)row * a.ntiles + tile;
+        a.tile_cnt[at] = n1;
+        a.se_tie[at] = make_uint2(n2, n3);
+    }
+}
+
+// Per row: entries before every tile, equal keys before every tile, where the row's message starts.
+__global__ __launch_bounds__(1024) void k_se_offsets(StopkArgs a) {
+    __shared__ uint32_t s_scan[1024 / 64 + 1];
+    const int row = blockIdx.x, tid = threadIdx.x;
+    const SegTest st(a, row);
+    uint32_t* to = a.tile_off + (size_t)row * (a.ntiles + 1);
+    const uint32_t* tc = a.tile_cnt + (size_t)row * a.ntiles;
+    uint2* tie = a.se_tie + (size_t)row * a.ntiles;
+    uint32_t carry = 0, carry2 = 0, carry3 = 0;
+    for (int64_t j0 = 0; j0 < a.ntiles; j0 += 1024) {
+        const int64_t t = j0 + tid;
+        uint32_t c = t < a.ntiles ? tc[t] : 0u, round_total;
+        if (st.cut_hi || st.cut_lo) {   // uniform
+            const uint2 n = t < a.ntiles ? tie[t] : make_uint2(0u, 0u);
+            uint2 before;
+            uint32_t all2, all3;
+            before.x = carry2 + block_excl_scan<1024>(n.x, s_scan, all2);
+            before.y = carry3 + block_excl_scan<1024>(n.y, s_scan, all3);
+            carry2 += all2;
+            carry3 += all3;
+            if (t < a.ntiles) tie[t] = before;
+            c += st.count_hi(before.x, n.x) + st.count_lo(before.y, n.y);
+        }
+        const uint32_t ex = block_excl_scan<1024>(c, s_scan, round_total);
+        if (t < a.ntiles) to[t] = carry + ex;
+        carry += round_total;
+    }
+    if (tid == 0) {
+        to[a.ntiles] = carry;
+        if ((int64_t)carry != a.srow[row].count) atomicOr(a.dev_status, MLMC_DEV_INTERNAL);
+        int64_t start = 0;
+        for (int r = 0; r < row; ++r) start += a.srow[r].count;
+        a.row_off[row] = start;
+        if (row == a.M - 1) {
+            a.row_off[a.M] = start + carry;
+            if (start + (int64_t)carry > a.capacity) atomicOr(a.dev_status, MLMC_DEV_CAPACITY);
+        }
+    }
+}
+
+// The message in index order where equal keys may be split: a wave takes a tile, a lane two words of its bitmap.
+template <int DT>
+__global__ __launch_bounds__(256) void k_se_write(StopkArgs a) {
+    const int row = blockIdx.y;
+    const uint32_t lane = lane_id(), wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t tile = (int64_t)blockIdx.x * 4 + wave;
+    if (tile >= a.ntiles) return;
+    const uint32_t* to = a.tile_off + (size_t)row * (a.ntiles + 1);
+    if (to[tile + 1] == to[tile]) return;   // nothing of the segment in this tile
+    const SegTest st(a, row);
+    const uint32_t* bm = a.bitmap + (size_t)row * a.bm_words;
+    RowLoader<DT, true> ld(a.g, a.ld, a.d, row);
+    const float w = a.srow[row].weight;
+    const int64_t w0 = tile * (TILE / 32) + lane * 2;
+    uint2 m = w0 < a.bm_words ? *(const uint2*)(bm + w0) : make_uint2(0u, 0u);
+    uint64_t bits = (uint64_t)m.y << 32 | m.x;
+    if (st.cut_hi || st.cut_lo) {   // uniform: entries decided by rank are kept or cleared
+        uint32_t n2 = 0, n3 = 0;
+        for (uint64_t b = bits; b; b &= b - 1) {
+            const int kd = st.kind(key_of_bits(ld.load1(w0 * 32 + __builtin_ctzll(b))));
+            n2 += kd == 2;
+            n3 += kd == 3;
+        }
+        uint32_t i2 = n2, i3 = n3;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t u2 = __shfl_up(i2, o, 64), u3 = __shfl_up(i3, o, 64);
+            if (lane >= (uint32_t)o) { i2 += u2; i3 += u3; }
+        }
+        const uint2 before = a.se_tie[(size_t)row * a.ntiles + tile];
+        uint32_t r2 = before.x + i2 - n2, r3 = before.y + i3 - n3;
+        for (uint64_t b = bits; b; b &= b - 1) {
+            const int at = __builtin_ctzll(b);
+            const int kd = st.kind(key_of_bits(ld.load1(w0 * 32 + at)));
+            if (kd == 2 && !st.in_hi(r2++)) bits &= ~(1ull << at);
+            if (kd == 3 && !st.in_lo(r3++)) bits &= ~(1ull << at);
+        }
+    }
+    const uint32_t mine = (uint32_t)__popcll(bits);
+    uint32_t inc = mine;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t u = __shfl_up(inc, o, 64);
+        if (lane >= (uint32_t)o) inc += u;
+    }
+    int64_t at = a.row_off[row] + to[tile] + (inc - mine);
+    for (; bits; bits &= bits - 1, ++at) {
+        const int64_t j = w0 * 32 + __builtin_ctzll(bits);
+        if (at < a.capacity) {
+            a.idx[at] = (uint32_t)j;
+            a.val[at] = __fmul_rn(__uint_as_float(ld.load1(j)), w);
+        }
+    }
+}
+
+template <int DT>
+static mlmc_status launch_bins(const mlmc_plan_t* pl, const StopkArgs& a, bool message, hipStream_t st) {
+    const int M = pl->M;
+    {
+        const size_t n16 = a.clear_bytes / 16;   // coarse histograms and band sums
+        int blocks = (int)((n16 + 255) / 256);
+        if (blocks > 2048) blocks = 2048;
+        MLMC_LAUNCH(K_ZERO, st, k_sb_clear<<<blocks, 256, 0, st>>>((uint4*)a.se_coarse, n16, a.dev_status));
+    }
+    {
+        const int64_t ns = ((a.d + 1023) / 1024 + (1 << a.se_shift) - 1) >> a.se_shift;
+        int64_t gx = (ns + 63) / 64, cap = 1024 / M > 0 ? 1024 / M : 1;
+        if (gx > cap) gx = cap;
+        MLMC_LAUNCH(K_HIST, st, k_se_coarse<DT><<<dim3((unsigned)gx, M), 512, 0, st>>>(a));
+    }
+    MLMC_LAUNCH(K_SCAN, st, k_se_map<DT><<<M, 1024, 0, st>>>(a));
+    MLMC_LAUNCH(K_SE_COUNT, st, k_se_count<DT><<<dim3(a.se_wgs, M), SE_THREADS, 0, st>>>(a));
+    MLMC_LAUNCH(K_SE_SCAN, st, k_se_reduce<<<dim3(SE_BLOCKS, M), 256, 0, st>>>(a));
+    MLMC_LAUNCH(K_SE_SCAN, st, k_se_scan<<<dim3(SE_BLOCKS, M), 256, 0, st>>>(a));
+    MLMC_LAUNCH(K_SE_SPLIT, st, k_se_split<DT><<<dim3(a.se_wgs, M), SE_THREADS, 0, st>>>(a));
+    if (a.L > 1) MLMC_LAUNCH(K_SE_ZONE, st, k_se_zone<<<dim3(a.L - 1, M), SZ_THREADS, 0, st>>>(a));
+    MLMC_LAUNCH(K_SB_NORMS, st, k_se_norms<<<dim3((a.L + 63) / 64, M), 64, 0, st>>>(a));
+    if (!message) return MLMC_OK;
+    const dim3 tgrid((unsigned)((a.ntiles + 3) / 4), M);
+    MLMC_LAUNCH(K_SB_DRAW, st, k_sb_draw<<<M, 1024, 0, st>>>(a));
+    MLMC_LAUNCH(K_SB_MARK, st, k_se_mark<DT><<<tgrid, 256, 0, st>>>(a));
+    MLMC_LAUNCH(K_SB_OFFSETS, st, k_se_offsets<<<M, 1024, 0, st>>>(a));
+    MLMC_LAUNCH(K_SB_WRITE, st, k_se_write<DT><<<tgrid, 256, 0, st>>>(a));
+    return MLMC_OK;
+}
+
 mlmc_status stopk_run(const mlmc_plan_t* pl, const StopkArgs& a, bool message, hipStream_t st) {
+    if (pl->off_se_end) {
+        if (pl->dtype == MLMC_F32) return launch_bins<MLMC_F32>(pl, a, message, st);
+        return launch_bins<MLMC_BF16>(pl, a, message, st);
+    }
     if (pl->dtype == MLMC_F32) return launch_stopk<MLMC_F32>(pl, a, message, st);
     return launch_stopk<MLMC_BF16>(pl, a, message, st);
 }

@@ -82,3 +82,44 @@ def test_stopk_plan_validation():
             P.Plan(P.MLMC_STOPK, 2, bad["d"], P.MLMC_F32, [bad["s"]], None, allocate=False)
     with pytest.raises(P.MlmcError):
         P.Plan(P.MLMC_STOPK, 2, 1000, P.MLMC_F32, [10], [0.5, 0.5], allocate=False)   # fixed p is not defined here
+
+
+def _few_values(d, rng):
+    """Most entries share a few magnitudes, so that many boundaries fall among equal keys and one key may hold a whole segment."""
+    v = np.array([0.0, 1e-3, 1.0000001, 1.0000002, 3.5, 1e-42], dtype=np.float32)
+    g = v[rng.integers(0, len(v), d)] * rng.choice(np.array([-1, 1], dtype=np.float32), d)
+    g[:: 97] = rng.standard_normal(len(g[:: 97])).astype(np.float32)
+    return g
+
+
+def _misled_sample(d, rng):
+    """Rows of 2^21 entries or more are sampled, every other block of 1024 of them: the sampled blocks are zero, the others lie in one
+    coarse bucket of keys, so that a single bin holds a million distinct keys and most boundaries."""
+    g = np.zeros(d, dtype=np.float32)
+    even = (np.arange(d) >> 10) % 2 == 0
+    g[even] = (1.0 + rng.random(int(even.sum())) * 0.03).astype(np.float32)
+    return g
+
+
+@pytest.mark.parametrize("what,d,s,dtype,ld", [
+    ("normal", 4096 * 9, 9, "f32", None),              # 4096 levels: the most without a sort
+    ("normal", 4097 * 9, 9, "f32", None),              # 4097: sorted
+    ("normal", 4096, 1, "f32", None),                  # every entry a segment
+    ("normal", 300_001, 70_000, "f32", 300_003),       # segments of more than 2^16 entries, odd rows
+    ("normal", 1025 * 64 - 1, 64, "f32", None),        # 1025 levels: two copies of the sums
+    ("normal", 3, 2, "f32", None),
+    ("few", 50_021, 37, "f32", None),
+    ("few", 50_021, 9_000, "f32", None),
+    ("few", 50_021, 37, "bf16", 50_023),
+    ("misled", (1 << 21) + 777, 40_000, "f32", None),  # zones of more keys than LDS holds, with many boundaries each
+])
+def test_stopk_edges_of_the_binned_path(what, d, s, dtype, ld):
+    rng = np.random.default_rng(d + s)
+    make = {"normal": lambda: rng.standard_normal(d).astype(np.float32), "few": lambda: _few_values(d, rng), "misled": lambda: _misled_sample(d, rng)}[what]
+    G = np.stack([make() for _ in range(2)])
+    dt = P.MLMC_F32
+    if dtype == "bf16":
+        dt = P.MLMC_BF16
+        G = W.f32_to_bf16_bits(G)
+    print(f"stopk binned {what} d={d} s={s} {dtype} ld={ld}", flush=True)
+    _run_and_check(G, s, dtype=dt, steps=(0, 1), ld=ld)
