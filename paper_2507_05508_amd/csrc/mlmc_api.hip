@@ -266,6 +266,7 @@ static mlmc_status plan_stopk(mlmc_plan_t** plan, int M, int64_t d, int in_dtype
         pl->se_wgs = (int)((d + pl->se_slice - 1) / pl->se_slice);
         pl->off_se_coarse = take(sizeof(uint32_t) * 8192 * (size_t)M);
         pl->off_se_big = take(sizeof(uint64_t) * SE_WORDS * (size_t)L * M);
+        pl->off_se_gsum = take(sizeof(uint64_t) * 2 * (size_t)(L + 256) * M);
         pl->off_se_nz = take(sizeof(uint32_t) * 2 * (size_t)M);
         pl->off_se_end = off;
         pl->off_se_bsum = take(sizeof(uint32_t) * ((SE_BINS + 255) / 256) * (size_t)M);
@@ -344,6 +345,7 @@ static void fill_stopk_args(const mlmc_plan_t* pl, StopkArgs& a, const void* g, 
         a.se_thr = (uint2*)(w + pl->off_se_thr);
         a.se_zone = (SZone*)(w + pl->off_se_zone);
         a.se_bsum = (uint32_t*)(w + pl->off_se_bsum);
+        a.se_gsum = (unsigned long long*)(w + pl->off_se_gsum);
         a.se_nz = (uint32_t*)(w + pl->off_se_nz);
         a.se_list = (uint32_t*)(w + pl->off_se_list);
         a.se_list2 = (uint32_t*)(w + pl->off_se_list2);

@@ -242,6 +242,7 @@ struct StopkArgs {
     uint32_t* se_gtab;       // [M][SE_LMAX + 256] exponent << 16 | band of a sum group
     uint2* se_thr;           // [M][L + 1] thresholds of the boundaries: {key, how many of its equals are inside}
     SZone* se_zone;          // [M][SE_LMAX]
+    unsigned long long* se_gsum;  // [M][L + 256][2] sums of the groups, low and high 32-bit halves (cleared per call)
     uint32_t* se_nz;         // [M][2] zones, their entries (cleared per call)
     uint32_t* se_bsum;       // [M][SE_BINS / 256] totals of 256 bins each
     uint32_t* se_list;       // [M][d] keys of the zones
@@ -293,7 +294,7 @@ struct mlmc_plan_s {
     int64_t bm_words;
     size_t off_pa, off_pb, off_counts, off_bitmap, off_tilecnt, off_clear_end, off_srow, off_bintot;
     size_t off_se_coarse, off_se_big, off_se_end, off_se_map, off_se_info, off_se_nbins, off_se_part, off_se_total, off_se_class, off_se_gtab, off_se_thr,
-        off_se_zone, off_se_nz, off_se_list, off_se_list2, off_se_tie, off_se_bsum;   // off_se_end: end of what is cleared per call (0: the plan sorts)
+        off_se_zone, off_se_nz, off_se_list, off_se_list2, off_se_tie, off_se_bsum, off_se_gsum;   // off_se_end: end of what is cleared per call (0: the plan sorts)
     int se_shift, se_wgs, se_rep;
     int64_t se_slice;
     size_t off_rtn_sums;   // Round-to-Nearest plans

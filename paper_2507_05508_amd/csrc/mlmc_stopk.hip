@@ -464,7 +464,7 @@ static mlmc_status launch_stopk(const mlmc_plan_t* pl, const StopkArgs& a, bool 
 //   k_se_mark / k_se_offsets / k_se_write   third read: bitmap of the drawn segment and its message; entries equal to a
 //                 threshold whose equal keys are split are told apart by their rank in index order
 // Three reads of the rows and about 10 bytes per entry of other traffic against 4 x 24 bytes and more for the sort of pairs:
-// 8 rows of 1.17e7 fp32 entries at 1000 levels, compress + aggregate: 2788 -> 583 us.  The line at SE_LMAX levels is where the
+// 8 rows of 1.17e7 fp32 entries at 1000 levels, compress + aggregate: 2788 -> 430 us.  The line at SE_LMAX levels is where the
 // class of a bin and the list cursors of a zone per boundary still fit LDS beside the map and the sums.
 constexpr int SE_CB = 8192;             // coarse buckets: key >> SE_CSHIFT
 constexpr int SE_CSHIFT = 18;
@@ -565,7 +565,7 @@ __global__ __launch_bounds__(512) void k_se_coarse(StopkArgs a) {
 template <int DT>
 __global__ __launch_bounds__(1024) void k_se_map(StopkArgs a) {
     __shared__ uint32_t s_map[SE_CB];
-    __shared__ uint32_t s_scan[1024 / 64 + 1];
+    __shared__ uint32_t s_scan[1024 / 64 + 1], s_need[5];
     constexpr int PER = SE_CB / 1024;
     constexpr uint32_t ROOM = SE_BINS - 1;          // zero has a bin of its own
     constexpr uint32_t SHARE = ROOM - SE_CB;
@@ -574,28 +574,32 @@ __global__ __launch_bounds__(1024) void k_se_map(StopkArgs a) {
 #pragma unroll
     for (int i = 0; i < PER; ++i) { c[i] = a.se_coarse[(size_t)row * SE_CB + tid * PER + i]; sum += c[i]; }
     uint32_t ns;
+    if (tid < 5) s_need[tid] = 0;
     block_excl_scan<1024>(sum, s_scan, ns);
-    uint32_t kb[PER], before = 0, nbins = 0;
-    bool done = false;
-    for (uint32_t m = DT == MLMC_BF16 ? 9u : 8u; !done; --m) {   // uniform; m = 4 always fits
+    // log2 of the bins of bucket i at share m / 4 (16-bit inputs: m = 8 stands for a bin per key, 4 for one per bucket)
+    const unsigned long long unit = ((unsigned long long)SHARE << 30) / ns;   // bins per sampled entry at share 1, times 2^30
+    auto bits = [&](int i, uint32_t m) -> uint32_t {
+        if (!c[i]) return 0u;
+        if (DT == MLMC_BF16) return m == 8u ? 2u : 0u;
+        const uint32_t v = (uint32_t)((c[i] * unit * m) >> 32);   // rounded down; c unit <= SHARE 2^30
+        const uint32_t k = v ? 31u - (uint32_t)__clz((int)v) : 0u;
+        return k < (uint32_t)SE_CSHIFT ? k : (uint32_t)SE_CSHIFT;
+    };
+#pragma unroll
+    for (uint32_t m = 4; m <= 8; ++m) {
         uint32_t need = 0;
 #pragma unroll
-        for (int i = 0; i < PER; ++i) {
-            kb[i] = 0;
-            if (c[i]) {
-                if (DT == MLMC_BF16) {
-                    kb[i] = m == 9u ? 2u : 0u;
-                } else {
-                    const unsigned long long v = (unsigned long long)c[i] * (SHARE * m / 4u) / ns;
-                    kb[i] = v ? 31u - (uint32_t)__clz((int)(uint32_t)v) : 0u;
-                    if (kb[i] > (uint32_t)SE_CSHIFT) kb[i] = SE_CSHIFT;
-                }
-            }
-            need += 1u << kb[i];
-        }
-        before = block_excl_scan<1024>(need, s_scan, nbins);
-        done = nbins <= ROOM || m <= 4u;
+        for (int i = 0; i < PER; ++i) need += 1u << bits(i, m);
+        need = wave_sum(need);
+        if (lane_id() == 0) atomicAdd(&s_need[m - 4u], need);
     }
+    __syncthreads();
+    uint32_t m = 8;
+    while (m > 4u && s_need[m - 4u] > ROOM) --m;   // m = 4 always fits
+    uint32_t kb[PER], need = 0, nbins;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) { kb[i] = bits(i, m); need += 1u << kb[i]; }
+    const uint32_t before = block_excl_scan<1024>(need, s_scan, nbins);
     uint2* info = a.se_info + (size_t)row * SE_BINS;   // {lowest key, shift}
     uint32_t* map = a.se_map + (size_t)row * SE_CB;
     uint32_t base = before;
@@ -833,7 +837,7 @@ __global__ __launch_bounds__(SE_THREADS) void k_se_split(StopkArgs a) {
                 if (cl[q][c] >= SE_ZONE) list[pos[q][c]] = k[q][c];
     });
     __syncthreads();
-    const uint32_t* gtab = a.se_gtab + (size_t)row * (SE_LMAX + 256);
+    unsigned long long* gsum = a.se_gsum + (size_t)row * (a.L + 256) * 2;
     for (int g = tid; g < a.L + 255; g += SE_THREADS) {
         unsigned long long lo = 0, hi = 0;
         for (int r = 0; r < (1 << rs); ++r) {
@@ -841,13 +845,8 @@ __global__ __launch_bounds__(SE_THREADS) void k_se_split(StopkArgs a) {
             lo += v & 0xFFFFFFFFull;
             hi += v >> 32;
         }
-        if (lo | hi) {
-            const uint32_t t = gtab[g];
-            const int sh = se_exp_shift((t >> 16) << 23);
-            unsigned long long* wide = a.se_big + ((size_t)row * a.L + (t & 0xFFFFu)) * SE_WORDS;
-            se_add(wide, lo, sh);
-            se_add(wide, hi, sh + 32);
-        }
+        if (lo) atomicAdd(&gsum[2 * g], lo);
+        if (hi) atomicAdd(&gsum[2 * g + 1], hi);
     }
 }
 
@@ -863,6 +862,21 @@ __global__ __launch_bounds__(SZ_THREADS) void k_se_zone(StopkArgs a) {
     __shared__ uint32_t s_scan[SZ_THREADS / 64 + 1];
     __shared__ uint32_t s_min, s_max;
     const int row = blockIdx.y, tid = threadIdx.x;
+    if ((int)blockIdx.x >= a.L - 1) {   // the last workgroups of a row: sums of the regions to their bands
+        const int g = ((int)blockIdx.x - (a.L - 1)) * SZ_THREADS + tid;
+        if (g < a.L + 255) {
+            const unsigned long long* gs = a.se_gsum + ((size_t)row * (a.L + 256) + g) * 2;
+            const unsigned long long lo = gs[0], hi = gs[1];
+            if (lo | hi) {
+                const uint32_t t = a.se_gtab[(size_t)row * (SE_LMAX + 256) + g];
+                const int sh = se_exp_shift((t >> 16) << 23);
+                unsigned long long* wide = a.se_big + ((size_t)row * a.L + (t & 0xFFFFu)) * SE_WORDS;
+                se_add(wide, lo, sh);
+                se_add(wide, hi, sh + 32);
+            }
+        }
+        return;
+    }
     if (blockIdx.x >= a.se_nz[2 * row]) return;
     const uint32_t lane = lane_id(), wave = (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6);
     const SZone zn = a.se_zone[(size_t)row * SE_LMAX + blockIdx.x];
@@ -1257,7 +1271,7 @@ static mlmc_status launch_bins(const mlmc_plan_t* pl, const StopkArgs& a, bool m
     MLMC_LAUNCH(K_SE_SCAN, st, k_se_reduce<<<dim3(SE_BLOCKS, M), 256, 0, st>>>(a));
     MLMC_LAUNCH(K_SE_SCAN, st, k_se_scan<<<dim3(SE_BLOCKS, M), 256, 0, st>>>(a));
     MLMC_LAUNCH(K_SE_SPLIT, st, k_se_split<DT><<<dim3(a.se_wgs, M), SE_THREADS, 0, st>>>(a));
-    if (a.L > 1) MLMC_LAUNCH(K_SE_ZONE, st, k_se_zone<<<dim3(a.L - 1, M), SZ_THREADS, 0, st>>>(a));
+    MLMC_LAUNCH(K_SE_ZONE, st, k_se_zone<<<dim3(a.L - 1 + (a.L + 255 + SZ_THREADS - 1) / SZ_THREADS, M), SZ_THREADS, 0, st>>>(a));
     MLMC_LAUNCH(K_SB_NORMS, st, k_se_norms<<<dim3((a.L + 63) / 64, M), 64, 0, st>>>(a));
     if (!message) return MLMC_OK;
     const dim3 tgrid((unsigned)((a.ntiles + 3) / 4), M);
