@@ -169,6 +169,11 @@ static void fill_bits_args(const mlmc_plan_t* pl, BitsArgs& b, const void* g, in
     if (pl->kind == MLMC_RTN && ws) {
         b.rtn_sums = (unsigned long long*)(w + pl->off_rtn_sums);
         b.norms = (double*)(w + pl->off_norms);
+        if (pl->rtn_wgs) {
+            b.rtn_part = (uint32_t*)(w + pl->off_rtn_part);
+            b.rtn_total = (uint32_t*)(w + pl->off_rtn_total);
+            b.rtn_slice = pl->rtn_slice;
+        }
     }
     b.nplanes = pl->nplanes;
     b.nwords = (pl->d + 63) / 64;
@@ -479,6 +484,18 @@ mlmc_status mlmc_plan(mlmc_plan_t** plan, int kind, int M, int64_t d, int in_dty
         off = align_up(off + sizeof(unsigned long long) * 2 * (size_t)L * M, 256);
         pl->off_norms = off;
         off = align_up(off + sizeof(double) * (size_t)L * M, 256);
+        // Counting magnitudes costs a workgroup 128 KB to clear and to store, about 25 us in all; the two reads it replaces take
+        // about 1.2 us per 1e6 entries.
+        if (in_dtype == MLMC_BF16 && (int64_t)M * d >= ((int64_t)1 << 25)) {
+            int64_t wgs = 256 / M > 0 ? 256 / M : 1;   // one workgroup per CU in one round
+            if (wgs > (d + 8191) / 8192) wgs = (d + 8191) / 8192;
+            pl->rtn_slice = ((d + wgs - 1) / wgs + 1023) / 1024 * 1024;
+            pl->rtn_wgs = (int)((d + pl->rtn_slice - 1) / pl->rtn_slice);
+            pl->off_rtn_part = off;
+            off = align_up(off + sizeof(uint32_t) * 32768 * (size_t)pl->rtn_wgs * M, 256);
+            pl->off_rtn_total = off;
+            off = align_up(off + sizeof(uint32_t) * 32768 * (size_t)M, 256);
+        }
     }
     if (kind == MLMC_TOPK) {
         pl->off_table = off;

@@ -197,6 +197,55 @@ struct RowLoader {
     }
 };
 
+// [i0, i1) of a row by the NW waves of a workgroup, 1024 elements at a time with the next 1024 in flight; i0 is a multiple of
+// 1024.  f(keys of four times four consecutive elements of every lane, how many of each four are there).  f gets all sixteen
+// at once so that it waits for its loads before it stores anything: the waits count loads and stores alike but can only
+// rely on the loads, so a store between them would cut the loads in flight short.
+template <int DT, int NW, class F>
+__device__ __forceinline__ void stream_slice(const RowLoader<DT, true>& ld, int64_t i0, int64_t i1, uint32_t wave, uint32_t lane, F f) {
+    const int n = (int)((i1 - i0) >> 10);
+    uint32_t b0[4][4], b1[4][4];
+    auto fetch = [&](int p, uint32_t (&b)[4][4]) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) ld.load4_full(i0 + (int64_t)p * 1024 + q * 256 + lane * 4, b[q]);
+    };
+    auto use = [&](uint32_t (&b)[4][4]) {
+        const int nv[4] = {4, 4, 4, 4};
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) b[q][c] = key_of_bits(b[q][c]);
+        f(b, nv);
+    };
+    int p = (int)wave;
+    if (p < n) {
+        fetch(p, b0);
+        while (true) {   // uniform
+            const bool more1 = p + NW < n;
+            if (more1) fetch(p + NW, b1);
+            use(b0);
+            if (!more1) break;
+            p += NW;
+            const bool more0 = p + NW < n;
+            if (more0) fetch(p + NW, b0);
+            use(b1);
+            if (!more0) break;
+            p += NW;
+        }
+    }
+    if ((int)wave == n % NW && i0 + (int64_t)n * 1024 < i1) {   // the ragged rest
+        int nv[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int64_t j = i0 + (int64_t)n * 1024 + q * 256 + lane * 4;
+            nv[q] = j < i1 ? ld.load4(j, b0[q]) : 0;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) b0[q][c] = c < nv[q] ? key_of_bits(b0[q][c]) : 0u;
+        }
+        f(b0, nv);
+    }
+}
+
 // ---- Philox4x32-10 (Salmon et al., SC'11), from the published round function ----------------------
 __device__ __forceinline__ uint32_t philox_word0(uint64_t seed, uint64_t step, uint32_t worker) {
     uint32_t c0 = (uint32_t)step, c1 = (uint32_t)(step >> 32), c2 = worker, c3 = 0u;

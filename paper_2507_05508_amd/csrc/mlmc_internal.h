@@ -168,6 +168,9 @@ struct BitsArgs {
     int32_t smax_parts;      // > 0: k_bits_smax left the maxima of its workgroups (this many per row) in the row's gsum words instead of
                              // one atomic maximum in smpmax_key, which would have to be cleared by a launch before it
     unsigned long long* rtn_sums;   // RTN: [M][L][2] sums of squared residual integers, low and high 32-bit halves (zeroed per call)
+    uint32_t* rtn_part;      // RTN, long 16-bit rows: [M][workgroups][2^15] counts of the magnitudes (null: the other way)
+    uint32_t* rtn_total;     // [M][2^15]
+    int64_t rtn_slice;       // entries a workgroup counts
     double* norms;           // RTN: [M][L]
     double* norms_user;      // RTN: optional copy
     int32_t nplanes;         // planes per row in the message buffer
@@ -297,7 +300,9 @@ struct mlmc_plan_s {
         off_se_zone, off_se_nz, off_se_list, off_se_list2, off_se_tie, off_se_bsum, off_se_gsum;   // off_se_end: end of what is cleared per call (0: the plan sorts)
     int se_shift, se_wgs, se_rep;
     int64_t se_slice;
-    size_t off_rtn_sums;   // Round-to-Nearest plans
+    size_t off_rtn_sums, off_rtn_part, off_rtn_total;   // Round-to-Nearest plans
+    int rtn_wgs;              // workgroups per row that count magnitudes (0: not counted)
+    int64_t rtn_slice;
     // Side stream of the message step (MLMC_TOPK): the second read of the rows whose band was not staged runs beside the
     // assembly of the other rows' messages from the staged lists.  Created at the first call that uses it, on the device
     // current then; default priority.  Host objects only; destroyed with the plan.

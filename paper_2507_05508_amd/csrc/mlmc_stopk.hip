@@ -478,55 +478,6 @@ __device__ __forceinline__ uint32_t se_bin(uint32_t entry, uint32_t key) {   // 
     return (entry & 0xFFFFu) + ((key & ((1u << SE_CSHIFT) - 1u)) >> (entry >> 16)) + (key ? 1u : 0u);
 }
 
-// [i0, i1) of a row by the waves of a workgroup, 1024 elements at a time with the next 1024 in flight; i0 is a multiple of
-// 1024.  f(keys of four times four consecutive elements of every lane, how many of each four are there).  f gets all sixteen
-// at once so that it waits for its loads before it stores anything: the waits count loads and stores alike but can only
-// rely on the loads, so a store between them would cut the loads in flight short.
-template <int DT, class F>
-__device__ __forceinline__ void se_stream(const RowLoader<DT, true>& ld, int64_t i0, int64_t i1, uint32_t wave, uint32_t lane, F f) {
-    const int n = (int)((i1 - i0) >> 10);
-    uint32_t b0[4][4], b1[4][4];
-    auto fetch = [&](int p, uint32_t (&b)[4][4]) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) ld.load4_full(i0 + (int64_t)p * 1024 + q * 256 + lane * 4, b[q]);
-    };
-    auto use = [&](uint32_t (&b)[4][4]) {
-        const int nv[4] = {4, 4, 4, 4};
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-#pragma unroll
-            for (int c = 0; c < 4; ++c) b[q][c] = key_of_bits(b[q][c]);
-        f(b, nv);
-    };
-    int p = (int)wave;
-    if (p < n) {
-        fetch(p, b0);
-        while (true) {   // uniform
-            const bool more1 = p + SE_WAVES < n;
-            if (more1) fetch(p + SE_WAVES, b1);
-            use(b0);
-            if (!more1) break;
-            p += SE_WAVES;
-            const bool more0 = p + SE_WAVES < n;
-            if (more0) fetch(p + SE_WAVES, b0);
-            use(b1);
-            if (!more0) break;
-            p += SE_WAVES;
-        }
-    }
-    if ((int)wave == n % SE_WAVES && i0 + (int64_t)n * 1024 < i1) {   // the ragged rest
-        int nv[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int64_t j = i0 + (int64_t)n * 1024 + q * 256 + lane * 4;
-            nv[q] = j < i1 ? ld.load4(j, b0[q]) : 0;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) b0[q][c] = c < nv[q] ? key_of_bits(b0[q][c]) : 0u;
-        }
-        f(b0, nv);
-    }
-}
-
 // Coarse histogram of the sampled blocks of 1024 entries (block b is sampled when b % 2^shift == 2^shift / 2).
 template <int DT>
 __global__ __launch_bounds__(512) void k_se_coarse(StopkArgs a) {
@@ -643,7 +594,7 @@ __global__ __launch_bounds__(SE_THREADS) void k_se_count(StopkArgs a) {
     RowLoader<DT, true> ld(a.g, a.ld, a.d, row);
     const int64_t i0 = (int64_t)blockIdx.x * a.se_slice, i1 = i0 + a.se_slice < a.d ? i0 + a.se_slice : a.d;
     uint32_t maxkey = 0;
-    se_stream<DT>(ld, i0, i1, wave, lane, [&](const uint32_t (&k)[4][4], const int (&nv)[4]) {
+    stream_slice<DT, SE_WAVES>(ld, i0, i1, wave, lane, [&](const uint32_t (&k)[4][4], const int (&nv)[4]) {
         uint32_t e[4][4];
 #pragma unroll
         for (int q = 0; q < 4; ++q)
@@ -806,7 +757,7 @@ __global__ __launch_bounds__(SE_THREADS) void k_se_split(StopkArgs a) {
     uint32_t* list = a.se_list + (size_t)row * a.d;
     const int rs = a.se_rep;
     const uint32_t rlane = lane & ((1u << rs) - 1u), nobody = (uint32_t)a.L + 255u;
-    se_stream<DT>(ld, i0, i1, wave, lane, [&](const uint32_t (&k)[4][4], const int (&nv)[4]) {
+    stream_slice<DT, SE_WAVES>(ld, i0, i1, wave, lane, [&](const uint32_t (&k)[4][4], const int (&nv)[4]) {
         uint32_t cl[4][4], pos[4][4];
 #pragma unroll
         for (int q = 0; q < 4; ++q)

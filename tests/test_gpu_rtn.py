@@ -124,3 +124,34 @@ def test_rtn_random_plans_and_inputs(seed):
             assert np.array_equal(out.cpu().numpy().view(np.uint32), ref.view(np.uint32))
             assert np.array_equal(x.cpu().numpy().view(np.uint32), O.server_update(x0, ref, 0.1).view(np.uint32))
             assert bits.cpu().numpy().tolist() == [O.message_bits_rtn(B, m["level"], d) for m in want]
+
+
+def test_rtn_bf16_rows_whose_magnitudes_are_counted():
+    """16-bit plans of 2^25 entries or more count magnitudes instead of forming a code per entry: 1024 odd rows, eight distinct ones
+    (ties of a width, zeros, one value, tiny and mixed scales) in turn."""
+    d, M, B = 32_771, 1024, [0, 2, 4, 8, 16]
+    rng = np.random.default_rng(5)
+    x = rng.standard_normal((8, d)).astype(np.float32)
+    x[1] = np.tile(np.array([0.5, -1.5, 2.5, -0.5, 3.5], dtype=np.float32), d // 5 + 1)[:d]
+    x[2] = 0.0
+    x[3] = -2.0
+    x[4] *= np.float32(1e-39)
+    x[5, ::3] = 0.0
+    x[6, :1000] *= np.float32(1e30)
+    G8 = W.f32_to_bf16_bits(x)
+    Gf = np.stack([O.as_f32(G8[i]) for i in range(8)])
+    plan = P.Plan(P.MLMC_RTN, M, d, P.MLMC_BF16, B, None)
+    g = to_device(np.tile(G8, (M // 8, 1)))
+    for step in range(2):
+        print(f"rtn counted magnitudes step={step}", flush=True)
+        msg = P.mlmc_compress_rtn(plan, g, seed=3, step=step)
+        torch.cuda.synchronize()
+        assert plan.status() == 0
+        want = O.compress_rtn(Gf, B, None, 3, step)
+        norms = msg.norms.cpu().numpy()
+        for i in range(M):
+            assert np.array_equal(norms[i].view(np.uint64), np.array(want[i % 8]["norms"], dtype=np.float64).view(np.uint64)), i
+        level, planes = msg.level.cpu().numpy(), msg.planes[:8].cpu().numpy().view(np.uint64)
+        for i in range(8):
+            n = want[i]["planes"].shape[0]
+            assert level[i] == want[i]["level"] and np.array_equal(planes[i, :n], want[i]["planes"]), i
