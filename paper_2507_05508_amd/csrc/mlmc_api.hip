@@ -120,7 +120,13 @@ static void fill_topk_args(const mlmc_plan_t* pl, TopkArgs& a, const void* g, in
     a.csub = pl->csub;
     a.cchunks_per_row = pl->cchunks_per_row;
     a.sample_shift = pl->sample_shift;
-    a.staging = pl->staging;
+    // Short rows are bound by the number of launches (5 to 6 us each), so what a launch saves there is less than it costs: a
+    // zone of an exact histogram is one bucket, a few hundred candidates that one workgroup ranks without the two sliced
+    // passes, and the second read of half a million entries is cheaper than a kernel that assembles staged lists: 4 rows of
+    // 65536, 81 -> 63 us.  Longer rows keep the sliced passes for zones with many equal keys (one workgroup would take 0.24 ms
+    // for a row of 2.6e5 that is mostly zeros, as long as the passes).
+    a.alone = pl->sample_shift == 0 && pl->d <= ((int64_t)1 << 17) ? 1 : 0;
+    a.staging = pl->staging && (int64_t)pl->M * pl->d > ((int64_t)1 << 19) ? 1 : 0;
     {
         int fx = FIN_WGS;
         if (pl->M < 16) fx = 512 / pl->M < FIN_WGS_MAX ? 512 / pl->M : FIN_WGS_MAX;   // about 512 workgroups in all
@@ -251,7 +257,9 @@ static mlmc_status plan_stopk(mlmc_plan_t** plan, int M, int64_t d, int in_dtype
     pl->bm_words = ((d + 31) / 32 + 3) / 4 * 4;   // whole 16-byte groups per row
     size_t off = 0;
     auto take = [&](size_t bytes) { const size_t at = off; off = align_up(off + bytes, 256); return at; };
-    const bool bins = L <= SE_LMAX;   // more levels: a boundary in every few bins, most entries would be zone entries
+    // More levels: a boundary in every few bins, most entries would be zone entries.  Short rows: the tables of a row (0.8 MB) are not
+    // worth it, a sort of a few blocks is a handful of short launches (at 16384 entries the bins are 20 us ahead).
+    const bool bins = L <= SE_LMAX && d >= 8192;
     if (bins) {
         pl->se_rep = L <= 1024 ? 2 : (L <= 2304 ? 1 : 0);   // (L + 256) << se_rep sums fill 40 KB of LDS
         while (pl->se_shift < 4 && (d >> (pl->se_shift + 1)) >= (1 << 20)) ++pl->se_shift;

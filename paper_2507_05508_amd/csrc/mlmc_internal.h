@@ -118,6 +118,7 @@ struct TopkArgs {
     int32_t csub;            // count chunks per chunk (1 or 4)
     int32_t cchunks_per_row;
     int32_t sample_shift;    // the first histogram reads one 1024-element block out of 2^sample_shift
+    int32_t alone;           // short rows with exact histograms: k_finish<1> resolves every zone by itself
     int32_t staging;         // 1: the selection read stages the members of the (predicted) drawn band
     int32_t fin_wgs, fin_slice, fin_slices;   // zone passes: workgroups per row, least candidates per slice, most slices per zone
     int64_t ntiles;

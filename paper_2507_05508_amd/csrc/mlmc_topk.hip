@@ -1011,6 +1011,11 @@ __device__ __forceinline__ int finish_slices(const TopkArgs& a, uint32_t n) {
     const uint32_t s = (n + (uint32_t)a.fin_slice - 1u) / (uint32_t)a.fin_slice;
     return s < 1u ? 1 : (s > (uint32_t)a.fin_slices ? a.fin_slices : (int)s);
 }
+// A zone that the ranking launch resolves by itself: all of them in a short row, those with few candidates where the histogram is
+// exact (a zone is one bucket then).  A workgroup makes such a zone's histogram and ranks it faster than two sliced passes
+// start: 32 bf16 rows of 1e6 entries, 17 + 39 + 58 us (histogram, sliced pass, ranking) -> 6 + 7 + 61.
+constexpr uint32_t ALONE_MAX = 16384;
+__device__ __forceinline__ bool zone_alone(const TopkArgs& a, uint32_t n) { return a.alone || (a.sample_shift == 0 && n <= ALONE_MAX); }
 // Key range of a zone: its buckets, cut at the largest key of the row (the top zone of a small sample reaches up to
 // the highest bucket, which would otherwise stretch the zone over every exponent above the data).
 __device__ __forceinline__ void zone_key_range(const RowInfo* ri, const RowAcc* ra, int z, uint32_t& kmin, uint32_t& kmax) {
@@ -1037,7 +1042,7 @@ __device__ __forceinline__ int finish_items(const TopkArgs& a, const RowInfo* ri
         int run = 0;
         for (int z = 0; z < nz; ++z) {
             s_first[z] = run;
-            run += sliced ? finish_slices(a, s_fill[z]) : 1;
+            run += !sliced ? 1 : zone_alone(a, s_fill[z]) ? 0 : finish_slices(a, s_fill[z]);
         }
         s_first[nz] = run;
     }
@@ -1193,6 +1198,7 @@ __global__ __launch_bounds__(FN_THREADS, PHASE == 0 ? 8 : 4) void k_finish(TopkA
     auto run_item = [&](const int z, const int slice) {
     const uint32_t n = s_fill[z];
     const int S = finish_slices(a, n);
+    const bool alone = PHASE == 1 && (exact_pass || zone_alone(a, n));   // the sliced pass has no items for such zones
     const uint2* kl = a.cand + (size_t)row * (size_t)a.d + ri->zone_off[z];   // {bits, index}
 
     if (tid == 0) {
@@ -1250,14 +1256,26 @@ __global__ __launch_bounds__(FN_THREADS, PHASE == 0 ? 8 : 4) void k_finish(TopkA
     unsigned long long* zcol = a.zcol + ((size_t)row * ZMAX + z) * COLLECT_CAP;
     auto slot_of = [&](int part) -> int { return part < nthr ? s_t[part] : TMAX + z; };
 
-    if (PHASE == 1 && exact_pass) {
-        // the redo round has no launches of its own for the histogram and the sliced pass: this workgroup makes the
+    // one more in h[b], for the active lanes that want it: lanes that share the first one's word are added at once (massive
+    // ties put all of a wave on one word, and LDS atomics of many lanes on one word take a turn each)
+    auto add_one = [&](uint32_t* h, uint32_t b, bool want) {
+        const uint64_t w = __ballot(want);
+        if (w == 0) return;
+        const int first = __builtin_ctzll(w);
+        const uint32_t b0 = (uint32_t)__builtin_amdgcn_readlane((int)b, first);
+        const uint64_t same = __ballot(want && b == b0);
+        if ((int)lane == first) atomicAdd(&h[b0], (uint32_t)__popcll(same));
+        if (want && b != b0) atomicAdd(&h[b], 1u);
+    };
+    if (PHASE == 1 && alone) {
+        // the redo round and zones resolved alone have no launches of its own for the histogram and the sliced pass: this workgroup makes the
         // zone's histogram here (a zone of an exact histogram is one bucket) and resolves the zone alone
         for (int i = tid; i < FH_BINS; i += FN_THREADS) s_fh[i] = 0;
         __syncthreads();
         batched_loop<8, FN_THREADS>(0u, n, (uint32_t)tid, [&](uint32_t i) { return kl[i].x; }, [&](uint32_t, uint32_t bits) {
-            const uint32_t b = (key_of_bits(bits) - kmin) >> sh;
-            atomicAdd(&s_fh[b < (uint32_t)FH_BINS ? b : (uint32_t)FH_BINS - 1], 1u);
+            uint32_t b = (key_of_bits(bits) - kmin) >> sh;
+            b = b < (uint32_t)FH_BINS ? b : (uint32_t)FH_BINS - 1;
+            add_one(s_fh, b, true);
         });
     } else {
         const uint32_t* zh = a.zhist + ((size_t)row * ZMAX + z) * FH_BINS;
@@ -1335,7 +1353,7 @@ __global__ __launch_bounds__(FN_THREADS, PHASE == 0 ? 8 : 4) void k_finish(TopkA
     // bins hold few candidates (par_ok) they are gathered for ranking in LDS; when they hold many (massive ties,
     // e.g. bf16 keys: par_big) they are moved to the zone's overflow list, on which phase 1 runs a radix select.
     // Every other zone is resolved by one workgroup in phase 1.
-    const bool fits0 = !exact_pass && nparts * nchunks <= ZC0_CAP;   // the redo round: phase 1 only
+    const bool fits0 = (PHASE == 0 ? !exact_pass : !alone) && nparts * nchunks <= ZC0_CAP;   // the redo round: phase 1 only
     const bool par_ok = s_fast && fits0;
     const bool par_big = !s_fast && fits0;
     if (PHASE == 0 && !par_ok && !par_big) return;
@@ -1502,7 +1520,43 @@ __global__ __launch_bounds__(FN_THREADS, PHASE == 0 ? 8 : 4) void k_finish(TopkA
         //      keys, digits of 8, 8, 8, 7 bits from the top, then on the indices of the entries equal to the key.
         //      It runs on the overflow list (the thresholds' bins only) when phase 0 built one, else on the whole list ----
         const uint2* xl = par_big ? c2l : kl;
-        const uint32_t xn = par_big ? ncollect_zone : n;
+        // A zone that this workgroup resolves alone, one threshold, one key in its bin (zeros, rows of few values): the index
+        // histogram of the bin's entries is made here and the rest goes as after the sliced pass.
+        bool own_single = false;
+        if (!par_big && nthr == 1 && nchunks <= FH_BINS && count_fits) {   // uniform
+            const uint32_t tbin = s_bin[0];
+            auto bin_of = [&](uint32_t key) -> uint32_t {
+                const uint32_t b = (key - kmin) >> sh;
+                return b < (uint32_t)FH_BINS ? b : (uint32_t)FH_BINS - 1;
+            };
+            if (tid == 0) { s_q[0] = 0xFFFFFFFFu; s_eq[0] = 0u; }
+            uint32_t kmx = 0, kmn_inv = 0;
+            batched_loop<8, FN_THREADS>(0u, n, (uint32_t)tid, [&](uint32_t i) { return kl[i].x; }, [&](uint32_t, uint32_t bits) {
+                const uint32_t key = key_of_bits(bits);
+                if (bin_of(key) == tbin) {
+                    kmx = key > kmx ? key : kmx;
+                    kmn_inv = ~key > kmn_inv ? ~key : kmn_inv;
+                }
+            });
+            kmx = wave_max(kmx);
+            kmn_inv = wave_max(kmn_inv);
+            __syncthreads();
+            if (lane == 0 && kmn_inv) { atomicMax(&s_eq[0], kmx); atomicMin(&s_q[0], ~kmn_inv); }
+            __syncthreads();
+            own_single = s_q[0] == s_eq[0];
+            if (own_single) {
+                for (int i = tid; i < FH_BINS; i += FN_THREADS) s_fh[i] = 0;
+                __syncthreads();
+                batched_loop<8, FN_THREADS>(0u, n, (uint32_t)tid, [&](uint32_t i) { return kl[i]; }, [&](uint32_t, uint2 e) {
+                    const uint32_t key = key_of_bits(e.x), b = bin_of(key);
+                    add_one(s_fh, chunk_of(e.y), b == tbin);
+                    if (b != tbin) classify(b > tbin ? 0 : 1, key, e.y);
+                });
+            }
+            __syncthreads();
+            if (own_single && tid == 0) s_res[0] = s_pos[0] + 1u;   // rank among the bin's entries
+        }
+        const uint32_t xn = par_big || own_single ? ncollect_zone : n;
         if (par_big) {
             if (ra->zone_colcnt[z] != ncollect_zone || ncollect_zone > zcap) {
                 if (tid == 0) fail();
@@ -1520,13 +1574,16 @@ __global__ __launch_bounds__(FN_THREADS, PHASE == 0 ? 8 : 4) void k_finish(TopkA
         const bool chunk_bins = nchunks <= FH_BINS;
         bool single_key = false;
         uint32_t cut_chunk = (uint32_t)nchunks, cut_inside = 0;   // count chunk of the cut, entries of it inside the top k
-        if (par_big && nthr == 1) {
+        if ((par_big || own_single) && nthr == 1) {
             // key range and index histogram of the overflow list: made by the sliced launch while it copied
             const uint32_t* zi = (const uint32_t*)zcol;
             int ish = 0;
             while (((uint32_t)(a.d - 1) >> ish) >= (uint32_t)FH_BINS) ++ish;
-            for (int i = tid; i < FH_BINS; i += FN_THREADS) s_fh[i] = zi[i];
-            if (tid == 0) { s_q[0] = ~zi[FH_BINS]; s_eq[0] = zi[FH_BINS + 1]; s_ncollect = 0; }
+            if (par_big) {
+                for (int i = tid; i < FH_BINS; i += FN_THREADS) s_fh[i] = zi[i];
+                if (tid == 0) { s_q[0] = ~zi[FH_BINS]; s_eq[0] = zi[FH_BINS + 1]; }
+            }
+            if (tid == 0) s_ncollect = 0;
             __syncthreads();
             const uint32_t key1 = s_q[0];
             const bool single = key1 == s_eq[0];
@@ -1637,6 +1694,10 @@ __global__ __launch_bounds__(FN_THREADS, PHASE == 0 ? 8 : 4) void k_finish(TopkA
         }
         const bool resolved = s_any != 0;
         __syncthreads();
+        if (own_single && !resolved) {   // cannot be: the bin's entries are all in this list
+            if (tid == 0) fail();
+            return;
+        }
         if (!resolved) {
             for (int pass = 0; pass < 4; ++pass) {
                 const int shift = pass == 0 ? 23 : pass == 1 ? 15 : pass == 2 ? 7 : 0;
@@ -2357,14 +2418,15 @@ static mlmc_status launch_select(const mlmc_plan_t* pl, const TopkArgs& a, bool 
         }
         // the redo round resolves every zone in the ranking launch alone (two launches fewer to pay for when, as
         // nearly always, no row needs it)
-        if (!exact_pass) MLMC_LAUNCH(K_FHIST, st, k_fhist<<<fgrid, FN_THREADS, 0, st>>>(a, exact_pass));
+        const bool sliced = !exact_pass && !a.alone;
+        if (sliced) MLMC_LAUNCH(K_FHIST, st, k_fhist<<<fgrid, FN_THREADS, 0, st>>>(a, exact_pass));
         const dim3 rgrid(pl->L + 1 < FIN_WGS ? pl->L + 1 : FIN_WGS, pl->M);
         const int k0 = exact_pass ? K_REDO : K_FINISH, k1 = exact_pass ? K_REDO : K_FINISH1;
         if (sums) {
-            if (!exact_pass) MLMC_LAUNCH(k0, st, k_finish<true, 0><<<fgrid, FN_THREADS, 0, st>>>(a, exact_pass));
+            if (sliced) MLMC_LAUNCH(k0, st, k_finish<true, 0><<<fgrid, FN_THREADS, 0, st>>>(a, exact_pass));
             MLMC_LAUNCH(k1, st, k_finish<true, 1><<<rgrid, FN_THREADS, 0, st>>>(a, exact_pass));
         } else {
-            if (!exact_pass) MLMC_LAUNCH(k0, st, k_finish<false, 0><<<fgrid, FN_THREADS, 0, st>>>(a, exact_pass));
+            if (sliced) MLMC_LAUNCH(k0, st, k_finish<false, 0><<<fgrid, FN_THREADS, 0, st>>>(a, exact_pass));
             MLMC_LAUNCH(k1, st, k_finish<false, 1><<<rgrid, FN_THREADS, 0, st>>>(a, exact_pass));
         }
     }
@@ -2403,14 +2465,14 @@ static mlmc_status launch_compact(const mlmc_plan_t* pl, const TopkArgs& a, hipS
     // latency): the second read goes to the plan's side stream, forked from and joined to the caller's stream with
     // events, so the caller still sees one in-order stream.
     hipStream_t sw = st;
-    const bool fork = pl->M > 1 && side_stream_ready(pl);
+    const bool fork = a.staging && pl->M > 1 && side_stream_ready(pl);
     if (fork) {
         if (hipEventRecord(pl->side_fork, st) != hipSuccess || hipStreamWaitEvent(pl->side_stream, pl->side_fork, 0) != hipSuccess)
             return MLMC_EHIP;
         sw = pl->side_stream;
     }
     MLMC_LAUNCH(K_WRITE, sw, k_write<DT, VEC><<<wgrid, WR_THREADS, 0, sw>>>(a));
-    MLMC_LAUNCH(K_FILTER, st, k_filter<<<grid, FL_THREADS, fl_lds, st>>>(a));
+    if (a.staging) MLMC_LAUNCH(K_FILTER, st, k_filter<<<grid, FL_THREADS, fl_lds, st>>>(a));
     if (fork) {
         if (hipEventRecord(pl->side_join, sw) != hipSuccess || hipStreamWaitEvent(st, pl->side_join, 0) != hipSuccess)
             return MLMC_EHIP;

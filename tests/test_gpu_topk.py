@@ -440,3 +440,26 @@ def test_capacity_and_nonfinite_flags():
         n = len(want[i]["idx"])
         assert np.array_equal(u32(msg.idx)[off:off + n], want[i]["idx"])   # ordered by bit pattern
         off += n
+
+
+@pytest.mark.parametrize("what", ["zeros", "few", "normal"])
+@pytest.mark.parametrize("d,dtype", [((1 << 17) + 0, P.MLMC_F32), ((1 << 17) + 1, P.MLMC_BF16), (40_000, P.MLMC_BF16)])
+def test_zones_resolved_by_one_workgroup(what, d, dtype):
+    """Rows with exact histograms: zones that the ranking launch resolves alone (all of them up to 2^17 entries, those of up to 16384
+    candidates in longer rows) and zones that take the sliced passes, with one key or several at a threshold."""
+    rng = np.random.default_rng(d)
+    G = rng.standard_normal((3, d)).astype(np.float32)
+    if what == "zeros":
+        G[:, rng.random(d) < 0.6] = 0.0
+    if what == "few":
+        G = (np.round(G * 4) / 4).astype(np.float32)
+    if dtype == P.MLMC_BF16:
+        G = W.f32_to_bf16_bits(G)
+    ladder = [d >> (8 - l) for l in range(9)]
+    plan = P.Plan(P.MLMC_TOPK, 3, d, dtype, ladder, None)
+    g = to_device(G)
+    for step in range(2):
+        print(f"zones alone {what} d={d} dtype={dtype} step={step}", flush=True)
+        msg = P.mlmc_compress_topk(plan, g, seed=4, step=step)
+        check_topk_against_oracle(plan, G, 4, step, msg, adaptive=True)
+        assert plan.status() == 0
