@@ -33,7 +33,7 @@ def algorithmic_bytes(w, kernel, nnz_total, planes_bytes):
     produces (no re-reads, no scratch lists)."""
     s_in = 2 if w.dtype == "bf16" else 4
     in_bytes = w.M * w.d * s_in
-    if kernel in ("k_main", "k_bits_max", "k_bits_smax", "k_rtn_norms"):
+    if kernel in ("k_main", "k_bits_max", "k_bits_smax", "k_rtn_norms", "k_se_count", "k_se_split"):
         return in_bytes                                   # one read of every input element
     if kernel == "k_rs_scatter":
         return 16 * w.M * w.d                             # a sort pass: every {key, index} pair read and written
@@ -63,7 +63,9 @@ def kernel_sources_digest():
 
 
 # kernels that the library times under one name (mlmc_profile_*) and the kernel trace lists under their own
-_TRACE_NAME = {"k_main2": "k_main", "k_rtn_extract": "k_bits_extract", "k_sb_clear": "k_zero"}
+_TRACE_NAME = {"k_main2": "k_main", "k_rtn_extract": "k_bits_extract", "k_sb_clear": "k_zero", "k_agg_planes": "k_agg_bits",
+               "k_se_coarse": "k_hist", "k_se_map": "k_scan", "k_se_reduce": "k_se_scan", "k_se_norms": "k_sb_norms",
+               "k_se_mark": "k_sb_mark", "k_se_offsets": "k_sb_offsets", "k_se_write": "k_sb_write"}
 
 
 def measured_traffic(workload, kernel):

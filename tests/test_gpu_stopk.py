@@ -104,7 +104,9 @@ def _misled_sample(d, rng):
 @pytest.mark.parametrize("what,d,s,dtype,ld", [
     ("normal", 4096 * 9, 9, "f32", None),              # 4096 levels: the most without a sort
     ("normal", 4097 * 9, 9, "f32", None),              # 4097: sorted
-    ("normal", 4096, 1, "f32", None),                  # every entry a segment
+    ("normal", 4096, 1, "f32", None),                  # every entry a segment (short rows are sorted)
+    ("normal", 8192, 2, "f32", None),                  # the shortest binned row, 4096 levels
+    ("few", 8191, 2, "f32", None),
     ("normal", 300_001, 70_000, "f32", 300_003),       # segments of more than 2^16 entries, odd rows
     ("normal", 1025 * 64 - 1, 64, "f32", None),        # 1025 levels: two copies of the sums
     ("normal", 3, 2, "f32", None),
