@@ -45,7 +45,6 @@ __global__ __launch_bounds__(256, LV <= 4 ? 4 : 2) void k_rtn_norms(BitsArgs a) 
     const uint32_t ckey = a.racc[row].smpmax_key;
     if (ckey == 0u) return;   // a zero row: every residual is zero
     const double c = key_to_double(ckey), den = 2.0 * c, inv_den = __ddiv_rn(1.0, den);
-    const bool force = ckey >= 0x7F800000u;   // a row with non-finite entries: every code the long way
     RowLoader<DT, true> ld(a.g, a.ld, a.d, row);
     double mul_in[LV + 1], mul_out[LV + 1];
 #pragma unroll
@@ -81,7 +80,7 @@ __global__ __launch_bounds__(256, LV <= 4 ? 4 : 2) void k_rtn_norms(BitsArgs a) 
 #pragma unroll
         for (int t = 0; t <= LV; ++t) {
             if (t == 0 && a.F[0] == 0) continue;   // uniform: no base code
-            uint32_t differ = force ? 1u : 0u;
+            uint32_t differ = 0;
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
                 cur[i] = (uint32_t)__double2loint(__fma_rn(av[i], mul_in[t], 0x1.8p52));
@@ -91,7 +90,7 @@ __global__ __launch_bounds__(256, LV <= 4 ? 4 : 2) void k_rtn_norms(BitsArgs a) 
                 const RtnCode code = rtn_code_of(a.F[t]);
 #pragma unroll
                 for (int i = 0; i < 8; ++i)
-                    if (force || cur[i] != (uint32_t)__double2loint(__fma_rn(av[i], mul_out[t], 0x1.8p52)))
+                    if (cur[i] != (uint32_t)__double2loint(__fma_rn(av[i], mul_out[t], 0x1.8p52)))
                         cur[i] = (uint32_t)rtn_code_abs(av[i], code, c, den, inv_den);
             }
             dot(cur, cur, 2 * a.F[t] - 2, sqr[t]);
@@ -114,6 +113,24 @@ __global__ __launch_bounds__(256, LV <= 4 ? 4 : 2) void k_rtn_norms(BitsArgs a) 
     };
     auto whole = [&](int64_t at) -> bool { return at + 3 * qstride < nq - 1; };   // none of the four is the row's last (possibly partial) group
     uint32_t b[16];
+    if (ckey >= 0x7F800000u) {   // uniform: Inf and NaN are the numbers their bit patterns spell, as in c; entry by entry
+        for (; q < nq; q += qstride) {
+            uint32_t v[4];
+            const int nv = ld.load4(q * 4, v);
+#pragma unroll 1
+            for (int e = 0; e < nv; ++e) {
+                const double av = key_to_double(key_of_bits(e == 0 ? v[0] : e == 1 ? v[1] : e == 2 ? v[2] : v[3]));
+                uint32_t prev = 0;
+#pragma unroll
+                for (int t = 0; t <= LV; ++t) {
+                    const uint32_t cur = a.F[t] > 0 ? (uint32_t)rtn_code_abs(av, rtn_code_of(a.F[t]), c, den, inv_den) : 0u;
+                    sqr[t] += cur * cur;
+                    if (t > 0) prod[t] += cur * prev;
+                    prev = cur;
+                }
+            }
+        }
+    }
     for (; whole(q); q += 4 * qstride) {
         fetch(q, b);
         batch(b);

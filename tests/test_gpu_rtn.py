@@ -155,3 +155,53 @@ def test_rtn_bf16_rows_whose_magnitudes_are_counted():
         for i in range(8):
             n = want[i]["planes"].shape[0]
             assert level[i] == want[i]["level"] and np.array_equal(planes[i, :n], want[i]["planes"]), i
+
+
+@pytest.mark.parametrize("dtype,M,d,B", [
+    ("f32", 3, 4096 + 77, [0, 2, 4, 8, 16]), ("f32", 3, 100_003, [3, 5, 9]), ("bf16", 3, 4096 + 77, [0, 2, 4, 8, 16]),
+    ("bf16", 9, (1 << 22) + 5, [0, 2, 4, 8, 16]),   # magnitudes counted
+])
+def test_rtn_rows_with_non_finite_entries(dtype, M, d, B):
+    """Inf and NaN are ordered, and read, by their bit pattern: the largest pattern is c, every entry the number its exponent and
+    fraction bits spell.  One NaN; Inf below a NaN; Inf alone."""
+    rng = np.random.default_rng(d)
+    G = (rng.standard_normal((3, d)) * np.exp(rng.uniform(-20, 86, size=(3, d)))).astype(np.float32)
+    key = G.view(np.uint32)
+    key[0, 7] = 0xFFC00000
+    key[1, 5], key[1, d - 1] = 0x7F800000, 0x7FE00000
+    key[2, 11] = 0xFF800000
+    if dtype == "bf16":
+        key &= np.uint32(0xFFFF0000)
+        G = (key >> np.uint32(16)).astype(np.uint16)
+    G = np.tile(G, (M // 3, 1))
+    plan = P.Plan(P.MLMC_RTN, M, d, P.MLMC_F32 if dtype == "f32" else P.MLMC_BF16, B, None)
+    g = to_device(G)
+    want = []
+    for i in range(3):
+        mag = (key[i] & np.uint32(0x7FFFFFFF)).astype(np.int64)
+        E = mag >> 23
+        a = np.ldexp(np.where(E > 0, (mag & 0x7FFFFF) | 0x800000, mag).astype(np.float64), np.maximum(E, 1).astype(np.int32) - 150)
+        v, c = np.where(key[i] >> 31 != 0, -a, a), float(a.max())
+        norms = []
+        for l in range(1, len(B)):
+            k = O.rtn_residual_ints(v, c, B[l - 1], B[l])
+            DD = ((1 << B[l]) - 1) * ((1 << B[l - 1]) - 1 if B[l - 1] else 1)
+            norms.append(2.0 * c / float(DD) * np.sqrt(float(int(np.dot(k, k)))))
+        want.append((v, c, norms, int(mag.max())))
+    nr = P.mlmc_level_norms(plan, g).cpu().numpy()
+    for step in range(2):
+        print(f"rtn non-finite {dtype} M={M} d={d} step={step}", flush=True)
+        msg = P.mlmc_compress_rtn(plan, g, seed=6, step=step)
+        torch.cuda.synchronize()
+        assert plan.status() == P.MLMC_DEV_NONFINITE
+        got, scale = msg.norms.cpu().numpy(), msg.scale_exp.cpu().numpy().view(np.uint32)
+        planes = msg.planes[:3].cpu().numpy().view(np.uint64)
+        for i in range(M):
+            v, c, norms, ckey = want[i % 3]
+            assert np.array_equal(got[i], norms) and np.array_equal(nr[i], norms), (i, got[i], nr[i], norms)
+            level = O.draw_level(O.adaptive_p(norms), 6, step, i)
+            assert int(msg.level[i]) == level and int(scale[i, 0]) == ckey
+            if i < 3:
+                widths = [b for b in (B[0], B[level - 1] if level > 1 else 0, B[level]) if b]
+                ref = np.stack(sum((O._rtn_code_planes(O.rtn_codes(v, c, b), b) for b in widths), []))
+                assert np.array_equal(planes[i, :len(ref)], ref), i
