@@ -570,13 +570,19 @@ __global__ __launch_bounds__(1024) void k_se_map(StopkArgs a) {
     for (uint32_t b0 = tid & ~63u; b0 < (uint32_t)SE_CB; b0 += 1024) {   // a wave takes 64 buckets: small ones a lane each, large ones together
         const uint32_t e = s_map[b0 + lane], sh = e >> 16, n = 1u << (SE_CSHIFT - sh);
         if (n <= 8u)
-            for (uint32_t i = 0; i < n; ++i) info[1 + (e & 0xFFFFu) + i] = make_uint2(((b0 + lane) << SE_CSHIFT) + (i << sh), sh);
+            for (uint32_t i = 0; i < n; ++i) {
+                const uint32_t key = ((b0 + lane) << SE_CSHIFT) + (i << sh);
+                info[1 + (e & 0xFFFFu) + i] = make_uint2(key ? key : 1u, sh);   // zeros are in bin 0: a threshold at this bin leaves them out
+            }
         uint64_t big = __ballot(n > 8u);
         while (big) {   // uniform
             const int l = __builtin_ctzll(big);
             big &= big - 1;
             const uint32_t eb = (uint32_t)__builtin_amdgcn_readlane((int)e, l), shb = eb >> 16, nb = 1u << (SE_CSHIFT - shb);
-            for (uint32_t i = lane; i < nb; i += 64) info[1 + (eb & 0xFFFFu) + i] = make_uint2(((b0 + (uint32_t)l) << SE_CSHIFT) + (i << shb), shb);
+            for (uint32_t i = lane; i < nb; i += 64) {
+                const uint32_t key = ((b0 + (uint32_t)l) << SE_CSHIFT) + (i << shb);
+                info[1 + (eb & 0xFFFFu) + i] = make_uint2(key ? key : 1u, shb);
+            }
         }
     }
 }

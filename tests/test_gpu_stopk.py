@@ -125,3 +125,17 @@ def test_stopk_edges_of_the_binned_path(what, d, s, dtype, ld):
         G = W.f32_to_bf16_bits(G)
     print(f"stopk binned {what} d={d} s={s} {dtype} ld={ld}", flush=True)
     _run_and_check(G, s, dtype=dt, steps=(0, 1), ld=ld)
+
+
+@pytest.mark.parametrize("d,s,nnz,smallest", [(8192, 8191, 8191, 7), (9000, 4000, 8000, 1), (9000, 2000, 8000, 15), (40_000, 39, 39 * 1000, 3)])
+def test_stopk_boundary_between_the_smallest_entries_and_zeros(d, s, nnz, smallest):
+    """The non-zero entries fill whole segments, the least of them among the smallest subnormals, with zeros behind: no zero
+    belongs to the last segment that has a norm."""
+    rng = np.random.default_rng(d + s)
+    G = np.zeros((2, d), dtype=np.float32)
+    for r in range(2):
+        at = rng.permutation(d)[:nnz]
+        G[r, at] = (rng.standard_normal(nnz) + 3.0).astype(np.float32)
+        G[r, at[: 2 - r]] = np.array([smallest, 20_000_000], dtype=np.uint32).view(np.float32)[: 2 - r]
+    print(f"stopk subnormals before zeros d={d} s={s}", flush=True)
+    _run_and_check(G, s, steps=(0, 1, 2, 3))
