@@ -280,7 +280,7 @@ static mlmc_status plan_stopk(mlmc_plan_t** plan, int M, int64_t d, int in_dtype
         pl->off_se_coarse = take(sizeof(uint32_t) * 8192 * (size_t)M);
         pl->off_se_big = take(sizeof(uint64_t) * SE_WORDS * (size_t)L * M);
         pl->off_se_gsum = take(sizeof(uint64_t) * 2 * (size_t)(L + 256) * M);
-        pl->off_se_nz = take(sizeof(uint32_t) * 2 * (size_t)M);
+        pl->off_se_nz = take(sizeof(uint32_t) * SE_NZ * (size_t)M);
         pl->off_se_end = off;
         pl->off_se_bsum = take(sizeof(uint32_t) * ((SE_BINS + 255) / 256) * (size_t)M);
         pl->off_se_map = take(sizeof(uint32_t) * 8192 * (size_t)M);
@@ -289,11 +289,18 @@ static mlmc_status plan_stopk(mlmc_plan_t** plan, int M, int64_t d, int in_dtype
         pl->off_se_part = take(sizeof(uint32_t) * SE_BINS * (size_t)pl->se_wgs * M);
         pl->off_se_total = take(sizeof(uint32_t) * SE_BINS * (size_t)M);
         pl->off_se_class = take(sizeof(uint16_t) * SE_BINS * (size_t)M);
-        pl->off_se_gtab = take(sizeof(uint32_t) * (SE_LMAX + 256) * (size_t)M);
+        pl->off_se_gtab = take(sizeof(uint32_t) * (size_t)(L + 256) * M);
         pl->off_se_thr = take(sizeof(uint2) * (size_t)(L + 1) * M);
-        pl->off_se_zone = take(sizeof(SZone) * SE_LMAX * (size_t)M);
+        pl->off_se_zone = take(sizeof(SZone) * (size_t)L * M);
+        // zones of more than 2048 entries; of more than SE_ZBIG; slices of 65536 entries of the latter
+        pl->se_mids = (int)(d / 2049 + 1);
+        pl->se_bigs = (int)(d / (SE_ZBIG + 1) + 1);
+        pl->se_items = (int)(d / 32768 + 1);
+        pl->off_se_mid = take(sizeof(uint32_t) * (size_t)pl->se_mids * M);
+        pl->off_se_bigz = take(sizeof(uint32_t) * (size_t)pl->se_bigs * M);
+        pl->off_se_item = take(sizeof(uint2) * (size_t)pl->se_items * M);
         pl->off_se_list = take(sizeof(uint32_t) * (size_t)d * M);
-        pl->off_se_list2 = take(sizeof(uint32_t) * (size_t)d * M);
+        if (d > SE_ZBIG) pl->off_se_list2 = take(sizeof(uint32_t) * (size_t)d * M);
         pl->off_se_tie = take(sizeof(uint2) * (size_t)pl->ntiles * M);
     }
     pl->off_bitmap = off;
@@ -360,6 +367,12 @@ static void fill_stopk_args(const mlmc_plan_t* pl, StopkArgs& a, const void* g, 
         a.se_bsum = (uint32_t*)(w + pl->off_se_bsum);
         a.se_gsum = (unsigned long long*)(w + pl->off_se_gsum);
         a.se_nz = (uint32_t*)(w + pl->off_se_nz);
+        a.se_mid = (uint32_t*)(w + pl->off_se_mid);
+        a.se_bigz = (uint32_t*)(w + pl->off_se_bigz);
+        a.se_item = (uint2*)(w + pl->off_se_item);
+        a.se_mids = pl->se_mids;
+        a.se_bigs = pl->se_bigs;
+        a.se_items = pl->se_items;
         a.se_list = (uint32_t*)(w + pl->off_se_list);
         a.se_list2 = (uint32_t*)(w + pl->off_se_list2);
         a.se_tie = (uint2*)(w + pl->off_se_tie);

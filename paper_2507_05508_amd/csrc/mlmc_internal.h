@@ -198,6 +198,8 @@ struct SRow {           // per row: the drawn segment
 constexpr int SE_LMAX = 4096;
 constexpr int SE_BINS = 32000;          // bins of a row's exact histogram: with the coarse map they fill a CU's LDS
 constexpr int SE_WORDS = 20;            // 32-bit words of a band's sum of squares (2^-298 units), each in a 64-bit counter
+constexpr int SE_ZBIG = 81920;          // zones of more entries are resolved by several workgroups
+constexpr int SE_NZ = 8;                // words of a row's zone counters
 constexpr uint32_t SE_ALL = 0xFFFFFFFFu;  // threshold {key, SE_ALL}: every entry equal to the key is inside
 struct SZone {          // a bin that holds band boundaries
     uint32_t cum, n;        // entries of the row above it, entries in it
@@ -243,14 +245,18 @@ struct StopkArgs {
     uint32_t* se_part;       // [M][se_wgs][SE_BINS] counts of a workgroup, then those of the workgroups before it
     uint32_t* se_total;      // [M][SE_BINS]
     uint16_t* se_class;      // [M][SE_BINS]
-    uint32_t* se_gtab;       // [M][SE_LMAX + 256] exponent << 16 | band of a sum group
+    uint32_t* se_gtab;       // [M][L + 256] exponent << 16 | band of a sum group
     uint2* se_thr;           // [M][L + 1] thresholds of the boundaries: {key, how many of its equals are inside}
-    SZone* se_zone;          // [M][SE_LMAX]
+    SZone* se_zone;          // [M][L]
     unsigned long long* se_gsum;  // [M][L + 256][2] sums of the groups, low and high 32-bit halves (cleared per call)
-    uint32_t* se_nz;         // [M][2] zones, their entries (cleared per call)
+    uint32_t* se_nz;         // [M][SE_NZ] zones, their entries, zones of se_mid and of se_bigz, items of se_item (cleared per call)
+    uint32_t* se_mid;        // [M][se_mids] zones of more than 2048 entries that one workgroup resolves
+    uint32_t* se_bigz;       // [M][se_bigs] zones of more than SE_ZBIG entries
+    uint2* se_item;          // [M][se_items] their slices: {zone, slice}
+    int32_t se_mids, se_bigs, se_items;
     uint32_t* se_bsum;       // [M][SE_BINS / 256] totals of 256 bins each
     uint32_t* se_list;       // [M][d] keys of the zones
-    uint32_t* se_list2;      // [M][d]
+    uint32_t* se_list2;      // [M][d] counts of the zones of se_bigz, at the places of their lists (rows longer than SE_ZBIG)
     uint2* se_tie;           // [M][ntiles] entries equal to the two thresholds of the drawn segment, where they are split
 };
 
@@ -298,8 +304,8 @@ struct mlmc_plan_s {
     int64_t bm_words;
     size_t off_pa, off_pb, off_counts, off_bitmap, off_tilecnt, off_clear_end, off_srow, off_bintot;
     size_t off_se_coarse, off_se_big, off_se_end, off_se_map, off_se_info, off_se_nbins, off_se_part, off_se_total, off_se_class, off_se_gtab, off_se_thr,
-        off_se_zone, off_se_nz, off_se_list, off_se_list2, off_se_tie, off_se_bsum, off_se_gsum;   // off_se_end: end of what is cleared per call (0: the plan sorts)
-    int se_shift, se_wgs, se_rep;
+        off_se_zone, off_se_nz, off_se_list, off_se_list2, off_se_tie, off_se_bsum, off_se_gsum, off_se_mid, off_se_bigz, off_se_item;   // off_se_end: end of what is cleared per call (0: the plan sorts)
+    int se_shift, se_wgs, se_rep, se_mids, se_bigs, se_items;
     int64_t se_slice;
     size_t off_rtn_sums, off_rtn_part, off_rtn_total;   // Round-to-Nearest plans
     int rtn_wgs;              // workgroups per row that count magnitudes (0: not counted)

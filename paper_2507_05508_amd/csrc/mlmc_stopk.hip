@@ -458,8 +458,9 @@ static mlmc_status launch_stopk(const mlmc_plan_t* pl, const StopkArgs& a, bool 
 //                 entries have one key, in which case the boundaries' parts follow from the counts
 //   k_se_split    second read: squares of region entries are added per (band, exponent) in LDS, keys of zone entries go to
 //                 their zones' lists, whose places are exact (the counts are)
-//   k_se_zone     per zone: keys in order, thresholds of its boundaries (key, how many of the equal keys are inside), sums of
-//                 its parts
+//   k_se_zone     per zone of few entries: keys in order, thresholds of its boundaries (key, how many of the equal keys are
+//                 inside), sums of its parts
+//   k_se_wide     the same for zones of many entries (repeated keys; rows that the sample misjudged), by counts of their keys
 //   k_se_norms / k_sb_draw   Delta_l, level
 //   k_se_mark / k_se_offsets / k_se_write   third read: bitmap of the drawn segment and its message; entries equal to a
 //                 threshold whose equal keys are split are told apart by their rank in index order
@@ -472,10 +473,32 @@ constexpr int SE_THREADS = 1024;
 constexpr int SE_WAVES = SE_THREADS / 64;
 constexpr uint32_t SE_ZONE = 0x8000u;   // class of a bin: sum group, or SE_ZONE | zone
 constexpr int SE_ZCAP = 2048;           // keys that a zone's workgroup puts in order in LDS
+// Zones of more entries: first counts of 2^SE_ZBITS sub-bins, then of the (at most 16) keys of every sub-bin that holds boundaries.
+// Up to SE_ZBIG entries one workgroup does both in LDS; more are taken in slices of SE_ZSLICE by many, the counts in the
+// zone's place of the second list: 2^SE_ZBITS + 16 SE_LMAX words and one for the ticket.
+constexpr int SE_ZBITS = 14;
+constexpr uint32_t SE_ZSUB = 1u << SE_ZBITS, SE_ZSLICE = 65536;   // a slice's squares (below 2^48 each) fit a 64-bit sum
+static_assert(SE_CSHIFT - SE_ZBITS <= 4 && SE_ZBIG == (1 << SE_ZBITS) + 16 * SE_LMAX, "place of a zone's counts");
 static_assert(SE_LMAX <= 0x8000 && SE_LMAX + 256 < 0x8000, "class field");
 
 __device__ __forceinline__ uint32_t se_bin(uint32_t entry, uint32_t key) {   // entry: of the key's coarse bucket, base | shift << 16
     return (entry & 0xFFFFu) + ((key & ((1u << SE_CSHIFT) - 1u)) >> (entry >> 16)) + (key ? 1u : 0u);
+}
+
+// One more in h[b] for the active lanes that want it.  LDS atomics of many lanes on one word take a turn each (about three
+// clocks): where many share the first one's word, and then the next one's, they are added at once.
+__device__ __forceinline__ void se_count_peeled(uint32_t* h, uint32_t b, bool want) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const uint64_t w = __ballot(want);
+        if (w == 0) return;
+        const uint32_t b0 = (uint32_t)__builtin_amdgcn_readlane((int)b, __builtin_ctzll(w));
+        const uint64_t same = __ballot(want && b == b0);
+        if (__popcll(same) < 8) break;   // uniform
+        if (lane_id() == (uint32_t)__builtin_ctzll(w)) atomicAdd(&h[b0], (uint32_t)__popcll(same));
+        want = want && b != b0;
+    }
+    if (want) atomicAdd(&h[b], 1u);
 }
 
 // Coarse histogram of the sampled blocks of 1024 entries (block b is sampled when b % 2^shift == 2^shift / 2).
@@ -499,11 +522,23 @@ __global__ __launch_bounds__(512) void k_se_coarse(StopkArgs a) {
 #pragma unroll
             for (int q = 0; q < 4; ++q) nv[q] = ld.load4(base + q * 256 + lane * 4, b[q]);
         }
+        uint32_t other = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                b[q][c] = c < nv[q] ? key_of_bits(b[q][c]) >> SE_CSHIFT : SE_CB;
+                other |= b[q][c] ^ b[0][0];
+            }
+        if (other == 0 && nv[0] == 4) {   // (all four are whole: a missing entry is unlike any other)
+            atomicAdd(&s_h[b[0][0]], 16u);   // LDS atomics of many lanes on one word take turns: rows of one value
+            continue;
+        }
 #pragma unroll
         for (int q = 0; q < 4; ++q)
 #pragma unroll
             for (int c = 0; c < 4; ++c)
-                if (c < nv[q]) atomicAdd(&s_h[key_of_bits(b[q][c]) >> SE_CSHIFT], 1u);
+                if (b[q][c] < (uint32_t)SE_CB) atomicAdd(&s_h[b[q][c]], 1u);
     }
     __syncthreads();
     uint32_t* h = a.se_coarse + (size_t)row * SE_CB;
@@ -670,7 +705,8 @@ __device__ __forceinline__ int se_exp_shift(uint32_t key) {   // of the square o
 // Per 256 bins: their ranks in descending order of their keys, classes, zones, thresholds that fall on bin edges.
 __global__ __launch_bounds__(256) void k_se_scan(StopkArgs a) {
     __shared__ uint32_t s_scan[256 / 64 + 1];
-    __shared__ uint32_t s_z0, s_off0;
+    __shared__ uint32_t s_z0, s_off0, s_many;
+    __shared__ uint4 s_key[256];   // one-key bins with many boundaries: key, entries above, entries, boundaries
     const int row = blockIdx.y, blk = blockIdx.x, tid = threadIdx.x;
     const int nbins = (int)a.se_nbins[row], nblk = (nbins + 255) / 256;
     if (blk >= nblk) return;
@@ -694,16 +730,30 @@ __global__ __launch_bounds__(256) void k_se_scan(StopkArgs a) {
     const uint32_t z = block_excl_scan<256>(zone ? 1u : 0u, s_scan, zones);
     const uint32_t zoff = block_excl_scan<256>(zone ? n : 0u, s_scan, zents);
     if (tid == 0 && zones) {
-        s_z0 = atomicAdd(&a.se_nz[2 * row], zones);
-        s_off0 = atomicAdd(&a.se_nz[2 * row + 1], zents);
+        s_z0 = atomicAdd(&a.se_nz[SE_NZ * row], zones);
+        s_off0 = atomicAdd(&a.se_nz[SE_NZ * row + 1], zents);
     }
+    if (tid == 0) s_many = 0;
     __syncthreads();
     uint2* thr = a.se_thr + (size_t)row * (a.L + 1);
+    // parts u0, u0 + step, ... of a key's entries: the first t s - above of them (by index) are inside boundary t
+    auto key_parts = [&](uint32_t key, uint32_t above, uint32_t n, uint32_t nb, uint32_t u0, uint32_t step) {
+        const uint64_t sq = sig_square(key);
+        const int sh = se_exp_shift(key);
+        const uint32_t t0 = above / s + 1u;
+        for (uint32_t u = u0; u <= nb; u += step) {
+            const uint32_t r0 = u ? (t0 + u - 1u) * s - above : 0u, r1 = u < nb ? (t0 + u) * s - above : n;
+            unsigned long long* wide = a.se_big + ((size_t)row * a.L + (t0 + u - 1u)) * SE_WORDS;
+            se_add(wide, (sq & 0xFFFFFFFFull) * (r1 - r0), sh);
+            se_add(wide, (sq >> 32) * (r1 - r0), sh + 32);
+            if (u < nb) thr[t0 + u] = make_uint2(key, r1);
+        }
+    };
     uint32_t code = (uint32_t)a.L + 255u;   // sums nobody reads: an empty bin, or one key with boundaries inside
     if (n && nb == 0) {
         // (255 - exponent) + band: one step at least whenever the exponent or the band changes
         code = 255u - (in.x >> 23) + (t0 - 1u);
-        a.se_gtab[(size_t)row * (SE_LMAX + 256) + code] = (in.x >> 23) << 16 | (t0 - 1u);   // exponent, band (from 0)
+        a.se_gtab[(size_t)row * (a.L + 256) + code] = (in.x >> 23) << 16 | (t0 - 1u);   // exponent, band (from 0)
     } else if (zone) {
         code = SE_ZONE | (s_z0 + z);   // a zone holds a boundary: fewer than L <= SE_LMAX zones
         SZone zr;
@@ -715,20 +765,20 @@ __global__ __launch_bounds__(256) void k_se_scan(StopkArgs a) {
         zr.nb = nb;
         zr.off = s_off0 + zoff;
         zr.bin = (uint32_t)bin;
-        a.se_zone[(size_t)row * SE_LMAX + s_z0 + z] = zr;
-    } else if (nb) {
-        // the first t s - cum of the equal keys (by index) are inside boundary t
-        const uint64_t sq = sig_square(in.x);
-        const int sh = se_exp_shift(in.x);
-        uint32_t r0 = 0;
-        for (uint32_t u = 0; u <= nb; ++u) {
-            const uint32_t r1 = u < nb ? (t0 + u) * s - cum : n;
-            unsigned long long* wide = a.se_big + ((size_t)row * a.L + (t0 + u - 1u)) * SE_WORDS;
-            se_add(wide, (sq & 0xFFFFFFFFull) * (r1 - r0), sh);
-            se_add(wide, (sq >> 32) * (r1 - r0), sh + 32);
-            if (u < nb) thr[t0 + u] = make_uint2(in.x, r1);
-            r0 = r1;
+        a.se_zone[(size_t)row * a.L + s_z0 + z] = zr;
+        if (n > (uint32_t)SE_ZCAP) {   // work of k_se_wide
+            uint32_t* nz = a.se_nz + SE_NZ * row;
+            if (n <= (uint32_t)SE_ZBIG) {
+                a.se_mid[(size_t)row * a.se_mids + atomicAdd(&nz[2], 1u)] = s_z0 + z;
+            } else {
+                a.se_bigz[(size_t)row * a.se_bigs + atomicAdd(&nz[3], 1u)] = s_z0 + z;
+                const uint32_t ns = (n + SE_ZSLICE - 1u) / SE_ZSLICE, at = atomicAdd(&nz[4], ns);
+                for (uint32_t i = 0; i < ns; ++i) a.se_item[(size_t)row * a.se_items + at + i] = make_uint2(s_z0 + z, i);
+            }
         }
+    } else if (nb) {
+        if (nb <= 32u) key_parts(in.x, cum, n, nb, 0u, 1u);
+        else s_key[atomicAdd(&s_many, 1u)] = make_uint4(in.x, cum, n, nb);
     }
     if (n && (cum + n) % s == 0u && (cum + n) / s <= last_t) thr[(cum + n) / s] = make_uint2(in.x, SE_ALL);   // a boundary at the bin's lower edge
     if (bin < nbins) a.se_class[(size_t)row * SE_BINS + bin] = (uint16_t)code;
@@ -736,6 +786,9 @@ __global__ __launch_bounds__(256) void k_se_scan(StopkArgs a) {
         thr[0] = make_uint2(0xFFFFFFFFu, 0u);
         thr[a.L] = make_uint2(0u, SE_ALL);
     }
+    __syncthreads();
+    for (uint32_t i = 0; i < s_many; ++i)   // (zeros; a row of one value has every boundary here)
+        key_parts(s_key[i].x, s_key[i].y, s_key[i].z, s_key[i].w, (uint32_t)tid, 256u);
 }
 
 // Second read: sums of the regions, lists of the zones.
@@ -752,10 +805,16 @@ __global__ __launch_bounds__(SE_THREADS) void k_se_split(StopkArgs a) {
     for (int i = tid; i < SE_BINS / 8; i += SE_THREADS) ((uint4*)s_class)[i] = ((const uint4*)(a.se_class + (size_t)row * SE_BINS))[i];
     for (int i = tid; i < SE_SUMS_BYTES / 8; i += SE_THREADS) s_sum[i] = 0ull;
     {
-        const int nz = (int)a.se_nz[2 * row];
+        const int nz = (int)a.se_nz[SE_NZ * row];
         const uint32_t* part = a.se_part + ((size_t)row * a.se_wgs + blockIdx.x) * SE_BINS;
-        const SZone* zr = a.se_zone + (size_t)row * SE_LMAX;
+        const SZone* zr = a.se_zone + (size_t)row * a.L;
         for (int z = tid; z < nz; z += SE_THREADS) s_cur[z] = zr[z].off + part[zr[z].bin];
+        // the counts that k_se_wide adds to start at zero
+        const uint32_t nbig = a.se_nz[SE_NZ * row + 3];
+        for (uint32_t b = 0; b < nbig; ++b) {
+            uint32_t* tab = a.se_list2 + (size_t)row * a.d + zr[a.se_bigz[(size_t)row * a.se_bigs + b]].off;
+            for (uint32_t i = blockIdx.x * SE_THREADS + tid; i <= (uint32_t)SE_ZBIG; i += gridDim.x * SE_THREADS) tab[i] = 0;
+        }
     }
     __syncthreads();
     RowLoader<DT, true> ld(a.g, a.ld, a.d, row);
@@ -807,17 +866,16 @@ __global__ __launch_bounds__(SE_THREADS) void k_se_split(StopkArgs a) {
     }
 }
 
-// One workgroup per zone.  Keys of a zone differ in their low `shift` bits only.  Up to SE_ZCAP keys are put in order in LDS:
-// 256 buckets of the zone's key range, then a thread orders its bucket by insertion (a few keys); where a bucket holds many,
-// all keys by a bitonic sort, which takes three times as long.  More keys are ordered by a radix sort between the two lists in memory (a row that the sample misjudged: linear in the number of
-// keys, one workgroup), unless they are all the same.
+// One workgroup per zone of up to SE_ZCAP entries.  Keys of a zone differ in their low `shift` bits only.  They are put in order in
+// LDS: 256 buckets of the zone's key range, then a thread orders its bucket by insertion (a few keys); where a bucket holds many,
+// all keys by a bitonic sort, which takes three times as long.
 constexpr int SZ_THREADS = 256;
 constexpr uint32_t SZ_FEW = 32;
 __global__ __launch_bounds__(SZ_THREADS) void k_se_zone(StopkArgs a) {
     __shared__ uint32_t s_k[SE_ZCAP];
     __shared__ uint32_t s_h[256];
     __shared__ uint32_t s_scan[SZ_THREADS / 64 + 1];
-    __shared__ uint32_t s_min, s_max;
+    __shared__ uint32_t s_crowd;
     const int row = blockIdx.y, tid = threadIdx.x;
     if ((int)blockIdx.x >= a.L - 1) {   // the last workgroups of a row: sums of the regions to their bands
         const int g = ((int)blockIdx.x - (a.L - 1)) * SZ_THREADS + tid;
@@ -825,7 +883,7 @@ __global__ __launch_bounds__(SZ_THREADS) void k_se_zone(StopkArgs a) {
             const unsigned long long* gs = a.se_gsum + ((size_t)row * (a.L + 256) + g) * 2;
             const unsigned long long lo = gs[0], hi = gs[1];
             if (lo | hi) {
-                const uint32_t t = a.se_gtab[(size_t)row * (SE_LMAX + 256) + g];
+                const uint32_t t = a.se_gtab[(size_t)row * (a.L + 256) + g];
                 const int sh = se_exp_shift((t >> 16) << 23);
                 unsigned long long* wide = a.se_big + ((size_t)row * a.L + (t & 0xFFFFu)) * SE_WORDS;
                 se_add(wide, lo, sh);
@@ -834,14 +892,13 @@ __global__ __launch_bounds__(SZ_THREADS) void k_se_zone(StopkArgs a) {
         }
         return;
     }
-    if (blockIdx.x >= a.se_nz[2 * row]) return;
+    if (blockIdx.x >= a.se_nz[SE_NZ * row]) return;
     const uint32_t lane = lane_id(), wave = (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6);
-    const SZone zn = a.se_zone[(size_t)row * SE_LMAX + blockIdx.x];
+    const SZone zn = a.se_zone[(size_t)row * a.L + blockIdx.x];
     const uint32_t n = zn.n;
-    uint32_t* src = a.se_list + (size_t)row * a.d + zn.off;
-    const uint32_t* sorted = nullptr;   // descending; null: in s_k
-    bool equal = false;
-    if (n <= (uint32_t)SE_ZCAP) {
+    if (n > (uint32_t)SE_ZCAP) return;   // k_se_wide
+    const uint32_t* src = a.se_list + (size_t)row * a.d + zn.off;
+    {
         constexpr int PER = SE_ZCAP / SZ_THREADS;
         const uint32_t dsh = zn.shift > 8u ? zn.shift - 8u : 0u;
         auto digit = [&](uint32_t k) -> uint32_t { return 255u - ((k - zn.lo) >> dsh); };
@@ -852,7 +909,7 @@ __global__ __launch_bounds__(SZ_THREADS) void k_se_zone(StopkArgs a) {
             my[i] = at < n ? src[at] : 0u;   // a zone holds no zeros
         }
         s_h[tid] = 0;
-        if (tid == 0) s_max = 0;
+        if (tid == 0) s_crowd = 0;
         __syncthreads();
 #pragma unroll
         for (int i = 0; i < PER; ++i)
@@ -862,9 +919,9 @@ __global__ __launch_bounds__(SZ_THREADS) void k_se_zone(StopkArgs a) {
         uint32_t all;
         const uint32_t start = block_excl_scan<SZ_THREADS>(c, s_scan, all);
         s_h[tid] = start;
-        if (c > SZ_FEW) s_max = 1u;
+        if (c > SZ_FEW) s_crowd = 1u;
         __syncthreads();
-        if (s_max == 0u) {   // uniform
+        if (s_crowd == 0u) {   // uniform
 #pragma unroll
             for (int i = 0; i < PER; ++i)
                 if (my[i]) s_k[atomicAdd(&s_h[digit(my[i])], 1u)] = my[i];
@@ -877,125 +934,299 @@ __global__ __launch_bounds__(SZ_THREADS) void k_se_zone(StopkArgs a) {
             }
             __syncthreads();
         } else {
-        uint32_t np2 = 64;
-        while (np2 < n) np2 <<= 1;
+            uint32_t np2 = 64, other = 0;
+            while (np2 < n) np2 <<= 1;
 #pragma unroll
-        for (int i = 0; i < PER; ++i)
-            if ((uint32_t)(tid + i * SZ_THREADS) < np2) s_k[tid + i * SZ_THREADS] = my[i];
-        __syncthreads();
-        for (uint32_t k = 2; k <= np2; k <<= 1) {
-            for (uint32_t j = k >> 1; j > 0; j >>= 1) {
-                for (uint32_t p = tid; p < (np2 >> 1); p += SZ_THREADS) {
-                    const uint32_t i = ((p & ~(j - 1u)) << 1) | (p & (j - 1u)), l = i | j;
-                    const uint32_t x = s_k[i], y = s_k[l];
-                    if ((x < y) == ((i & k) == 0u)) { s_k[i] = y; s_k[l] = x; }
-                }
-                __syncthreads();
-            }
-        }
-        }
-    } else {
-        uint32_t mn = 0xFFFFFFFFu, mx = 0;
-        for (uint32_t i = tid; i < n; i += SZ_THREADS) {
-            const uint32_t k = src[i];
-            mn = k < mn ? k : mn;
-            mx = k > mx ? k : mx;
-        }
-        if (tid == 0) { s_min = 0xFFFFFFFFu; s_max = 0; }
-        __syncthreads();
-        atomicMin(&s_min, mn);
-        atomicMax(&s_max, mx);
-        __syncthreads();
-        equal = s_min == s_max;
-        sorted = src;
-        if (!equal) {
-            // stable passes of eight bits, descending; wave w owns a quarter of the list, in order
-            uint32_t (*h)[256] = (uint32_t (*)[256])s_k;   // [4 waves][256]: counts, then places
-            uint32_t* in = src;
-            uint32_t* out = a.se_list2 + (size_t)row * a.d + zn.off;
-            const uint32_t per = (n + SZ_THREADS - 1) / SZ_THREADS * 64;   // whole groups of 64 per wave
-            const uint32_t w0 = wave * per < n ? wave * per : n, w1 = w0 + per < n ? w0 + per : n;
-            for (uint32_t sh = 0; sh < zn.shift; sh += 8) {
-                __syncthreads();   // the keys a wave reads were written by others
-                for (int i = tid; i < 4 * 256; i += SZ_THREADS) s_k[i] = 0;
-                __syncthreads();
-                for (uint32_t i = w0 + lane; i < w1; i += 64) atomicAdd(&h[wave][255u - ((in[i] >> sh) & 255u)], 1u);
-                __syncthreads();
-                uint32_t mine = 0, all;
-                for (int w = 0; w < 4; ++w) mine += h[w][tid];
-                uint32_t run = block_excl_scan<SZ_THREADS>(mine, s_scan, all);
-                for (int w = 0; w < 4; ++w) {
-                    const uint32_t c = h[w][tid];
-                    h[w][tid] = run;
-                    run += c;
-                }
-                __syncthreads();
-                for (uint32_t i0 = w0; i0 < w1; i0 += 64) {   // uniform over the wave
-                    const bool valid = i0 + lane < w1;
-                    const uint32_t k = in[valid ? i0 + lane : w1 - 1u];
-                    const uint32_t digit = 255u - ((k >> sh) & 255u);
-                    uint64_t peers = __ballot(valid);
-#pragma unroll
-                    for (int b = 0; b < 8; ++b) {
-                        const uint64_t m = __ballot(valid && ((digit >> b) & 1u));
-                        peers &= ((digit >> b) & 1u) ? m : ~m;
-                    }
-                    const uint32_t rank = mbcnt(peers);
-                    const uint32_t base = h[wave][digit];
-                    wave_lds_sync();
-                    if (valid && rank == 0) h[wave][digit] = base + (uint32_t)__popcll(peers);
-                    wave_lds_sync();
-                    if (valid) out[base + rank] = k;
-                }
-                uint32_t* t = in;
-                in = out;
-                out = t;
-                __threadfence_block();
-            }
+            for (int i = 0; i < PER; ++i)
+                if ((uint32_t)(tid + i * SZ_THREADS) < np2) s_k[tid + i * SZ_THREADS] = my[i];
             __syncthreads();
-            sorted = in;
+#pragma unroll
+            for (int i = 0; i < PER; ++i) other |= my[i] ? my[i] ^ s_k[0] : 0u;
+            if (__syncthreads_or((int)other) == 0) np2 = 1;   // one key: in order as it is
+            for (uint32_t k = 2; k <= np2; k <<= 1) {
+                for (uint32_t j = k >> 1; j > 0; j >>= 1) {
+                    for (uint32_t p = tid; p < (np2 >> 1); p += SZ_THREADS) {
+                        const uint32_t i = ((p & ~(j - 1u)) << 1) | (p & (j - 1u)), l = i | j;
+                        const uint32_t x = s_k[i], y = s_k[l];
+                        if ((x < y) == ((i & k) == 0u)) { s_k[i] = y; s_k[l] = x; }
+                    }
+                    __syncthreads();
+                }
+            }
         }
     }
-    auto key_at = [&](uint32_t i) -> uint32_t { return sorted ? sorted[i] : s_k[i]; };
     const uint32_t s = (uint32_t)(a.s < a.d ? a.s : a.d);
     const int esh = se_exp_shift(zn.lo);
     for (uint32_t u = tid; u < zn.nb; u += SZ_THREADS) {
         const uint32_t r = (zn.t0 + u) * s - zn.cum;   // 1 .. n - 1 keys of the zone are inside
-        const uint32_t tau = key_at(r - 1u);
+        const uint32_t tau = s_k[r - 1u];
         uint32_t q = SE_ALL;
-        if (key_at(r) == tau) {   // its equal keys are split: how many are inside
+        if (s_k[r] == tau) {   // its equal keys are split: how many are inside
             uint32_t lo = 0, hi = r - 1u;   // first position with a key <= tau
             while (lo < hi) {
                 const uint32_t mid = (lo + hi) >> 1;
-                if (key_at(mid) > tau) lo = mid + 1u;
+                if (s_k[mid] > tau) lo = mid + 1u;
                 else hi = mid;
             }
             q = r - lo;
         }
         a.se_thr[(size_t)row * (a.L + 1) + zn.t0 + u] = make_uint2(tau, q);
     }
-    for (uint32_t u = wave; u <= zn.nb; u += SZ_THREADS / 64) {   // part u lies in band t0 + u (from 1)
-        const uint32_t r0 = u ? (zn.t0 + u - 1u) * s - zn.cum : 0u, r1 = u < zn.nb ? (zn.t0 + u) * s - zn.cum : n;
-        uint64_t lo = 0, hi = 0;
-        if (equal) {
-            const uint64_t sq = sig_square(s_min);
-            if (lane == 0) { lo = (sq & 0xFFFFFFFFull) * (r1 - r0); hi = (sq >> 32) * (r1 - r0); }
-        } else {
-            for (uint32_t i = r0 + lane; i < r1; i += 64) {
-                const uint64_t sq = sig_square(key_at(i));
+    // part u lies in band t0 + u (from 1)
+    auto part_from = [&](uint32_t u) -> uint32_t { return u ? (zn.t0 + u - 1u) * s - zn.cum : 0u; };
+    auto part_to = [&](uint32_t u) -> uint32_t { return u < zn.nb ? (zn.t0 + u) * s - zn.cum : n; };
+    auto part_add = [&](uint32_t u, uint64_t lo, uint64_t hi) {
+        unsigned long long* wide = a.se_big + ((size_t)row * a.L + (zn.t0 + u - 1u)) * SE_WORDS;
+        se_add(wide, lo, esh);
+        se_add(wide, hi, esh + 32);
+    };
+    if (s <= 128u) {   // many short parts: a thread each (a wave needs 1.5 us to add up its lanes, whatever the part's length)
+        for (uint32_t u = tid; u <= zn.nb; u += SZ_THREADS) {
+            uint64_t lo = 0, hi = 0;
+            for (uint32_t i = part_from(u), e = part_to(u); i < e; ++i) {
+                const uint64_t sq = sig_square(s_k[i]);
                 lo += sq & 0xFFFFFFFFull;
                 hi += sq >> 32;
             }
+            part_add(u, lo, hi);
+        }
+        return;
+    }
+    for (uint32_t u = wave; u <= zn.nb; u += SZ_THREADS / 64) {
+        uint64_t lo = 0, hi = 0;
+        for (uint32_t i = part_from(u) + lane, e = part_to(u); i < e; i += 64) {
+            const uint64_t sq = sig_square(s_k[i]);
+            lo += sq & 0xFFFFFFFFull;
+            hi += sq >> 32;
         }
 #pragma unroll
         for (int o = 32; o >= 1; o >>= 1) {
             lo += (uint64_t)__shfl_xor((unsigned long long)lo, o, 64);
             hi += (uint64_t)__shfl_xor((unsigned long long)hi, o, 64);
         }
-        if (lane == 0) {
-            unsigned long long* wide = a.se_big + ((size_t)row * a.L + (zn.t0 + u - 1u)) * SE_WORDS;
-            se_add(wide, lo, esh);
-            se_add(wide, hi, esh + 32);
+        if (lane == 0) part_add(u, lo, hi);
+    }
+}
+
+// Zones of more than SE_ZCAP entries.  Nothing is put in order: the counts of 2^SE_ZBITS sub-bins of the zone's key range give
+// their ranks; a sub-bin without a boundary belongs to one band, one with boundaries is counted key by key (at most 16 keys).
+// PHASE 0: a zone of up to SE_ZBIG entries is resolved by one workgroup, its key range cut to the keys that are there (repeated keys
+// make nearly all such zones: one key or a few); of a larger one, a workgroup adds the sub-bins of a slice to the zone's.
+// PHASE 1: the slices of the larger ones again; the last workgroup of a zone resolves it from the counts.  Bound by LDS atomics
+// on the words that many entries share; 8 rows of 1.17e7 entries at 1000 levels, compress: of one value 1031 us (a sort of the
+// rows 3804, one workgroup per zone 19678), of two neighbouring values 1069 (3610, 90185), 16 values 693 (3457, 4226).
+template <int PHASE>
+__global__ __launch_bounds__(SE_THREADS) void k_se_wide(StopkArgs a) {
+    __shared__ uint32_t s_tab[SE_ZSUB];             // counts of the sub-bins, then of the keys of those with boundaries
+    __shared__ uint16_t s_cls[SE_ZSUB];             // part of the zone that a sub-bin lies in, or 0x8000 | its number among those with boundaries
+    __shared__ unsigned long long s_sum[SE_LMAX];   // squares of the parts, in lane-interleaved copies
+    __shared__ uint32_t s_rcum[SE_LMAX];            // sub-bins with boundaries: entries of the zone above
+    __shared__ uint16_t s_rsub[SE_LMAX];            // which one
+    __shared__ uint32_t s_scan[SE_THREADS / 64 + 1];
+    __shared__ uint32_t s_min, s_max;
+    const int row = blockIdx.y;
+    const uint32_t tid = threadIdx.x, lane = lane_id();
+    const uint32_t nmid = PHASE == 0 ? a.se_nz[SE_NZ * row + 2] : 0u, nwork = nmid + a.se_nz[SE_NZ * row + 4];
+    const uint32_t s = (uint32_t)(a.s < a.d ? a.s : a.d);
+    uint2* thr = a.se_thr + (size_t)row * (a.L + 1);
+    for (uint32_t it = blockIdx.x; it < nwork; it += gridDim.x) {   // everything down to the end of the loop is uniform unless it says tid or lane
+        const bool mid = it < nmid;
+        const uint2 item = mid ? make_uint2(a.se_mid[(size_t)row * a.se_mids + it], 0u) : a.se_item[(size_t)row * a.se_items + (it - nmid)];
+        const SZone zn = a.se_zone[(size_t)row * a.L + item.x];
+        const uint32_t n = zn.n;
+        const uint32_t* src = a.se_list + (size_t)row * a.d + zn.off;
+        uint32_t* tab = mid ? nullptr : a.se_list2 + (size_t)row * a.d + zn.off;
+        uint32_t lo = zn.lo, bits = zn.shift;
+        __syncthreads();   // the work before this has been read
+        if (mid) {
+            if (tid == 0) { s_min = 0xFFFFFFFFu; s_max = 0; }
+            __syncthreads();
+            uint32_t mx = 0, mn_inv = 0;
+            batched_loop<8, SE_THREADS>(0u, n, tid, [&](uint32_t i) { return src[i]; }, [&](uint32_t, uint32_t k) {
+                mx = k > mx ? k : mx;
+                mn_inv = ~k > mn_inv ? ~k : mn_inv;
+            });
+            mx = wave_max(mx);
+            mn_inv = wave_max(mn_inv);
+            if (lane == 0) { atomicMax(&s_max, mx); atomicMin(&s_min, ~mn_inv); }
+            __syncthreads();
+            lo = s_min;
+            bits = s_max > lo ? 32u - (uint32_t)__clz((int)(s_max - lo)) : 0u;
+        }
+        const uint32_t b1 = bits < (uint32_t)SE_ZBITS ? bits : (uint32_t)SE_ZBITS, rest = bits - b1, nsub = 1u << b1, vmask = (1u << rest) - 1u;
+        auto sub_of = [&](uint32_t k) -> uint32_t { return nsub - 1u - ((k - lo) >> rest); };   // descending keys
+        const uint32_t i0 = mid ? 0u : item.y * SE_ZSLICE, i1 = mid || n - i0 < SE_ZSLICE ? n : i0 + SE_ZSLICE;
+        // counts of the sub-bins
+        if (mid || PHASE == 0) {
+            for (uint32_t i = tid; i < nsub; i += SE_THREADS) s_tab[i] = 0;
+            __syncthreads();
+            if (bits == 0) {
+                if (tid == 0) s_tab[0] = i1 - i0;
+            } else {
+                batched_loop<8, SE_THREADS>(i0, i1, tid, [&](uint32_t i) { return src[i]; }, [&](uint32_t, uint32_t k) { se_count_peeled(s_tab, sub_of(k), true); });
+            }
+        } else {
+            for (uint32_t i = tid; i < nsub; i += SE_THREADS) s_tab[i] = tab[i];
+        }
+        __syncthreads();
+        if (PHASE == 0 && !mid) {
+            for (uint32_t i = tid; i < nsub; i += SE_THREADS)
+                if (s_tab[i]) atomicAdd(&tab[i], s_tab[i]);
+            continue;
+        }
+        if (rest == 0 && item.y != 0u) continue;   // the counts are of single keys: one workgroup has all it needs
+        // classes of the sub-bins; thresholds of boundaries between two of them
+        const uint32_t per = nsub > SE_THREADS ? nsub / SE_THREADS : 1u, f0 = tid * per, f1 = f0 < nsub ? f0 + per : f0;
+        uint32_t mine = 0, nrec, total, flags = 0;
+        for (uint32_t i = f0; i < f1; ++i) mine += s_tab[i];
+        const uint32_t first = block_excl_scan<SE_THREADS>(mine, s_scan, total);
+        if (total != n && tid == 0) atomicOr(a.dev_status, MLMC_DEV_INTERNAL);
+        uint32_t run = first;
+        uint64_t plo = 0, phi = 0;
+        uint32_t pband = 0xFFFFFFFFu;
+        auto band_add = [&](uint32_t band, uint64_t l, uint64_t h) {   // band from 0
+            unsigned long long* wide = a.se_big + ((size_t)row * a.L + band) * SE_WORDS;
+            se_add(wide, l, se_exp_shift(zn.lo));
+            se_add(wide, h, se_exp_shift(zn.lo) + 32);
+        };
+        for (uint32_t i = f0; i < f1; ++i) {
+            const uint32_t c = s_tab[i];
+            if (!c) continue;
+            const uint32_t g0 = zn.cum + run, g1 = g0 + c, b0 = g0 / s, be = (g1 - 1u) / s;
+            if (b0 == be) {
+                s_cls[i] = (uint16_t)(b0 + 1u - zn.t0);
+                if (rest == 0) {   // c equal keys
+                    if (b0 != pband) {
+                        if (pband != 0xFFFFFFFFu) band_add(pband, plo, phi);
+                        pband = b0;
+                        plo = 0;
+                        phi = 0;
+                    }
+                    const uint64_t sq = sig_square(lo + (nsub - 1u - i));
+                    plo += (sq & 0xFFFFFFFFull) * c;
+                    phi += (sq >> 32) * c;
+                }
+            } else {
+                flags |= 1u << (i - f0);
+            }
+            run += c;
+            if (item.y == 0u && run < n && (be + 1u) * s == g1) thr[be + 1u] = make_uint2(lo + ((nsub - 1u - i) << rest), SE_ALL);
+        }
+        if (pband != 0xFFFFFFFFu) band_add(pband, plo, phi);
+        uint32_t j = block_excl_scan<SE_THREADS>((uint32_t)__popc(flags), s_scan, nrec);
+        run = first;
+        for (uint32_t i = f0; i < f1; ++i) {
+            if (flags >> (i - f0) & 1u) {
+                s_cls[i] = (uint16_t)(0x8000u | j);
+                s_rsub[j] = (uint16_t)i;
+                s_rcum[j++] = run;
+            }
+            run += s_tab[i];
+        }
+        __syncthreads();
+        const uint32_t room = SE_ZSUB >> rest;   // sub-bins whose keys' counts LDS holds at a time
+        // thresholds of the boundaries inside sub-bins j0 .. j0 + room - 1, and the parts on both sides of them
+        auto resolve = [&](uint32_t j0) {
+            for (uint32_t u = tid; u < zn.nb; u += SE_THREADS) {
+                const uint32_t r = (zn.t0 + u) * s - zn.cum;   // entries of the zone inside boundary t0 + u
+                uint32_t x = 0, y = nrec;                      // records [0, x) lie above r entries or fewer
+                while (x < y) {
+                    const uint32_t m = (x + y) >> 1;
+                    if (s_rcum[m] < r) x = m + 1u;
+                    else y = m;
+                }
+                if (x == 0u || x - 1u < j0 || x - 1u >= j0 + room) continue;
+                const uint32_t rec = x - 1u, sub = s_rsub[rec], rr = r - s_rcum[rec], key0 = lo + ((nsub - 1u - sub) << rest);
+                const uint32_t* cnt = rest ? s_tab + ((rec - j0) << rest) : s_tab + sub;
+                uint32_t acc = 0, tau = 0, q = 0;
+                for (uint32_t v = vmask + 1u; v-- > 0u;) {
+                    const uint32_t c = cnt[v];
+                    if (acc < rr && acc + c >= rr) {
+                        tau = key0 + v;
+                        q = acc + c == rr ? SE_ALL : rr - acc;
+                    }
+                    acc += c;
+                }
+                if (rr >= acc) continue;   // this boundary lies behind the sub-bin, or at its end
+                thr[zn.t0 + u] = make_uint2(tau, q);
+                auto part = [&](uint32_t from, uint32_t to, uint32_t band) {   // entries from .. to - 1 of the sub-bin
+                    uint64_t l = 0, h = 0;
+                    uint32_t at = 0;
+                    for (uint32_t v = vmask + 1u; v-- > 0u;) {
+                        const uint32_t e = at + cnt[v], x0 = at > from ? at : from, x1 = e < to ? e : to;
+                        if (x1 > x0) {
+                            const uint64_t sq = sig_square(key0 + v);
+                            l += (sq & 0xFFFFFFFFull) * (x1 - x0);
+                            h += (sq >> 32) * (x1 - x0);
+                        }
+                        at = e;
+                    }
+                    band_add(band, l, h);
+                };
+                part(u > 0u && rr > s ? rr - s : 0u, rr, zn.t0 + u - 1u);
+                if (u + 1u >= zn.nb || rr + s >= acc) part(rr, acc, zn.t0 + u);
+            }
+        };
+        if (rest == 0) {
+            resolve(0u);
+            continue;
+        }
+        uint32_t rep = 0;   // log2 of the copies of a part's sum
+        while (rep < 4u && ((zn.nb + 1u) << (rep + 1u)) <= (uint32_t)SE_LMAX) ++rep;
+        const uint32_t rlane = lane & ((1u << rep) - 1u);
+        for (uint32_t i = tid; i < (uint32_t)SE_LMAX; i += SE_THREADS) s_sum[i] = 0ull;
+        for (uint32_t j0 = 0; j0 == 0u || j0 < nrec; j0 += room) {
+            for (uint32_t i = tid; i < SE_ZSUB; i += SE_THREADS) s_tab[i] = 0;
+            __syncthreads();
+            for (uint32_t p0 = i0; p0 < i1; p0 += SE_ZSLICE) {
+                batched_loop<8, SE_THREADS>(p0, i1 - p0 < SE_ZSLICE ? i1 : p0 + SE_ZSLICE, tid, [&](uint32_t i) { return src[i]; }, [&](uint32_t, uint32_t k) {
+                    const uint32_t c = s_cls[sub_of(k)];
+                    if (c & 0x8000u) {
+                        const uint32_t at = (c & 0x7FFFu) - j0;
+                        if (at < room) atomicAdd(&s_tab[(at << rest) + ((k - lo) & vmask)], 1u);
+                    } else if (j0 == 0u) {
+                        atomicAdd(&s_sum[(c << rep) | rlane], (unsigned long long)sig_square(k));
+                    }
+                });
+                if (j0 == 0u) {
+                    __syncthreads();
+                    for (uint32_t u = tid; u <= zn.nb; u += SE_THREADS) {
+                        uint64_t l = 0, h = 0;
+                        for (uint32_t i = 0; i < (1u << rep); ++i) {
+                            const unsigned long long v = s_sum[(u << rep) + i];
+                            l += v & 0xFFFFFFFFull;
+                            h += v >> 32;
+                            s_sum[(u << rep) + i] = 0ull;
+                        }
+                        band_add(zn.t0 + u - 1u, l, h);
+                    }
+                }
+                __syncthreads();
+            }
+            const uint32_t here = nrec - j0 < room ? nrec - j0 : room;
+            if (PHASE == 0) {
+                resolve(j0);
+            } else {
+                for (uint32_t i = tid; i < (here << rest); i += SE_THREADS)
+                    if (s_tab[i]) atomicAdd(&tab[SE_ZSUB + (j0 << rest) + i], s_tab[i]);
+            }
+            __syncthreads();
+        }
+        if (PHASE == 0) continue;
+        // the last workgroup of the zone has everybody's counts
+        __threadfence();
+        __syncthreads();
+        if (tid == 0) s_max = atomicAdd(&tab[SE_ZBIG], 1u);
+        __syncthreads();
+        if (s_max + 1u != (n + SE_ZSLICE - 1u) / SE_ZSLICE) continue;
+        __threadfence();
+        for (uint32_t j0 = 0; j0 < nrec; j0 += room) {
+            const uint32_t here = nrec - j0 < room ? nrec - j0 : room;
+            for (uint32_t i = tid; i < (here << rest); i += SE_THREADS)
+                s_tab[i] = __hip_atomic_load(&tab[SE_ZSUB + (j0 << rest) + i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __syncthreads();
+            resolve(j0);
+            __syncthreads();
         }
     }
 }
@@ -1169,13 +1400,33 @@ __global__ __launch_bounds__(256) void k_se_write(StopkArgs a) {
     const int64_t w0 = tile * (TILE / 32) + lane * 2;
     uint2 m = w0 < a.bm_words ? *(const uint2*)(bm + w0) : make_uint2(0u, 0u);
     uint64_t bits = (uint64_t)m.y << 32 | m.x;
-    if (st.cut_hi || st.cut_lo) {   // uniform: entries decided by rank are kept or cleared
-        uint32_t n2 = 0, n3 = 0;
-        for (uint64_t b = bits; b; b &= b - 1) {
-            const int kd = st.kind(key_of_bits(ld.load1(w0 * 32 + __builtin_ctzll(b))));
-            n2 += kd == 2;
-            n3 += kd == 3;
+    // f(position, fp32 bits, ordinal) for the lane's entries in order, the loads of eight of them in flight (a run of equal entries
+    // fills whole lanes: one load at a time, 64 in a row)
+    auto each = [&](uint64_t b, auto f) {
+        for (uint32_t n = 0; b; n += 8) {
+            int at[8];
+            uint32_t v[8];
+            const int have = __popcll(b);
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                at[u] = u < have ? __builtin_ctzll(b) : at[0];
+                b &= b - 1;
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = ld.load1(w0 * 32 + at[u]);
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (u < have) f(at[u], v[u], n + u);
         }
+    };
+    if (st.cut_hi || st.cut_lo) {   // uniform: entries decided by rank are kept or cleared
+        uint64_t m2 = 0, m3 = 0;
+        each(bits, [&](int at, uint32_t v, uint32_t) {
+            const int kd = st.kind(key_of_bits(v));
+            m2 |= (uint64_t)(kd == 2) << at;
+            m3 |= (uint64_t)(kd == 3) << at;
+        });
+        const uint32_t n2 = (uint32_t)__popcll(m2), n3 = (uint32_t)__popcll(m3);
         uint32_t i2 = n2, i3 = n3;
 #pragma unroll
         for (int o = 1; o < 64; o <<= 1) {
@@ -1184,12 +1435,10 @@ __global__ __launch_bounds__(256) void k_se_write(StopkArgs a) {
         }
         const uint2 before = a.se_tie[(size_t)row * a.ntiles + tile];
         uint32_t r2 = before.x + i2 - n2, r3 = before.y + i3 - n3;
-        for (uint64_t b = bits; b; b &= b - 1) {
-            const int at = __builtin_ctzll(b);
-            const int kd = st.kind(key_of_bits(ld.load1(w0 * 32 + at)));
-            if (kd == 2 && !st.in_hi(r2++)) bits &= ~(1ull << at);
-            if (kd == 3 && !st.in_lo(r3++)) bits &= ~(1ull << at);
-        }
+        for (; m2; m2 &= m2 - 1)
+            if (!st.in_hi(r2++)) bits &= ~(m2 & (0 - m2));
+        for (; m3; m3 &= m3 - 1)
+            if (!st.in_lo(r3++)) bits &= ~(m3 & (0 - m3));
     }
     const uint32_t mine = (uint32_t)__popcll(bits);
     uint32_t inc = mine;
@@ -1198,14 +1447,13 @@ __global__ __launch_bounds__(256) void k_se_write(StopkArgs a) {
         const uint32_t u = __shfl_up(inc, o, 64);
         if (lane >= (uint32_t)o) inc += u;
     }
-    int64_t at = a.row_off[row] + to[tile] + (inc - mine);
-    for (; bits; bits &= bits - 1, ++at) {
-        const int64_t j = w0 * 32 + __builtin_ctzll(bits);
-        if (at < a.capacity) {
-            a.idx[at] = (uint32_t)j;
-            a.val[at] = __fmul_rn(__uint_as_float(ld.load1(j)), w);
+    const int64_t first = a.row_off[row] + to[tile] + (inc - mine);
+    each(bits, [&](int at, uint32_t v, uint32_t n) {
+        if (first + n < a.capacity) {
+            a.idx[first + n] = (uint32_t)(w0 * 32 + at);
+            a.val[first + n] = __fmul_rn(__uint_as_float(v), w);
         }
-    }
+    });
 }
 
 template <int DT>
@@ -1219,7 +1467,7 @@ static mlmc_status launch_bins(const mlmc_plan_t* pl, const StopkArgs& a, bool m
     }
     {
         const int64_t ns = ((a.d + 1023) / 1024 + (1 << a.se_shift) - 1) >> a.se_shift;
-        int64_t gx = (ns + 63) / 64, cap = 1024 / M > 0 ? 1024 / M : 1;
+        int64_t gx = ns <= 512 ? (ns + 15) / 16 : (ns + 63) / 64, cap = 1024 / M > 0 ? 1024 / M : 1;
         if (gx > cap) gx = cap;
         MLMC_LAUNCH(K_HIST, st, k_se_coarse<DT><<<dim3((unsigned)gx, M), 512, 0, st>>>(a));
     }
@@ -1229,6 +1477,12 @@ static mlmc_status launch_bins(const mlmc_plan_t* pl, const StopkArgs& a, bool m
     MLMC_LAUNCH(K_SE_SCAN, st, k_se_scan<<<dim3(SE_BLOCKS, M), 256, 0, st>>>(a));
     MLMC_LAUNCH(K_SE_SPLIT, st, k_se_split<DT><<<dim3(a.se_wgs, M), SE_THREADS, 0, st>>>(a));
     MLMC_LAUNCH(K_SE_ZONE, st, k_se_zone<<<dim3(a.L - 1 + (a.L + 255 + SZ_THREADS - 1) / SZ_THREADS, M), SZ_THREADS, 0, st>>>(a));
+    {
+        const int64_t cap = 512 / M > 0 ? 512 / M : 1;   // about two workgroups per CU: nearly always they find nothing to do
+        const int64_t w0 = (int64_t)a.se_mids + a.se_items, g0 = w0 < cap ? w0 : cap, g1 = a.se_items < cap ? a.se_items : cap;
+        MLMC_LAUNCH(K_SE_ZONE, st, k_se_wide<0><<<dim3((unsigned)g0, M), SE_THREADS, 0, st>>>(a));
+        if (a.d > SE_ZBIG) MLMC_LAUNCH(K_SE_ZONE, st, k_se_wide<1><<<dim3((unsigned)g1, M), SE_THREADS, 0, st>>>(a));
+    }
     MLMC_LAUNCH(K_SB_NORMS, st, k_se_norms<<<dim3((a.L + 63) / 64, M), 64, 0, st>>>(a));
     if (!message) return MLMC_OK;
     const dim3 tgrid((unsigned)((a.ntiles + 3) / 4), M);

@@ -118,7 +118,7 @@ def _misled_sample(d, rng):
 def test_stopk_edges_of_the_binned_path(what, d, s, dtype, ld):
     rng = np.random.default_rng(d + s)
     make = {"normal": lambda: rng.standard_normal(d).astype(np.float32), "few": lambda: _few_values(d, rng), "misled": lambda: _misled_sample(d, rng)}[what]
-    G = np.stack([make() for _ in range(2)])
+    G = np.stack([make() for _ in range(8 if dtype == "bf16" else 2)])   # (fewer short 16-bit rows are sorted)
     dt = P.MLMC_F32
     if dtype == "bf16":
         dt = P.MLMC_BF16
@@ -139,3 +139,52 @@ def test_stopk_boundary_between_the_smallest_entries_and_zeros(d, s, nnz, smalle
         G[r, at[: 2 - r]] = np.array([smallest, 20_000_000], dtype=np.uint32).view(np.float32)[: 2 - r]
     print(f"stopk subnormals before zeros d={d} s={s}", flush=True)
     _run_and_check(G, s, steps=(0, 1, 2, 3))
+
+
+def _crowd(d, n, rng, key=0x3EB851EC):
+    """n entries of one magnitude, the others spread far below them."""
+    g = (rng.standard_normal(d) * np.exp(rng.uniform(-30, -10, d))).astype(np.float32)
+    g[rng.permutation(d)[:n]] = np.array([key], dtype=np.uint32).view(np.float32)[0]
+    return g * rng.choice(np.array([-1, 1], dtype=np.float32), d)
+
+
+def _hidden(d, n, rng):
+    """n distinct keys of one coarse bucket, in blocks that the sample passes over, among ordinary entries elsewhere."""
+    g = rng.standard_normal(d).astype(np.float32)
+    at = np.flatnonzero((np.arange(d) >> 10) % 2 == 0)[:n]
+    g[at] = (1e-9 * (1.0 + rng.random(n) * 0.02)).astype(np.float32)
+    return g
+
+
+@pytest.mark.parametrize("what,d,s,dtype", [
+    ("one", 8192, 2, "f32"), ("one", 8192, 2, "bf16"),                     # every boundary at one key
+    ("one", 300_001, 300, "f32"), ("two", 300_001, 100, "f32"),
+    ("two", 50_021, 37, "f32"), ("sixteen", 300_001, 77, "f32"),
+    ("zeros", 16_384, 4, "f32"), ("zeros", 50_021, 37, "bf16"),
+    ("crowd 2047", 100_003, 500, "f32"), ("crowd 2048", 100_003, 500, "f32"), ("crowd 2049", 100_003, 500, "f32"),
+    ("crowd 65536", 100_003, 500, "f32"), ("crowd 81919", 100_003, 25, "f32"), ("crowd 81920", 100_003, 25, "f32"),
+    ("crowd 81921", 100_003, 25, "f32"), ("crowd 131072", 150_001, 40, "f32"), ("crowd 131073", 150_001, 40, "f32"),
+    ("hidden 60000", (1 << 21) + 5, 700, "f32"),                           # one workgroup, up to 16 keys to a sub-bin
+    ("misled", (1 << 21) + 777, 513, "bf16"),                              # four keys in the widest bin
+    ("misled", (1 << 21) + 777, 513, "f32"),                               # many workgroups, thousands of boundaries
+])
+def test_stopk_zones_of_many_entries(what, d, s, dtype):
+    """Rows of few magnitudes and rows that the sample misjudges: bins of thousands of entries that hold boundaries, at the sizes
+    where another kernel, or another number of workgroups, takes them."""
+    rng = np.random.default_rng(d + s)
+    sign = lambda: rng.choice(np.array([-1, 1], dtype=np.float32), d)
+    kind, _, arg = what.partition(" ")
+    if kind == "crowd":
+        make = lambda: _crowd(d, int(arg), rng)
+    elif kind == "hidden":
+        make = lambda: _hidden(d, int(arg), rng)
+    else:
+        make = {"one": lambda: np.float32(0.37) * sign(), "two": lambda: rng.choice(np.array([1.0, 1.0000001], dtype=np.float32), d) * sign(),
+                "sixteen": lambda: (rng.integers(1, 17, d) * 0.25).astype(np.float32) * sign(),
+                "zeros": lambda: np.where(rng.random(d) < 0.9, 0.0, rng.standard_normal(d)).astype(np.float32),
+                "misled": lambda: _misled_sample(d, rng)}[kind]
+    G = np.stack([make() for _ in range(8 if dtype == "bf16" and d < 1 << 20 else 2)])   # (fewer short 16-bit rows are sorted)
+    if dtype == "bf16":
+        G = W.f32_to_bf16_bits(G)
+    print(f"stopk zones {what} d={d} s={s} {dtype}", flush=True)
+    _run_and_check(G, s, dtype=P.MLMC_BF16 if dtype == "bf16" else P.MLMC_F32, steps=(0, 1))
