@@ -259,7 +259,9 @@ static mlmc_status plan_stopk(mlmc_plan_t** plan, int M, int64_t d, int in_dtype
     auto take = [&](size_t bytes) { const size_t at = off; off = align_up(off + bytes, 256); return at; };
     // More levels: a boundary in every few bins, most entries would be zone entries.  Short rows: the tables of a row (0.8 MB) are not
     // worth it, a sort of a few blocks is a handful of short launches (at 16384 entries the bins are 20 us ahead).
-    const bool bins = L <= SE_LMAX && d >= 8192;
+    // 16-bit rows are sorted in two passes: with few of them the sort is the faster one up to some 2^22 entries in all (1 row of 1e6: 94 us
+    // against 110, 4 of 524289: 112 against 112, or 129 against 152 where nine in ten are zero; 8 of 8192: 106 against 102).
+    const bool bins = L <= SE_LMAX && d >= 8192 && (in_dtype == MLMC_F32 || M >= 8 || (int64_t)M * d >= ((int64_t)1 << 22));
     if (bins) {
         pl->se_rep = L <= 1024 ? 2 : (L <= 2304 ? 1 : 0);   // (L + 256) << se_rep sums fill 40 KB of LDS
         while (pl->se_shift < 4 && (d >> (pl->se_shift + 1)) >= (1 << 20)) ++pl->se_shift;
