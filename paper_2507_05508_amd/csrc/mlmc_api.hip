@@ -122,11 +122,10 @@ static void fill_topk_args(const mlmc_plan_t* pl, TopkArgs& a, const void* g, in
     a.sample_shift = pl->sample_shift;
     // Short rows are bound by the number of launches (5 to 6 us each), so what a launch saves there is less than it costs: a
     // zone of an exact histogram is one bucket, a few hundred candidates that one workgroup ranks without the two sliced
-    // passes, and the second read of half a million entries is cheaper than a kernel that assembles staged lists: 4 rows of
-    // 65536, 81 -> 63 us.  Longer rows keep the sliced passes for zones with many equal keys (one workgroup would take 0.24 ms
+    // passes: 4 rows of 65536, 81 -> 63 us, together with the plan's default for staging.  Longer rows keep the sliced passes for zones with many equal keys (one workgroup would take 0.24 ms
     // for a row of 2.6e5 that is mostly zeros, as long as the passes).
     a.alone = pl->sample_shift == 0 && pl->d <= ((int64_t)1 << 17) ? 1 : 0;
-    a.staging = pl->staging && (int64_t)pl->M * pl->d > ((int64_t)1 << 19) ? 1 : 0;
+    a.staging = pl->staging;
     {
         int fx = FIN_WGS;
         if (pl->M < 16) fx = 512 / pl->M < FIN_WGS_MAX ? 512 / pl->M : FIN_WGS_MAX;   // about 512 workgroups in all
@@ -478,7 +477,7 @@ mlmc_status mlmc_plan(mlmc_plan_t** plan, int kind, int M, int64_t d, int in_dty
     // rows long enough that a second full read matters get their thresholds from a sampled histogram
     pl->sample_shift = d >= ((int64_t)1 << 23) ? 4 : d >= ((int64_t)1 << 21) ? 2 : 0;
     if (kind == MLMC_VBITS || kind == MLMC_RTN) pl->sample_shift = 0;   // the largest entry itself is needed, not its binade
-    pl->staging = 1;
+    pl->staging = (int64_t)M * d > ((int64_t)1 << 19) ? 1 : 0;   // a second read of fewer entries is cheaper than the launch that assembles staged lists
     // The fork and the join cost some twenty microseconds of stream operations, paid in every call, while the second read
     // has work in a call only when some row's band was not staged: worth it for many long rows (measured: -11 us per call
     // at 16 rows of 2.6e7 elements, +5 us at 4 rows of 1.2e8).

@@ -171,8 +171,35 @@ def test_message_kernels_side_by_side_or_in_turn():
             assert np.array_equal(out.cpu().numpy().view(np.uint32), O.aggregate_sparse(want, w.d, 1.0 / w.M).view(np.uint32))
 
 
+def _launched(call):
+    """Names of the kernels that `call` launches."""
+    P.mlmc_profile_reset()
+    P.mlmc_profile_enable(True)
+    try:
+        call()
+        torch.cuda.synchronize()
+        return set(P.mlmc_profile_get())
+    finally:
+        P.mlmc_profile_enable(False)
+        P.mlmc_profile_reset()
+
+
+@pytest.mark.parametrize("d,default", [(4096, False), ((1 << 18) + 1, True)])
+def test_staging_hook_decides_whatever_the_size(d, default):
+    """The size of the plan chooses the default; the hook turns the staged message on and off on every plan."""
+    g = torch.randn((2, d), device="cuda:0")
+    plan = P.Plan(P.MLMC_TOPK, 2, d, P.MLMC_F32, [d // 16, d // 4, d], None)
+    staged = lambda: "k_filter" in _launched(lambda: P.mlmc_compress_topk(plan, g, seed=1, step=0))
+    print(f"staging hook d={d}", flush=True)
+    assert staged() == default
+    for on in (True, False, True):
+        plan.set_staging(on)
+        assert staged() == on
+
+
+@pytest.mark.parametrize("staging", [False, True])
 @pytest.mark.parametrize("shift", [0, 2])
-def test_adversarial_rows_ties_zeros_denormals(shift):
+def test_adversarial_rows_ties_zeros_denormals(shift, staging):
     d = 3 * 4096 + 517
     rows = W.adversarial_rows(d)
     G = np.stack(rows)
@@ -189,6 +216,8 @@ def test_adversarial_rows_ties_zeros_denormals(shift):
         assert np.array_equal(norms[i].view(np.uint64), np.array(want).view(np.uint64)), (i, norms[i], want)
     plan_f = P.Plan(P.MLMC_TOPK, M, d, P.MLMC_F32, ladder, O.geometric_p(L))
     plan_f.set_sampling(shift)
+    plan_a.set_staging(staging)
+    plan_f.set_staging(staging)
     for step in range(10):
         print(f"adversarial step={step}", flush=True)
         msg = P.mlmc_compress_topk(plan_f, g, seed=9, step=step)
@@ -252,12 +281,14 @@ def test_one_key_holds_the_threshold_massive_ties(bf16):
                 assert plan.status() == 0
 
 
+@pytest.mark.parametrize("staging", [False, True])
 @pytest.mark.parametrize("ld_pad", [1, 2, 3, 8])
-def test_padded_and_misaligned_rows(ld_pad):
+def test_padded_and_misaligned_rows(ld_pad, staging):
     w = W.scaled(W.WORKLOADS["resnet18_topk"], d=2 * 4096 + 1001, M=3)
     G = W.generate(w)
     g = to_device(G, ld=w.d + ld_pad)
     plan = _plan_for(w, None)
+    plan.set_staging(staging)
     for step in range(3):
         print(f"padded ld=d+{ld_pad} step={step}", flush=True)
         msg = P.mlmc_compress_topk(plan, g, seed=5, step=step)
@@ -286,15 +317,17 @@ def test_bf16_rows():
     check_topk_against_oracle(plan, G, 77, 1, msg, adaptive=True)
 
 
+@pytest.mark.parametrize("staging", [False, True])
 @pytest.mark.parametrize("d,ladder", [(1, [0, 1]), (5, [0, 2, 5]), (64, [0, 1, 2, 3, 64]), (4097, [0, 4097]),
                                        (9000, [10, 20, 8000]), (4096, [4095, 4096])])
-def test_degenerate_shapes(d, ladder):
+def test_degenerate_shapes(d, ladder, staging):
     rng = np.random.default_rng(d)
     G = rng.standard_normal((2, d)).astype(np.float32)
     L = len(ladder) - 1
     g = to_device(G)
     for pf in (O.geometric_p(L), None):
         plan = P.Plan(P.MLMC_TOPK, 2, d, P.MLMC_F32, ladder, pf)
+        plan.set_staging(staging)
         for step in range(4):
             print(f"degenerate d={d} ladder={ladder} adaptive={pf is None} step={step}", flush=True)
             msg = P.mlmc_compress_topk(plan, g, seed=3, step=step)
@@ -458,7 +491,8 @@ def test_zones_resolved_by_one_workgroup(what, d, dtype):
     ladder = [d >> (8 - l) for l in range(9)]
     plan = P.Plan(P.MLMC_TOPK, 3, d, dtype, ladder, None)
     g = to_device(G)
-    for step in range(2):
+    for step in range(4):
+        plan.set_staging(step >= 2)
         print(f"zones alone {what} d={d} dtype={dtype} step={step}", flush=True)
         msg = P.mlmc_compress_topk(plan, g, seed=4, step=step)
         check_topk_against_oracle(plan, G, 4, step, msg, adaptive=True)
