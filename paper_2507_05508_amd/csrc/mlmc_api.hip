@@ -506,9 +506,11 @@ mlmc_status mlmc_plan(mlmc_plan_t** plan, int kind, int M, int64_t d, int in_dty
         off = align_up(off + sizeof(unsigned long long) * 2 * (size_t)L * M, 256);
         pl->off_norms = off;
         off = align_up(off + sizeof(double) * (size_t)L * M, 256);
-        // Counting magnitudes costs a workgroup 128 KB to clear and to store, about 25 us in all; the two reads it replaces take
-        // about 1.2 us per 1e6 entries.
-        if (in_dtype == MLMC_BF16 && (int64_t)M * d >= ((int64_t)1 << 25)) {
+        // Counting magnitudes costs a workgroup 128 KB to clear and to store and a row 128 KB of totals and 2^15 codes, whatever its length;
+        // the two reads it replaces take about 1.2 us per 1e6 entries.  So the rows have to be long, not only many (us, four levels,
+        // not counted / counted): 8 rows of 1048579 84 / 89, of 4194307 176 / 156; 64 of 524291 195 / 193; 128 of 262147 196 / 222,
+        // of 524291 328 / 300; 256 of 524291 580 / 511; 512 of 131075 326 / 475; 1024 of 32771 217 / 645.
+        if (in_dtype == MLMC_BF16 && (int64_t)M * d >= ((int64_t)1 << 25) && d >= ((int64_t)1 << 19)) {
             int64_t wgs = 256 / M > 0 ? 256 / M : 1;   // one workgroup per CU in one round
             if (wgs > (d + 8191) / 8192) wgs = (d + 8191) / 8192;
             pl->rtn_slice = ((d + wgs - 1) / wgs + 1023) / 1024 * 1024;

@@ -54,3 +54,16 @@ def check_topk_against_oracle(plan, G, seed, step, msg, *, adaptive, norms_overr
         off += n
     assert row_off[M] == off
     return want
+
+
+def launched(call):
+    """Names of the kernels that `call` launches."""
+    P.mlmc_profile_reset()
+    P.mlmc_profile_enable(True)
+    try:
+        call()
+        torch.cuda.synchronize()
+        return set(P.mlmc_profile_get())
+    finally:
+        P.mlmc_profile_enable(False)
+        P.mlmc_profile_reset()

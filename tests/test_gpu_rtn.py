@@ -7,7 +7,7 @@ import torch
 import mlmc_workloads as W
 import paper_2507_05508_amd as P
 from oracle import mlmc as O
-from gpu_util import to_device
+from gpu_util import launched, to_device
 
 pytestmark = pytest.mark.gpu
 
@@ -126,10 +126,11 @@ def test_rtn_random_plans_and_inputs(seed):
             assert bits.cpu().numpy().tolist() == [O.message_bits_rtn(B, m["level"], d) for m in want]
 
 
-def test_rtn_bf16_rows_whose_magnitudes_are_counted():
-    """16-bit plans of 2^25 entries or more count magnitudes instead of forming a code per entry: 1024 odd rows, eight distinct ones
-    (ties of a width, zeros, one value, tiny and mixed scales) in turn."""
-    d, M, B = 32_771, 1024, [0, 2, 4, 8, 16]
+@pytest.mark.parametrize("M,d,counted", [(64, (1 << 19) + 3, True), (65, (1 << 19) - 1, False), (1024, 32_771, False)])
+def test_rtn_bf16_rows_whose_magnitudes_are_counted(M, d, counted):
+    """16-bit plans of 2^25 entries or more in rows of 2^19 or more count magnitudes instead of forming a code per entry; many
+    shorter rows do not.  Odd rows, eight distinct ones (ties of a width, zeros, one value, tiny and mixed scales) in turn."""
+    B = [0, 2, 4, 8, 16]
     rng = np.random.default_rng(5)
     x = rng.standard_normal((8, d)).astype(np.float32)
     x[1] = np.tile(np.array([0.5, -1.5, 2.5, -0.5, 3.5], dtype=np.float32), d // 5 + 1)[:d]
@@ -141,9 +142,10 @@ def test_rtn_bf16_rows_whose_magnitudes_are_counted():
     G8 = W.f32_to_bf16_bits(x)
     Gf = np.stack([O.as_f32(G8[i]) for i in range(8)])
     plan = P.Plan(P.MLMC_RTN, M, d, P.MLMC_BF16, B, None)
-    g = to_device(np.tile(G8, (M // 8, 1)))
+    g = to_device(np.tile(G8, (-(-M // 8), 1))[:M])
+    assert ("k_bits_smax" not in launched(lambda: P.mlmc_compress_rtn(plan, g, seed=3, step=0))) == counted
     for step in range(2):
-        print(f"rtn counted magnitudes step={step}", flush=True)
+        print(f"rtn counted magnitudes M={M} step={step}", flush=True)
         msg = P.mlmc_compress_rtn(plan, g, seed=3, step=step)
         torch.cuda.synchronize()
         assert plan.status() == 0

@@ -6,7 +6,7 @@ import torch
 import mlmc_workloads as W
 import paper_2507_05508_amd as P
 from oracle import mlmc as O
-from gpu_util import check_topk_against_oracle, to_device, u32
+from gpu_util import check_topk_against_oracle, launched, to_device, u32
 
 pytestmark = pytest.mark.gpu
 
@@ -171,25 +171,12 @@ def test_message_kernels_side_by_side_or_in_turn():
             assert np.array_equal(out.cpu().numpy().view(np.uint32), O.aggregate_sparse(want, w.d, 1.0 / w.M).view(np.uint32))
 
 
-def _launched(call):
-    """Names of the kernels that `call` launches."""
-    P.mlmc_profile_reset()
-    P.mlmc_profile_enable(True)
-    try:
-        call()
-        torch.cuda.synchronize()
-        return set(P.mlmc_profile_get())
-    finally:
-        P.mlmc_profile_enable(False)
-        P.mlmc_profile_reset()
-
-
 @pytest.mark.parametrize("d,default", [(4096, False), ((1 << 18) + 1, True)])
 def test_staging_hook_decides_whatever_the_size(d, default):
     """The size of the plan chooses the default; the hook turns the staged message on and off on every plan."""
     g = torch.randn((2, d), device="cuda:0")
     plan = P.Plan(P.MLMC_TOPK, 2, d, P.MLMC_F32, [d // 16, d // 4, d], None)
-    staged = lambda: "k_filter" in _launched(lambda: P.mlmc_compress_topk(plan, g, seed=1, step=0))
+    staged = lambda: "k_filter" in launched(lambda: P.mlmc_compress_topk(plan, g, seed=1, step=0))
     print(f"staging hook d={d}", flush=True)
     assert staged() == default
     for on in (True, False, True):
