@@ -412,7 +412,7 @@ __global__ __launch_bounds__(EX_THREADS, 4) void k_bits_extract(BitsArgs a) {
     uint32_t Ex = Es;
     if (REDO) {
         Ex = ra->rowmax_key >> 23;
-        if (Ex == Es) return;
+        if (Ex <= Es) return;
     }
     const int Emax = Ex ? (int)Ex : 1;
     const int level = a.rinfo[row].level;
@@ -461,7 +461,6 @@ __global__ __launch_bounds__(EX_THREADS, 4) void k_bits_extract(BitsArgs a) {
             write_block<KIND, BASE>(a, e, level, x, sign, PlaneWriter(a, row, b0));
     });
     if (!REDO) {
-        // one atomic per workgroup (the workgroups of a launch end together, and atomics on one address take turns)
         maxkey = wave_max(maxkey);
         __shared__ uint32_t s_max[EX_THREADS / 64];
         if (lane == 0) s_max[wave] = maxkey;
@@ -470,10 +469,10 @@ __global__ __launch_bounds__(EX_THREADS, 4) void k_bits_extract(BitsArgs a) {
             uint32_t m = s_max[0];
 #pragma unroll
             for (int w = 1; w < EX_THREADS / 64; ++w) m = s_max[w] > m ? s_max[w] : m;
-            if (m) {
-                atomicMax(&ra->rowmax_key, m);
-                if (m >= 0x7F800000u) atomicOr(a.dev_status, MLMC_DEV_NONFINITE);
-            }
+            // Only a key above the sampled maximum's binade is reported: with every workgroup's, the atomics of a single long row met on the line
+            // that all its workgroups read the sampled maxima from (1 row of 5e7 fp32 entries: 81 us, 41 now; 1 row of 1e8: 122, 83).
+            if (KIND == 0 && (m >> 23) > Es) atomicMax(&ra->rowmax_key, m);
+            if (m >= 0x7F800000u) atomicOr(a.dev_status, MLMC_DEV_NONFINITE);
         }
     }
 }
