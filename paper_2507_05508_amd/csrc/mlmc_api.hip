@@ -122,7 +122,7 @@ static void fill_topk_args(const mlmc_plan_t* pl, TopkArgs& a, const void* g, in
     a.sample_shift = pl->sample_shift;
     // Short rows are bound by the number of launches (5 to 6 us each), so what a launch saves there is less than it costs: a
     // zone of an exact histogram is one bucket, a few hundred candidates that one workgroup ranks without the two sliced
-    // passes: 4 rows of 65536, 81 -> 63 us, together with the plan's default for staging.  Longer rows keep the sliced passes for zones with many equal keys (one workgroup would take 0.24 ms
+    // passes: 4 rows of 65536, 81 -> 62 us.  Longer rows keep the sliced passes for zones with many equal keys (one workgroup would take 0.24 ms
     // for a row of 2.6e5 that is mostly zeros, as long as the passes).
     a.alone = pl->sample_shift == 0 && pl->d <= ((int64_t)1 << 17) ? 1 : 0;
     a.staging = pl->staging;
@@ -477,7 +477,10 @@ mlmc_status mlmc_plan(mlmc_plan_t** plan, int kind, int M, int64_t d, int in_dty
     // rows long enough that a second full read matters get their thresholds from a sampled histogram
     pl->sample_shift = d >= ((int64_t)1 << 23) ? 4 : d >= ((int64_t)1 << 21) ? 2 : 0;
     if (kind == MLMC_VBITS || kind == MLMC_RTN) pl->sample_shift = 0;   // the largest entry itself is needed, not its binade
-    pl->staging = (int64_t)M * d > ((int64_t)1 << 19) ? 1 : 0;   // a second read of fewer entries is cheaper than the launch that assembles staged lists
+    // Small adaptive plans of several rows take the second read instead of the kernel that assembles staged lists: 4 rows of 65536 90.5 us
+    // against 96.4, 16 of 30000 99.6 / 105.9.  One or two rows leave the second read too few workgroups (2 of 200000 112.9 / 110.7, or 146.3 /
+    // 125.0 where keys repeat), and with fixed p it gains nothing (4 of 65536 67.6 / 68.0, 76.3 / 70.7 where keys repeat).
+    pl->staging = p_fixed == nullptr && M >= 4 && (int64_t)M * d <= ((int64_t)1 << 19) ? 0 : 1;
     // The fork and the join cost some twenty microseconds of stream operations, paid in every call, while the second read
     // has work in a call only when some row's band was not staged: worth it for many long rows (measured: -11 us per call
     // at 16 rows of 2.6e7 elements, +5 us at 4 rows of 1.2e8).

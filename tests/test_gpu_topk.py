@@ -171,13 +171,14 @@ def test_message_kernels_side_by_side_or_in_turn():
             assert np.array_equal(out.cpu().numpy().view(np.uint32), O.aggregate_sparse(want, w.d, 1.0 / w.M).view(np.uint32))
 
 
-@pytest.mark.parametrize("d,default", [(4096, False), ((1 << 18) + 1, True)])
-def test_staging_hook_decides_whatever_the_size(d, default):
-    """The size of the plan chooses the default; the hook turns the staged message on and off on every plan."""
-    g = torch.randn((2, d), device="cuda:0")
-    plan = P.Plan(P.MLMC_TOPK, 2, d, P.MLMC_F32, [d // 16, d // 4, d], None)
+@pytest.mark.parametrize("M,d,adaptive,default", [(4, 4096, True, False), (4, 1 << 17, True, False), (4, (1 << 17) + 1, True, True),
+                                                   (3, 4096, True, True), (4, 4096, False, True)])
+def test_staging_hook_decides_whatever_the_size(M, d, adaptive, default):
+    """Size and probabilities of the plan choose the default; the hook turns the staged message on and off on every plan."""
+    g = torch.randn((M, d), device="cuda:0")
+    plan = P.Plan(P.MLMC_TOPK, M, d, P.MLMC_F32, [d // 16, d // 4, d], None if adaptive else [0.5, 0.5])
     staged = lambda: "k_filter" in launched(lambda: P.mlmc_compress_topk(plan, g, seed=1, step=0))
-    print(f"staging hook d={d}", flush=True)
+    print(f"staging hook M={M} d={d} adaptive={adaptive}", flush=True)
     assert staged() == default
     for on in (True, False, True):
         plan.set_staging(on)
