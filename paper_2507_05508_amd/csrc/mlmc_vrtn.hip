@@ -36,15 +36,15 @@ __device__ __forceinline__ uint32_t mad_u24(uint32_t a, uint32_t b, uint32_t c) 
 // Sums of squared residual integers, LV levels.  k_l = n_l D' - n_{l-1} D, so sum k_l^2 = D'^2 sum n_l^2 - 2 D D' sum n_l n_{l-1}
 // + D^2 sum n_{l-1}^2: per entry and level two products of codes below 2^15 (signs cancel in them), 24-bit multiply-adds that
 // meet in 32 bits for as many entries as fit, then in 64.  A code is the low word of |g| fl(D / 2c) + 1.5 2^52, formed with
-// the multiplier moved towards and away from zero as in k_rtn_extract; where the two differ it is computed the long way.  Bound
-// by instruction issue: with every code and residual in fp64 the kernel took 172 us for 8 rows of 1.17e7 at four levels, now 108
+// the multiplier moved towards and away from zero as in k_rtn_extract; where the two differ it is the even one.  Bound
+// by instruction issue: with every code and residual in fp64 the kernel took 172 us for 8 rows of 1.17e7 at four levels, now 106
 // (the bare read: 62).  Eight entries at a time and four waves per SIMD; sixteen, or two waves, took 10 % longer.
 template <int DT, int LV>
 __global__ __launch_bounds__(256, LV <= 4 ? 4 : 2) void k_rtn_norms(BitsArgs a) {
     const int row = blockIdx.y;
     const uint32_t ckey = a.racc[row].smpmax_key;
     if (ckey == 0u) return;   // a zero row: every residual is zero
-    const double c = key_to_double(ckey), den = 2.0 * c, inv_den = __ddiv_rn(1.0, den);
+    const double den = 2.0 * key_to_double(ckey);
     RowLoader<DT, true> ld(a.g, a.ld, a.d, row);
     double mul_in[LV + 1], mul_out[LV + 1];
 #pragma unroll
@@ -86,12 +86,14 @@ __global__ __launch_bounds__(256, LV <= 4 ? 4 : 2) void k_rtn_norms(BitsArgs a) 
                 cur[i] = (uint32_t)__double2loint(__fma_rn(av[i], mul_in[t], 0x1.8p52));
                 differ |= cur[i] ^ (uint32_t)__double2loint(__fma_rn(av[i], mul_out[t], 0x1.8p52));
             }
-            if (__builtin_expect(__ballot(differ != 0u) != 0ull, 0)) {
-                const RtnCode code = rtn_code_of(a.F[t]);
+            if (__ballot(differ != 0u) != 0ull) {   // a tie: the even one; the largest entry's code is cut
+                const uint32_t N = (1u << (a.F[t] - 1)) - 1u;
 #pragma unroll
-                for (int i = 0; i < 8; ++i)
-                    if (cur[i] != (uint32_t)__double2loint(__fma_rn(av[i], mul_out[t], 0x1.8p52)))
-                        cur[i] = (uint32_t)rtn_code_abs(av[i], code, c, den, inv_den);
+                for (int i = 0; i < 8; ++i) {
+                    const uint32_t out = (uint32_t)__double2loint(__fma_rn(av[i], mul_out[t], 0x1.8p52));
+                    cur[i] = cur[i] & 1u ? out : cur[i];
+                    cur[i] = cur[i] < N ? cur[i] : N;
+                }
             }
             dot(cur, cur, 2 * a.F[t] - 2, sqr[t]);
             if (t > 0 && a.F[t - 1] > 0) dot(cur, prev, a.F[t] + a.F[t - 1] - 2, prod[t]);
@@ -123,7 +125,9 @@ __global__ __launch_bounds__(256, LV <= 4 ? 4 : 2) void k_rtn_norms(BitsArgs a) 
                 uint32_t prev = 0;
 #pragma unroll
                 for (int t = 0; t <= LV; ++t) {
-                    const uint32_t cur = a.F[t] > 0 ? (uint32_t)rtn_code_abs(av, rtn_code_of(a.F[t]), c, den, inv_den) : 0u;
+                    const uint32_t N = a.F[t] > 0 ? (1u << (a.F[t] - 1)) - 1u : 0u, in = (uint32_t)__double2loint(__fma_rn(av, mul_in[t], 0x1.8p52));
+                    uint32_t cur = in & 1u ? (uint32_t)__double2loint(__fma_rn(av, mul_out[t], 0x1.8p52)) : in;
+                    cur = cur < N ? cur : N;
                     sqr[t] += cur * cur;
                     if (t > 0) prod[t] += cur * prev;
                     prev = cur;
@@ -321,8 +325,9 @@ struct RtnPlaneCode {    // one of the (up to three) codes of a row's message
 // 1.5 2^52 leaves the rounded integer, sign included, in the low word.  Rounding the multiplier can only matter at an
 // exact half-integer (the exact quotient is otherwise at least 2^-40 of itself away from one: its numerator is an
 // integer below 2^40), so the product is formed twice, with the multiplier moved 2^-44 towards and away from zero:
-// where the two agree the code is exact; a block where they differ anywhere (a tie; always at the largest entry itself,
-// whose code is cut) and a row of non-finite numbers have their codes computed the long way.
+// where the two agree the code is exact; they differ at a tie and only there, and the code is the even one of them (at the
+// largest entry itself, D / 2, it is cut).  A block with a tie is formed twice; rows with few significant bits (16-bit ones, or such
+// widened) may tie in every block: 8 rows of 1.17e7 fp32 entries, compress, 272 us, 338 with ties everywhere (1829 with a division each).
 // A block's elements stay in LDS and are read once per code, so that the codes in the making are all the registers hold.
 template <int DT>
 __global__ __launch_bounds__(EX_THREADS, 4) void k_rtn_extract(BitsArgs a) {
@@ -354,8 +359,9 @@ __global__ __launch_bounds__(EX_THREADS, 4) void k_rtn_extract(BitsArgs a) {
     }
     __syncthreads();
     unsigned char* buf = s_buf[wave];
+    const bool nonfinite = ckey >= 0x7F800000u;
     for_blocks(ld, buf, blk, stride, nblk, nwhole, [&](int64_t at_blk) {
-        uint32_t x[32], tie = ckey >= 0x7F800000u ? 1u : 0u;
+        uint32_t x[32], tie = nonfinite ? 1u : 0u;
 #pragma unroll
         for (int i = 0; i < 32; ++i) x[i] = 0;
 #pragma unroll 1
@@ -377,30 +383,55 @@ __global__ __launch_bounds__(EX_THREADS, 4) void k_rtn_extract(BitsArgs a) {
                 }
             }
         }
-        if (__builtin_expect(__ballot(tie != 0u) != 0ull, 0)) {
-            RowLoader<DT, false> ld1(a.g, a.ld, a.d, row);
-            const int64_t j0 = at_blk * EX_ELEMS + 32 * (int64_t)lane;
-            const double inv_den = c > 0.0 ? __ddiv_rn(1.0, den) : 0.0;
-            wave_lds_sync();   // every lane has read its elements: their place takes the codes
-            uint32_t* mine = (uint32_t*)buf + 32 * lane;
+        if (__ballot(tie != 0u) != 0ull) {
+            // again, four of a lane's elements at a time: in LDS they take the place of the block, the codes theirs
+            wave_lds_sync();
+            const uint32_t from = ld.take_at(wave * (EX_ELEMS * 4));
+#pragma unroll
+            for (int h = 0; h < Loader::CPL; ++h) {
+                uint32_t b[Loader::EPC];
+                ld.take_chunk(&s_buf[0][0], from, h, b);
+#pragma unroll
+                for (int i = 0; i < Loader::EPC; ++i) x[h * Loader::EPC + i] = b[i];
+            }
+            wave_lds_sync();   // every lane has read its elements
+            uint32_t* mine = (uint32_t*)buf + lane;
+            auto slot = [&](int i) -> uint32_t& { return mine[64 * i]; };
+#pragma unroll
+            for (int i = 0; i < 32; ++i) slot(i) = x[i];
 #pragma unroll 1
-            for (int i = 0; i < 32; ++i) {
-                uint32_t v = 0;
-                const uint32_t bits = j0 + i < a.d ? ld1.load1(j0 + i) : 0u;
+            for (int i = 0; i < 32; i += 4) {
+                double av[4];
+                uint32_t v[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const uint32_t bits = slot(i + u);
+                    av[u] = (double)__uint_as_float(bits);
+                    if (nonfinite) {   // uniform: Inf and NaN are the numbers their bit patterns spell, as in c
+                        av[u] = key_to_double(key_of_bits(bits));
+                        av[u] = (int32_t)bits < 0 ? -av[u] : av[u];
+                    }
+                    v[u] = 0;
+                }
 #pragma unroll 1
                 for (int k = 0; k < nc; ++k) {
-                    const RtnCode kc = s_code[k].code;
-                    int32_t n = c > 0.0 ? rtn_code_abs(key_to_double(key_of_bits(bits)), kc, c, den, inv_den) : 0;
-                    n = (int32_t)bits < 0 ? -n : n;
-                    v |= ((uint32_t)n & ((1u << kc.b) - 1u)) << s_code[k].at;
+                    const double mul_in = s_code[k].mul_in, mul_out = s_code[k].mul_out;
+                    const uint32_t mask = (1u << s_code[k].code.b) - 1u, at = (uint32_t)s_code[k].at;
+                    const int N = s_code[k].code.N;
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        int n = __double2loint(__fma_rn(av[u], mul_in, 0x1.8p52));
+                        const int m = __double2loint(__fma_rn(av[u], mul_out, 0x1.8p52));
+                        n = n & 1 ? m : n;
+                        n = n < -N ? -N : n > N ? N : n;
+                        v[u] |= ((uint32_t)n & mask) << at;
+                    }
                 }
-                mine[i] = v;
+#pragma unroll
+                for (int u = 0; u < 4; ++u) slot(i + u) = v[u];
             }
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const uint4 v = ((const uint4*)mine)[i];
-                x[4 * i] = v.x; x[4 * i + 1] = v.y; x[4 * i + 2] = v.z; x[4 * i + 3] = v.w;
-            }
+            for (int i = 0; i < 32; ++i) x[i] = slot(i);
         }
         if (at_blk * 64 + lane < a.nwords * 2) {   // a plane's half words end inside the row's last block
             PlaneWriter w(a, row, at_blk);

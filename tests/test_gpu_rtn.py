@@ -77,6 +77,24 @@ def test_rtn_ties_adversarial_padded_and_bf16_rows():
         _check(planb, Gf, [0, 2, 4, 8], None, 1, step, msg)
 
 
+@pytest.mark.parametrize("B", [[0, 2, 4, 8, 16], [5, 9, 16], [3, 8]])
+@pytest.mark.parametrize("dtype", [P.MLMC_F32, P.MLMC_BF16])
+def test_rtn_rows_that_tie_in_every_block(B, dtype):
+    """The largest entry's significand is a multiple of 2^b - 1 or shares factors with it, so that odd multiples of the others fall
+    halfway between two codes at several widths, of either sign, up to the last partial block."""
+    d = 3 * 2048 + 77
+    rng = np.random.default_rng(4)
+    G = (rng.integers(0, 120, size=(4, d)) * rng.choice([-1, 1], size=(4, d))).astype(np.float32)
+    G[:, d - 1] = [255.0, -153.0, 231.0, 127.0]   # 255 = 3 5 17, 153 = 9 17, 231 = 3 7 11; 127 = 2^7 - 1
+    G[3] *= np.float32(2.0 ** -140) if dtype == P.MLMC_F32 else np.float32(2.0 ** -100)   # subnormals
+    plan = P.Plan(P.MLMC_RTN, 4, d, dtype, B, None)
+    g = to_device(W.f32_to_bf16_bits(G) if dtype == P.MLMC_BF16 else G)
+    for step in range(4):
+        print(f"rtn ties B={B} dtype={dtype} step={step}", flush=True)
+        msg = P.mlmc_compress_rtn(plan, g, seed=5, step=step)
+        _check(plan, G, B, None, 5, step, msg)
+
+
 @pytest.mark.parametrize("seed", [7, 8])
 def test_rtn_random_plans_and_inputs(seed):
     """Randomised valid calls (row counts, lengths, ladders, value families with zeros and extreme scales, padded rows),
