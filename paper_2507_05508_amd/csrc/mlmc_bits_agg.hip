@@ -2,8 +2,8 @@
 //
 //   k_bits_prep     level draw of every row (floating-point ladder; the other ladders draw in k_bits_smax)
 //   k_bits_smax     largest |g| key of a sample of every row -> predicted power-of-two scale; level draw             [mlmc_extract.h]
-//   k_bits_extract  the one full read: digits floor(|g_j| / s * 2^F), sign plane + field planes packed by wave      [mlmc_extract.h]
-//                   ballot, and the true row maximum; a row whose true maximum has a larger exponent than the
+//   k_bits_extract  the one full read: digits floor(|g_j| / s * 2^F), sign plane + field planes by bit transposes   [mlmc_extract.h]
+//                   inside a lane, and the true row maximum; a row whose true maximum has a larger exponent than the
 //                   sampled one is extracted again by a second launch (which returns at once for every other row)
 //   k_agg_planes    out = alpha * sum_i decode_i, rows added in worker order (all plane messages, Round-to-Nearest included)
 //   k_tileoff       (fallback) per-tile offsets of index-sorted sparse rows by binary search

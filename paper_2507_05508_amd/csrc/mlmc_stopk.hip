@@ -1,7 +1,7 @@
 // s-segmented Top-k MLMC on gfx950 (Sec. 2.2 "s-Top-k", Sec. 3.2, Lemma 3.4, App. D): the ladder k_l = min(s l, d),
 // l = 0..L = ceil(d / s), g^0 = 0, adaptive level probabilities over all L bands.  The residual of level l is the
 // l-th segment of the row sorted by magnitude.  Ladders of up to SE_LMAX levels are handled without a sort (second half of this
-// file); longer ones, whose segments are a few entries, sort the whole row once:
+// file); longer ones, whose segments are a few entries, short rows and few short rows of 16 bits sort the whole row once:
 //
 //   k_rs_hist / k_rs_scan / k_rs_scatter   stable least-significant-digit radix sort of {inverted |g| key, index} pairs,
 //                 8 bits per pass (4 passes for fp32, 2 for bf16 inputs whose keys have 16 significant bits); the

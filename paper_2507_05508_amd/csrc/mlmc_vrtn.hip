@@ -467,7 +467,7 @@ mlmc_status rtn_compress(const mlmc_plan_t* pl, const BitsArgs& a, bool message,
     int64_t nw = (pl->d + 4 * 256 * 8 - 1) / (4 * 256 * 8);   // a thread takes at least about eight groups of four elements
     const int64_t ncap = 2048 / M > 0 ? 2048 / M : 1;          // eight workgroups per CU in all: few atomics per sum
     if (nw > ncap) nw = ncap;
-    const int64_t nmin = (pl->d + ((int64_t)1 << 24) - 1) >> 24;   // a thread adds at most 2^16 squares below 2^36: exact in fp64
+    const int64_t nmin = (pl->d + ((int64_t)1 << 24) - 1) >> 24;   // a thread adds at most 2^16 squares below 2^36, a workgroup 2^60 in all
     if (nw < nmin) nw = nmin;
     if (nw < 1) nw = 1;
     const dim3 ngrid((unsigned)nw, M);
