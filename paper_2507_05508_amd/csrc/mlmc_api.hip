@@ -13,6 +13,7 @@ namespace mlmc {
 mlmc_status topk_zero(const mlmc_plan_t* pl, void* ws, int32_t* dev_status, hipStream_t st);
 mlmc_status topk_select(const mlmc_plan_t* pl, const TopkArgs& a, bool sums, bool vec, hipStream_t st);
 mlmc_status topk_compact(const mlmc_plan_t* pl, const TopkArgs& a, bool vec, hipStream_t st);
+mlmc_status topk16_run(const mlmc_plan_t* pl, const TopkArgs& a, bool message, hipStream_t st);
 mlmc_status bits_compress(const mlmc_plan_t* pl, const BitsArgs& a, hipStream_t st);
 mlmc_status rtn_compress(const mlmc_plan_t* pl, const BitsArgs& a, bool message, hipStream_t st);
 mlmc_status agg_bits(const mlmc_plan_t* pl, const BitsArgs& b, const int32_t* level, const int32_t* scale_exp,
@@ -53,7 +54,7 @@ static const char* const k_names[K_NUM] = {
     "k_zero", "k_hist", "k_scan", "k_main", "k_fhist", "k_finish", "k_finish_rank", "redo_pass", "k_norms", "k_bits_prep", "k_msgplan", "k_filter", "k_write",
     "k_bits_smax", "k_bits_extract", "k_bits_redo", "k_agg_bits", "k_tileoff", "k_agg_sparse", "k_message_bits", "k_rtn_norms", "k_rtn_draw",
     "k_rs_hist", "k_rs_scan", "k_rs_scatter", "k_sb_norms", "k_sb_draw", "k_sb_mark", "k_sb_offsets", "k_sb_write", "k_se_count", "k_se_scan",
-    "k_se_split", "k_se_zone"};
+    "k_se_split", "k_se_zone", "k_c16_hist", "k_c16_scan", "k_c16_mark", "k_c16_write"};
 struct ProfPair { int id; hipEvent_t e0, e1; };
 static std::vector<ProfPair> g_pending;
 static std::vector<ProfPair> g_free;
@@ -98,11 +99,8 @@ void prof_end(int id, hipStream_t st) {
     g_open = false;
 }
 
-// rows can be read with aligned 16-byte (fp32) / 8-byte (bf16) loads
-static bool vec_ok(const mlmc_plan_t* pl, const void* g, int64_t ld) {
-    if (pl->dtype == MLMC_F32) return ((uintptr_t)g % 16 == 0) && (ld % 4 == 0);
-    return ((uintptr_t)g % 8 == 0) && (ld % 4 == 0);
-}
+// 32-bit rows can be read with aligned 16-byte loads
+static bool vec_ok(const void* g, int64_t ld) { return ((uintptr_t)g % 16 == 0) && (ld % 4 == 0); }
 
 static void fill_topk_args(const mlmc_plan_t* pl, TopkArgs& a, const void* g, int64_t ld, void* ws, int32_t* dev_status) {
     std::memset(&a, 0, sizeof(a));
@@ -112,7 +110,6 @@ static void fill_topk_args(const mlmc_plan_t* pl, TopkArgs& a, const void* g, in
     a.d = pl->d;
     a.M = pl->M;
     a.L = pl->L;
-    a.dtype = pl->dtype;
     for (int t = 0; t <= pl->L; ++t) a.k[t] = pl->ladder[t];
     a.chunk = pl->chunk;
     a.chunks_per_row = pl->chunks_per_row;
@@ -154,6 +151,14 @@ static void fill_topk_args(const mlmc_plan_t* pl, TopkArgs& a, const void* g, in
     a.priv_cnt = (uint32_t*)(w + pl->off_priv_cnt);
     a.chunk_base = (uint32_t*)(w + pl->off_chunk_base);
     a.row_order = (int32_t*)(w + pl->off_row_order);
+    a.c16_part = (uint32_t*)(w + pl->off_c16_part);
+    a.c16_wgs = pl->c16_wgs;
+    a.c16_slice = pl->c16_slice;
+    if (pl->off_c16_list) {
+        a.c16_list = (uint32_t*)(w + pl->off_c16_list);
+        a.c16_cnt = (uint4*)(w + pl->off_c16_cnt);
+        a.c16_pre = (uint4*)(w + pl->off_c16_pre);
+    }
     a.dev_status = dev_status;
 }
 
@@ -489,7 +494,10 @@ mlmc_status mlmc_plan(mlmc_plan_t** plan, int kind, int M, int64_t d, int in_dty
     size_t off = 0;
     pl->off_racc = off;
     off = align_up(off + sizeof(RowAcc) * (size_t)M, 256);
-    if (kind == MLMC_TOPK) {
+    // 16-bit rows have few enough magnitudes to count them all, at any size: compress, adaptive, us, against the way of the 32-bit rows, 1 row of 16384
+    // 73 -> 35, 32 of 16385 114 -> 56, 4 of 2500000 192 -> 68, 1024 of 16384 959 -> 277, 4 of 30000001 358 -> 193; rows of one value, 4 of 2500000, 22828 -> 99.
+    const bool counted = kind == MLMC_TOPK && in_dtype == MLMC_BF16;
+    if (kind == MLMC_TOPK && !counted) {
         pl->off_hist = off;
         off = align_up(off + sizeof(uint32_t) * NB1 * (size_t)M, 256);
         pl->off_hist2 = off;
@@ -524,7 +532,29 @@ mlmc_status mlmc_plan(mlmc_plan_t** plan, int kind, int M, int64_t d, int in_dty
             off = align_up(off + sizeof(uint32_t) * 32768 * (size_t)M, 256);
         }
     }
-    if (kind == MLMC_TOPK) {
+    if (counted) {
+        int64_t wgs = 256 / M > 0 ? 256 / M : 1;   // one workgroup per CU in one round
+        if (wgs > (d + 16383) / 16384) wgs = (d + 16383) / 16384;
+        pl->c16_slice = ((d + wgs - 1) / wgs + TILE - 1) / TILE * TILE;
+        pl->c16_wgs = (int)((d + pl->c16_slice - 1) / pl->c16_slice);
+        pl->off_c16_part = off;
+        off = align_up(off + sizeof(uint32_t) * 32768 * (size_t)(pl->c16_wgs + 1) * M, 256);
+        // The message read by slices (one launch) against the one by tiles (three), compress, us: 32 rows of 1000003 (slices of 126976) 102 to 108 / 92 to 117,
+        // 4 of 2500000 67 / 71 to 83; 8 of 11689512 (slices of 368640) 184 / 166, 4 of 30000001 219 / 193, 1 of 1e8 176 / 169, 4 of 1.24e8 with
+        // stretches of many scales 700 / 480.  Rows of one value, all of which may be in the message, are slower by tiles (604 / 796).
+        if (pl->c16_slice >= (1 << 18)) {
+            pl->off_c16_list = off;
+            off = align_up(off + sizeof(uint32_t) * TILE * (size_t)pl->ntiles * M, 256);
+            pl->off_c16_cnt = off;
+            off = align_up(off + sizeof(uint4) * (size_t)pl->ntiles * M, 256);
+            pl->off_c16_pre = off;
+            off = align_up(off + sizeof(uint4) * (size_t)pl->ntiles * M, 256);
+        }
+        pl->off_tileoff = off;
+        off = align_up(off + sizeof(uint32_t) * (size_t)(pl->ntiles + 1) * M, 256);
+        pl->off_norms = off;
+        off = align_up(off + sizeof(double) * (size_t)L * M, 256);
+    } else if (kind == MLMC_TOPK) {
         pl->off_table = off;
         off = align_up(off + sizeof(uint32_t) * NB1 * (size_t)M, 256);
         pl->off_chunk_cnt = off;
@@ -619,9 +649,10 @@ mlmc_status mlmc_level_norms(const mlmc_plan_t* plan, const void* g, int64_t ld,
     a.all_thresholds = 1;
     a.draw_mode = -1;  // norms only, no draw
     a.norms_user = norms;
+    if (plan->c16_wgs) return topk16_run(plan, a, false, st);
     mlmc_status rc = topk_zero(plan, ws, dev_status, st);
     if (rc != MLMC_OK) return rc;
-    return topk_select(plan, a, true, vec_ok(plan, g, ld), st);
+    return topk_select(plan, a, true, vec_ok(g, ld), st);
 }
 
 mlmc_status mlmc_compress_topk(const mlmc_plan_t* plan, const void* g, int64_t ld, const double* p, int p_is_norms,
@@ -646,7 +677,7 @@ mlmc_status mlmc_compress_topk(const mlmc_plan_t* plan, const void* g, int64_t l
         sa.step = step;
         return stopk_run(plan, sa, true, st);
     }
-    const bool vec = vec_ok(plan, g, ld);
+    const bool vec = vec_ok(g, ld);
     const bool internal_norms = plan->adaptive && p == nullptr;
     TopkArgs a;
     fill_topk_args(plan, a, g, ld, ws, dev_status);
@@ -670,6 +701,7 @@ mlmc_status mlmc_compress_topk(const mlmc_plan_t* plan, const void* g, int64_t l
     } else {
         a.draw_mode = 3;
     }
+    if (plan->c16_wgs) return topk16_run(plan, a, true, st);
     mlmc_status rc = topk_zero(plan, ws, dev_status, st);
     if (rc != MLMC_OK) return rc;
     // draw_mode < 3: the level is drawn before the data is touched (inside the threshold scan), so only

@@ -1,0 +1,66 @@
+// Counting the magnitudes of 16-bit rows, shared by the translation units that do it (rank ladder, Round-to-Nearest).
+#pragma once
+#include "mlmc_device.h"
+
+namespace mlmc {
+
+constexpr int C16_KEYS = 1 << 15;       // magnitudes of a 16-bit entry: its bits without the sign
+constexpr int C16_THREADS = 1024;
+constexpr int C16_LDS = C16_KEYS + 64;  // words: a counter per magnitude; zeros are counted per lane behind them
+
+typedef uint32_t u32x4_b16 __attribute__((ext_vector_type(4), aligned(2)));
+
+// Counts of the magnitudes of entries [i0, i1) of a 16-bit row, in LDS (s_h[C16_LDS]), by a workgroup of C16_THREADS threads; at the
+// return every counter is final (s_h[0] among them).  One LDS atomic per entry.  Zeros, which a gradient may mostly consist of, go to a
+// counter per lane: on one word the lanes of a wave take turns.  16-byte loads (8 entries) at any alignment, past the cache, four of a wave's in
+// flight while four are counted: bound by the read, 4 rows of 1.24e8 entries in 166 us (6.0 TB/s; with plain 8-byte loads 188).
+__device__ __forceinline__ void count16_slice(const uint16_t* row, int64_t i0, int64_t i1, uint32_t* s_h) {
+    const int tid = threadIdx.x;
+    for (int i = tid; i < C16_LDS / 4; i += C16_THREADS) ((uint4*)s_h)[i] = make_uint4(0, 0, 0, 0);
+    __syncthreads();
+    const uint32_t lane = lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    constexpr int NW = C16_THREADS / 64, PIECE = 2048;
+    char* h = (char*)s_h;
+    const uint32_t zero_at = (uint32_t)(C16_KEYS * 4) + lane * 4u;
+    auto count1 = [&](uint32_t at) { atomicAdd((uint32_t*)(h + (at ? at : zero_at)), 1u); };
+    auto count2 = [&](uint32_t w) {
+        count1((w << 2) & 0x1FFFCu);
+        count1((w >> 14) & 0x1FFFCu);
+    };
+    auto fetch = [&](int64_t p, u32x4_b16 (&b)[4]) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) b[q] = __builtin_nontemporal_load((const u32x4_b16*)(row + i0 + p * PIECE + q * 512 + lane * 8));
+    };
+    auto use = [&](const u32x4_b16 (&b)[4]) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) { count2(b[q].x); count2(b[q].y); count2(b[q].z); count2(b[q].w); }
+    };
+    const int64_t n = i1 > i0 ? (i1 - i0) / PIECE : 0;   // whole pieces; wave w takes w, w + NW, ...
+    u32x4_b16 b0[4], b1[4];
+    int64_t p = wave;
+    if (p < n) {
+        fetch(p, b0);
+        while (true) {   // uniform
+            const bool more1 = p + NW < n;
+            if (more1) fetch(p + NW, b1);
+            use(b0);
+            if (!more1) break;
+            p += NW;
+            const bool more0 = p + NW < n;
+            if (more0) fetch(p + NW, b0);
+            use(b1);
+            if (!more0) break;
+            p += NW;
+        }
+    }
+    for (int64_t j = i0 + n * PIECE + tid; j < i1; j += C16_THREADS) count1(((uint32_t)row[j] << 2) & 0x1FFFCu);
+    __syncthreads();
+    if (wave == 0) {
+        const uint32_t z = wave_sum(s_h[C16_KEYS + lane]);
+        if (lane == 0) s_h[0] = z;
+    }
+    __syncthreads();
+}
+
+}  // namespace mlmc

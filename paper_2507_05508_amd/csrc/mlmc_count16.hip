@@ -1,0 +1,788 @@
+// Top-k MLMC of 16-bit rows on gfx950.  A 16-bit row has at most 2^15 magnitudes: one read that counts them gives every rank threshold,
+// every band's exact sum of squares and, slice by slice, where the message of a slice begins, so that a second read writes it.
+//
+//   k_c16_hist    first read: counts of a slice of a row in LDS, one workgroup per slice                      [mlmc_count16.h]
+//   k_c16_reduce  per magnitude: the row's total and, short slices, the entries in the slices before each slice
+//   k_c16_scan    per row: threshold keys and how many of their equals are inside, norms (Lemma 3.4), level draw
+//   k_c16_write   short slices: the second read writes the message, a slice per workgroup
+//   k_c16_mark, k_c16_offsets, k_c16_expand   long slices: the second read leaves the tiles' entries in lists, which become the message
+//
+// Against the way of the 32-bit rows (sampled histogram, selection read with candidate lists, ranking, message from staged lists), which these
+// rows took before, adaptive, compress + aggregate: 4 rows of 1.24e8 entries 777 -> 512 us, 32 of 1e6 289 -> 135.
+#include "mlmc_count16.h"
+
+namespace mlmc {
+
+// One workgroup per (slice, row), one per CU: the counters fill its LDS.  Bound by the read.
+__global__ __launch_bounds__(C16_THREADS) void k_c16_hist(TopkArgs a) {
+    __shared__ __align__(16) uint32_t s_h[C16_LDS];
+    const int row = blockIdx.y;
+    if (row == 0 && blockIdx.x == 0 && threadIdx.x == 0) *a.dev_status = 0;   // nothing of this launch reports through it
+    const int64_t i0 = (int64_t)blockIdx.x * a.c16_slice, i1 = i0 + a.c16_slice < a.d ? i0 + a.c16_slice : a.d;
+    count16_slice((const uint16_t*)a.g + (int64_t)row * a.ld, i0, i1, s_h);
+    uint4* part = (uint4*)(a.c16_part + ((size_t)row * (a.c16_wgs + 1) + blockIdx.x) * C16_KEYS);
+    for (int i = threadIdx.x; i < C16_KEYS / 4; i += C16_THREADS) part[i] = ((const uint4*)s_h)[i];
+}
+
+// Slice c16_wgs of c16_part: the totals; BEFORE: the counts of slice s become those of the slices before it.  G groups of consecutive
+// slices are taken side by side, at most C16_PER slices each, so that a thread's loads are all in flight at once.
+constexpr int C16_PER = 16;
+template <int G, bool BEFORE>
+__global__ __launch_bounds__(64 * G) void k_c16_reduce(TopkArgs a) {
+    __shared__ uint32_t s_sum[G][64];
+    const int W = a.c16_wgs, grp = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int per = (W + G - 1) / G, s0 = grp * per, n = s0 >= W ? 0 : (s0 + per < W ? per : W - s0);
+    uint32_t* p = a.c16_part + (size_t)blockIdx.y * (W + 1) * C16_KEYS + blockIdx.x * 64 + lane;
+    uint32_t v[C16_PER], sum = 0;
+#pragma unroll
+    for (int i = 0; i < C16_PER; ++i) v[i] = i < n ? p[(size_t)(s0 + i) * C16_KEYS] : 0u;
+#pragma unroll
+    for (int i = 0; i < C16_PER; ++i) sum += v[i];
+    s_sum[grp][lane] = sum;
+    __syncthreads();
+    uint32_t run = 0, total = 0;
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        const uint32_t t = s_sum[g][lane];
+        run += g < grp ? t : 0u;
+        total += t;
+    }
+    if (BEFORE) {
+#pragma unroll
+        for (int i = 0; i < C16_PER; ++i) {
+            if (i < n) p[(size_t)(s0 + i) * C16_KEYS] = run;
+            run += v[i];
+        }
+    }
+    if (grp == 0) p[(size_t)W * C16_KEYS] = total;
+}
+
+// One workgroup per row.  thr_tau[t]: the magnitude at rank k_t - 1 (C16_KEYS: k_t == 0); thr_jx[t]: how many entries equal to it, in index
+// order, are within the top k_t.
+__global__ __launch_bounds__(1024) void k_c16_scan(TopkArgs a) {
+    __shared__ uint32_t s_scan[17];
+    __shared__ int64_t s_k[TMAX];
+    __shared__ uint32_t s_big[TMAX][20];
+    __shared__ unsigned long long s_wide[TMAX][20];
+    __shared__ double s_norm[LMAX];
+    __shared__ uint32_t s_top;
+    const int row = blockIdx.x, tid = threadIdx.x, L = a.L;
+    RowInfo* ri = a.rinfo + row;
+    const int lo_key = C16_KEYS - 32 * (tid + 1);   // this thread's 32 magnitudes: lo_key .. lo_key + 31, descending with the thread
+    uint32_t n[32];
+    {
+        const uint4* src = (const uint4*)(a.c16_part + ((size_t)row * (a.c16_wgs + 1) + a.c16_wgs) * C16_KEYS + lo_key);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const uint4 q = src[i];
+            n[4 * i] = q.x; n[4 * i + 1] = q.y; n[4 * i + 2] = q.z; n[4 * i + 3] = q.w;
+        }
+    }
+    if (tid <= L) s_k[tid] = a.k[tid];
+    for (int i = tid; i < TMAX * 20; i += 1024) (&s_wide[0][0])[i] = 0ull;
+    if (tid == 0) s_top = 0u;
+    uint32_t sum = 0;
+    int top = -1;
+#pragma unroll
+    for (int i = 0; i < 32; ++i) { sum += n[i]; if (n[i]) top = i; }
+    uint32_t total;
+    const uint32_t before = block_excl_scan<1024>(sum, s_scan, total);
+    if (sum && before == 0u) s_top = (uint32_t)(lo_key + top);   // the row's largest magnitude: one thread
+    if (tid == 0 && (int64_t)total != a.d) atomicOr(a.dev_status, MLMC_DEV_INTERNAL);
+    if (tid <= L && s_k[tid] == 0) { ri->thr_tau[tid] = (uint32_t)C16_KEYS; ri->thr_jx[tid] = 0u; }
+    if (sum) {
+        const int64_t r0 = before;   // rank of this thread's first entry
+        int t = 0;
+        while (t <= L && s_k[t] <= r0) ++t;   // the first band boundary behind rank r0: rank r0 lies in band t
+        const int E = lo_key >> 7, e1 = E ? E : 1;   // one exponent for all 32
+        const int sh = 2 * (e1 - 1) + 32;
+        uint64_t acc = 0;
+        if (t > L || s_k[t] > r0 + (int64_t)sum) {   // all of them in one band
+#pragma unroll
+            for (int i = 0; i < 32; ++i) {
+                const uint32_t sig = (uint32_t)((lo_key + i) & 127) | (E ? 128u : 0u);
+                acc += (uint64_t)n[i] * (sig * sig);   // the square of the significand in units of 2^32
+            }
+        } else {
+            int64_t r = r0;
+#pragma unroll
+            for (int i = 31; i >= 0; --i) {
+                const uint32_t sig = (uint32_t)((lo_key + i) & 127) | (E ? 128u : 0u);
+                const uint64_t sq = sig * sig;
+                int64_t left = n[i];
+                while (t <= L && s_k[t] <= r + left) {   // boundary t lies among these entries or right behind them
+                    const int64_t take = s_k[t] - r;
+                    ri->thr_tau[t] = (uint32_t)(lo_key + i);
+                    ri->thr_jx[t] = n[i] - (uint32_t)(left - take);
+                    acc += (uint64_t)take * sq;
+                    if (a.all_thresholds && t >= 1) wide_add(s_wide[t], acc, sh);
+                    acc = 0;
+                    left -= take;
+                    r += take;
+                    ++t;
+                }
+                acc += (uint64_t)left * sq;
+                r += left;
+            }
+        }
+        if (a.all_thresholds && t >= 1 && t <= L) wide_add(s_wide[t], acc, sh);
+    }
+    __syncthreads();
+    if (a.all_thresholds && tid >= 1 && tid <= L) {
+        const double nrm = __dsqrt_rn(wide_to_double(s_wide[tid], s_big[tid]));
+        s_norm[tid - 1] = nrm;
+        a.norms[(size_t)row * L + (tid - 1)] = nrm;
+        if (a.norms_user) a.norms_user[(size_t)row * L + (tid - 1)] = nrm;
+    }
+    __syncthreads();
+    if (tid == 0) {
+        ri->topkey = s_top;
+        if (s_top >= 0x7F80u) atomicOr(a.dev_status, MLMC_DEV_NONFINITE);
+    }
+    if (tid < 64 && a.draw_mode >= 0) draw_row(a, row, s_norm);
+}
+
+// Inclusive sum over the lanes of a wave, two 16-bit halves side by side.
+__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, true);   // row_shr:1
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, true);   // row_shr:2
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, true);   // row_shr:4
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, true);   // row_shr:8
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);  // row_bcast:15 into rows 1 and 3
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);  // row_bcast:31 into rows 2 and 3
+    return v;
+}
+
+// ---------------------------------------------------------------------------------------------------
+// A step of the message kernels: C16_STEP entries, a wave takes 1024 consecutive ones in two loads, a lane 8 of either half.
+constexpr int C16_STEP = 16 * C16_THREADS;
+constexpr int C16_WAVES = C16_THREADS / 64;
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ u16x2 both16(int32_t x) { const u16x2 r = {(uint16_t)x, (uint16_t)x}; return r; }
+// key in [from, from + n), per half: non-zero where it is (wraps below `from`, 0 <= n <= 2^15)
+__device__ __forceinline__ u16x2 in_range16(u16x2 key, u16x2 from, u16x2 n) { return __builtin_elementwise_sub_sat(n, (u16x2)(key - from)); }
+// bit e of the result: entry e of a lane's 16 satisfies f (non-zero halves per pair of keys), two entries per instruction
+template <class F>
+__device__ __forceinline__ uint32_t mask16(const uint32_t (&b)[8], F f) {
+    const u16x2 one = {1, 1};
+    uint32_t acc = 0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const u16x2 r = __builtin_elementwise_min(f(__builtin_bit_cast(u16x2, b[i] & 0x7FFF7FFFu)), one);
+        acc |= __builtin_bit_cast(uint32_t, r) << (2 * i);
+    }
+    return (acc & 0x5555u) | ((acc >> 15) & 0xAAAAu);
+}
+// A lane's entries of the step that starts at entry j of the row (j: the lane's own first entry), [j, i1) of it there.
+__device__ __forceinline__ void fetch_step(const uint16_t* g, int64_t j, u32x4_b16 (&v)[2]) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) v[h] = __builtin_nontemporal_load((const u32x4_b16*)(g + j + 512 * h));
+}
+__device__ __forceinline__ uint32_t fetch_part(const uint16_t* g, int64_t j, int64_t i1, u32x4_b16 (&v)[2]) {   // a step that ends early: which entries are there
+    uint32_t valid = 0;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int64_t jh = j + 512 * h, left = i1 - jh;
+        v[h] = (u32x4_b16){0u, 0u, 0u, 0u};
+        if (left >= 8) {
+            v[h] = __builtin_nontemporal_load((const u32x4_b16*)(g + jh));
+            valid |= 0xFFu << (8 * h);
+        } else if (left > 0) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                if (e < left) {
+                    v[h][e >> 1] |= (uint32_t)g[jh + e] << (16 * (e & 1));
+                    valid |= 1u << (8 * h + e);
+                }
+        }
+    }
+    return valid;
+}
+__device__ __forceinline__ void words_of(const u32x4_b16 (&v)[2], uint32_t (&b)[8]) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) b[i] = v[i >> 2][i & 3];
+}
+
+// The three thresholds of a row's message (0, l-1, l) as a stretch of the row sees them: an entry is inside the i-th when its key is at least
+// lo[i]; where `cut` has bit i, `left[i]` of the entries equal to tau[i] = lo[i] - 1, in index order, are inside too (fewer than there are).
+struct C16Cuts {
+    int32_t lo[3], tau[3];
+    uint32_t left[3];
+    uint32_t cut;
+};
+// `before` entries equal to tau lie in front of the stretch, `here` in it, q in all are inside.
+__device__ __forceinline__ void set_cut(C16Cuts& c, int i, int32_t tau, uint32_t before, uint32_t here, uint32_t q) {
+    c.tau[i] = tau;
+    c.left[i] = 0;
+    c.lo[i] = tau + 1 < C16_KEYS ? tau + 1 : C16_KEYS;
+    if (before < q) {
+        if (before + here <= q) c.lo[i] = tau;
+        else { c.cut |= 1u << i; c.left[i] = q - before; }
+    }
+}
+// Slice s of the row: its thresholds, the message entries of the row in front of it and its own.  A whole workgroup of NT threads.
+template <int NT>
+__device__ __forceinline__ void slice_state(const TopkArgs& a, int row, int s, C16Cuts& c, uint32_t& base, uint32_t& members, uint32_t* s_red) {
+    const RowInfo* ri = a.rinfo + row;
+    const uint32_t* p0 = a.c16_part + ((size_t)row * (a.c16_wgs + 1) + s) * C16_KEYS;
+    const uint32_t* p1 = p0 + C16_KEYS;
+    const int lev = ri->level, top = (int)ri->topkey, tid = threadIdx.x;
+    uint32_t in0 = 0, in1 = 0;   // entries equal to a threshold that are inside it: in front of the slice, to its end
+    c.cut = 0;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        const int t = i == 0 ? 0 : lev - 2 + i;
+        const int32_t tau = (int32_t)ri->thr_tau[t];
+        const uint32_t q = ri->thr_jx[t];
+        const uint32_t b = tau < C16_KEYS ? p0[tau] : 0u, e = tau < C16_KEYS ? p1[tau] : 0u;
+        set_cut(c, i, tau, b, e - b, q);
+        const uint32_t sign = i == 1 ? ~0u : 1u;
+        in0 += sign * (b < q ? b : q);
+        in1 += sign * (e < q ? e : q);
+    }
+    uint32_t m0 = 0, m1 = 0;
+    for (int k = c.tau[0] + 1 + tid; k <= top; k += NT) { m0 += p0[k]; m1 += p1[k]; }
+    const int t1 = c.tau[1] < top ? c.tau[1] : top;
+    for (int k = c.tau[2] + 1 + tid; k <= t1; k += NT) { m0 += p0[k]; m1 += p1[k]; }
+    m0 = wave_sum(m0);
+    m1 = wave_sum(m1);
+    const int wave = tid >> 6;
+    if (lane_id() == 0) { s_red[wave] = m0; s_red[NT / 64 + wave] = m1; }
+    __syncthreads();
+    for (int i = 0; i < NT / 64; ++i) { in0 += s_red[i]; in1 += s_red[NT / 64 + i]; }
+    __syncthreads();
+    base = in0;
+    members = in1 - in0;
+}
+
+// ---------------------------------------------------------------------------------------------------
+// Long rows: the message by way of tile lists.  k_c16_mark leaves, tile by tile, the entries that may be in the message (its members and, where
+// a threshold splits them, all entries equal to it) in index order, k_c16_offsets turns the counts of the tiles into places, k_c16_expand
+// writes the message.  Waves are on their own throughout, so a row of stretches with different scales, some of which hold a hundred times as
+// many members as others, keeps no workgroup waiting: 4 rows of 1.24e8 entries in 148 stretches took 480 us with a slice per workgroup (k_c16_write),
+// and 317 with the fuller slices cut into parts after a count of 190; now 198 + 13 + 67 (1 GB at 6.3 TB/s: 158).
+struct C16Message {       // a row's thresholds 0, l-1, l
+    uint32_t lo[3];       // keys from here on are inside whatever their position
+    uint32_t tau[3];      // the key whose entries are split (C16_KEYS: none are)
+    uint32_t q[3];        // of them, in index order, the first q are inside
+};
+__device__ __forceinline__ C16Message message_of(const RowInfo* ri, const uint32_t* total) {
+    C16Message m;
+    const int lev = ri->level;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        const int t = i == 0 ? 0 : lev - 2 + i;
+        const uint32_t tau = ri->thr_tau[t], q = ri->thr_jx[t];
+        const bool split = tau < (uint32_t)C16_KEYS && q < total[tau];
+        m.lo[i] = tau + (split ? 1u : 0u);
+        m.tau[i] = split ? tau : (uint32_t)C16_KEYS;
+        m.q[i] = q;
+    }
+    return m;
+}
+constexpr int MK_THREADS = 256, MK_WAVES = MK_THREADS / 64;
+__global__ __launch_bounds__(MK_THREADS, 6) void k_c16_mark(TopkArgs a) {
+    __shared__ __align__(16) uint32_t s_ent[MK_WAVES][1024];
+    const int row = blockIdx.y;
+    const uint32_t lane = lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t* total = a.c16_part + ((size_t)row * (a.c16_wgs + 1) + a.c16_wgs) * C16_KEYS;
+    C16Message ms = message_of(a.rinfo + row, total);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        ms.lo[i] = (uint32_t)__builtin_amdgcn_readfirstlane((int)ms.lo[i]);
+        ms.tau[i] = (uint32_t)__builtin_amdgcn_readfirstlane((int)ms.tau[i]);
+    }
+    // candidates: keys in [f2, f2 + n2) or [f0, ...)
+    const int32_t lo0 = (int32_t)(ms.tau[0] < (uint32_t)C16_KEYS ? ms.tau[0] : ms.lo[0]), lo2 = (int32_t)(ms.tau[2] < (uint32_t)C16_KEYS ? ms.tau[2] : ms.lo[2]);
+    const u16x2 f2 = both16(lo2), n2 = both16((int32_t)ms.lo[1] - lo2), f0 = both16(lo0), n0 = both16(C16_KEYS - lo0);
+    const bool based = lo0 < C16_KEYS;   // uniform: a base band
+    const uint16_t* g = (const uint16_t*)a.g + (int64_t)row * a.ld;
+    uint32_t* ent = s_ent[wave];
+    const int64_t stride = (int64_t)gridDim.x * MK_WAVES, nfull = a.d / TILE;
+    const uint32_t t0 = ms.tau[0] << 16, t1 = ms.tau[1] << 16, t2 = ms.tau[2] << 16;
+    uint32_t* list = nullptr;
+    uint32_t head = 0, e0 = 0, e1 = 0, e2 = 0;   // uniform: candidates of the tile so far, those equal to a split key
+    // 1024 entries of a tile, block `blk` of it
+    auto block = [&](const u32x4_b16& va, const u32x4_b16& vb, uint32_t blk, uint32_t valid) {
+        const uint32_t b[8] = {va.x, va.y, va.z, va.w, vb.x, vb.y, vb.z, vb.w};
+        uint32_t m;
+        if (based) m = mask16(b, [&](u16x2 k) { return (u16x2)(in_range16(k, f2, n2) | in_range16(k, f0, n0)); }) & valid;
+        else m = mask16(b, [&](u16x2 k) { return in_range16(k, f2, n2); }) & valid;
+        if (__ballot(m != 0u) == 0ull) return;   // uniform
+        const uint32_t c0 = __popc(m & 0xFFu), c1 = __popc(m >> 8);
+        const uint32_t inc = wave_incl_scan(c0 | (c1 << 16));
+        const uint32_t tot = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63), tot0 = tot & 0xFFFFu, n = tot0 + (tot >> 16);
+        const uint32_t at0 = (inc & 0xFFFFu) - c0, at1 = tot0 + (inc >> 16) - c1;
+        const uint32_t off = blk * 1024u + lane * 8u;
+        wave_lds_sync();
+        if (n > 192u) {   // uniform: entry by entry
+            uint32_t at = at0;
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {
+                if (k == 8) at = at1;
+                if ((m >> k) & 1u) { ent[at] = (k & 1 ? b[k >> 1] & 0xFFFF0000u : b[k >> 1] << 16) | (off + (uint32_t)k + (k >= 8 ? 504u : 0u)); ++at; }
+            }
+        } else {
+            uint32_t rank = 0;
+            while (m) {
+                const uint32_t k = (uint32_t)__builtin_ctz(m), q = k >> 1;
+                const uint32_t x0 = q & 1u ? b[1] : b[0], x1 = q & 1u ? b[3] : b[2], x2 = q & 1u ? b[5] : b[4], x3 = q & 1u ? b[7] : b[6];
+                const uint32_t y0 = q & 2u ? x1 : x0, y1 = q & 2u ? x3 : x2, z = q & 4u ? y1 : y0;
+                ent[k < 8u ? at0 + rank : at1 + rank - c0] = (k & 1u ? z & 0xFFFF0000u : z << 16) | (off + k + (k >= 8u ? 504u : 0u));
+                ++rank;
+                m &= m - 1u;
+            }
+        }
+        wave_lds_sync();
+        for (uint32_t i = 0; i < n; i += 64) {
+            const bool on = i + lane < n;
+            const uint32_t e = on ? ent[i + lane] : 0x80000000u, key = on ? e & 0x7FFF0000u : ~0u;
+            if (on) list[head + i + lane] = e;
+            e0 += (uint32_t)__popcll(__ballot(key == t0));
+            e1 += (uint32_t)__popcll(__ballot(key == t1));
+            e2 += (uint32_t)__popcll(__ballot(key == t2));
+        }
+        head += n;
+    };
+    uint4* cnt = a.c16_cnt + (size_t)row * a.ntiles;
+    auto begin = [&](int64_t tile) {
+        list = a.c16_list + ((size_t)row * a.ntiles + tile) * TILE;
+        head = e0 = e1 = e2 = 0;
+    };
+    auto end = [&](int64_t tile) { if (lane == 0) cnt[tile] = make_uint4(head, e0, e1, e2); };
+    auto fetch = [&](int64_t tile, int half, u32x4_b16 (&v)[4]) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[q] = __builtin_nontemporal_load((const u32x4_b16*)(g + tile * TILE + half * 2048 + q * 512 + lane * 8));
+    };
+    u32x4_b16 va[4], vb[4];
+    int64_t tile = (int64_t)blockIdx.x * MK_WAVES + wave;
+    if (tile < nfull) {
+        fetch(tile, 0, va);
+        while (true) {   // uniform
+            fetch(tile, 1, vb);
+            begin(tile);
+            block(va[0], va[1], 0, 0xFFFFu);
+            block(va[2], va[3], 1, 0xFFFFu);
+            const bool more = tile + stride < nfull;
+            if (more) fetch(tile + stride, 0, va);
+            block(vb[0], vb[1], 2, 0xFFFFu);
+            block(vb[2], vb[3], 3, 0xFFFFu);
+            end(tile);
+            if (!more) break;
+            tile += stride;
+        }
+        tile += stride;
+    }
+    if (tile == nfull && tile < a.ntiles) {   // the row's last tile, when it is not whole
+        begin(tile);
+        for (uint32_t blk = 0; blk < 4; ++blk) {
+            u32x4_b16 v[2];
+            const uint32_t valid = fetch_part(g, tile * TILE + blk * 1024 + lane * 8, a.d, v);
+            block(v[0], v[1], blk, valid);
+        }
+        end(tile);
+    }
+}
+
+// Of the e entries equal to key v that follow E others, how many are in the message: inside threshold 0, or inside l and not inside l-1.
+__device__ __forceinline__ uint32_t equals_inside(const C16Message& m, uint32_t v, uint32_t E, uint32_t e) {
+    uint32_t n = 0;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        uint32_t f = 0;
+        if (v >= m.lo[i]) f = e;
+        else if (v == m.tau[i] && m.q[i] > E) f = m.q[i] - E < e ? m.q[i] - E : e;
+        n += i == 1 ? 0u - f : f;
+    }
+    return n;
+}
+// The tiles' places in the message, and how many of the split entries lie before every tile.  A workgroup takes `span` tiles of a row, 1024 at a time, after
+// adding up those in front of them (with one workgroup per row, its threads on a run of tiles each, 72 us at 30381 tiles; this way
+// 13, of which a launch takes 5).
+__global__ __launch_bounds__(1024) void k_c16_offsets(TopkArgs a, int64_t span) {
+    __shared__ uint32_t s_scan[17];
+    __shared__ int64_t s_k[TMAX];
+    __shared__ unsigned long long s_rows;
+    __shared__ uint32_t s_sum[4];
+    const int row = blockIdx.y, tid = threadIdx.x;
+    if (tid < TMAX) s_k[tid] = tid <= a.L ? a.k[tid] : 0;
+    if (tid == 0) s_rows = 0ull;
+    if (tid < 4) s_sum[tid] = 0u;
+    const uint4* cnt = a.c16_cnt + (size_t)row * a.ntiles;
+    const int64_t t0 = (int64_t)blockIdx.x * span, t1 = t0 + span < a.ntiles ? t0 + span : a.ntiles;
+    uint4 sum = make_uint4(0, 0, 0, 0);
+    batched_loop<8, 1024>(0u, (uint32_t)t0, (uint32_t)tid, [&](uint32_t t) { return cnt[t]; }, [&](uint32_t, uint4 c) {
+        sum.x += c.x; sum.y += c.y; sum.z += c.z; sum.w += c.w;
+    });
+    __syncthreads();
+    if (t0 > 0) {   // uniform
+        sum.x = wave_sum(sum.x); sum.y = wave_sum(sum.y); sum.z = wave_sum(sum.z); sum.w = wave_sum(sum.w);
+        if (lane_id() == 0) { atomicAdd(&s_sum[0], sum.x); atomicAdd(&s_sum[1], sum.y); atomicAdd(&s_sum[2], sum.z); atomicAdd(&s_sum[3], sum.w); }
+    }
+    const bool last = t1 == a.ntiles;
+    const int lev = a.rinfo[row].level;
+    if (last && tid < row) {
+        const int li = a.level[tid];
+        atomicAdd(&s_rows, (unsigned long long)(s_k[0] + s_k[li] - s_k[li - 1]));
+    }
+    static_assert(MLMC_MAX_WORKERS <= 1024, "a thread per row");
+    const C16Message m = message_of(a.rinfo + row, a.c16_part + ((size_t)row * (a.c16_wgs + 1) + a.c16_wgs) * C16_KEYS);
+    // each split key once
+    const bool s0 = m.tau[0] < (uint32_t)C16_KEYS, s1 = m.tau[1] < (uint32_t)C16_KEYS && !(s0 && m.tau[1] == m.tau[0]),
+               s2 = m.tau[2] < (uint32_t)C16_KEYS && !(s0 && m.tau[2] == m.tau[0]) && !(s1 && m.tau[2] == m.tau[1]);
+    // the message entries of a stretch of tiles
+    auto inside = [&](const uint4& at, const uint4& c) -> uint32_t {
+        uint32_t n = c.x;
+        if (s0) n += equals_inside(m, m.tau[0], at.y, c.y) - c.y;
+        if (s1) n += equals_inside(m, m.tau[1], at.z, c.z) - c.z;
+        if (s2) n += equals_inside(m, m.tau[2], at.w, c.w) - c.w;
+        return n;
+    };
+    __syncthreads();
+    uint4 run = make_uint4(0, s_sum[1], s_sum[2], s_sum[3]);
+    run.x = inside(make_uint4(0, 0, 0, 0), make_uint4(s_sum[0], s_sum[1], s_sum[2], s_sum[3]));
+    uint4* pre = a.c16_pre + (size_t)row * a.ntiles;
+    uint32_t* tile_off = a.tile_off + (size_t)row * (a.ntiles + 1);
+    for (int64_t tb = t0; tb < t1; tb += 1024) {   // uniform
+        const int64_t t = tb + tid;
+        const uint4 c = t < t1 ? cnt[t] : make_uint4(0, 0, 0, 0);
+        uint4 at = run, all;
+        at.y += block_excl_scan<1024>(c.y, s_scan, all.y);
+        at.z += block_excl_scan<1024>(c.z, s_scan, all.z);
+        at.w += block_excl_scan<1024>(c.w, s_scan, all.w);
+        at.x += block_excl_scan<1024>(inside(at, c), s_scan, all.x);
+        if (t < t1) {
+            tile_off[t] = at.x;
+            pre[t] = make_uint4(c.x, at.y, at.z, at.w);
+        }
+        run.x += all.x; run.y += all.y; run.z += all.z; run.w += all.w;
+    }
+    if (last && tid == 0) {
+        const int64_t rowstart = (int64_t)s_rows, nnz = s_k[0] + s_k[lev] - s_k[lev - 1];
+        tile_off[a.ntiles] = (uint32_t)nnz;
+        a.rinfo[row].msg.rowstart = rowstart;
+        if ((int64_t)run.x != nnz) atomicOr(a.dev_status, MLMC_DEV_INTERNAL);
+        a.row_off[row] = rowstart;
+        if (row == a.M - 1) {
+            a.row_off[a.M] = rowstart + nnz;
+            if (rowstart + nnz > a.capacity) atomicOr(a.dev_status, MLMC_DEV_CAPACITY);
+        }
+    }
+}
+// A wave per tile, 64 entries of its list at a time.
+__global__ __launch_bounds__(256) void k_c16_expand(TopkArgs a) {
+    const int row = blockIdx.y;
+    const uint32_t lane = lane_id();
+    const RowInfo* ri = a.rinfo + row;
+    const C16Message m = message_of(ri, a.c16_part + ((size_t)row * (a.c16_wgs + 1) + a.c16_wgs) * C16_KEYS);
+    const float w = ri->weight;
+    const int64_t rowstart = ri->msg.rowstart, room = a.capacity - rowstart;
+    const bool any_split = m.tau[0] < (uint32_t)C16_KEYS || m.tau[1] < (uint32_t)C16_KEYS || m.tau[2] < (uint32_t)C16_KEYS;
+    uint32_t* idx = a.idx + rowstart;
+    float* val = a.val + rowstart;
+    for (int64_t tile = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); tile < a.ntiles; tile += (int64_t)gridDim.x * 4) {
+        const uint4 c = a.c16_pre[(size_t)row * a.ntiles + tile];
+        const uint32_t n = (uint32_t)__builtin_amdgcn_readfirstlane((int)c.x);
+        if (n == 0) continue;   // uniform
+        uint32_t at = (uint32_t)__builtin_amdgcn_readfirstlane((int)a.tile_off[(size_t)row * (a.ntiles + 1) + tile]);
+        uint32_t E[3] = {c.y, c.z, c.w};
+        const uint32_t* list = a.c16_list + ((size_t)row * a.ntiles + tile) * TILE;
+        constexpr int U = 4;
+        for (uint32_t i0 = 0; i0 < n; i0 += 64 * U) {
+            uint32_t e[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) { const uint32_t i = i0 + 64u * u + lane; e[u] = list[i < n ? i : n - 1u]; }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const bool on = i0 + 64u * u + lane < n;
+                const uint32_t key = (e[u] >> 16) & 0x7FFFu;
+                bool in[3];
+#pragma unroll
+                for (int i = 0; i < 3; ++i) {
+                    in[i] = key >= m.lo[i];
+                    if (any_split) {   // uniform
+                        const uint64_t eq = __ballot(on && key == m.tau[i]);
+                        in[i] = in[i] || (key == m.tau[i] && E[i] + mbcnt(eq) < m.q[i]);
+                        E[i] += (uint32_t)__popcll(eq);
+                    }
+                }
+                const bool member = on && (in[0] || (in[2] && !in[1]));
+                const uint64_t mm = __ballot(member);
+                const uint32_t pos = at + mbcnt(mm);
+                if (member && (int64_t)pos < room) {
+                    const float v = __uint_as_float(e[u] & 0xFFFF0000u);
+                    idx[pos] = (uint32_t)(tile * TILE) + (e[u] & 0xFFFu);
+                    val[pos] = in[0] ? v : __fmul_rn(v, w);
+                }
+                at += (uint32_t)__popcll(mm);
+            }
+        }
+    }
+}
+
+// Short slices: the message (Eq. (6)) of a slice by one workgroup.  Bound by the instructions of a step and its barrier: 32 rows of 1e6 entries 45 us.
+// A step's members are found as one 16-bit mask per lane, ranked by a scan
+// over the lanes and one LDS word per wave, and gathered in LDS ({entry's bits, offset in the step}); the next step writes them out densely, four
+// to a store.  One barrier per step, the loads of the next two steps in flight.
+// Of a threshold's equals the first few are inside.  Only in the one stretch in which they run out is that a matter of position:
+// there a step first counts them, and the one step that holds the last of them ranks them.
+__global__ __launch_bounds__(C16_THREADS) void k_c16_write(TopkArgs a) {
+    __shared__ __align__(16) uint32_t s_ent[2][C16_STEP];   // members of a step in index order: bits << 16 | base band by position << 15 | offset
+    __shared__ uint32_t s_tot[2][C16_WAVES];
+    __shared__ uint32_t s_eq[3][C16_WAVES];
+    __shared__ uint32_t s_red[2 * C16_WAVES];
+    __shared__ int64_t s_k[TMAX];
+    __shared__ unsigned long long s_rows;
+    const int tid = threadIdx.x;
+    const uint32_t lane = lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int row = blockIdx.y, slice = blockIdx.x;
+    const RowInfo* ri = a.rinfo + row;
+    if (tid < TMAX) s_k[tid] = tid <= a.L ? a.k[tid] : 0;
+    if (tid == 0) s_rows = 0ull;
+    __syncthreads();
+    const int lev = ri->level;
+    const float w = ri->weight;
+    if (tid < row) {   // at most C16_THREADS rows
+        const int li = a.level[tid];
+        atomicAdd(&s_rows, (unsigned long long)(s_k[0] + s_k[li] - s_k[li - 1]));
+    }
+    static_assert(MLMC_MAX_WORKERS <= C16_THREADS, "a thread per row");
+    const int64_t i0 = (int64_t)slice * a.c16_slice, i1 = i0 + a.c16_slice < a.d ? i0 + a.c16_slice : a.d;
+    const bool last = i1 == a.d;
+    C16Cuts cuts;
+    uint32_t base, left_in_row = 0;
+    slice_state<C16_THREADS>(a, row, slice, cuts, base, left_in_row, s_red);
+    __syncthreads();
+    const int64_t rowstart = (int64_t)s_rows;
+    const int64_t nnz = s_k[0] + s_k[lev] - s_k[lev - 1];
+    base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        cuts.lo[i] = __builtin_amdgcn_readfirstlane(cuts.lo[i]);
+        cuts.tau[i] = __builtin_amdgcn_readfirstlane(cuts.tau[i]);
+        cuts.left[i] = (uint32_t)__builtin_amdgcn_readfirstlane((int)cuts.left[i]);
+    }
+    cuts.cut = (uint32_t)__builtin_amdgcn_readfirstlane((int)cuts.cut);
+    uint32_t* tile_off = a.tile_off + (size_t)row * (a.ntiles + 1);
+    if (last && tid == 0) {
+        a.row_off[row] = rowstart;
+        tile_off[a.ntiles] = (uint32_t)nnz;
+        if (row == a.M - 1) {
+            a.row_off[a.M] = rowstart + nnz;
+            if (rowstart + nnz > a.capacity) atomicOr(a.dev_status, MLMC_DEV_CAPACITY);
+        }
+    }
+    const uint16_t* g = (const uint16_t*)a.g + (int64_t)row * a.ld;
+    const uint32_t lane_off = (uint32_t)wave * 1024u + lane * 8u;   // this lane's first entry of a step; the other half is 512 further on
+    const int nfull = i1 > i0 ? (int)((i1 - i0) / C16_STEP) : 0, nsteps = i1 > i0 ? (int)((i1 - i0 + C16_STEP - 1) / C16_STEP) : 0;
+    uint32_t* idx = a.idx + rowstart;
+    float* val = a.val + rowstart;
+    const int64_t room = a.capacity - rowstart;   // entries past the capacity are not written
+
+    uint32_t run = base;
+    uint32_t par = 0, prev_first = 0, prev_count = 0, prev_sb = 0, prev_lo0 = 0;
+    typedef uint32_t u32x4_out __attribute__((ext_vector_type(4), aligned(4)));
+    typedef float f32x4_out __attribute__((ext_vector_type(4), aligned(4)));
+    auto value = [&](uint32_t e, uint32_t lo0) -> float {
+        const float v = __uint_as_float(e & 0xFFFF0000u);
+        return (e & 0x7FFF0000u) >= lo0 || (e & 0x8000u) ? v : __fmul_rn(v, w);
+    };
+    auto write_out = [&](uint32_t p, uint32_t first, uint32_t count, uint32_t sb, uint32_t lo0) {   // lo0: shifted, a key's place in an entry
+        if ((int64_t)first + count <= room) {   // uniform
+            const uint32_t quads = count / 4;
+            for (uint32_t i = tid; i < quads; i += C16_THREADS) {
+                const uint4 e = *(const uint4*)&s_ent[p][4 * i];
+                u32x4_out j;
+                f32x4_out v;
+                j.x = sb + (e.x & 0x3FFFu); j.y = sb + (e.y & 0x3FFFu); j.z = sb + (e.z & 0x3FFFu); j.w = sb + (e.w & 0x3FFFu);
+                v.x = value(e.x, lo0); v.y = value(e.y, lo0); v.z = value(e.z, lo0); v.w = value(e.w, lo0);
+                *(u32x4_out*)(idx + first + 4 * i) = j;
+                *(f32x4_out*)(val + first + 4 * i) = v;
+            }
+            const uint32_t i = quads * 4 + tid;
+            if (i < count) {
+                const uint32_t e = s_ent[p][i];
+                idx[first + i] = sb + (e & 0x3FFFu);
+                val[first + i] = value(e, lo0);
+            }
+        } else {
+            for (uint32_t i = tid; i < count && (int64_t)first + i < room; i += C16_THREADS) {
+                const uint32_t e = s_ent[p][i];
+                idx[first + i] = sb + (e & 0x3FFFu);
+                val[first + i] = value(e, lo0);
+            }
+        }
+    };
+    auto step = [&](int s, const u32x4_b16 (&v)[2], uint32_t valid) {
+        uint32_t b[8];
+        words_of(v, b);
+        const int64_t sb = i0 + (int64_t)s * C16_STEP;
+        C16Cuts now = cuts;                        // of this step
+        uint32_t split = 0;
+        uint32_t before_eq[3] = {0, 0, 0};         // equals in the waves before this one
+        if (cuts.cut) {   // uniform
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                uint32_t c = 0;
+                if ((cuts.cut >> i) & 1u) c = __popc(mask16(b, [&](u16x2 k) { return in_range16(k, both16(cuts.tau[i]), both16(1)); }) & valid);
+                c = wave_sum(c);
+                if (lane == 0) s_eq[i][wave] = c;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                if (!((now.cut >> i) & 1u)) continue;
+                uint32_t all = 0;
+                for (int u = 0; u < C16_WAVES; ++u) {
+                    const uint32_t x = s_eq[i][u];
+                    before_eq[i] += u < wave ? x : 0u;
+                    all += x;
+                }
+                all = (uint32_t)__builtin_amdgcn_readfirstlane((int)all);
+                if (all > cuts.left[i]) {   // they run out here
+                    split |= 1u << i;
+                    cuts.cut &= ~(1u << i);
+                } else {
+                    cuts.left[i] -= all;
+                    now.lo[i] = cuts.tau[i];
+                }
+            }
+        }
+        uint32_t m;
+        uint32_t by_position = 0;   // base band members that now.lo[0] does not tell
+        if (split) {   // uniform
+            uint32_t in[3];
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                in[i] = mask16(b, [&](u16x2 k) { return in_range16(k, both16(now.lo[i]), both16(C16_KEYS - now.lo[i])); }) & valid;
+                if (!((split >> i) & 1u)) continue;
+                const uint32_t e = mask16(b, [&](u16x2 k) { return in_range16(k, both16(now.tau[i]), both16(1)); }) & valid;
+                const uint32_t c0 = __popc(e & 0xFFu), c1 = __popc(e >> 8);
+                const uint32_t inc = wave_incl_scan(c0 | (c1 << 16));
+                const uint32_t tot0 = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63) & 0xFFFFu;
+                uint32_t keep = 0, r = before_eq[i] + (inc & 0xFFFFu) - c0;
+#pragma unroll 1
+                for (int k = 0; k < 16; ++k) {
+                    if (k == 8) r = before_eq[i] + tot0 + (inc >> 16) - c1;
+                    if ((e >> k) & 1u) { if (r < now.left[i]) keep |= 1u << k; ++r; }
+                }
+                in[i] |= keep;
+                if (i == 0) by_position = keep;
+            }
+            m = in[0] | (in[2] & ~in[1]);
+        } else {
+            const u16x2 from = both16(now.lo[2]), n = both16(now.lo[1] - now.lo[2]);
+            if (now.lo[0] < C16_KEYS) {   // uniform: a base band
+                const u16x2 f0 = both16(now.lo[0]), n0 = both16(C16_KEYS - now.lo[0]);
+                m = mask16(b, [&](u16x2 k) { return (u16x2)(in_range16(k, from, n) | in_range16(k, f0, n0)); }) & valid;
+            } else {
+                m = mask16(b, [&](u16x2 k) { return in_range16(k, from, n); }) & valid;
+            }
+        }
+        const uint32_t c0 = __popc(m & 0xFFu), c1 = __popc(m >> 8);
+        const uint32_t inc = wave_incl_scan(c0 | (c1 << 16));
+        const uint32_t tot = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63), tot0 = tot & 0xFFFFu, wtot = tot0 + (tot >> 16);
+        if (lane == 0) s_tot[par][wave] = wtot;
+        __syncthreads();
+        if (prev_count) write_out(par ^ 1u, prev_first, prev_count, prev_sb, prev_lo0);   // every wave is past its gathering of that step
+        uint32_t pre = 0, total = 0;
+#pragma unroll
+        for (int u = 0; u < C16_WAVES; ++u) {
+            const uint32_t x = s_tot[par][u];
+            pre += u < wave ? x : 0u;
+            total += x;
+        }
+        total = (uint32_t)__builtin_amdgcn_readfirstlane((int)total);
+        if ((wave & 3) == 0 && lane == 0 && sb + wave * 1024 < i1) tile_off[sb / TILE + wave / 4] = run + pre;
+        if (wtot) {   // uniform
+            uint32_t* out = s_ent[par];
+            const uint32_t at0 = pre + (inc & 0xFFFFu) - c0, at1 = pre + tot0 + (inc >> 16) - c1;   // first member of either half
+            auto put = [&](uint32_t at, uint32_t bits, uint32_t k) {   // bits: the entry in the upper half
+                out[at] = bits | (((by_position >> k) & 1u) << 15) | (lane_off + k + (k >= 8u ? 504u : 0u));
+            };
+            if (wtot > 192u) {   // uniform: entry by entry
+                uint32_t at = at0;
+#pragma unroll
+                for (int k = 0; k < 16; ++k) {
+                    if (k == 8) at = at1;
+                    if ((m >> k) & 1u) { put(at, k & 1 ? b[k >> 1] & 0xFFFF0000u : b[k >> 1] << 16, (uint32_t)k); ++at; }
+                }
+            } else {
+                uint32_t rank = 0;
+                while (m) {
+                    const uint32_t k = (uint32_t)__builtin_ctz(m), q = k >> 1;
+                    const uint32_t x0 = q & 1u ? b[1] : b[0], x1 = q & 1u ? b[3] : b[2], x2 = q & 1u ? b[5] : b[4], x3 = q & 1u ? b[7] : b[6];
+                    const uint32_t y0 = q & 2u ? x1 : x0, y1 = q & 2u ? x3 : x2, z = q & 4u ? y1 : y0;
+                    put(k < 8u ? at0 + rank : at1 + rank - c0, k & 1u ? z & 0xFFFF0000u : z << 16, k);
+                    ++rank;
+                    m &= m - 1u;
+                }
+            }
+        }
+        prev_first = run;
+        prev_count = total;
+        prev_sb = (uint32_t)sb;
+        prev_lo0 = (uint32_t)now.lo[0] << 16;
+        run += total;
+        par ^= 1u;
+    };
+    static_assert(TILE == 4 * 1024 && C16_STEP <= 0x4000, "a tile is four waves' entries; offsets have 14 bits");
+    u32x4_b16 buf[2][2];
+    const int64_t mine = i0 + lane_off;
+    int s = 0;
+    if (nfull >= 2) {
+        fetch_step(g, mine, buf[0]);
+        fetch_step(g, mine + C16_STEP, buf[1]);
+        for (; s + 4 <= nfull; s += 2) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                step(s + u, buf[u], 0xFFFFu);
+                fetch_step(g, mine + (int64_t)(s + u + 2) * C16_STEP, buf[u]);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u) step(s + u, buf[u], 0xFFFFu);
+        s += 2;
+    }
+    for (; s < nsteps; ++s) {
+        const uint32_t valid = fetch_part(g, mine + (int64_t)s * C16_STEP, i1, buf[0]);
+        step(s, buf[0], valid);
+    }
+    __syncthreads();
+    if (prev_count) write_out(par ^ 1u, prev_first, prev_count, prev_sb, prev_lo0);
+    if (last && tid == 0 && (int64_t)run != nnz) atomicOr(a.dev_status, MLMC_DEV_INTERNAL);
+}
+
+// message == false: norms only.
+mlmc_status topk16_run(const mlmc_plan_t* pl, const TopkArgs& a, bool message, hipStream_t st) {
+    const dim3 grid(pl->c16_wgs, pl->M);
+    MLMC_LAUNCH(K_C16_HIST, st, k_c16_hist<<<grid, C16_THREADS, 0, st>>>(a));
+    const dim3 rgrid(C16_KEYS / 64, pl->M);
+#define MLMC_C16_REDUCE(G)                                                                                               \
+    do {                                                                                                                \
+        if (message && !a.c16_list) MLMC_LAUNCH(K_C16_SCAN, st, k_c16_reduce<G, true><<<rgrid, 64 * G, 0, st>>>(a));      \
+        else MLMC_LAUNCH(K_C16_SCAN, st, k_c16_reduce<G, false><<<rgrid, 64 * G, 0, st>>>(a));                            \
+    } while (0)
+    if (pl->c16_wgs > C16_PER) MLMC_C16_REDUCE(16);
+    else if (pl->c16_wgs > 1) MLMC_C16_REDUCE(4);
+    else MLMC_C16_REDUCE(1);
+#undef MLMC_C16_REDUCE
+    MLMC_LAUNCH(K_C16_SCAN, st, k_c16_scan<<<pl->M, 1024, 0, st>>>(a));
+    if (!message) return MLMC_OK;
+    if (a.c16_list) {
+        int64_t mw = (pl->ntiles + MK_WAVES - 1) / MK_WAVES;
+        const int64_t cap = 2048 / pl->M > 0 ? 2048 / pl->M : 1;
+        const dim3 mgrid((unsigned)(mw < cap ? mw : cap), pl->M), egrid((unsigned)(mw < 4 * cap ? mw : 4 * cap), pl->M);
+        MLMC_LAUNCH(K_C16_MARK, st, k_c16_mark<<<mgrid, MK_THREADS, 0, st>>>(a));
+        const int64_t span = (pl->ntiles + 65535) / 65536 * 1024;   // at most 64 workgroups a row: what they add up in front of their tiles stays small
+        MLMC_LAUNCH(K_C16_MARK, st, k_c16_offsets<<<dim3((unsigned)((pl->ntiles + span - 1) / span), pl->M), 1024, 0, st>>>(a, span));
+        MLMC_LAUNCH(K_C16_WRITE, st, k_c16_expand<<<egrid, 256, 0, st>>>(a));
+    } else {
+        MLMC_LAUNCH(K_C16_WRITE, st, k_c16_write<<<grid, C16_THREADS, 0, st>>>(a));
+    }
+    return MLMC_OK;
+}
+
+}  // namespace mlmc

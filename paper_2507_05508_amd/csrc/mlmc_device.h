@@ -318,4 +318,79 @@ struct BigAcc {
     }
 };
 
+// The same integer as LDS counters of 32-bit words (64 bits each, carries not yet propagated): v << shift is split into three words that are
+// added with LDS atomics in any order; fewer than 2^32 addends cannot overflow a counter.
+__device__ __forceinline__ void wide_add(unsigned long long* wide, uint64_t v, int shift) {
+    if (!v) return;
+    const int wi = shift >> 5, bs = shift & 31;
+    uint32_t parts[3];
+    parts[0] = (uint32_t)(v << bs);
+    parts[1] = (uint32_t)(bs ? v >> (32 - bs) : v >> 32);
+    parts[2] = bs ? (uint32_t)(v >> (64 - bs)) : 0u;
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+        if (parts[i] && wi + i < 20) atomicAdd(&wide[wi + i], (unsigned long long)parts[i]);
+}
+// One thread: the carries propagated into `words` (20 of them), the value as a correctly rounded double.
+__device__ __forceinline__ double wide_to_double(const unsigned long long* wide, uint32_t* words) {
+    uint64_t w[20];
+#pragma unroll
+    for (int i = 0; i < 20; ++i) w[i] = wide[i];
+    uint64_t carry = 0;
+#pragma unroll
+    for (int i = 0; i < 20; ++i) {
+        const uint64_t t = w[i] + carry;
+        words[i] = (uint32_t)t;
+        carry = t >> 32;
+    }
+    BigAcc acc;
+    acc.w = words;
+    return acc.to_double();
+}
+
+// ---------------------------------------------------------------------------------------------------
+// Level draw of one row (Alg. 2 / Alg. 3 "Sample l ~ p") by one wave, a lane per level: the sums, whose order fixes their roundings, go through the
+// lanes one by one, the divisions and the integer thresholds are made side by side (one thread took 6 us for twelve levels).
+__device__ __forceinline__ double lane_f64(double v, int l) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l), __builtin_amdgcn_readlane(__double2loint(v), l));
+}
+// p: the lane's probability (lane l: level l + 1, l < L <= 64).  Returns the level in 1..L, to every lane.
+__device__ __forceinline__ int wave_draw_from_p(double p, int L, uint32_t x) {
+    const int lane = (int)lane_id();
+    double c = 0.0, mine = 0.0;
+    for (int l = 0; l < L; ++l) {
+        c = __dadd_rn(c, lane_f64(p, l));
+        mine = lane == l ? c : mine;
+    }
+    const double t = floor(__dmul_rn(mine, 4294967296.0));
+    uint64_t T = !(t > 0.0) ? 0ull : t >= 4294967296.0 ? 4294967296ull : (uint64_t)t;
+    if (lane == L - 1) T = 4294967296ull;
+    const uint64_t below = __ballot(lane < L && (uint64_t)x < T);   // the last level's lane is always among them
+    return (int)__builtin_ctzll(below) + 1;
+}
+__device__ inline void draw_row(const TopkArgs& a, int row, const double* norms_row) {
+    const int L = a.L, lane = (int)lane_id(), l = lane < L ? lane : L - 1;
+    double p;
+    if (a.draw_mode == 0) {
+        p = a.p_fixed[l];
+    } else if (a.draw_mode == 1) {
+        p = a.p_dev[(size_t)row * L + l];
+    } else {
+        const double n = a.draw_mode == 2 ? a.p_dev[(size_t)row * L + l] : norms_row[l];
+        double tot = 0.0;
+        for (int i = 0; i < L; ++i) tot = __dadd_rn(tot, lane_f64(n, i));
+        p = tot == 0.0 ? __ddiv_rn(1.0, (double)L) : __ddiv_rn(n, tot);
+    }
+    const uint32_t x = philox_word0(a.seed, a.step, (uint32_t)row);
+    const int level = wave_draw_from_p(p, L, x);
+    const double pl = lane_f64(p, level - 1);
+    if (lane == 0) {
+        RowInfo* ri = a.rinfo + row;
+        ri->level = level;
+        ri->weight = pl == 0.0 ? 0.0f : (float)__ddiv_rn(1.0, pl);
+        ri->draw_x = x;
+        a.level[row] = level;
+    }
+}
+
 }  // namespace mlmc

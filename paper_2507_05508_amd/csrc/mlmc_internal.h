@@ -84,6 +84,7 @@ struct RowInfo {
     MsgPlan msg;
     float weight;
     uint32_t draw_x;
+    uint32_t topkey;          // counted 16-bit rows: the largest magnitude
     uint32_t zone_top[ZMAX], zone_bot[ZMAX];   // first-digit buckets of the zone, top >= bot, both inclusive
     uint32_t zone_off[ZMAX], zone_cap[ZMAX];   // its candidate list inside the row's candidate buffer
     int32_t zone_t0[ZMAX], zone_t1[ZMAX];      // thresholds t0..t1 (those that are active) lie in the zone
@@ -109,7 +110,6 @@ struct TopkArgs {
     const void* g;
     int64_t ld, d;
     int32_t M, L;
-    int32_t dtype;           // MLMC_F32 / MLMC_BF16 (the kernels that stream rows are compiled per type; this is for the few loads elsewhere)
     int64_t k[TMAX];
     int32_t all_thresholds;  // 1: every ladder threshold + band sums (adaptive); 0: thresholds 0, l-1, l only
     int32_t chunk;           // elements per workgroup chunk (multiple of TILE, <= CHUNK_MAX)
@@ -143,6 +143,13 @@ struct TopkArgs {
     double* norms;           // [M][L]
     double* norms_user;      // optional copy
     int32_t* dev_status;
+    // 16-bit rows, whose magnitudes are counted
+    uint32_t* c16_part;      // [M][c16_wgs + 1][2^15] counts of a slice, then those of the slices before it; last: of the row
+    int32_t c16_wgs;         // slices per row
+    int64_t c16_slice;       // entries of a slice, a multiple of TILE
+    uint32_t* c16_list;      // [M][ntiles][TILE] entries that may be in the message: bits << 16 | offset in the tile (null: one workgroup per slice writes it)
+    uint4* c16_cnt;          // [M][ntiles] of every tile: its list's length, entries equal to the split keys in it
+    uint4* c16_pre;          // the same with the entries equal to the split keys before it
     // level draw (Alg. 2 / Alg. 3 "Sample l"): mode 0 p_fixed, 1 dev p, 2 dev norms, 3 norms computed by this call
     int32_t draw_mode;
     double p_fixed[LMAX];
@@ -264,7 +271,8 @@ struct StopkArgs {
 enum KernelId {
     K_ZERO = 0, K_HIST, K_SCAN, K_MAIN, K_FHIST, K_FINISH, K_FINISH1, K_REDO, K_NORMS, K_DRAW, K_MSGPLAN, K_FILTER, K_WRITE,
     K_BITS_MAX, K_BITS_EXTRACT, K_BITS_REDO, K_AGG_BITS, K_TILEOFF, K_AGG_SPARSE, K_MSGBITS, K_RTN_NORMS, K_RTN_DRAW,
-    K_RS_HIST, K_RS_SCAN, K_RS_SCATTER, K_SB_NORMS, K_SB_DRAW, K_SB_MARK, K_SB_OFFSETS, K_SB_WRITE, K_SE_COUNT, K_SE_SCAN, K_SE_SPLIT, K_SE_ZONE, K_NUM
+    K_RS_HIST, K_RS_SCAN, K_RS_SCATTER, K_SB_NORMS, K_SB_DRAW, K_SB_MARK, K_SB_OFFSETS, K_SB_WRITE, K_SE_COUNT, K_SE_SCAN, K_SE_SPLIT, K_SE_ZONE,
+    K_C16_HIST, K_C16_SCAN, K_C16_MARK, K_C16_WRITE, K_NUM
 };
 extern bool g_prof_on;
 void prof_begin(int id, hipStream_t st);
@@ -310,6 +318,9 @@ struct mlmc_plan_s {
     size_t off_rtn_sums, off_rtn_part, off_rtn_total;   // Round-to-Nearest plans
     int rtn_wgs;              // workgroups per row that count magnitudes (0: not counted)
     int64_t rtn_slice;
+    size_t off_c16_part, off_c16_list, off_c16_cnt, off_c16_pre;   // Top-k plans of 16-bit rows
+    int c16_wgs;              // slices per row (0: not counted)
+    int64_t c16_slice;
     // Side stream of the message step (MLMC_TOPK): the second read of the rows whose band was not staged runs beside the
     // assembly of the other rows' messages from the staged lists.  Created at the first call that uses it, on the device
     // current then; default priority.  Host objects only; destroyed with the plan.

@@ -1,4 +1,4 @@
-// Top-k MLMC on gfx950: exact multi-rank select on |g| keys, exact band sums of squares, level draw,
+// Top-k MLMC of 32-bit rows on gfx950 (16-bit ones: mlmc_count16.hip): exact multi-rank select on |g| keys, exact band sums of squares, level draw,
 // index-ordered band message.  A row is normally read once (plus a sample); a second read happens only when
 // the band that was set aside during the first read is not the band that is drawn.
 //
@@ -47,7 +47,7 @@ __global__ __launch_bounds__(256) void k_zero(uint4* p, size_t n16, int32_t* dev
 // First-digit histogram of the sampled blocks (block b of 1024 elements is sampled when b % S == S / 2).
 // exact_pass: only rows flagged for an exact redo are read, every block, into hist2.
 constexpr int HIST_THREADS = 512;
-template <int DT, bool VEC>
+template <bool VEC>
 __global__ __launch_bounds__(HIST_THREADS) void k_hist(TopkArgs a, int exact_pass) {
     __shared__ uint32_t h[NB1];
     const int row = blockIdx.y;
@@ -62,7 +62,7 @@ __global__ __launch_bounds__(HIST_THREADS) void k_hist(TopkArgs a, int exact_pas
     if (i0 >= i1) return;
     for (int b = threadIdx.x; b < NB1; b += HIST_THREADS) h[b] = 0;
     __syncthreads();
-    RowLoader<DT, VEC> ld(a.g, a.ld, a.d, row);
+    RowLoader<MLMC_F32, VEC> ld(a.g, a.ld, a.d, row);
     const uint32_t lane = lane_id(), wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     uint32_t maxkey = 0;
     auto count4 = [&](const uint32_t (&b)[4], int nv) {
@@ -121,31 +121,6 @@ __global__ __launch_bounds__(HIST_THREADS) void k_hist(TopkArgs a, int exact_pas
 }
 
 // ---------------------------------------------------------------------------------------------------
-// Level draw of one row (Alg. 2 / Alg. 3 "Sample l ~ p"), run by one thread.
-// `p` is LMAX doubles of LDS scratch: a thread-local array indexed by a loop variable would live in scratch memory.
-__device__ void draw_row(const TopkArgs& a, int row, const double* norms_row, double* p) {
-    const int L = a.L;
-    if (a.draw_mode == 0) {
-        for (int l = 0; l < L; ++l) p[l] = a.p_fixed[l];
-    } else if (a.draw_mode == 1) {
-        for (int l = 0; l < L; ++l) p[l] = a.p_dev[(size_t)row * L + l];
-    } else {
-        const double* n = a.draw_mode == 2 ? a.p_dev + (size_t)row * L : norms_row;
-        double tot = 0.0;
-        for (int l = 0; l < L; ++l) tot = __dadd_rn(tot, n[l]);
-        for (int l = 0; l < L; ++l) p[l] = tot == 0.0 ? __ddiv_rn(1.0, (double)L) : __ddiv_rn(n[l], tot);
-    }
-    uint32_t x = philox_word0(a.seed, a.step, (uint32_t)row);
-    int level = draw_from_p(p, L, x);
-    double pl = p[level - 1];
-    RowInfo* ri = a.rinfo + row;
-    ri->level = level;
-    ri->weight = pl == 0.0 ? 0.0f : (float)__ddiv_rn(1.0, pl);
-    ri->draw_x = x;
-    a.level[row] = level;
-}
-
-// ---------------------------------------------------------------------------------------------------
 // Per row: zones and regions from the histogram, candidate list layout, the class table.
 // How far (in standard deviations of the sampled count) a zone reaches on either side of the estimated rank.  The
 // binomial model fits when every homogeneous stretch of a row contributes many sampled blocks; a small sample of a
@@ -167,7 +142,6 @@ __global__ __launch_bounds__(1024) void k_scan(TopkArgs a, int exact_pass) {
     __shared__ uint32_t s_ztop[ZMAX], s_zbot[ZMAX];
     __shared__ int32_t s_label[RMAX];
     __shared__ float s_est[LMAX + 2];
-    __shared__ double s_p[LMAX];
     __shared__ double s_kd[TMAX];
     __shared__ int64_t s_k[TMAX];            // the ladder (indexed by loop variables below: kept out of the argument block)
     __shared__ uint16_t s_gexp[GMAX], s_gband[GMAX];
@@ -193,11 +167,9 @@ __global__ __launch_bounds__(1024) void k_scan(TopkArgs a, int exact_pass) {
     const bool exact = exact_pass || a.sample_shift == 0;
     const uint32_t* gh = (exact_pass ? a.hist2 : a.hist) + (size_t)row * NB1;
 
+    if (tid < 64 && !exact_pass && !a.all_thresholds) draw_row(a, row, a.norms + (size_t)row * L);  // p is known up front: draw before anything else
     if (tid == 0) {
-        if (!exact_pass) {
-            ri->respec = 0;
-            if (!a.all_thresholds) draw_row(a, row, nullptr, s_p);  // p is known up front: draw before anything else
-        }
+        if (!exact_pass) ri->respec = 0;
         ri->exact = exact ? 1 : 0;
         s_lev = a.all_thresholds ? 0 : ri->level;
     }
@@ -396,14 +368,13 @@ __global__ __launch_bounds__(1024) void k_scan(TopkArgs a, int exact_pass) {
             }
         }
         __syncthreads();
-        if (tid < L) s_p[tid] = sqrt((double)s_est[tid + 1]);   // the square roots side by side, the rest in order
-        __syncthreads();
-        if (tid == 0) {
-            double* p = s_p;
+        if (tid < 64) {   // as in draw_row
+            const double n = sqrt((double)s_est[tid < L ? tid + 1 : 0]);
             double tot = 0.0;
-            for (int l = 0; l < L; ++l) tot += p[l];
-            for (int l = 0; l < L; ++l) p[l] = tot > 0.0 ? p[l] / tot : 1.0 / (double)L;
-            s_lev = draw_from_p(p, L, philox_word0(a.seed, a.step, (uint32_t)row));
+            for (int l = 0; l < L; ++l) tot += lane_f64(n, l);
+            const double p = tot > 0.0 ? n / tot : 1.0 / (double)L;
+            const int lev_p = wave_draw_from_p(p, L, philox_word0(a.seed, a.step, (uint32_t)row));
+            if (tid == 0) s_lev = lev_p;
         }
         __syncthreads();
     }
@@ -500,7 +471,7 @@ static_assert(ZMAX <= 64 && RMAX <= 64 && GMAX <= 512, "field widths of the clas
 // LOOPED: a workgroup takes the chunks blockIdx.x, blockIdx.x + gridDim.x, ... of its row.  The redo round is launched
 // that way with a small grid, so that it costs little when, as nearly always, no row needs it; the first round has a
 // workgroup per chunk and no loop.
-template <int DT, bool VEC, bool SUMS, bool LOOPED>
+template <bool VEC, bool SUMS, bool LOOPED>
 __global__ __launch_bounds__(MAIN_THREADS) void k_main(TopkArgs a, int exact_pass) {
     __shared__ __align__(16) unsigned char lm[lm_total<SUMS>()];
     uint32_t* s_cnt = (uint32_t*)(lm + LM_CNT);
@@ -541,7 +512,7 @@ __global__ __launch_bounds__(MAIN_THREADS) void k_main(TopkArgs a, int exact_pas
 
     const int64_t c0 = (int64_t)chunk_id * a.chunk;
     const int64_t c1 = c0 + a.chunk < a.d ? c0 + a.chunk : a.d;
-    RowLoader<DT, VEC> ld(a.g, a.ld, a.d, row);
+    RowLoader<MLMC_F32, VEC> ld(a.g, a.ld, a.d, row);
     // this wave's private, worst-case sized part of the scratch list: its candidates in the order met
     // (room for twice the wave's even share of the chunk: the waves of k_main2 may take more than that share)
     uint2* priv = a.cand_priv + ((size_t)row * a.chunks_per_row + chunk_id) * (size_t)(2 * a.chunk) + (size_t)wave * (a.chunk / (MAIN_WAVES / 2));
@@ -744,7 +715,7 @@ constexpr int M2_CNT = 56 * 1024;                            // uint32 [M2_CSUB]
 constexpr int M2_END = M2_CNT + M2_CSUB * 128 * REP_CNT * 4;
 static_assert(M2_MISC_END <= M2_CNT && 2 * M2_END <= 160 * 1024 && M2_SUM % 16 == 0 && M2_ZCUR % 16 == 0, "LDS layout: two workgroups per CU");
 
-template <int DT, bool VEC, bool SUMS>
+template <bool VEC, bool SUMS>
 __global__ __launch_bounds__(M2_THREADS, 4) void k_main2(TopkArgs a) {
     __shared__ __align__(16) unsigned char lm[M2_END];
     uint32_t* s_cnt = (uint32_t*)(lm + M2_CNT);
@@ -787,7 +758,7 @@ __global__ __launch_bounds__(M2_THREADS, 4) void k_main2(TopkArgs a) {
     const int64_t c1 = c0 + hlen < a.d ? c0 + hlen : a.d;
     const int span = c1 > c0 ? (int)(c1 - c0) : 0;   // the second half of a row's last chunk may be empty
     const uint32_t relh = (uint32_t)(half * hlen);   // offsets in the entries count from the start of the chunk
-    RowLoader<DT, VEC> ld(a.g, a.ld, a.d, row);
+    RowLoader<MLMC_F32, VEC> ld(a.g, a.ld, a.d, row);
     uint2* priv = a.cand_priv + ((size_t)row * a.chunks_per_row + chunk_id) * (size_t)(2 * a.chunk) +
                   (size_t)(half * M2_WAVES + (int)wave) * (a.chunk / 8);
     const uint32_t cnt_lane = (uint32_t)M2_CNT + (lane & 15u) * 4u;
@@ -1013,7 +984,7 @@ __device__ __forceinline__ int finish_slices(const TopkArgs& a, uint32_t n) {
 }
 // A zone that the ranking launch resolves by itself: all of them in a short row, those with few candidates where the histogram is
 // exact (a zone is one bucket then).  A workgroup makes such a zone's histogram and ranks it faster than two sliced passes
-// start: 32 bf16 rows of 1e6 entries, 17 + 39 + 58 us (histogram, sliced pass, ranking) -> 6 + 7 + 61.
+// start.
 constexpr uint32_t ALONE_MAX = 16384;
 __device__ __forceinline__ bool zone_alone(const TopkArgs& a, uint32_t n) { return a.alone || (a.sample_shift == 0 && n <= ALONE_MAX); }
 // Key range of a zone: its buckets, cut at the largest key of the row (the top zone of a small sample reaches up to
@@ -1104,7 +1075,7 @@ __device__ __forceinline__ void bitonic_sort_desc(unsigned long long* v, uint32_
 
 // Read 1 of a candidate list, one item per (zone, slice): histogram of (key - kmin) >> shift.
 __global__ __launch_bounds__(FN_THREADS) void k_fhist(TopkArgs a, int exact_pass) {
-    // four lane-interleaved copies: keys with few distinct values (16-bit inputs) put many lanes on one bin, and LDS
+    // four lane-interleaved copies: keys with few distinct values put many lanes on one bin, and LDS
     // atomics of many lanes on one word take a turn each
     __shared__ uint32_t s_fh[4 * FH_BINS];
     __shared__ uint32_t s_fill[ZMAX], s_rcnt[RMAX];
@@ -1351,7 +1322,7 @@ __global__ __launch_bounds__(FN_THREADS, PHASE == 0 ? 8 : 4) void k_finish(TopkA
     if (!s_ok) return;
     // Zones that the sliced pass (phase 0) takes: those whose per-chunk counters fit its LDS.  When the thresholds'
     // bins hold few candidates (par_ok) they are gathered for ranking in LDS; when they hold many (massive ties,
-    // e.g. bf16 keys: par_big) they are moved to the zone's overflow list, on which phase 1 runs a radix select.
+    // e.g. quantised rows: par_big) they are moved to the zone's overflow list, on which phase 1 runs a radix select.
     // Every other zone is resolved by one workgroup in phase 1.
     const bool fits0 = (PHASE == 0 ? !exact_pass : !alone) && nparts * nchunks <= ZC0_CAP;   // the redo round: phase 1 only
     const bool par_ok = s_fast && fits0;
@@ -1564,7 +1535,7 @@ __global__ __launch_bounds__(FN_THREADS, PHASE == 0 ? 8 : 4) void k_finish(TopkA
             }
             if (tid < nthr) { s_res[tid] = s_pos[tid] + 1u; s_pfx[tid] = 0; }   // rank inside the overflow list
         }
-        // One threshold and a single distinct key in the overflow list (the usual case for 16-bit inputs): the key is
+        // One threshold and a single distinct key in the overflow list (the usual case of ties): the key is
         // the threshold, only the index cut is left: histogram of the indices, then the one bin ranked in LDS.
         if (tid == 0) { s_any = 0; s_nsub = 0; }
         __syncthreads();
@@ -1611,25 +1582,21 @@ __global__ __launch_bounds__(FN_THREADS, PHASE == 0 ? 8 : 4) void k_finish(TopkA
                         const int64_t w0 = e0 + (int64_t)wave * per, w1 = w0 + per < e1 ? w0 + per : e1;
                         // sixteen groups at a time, their loads issued together (a load per group in turn would cost a
                         // memory latency per 64 elements); a lane past the end of the wave's run reads the run's last element
-                        // (the element type is a compile-time tag: a run-time test inside the loop would split the loads up again)
-                        auto equal_masks = [&](auto is_bf16, int64_t j0, uint64_t (&m)[16]) {
-                            constexpr bool BF = decltype(is_bf16)::value;
+                        auto equal_masks = [&](int64_t j0, uint64_t (&m)[16]) {
                             uint32_t v[16];
 #pragma unroll
                             for (int u = 0; u < 16; ++u) {
                                 const int64_t j = j0 + u * 64 + lane;
                                 const int64_t jc = (int64_t)row * a.ld + (j < w1 ? j : w1 - 1);
-                                if (BF) v[u] = (uint32_t)((const uint16_t*)a.g)[jc] << 16;
-                                else v[u] = ((const uint32_t*)a.g)[jc];
+                                v[u] = ((const uint32_t*)a.g)[jc];
                             }
 #pragma unroll
                             for (int u = 0; u < 16; ++u) m[u] = __ballot(j0 + u * 64 + lane < w1 && key_of_bits(v[u]) == key1);
                         };
-                        auto scan_chunk = [&](auto is_bf16) {
                         uint32_t mine = 0;
                         for (int64_t j0 = w0; j0 < w1; j0 += 1024) {
                             uint64_t m[16];
-                            equal_masks(is_bf16, j0, m);
+                            equal_masks(j0, m);
 #pragma unroll
                             for (int u = 0; u < 16; ++u) mine += (uint32_t)__popcll(m[u]);
                         }
@@ -1648,7 +1615,7 @@ __global__ __launch_bounds__(FN_THREADS, PHASE == 0 ? 8 : 4) void k_finish(TopkA
                             bool found = false;
                             for (int64_t j0 = w0; j0 < w1 && !found; j0 += 1024) {
                                 uint64_t m[16];
-                                equal_masks(is_bf16, j0, m);
+                                equal_masks(j0, m);
 #pragma unroll
                                 for (int u = 0; u < 16; ++u) {
                                     const uint32_t c = (uint32_t)__popcll(m[u]);
@@ -1664,9 +1631,6 @@ __global__ __launch_bounds__(FN_THREADS, PHASE == 0 ? 8 : 4) void k_finish(TopkA
                                 }
                             }
                         }
-                        };   // scan_chunk
-                        if (a.dtype == MLMC_BF16) scan_chunk(std::true_type{});
-                        else scan_chunk(std::false_type{});
                     } else if (s_bcnt[0] <= (uint32_t)COLLECT_CAP && s_bcnt[0] > 0) {
                         const uint32_t ibin = s_bin[0];
                         batched_loop<16, FN_THREADS>(0u, xn, (uint32_t)tid, [&](uint32_t i) { return xl[i].y; }, [&](uint32_t, uint32_t j) {
@@ -1916,25 +1880,12 @@ __global__ __launch_bounds__(256) void k_norms(TopkArgs a) {
     __shared__ uint32_t s_big[TMAX][20];
     __shared__ unsigned long long s_wide[TMAX][20];   // per 32-bit word position: sum of the addends' words, carries not yet propagated
     __shared__ double s_norm[LMAX];
-    __shared__ double s_p[LMAX];
     const int row = blockIdx.x, tid = threadIdx.x;
     const RowInfo* ri = a.rinfo + row;
     const RowAcc* ra = a.racc + row;
     for (int i = tid; i < TMAX * 20; i += 256) (&s_wide[0][0])[i] = 0ull;
     __syncthreads();
-    // Every non-zero group or part sum goes to its band: v << shift is split into three 32-bit words that are added
-    // (LDS atomics, any order) to 64-bit counters of their word positions; a few hundred addends cannot overflow them.
-    auto add = [&](int band, uint64_t v, int shift) {
-        if (!v) return;
-        const int wi = shift >> 5, bs = shift & 31;
-        uint32_t parts[3];
-        parts[0] = (uint32_t)(v << bs);
-        parts[1] = (uint32_t)(bs ? v >> (32 - bs) : v >> 32);
-        parts[2] = bs ? (uint32_t)(v >> (64 - bs)) : 0u;
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-            if (parts[i] && wi + i < 20) atomicAdd(&s_wide[band][wi + i], (unsigned long long)parts[i]);
-    };
+    auto add = [&](int band, uint64_t v, int shift) { wide_add(s_wide[band], v, shift); };
     const int np = ra->n_pieces < (uint32_t)PMAX ? (int)ra->n_pieces : PMAX;
     for (int g = tid; g < GMAX + np; g += 256) {
         int band, sh;
@@ -1959,28 +1910,16 @@ __global__ __launch_bounds__(256) void k_norms(TopkArgs a) {
     __syncthreads();
     const int l = tid;
     if (l >= 1 && l <= a.L) {
-        uint64_t wide[20];
-#pragma unroll
-        for (int i = 0; i < 20; ++i) wide[i] = s_wide[l][i];
-        uint64_t carry = 0;
-#pragma unroll
-        for (int i = 0; i < 20; ++i) {
-            const uint64_t t = wide[i] + carry;
-            s_big[l][i] = (uint32_t)t;
-            carry = t >> 32;
-        }
-        BigAcc acc;
-        acc.w = s_big[l];
-        double nrm = __dsqrt_rn(acc.to_double());
+        const double nrm = __dsqrt_rn(wide_to_double(s_wide[l], s_big[l]));
         s_norm[l - 1] = nrm;
         a.norms[(size_t)row * a.L + (l - 1)] = nrm;
         if (a.norms_user) a.norms_user[(size_t)row * a.L + (l - 1)] = nrm;
     }
     __syncthreads();
-    if (tid == 0 && a.draw_mode == 3) {
-        draw_row(a, row, s_norm, s_p);
+    if (tid < 64 && a.draw_mode == 3) {
+        draw_row(a, row, s_norm);
         RowInfo* rw = a.rinfo + row;
-        rw->spec_ok = (rw->spec_level > 0 && rw->spec_level == rw->level) ? 1 : 0;
+        if (tid == 0) rw->spec_ok = (rw->spec_level > 0 && rw->spec_level == rw->level) ? 1 : 0;
     }
 }
 
@@ -2116,7 +2055,7 @@ constexpr int WR_LINES = TILE / (WR_WAVES * 64);   // 64-element lines of a wave
 constexpr int WR_STAGE = 1024;   // entries of one step that are gathered in LDS and written densely
 constexpr int WR_DIRECT = 1024;  // steps with more entries write them straight from the lanes (at most WR_STAGE)
 
-template <int DT, bool VEC>
+template <bool VEC>
 __global__ __launch_bounds__(WR_THREADS, 4) void k_write(TopkArgs a) {
     __shared__ uint32_t s_wemit[2][WR_WAVES];
     __shared__ uint2 s_out[2][WR_STAGE];
@@ -2132,7 +2071,7 @@ __global__ __launch_bounds__(WR_THREADS, 4) void k_write(TopkArgs a) {
 #pragma unroll
     for (int i = 0; i < 3; ++i) { th.tau[i] = mp.tau[i]; th.jx[i] = mp.jx[i]; }
     const float w = mp.weight;
-    RowLoader<DT, VEC> ld(a.g, a.ld, a.d, row);
+    RowLoader<MLMC_F32, VEC> ld(a.g, a.ld, a.d, row);
     const int64_t c0 = (int64_t)chunk_id * a.cchunk;
     const int64_t c1 = c0 + a.cchunk < a.d ? c0 + a.cchunk : a.d;
     const uint32_t base = a.chunk_base[(size_t)row * (nc + 1) + chunk_id];
@@ -2381,7 +2320,7 @@ __global__ __launch_bounds__(FL_THREADS) void k_filter(TopkArgs a) {
 
 // ---------------------------------------------------------------------------------------------------
 // host-side launchers
-template <int DT, bool VEC>
+template <bool VEC>
 static mlmc_status launch_select(const mlmc_plan_t* pl, const TopkArgs& a, bool sums, hipStream_t st) {
     const dim3 fgrid(a.fin_wgs, pl->M);
     const int rounds = pl->sample_shift > 0 ? 2 : 1;   // second round: rows whose sampled zones were refuted
@@ -2399,21 +2338,21 @@ static mlmc_status launch_select(const mlmc_plan_t* pl, const TopkArgs& a, bool 
         // the kernels of the redo round exit at once for rows that need none: they are timed as one entry
         const int kh = exact_pass ? K_REDO : K_HIST, ks = exact_pass ? K_REDO : K_SCAN;
         const int km = exact_pass ? K_REDO : K_MAIN;
-        MLMC_LAUNCH(kh, st, k_hist<DT, VEC><<<hgrid, HIST_THREADS, 0, st>>>(a, exact_pass));
+        MLMC_LAUNCH(kh, st, k_hist<VEC><<<hgrid, HIST_THREADS, 0, st>>>(a, exact_pass));
         MLMC_LAUNCH(ks, st, k_scan<<<pl->M, 1024, 0, st>>>(a, exact_pass));
         if (exact_pass) {
-            if (sums) MLMC_LAUNCH(km, st, k_main<DT, VEC, true, true><<<mgrid, MAIN_THREADS, 0, st>>>(a, exact_pass));
-            else MLMC_LAUNCH(km, st, k_main<DT, VEC, false, true><<<mgrid, MAIN_THREADS, 0, st>>>(a, exact_pass));
+            if (sums) MLMC_LAUNCH(km, st, k_main<VEC, true, true><<<mgrid, MAIN_THREADS, 0, st>>>(a, exact_pass));
+            else MLMC_LAUNCH(km, st, k_main<VEC, false, true><<<mgrid, MAIN_THREADS, 0, st>>>(a, exact_pass));
         } else {
             // chunks of 64 K elements or more in four count chunks: two workgroups per chunk, two per CU
             if (pl->chunk >= 65536 && pl->csub == 4) {
                 const dim3 grid2(2 * pl->chunks_per_row, pl->M);
-                if (sums) MLMC_LAUNCH(km, st, k_main2<DT, VEC, true><<<grid2, M2_THREADS, 0, st>>>(a));
-                else MLMC_LAUNCH(km, st, k_main2<DT, VEC, false><<<grid2, M2_THREADS, 0, st>>>(a));
+                if (sums) MLMC_LAUNCH(km, st, k_main2<VEC, true><<<grid2, M2_THREADS, 0, st>>>(a));
+                else MLMC_LAUNCH(km, st, k_main2<VEC, false><<<grid2, M2_THREADS, 0, st>>>(a));
             } else if (sums) {
-                MLMC_LAUNCH(km, st, k_main<DT, VEC, true, false><<<mgrid, MAIN_THREADS, 0, st>>>(a, exact_pass));
+                MLMC_LAUNCH(km, st, k_main<VEC, true, false><<<mgrid, MAIN_THREADS, 0, st>>>(a, exact_pass));
             } else {
-                MLMC_LAUNCH(km, st, k_main<DT, VEC, false, false><<<mgrid, MAIN_THREADS, 0, st>>>(a, exact_pass));
+                MLMC_LAUNCH(km, st, k_main<VEC, false, false><<<mgrid, MAIN_THREADS, 0, st>>>(a, exact_pass));
             }
         }
         // the redo round resolves every zone in the ranking launch alone (two launches fewer to pay for when, as
@@ -2449,7 +2388,7 @@ static bool side_stream_ready(const mlmc_plan_t* pl) {
     return true;
 }
 
-template <int DT, bool VEC>
+template <bool VEC>
 static mlmc_status launch_compact(const mlmc_plan_t* pl, const TopkArgs& a, hipStream_t st) {
     const dim3 grid(pl->chunks_per_row, pl->M), wgrid(pl->cchunks_per_row, pl->M);
     // rows whose drawn band was staged get their message from the staged lists, the others from a second read
@@ -2471,7 +2410,7 @@ static mlmc_status launch_compact(const mlmc_plan_t* pl, const TopkArgs& a, hipS
             return MLMC_EHIP;
         sw = pl->side_stream;
     }
-    MLMC_LAUNCH(K_WRITE, sw, k_write<DT, VEC><<<wgrid, WR_THREADS, 0, sw>>>(a));
+    MLMC_LAUNCH(K_WRITE, sw, k_write<VEC><<<wgrid, WR_THREADS, 0, sw>>>(a));
     if (a.staging) MLMC_LAUNCH(K_FILTER, st, k_filter<<<grid, FL_THREADS, fl_lds, st>>>(a));
     if (fork) {
         if (hipEventRecord(pl->side_join, sw) != hipSuccess || hipStreamWaitEvent(st, pl->side_join, 0) != hipSuccess)
@@ -2490,15 +2429,11 @@ mlmc_status topk_zero(const mlmc_plan_t* pl, void* ws, int32_t* dev_status, hipS
 }
 
 mlmc_status topk_select(const mlmc_plan_t* pl, const TopkArgs& a, bool sums, bool vec, hipStream_t st) {
-    if (pl->dtype == MLMC_F32)
-        return vec ? launch_select<MLMC_F32, true>(pl, a, sums, st) : launch_select<MLMC_F32, false>(pl, a, sums, st);
-    return vec ? launch_select<MLMC_BF16, true>(pl, a, sums, st) : launch_select<MLMC_BF16, false>(pl, a, sums, st);
+    return vec ? launch_select<true>(pl, a, sums, st) : launch_select<false>(pl, a, sums, st);
 }
 
 mlmc_status topk_compact(const mlmc_plan_t* pl, const TopkArgs& a, bool vec, hipStream_t st) {
-    if (pl->dtype == MLMC_F32)
-        return vec ? launch_compact<MLMC_F32, true>(pl, a, st) : launch_compact<MLMC_F32, false>(pl, a, st);
-    return vec ? launch_compact<MLMC_BF16, true>(pl, a, st) : launch_compact<MLMC_BF16, false>(pl, a, st);
+    return vec ? launch_compact<true>(pl, a, st) : launch_compact<false>(pl, a, st);
 }
 
 }  // namespace mlmc

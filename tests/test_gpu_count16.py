@@ -1,0 +1,96 @@
+"""Top-k of 16-bit rows, whose magnitudes are counted: both ways of the message read (slices, tile lists), at the edges of a
+step, a slice and a tile, with thresholds whose equal entries are split, against the oracle bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+import mlmc_workloads as W
+import paper_2507_05508_amd as P
+from gpu_util import check_topk_against_oracle, to_device, u32
+from oracle import mlmc as O
+
+pytestmark = pytest.mark.gpu
+
+
+def _rows(what, M, d, seed):
+    rng = np.random.default_rng(seed)
+    x = rng.standard_normal((M, d)).astype(np.float32)
+    if what == "few":
+        x = (np.round(x * 4) / 4).astype(np.float32)
+    if what == "one":
+        x = np.full((M, d), -0.75, np.float32)
+    if what == "zeros":
+        x[:, rng.random(d) < 0.9] = 0.0
+        x[M - 1] = 0.0
+    if what == "loud":      # one stretch holds nearly every large entry
+        x[:, : max(1, d // 9)] *= 1000.0
+    if what == "tiny":      # subnormal entries, and one Inf
+        x = (x * 1e-39).astype(np.float32)
+        x[0, d // 2] = np.inf
+    return W.f32_to_bf16_bits(x)
+
+
+@pytest.mark.parametrize("what", ["normal", "few", "one", "zeros", "loud", "tiny"])
+@pytest.mark.parametrize("M,d,pad", [(1, 1, 0), (2, 16384, 0), (3, 16385, 3), (1, 3 * 16384 - 1, 0), (5, 70_001, 1), (2, 300_000, 8)])
+def test_message_by_slices(what, M, d, pad):
+    G = _rows(what, M, d, 31 * d + M)
+    g = to_device(G, ld=d + pad)
+    for ladder in ([[0, 1]] if d == 1 else [[0, d // 7 + 1, d // 3 + 2, d], [d // 50, d // 50 + 1, d // 2 + 1, d - 1]]):
+        L = len(ladder) - 1
+        for p in (None, O.geometric_p(L)):
+            plan = P.Plan(P.MLMC_TOPK, M, d, P.MLMC_BF16, ladder, p)
+            plan.ws.fill_(0xFF)      # nothing is expected in it
+            for step in range(2 * L):
+                print(f"slices {what} {M}x{d}+{pad} {ladder} adaptive={p is None} step={step}", flush=True)
+                msg = P.mlmc_compress_topk(plan, g, seed=9, step=step)
+                check_topk_against_oracle(plan, G, 9, step, msg, adaptive=p is None)
+                assert plan.status() == (P.MLMC_DEV_NONFINITE if what == "tiny" else 0)
+            if p is None:
+                norms = P.mlmc_level_norms(plan, g).cpu().numpy()
+                for i in range(M):
+                    assert np.array_equal(norms[i].view(np.uint64), np.array(O.level_norms_row(G[i], ladder)[0]).view(np.uint64))
+
+
+@pytest.mark.parametrize("d", [1 << 18, (1 << 18) + 5, (1 << 18) + 4096 * 3 + 1030])
+def test_message_by_tile_lists(d):
+    """256 rows, a slice each, long enough for the tile lists; a few rows of every kind are compared."""
+    M, kinds = 256, ["normal", "few", "one", "zeros", "loud", "tiny"]
+    few = np.concatenate([_rows(k, 1, d, 7 + i) for i, k in enumerate(kinds)])
+    g = to_device(few).repeat(-(-M // len(kinds)), 1)[:M].contiguous()
+    picks = list(range(6)) + list(range(M - 7, M))
+    for ladder in ([0, 5000, d // 3 + 2, d], [d // 50, d // 50 + 1, d // 2 + 1, d - 1]):
+        plan = P.Plan(P.MLMC_TOPK, M, d, P.MLMC_BF16, ladder, None)
+        plan.ws.fill_(0xFF)
+        for step in range(3):
+            print(f"tile lists d={d} {ladder} step={step}", flush=True)
+            msg = P.mlmc_compress_topk(plan, g, seed=2, step=step)
+            torch.cuda.synchronize()
+            assert plan.status() == P.MLMC_DEV_NONFINITE
+            off = msg.row_off.cpu().numpy()
+            level = msg.level.cpu().numpy()
+            assert np.array_equal(np.diff(off), [ladder[0] + ladder[l] - ladder[l - 1] for l in level])
+            for i in picks:
+                want = O.compress_topk_row(few[i % len(kinds)], ladder, None, 2, step, i)
+                assert level[i] == want["level"]
+                assert np.array_equal(msg.norms[i].cpu().numpy().view(np.uint64), np.array(want["norms"]).view(np.uint64))
+                assert np.array_equal(u32(msg.idx[off[i]:off[i + 1]]), want["idx"]), (i, step)
+                assert np.array_equal(u32(msg.val[off[i]:off[i + 1]]), want["val"].view(np.uint32)), (i, step)
+                bounds = np.searchsorted(want["idx"], np.arange(plan.num_tiles + 1, dtype=np.int64) * P.MLMC_TILE)
+                assert np.array_equal(u32(msg.tile_off[i]), bounds.astype(np.uint32))
+
+
+@pytest.mark.parametrize("M,d", [(3, 50_003), (256, 1 << 18)])
+def test_entries_past_the_capacity_are_not_written(M, d):
+    G = _rows("normal", 1, d, 5)
+    g = to_device(G).repeat(M, 1).contiguous()
+    ladder = [100, d // 2, d]
+    plan = P.Plan(P.MLMC_TOPK, M, d, P.MLMC_BF16, ladder, None)
+    whole = P.mlmc_compress_topk(plan, g, seed=1, step=0)
+    cap = int(whole.row_off[1]) + 1001
+    cut = P.SparseMessage(plan, capacity=plan.sparse_capacity_worst, with_norms=True)
+    cut.idx.fill_(-7)
+    cut.capacity = cap
+    P.mlmc_compress_topk(plan, g, seed=1, step=0, out=cut)
+    assert plan.status() == P.MLMC_DEV_CAPACITY
+    assert torch.equal(cut.idx[:cap], whole.idx[:cap]) and torch.equal(cut.val[:cap], whole.val[:cap])
+    assert bool((cut.idx[cap:] == -7).all())
