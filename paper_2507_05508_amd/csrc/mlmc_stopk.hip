@@ -1320,7 +1320,7 @@ __global__ __launch_bounds__(256) void k_se_mark(StopkArgs a) {
     if (j0 + TILE <= a.d) {   // uniform
         uint32_t b[16][4];
 #pragma unroll
-        for (int q = 0; q < 16; ++q) ld.load4_full(j0 + q * 256 + lane * 4, b[q]);
+        for (int q = 0; q < 16; ++q) ld.load4_stream(j0 + q * 256 + lane * 4, b[q]);
 #pragma unroll
         for (int q = 0; q < 16; ++q) test(b[q], q, 4);
     } else {

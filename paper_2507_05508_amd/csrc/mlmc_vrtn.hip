@@ -1,4 +1,5 @@
 // Round-to-Nearest MLMC (Sec. 3.3, App. G.2) on gfx950.
+#include "mlmc_count16.h"
 #include "mlmc_extract.h"
 
 namespace mlmc {
@@ -191,36 +192,23 @@ static void launch_rtn_norms(int L, dim3 grid, hipStream_t st, const BitsArgs& a
 // 16-bit rows that are long enough: a row has at most 2^15 magnitudes, so one read that counts them (in LDS, one 32-bit atomic
 // per entry) gives the largest entry and, a code per magnitude instead of one per entry, the exact sums: k_bits_smax and
 // k_rtn_norms, two reads and the codes of every entry, took 154 + 440 us for 4 rows of 1.24e8 (773 before).
-constexpr int RH_KEYS = 1 << 15;
-constexpr int RH_THREADS = 1024;
-__global__ __launch_bounds__(RH_THREADS) void k_rtn_hist(BitsArgs a) {
-    __shared__ __align__(16) uint32_t s_h[RH_KEYS];
-    const int row = blockIdx.y, tid = threadIdx.x;
-    for (int i = tid; i < RH_KEYS / 4; i += RH_THREADS) ((uint4*)s_h)[i] = make_uint4(0, 0, 0, 0);
-    __syncthreads();
-    RowLoader<MLMC_BF16, true> ld(a.g, a.ld, a.d, row);
+__global__ __launch_bounds__(C16_THREADS) void k_rtn_hist(BitsArgs a) {
+    __shared__ __align__(16) uint32_t s_h[C16_LDS];
+    const int row = blockIdx.y;
     const int64_t i0 = (int64_t)blockIdx.x * a.rtn_slice, i1 = i0 + a.rtn_slice < a.d ? i0 + a.rtn_slice : a.d;
-    stream_slice<MLMC_BF16, RH_THREADS / 64>(ld, i0, i1, (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6), lane_id(),
-                                             [&](const uint32_t (&k)[4][4], const int (&nv)[4]) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-#pragma unroll
-            for (int c = 0; c < 4; ++c)
-                if (c < nv[q]) atomicAdd(&s_h[k[q][c] >> 16], 1u);
-    });
-    __syncthreads();
-    uint4* part = (uint4*)(a.rtn_part + ((size_t)row * gridDim.x + blockIdx.x) * RH_KEYS);
-    for (int i = tid; i < RH_KEYS / 4; i += RH_THREADS) part[i] = ((const uint4*)s_h)[i];
+    count16_slice((const uint16_t*)a.g + (int64_t)row * a.ld, i0, i1, s_h);
+    uint4* part = (uint4*)(a.rtn_part + ((size_t)row * gridDim.x + blockIdx.x) * C16_KEYS);
+    for (int i = threadIdx.x; i < C16_KEYS / 4; i += C16_THREADS) part[i] = ((const uint4*)s_h)[i];
 }
 // Totals over the workgroups and the largest magnitude.
 __global__ __launch_bounds__(256) void k_rtn_hmax(BitsArgs a, int wgs) {
     const int row = blockIdx.y;
     const uint32_t k = blockIdx.x * 256 + threadIdx.x;
-    const uint32_t* p = a.rtn_part + (size_t)row * wgs * RH_KEYS + k;
+    const uint32_t* p = a.rtn_part + (size_t)row * wgs * C16_KEYS + k;
     uint32_t n = 0;
 #pragma unroll 8
-    for (int g = 0; g < wgs; ++g) n += p[(size_t)g * RH_KEYS];
-    a.rtn_total[(size_t)row * RH_KEYS + k] = n;
+    for (int g = 0; g < wgs; ++g) n += p[(size_t)g * C16_KEYS];
+    a.rtn_total[(size_t)row * C16_KEYS + k] = n;
     const uint32_t m = wave_max(n ? k << 16 : 0u);
     if (m && lane_id() == 0) atomicMax(&a.racc[row].smpmax_key, m);
 }
@@ -235,7 +223,7 @@ __global__ __launch_bounds__(256) void k_rtn_hsum(BitsArgs a) {
     const double c = key_to_double(ckey), den = 2.0 * c, inv_den = __ddiv_rn(1.0, den);
     if (threadIdx.x < RTN_LMAX) { s_lo[threadIdx.x] = 0ull; s_hi[threadIdx.x] = 0ull; }
     __syncthreads();
-    const unsigned long long n = a.rtn_total[(size_t)row * RH_KEYS + key];
+    const unsigned long long n = a.rtn_total[(size_t)row * C16_KEYS + key];
     if (n) {
         const double x = key_to_double(key << 16);
         long long prev = a.F[0] > 0 ? rtn_code_abs(x, rtn_code_of(a.F[0]), c, den, inv_den) : 0;
@@ -482,9 +470,9 @@ mlmc_status rtn_compress(const mlmc_plan_t* pl, const BitsArgs& a, bool message,
         if (message) MLMC_LAUNCH(K_BITS_EXTRACT, st, k_rtn_extract<DT><<<egrid, EX_THREADS, 0, st>>>(a));                  \
     } while (0)
     if (need_norms && a.rtn_part) {
-        MLMC_LAUNCH(K_RTN_NORMS, st, k_rtn_hist<<<dim3(pl->rtn_wgs, M), RH_THREADS, 0, st>>>(a));
-        MLMC_LAUNCH(K_RTN_NORMS, st, k_rtn_hmax<<<dim3(RH_KEYS / 256, M), 256, 0, st>>>(a, pl->rtn_wgs));
-        MLMC_LAUNCH(K_RTN_NORMS, st, k_rtn_hsum<<<dim3(RH_KEYS / 256, M), 256, 0, st>>>(a));
+        MLMC_LAUNCH(K_RTN_NORMS, st, k_rtn_hist<<<dim3(pl->rtn_wgs, M), C16_THREADS, 0, st>>>(a));
+        MLMC_LAUNCH(K_RTN_NORMS, st, k_rtn_hmax<<<dim3(C16_KEYS / 256, M), 256, 0, st>>>(a, pl->rtn_wgs));
+        MLMC_LAUNCH(K_RTN_NORMS, st, k_rtn_hsum<<<dim3(C16_KEYS / 256, M), 256, 0, st>>>(a));
         MLMC_LAUNCH(K_RTN_DRAW, st, k_rtn_draw<<<(M + 63) / 64, 64, 0, st>>>(a, message ? 0 : 1));
         if (message) MLMC_LAUNCH(K_BITS_EXTRACT, st, k_rtn_extract<MLMC_BF16><<<egrid, EX_THREADS, 0, st>>>(a));
         return MLMC_OK;
