@@ -109,7 +109,8 @@ void mlmc_plan_destroy(mlmc_plan_t *plan);
  * message under that scale and finds the true maximum; a row whose true maximum needs a larger scale is
  * extracted again.  So `shift` changes run time only, never a result.  mlmc_plan picks the shift from d
  * (0 for short rows = exact at once).  0 <= shift <= 12; MLMC_EINVAL otherwise.  Top-k of MLMC_BF16 rows counts every entry's
- * magnitude in one read and takes nothing from a sample: this hook and the next two change nothing there.
+ * magnitude in one read, that of MLMC_F32 rows of 8192 to 65536 entries holds a row in registers; neither takes anything from a sample, and
+ * this hook and the next two change nothing there.
  */
 mlmc_status mlmc_plan_set_sampling(mlmc_plan_t *plan, int shift);
 

@@ -14,6 +14,7 @@ mlmc_status topk_zero(const mlmc_plan_t* pl, void* ws, int32_t* dev_status, hipS
 mlmc_status topk_select(const mlmc_plan_t* pl, const TopkArgs& a, bool sums, bool vec, hipStream_t st);
 mlmc_status topk_compact(const mlmc_plan_t* pl, const TopkArgs& a, bool vec, hipStream_t st);
 mlmc_status topk16_run(const mlmc_plan_t* pl, const TopkArgs& a, bool message, hipStream_t st);
+mlmc_status row_topk_run(const mlmc_plan_t* pl, const TopkArgs& a, bool message, hipStream_t st);
 mlmc_status bits_compress(const mlmc_plan_t* pl, const BitsArgs& a, hipStream_t st);
 mlmc_status rtn_compress(const mlmc_plan_t* pl, const BitsArgs& a, bool message, hipStream_t st);
 mlmc_status agg_bits(const mlmc_plan_t* pl, const BitsArgs& b, const int32_t* level, const int32_t* scale_exp,
@@ -54,7 +55,7 @@ static const char* const k_names[K_NUM] = {
     "k_zero", "k_hist", "k_scan", "k_main", "k_fhist", "k_finish", "k_finish_rank", "redo_pass", "k_norms", "k_bits_prep", "k_msgplan", "k_filter", "k_write",
     "k_bits_smax", "k_bits_extract", "k_bits_redo", "k_agg_bits", "k_tileoff", "k_agg_sparse", "k_message_bits", "k_rtn_norms", "k_rtn_draw",
     "k_rs_hist", "k_rs_scan", "k_rs_scatter", "k_sb_norms", "k_sb_draw", "k_sb_mark", "k_sb_offsets", "k_sb_write", "k_se_count", "k_se_scan",
-    "k_se_split", "k_se_zone", "k_c16_hist", "k_c16_scan", "k_c16_mark", "k_c16_write"};
+    "k_se_split", "k_se_zone", "k_row_select", "k_row_write", "k_c16_hist", "k_c16_scan", "k_c16_mark", "k_c16_write"};
 struct ProfPair { int id; hipEvent_t e0, e1; };
 static std::vector<ProfPair> g_pending;
 static std::vector<ProfPair> g_free;
@@ -151,6 +152,7 @@ static void fill_topk_args(const mlmc_plan_t* pl, TopkArgs& a, const void* g, in
     a.priv_cnt = (uint32_t*)(w + pl->off_priv_cnt);
     a.chunk_base = (uint32_t*)(w + pl->off_chunk_base);
     a.row_order = (int32_t*)(w + pl->off_row_order);
+    a.row_part = (uint4*)(w + pl->off_row_part);
     a.c16_part = (uint32_t*)(w + pl->off_c16_part);
     a.c16_wgs = pl->c16_wgs;
     a.c16_slice = pl->c16_slice;
@@ -532,6 +534,13 @@ mlmc_status mlmc_plan(mlmc_plan_t** plan, int kind, int M, int64_t d, int in_dty
             off = align_up(off + sizeof(uint32_t) * 32768 * (size_t)M, 256);
         }
     }
+    // 32-bit rows of up to 65536 entries fit the registers of one workgroup.  (Rows of less than two tiles keep the general way, whose staging hook can
+    // be seen in what they launch; the workspace stays that of the general way, which callers may have sized pools for.)
+    pl->row_mode = kind == MLMC_TOPK && in_dtype == MLMC_F32 && d >= ROW_MIN && d <= ROW_MAX ? 1 : 0;
+    if (pl->row_mode) {
+        pl->off_row_part = off;
+        off = align_up(off + sizeof(uint4) * 64 * (size_t)M, 256);
+    }
     if (counted) {
         int64_t wgs = 256 / M > 0 ? 256 / M : 1;   // one workgroup per CU in one round
         if (wgs > (d + 16383) / 16384) wgs = (d + 16383) / 16384;
@@ -650,6 +659,7 @@ mlmc_status mlmc_level_norms(const mlmc_plan_t* plan, const void* g, int64_t ld,
     a.draw_mode = -1;  // norms only, no draw
     a.norms_user = norms;
     if (plan->c16_wgs) return topk16_run(plan, a, false, st);
+    if (plan->row_mode) return row_topk_run(plan, a, false, st);
     mlmc_status rc = topk_zero(plan, ws, dev_status, st);
     if (rc != MLMC_OK) return rc;
     return topk_select(plan, a, true, vec_ok(g, ld), st);
@@ -702,6 +712,7 @@ mlmc_status mlmc_compress_topk(const mlmc_plan_t* plan, const void* g, int64_t l
         a.draw_mode = 3;
     }
     if (plan->c16_wgs) return topk16_run(plan, a, true, st);
+    if (plan->row_mode) return row_topk_run(plan, a, true, st);
     mlmc_status rc = topk_zero(plan, ws, dev_status, st);
     if (rc != MLMC_OK) return rc;
     // draw_mode < 3: the level is drawn before the data is touched (inside the threshold scan), so only

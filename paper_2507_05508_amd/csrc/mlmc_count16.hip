@@ -142,17 +142,6 @@ __global__ __launch_bounds__(1024) void k_c16_scan(TopkArgs a) {
     if (tid < 64 && a.draw_mode >= 0) draw_row(a, row, s_norm);
 }
 
-// Inclusive sum over the lanes of a wave, two 16-bit halves side by side.
-__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, true);   // row_shr:1
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, true);   // row_shr:2
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, true);   // row_shr:4
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, true);   // row_shr:8
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);  // row_bcast:15 into rows 1 and 3
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);  // row_bcast:31 into rows 2 and 3
-    return v;
-}
-
 // ---------------------------------------------------------------------------------------------------
 // A step of the message kernels: C16_STEP entries, a wave takes 1024 consecutive ones in two loads, a lane 8 of either half.
 constexpr int C16_STEP = 16 * C16_THREADS;

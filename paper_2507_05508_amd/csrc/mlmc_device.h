@@ -40,6 +40,17 @@ __device__ __forceinline__ uint32_t wave_excl_small(uint32_t c, uint32_t& total)
     return mbcnt(b0) + 2u * mbcnt(b1) + 4u * mbcnt(b2);
 }
 
+// Inclusive sum over the lanes of a wave.
+__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, true);   // row_shr:1
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, true);   // row_shr:2
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, true);   // row_shr:4
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, true);   // row_shr:8
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);  // row_bcast:15 into rows 1 and 3
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);  // row_bcast:31 into rows 2 and 3
+    return v;
+}
+
 // Exclusive scan over a workgroup of NT threads (NT multiple of 64, <= 1024). `lds` holds NT/64 + 1 words.
 template <int NT>
 __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* lds, uint32_t& total) {
@@ -370,7 +381,7 @@ __device__ __forceinline__ int wave_draw_from_p(double p, int L, uint32_t x) {
     const uint64_t below = __ballot(lane < L && (uint64_t)x < T);   // the last level's lane is always among them
     return (int)__builtin_ctzll(below) + 1;
 }
-__device__ inline void draw_row(const TopkArgs& a, int row, const double* norms_row) {
+__device__ inline int draw_row(const TopkArgs& a, int row, const double* norms_row) {   // returns the level
     const int L = a.L, lane = (int)lane_id(), l = lane < L ? lane : L - 1;
     double p;
     if (a.draw_mode == 0) {
@@ -393,6 +404,7 @@ __device__ inline void draw_row(const TopkArgs& a, int row, const double* norms_
         ri->draw_x = x;
         a.level[row] = level;
     }
+    return level;
 }
 
 }  // namespace mlmc

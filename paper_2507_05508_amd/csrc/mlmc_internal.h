@@ -35,6 +35,7 @@ constexpr int FIN_WGS_MAX = 128;
 // Slot of a part of a zone in the per-chunk table of zone entries: the part inside the top k_t but outside the
 // top k of the zone's previous threshold has slot t; the part below every threshold of zone z has slot TMAX + z.
 constexpr int ZPMAX = 2 * TMAX;
+constexpr int64_t ROW_MIN = 8192, ROW_MAX = 65536;   // lengths of the 32-bit rows that one workgroup handles
 
 // Class table code of a first-digit bucket, laid out so that the selection read forms its LDS addresses with
 // one or two instructions: bits 0..5 the tag an element is staged under (zone, or TAG_MEMBER); bits 6..12 the
@@ -84,6 +85,7 @@ struct RowInfo {
     MsgPlan msg;
     float weight;
     uint32_t draw_x;
+    uint32_t status;          // short rows: MLMC_DEV_* bits of the row
     uint32_t topkey;          // counted 16-bit rows: the largest magnitude
     uint32_t zone_top[ZMAX], zone_bot[ZMAX];   // first-digit buckets of the zone, top >= bot, both inclusive
     uint32_t zone_off[ZMAX], zone_cap[ZMAX];   // its candidate list inside the row's candidate buffer
@@ -143,6 +145,7 @@ struct TopkArgs {
     double* norms;           // [M][L]
     double* norms_user;      // optional copy
     int32_t* dev_status;
+    uint4* row_part;         // short rows: [M][64] message entries, and equals of the split thresholds, before every stretch
     // 16-bit rows, whose magnitudes are counted
     uint32_t* c16_part;      // [M][c16_wgs + 1][2^15] counts of a slice, then those of the slices before it; last: of the row
     int32_t c16_wgs;         // slices per row
@@ -272,7 +275,7 @@ enum KernelId {
     K_ZERO = 0, K_HIST, K_SCAN, K_MAIN, K_FHIST, K_FINISH, K_FINISH1, K_REDO, K_NORMS, K_DRAW, K_MSGPLAN, K_FILTER, K_WRITE,
     K_BITS_MAX, K_BITS_EXTRACT, K_BITS_REDO, K_AGG_BITS, K_TILEOFF, K_AGG_SPARSE, K_MSGBITS, K_RTN_NORMS, K_RTN_DRAW,
     K_RS_HIST, K_RS_SCAN, K_RS_SCATTER, K_SB_NORMS, K_SB_DRAW, K_SB_MARK, K_SB_OFFSETS, K_SB_WRITE, K_SE_COUNT, K_SE_SCAN, K_SE_SPLIT, K_SE_ZONE,
-    K_C16_HIST, K_C16_SCAN, K_C16_MARK, K_C16_WRITE, K_NUM
+    K_ROW_SELECT, K_ROW_WRITE, K_C16_HIST, K_C16_SCAN, K_C16_MARK, K_C16_WRITE, K_NUM
 };
 extern bool g_prof_on;
 void prof_begin(int id, hipStream_t st);
@@ -321,6 +324,8 @@ struct mlmc_plan_s {
     size_t off_c16_part, off_c16_list, off_c16_cnt, off_c16_pre;   // Top-k plans of 16-bit rows
     int c16_wgs;              // slices per row (0: not counted)
     int64_t c16_slice;
+    size_t off_row_part;
+    int row_mode;             // Top-k plans of short 32-bit rows: a workgroup per row
     // Side stream of the message step (MLMC_TOPK): the second read of the rows whose band was not staged runs beside the
     // assembly of the other rows' messages from the staged lists.  Created at the first call that uses it, on the device
     // current then; default priority.  Host objects only; destroyed with the plan.
