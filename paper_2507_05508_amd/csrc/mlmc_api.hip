@@ -154,6 +154,7 @@ static void fill_topk_args(const mlmc_plan_t* pl, TopkArgs& a, const void* g, in
     a.row_order = (int32_t*)(w + pl->off_row_order);
     a.row_part = (uint4*)(w + pl->off_row_part);
     a.c16_part = (uint32_t*)(w + pl->off_c16_part);
+    a.c16_occ = (uint32_t*)(w + pl->off_c16_occ);
     a.c16_wgs = pl->c16_wgs;
     a.c16_slice = pl->c16_slice;
     if (pl->off_c16_list) {
@@ -548,6 +549,8 @@ mlmc_status mlmc_plan(mlmc_plan_t** plan, int kind, int M, int64_t d, int in_dty
         pl->c16_wgs = (int)((d + pl->c16_slice - 1) / pl->c16_slice);
         pl->off_c16_part = off;
         off = align_up(off + sizeof(uint32_t) * 32768 * (size_t)(pl->c16_wgs + 1) * M, 256);
+        pl->off_c16_occ = off;
+        off = align_up(off + sizeof(uint32_t) * 8 * (size_t)pl->c16_wgs * M, 256);
         // The message read by slices (one launch) against the one by tiles (three), compress, us: 32 rows of 1000003 (slices of 126976) 102 to 108 / 92 to 117,
         // 4 of 2500000 67 / 71 to 83; 8 of 11689512 (slices of 368640) 184 / 166, 4 of 30000001 219 / 193, 1 of 1e8 176 / 169, 4 of 1.24e8 with
         // stretches of many scales 700 / 480.  Rows of one value, all of which may be in the message, are slower by tiles (604 / 796).

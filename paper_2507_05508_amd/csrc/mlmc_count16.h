@@ -6,6 +6,7 @@ namespace mlmc {
 
 constexpr int C16_KEYS = 1 << 15;       // magnitudes of a 16-bit entry: its bits without the sign
 constexpr int C16_THREADS = 1024;
+constexpr int C16_BLOCK = 128;          // magnitudes of one exponent
 constexpr int C16_LDS = C16_KEYS + 64;  // words: a counter per magnitude; zeros are counted per lane behind them
 
 typedef uint32_t u32x4_b16 __attribute__((ext_vector_type(4), aligned(2)));

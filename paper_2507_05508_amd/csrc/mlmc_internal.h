@@ -87,6 +87,7 @@ struct RowInfo {
     uint32_t draw_x;
     uint32_t status;          // short rows: MLMC_DEV_* bits of the row
     uint32_t topkey;          // counted 16-bit rows: the largest magnitude
+    uint32_t occ[8];          // the exponents that occur, a bit each
     uint32_t zone_top[ZMAX], zone_bot[ZMAX];   // first-digit buckets of the zone, top >= bot, both inclusive
     uint32_t zone_off[ZMAX], zone_cap[ZMAX];   // its candidate list inside the row's candidate buffer
     int32_t zone_t0[ZMAX], zone_t1[ZMAX];      // thresholds t0..t1 (those that are active) lie in the zone
@@ -148,6 +149,7 @@ struct TopkArgs {
     uint4* row_part;         // short rows: [M][64] message entries, and equals of the split thresholds, before every stretch
     // 16-bit rows, whose magnitudes are counted
     uint32_t* c16_part;      // [M][c16_wgs + 1][2^15] counts of a slice, then those of the slices before it; last: of the row
+    uint32_t* c16_occ;       // [M][c16_wgs][8] a bit per exponent: it occurs in the slice
     int32_t c16_wgs;         // slices per row
     int64_t c16_slice;       // entries of a slice, a multiple of TILE
     uint32_t* c16_list;      // [M][ntiles][TILE] entries that may be in the message: bits << 16 | offset in the tile (null: one workgroup per slice writes it)
@@ -321,7 +323,7 @@ struct mlmc_plan_s {
     size_t off_rtn_sums, off_rtn_part, off_rtn_total;   // Round-to-Nearest plans
     int rtn_wgs;              // workgroups per row that count magnitudes (0: not counted)
     int64_t rtn_slice;
-    size_t off_c16_part, off_c16_list, off_c16_cnt, off_c16_pre;   // Top-k plans of 16-bit rows
+    size_t off_c16_part, off_c16_occ, off_c16_list, off_c16_cnt, off_c16_pre;   // Top-k plans of 16-bit rows
     int c16_wgs;              // slices per row (0: not counted)
     int64_t c16_slice;
     size_t off_row_part;
