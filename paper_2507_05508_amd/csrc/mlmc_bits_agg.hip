@@ -56,9 +56,13 @@ struct AggBitsArgs {
 //
 // The extraction's packing run backwards: a wave owns a block of EX_ELEMS elements, a lane 32 of them (half a word of every
 // plane) and their sums in registers.  Eight planes of a row transposed (transpose8) are the low bytes of the lane's 32 values, so
-// that a value costs an instruction or two to assemble whatever its width.  8 rows of 1.17e7 elements: 33 us at two or three planes
-// (wave latency: a wave's rows come one after the other), 40 us at ten (0.16 GB, 4 TB/s), 44 us for Round-to-Nearest codes; with plane
-// words as wave-wide lane masks, one conditional add per plane, it took 48, 136 and 114 us.
+// that a value costs an instruction or two to assemble whatever its width.  8 rows of 1.17e7 elements: 24 us at two or three planes
+// (wave latency: a wave's rows come one after the other), 35 us at ten (0.16 GB, 4.6 TB/s), 31 us for Round-to-Nearest codes; 4 rows of
+// 1.24e8 elements and 38 code planes in all 252 us (1.09 GB, 4.4 TB/s).  The vector instructions were two thirds of the time for the codes, so
+// their residual integers come straight from dot products of the transposed bytes (before, with every code taken out and sign-extended and two
+// 24-bit multiplications: 41 and 302 us), and the loads' addresses are scalar (a 64-bit multiplication per load in vector registers before: 27 us
+// at two or three planes, 38 at ten).  A block per wave at a time and many of them: a grid that fits the chip and goes from block to
+// block, the next one's planes in flight, took 8 % longer on the long rows.
 // The next row's first planes (the low eight of both codes for Round-to-Nearest) are in flight while a row is decoded.  The sums leave through LDS in the order of the
 // loads of the extraction, so that the dense vector is read and written 1 KB at a time.
 // PK 0: fixed point (both scales), 1: floating point, 2: Round-to-Nearest.  BASE: the ladder has a base field (F_0 > 0).
@@ -126,7 +130,17 @@ __global__ __launch_bounds__(EX_THREADS, 4) void k_agg_planes(AggBitsArgs a, con
     typedef const __attribute__((address_space(1))) char* GlobalBytes;
     const size_t step = (size_t)b.nwords * 8;
     const GlobalBytes base = (GlobalBytes)planes + h0 * 4;
-    auto plane = [&](GlobalBytes row, int p) -> uint32_t { return *(const __attribute__((address_space(1))) uint32_t*)(row + (size_t)p * step + off); };
+    // n planes of the row from p0 on, q past the last of them: that one again.  The address is scalar and goes from plane to plane (opaque, or the
+    // compiler keeps a vector of addresses for every load).
+    auto planes_from = [&](GlobalBytes row, int p0, int have, auto n, uint32_t* r) {
+        GlobalBytes at = row + (size_t)(uint32_t)p0 * step;
+#pragma unroll
+        for (int q = 0; q < decltype(n)::value; ++q) {
+            r[q] = *(const __attribute__((address_space(1))) uint32_t*)(at + off);
+            at += q + 1 < have ? step : (size_t)0;
+            asm volatile("" : "+s"(at));
+        }
+    };
     auto uni = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
     auto funi = [](float v) { return __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(v))); };
 
@@ -139,16 +153,11 @@ __global__ __launch_bounds__(EX_THREADS, 4) void k_agg_planes(AggBitsArgs a, con
         const GlobalBytes row = base + (size_t)r * b.nplanes * step;
         const int np = uni(s_row[r].np);
         if (PK == 2) {
-            const int at = np - uni(s_row[r].w), pw = uni(s_row[r].fl);
-#pragma unroll
-            for (int p = 0; p < 8; ++p) ahead[p] = plane(row, at + p < np ? at + p : np - 1);
-            if (pw > 0) {
-#pragma unroll
-                for (int p = 0; p < 8; ++p) ahead[8 + p] = plane(row, F0 + (p < pw ? p : pw - 1));
-            }
+            const int w = uni(s_row[r].w), pw = uni(s_row[r].fl);
+            planes_from(row, np - w, w, std::integral_constant<int, 8>{}, ahead);
+            if (pw > 0) planes_from(row, F0, pw, std::integral_constant<int, 8>{}, ahead + 8);
         } else {
-#pragma unroll
-            for (int p = 0; p < AHEAD; ++p) ahead[p] = plane(row, p < np ? p : np - 1);
+            planes_from(row, 0, np, std::integral_constant<int, AHEAD>{}, ahead);
         }
     };
 #pragma unroll
@@ -166,8 +175,13 @@ __global__ __launch_bounds__(EX_THREADS, 4) void k_agg_planes(AggBitsArgs a, con
         auto group = [&](int p0, int n, uint32_t (&r8)[8]) {
 #pragma unroll
             for (int q = 0; q < 8; ++q) r8[q] = 0;
+                GlobalBytes at = row + (size_t)(uint32_t)p0 * step;
 #pragma unroll
-            for (int q = 0; q < 8; ++q) if (q < n) r8[q] = plane(row, p0 + q);   // uniform
+            for (int q = 0; q < 8; ++q) {
+                if (q < n) r8[q] = *(const __attribute__((address_space(1))) uint32_t*)(at + off);   // uniform
+                at += step;
+                asm volatile("" : "+s"(at));
+            }
             transpose8(r8);
         };
         if (PK == 0) {
@@ -262,55 +276,130 @@ __global__ __launch_bounds__(EX_THREADS, 4) void k_agg_planes(AggBitsArgs a, con
                     }
             }
         } else {
-            // codes n_{b_0} (if any), n_{b_{l-1}} (if sent) and n_{b_l}, sign-extended; the residual integer k = n_cur D' - n_prev D;
-            // value = fp32(n_0) c_0 + fp32(k) coefficient
-            const int bp = fl;
-            const int bprev = bp > 0 ? bp : F0;               // level 1: the previous code is the base code
-            const int D = (1 << w) - 1, Dp = bprev > 0 ? (1 << bprev) - 1 : 1;
-            uint32_t n8[3][8], p8[3][8], z8[3][8];
+            // codes n_{b_0} (if any), n_{b_{l-1}} (if sent) and n_{b_l}; the residual integer k = n_cur D' - n_prev D;
+            // value = fp32(n_0) c_0 + fp32(k) coefficient.
+            // k comes out of dot products of small unsigned numbers: with u = n_cur + 2^(w-1) (its top bit turned) and
+            // v = D' - (n_prev + 2^(pw-1)) (the other bits turned), k = u D' + v D + a constant, modulo 2^32.
+            const int bp = fl, pw = bp > 0 ? bp : F0;         // level 1: the previous code is the base code
+            const uint32_t D = (1u << w) - 1u, Dp = pw > 0 ? (1u << pw) - 1u : 1u;
+            const uint32_t c = (pw > 0 ? D * (1u << (pw - 1)) - D * Dp : 0u) - (Dp << (w - 1));
+            const uint32_t cturn = 1u << (w - 1), cmask = D, pturn = pw > 0 ? (1u << (pw - 1)) - 1u : 0u, pmask = pw > 0 ? Dp : 0u;
+            constexpr uint32_t BYTES = 0x01010101u;
+            uint32_t z8[3][8];
             if (BASE) {
                 group(0, F0, z8[0]);
                 if (F0 > 8) group(8, F0 - 8, z8[1]);
             }
-            auto low = [&](int at, int width, uint32_t (&r8)[8]) {   // the low eight planes of a code, from `cur`
-#pragma unroll
-                for (int q = 0; q < 8; ++q) r8[q] = q < width ? cur[at + q] : 0u;
-                transpose8(r8);
+            auto add = [&](int i, int k, uint32_t num) {
+                float v = __fmul_rn((float)(int32_t)num, cl);
+                if (BASE) {
+                    const int n0 = F0 > 8 ? __builtin_amdgcn_sbfe((int)assemble<2>(z8, i, k), 0, F0) : __builtin_amdgcn_sbfe((int)z8[0][i], 8 * k, F0);
+                    v = __fadd_rn(__fmul_rn((float)n0, c0), v);
+                }
+                acc[8 * k + i] = __fadd_rn(acc[8 * k + i], v);
             };
-            if (w > 8) group(F0 + bp + 8, w - 8, n8[1]);
-            if (bp > 8) group(F0 + 8, bp - 8, p8[1]);
-            low(0, w, n8[0]);
-            if (bp > 0) low(8, bp, p8[0]);
-            auto all = [&](auto cg, auto pg) {
-                constexpr int PG = decltype(pg)::value;   // bytes of the previous code (0: none sent)
+            auto masked = [&](uint32_t (&r8)[8], uint32_t turn, uint32_t mask) {   // bits of the byte, the same in every byte
+#pragma unroll
+                for (int q = 0; q < 8; ++q) r8[q] = (r8[q] ^ ((turn & 0xFFu) * BYTES)) & ((mask & 0xFFu) * BYTES);
+            };
+            // (an empty statement of its own at the end of every way: what they have in common is not moved behind them, which
+            // would keep 32 values in registers and spill)
+            if (w <= 4 && (!BASE || bp > 0)) {   // both codes in one byte: one transposition, one dot product of nibbles
+                uint32_t r8[8];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) { r8[q] = cur[q]; r8[4 + q] = cur[8 + q]; }
+                transpose8(r8);
+                masked(r8, cturn | pturn << 4, cmask | pmask << 4);
 #pragma unroll
                 for (int k = 0; k < 4; ++k)
 #pragma unroll
-                    for (int i = 0; i < 8; ++i) {
-                        auto value = [&](auto bytes, const uint32_t (&v)[3][8], int width) -> int {
-                            constexpr int G = decltype(bytes)::value;
-                            if (G == 1) return __builtin_amdgcn_sbfe((int)v[0][i], 8 * k, width);
-                            return __builtin_amdgcn_sbfe((int)assemble<2>(v, i, k), 0, width);
-                        };
-                        const int nc = value(cg, n8, w);
-                        int n0 = 0;
-                        if (BASE) n0 = F0 > 8 ? value(std::integral_constant<int, 2>{}, z8, F0) : value(std::integral_constant<int, 1>{}, z8, F0);
-                        const int prev = PG > 0 ? value(std::integral_constant<int, PG == 0 ? 1 : PG>{}, p8, bp) : n0;
-                        float v = __fmul_rn((float)(__mul24(nc, Dp) + (PG > 0 || BASE ? __mul24(prev, -D) : 0)), cl);
-                        if (BASE) v = __fadd_rn(__fmul_rn((float)n0, c0), v);
-                        acc[8 * k + i] = __fadd_rn(acc[8 * k + i], v);
-                    }
-            };
-            using I0 = std::integral_constant<int, 0>;
-            using I1 = std::integral_constant<int, 1>;
-            using I2 = std::integral_constant<int, 2>;
-            if (w <= 8) {
-                if (bp == 0) all(I1{}, I0{});
-                else all(I1{}, I1{});
+                    for (int i = 0; i < 8; ++i) add(i, k, __builtin_amdgcn_udot8(r8[i], (Dp | D << 4) << (8 * k), c, false));
+                asm volatile("; nibbles");
             } else {
-                if (bp == 0) all(I2{}, I0{});
-                else if (bp <= 8) all(I2{}, I1{});
-                else all(I2{}, I2{});
+                auto current = [&](uint32_t (&n0)[8]) {      // the low bytes of the codes
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) n0[q] = cur[q];
+                    transpose8(n0);
+                    masked(n0, w > 8 ? 0u : cturn, cmask);
+                };
+                auto previous = [&](uint32_t (&p0)[8]) {
+                    if (!BASE || bp > 0) {
+#pragma unroll
+                        for (int q = 0; q < 8; ++q) p0[q] = cur[8 + q];
+                        transpose8(p0);
+                    } else {
+#pragma unroll
+                        for (int q = 0; q < 8; ++q) p0[q] = z8[0][q];
+                    }
+                    masked(p0, pturn, pmask);
+                };
+                typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+                const u16x2 by = __builtin_bit_cast(u16x2, Dp | D << 16);
+                if (w <= 8) {
+                    uint32_t n8[8], p8[8];
+                    current(n8);
+                    if (pw > 0) {
+                        previous(p8);
+#pragma unroll
+                        for (int k = 0; k < 4; ++k)
+#pragma unroll
+                            for (int i = 0; i < 8; ++i)
+                                add(i, k, __builtin_amdgcn_udot4(p8[i], D << (8 * k), __builtin_amdgcn_udot4(n8[i], Dp << (8 * k), c, false), false));
+                        asm volatile("; bytes");
+                    } else {
+#pragma unroll
+                        for (int k = 0; k < 4; ++k)
+#pragma unroll
+                            for (int i = 0; i < 8; ++i) add(i, k, __builtin_amdgcn_udot4(n8[i], Dp << (8 * k), c, false));
+                        asm volatile("; first bytes");
+                    }
+                } else {
+                    uint32_t n8[8], h8[8];
+                    group(F0 + bp + 8, w - 8, h8);
+                    masked(h8, cturn >> 8, cmask >> 8);
+                    current(n8);
+                    if (pw == 0) {
+#pragma unroll
+                        for (int k = 0; k < 4; ++k)
+#pragma unroll
+                            for (int i = 0; i < 8; ++i) {
+                                const uint32_t both = __builtin_amdgcn_perm(h8[i], n8[i], 0x0C0C0400u + 0x0101u * (uint32_t)k);
+                                add(i, k, __builtin_amdgcn_udot2(__builtin_bit_cast(u16x2, both), by, c, false));
+                            }
+                        asm volatile("; first words");
+                    } else if (pw <= 8) {
+                        uint32_t p8[8];
+                        previous(p8);
+#pragma unroll
+                        for (int k = 0; k < 4; ++k)
+#pragma unroll
+                            for (int i = 0; i < 8; ++i) {
+                                const uint32_t one = __builtin_amdgcn_perm(h8[i], n8[i], 0x0C0C0400u + 0x0101u * (uint32_t)k);
+                                const uint32_t both = __builtin_amdgcn_perm(p8[i], one, 0x0C040100u + 0x010000u * (uint32_t)k);
+                                add(i, k, __builtin_amdgcn_udot2(__builtin_bit_cast(u16x2, both), by, c, false));
+                            }
+                        asm volatile("; words and bytes");
+                    } else {
+                        uint32_t p8[8], q8[8];
+                        if (bp > 0) {
+                            group(F0 + 8, bp - 8, q8);
+                        } else {
+#pragma unroll
+                            for (int q = 0; q < 8; ++q) q8[q] = BASE ? z8[1][q] : 0u;
+                        }
+                        masked(q8, pturn >> 8, pmask >> 8);
+                        previous(p8);
+#pragma unroll
+                        for (int k = 0; k < 4; ++k)
+#pragma unroll
+                            for (int i = 0; i < 8; ++i) {
+                                const uint32_t one = __builtin_amdgcn_perm(h8[i], n8[i], 0x0C0C0400u + 0x0101u * (uint32_t)k);
+                                const uint32_t both = one | __builtin_amdgcn_perm(q8[i], p8[i], 0x04000C0Cu + 0x01010000u * (uint32_t)k);
+                                add(i, k, __builtin_amdgcn_udot2(__builtin_bit_cast(u16x2, both), by, c, false));
+                            }
+                        asm volatile("; words");
+                    }
+                }
             }
         }
     }
