@@ -307,7 +307,6 @@ __global__ __launch_bounds__(64) void k_rtn_draw(BitsArgs a, int norms_only) {
 struct RtnPlaneCode {    // one of the (up to three) codes of a row's message
     double mul_in, mul_out;   // D / 2c, moved towards and away from zero
     RtnCode code;
-    int32_t at;               // its first plane
 };
 // Code planes of the drawn message.  A code n = rne(a D / 2c) comes from one fused multiply-add: a * fl(D / 2c) plus
 // 1.5 2^52 leaves the rounded integer, sign included, in the low word.  Rounding the multiplier can only matter at an
@@ -315,7 +314,10 @@ struct RtnPlaneCode {    // one of the (up to three) codes of a row's message
 // integer below 2^40), so the product is formed twice, with the multiplier moved 2^-44 towards and away from zero:
 // where the two agree the code is exact; they differ at a tie and only there, and the code is the even one of them (at the
 // largest entry itself, D / 2, it is cut).  A block with a tie is formed twice; rows with few significant bits (16-bit ones, or such
-// widened) may tie in every block: 8 rows of 1.17e7 fp32 entries, compress, 272 us, 338 with ties everywhere (1829 with a division each).
+// widened) may tie in every block: 8 rows of 1.17e7 fp32 entries, compress, 245 us, 260 with ties everywhere (1829 with a division each).
+// The codes of an element meet in one word, pushed in from its top, one instruction each (alignbit); masked and shifted into place it was two,
+// and the kernel, bound by instruction issue and short of registers, took 88 us for those rows instead of 69 (5.6 TB/s).  16-bit rows go at
+// the rate of a copy either way: 4 rows of 1.24e8, 38 planes in all, 316 us (5.0 TB/s).
 // A block's elements stay in LDS and are read once per code, so that the codes in the making are all the registers hold.
 template <int DT>
 __global__ __launch_bounds__(EX_THREADS, 4) void k_rtn_extract(BitsArgs a) {
@@ -342,7 +344,6 @@ __global__ __launch_bounds__(EX_THREADS, 4) void k_rtn_extract(BitsArgs a) {
             const double mul = c > 0.0 ? __ddiv_rn(k.code.D, den) : 0.0;   // a zero row has only zero codes
             k.mul_in = __dmul_rn(mul, 1.0 - 0x1p-44);
             k.mul_out = __dmul_rn(mul, 1.0 + 0x1p-44);
-            k.at = threadIdx.x == 0 ? 0 : threadIdx.x == 1 ? b0 : b0 + b1;
         }
     }
     __syncthreads();
@@ -351,11 +352,11 @@ __global__ __launch_bounds__(EX_THREADS, 4) void k_rtn_extract(BitsArgs a) {
     for_blocks(ld, buf, blk, stride, nblk, nwhole, [&](int64_t at_blk) {
         uint32_t x[32], tie = nonfinite ? 1u : 0u;
 #pragma unroll
-        for (int i = 0; i < 32; ++i) x[i] = 0;
+        for (int i = 0; i < 32; ++i) asm volatile("" : "=v"(x[i]));   // what the codes do not fill is not looked at
 #pragma unroll 1
         for (int k = 0; k < nc; ++k) {
             const double mul_in = s_code[k].mul_in, mul_out = s_code[k].mul_out;
-            const uint32_t mask = (1u << s_code[k].code.b) - 1u, at = (uint32_t)s_code[k].at;
+            const uint32_t width = (uint32_t)s_code[k].code.b;
             wave_lds_sync();   // the elements are read again for every code (kept, their doubles would take 64 registers)
             const uint32_t from = ld.take_at(wave * (EX_ELEMS * 4));
 #pragma unroll
@@ -366,8 +367,8 @@ __global__ __launch_bounds__(EX_THREADS, 4) void k_rtn_extract(BitsArgs a) {
                 for (int i = 0; i < Loader::EPC; ++i) {
                     const double av = (double)__uint_as_float(b[i]);
                     const int n = __double2loint(__fma_rn(av, mul_in, 0x1.8p52)), m = __double2loint(__fma_rn(av, mul_out, 0x1.8p52));
-                    tie |= (uint32_t)(n ^ m);
-                    x[h * Loader::EPC + i] |= ((uint32_t)n & mask) << at;
+                    tie = __builtin_amdgcn_bitop3_b32(tie, (uint32_t)n, (uint32_t)m, 0xF6);   // tie | (n ^ m)
+                    x[h * Loader::EPC + i] = __builtin_amdgcn_alignbit((uint32_t)n, x[h * Loader::EPC + i], width);
                 }
             }
         }
@@ -404,7 +405,7 @@ __global__ __launch_bounds__(EX_THREADS, 4) void k_rtn_extract(BitsArgs a) {
 #pragma unroll 1
                 for (int k = 0; k < nc; ++k) {
                     const double mul_in = s_code[k].mul_in, mul_out = s_code[k].mul_out;
-                    const uint32_t mask = (1u << s_code[k].code.b) - 1u, at = (uint32_t)s_code[k].at;
+                    const uint32_t width = (uint32_t)s_code[k].code.b;
                     const int N = s_code[k].code.N;
 #pragma unroll
                     for (int u = 0; u < 4; ++u) {
@@ -412,7 +413,7 @@ __global__ __launch_bounds__(EX_THREADS, 4) void k_rtn_extract(BitsArgs a) {
                         const int m = __double2loint(__fma_rn(av[u], mul_out, 0x1.8p52));
                         n = n & 1 ? m : n;
                         n = n < -N ? -N : n > N ? N : n;
-                        v[u] |= ((uint32_t)n & mask) << at;
+                        v[u] = __builtin_amdgcn_alignbit((uint32_t)n, v[u], width);
                     }
                 }
 #pragma unroll
@@ -430,12 +431,12 @@ __global__ __launch_bounds__(EX_THREADS, 4) void k_rtn_extract(BitsArgs a) {
                 transpose8(r);
 #pragma unroll
                 for (int p = 0; p < 8; ++p)
-                    if (8 * B + p < np) w.put(r[p]);   // uniform
+                    if (8 * B + p >= 32 - np) w.put(r[p]);   // uniform
             };
-            put(std::integral_constant<int, 0>{});
-            if (np > 8) put(std::integral_constant<int, 1>{});
-            if (np > 16) put(std::integral_constant<int, 2>{});
-            if (np > 24) put(std::integral_constant<int, 3>{});
+            if (np > 24) put(std::integral_constant<int, 0>{});
+            if (np > 16) put(std::integral_constant<int, 1>{});
+            if (np > 8) put(std::integral_constant<int, 2>{});
+            put(std::integral_constant<int, 3>{});
         }
     });
 }
