@@ -33,14 +33,16 @@ def algorithmic_bytes(w, kernel, nnz_total, planes_bytes):
     produces (no re-reads, no scratch lists)."""
     s_in = 2 if w.dtype == "bf16" else 4
     in_bytes = w.M * w.d * s_in
-    if kernel in ("k_main", "k_bits_max", "k_bits_smax", "k_rtn_norms", "k_se_count", "k_se_split"):
+    if kernel in ("k_main", "k_bits_max", "k_bits_smax", "k_rtn_norms", "k_se_count", "k_se_split", "k_c16_hist", "k_c16_mark", "k_row_select"):
         return in_bytes                                   # one read of every input element
     if kernel == "k_rs_scatter":
         return 16 * w.M * w.d                             # a sort pass: every {key, index} pair read and written
     if kernel == "k_rs_hist":
         return 8 * w.M * w.d
-    if kernel == "k_write":
+    if kernel in ("k_write", "k_row_write"):
         return in_bytes + 8 * nnz_total                   # read the rows, write (idx, val)
+    if kernel == "k_c16_write":
+        return 8 * nnz_total                              # the message; its short-slice form reads the rows once more
     if kernel == "k_agg_sparse":
         return 8 * nnz_total + 4 * w.d                    # read the messages, write the dense update
     if kernel == "k_bits_extract":
@@ -66,7 +68,8 @@ def kernel_sources_digest():
 _TRACE_NAME = {"k_main2": "k_main", "k_rtn_extract": "k_bits_extract", "k_sb_clear": "k_zero", "k_agg_planes": "k_agg_bits",
                "k_se_coarse": "k_hist", "k_se_map": "k_scan", "k_se_reduce": "k_se_scan", "k_se_norms": "k_sb_norms",
                "k_se_wide": "k_se_zone", "k_se_mark": "k_sb_mark", "k_se_offsets": "k_sb_offsets", "k_se_write": "k_sb_write",
-               "k_rtn_prep": "k_bits_prep", "k_rtn_hist": "k_rtn_norms", "k_rtn_hmax": "k_rtn_norms", "k_rtn_hsum": "k_rtn_norms"}
+               "k_rtn_prep": "k_bits_prep", "k_rtn_hist": "k_rtn_norms", "k_rtn_hmax": "k_rtn_norms", "k_rtn_hsum": "k_rtn_norms",
+               "k_c16_reduce": "k_c16_scan", "k_c16_offsets": "k_c16_scan", "k_c16_expand": "k_c16_write"}
 
 
 def measured_traffic(workload, kernel):

@@ -807,7 +807,7 @@ mlmc_status topk16_run(const mlmc_plan_t* pl, const TopkArgs& a, bool message, h
         const dim3 mgrid((unsigned)(mw < cap ? mw : cap), pl->M), egrid((unsigned)(mw < 4 * cap ? mw : 4 * cap), pl->M);
         MLMC_LAUNCH(K_C16_MARK, st, k_c16_mark<<<mgrid, MK_THREADS, 0, st>>>(a));
         const int64_t span = (pl->ntiles + 65535) / 65536 * 1024;   // at most 64 workgroups a row: what they add up in front of their tiles stays small
-        MLMC_LAUNCH(K_C16_MARK, st, k_c16_offsets<<<dim3((unsigned)((pl->ntiles + span - 1) / span), pl->M), 1024, 0, st>>>(a, span));
+        MLMC_LAUNCH(K_C16_SCAN, st, k_c16_offsets<<<dim3((unsigned)((pl->ntiles + span - 1) / span), pl->M), 1024, 0, st>>>(a, span));
         MLMC_LAUNCH(K_C16_WRITE, st, k_c16_expand<<<egrid, 256, 0, st>>>(a));
     } else {
         MLMC_LAUNCH(K_C16_WRITE, st, k_c16_write<<<grid, C16_THREADS, 0, st>>>(a));
