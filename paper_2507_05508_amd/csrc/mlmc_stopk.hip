@@ -230,64 +230,75 @@ __global__ __launch_bounds__(SN_WAVES * 64) void k_sb_norms(StopkArgs a, const u
 // Level draw of every row (Alg. 3): p_l = Delta_l / (Delta_1 + ... + Delta_L).  The sum and the running CDF are taken in
 // level order by one thread (the order fixes the roundings) - but only the additions: the quotients before them and the
 // integer thresholds and comparisons after them are independent per level and spread over the workgroup.  The norms
-// pass through LDS in chunks.
+// pass through LDS in chunks.  Bound by the chain of additions, which the second time ends where the draw is settled: 1000 levels 25.7 -> 12.8 us
+// against reads that are waited for and a CDF to its end; 8 rows of 1.17e7, compress + aggregate, 419 -> 408.
 constexpr int SD_CHUNK = 8192;
+static_assert(SD_CHUNK % 16 == 0, "entries are taken by sixteen");
+// next(i, v): takes s_n[i .. i + 16), i = 0, 16, ... below n (a multiple of 16), in order; true: enough.  Returns the first entry it was not given.  Sixteen
+// reads are in flight while the sixteen before them are added: waited for in turn, they took as long as the additions.
+template <class F>
+__device__ __forceinline__ int sd_sixteens(const double* s_n, int n, F next) {
+    auto fetch = [&](int i, double (&v)[16]) {
+#pragma unroll
+        for (int u = 0; u < 16; ++u) v[u] = s_n[i + u];
+        __builtin_amdgcn_sched_barrier(0);   // issued before the additions that follow
+    };
+    double va[16], vb[16];
+    fetch(0, va);
+    for (int i = 0;; i += 32) {
+        fetch(i + 16 < n ? i + 16 : 0, vb);   // past the end: not used
+        if (next(i, va) || i + 16 >= n) return i + 16;
+        fetch(i + 32 < n ? i + 32 : 0, va);
+        if (next(i + 16, vb) || i + 32 >= n) return i + 32;
+    }
+}
 __global__ __launch_bounds__(1024) void k_sb_draw(StopkArgs a) {
     __shared__ double s_n[SD_CHUNK];     // norms, then probabilities, of the chunk
     __shared__ double s_cdf[SD_CHUNK];   // running sums of the probabilities up to every level of the chunk
     __shared__ double s_tot;
+    __shared__ int32_t s_done;           // levels of the chunk that have their running sum
     __shared__ int32_t s_found;          // lowest level met so far whose threshold lies above the drawn word
     const int row = blockIdx.x, tid = threadIdx.x;
     const double* nr = a.norms + (size_t)row * a.L;
     const int L = a.L;
     double tot = 0.0;
     for (int c0 = 0; c0 < L; c0 += SD_CHUNK) {
-        const int n = L - c0 < SD_CHUNK ? L - c0 : SD_CHUNK;
+        const int n = L - c0 < SD_CHUNK ? L - c0 : SD_CHUNK, n16 = (n + 15) & ~15;
         __syncthreads();
-        for (int i = tid; i < n; i += 1024) s_n[i] = nr[c0 + i];
+        for (int i = tid; i < n16; i += 1024) s_n[i] = i < n ? nr[c0 + i] : 0.0;   // (a zero more changes no sum)
         __syncthreads();
-        if (tid == 0) {
-            int i = 0;
-            for (; i + 16 <= n; i += 16) {   // the reads of sixteen together: a read per addition would cost its latency each time
-                double v[16];
-#pragma unroll
-                for (int u = 0; u < 16; ++u) v[u] = s_n[i + u];
+        if (tid == 0)
+            (void)sd_sixteens(s_n, n16, [&](int, const double (&v)[16]) {
 #pragma unroll
                 for (int u = 0; u < 16; ++u) tot = __dadd_rn(tot, v[u]);
-            }
-            for (; i < n; ++i) tot = __dadd_rn(tot, s_n[i]);
-        }
+                return false;
+            });
     }
     if (tid == 0) { s_tot = tot; s_found = 0x7FFFFFFF; }
     __syncthreads();
     tot = s_tot;
     const uint32_t x = philox_word0(a.seed, a.step, (uint32_t)row);
     const double uni = __ddiv_rn(1.0, (double)L);
+    const double stop = __dmul_rn((double)x + 1.0, 0x1p-32);   // (exact) a running sum from here on has its threshold above the drawn word: no later level is needed
     double c = 0.0, pl = 0.0;
     int level = L;
     for (int c0 = 0; c0 < L; c0 += SD_CHUNK) {
-        const int n = L - c0 < SD_CHUNK ? L - c0 : SD_CHUNK;
+        const int n = L - c0 < SD_CHUNK ? L - c0 : SD_CHUNK, n16 = (n + 15) & ~15;
         __syncthreads();
-        for (int i = tid; i < n; i += 1024) s_n[i] = tot == 0.0 ? uni : __ddiv_rn(nr[c0 + i], tot);
+        for (int i = tid; i < n16; i += 1024) s_n[i] = i >= n ? 0.0 : tot == 0.0 ? uni : __ddiv_rn(nr[c0 + i], tot);
         __syncthreads();
-        if (tid == 0) {
-            int i = 0;
-            for (; i + 16 <= n; i += 16) {
-                double v[16];
+        if (tid == 0)
+            s_done = sd_sixteens(s_n, n16, [&](int at, const double (&v)[16]) {
+                double run[16];
 #pragma unroll
-                for (int u = 0; u < 16; ++u) v[u] = s_n[i + u];
+                for (int u = 0; u < 16; ++u) { c = __dadd_rn(c, v[u]); run[u] = c; }
 #pragma unroll
-                for (int u = 0; u < 16; ++u) { c = __dadd_rn(c, v[u]); v[u] = c; }
-#pragma unroll
-                for (int u = 0; u < 16; ++u) s_cdf[i + u] = v[u];
-            }
-            for (; i < n; ++i) {
-                c = __dadd_rn(c, s_n[i]);
-                s_cdf[i] = c;
-            }
-        }
+                for (int u = 0; u < 16; ++u) s_cdf[at + u] = run[u];
+                return c >= stop;
+            });
         __syncthreads();
-        for (int i = tid; i < n; i += 1024) {
+        const int done = s_done < n ? s_done : n;
+        for (int i = tid; i < done; i += 1024) {
             const double t = floor(__dmul_rn(s_cdf[i], 4294967296.0));
             uint64_t T;
             if (!(t > 0.0)) T = 0;

@@ -188,3 +188,13 @@ def test_stopk_zones_of_many_entries(what, d, s, dtype):
         G = W.f32_to_bf16_bits(G)
     print(f"stopk zones {what} d={d} s={s} {dtype}", flush=True)
     _run_and_check(G, s, dtype=P.MLMC_BF16 if dtype == "bf16" else P.MLMC_F32, steps=(0, 1))
+
+
+@pytest.mark.parametrize("L", [1, 2, 15, 16, 17, 31, 32, 33, 48, 63, 8191, 8192, 8193, 8192 + 33])
+def test_stopk_draw_at_the_edges_of_its_stretches(L):
+    """The running sums are taken sixteen levels at a time, in chunks of 8192, up to the one that settles the draw: rows whose draw ends
+    anywhere (equal bands, a zero row), in the first levels (one large entry) and late (bands that differ little)."""
+    rng = np.random.default_rng(L)
+    G = np.stack([np.ones(L), np.zeros(L), np.r_[1e6, np.full(L - 1, 1e-6)], 1.0 + rng.random(L)]).astype(np.float32)
+    print(f"stopk draw L={L}", flush=True)
+    _run_and_check(G, 1, steps=(0, 1, 2, 3) if L < 1000 else (0, 1))
