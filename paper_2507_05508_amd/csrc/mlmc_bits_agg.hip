@@ -477,8 +477,12 @@ __global__ __launch_bounds__(256) void k_tileoff(AggSparseArgs a) {
 }
 
 // One workgroup per dense tile: LDS accumulators, rows added one after the other (indices within a row are
-// distinct, so plain read-modify-write is race free), then one coalesced write of alpha * acc.
-__global__ __launch_bounds__(256) void k_agg_sparse(AggSparseArgs a) {
+// distinct, so plain read-modify-write is race free), then one coalesced write of alpha * acc.  A row's step is the latency of LDS and a barrier, so
+// where the tiles leave the CUs room a tile gets more threads: up to 256 tiles 1024, up to 1024 tiles 512.  32 rows, some 500 entries of each in a
+// tile, us with 256 / 512 / 1024 threads: 245 tiles 26.8 / 20.8 / 18.0, 489 29.8 / 23.7 / 22.4, 977 33.7 / 29.6 / 41.0; 16 rows, 1954 tiles 28.5 / 32.3 /
+// 43.2; 16 rows of 8 entries a tile, 489 tiles 8.9 / 8.5 / 9.7.
+template <int NT>
+__global__ __launch_bounds__(NT) void k_agg_sparse(AggSparseArgs a) {
     // dynamic LDS, sized by the number of rows (M * 12 bytes), so that a CU holds as many workgroups as its wave
     // slots allow: the tile's accumulators, then every row's start and length inside the tile
     extern __shared__ __align__(16) unsigned char s_dyn_agg[];
@@ -487,8 +491,8 @@ __global__ __launch_bounds__(256) void k_agg_sparse(AggSparseArgs a) {
     uint32_t* s_len = (uint32_t*)(s_dyn_agg + TILE * sizeof(float) + (size_t)a.M * sizeof(int64_t));
     const int64_t tile = blockIdx.x;
     const int64_t base = tile * TILE;
-    for (int i = threadIdx.x; i < TILE; i += 256) s_acc[i] = 0.0f;
-    for (int r = threadIdx.x; r < a.M; r += 256) {
+    for (int i = threadIdx.x; i < TILE; i += NT) s_acc[i] = 0.0f;
+    for (int r = threadIdx.x; r < a.M; r += NT) {
         const uint32_t* to = a.tile_off + (size_t)r * (a.ntiles + 1);
         // a tile holds at most TILE entries of a row and they lie inside the row's message: an offset table that
         // says otherwise (a failed compress call, a caller's own table) must not steer reads out of bounds
@@ -500,9 +504,9 @@ __global__ __launch_bounds__(256) void k_agg_sparse(AggSparseArgs a) {
         s_len[r] = len;
     }
     __syncthreads();
-    // rows in groups of eight: the first 256 entries of every row of the group are fetched back to back (a thread's
+    // rows in groups of eight: the first NT entries of every row of the group are fetched back to back (a thread's
     // entry, or the row's last one when it has fewer), then added in worker order
-    constexpr int RG = 8;
+    constexpr int RG = 8, U = TILE / NT - 1 < 4 ? TILE / NT - 1 : 4;
     for (int r0 = 0; r0 < a.M; r0 += RG) {
         uint32_t pidx[RG];
         float pval[RG];
@@ -528,28 +532,28 @@ __global__ __launch_bounds__(256) void k_agg_sparse(AggSparseArgs a) {
                     const uint32_t off = pidx[k] - (uint32_t)base;
                     if (off < (uint32_t)TILE) s_acc[off] = __fadd_rn(s_acc[off], pval[k]);
                 }
-                // the rest of a long row: four loads per thread in flight (past the end: the last entry, discarded)
-                for (uint32_t i0 = threadIdx.x + 256; i0 < len; i0 += 1024) {
-                    uint32_t qi[4];
-                    float qv[4];
+                // the rest of a long row: four (or all) loads per thread in flight (past the end: the last entry, discarded)
+                for (uint32_t i0 = threadIdx.x + NT; i0 < len; i0 += U * NT) {
+                    uint32_t qi[U];
+                    float qv[U];
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        const uint32_t i = i0 + (uint32_t)u * 256u;
+                    for (int u = 0; u < U; ++u) {
+                        const uint32_t i = i0 + (uint32_t)(u * NT);
                         const uint32_t e = i < len ? i : len - 1u;
                         qi[u] = a.idx[beg + e];
                         qv[u] = a.val[beg + e];
                     }
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) {
+                    for (int u = 0; u < U; ++u) {
                         const uint32_t off = qi[u] - (uint32_t)base;
-                        if (i0 + (uint32_t)u * 256u < len && off < (uint32_t)TILE) s_acc[off] = __fadd_rn(s_acc[off], qv[u]);
+                        if (i0 + (uint32_t)(u * NT) < len && off < (uint32_t)TILE) s_acc[off] = __fadd_rn(s_acc[off], qv[u]);
                     }
                 }
                 __syncthreads();
             }
         }
     }
-    for (int i = threadIdx.x; i < TILE; i += 256) {
+    for (int i = threadIdx.x; i < TILE; i += NT) {
         int64_t j = base + i;
         if (j < a.d) finish_entry(a.alpha, s_acc[i], a.out, a.eta, a.x, j);
     }
@@ -698,7 +702,10 @@ mlmc_status agg_sparse(const mlmc_plan_t* pl, const int64_t* row_off, const uint
         a.tile_off = tile_off_ws;
     }
     const size_t lds = TILE * sizeof(float) + (size_t)pl->M * (sizeof(int64_t) + sizeof(uint32_t));
-    MLMC_LAUNCH(K_AGG_SPARSE, st, k_agg_sparse<<<(unsigned)pl->ntiles, 256, lds, st>>>(a));
+    const unsigned grid = (unsigned)pl->ntiles;
+    if (grid <= 256) MLMC_LAUNCH(K_AGG_SPARSE, st, k_agg_sparse<1024><<<grid, 1024, lds, st>>>(a));
+    else if (grid <= 1024) MLMC_LAUNCH(K_AGG_SPARSE, st, k_agg_sparse<512><<<grid, 512, lds, st>>>(a));
+    else MLMC_LAUNCH(K_AGG_SPARSE, st, k_agg_sparse<256><<<grid, 256, lds, st>>>(a));
     return MLMC_OK;
 }
 

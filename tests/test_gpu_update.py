@@ -74,3 +74,24 @@ def test_update_argument_checks():
         P.mlmc_aggregate_update(plan, msg, 1.0, 1.0, x, out=x)        # out must not alias x
     with pytest.raises(P.MlmcError):
         P.mlmc_aggregate_update(plan, msg, 1.0, 1.0, x[:500])         # wrong length
+
+
+@pytest.mark.parametrize("tiles", [1, 255, 256, 257, 1023, 1024, 1025])
+def test_aggregate_by_number_of_tiles(tiles):
+    """The threads that share a tile depend on how many tiles there are; rows of a few entries, of some hundreds and of nearly all entries of a
+    tile, more rows than one group holds."""
+    M, d = 9, tiles * 4096 - 5
+    L = 3
+    rng = np.random.default_rng(tiles)
+    G = rng.standard_normal((M, d), dtype=np.float32)
+    p = [0.25, 0.25, 0.5]
+    plan = P.Plan(P.MLMC_TOPK, M, d, P.MLMC_F32, [d // 500, d // 100, d // 10, d], p)
+    print(f"aggregate tiles={tiles}", flush=True)
+    msg = P.mlmc_compress_topk(plan, torch.from_numpy(G).to("cuda:0"), seed=6, step=tiles)
+    off, idx, val = msg.row_off.cpu().numpy(), msg.idx.cpu().numpy().view(np.uint32), msg.val.cpu().numpy()
+    assert len(set(msg.level.cpu().numpy().tolist())) == L
+    rows = [{"idx": idx[off[i]:off[i + 1]], "val": val[off[i]:off[i + 1]]} for i in range(M)]
+    want = O.aggregate_sparse(rows, d, 1.0 / M).view(np.uint32)
+    for use_tile in (True, False):
+        out = P.mlmc_aggregate(plan, msg, 1.0 / M, use_tile_off=use_tile)
+        assert np.array_equal(out.cpu().numpy().view(np.uint32), want)
