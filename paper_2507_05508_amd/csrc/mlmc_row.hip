@@ -8,7 +8,10 @@
 // read, ranking, message, each over several workgroups a row and with its own tables in memory to clear), two here.  The selection of a row of
 // 65536 takes 22 us with fixed p (load 4, first digit 6, table 1, candidates listed 6, the other digits 2, places 4) and 40 with adaptive p (sums of squares 9,
 // norms and draw 4 more); the message 6.  compress, us, before / now: 4 rows of 65536, fixed p 57 / 29, adaptive 80 / 49; 1 of 16384 53 / 20, 73 / 31;
-// 64 of 32768 74 / 26, 130 / 40; nine in ten zero, 4 of 65536, 116 / 67, 550 / 138.
+// 64 of 32768 74 / 26, 130 / 40.  What rows of few or close values cost is LDS atomics of many lanes on one word, so zeros are in no list and in no
+// atomic, and where a row's candidates do not fit the list its counts are kept in copies.  4 rows of 65536, fixed p and adaptive, us, the longer rows' way / this
+// one before / now: three in ten zero 61 / 57 / 28, 84 / 146 / 47; nine in ten 120 / 61 / 28, 550 / 130 / 46; quarters of a normal 77 / 62 / 59, 113 / 135 / 110; all
+// within 4e-4 of one 96 / 107 / 70, 128 / 241 / 109; 30 % of one value 220 / 108 / 84, 290 / 160 / 113.
 #include <type_traits>
 
 #include "mlmc_device.h"
@@ -45,10 +48,11 @@ struct RowPieces {
     }
 };
 
-// One more in h[b] for the lanes that want it, lanes that share the first one's word, and then the next one's, at once.
+// One more in h[b] for the lanes that want it, lanes that share the first one's word, and then the next one's (ROUNDS in all), at once.
+template <int ROUNDS>
 __device__ __forceinline__ void count_peeled(uint32_t* h, uint32_t b, bool want) {
 #pragma unroll
-    for (int i = 0; i < 3; ++i) {
+    for (int i = 0; i < ROUNDS; ++i) {
         const uint64_t w = __ballot(want);
         if (w == 0) return;
         const int first = __builtin_ctzll(w);
@@ -86,6 +90,27 @@ constexpr int RW_QUARTERS = 4;                 // stretches of a wave's pieces: 
 constexpr int RW_D2 = 512, RW_D3 = 256;        // bins of the second and third digit
 static_assert(TMAX * RW_D2 >= NB1 && TMAX * 20 * 8 <= TMAX * RW_D3 * 4, "shared arrays");
 
+// Copies of a digit's counts where the whole row is counted: tables of BINS words, as many copies of all of them as the place of TMAX tables holds, at most 16
+// (log2 of it).  A copy begins a word behind the end of the one before and a table's words change places by its number: rows of few values are in the
+// same few bins of every table, which would be few banks.
+__device__ __forceinline__ int copies_log2(int tables) { return tables > 16 ? 0 : tables > 8 ? 1 : tables > 4 ? 2 : tables > 2 ? 3 : 4; }
+__device__ __forceinline__ uint32_t copy_at(int words, int log2_copies) { return (lane_id() & ((1u << log2_copies) - 1u)) * (uint32_t)(words + 1); }
+template <int BINS>
+__device__ __forceinline__ uint32_t place_in_copy(uint32_t table, uint32_t bin) { return table * BINS + (bin ^ ((table & 15u) << 2)); }
+// The counts in the first copy, every word in its own place, by a whole workgroup; `zeros` more in word `zero_at` (< 0: nowhere).
+template <int BINS>
+__device__ __forceinline__ void add_copies(uint32_t* h, int words, int log2_copies, int zero_at, uint32_t zeros) {
+    static_assert(BINS % 64 == 0, "a wave's words change places among themselves");
+    for (int i = threadIdx.x; i < words; i += RW_THREADS) {
+        const uint32_t at = place_in_copy<BINS>(i / BINS, i % BINS);
+        uint32_t v = i == zero_at ? zeros : 0u;
+        for (int c = 0; c < (1 << log2_copies); ++c) v += h[c * (words + 1) + at];
+        wave_lds_sync();
+        h[i] = v;
+    }
+}
+static_assert(32 * RW_D3 + 16 <= TMAX * RW_D3 && 32 * RW_D2 + 16 <= TMAX * RW_D2, "tables times copies is at most 32");
+
 // thr_tau[t]: the key at rank k_t - 1 (0xFFFFFFFF: k_t == 0); thr_jx[t]: how many entries equal to it, in index order, are within the top k_t;
 // thr_zone[t]: 1 where that is not all of them.
 template <bool SUMS>
@@ -97,11 +122,12 @@ __global__ __launch_bounds__(RW_THREADS) void k_row_select(TopkArgs a) {
     __shared__ uint32_t s_scan[RW_WAVES + 1];
     __shared__ uint32_t s_need[TMAX];
     __shared__ int32_t s_t[TMAX], s_slot[TMAX], s_first[TMAX + 1];   // thresholds that are needed; their slots; a slot's first one
+    __shared__ int32_t s_sub1st[TMAX + 1], s_nsub;   // a sub-slot's first one
     __shared__ uint32_t s_bkt[TMAX], s_rank[TMAX], s_bin[TMAX], s_tau[TMAX], s_q[TMAX], s_eq[TMAX];
     __shared__ uint16_t s_gexp[GMAX], s_gband[GMAX];
     __shared__ double s_norm[LMAX];
     __shared__ int32_t s_na, s_ns, s_lev;
-    __shared__ uint32_t s_ncand;
+    __shared__ uint32_t s_ncand, s_zeros;
     __shared__ uint4 s_part[RW_WAVES * RW_QUARTERS];
     __shared__ uint32_t s_status;
     const int row = blockIdx.x, tid = threadIdx.x, L = a.L;
@@ -130,22 +156,31 @@ __global__ __launch_bounds__(RW_THREADS) void k_row_select(TopkArgs a) {
             if (tid == 0) s_na = L + 1;
         }
     }
-    uint32_t maxkey = 0;
-    // rows of few values put many of a wave's lanes on one word, and LDS atomics on one word take a turn each: seen in the first entries
-    const uint32_t b0 = key_of_bits(r.b[0][0]) >> B1_SHIFT;
-    const bool crowded = r.n > 0 && __popcll(__ballot(b0 == (uint32_t)__builtin_amdgcn_readfirstlane((int)b0))) >= 24;   // uniform
-    auto every = [&](auto f) {   // f(key, valid), all lanes
+    // LDS atomics of many lanes on one word take a turn each.  Zeros, which a gradient may to a good part consist of, are what is missing in the counts and
+    // are in no list; and rows of few values are seen in the first entries.
+    bool crowded = false;   // uniform
+    if (r.n > 0) {
+        const uint32_t k0 = key_of_bits(r.b[0][0]);
+        const uint64_t there = __ballot(k0 != 0u && r.valid(0, lane) > 0);
+        if (there) {
+            const uint32_t b0 = (uint32_t)__builtin_amdgcn_readlane((int)(k0 >> B1_SHIFT), (int)__builtin_ctzll(there));
+            crowded = __popcll(__ballot(k0 >> B1_SHIFT == b0) & there) >= 24;
+        }
+    }
+    auto every = [&](auto f) {   // f(key, whether to count it), all lanes
 #pragma unroll
         for (int q = 0; q < RW_PIECES; ++q) {
             if (q >= r.n) continue;
             const int nv = r.valid(q, lane);
 #pragma unroll
-            for (int c = 0; c < 4; ++c) f(key_of_bits(r.b[q][c]), c < nv);
+            for (int c = 0; c < 4; ++c) {
+                const uint32_t key = key_of_bits(r.b[q][c]);
+                f(key, c < nv && key != 0u);
+            }
         }
     };
-    if (crowded) every([&](uint32_t key, bool valid) { count_peeled(s_a, key >> B1_SHIFT, valid); maxkey = valid && key > maxkey ? key : maxkey; });
-    else every([&](uint32_t key, bool valid) { if (valid) atomicAdd(&s_a[key >> B1_SHIFT], 1u); maxkey = valid && key > maxkey ? key : maxkey; });
-    if (__ballot(maxkey >= 0x7F800000u) && lane == 0) atomicOr(&s_status, (uint32_t)MLMC_DEV_NONFINITE);
+    if (crowded) every([&](uint32_t key, bool on) { count_peeled<3>(s_a, key >> B1_SHIFT, on); });
+    else every([&](uint32_t key, bool on) { if (on) atomicAdd(&s_a[key >> B1_SHIFT], 1u); });
     __syncthreads();
     const int na = s_na;
     // ---- first digit: thread t holds 16 buckets, descending with the thread ----
@@ -161,7 +196,14 @@ __global__ __launch_bounds__(RW_THREADS) void k_row_select(TopkArgs a) {
         for (int i = 0; i < 16; ++i) sum += hv[i];
         uint32_t total;
         const uint32_t before = block_excl_scan<RW_THREADS>(sum, s_scan, total);
-        if (tid == 0 && total != (uint32_t)a.d) atomicOr(&s_status, (uint32_t)MLMC_DEV_INTERNAL);
+        if (tid == RW_THREADS - 1) {   // the lowest buckets, and nothing behind them
+            if (total > (uint32_t)a.d) atomicOr(&s_status, (uint32_t)MLMC_DEV_INTERNAL);
+            hv[0] += (uint32_t)a.d - total;
+            sum += (uint32_t)a.d - total;
+            s_zeros = (uint32_t)a.d - total;
+        }
+        static_assert((0x7F800000u >> B1_SHIFT) % 16 == 0, "the buckets of Inf and NaN are whole threads'");
+        if (b_lo >= (int)(0x7F800000u >> B1_SHIFT) && sum) atomicOr(&s_status, (uint32_t)MLMC_DEV_NONFINITE);
         for (int u = 0; u < na; ++u) {
             const uint32_t k = s_need[u];
             if (k - before - 1u >= sum) continue;   // before < k <= before + sum
@@ -193,7 +235,7 @@ __global__ __launch_bounds__(RW_THREADS) void k_row_select(TopkArgs a) {
         if (lane == 0) { s_ns = ns; s_first[ns] = na; }
     }
     __syncthreads();
-    const int ns = s_ns;
+    const int ns = s_ns, zero_slot = s_bkt[na - 1] == 0u ? ns - 1 : -1;   // of the threshold in the zeros' bucket, the lowest
     // the table, and the sum groups' exponents and bands: (255 - exponent) + band grows by one step at least whenever either changes
     auto group = [&](uint32_t bucket, uint32_t band) {
         const uint32_t E = bucket >> 6, g = 255u - E + band;
@@ -229,21 +271,32 @@ __global__ __launch_bounds__(RW_THREADS) void k_row_select(TopkArgs a) {
     // ---- second digit, of the entries that share a threshold's first one: a few per cent of the row, listed for what follows as long as there is room ----
     uint32_t* list = s_a + ns * RW_D2;
     const uint32_t room = (uint32_t)(TMAX * RW_D2 - ns * RW_D2);
-    auto entries = [&](auto f) {   // f(code, key, valid, which of the lane's 64), all lanes
+    auto fours = [&](auto with_zeros, auto f) {   // f(codes, keys, whether there is one (with_zeros: one other than zero), which piece), all lanes
 #pragma unroll
         for (int q = 0; q < RW_PIECES; ++q) {
             if (q >= r.n) continue;
             const int nv = r.valid(q, lane);
-            uint32_t code[4];
+            uint32_t code[4], key[4];
+            bool on[4];
 #pragma unroll
-            for (int c = 0; c < 4; ++c) code[c] = s_tab[key_of_bits(r.b[q][c]) >> B1_SHIFT];
-#pragma unroll
-            for (int c = 0; c < 4; ++c) f(code[c], key_of_bits(r.b[q][c]), c < nv, 4 * q + c);
+            for (int c = 0; c < 4; ++c) {
+                key[c] = key_of_bits(r.b[q][c]);
+                code[c] = s_tab[key[c] >> B1_SHIFT];
+                on[c] = c < nv && (!decltype(with_zeros)::value || key[c] != 0u);
+            }
+            f(code, key, on, q);
         }
     };
+    using yes = std::true_type;
+    using no = std::false_type;
     {
         uint64_t mine = 0;   // which of the lane's entries
-        entries([&](uint32_t code, uint32_t, bool valid, int e) { mine |= (uint64_t)(valid && (code & 0x80u)) << e; });
+        auto mark = [&](const uint32_t (&code)[4], const uint32_t (&)[4], const bool (&on)[4], int q) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) mine |= (uint64_t)(on[c] && (code[c] & 0x80u)) << (4 * q + c);
+        };
+        if (zero_slot >= 0) fours(yes{}, mark);   // uniform
+        else fours(no{}, mark);
         const uint32_t c = (uint32_t)__popcll(mine), inc = wave_incl_scan(c);
         uint32_t at = 0;
         if (lane == 63) at = atomicAdd(&s_ncand, inc);
@@ -261,23 +314,39 @@ __global__ __launch_bounds__(RW_THREADS) void k_row_select(TopkArgs a) {
     }
     __syncthreads();
     const uint32_t ncand = s_ncand;
-    const bool listed = ncand <= room;
-    auto candidates = [&](auto f) {   // f(slot, key, whether there is one), all lanes of a wave
-        if (listed) {
-            for (uint32_t i = (uint32_t)wave * 64u; i < ncand; i += RW_THREADS) {   // uniform
-                const bool on = i + lane < ncand;
-                const uint32_t key = list[on ? i + lane : i];
-                f(s_tab[key >> B1_SHIFT] & 0x7Fu, key, on);
-            }
-        } else {   // many equal keys
-            entries([&](uint32_t code, uint32_t key, bool valid, int) { f(code & 0x7Fu, key, valid && (code & 0x80u)); });
+    const bool listed = ncand <= room, clumped = crowded || ncand > room / 2;   // clumped: many of them may be of one value
+    auto candidates = [&](auto f) {   // the listed ones: f(slot, key, whether there is one), all lanes of a wave
+        for (uint32_t i = (uint32_t)wave * 64u; i < ncand; i += RW_THREADS) {   // uniform
+            const bool on = i + lane < ncand;
+            const uint32_t key = list[on ? i + lane : i];
+            f(s_tab[key >> B1_SHIFT] & 0x7Fu, key, on);
         }
     };
-    candidates([&](uint32_t slot, uint32_t key, bool on) {
-        const uint32_t at = on ? slot * RW_D2 + ((key >> 8) & (RW_D2 - 1u)) : 0u;
-        if (crowded) count_peeled(s_a, at, on);
-        else if (on) atomicAdd(&s_a[at], 1u);
-    });
+    auto prefixes = [&](const uint32_t (&code)[4], const uint32_t (&key)[4], uint32_t (&w)[4]) {   // what stands at the first two digits; code: a candidate's, or anything
+#pragma unroll
+        for (int c = 0; c < 4; ++c) w[c] = s_a[code[c] & 0x80u ? (code[c] & 0x7Fu) * RW_D2 + ((key[c] >> 8) & (RW_D2 - 1u)) : 0u];
+    };
+    // Where they do not fit (many equal keys, or close ones) the row is gone through again, and the list's place holds copies of the counts
+    if (listed) {
+        candidates([&](uint32_t slot, uint32_t key, bool on) {
+            const uint32_t at = on ? slot * RW_D2 + ((key >> 8) & (RW_D2 - 1u)) : 0u;
+            if (clumped) count_peeled<1>(s_a, at, on);
+            else if (on) atomicAdd(&s_a[at], 1u);
+        });
+        if (tid == 0 && zero_slot >= 0) atomicAdd(&s_a[zero_slot * RW_D2], s_zeros);
+    } else {
+        const int words = ns * RW_D2, lc = copies_log2(ns);
+        for (int i = tid; i < ((words + 1) << lc) - 1; i += RW_THREADS) s_a[i] = 0;
+        __syncthreads();
+        uint32_t* h = s_a + copy_at(words, lc);
+        fours(yes{}, [&](const uint32_t (&code)[4], const uint32_t (&key)[4], const bool (&on)[4], int) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if (on[c] && (code[c] & 0x80u)) atomicAdd(&h[place_in_copy<RW_D2>(code[c] & 0x7Fu, (key[c] >> 8) & (RW_D2 - 1u))], 1u);
+        });
+        __syncthreads();
+        add_copies<RW_D2>(s_a, words, lc, zero_slot * RW_D2, s_zeros);
+    }
     __syncthreads();
     for (int u = wave; u < na; u += RW_WAVES) {
         if (s_slot[u] < 0) continue;   // uniform
@@ -291,19 +360,37 @@ __global__ __launch_bounds__(RW_THREADS) void k_row_select(TopkArgs a) {
         const uint32_t pfx = valid ? (uint32_t)s_slot[lane] * RW_D2 + s_bin[lane] : 0u;
         int32_t sub;
         bool fresh;
-        (void)slots(valid, pfx, sub, fresh);
-        if (fresh) s_a[pfx] = 0x80000000u | (uint32_t)sub;
+        const int nsub = slots(valid, pfx, sub, fresh);
+        if (fresh) { s_a[pfx] = 0x80000000u | (uint32_t)sub; s_sub1st[sub] = (int32_t)lane; }
         if (valid) s_eq[lane] = (uint32_t)sub;
+        if (lane == 0) { s_nsub = nsub; s_sub1st[nsub] = na; }
     }
     __syncthreads();
     // ---- third digit ----
-    candidates([&](uint32_t slot, uint32_t key, bool on) {
-        const uint32_t w = s_a[on ? slot * RW_D2 + ((key >> 8) & (RW_D2 - 1u)) : 0u];
-        const bool want = on && (w >> 31);
-        const uint32_t at = (w & 63u) * RW_D3 + (key & (RW_D3 - 1u));
-        if (crowded) count_peeled(s_b, at, want);
-        else if (want) atomicAdd(&s_b[at], 1u);
-    });
+    const uint32_t zero_sub = zero_slot >= 0 ? s_a[zero_slot * RW_D2] : 0u;
+    const int zero_at = zero_sub >> 31 ? (int)(zero_sub & 63u) * RW_D3 : -1;
+    if (listed) {
+        if (tid == 0 && zero_at >= 0) atomicAdd(&s_b[zero_at], s_zeros);
+        candidates([&](uint32_t slot, uint32_t key, bool on) {
+            const uint32_t w = s_a[on ? slot * RW_D2 + ((key >> 8) & (RW_D2 - 1u)) : 0u];
+            const bool want = on && (w >> 31);
+            const uint32_t at = (w & 63u) * RW_D3 + (key & (RW_D3 - 1u));
+            if (clumped) count_peeled<1>(s_b, at, want);
+            else if (want) atomicAdd(&s_b[at], 1u);
+        });
+    } else {
+        const int words = s_nsub * RW_D3, lc = copies_log2(s_nsub);
+        uint32_t* h = s_b + copy_at(words, lc);
+        fours(yes{}, [&](const uint32_t (&code)[4], const uint32_t (&key)[4], const bool (&on)[4], int) {
+            uint32_t w[4];
+            prefixes(code, key, w);
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if (on[c] && (code[c] & 0x80u) && (w[c] >> 31)) atomicAdd(&h[place_in_copy<RW_D3>(w[c] & 63u, key[c] & (RW_D3 - 1u))], 1u);
+        });
+        __syncthreads();
+        add_copies<RW_D3>(s_b, words, lc, zero_at, s_zeros);
+    }
     __syncthreads();
     for (int u = wave; u < na; u += RW_WAVES) {
         uint32_t tau = 0xFFFFFFFFu, rin = 0, cnt = 0;
@@ -369,8 +456,6 @@ __global__ __launch_bounds__(RW_THREADS) void k_row_select(TopkArgs a) {
                 if (lane == 63) s_part[wave * RW_QUARTERS + h] = make_uint4(n[0], n[1], n[2], n[3]);
             }
         };
-        using yes = std::true_type;
-        using no = std::false_type;
         if (split[0] || split[1] || split[2]) count(yes{}, yes{});
         else if (lo[0] != 0xFFFFFFFFu) count(yes{}, no{});
         else count(no{}, no{});
@@ -403,18 +488,65 @@ __global__ __launch_bounds__(RW_THREADS) void k_row_select(TopkArgs a) {
     auto add_square = [&](uint32_t band, uint32_t key) {
         atomicAdd(&s_sum[(255u - (key >> 23) + band) * REP_SUM + (lane & (REP_SUM - 1u))], (unsigned long long)sig_square(key));
     };
-    entries([&](uint32_t code, uint32_t key, bool valid, int) { if (valid && !(code & 0x80u)) add_square(code, key); });
-    candidates([&](uint32_t slot, uint32_t key, bool on) {
-        int u = s_first[on ? slot : 0u];
-        const int u1 = s_first[on ? slot + 1u : 0u];
-        for (; u < u1; ++u) {   // thresholds descend: the first one not above the key ends its search
-            const uint32_t tau = s_tau[u];
-            if (key < tau) continue;
-            on = on && key != tau;
-            break;
+    if (listed) {
+        auto others = [&](const uint32_t (&code)[4], const uint32_t (&key)[4], const bool (&on)[4], int) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if (on[c] && !(code[c] & 0x80u)) add_square(code[c], key[c]);
+        };
+        if (s_zeros) fours(yes{}, others);   // uniform
+        else fours(no{}, others);
+        candidates([&](uint32_t slot, uint32_t key, bool on) {
+            int u = s_first[on ? slot : 0u];
+            const int u1 = s_first[on ? slot + 1u : 0u];
+            for (; u < u1; ++u) {   // thresholds descend: the first one not above the key ends its search
+                const uint32_t tau = s_tau[u];
+                if (key < tau) continue;
+                on = on && key != tau;
+                break;
+            }
+            if (on) add_square((uint32_t)u, key);
+        });
+    } else {
+        for (int i = tid; i < ns * RW_D2; i += RW_THREADS) {   // of a prefix: its first threshold and the one behind its last, or the band of its entries
+            const uint32_t w = s_a[i];
+            int u;
+            if (w >> 31) {
+                u = (int)(0x80000000u | (uint32_t)s_sub1st[(w & 63u) + 1u] << 8 | (uint32_t)s_sub1st[w & 63u]);
+            } else {
+                u = s_first[i / RW_D2];
+                const int u1 = s_first[i / RW_D2 + 1];
+                while (u < u1 && (uint32_t)(i % RW_D2) < ((s_tau[u] >> 8) & (RW_D2 - 1u))) ++u;
+            }
+            s_a[i] = (uint32_t)u;
         }
-        if (on) add_square((uint32_t)u, key);
-    });
+        __syncthreads();
+        fours(yes{}, [&](const uint32_t (&code)[4], const uint32_t (&key)[4], const bool (&on)[4], int) {
+            uint32_t w[4], tau[4], band[4];
+            prefixes(code, key, w);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                band[c] = code[c] & 0x80u ? w[c] : code[c];
+                tau[c] = s_tau[band[c] >> 31 ? band[c] & 63u : 0u];
+            }
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                bool add = on[c];
+                if (band[c] >> 31) {
+                    uint32_t u = band[c] & 63u;
+                    const uint32_t u1 = (band[c] >> 8) & 63u;
+                    uint32_t t = tau[c];
+                    while (key[c] < t) {
+                        if (++u == u1) break;
+                        t = s_tau[u];
+                    }
+                    add = add && (u == u1 || key[c] != t);
+                    band[c] = u;
+                }
+                if (add) add_square(band[c], key[c]);
+            }
+        });
+    }
     static_assert(ROW_MAX <= 1 << 16, "squares below 2^48 in a 64-bit counter");
     __syncthreads();
     for (int g = tid; g < GMAX; g += RW_THREADS) {

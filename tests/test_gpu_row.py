@@ -23,13 +23,15 @@ def _rows(what, M, d, seed):
     if what == "zeros":
         x[:, rng.random(d) < 0.9] = 0.0
         x[M - 1] = 0.0
+    if what == "third":     # a good part zeros, the rest dense
+        x[:, rng.random(d) < 0.3] = 0.0
     if what == "wide":      # every exponent, subnormals, and one Inf
         x = np.ldexp(x, rng.integers(-149, 120, size=(M, d))).astype(np.float32)
         x[0, d // 2] = np.inf
     return x
 
 
-@pytest.mark.parametrize("what", ["normal", "few", "one", "near", "zeros", "wide"])
+@pytest.mark.parametrize("what", ["normal", "few", "one", "near", "zeros", "third", "wide"])
 @pytest.mark.parametrize("M,d,pad", [(3, 8192, 0), (2, 8193, 1), (1, 16384 + 255, 0), (2, 3 * 16384 + 257, 3), (1, 65535, 0), (2, 65536, 4)])
 def test_short_rows(what, M, d, pad):
     G = _rows(what, M, d, 17 * d + M)
@@ -62,6 +64,24 @@ def test_thresholds_in_one_bucket():
         msg = P.mlmc_compress_topk(plan, to_device(G), seed=1, step=step)
         check_topk_against_oracle(plan, G, 1, step, msg, adaptive=True)
         assert plan.status() == 0
+
+
+@pytest.mark.parametrize("what", ["normal", "near", "few", "third", "wide"])
+@pytest.mark.parametrize("L", [1, 2, 4, 8, 16, 32])
+def test_copies_of_the_counts(what, L):
+    """From one to 33 thresholds, each in a bucket of its own where the values allow it: how many copies of the counts there are
+    depends on that, and with 33 there is no room for a list at all."""
+    d = 65_536 - 3
+    G = _rows(what, 2, d, L)
+    ladder = [0 if L == 1 else d // 1000] + [(d * l) // L for l in range(1, L + 1)]
+    g = to_device(G)
+    for p in (None, O.geometric_p(L)):
+        plan = P.Plan(P.MLMC_TOPK, 2, d, P.MLMC_F32, ladder, p)
+        for step in range(3):
+            print(f"copies {what} L={L} adaptive={p is None} step={step}", flush=True)
+            msg = P.mlmc_compress_topk(plan, g, seed=3, step=step)
+            check_topk_against_oracle(plan, G, 3, step, msg, adaptive=p is None)
+            assert plan.status() == (P.MLMC_DEV_NONFINITE if what == "wide" else 0)
 
 
 def test_capacity_of_short_rows():
