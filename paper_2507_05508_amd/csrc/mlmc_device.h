@@ -213,14 +213,18 @@ struct RowLoader {
 // [i0, i1) of a row by the NW waves of a workgroup, 1024 elements at a time with the next 1024 in flight; i0 is a multiple of
 // 1024.  f(keys of four times four consecutive elements of every lane, how many of each four are there).  f gets all sixteen
 // at once so that it waits for its loads before it stores anything: the waits count loads and stores alike but can only
-// rely on the loads, so a store between them would cut the loads in flight short.
-template <int DT, int NW, class F>
+// rely on the loads, so a store between them would cut the loads in flight short.  STREAM: the row is read past the cache (load4_stream).
+template <int DT, int NW, bool STREAM, class F>
 __device__ __forceinline__ void stream_slice(const RowLoader<DT, true>& ld, int64_t i0, int64_t i1, uint32_t wave, uint32_t lane, F f) {
     const int n = (int)((i1 - i0) >> 10);
     uint32_t b0[4][4], b1[4][4];
     auto fetch = [&](int p, uint32_t (&b)[4][4]) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) ld.load4_stream(i0 + (int64_t)p * 1024 + q * 256 + lane * 4, b[q]);
+        for (int q = 0; q < 4; ++q) {
+            const int64_t j = i0 + (int64_t)p * 1024 + q * 256 + lane * 4;
+            if (STREAM) ld.load4_stream(j, b[q]);
+            else ld.load4_full(j, b[q]);
+        }
     };
     auto use = [&](uint32_t (&b)[4][4]) {
         const int nv[4] = {4, 4, 4, 4};

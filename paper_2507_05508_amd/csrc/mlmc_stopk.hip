@@ -634,7 +634,7 @@ __global__ __launch_bounds__(1024) void k_se_map(StopkArgs a) {
 }
 
 // Exact counts of a workgroup's slice of a row.
-template <int DT>
+template <int DT, bool STREAM>
 __global__ __launch_bounds__(SE_THREADS) void k_se_count(StopkArgs a) {
     __shared__ __align__(16) uint32_t s_map[SE_CB];
     __shared__ __align__(16) uint32_t s_cnt[SE_BINS];
@@ -646,7 +646,7 @@ __global__ __launch_bounds__(SE_THREADS) void k_se_count(StopkArgs a) {
     RowLoader<DT, true> ld(a.g, a.ld, a.d, row);
     const int64_t i0 = (int64_t)blockIdx.x * a.se_slice, i1 = i0 + a.se_slice < a.d ? i0 + a.se_slice : a.d;
     uint32_t maxkey = 0;
-    stream_slice<DT, SE_WAVES>(ld, i0, i1, wave, lane, [&](const uint32_t (&k)[4][4], const int (&nv)[4]) {
+    stream_slice<DT, SE_WAVES, STREAM>(ld, i0, i1, wave, lane, [&](const uint32_t (&k)[4][4], const int (&nv)[4]) {
         uint32_t e[4][4];
 #pragma unroll
         for (int q = 0; q < 4; ++q)
@@ -804,7 +804,7 @@ __global__ __launch_bounds__(256) void k_se_scan(StopkArgs a) {
 
 // Second read: sums of the regions, lists of the zones.
 constexpr int SE_SUMS_BYTES = 40960;   // sums of L + 256 groups, in 1, 2 or 4 lane-interleaved copies
-template <int DT>
+template <int DT, bool STREAM>
 __global__ __launch_bounds__(SE_THREADS) void k_se_split(StopkArgs a) {
     __shared__ __align__(16) uint32_t s_map[SE_CB];
     __shared__ __align__(16) uint16_t s_class[SE_BINS];
@@ -833,7 +833,7 @@ __global__ __launch_bounds__(SE_THREADS) void k_se_split(StopkArgs a) {
     uint32_t* list = a.se_list + (size_t)row * a.d;
     const int rs = a.se_rep;
     const uint32_t rlane = lane & ((1u << rs) - 1u), nobody = (uint32_t)a.L + 255u;
-    stream_slice<DT, SE_WAVES>(ld, i0, i1, wave, lane, [&](const uint32_t (&k)[4][4], const int (&nv)[4]) {
+    stream_slice<DT, SE_WAVES, STREAM>(ld, i0, i1, wave, lane, [&](const uint32_t (&k)[4][4], const int (&nv)[4]) {
         uint32_t cl[4][4], pos[4][4];
 #pragma unroll
         for (int q = 0; q < 4; ++q)
@@ -1294,7 +1294,7 @@ struct SegTest {
 };
 
 // Third read: a wave takes a tile of 4096 entries; its bitmap (members, and entries that a rank decides) and its counts.
-template <int DT>
+template <int DT, bool STREAM>
 __global__ __launch_bounds__(256) void k_se_mark(StopkArgs a) {
     __shared__ uint32_t s_bm[4][TILE / 32];
     const int row = blockIdx.y;
@@ -1331,7 +1331,10 @@ __global__ __launch_bounds__(256) void k_se_mark(StopkArgs a) {
     if (j0 + TILE <= a.d) {   // uniform
         uint32_t b[16][4];
 #pragma unroll
-        for (int q = 0; q < 16; ++q) ld.load4_stream(j0 + q * 256 + lane * 4, b[q]);
+        for (int q = 0; q < 16; ++q) {
+            if (STREAM) ld.load4_stream(j0 + q * 256 + lane * 4, b[q]);
+            else ld.load4_full(j0 + q * 256 + lane * 4, b[q]);
+        }
 #pragma unroll
         for (int q = 0; q < 16; ++q) test(b[q], q, 4);
     } else {
@@ -1470,6 +1473,10 @@ __global__ __launch_bounds__(256) void k_se_write(StopkArgs a) {
 template <int DT>
 static mlmc_status launch_bins(const mlmc_plan_t* pl, const StopkArgs& a, bool message, hipStream_t st) {
     const int M = pl->M;
+    // The rows are read three times, and the message's entries once more: what the last cache (256 MB) holds is best left there.  compress, us, plain reads /
+    // past the cache, s = d / 100: 1 row of 4e6 fp32 (16 MB) 118 / 125, 8 of 5e6 (160 MB) 197 / 209, 8 of 1.1e7 bf16 (176 MB) 258 / 267, 8 of 8388608 fp32 (268 MB) 268 / 276,
+    // 8 of 9e6 (288 MB) 309 / 312 (s = d / 1000: 322 / 323), 8 of 1e7 (320 MB) 336 / 334, 8 of 2.3e7 bf16 (368 MB) 471 / 462, 8 of 11689512 fp32 (374 MB) 380 / 369.
+    const bool stream = (int64_t)M * a.d * (DT == MLMC_F32 ? 4 : 2) > ((int64_t)288 << 20);
     {
         const size_t n16 = a.clear_bytes / 16;   // coarse histograms and band sums
         int blocks = (int)((n16 + 255) / 256);
@@ -1483,10 +1490,12 @@ static mlmc_status launch_bins(const mlmc_plan_t* pl, const StopkArgs& a, bool m
         MLMC_LAUNCH(K_HIST, st, k_se_coarse<DT><<<dim3((unsigned)gx, M), 512, 0, st>>>(a));
     }
     MLMC_LAUNCH(K_SCAN, st, k_se_map<DT><<<M, 1024, 0, st>>>(a));
-    MLMC_LAUNCH(K_SE_COUNT, st, k_se_count<DT><<<dim3(a.se_wgs, M), SE_THREADS, 0, st>>>(a));
+    if (stream) MLMC_LAUNCH(K_SE_COUNT, st, k_se_count<DT, true><<<dim3(a.se_wgs, M), SE_THREADS, 0, st>>>(a));
+    else MLMC_LAUNCH(K_SE_COUNT, st, k_se_count<DT, false><<<dim3(a.se_wgs, M), SE_THREADS, 0, st>>>(a));
     MLMC_LAUNCH(K_SE_SCAN, st, k_se_reduce<<<dim3(SE_BLOCKS, M), 256, 0, st>>>(a));
     MLMC_LAUNCH(K_SE_SCAN, st, k_se_scan<<<dim3(SE_BLOCKS, M), 256, 0, st>>>(a));
-    MLMC_LAUNCH(K_SE_SPLIT, st, k_se_split<DT><<<dim3(a.se_wgs, M), SE_THREADS, 0, st>>>(a));
+    if (stream) MLMC_LAUNCH(K_SE_SPLIT, st, k_se_split<DT, true><<<dim3(a.se_wgs, M), SE_THREADS, 0, st>>>(a));
+    else MLMC_LAUNCH(K_SE_SPLIT, st, k_se_split<DT, false><<<dim3(a.se_wgs, M), SE_THREADS, 0, st>>>(a));
     MLMC_LAUNCH(K_SE_ZONE, st, k_se_zone<<<dim3(a.L - 1 + (a.L + 255 + SZ_THREADS - 1) / SZ_THREADS, M), SZ_THREADS, 0, st>>>(a));
     {
         const int64_t cap = 512 / M > 0 ? 512 / M : 1;   // about two workgroups per CU: nearly always they find nothing to do
@@ -1498,7 +1507,8 @@ static mlmc_status launch_bins(const mlmc_plan_t* pl, const StopkArgs& a, bool m
     if (!message) return MLMC_OK;
     const dim3 tgrid((unsigned)((a.ntiles + 3) / 4), M);
     MLMC_LAUNCH(K_SB_DRAW, st, k_sb_draw<<<M, 1024, 0, st>>>(a));
-    MLMC_LAUNCH(K_SB_MARK, st, k_se_mark<DT><<<tgrid, 256, 0, st>>>(a));
+    if (stream) MLMC_LAUNCH(K_SB_MARK, st, k_se_mark<DT, true><<<tgrid, 256, 0, st>>>(a));
+    else MLMC_LAUNCH(K_SB_MARK, st, k_se_mark<DT, false><<<tgrid, 256, 0, st>>>(a));
     MLMC_LAUNCH(K_SB_OFFSETS, st, k_se_offsets<<<M, 1024, 0, st>>>(a));
     MLMC_LAUNCH(K_SB_WRITE, st, k_se_write<DT><<<tgrid, 256, 0, st>>>(a));
     return MLMC_OK;
