@@ -478,9 +478,10 @@ __global__ __launch_bounds__(256) void k_tileoff(AggSparseArgs a) {
 
 // One workgroup per dense tile: LDS accumulators, rows added one after the other (indices within a row are
 // distinct, so plain read-modify-write is race free), then one coalesced write of alpha * acc.  A row's step is the latency of LDS and a barrier, so
-// where the tiles leave the CUs room a tile gets more threads: up to 256 tiles 1024, up to 1024 tiles 512.  32 rows, some 500 entries of each in a
-// tile, us with 256 / 512 / 1024 threads: 245 tiles 26.8 / 20.8 / 18.0, 489 29.8 / 23.7 / 22.4, 977 33.7 / 29.6 / 41.0; 16 rows, 1954 tiles 28.5 / 32.3 /
-// 43.2; 16 rows of 8 entries a tile, 489 tiles 8.9 / 8.5 / 9.7.
+// where the tiles leave the CUs room a tile gets more threads, as far as a row has entries for them (agg_threads).  32 rows, 512 entries of each in a
+// tile, us with 256 / 512 / 1024 threads: 245 tiles 34.1 / 21.6 / 13.8, 489 38.3 / 26.2 / 18.6, 977 44.3 / 32.8 / 34.9; 1024 entries 40.3 / 38.6 / 23.6, 41.5 / 42.9 / 30.7,
+// 49.7 / 54.7 / 55.0; 16 rows, some 500 entries, 1954 tiles 28.5 / 32.3 / 43.2.  Of 32 entries or 128 a row's step is its barrier, which more waves make
+// longer: 32 rows, 245 tiles 13.2 / 12.4 / 12.9, 977 14.9 / 16.7 / 29.1; 256 rows, 1 tile 73.5 / 72.9 / 76.8, 245 79.4 / 79.4 / 80.2, 489 83.8 / 84.7 / 102.8.
 template <int NT>
 __global__ __launch_bounds__(NT) void k_agg_sparse(AggSparseArgs a) {
     // dynamic LDS, sized by the number of rows (M * 12 bytes), so that a CU holds as many workgroups as its wave
@@ -677,6 +678,19 @@ mlmc_status agg_bits(const mlmc_plan_t* pl, const BitsArgs& b, const int32_t* le
     return MLMC_OK;
 }
 
+// Threads of a tile, by the tiles and the mean entries of a row in one (adaptive plans: every level as likely as the next).
+static int agg_threads(const mlmc_plan_t* pl) {
+    double mean = 0.0;
+    if (pl->kind == MLMC_STOPK) {
+        mean = (double)pl->s;
+    } else {
+        mean = (double)pl->ladder[0];
+        for (int l = 1; l <= pl->L; ++l) mean += (pl->adaptive ? 1.0 / pl->L : pl->p[l - 1]) * (double)(pl->ladder[l] - pl->ladder[l - 1]);
+    }
+    if (mean < 192.0 * (double)pl->ntiles) return pl->ntiles <= 512 ? 512 : 256;
+    return pl->ntiles <= 256 ? 1024 : pl->ntiles <= 1024 ? 512 : 256;
+}
+
 mlmc_status agg_sparse(const mlmc_plan_t* pl, const int64_t* row_off, const uint32_t* idx, const float* val, int64_t capacity,
                        const uint32_t* tile_off, uint32_t* tile_off_ws, float alpha, float* out, float eta, float* x,
                        hipStream_t st) {
@@ -703,8 +717,9 @@ mlmc_status agg_sparse(const mlmc_plan_t* pl, const int64_t* row_off, const uint
     }
     const size_t lds = TILE * sizeof(float) + (size_t)pl->M * (sizeof(int64_t) + sizeof(uint32_t));
     const unsigned grid = (unsigned)pl->ntiles;
-    if (grid <= 256) MLMC_LAUNCH(K_AGG_SPARSE, st, k_agg_sparse<1024><<<grid, 1024, lds, st>>>(a));
-    else if (grid <= 1024) MLMC_LAUNCH(K_AGG_SPARSE, st, k_agg_sparse<512><<<grid, 512, lds, st>>>(a));
+    const int nt = agg_threads(pl);
+    if (nt == 1024) MLMC_LAUNCH(K_AGG_SPARSE, st, k_agg_sparse<1024><<<grid, 1024, lds, st>>>(a));
+    else if (nt == 512) MLMC_LAUNCH(K_AGG_SPARSE, st, k_agg_sparse<512><<<grid, 512, lds, st>>>(a));
     else MLMC_LAUNCH(K_AGG_SPARSE, st, k_agg_sparse<256><<<grid, 256, lds, st>>>(a));
     return MLMC_OK;
 }

@@ -76,16 +76,17 @@ def test_update_argument_checks():
         P.mlmc_aggregate_update(plan, msg, 1.0, 1.0, x[:500])         # wrong length
 
 
-@pytest.mark.parametrize("tiles", [1, 255, 256, 257, 1023, 1024, 1025])
-def test_aggregate_by_number_of_tiles(tiles):
-    """The threads that share a tile depend on how many tiles there are; rows of a few entries, of some hundreds and of nearly all entries of a
-    tile, more rows than one group holds."""
+@pytest.mark.parametrize("top", [1, 30])
+@pytest.mark.parametrize("tiles", [1, 255, 256, 257, 512, 513, 1023, 1024, 1025])
+def test_aggregate_by_number_of_tiles(tiles, top):
+    """The threads that share a tile depend on how many tiles there are and on how long the messages are; rows of a few entries, of some hundreds and
+    (top = 1) of nearly all entries of a tile, more rows than one group holds."""
     M, d = 9, tiles * 4096 - 5
     L = 3
     rng = np.random.default_rng(tiles)
     G = rng.standard_normal((M, d), dtype=np.float32)
     p = [0.25, 0.25, 0.5]
-    plan = P.Plan(P.MLMC_TOPK, M, d, P.MLMC_F32, [d // 500, d // 100, d // 10, d], p)
+    plan = P.Plan(P.MLMC_TOPK, M, d, P.MLMC_F32, [d // 500, d // 100, d // 10 if top == 1 else d // 50, d // top], p)
     print(f"aggregate tiles={tiles}", flush=True)
     msg = P.mlmc_compress_topk(plan, torch.from_numpy(G).to("cuda:0"), seed=6, step=tiles)
     off, idx, val = msg.row_off.cpu().numpy(), msg.idx.cpu().numpy().view(np.uint32), msg.val.cpu().numpy()
