@@ -1575,26 +1575,28 @@ __global__ __launch_bounds__(FN_THREADS, PHASE == 0 ? 8 : 4) void k_finish(TopkA
                         const uint32_t target = cnt - rin + 1u;   // the cut is the target-th of the chunk's entries equal to the key, by index
                         cut_chunk = s_bin[0];
                         cut_inside = target;
-                        const int64_t e0 = (int64_t)cut_chunk * a.cchunk;
-                        const int64_t e1 = e0 + a.cchunk < a.d ? e0 + a.cchunk : a.d;
+                        const uint32_t e0 = cut_chunk * (uint32_t)a.cchunk;   // (d < 2^31)
+                        const uint32_t e1 = e0 + (uint32_t)a.cchunk < (uint32_t)a.d ? e0 + (uint32_t)a.cchunk : (uint32_t)a.d;
                         // wave w takes a run of whole 64-element groups of the chunk, in order
-                        const int64_t per = ((e1 - e0 + FN_THREADS - 1) / FN_THREADS) * 64;
-                        const int64_t w0 = e0 + (int64_t)wave * per, w1 = w0 + per < e1 ? w0 + per : e1;
+                        const uint32_t per = ((e1 - e0 + FN_THREADS - 1) / FN_THREADS) * 64;
+                        const uint32_t w0 = e0 + wave * per, w1 = w0 + per < e1 ? w0 + per : e1;
                         // sixteen groups at a time, their loads issued together (a load per group in turn would cost a
-                        // memory latency per 64 elements); a lane past the end of the wave's run reads the run's last element
-                        auto equal_masks = [&](int64_t j0, uint64_t (&m)[16]) {
+                        // memory latency per 64 elements); a lane past the end of the wave's run reads the run's last element.  Positions have 32 bits:
+                        // with 64 the registers of this rare way spilled and slowed the whole kernel, 1024 rows of 1000 entries, fixed p, 171 us against 145
+                        // (adaptive 492 / 447), 256 of 300000 58 / 47.
+                        const uint32_t* g = (const uint32_t*)a.g + (int64_t)row * a.ld;
+                        auto equal_masks = [&](uint32_t j0, uint64_t (&m)[16]) {
                             uint32_t v[16];
 #pragma unroll
                             for (int u = 0; u < 16; ++u) {
-                                const int64_t j = j0 + u * 64 + lane;
-                                const int64_t jc = (int64_t)row * a.ld + (j < w1 ? j : w1 - 1);
-                                v[u] = ((const uint32_t*)a.g)[jc];
+                                const uint32_t j = j0 + u * 64 + lane;
+                                v[u] = g[j < w1 ? j : w1 - 1];
                             }
 #pragma unroll
                             for (int u = 0; u < 16; ++u) m[u] = __ballot(j0 + u * 64 + lane < w1 && key_of_bits(v[u]) == key1);
                         };
                         uint32_t mine = 0;
-                        for (int64_t j0 = w0; j0 < w1; j0 += 1024) {
+                        for (uint32_t j0 = w0; j0 < w1; j0 += 1024) {
                             uint64_t m[16];
                             equal_masks(j0, m);
 #pragma unroll
@@ -1613,7 +1615,7 @@ __global__ __launch_bounds__(FN_THREADS, PHASE == 0 ? 8 : 4) void k_finish(TopkA
                         if (total == cnt && rin >= 1u && rin <= cnt && before < target && target <= before + mine) {
                             uint32_t run = before;
                             bool found = false;
-                            for (int64_t j0 = w0; j0 < w1 && !found; j0 += 1024) {
+                            for (uint32_t j0 = w0; j0 < w1 && !found; j0 += 1024) {
                                 uint64_t m[16];
                                 equal_masks(j0, m);
 #pragma unroll
