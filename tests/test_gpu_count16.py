@@ -6,7 +6,7 @@ import torch
 
 import mlmc_workloads as W
 import paper_2507_05508_amd as P
-from gpu_util import check_topk_against_oracle, to_device, u32
+from gpu_util import check_topk_against_oracle, launched, to_device, u32
 from oracle import mlmc as O
 
 pytestmark = pytest.mark.gpu
@@ -77,6 +77,60 @@ def test_message_by_tile_lists(d):
                 assert np.array_equal(u32(msg.val[off[i]:off[i + 1]]), want["val"].view(np.uint32)), (i, step)
                 bounds = np.searchsorted(want["idx"], np.arange(plan.num_tiles + 1, dtype=np.int64) * P.MLMC_TILE)
                 assert np.array_equal(u32(msg.tile_off[i]), bounds.astype(np.uint32))
+
+
+def _check_rows(plan, msg, rows, picks, ladder, seed, step):
+    """Rows `picks` of the message against the oracle; `rows`: the kinds that take turns."""
+    torch.cuda.synchronize()
+    off, level = msg.row_off.cpu().numpy(), msg.level.cpu().numpy()
+    assert np.array_equal(np.diff(off), [ladder[0] + ladder[l] - ladder[l - 1] for l in level])
+    for i in picks:
+        want = O.compress_topk_row(rows[i % len(rows)], ladder, None, seed, step, i)
+        assert level[i] == want["level"]
+        assert np.array_equal(msg.norms[i].cpu().numpy().view(np.uint64), np.array(want["norms"]).view(np.uint64))
+        assert np.array_equal(u32(msg.idx[off[i]:off[i + 1]]), want["idx"]), (i, step)
+        assert np.array_equal(u32(msg.val[off[i]:off[i + 1]]), want["val"].view(np.uint32)), (i, step)
+        bounds = np.searchsorted(want["idx"], np.arange(plan.num_tiles + 1, dtype=np.int64) * P.MLMC_TILE)
+        assert np.array_equal(u32(msg.tile_off[i]), bounds.astype(np.uint32))
+
+
+@pytest.mark.parametrize("what", ["normal", "few", "one"])
+@pytest.mark.parametrize("M,d", [(1, 64 * 16384 + 1), (2, 128 * 16384 - 9), (1, 256 * 16384 - 9)])
+def test_more_than_64_slices(what, M, d):
+    """One or two rows in 65, 128 and 256 slices: the counts of eight groups of up to 32 slices are added up, with and without the counts
+    before every slice (a message, norms alone)."""
+    G = _rows(what, M, d, d + M)
+    g = to_device(G)
+    ladder = [d // 50, d // 3 + 2, d // 2 + 1, d - 1]
+    plan = P.Plan(P.MLMC_TOPK, M, d, P.MLMC_BF16, ladder, None)
+    plan.ws.fill_(0xFF)
+    norms = P.mlmc_level_norms(plan, g).cpu().numpy()
+    assert plan.status() == 0
+    for i in range(M):
+        assert np.array_equal(norms[i].view(np.uint64), np.array(O.level_norms_row(G[i], ladder)[0]).view(np.uint64))
+    plan.ws.fill_(0xFF)
+    for step in range(3):
+        print(f"many slices {what} {M}x{d} step={step}", flush=True)
+        msg = P.mlmc_compress_topk(plan, g, seed=4, step=step)
+        assert plan.status() == 0
+        _check_rows(plan, msg, G, range(M), ladder, 4, step)
+
+
+def test_ties_in_more_tiles_than_a_workgroup_takes():
+    """Rows of 1065 tiles, whose places two workgroups find: a threshold splits entries equal to it in the first one's tiles and in the second one's."""
+    M, d = 16, 16 * (1 << 18) + 40 * 4096 + 77
+    kinds = ["one", "few", "zeros"]
+    few = np.concatenate([_rows(k, 1, d, 3 + i) for i, k in enumerate(kinds[:2])] + [_rows("zeros", 2, d, 5)[:1]])
+    g = to_device(few).repeat(6, 1)[:M].contiguous()
+    for ladder in ([d // 50, d // 2, d - 50_000, d], [1, d - 100_001, d - 3]):
+        plan = P.Plan(P.MLMC_TOPK, M, d, P.MLMC_BF16, ladder, None)
+        plan.ws.fill_(0xFF)
+        assert "k_c16_mark" in launched(lambda: P.mlmc_compress_topk(plan, g, seed=8, step=0))
+        for step in range(2):
+            print(f"ties over workgroups {ladder} step={step}", flush=True)
+            msg = P.mlmc_compress_topk(plan, g, seed=8, step=step)
+            assert plan.status() == 0
+            _check_rows(plan, msg, few, [0, 1, 2, M - 1], ladder, 8, step)
 
 
 @pytest.mark.parametrize("M,d", [(3, 50_003), (256, 1 << 18)])

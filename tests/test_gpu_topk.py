@@ -10,9 +10,17 @@ from gpu_util import check_topk_against_oracle, launched, to_device, u32
 
 pytestmark = pytest.mark.gpu
 
+LONG = 1 << 16   # 32-bit rows of more entries (and of fewer than 8192) take the general way, those up to it a workgroup each
+
 
 def _plan_for(w, p_fixed):
     return P.Plan(P.MLMC_TOPK, w.M, w.d, P.MLMC_BF16 if w.dtype == "bf16" else P.MLMC_F32, w.ladder, p_fixed)
+
+
+def _takes(d, call):
+    """`call` compresses 32-bit rows of d entries: it launches the kernels of the way that rows of that length are to take."""
+    names = launched(call)
+    assert ("k_row_select" in names) == (8192 <= d <= LONG) and ("k_main" in names) != ("k_row_select" in names), (d, names)
 
 
 @pytest.mark.parametrize("d", [65536, 5 * 4096 + 123, 1000])
@@ -90,18 +98,24 @@ def test_adaptive_norms_and_compress(name, d, M):
 
 
 @pytest.mark.parametrize("shift", [1, 3, 6])
-@pytest.mark.parametrize("name,d,M", [("resnet50_adaptive_topk", 9 * 65536 + 999, 3), ("tiny_topk", 150_000, 2),
-                                       ("bert_adaptive_topk_bf16", 6 * 65536 + 4096 + 5, 2)])
-def test_sampled_threshold_search_gives_the_same_message(name, d, M, shift):
+@pytest.mark.parametrize("name,d,M,widened", [("resnet50_adaptive_topk", 9 * 65536 + 999, 3, False), ("tiny_topk", 150_000, 2, False),
+                                               ("bert_adaptive_topk_bf16", 6 * 65536 + 4096 + 5, 2, False),
+                                               ("bert_adaptive_topk_bf16", 6 * 65536 + 4096 + 5, 2, True)])
+def test_sampled_threshold_search_gives_the_same_message(name, d, M, widened, shift):
     """Thresholds located from a histogram of one block in 2^shift, proven by exact counts (or redone exactly when
-    the sample was too thin to bracket them): the message must not depend on the sampling."""
+    the sample was too thin to bracket them): the message must not depend on the sampling.  Rows of 16-bit entries are counted whole, so for them
+    the shift changes nothing; widened to 32 bits they are sampled like others, with the many equal keys of 16-bit values."""
     w = W.scaled(W.WORKLOADS[name], d=d, M=M)
     G = W.generate(w)
+    if widened:
+        G = (G.astype(np.uint32) << 16).view(np.float32)
+    sampled = G.dtype == np.float32
     g = to_device(G)
     redone = set()
     for pf in (None, O.geometric_p(w.L)):
-        plan = _plan_for(w, pf)
+        plan = P.Plan(P.MLMC_TOPK, M, d, P.MLMC_F32 if sampled else P.MLMC_BF16, w.ladder, pf)
         plan.set_sampling(shift)
+        assert ("k_main" in launched(lambda: P.mlmc_compress_topk(plan, g, seed=11, step=0))) == sampled
         if pf is None:
             print(f"{name} sampled shift={shift} norms d={d}", flush=True)
             norms = P.mlmc_level_norms(plan, g).cpu().numpy()
@@ -119,7 +133,7 @@ def test_sampled_threshold_search_gives_the_same_message(name, d, M, shift):
             torch.cuda.synchronize()
             assert np.array_equal(out.cpu().numpy().view(np.uint32), O.aggregate_sparse(want, w.d, 0.5).view(np.uint32))
     print(f"{name} shift={shift}: exact redo seen {sorted(redone)}", flush=True)
-    if shift <= 3:
+    if sampled and shift <= 3:
         assert redone == {False}    # an eighth of the blocks is plenty: the zones must hold
 
 
@@ -187,8 +201,8 @@ def test_staging_hook_decides_whatever_the_size(M, d, adaptive, default):
 
 @pytest.mark.parametrize("staging", [False, True])
 @pytest.mark.parametrize("shift", [0, 2])
-def test_adversarial_rows_ties_zeros_denormals(shift, staging):
-    d = 3 * 4096 + 517
+@pytest.mark.parametrize("d", [3 * 4096 + 517, LONG + 4096 + 517])
+def test_adversarial_rows_ties_zeros_denormals(d, shift, staging):
     rows = W.adversarial_rows(d)
     G = np.stack(rows)
     M = G.shape[0]
@@ -206,6 +220,7 @@ def test_adversarial_rows_ties_zeros_denormals(shift, staging):
     plan_f.set_sampling(shift)
     plan_a.set_staging(staging)
     plan_f.set_staging(staging)
+    _takes(d, lambda: P.mlmc_compress_topk(plan_a, g, seed=9, step=0))
     for step in range(10):
         print(f"adversarial step={step}", flush=True)
         msg = P.mlmc_compress_topk(plan_f, g, seed=9, step=step)
@@ -271,12 +286,14 @@ def test_one_key_holds_the_threshold_massive_ties(bf16):
 
 @pytest.mark.parametrize("staging", [False, True])
 @pytest.mark.parametrize("ld_pad", [1, 2, 3, 8])
-def test_padded_and_misaligned_rows(ld_pad, staging):
-    w = W.scaled(W.WORKLOADS["resnet18_topk"], d=2 * 4096 + 1001, M=3)
+@pytest.mark.parametrize("d", [2 * 4096 + 1001, LONG + 4096 + 1001])
+def test_padded_and_misaligned_rows(d, ld_pad, staging):
+    w = W.scaled(W.WORKLOADS["resnet18_topk"], d=d, M=3)
     G = W.generate(w)
     g = to_device(G, ld=w.d + ld_pad)
     plan = _plan_for(w, None)
     plan.set_staging(staging)
+    _takes(d, lambda: P.mlmc_compress_topk(plan, g, seed=5, step=0))
     for step in range(3):
         print(f"padded ld=d+{ld_pad} step={step}", flush=True)
         msg = P.mlmc_compress_topk(plan, g, seed=5, step=step)
@@ -326,11 +343,12 @@ def test_degenerate_shapes(d, ladder, staging):
             assert np.array_equal(out.cpu().numpy().view(np.uint32), O.aggregate_sparse(want, d, 0.5).view(np.uint32))
 
 
-def test_many_levels_many_rows():
+@pytest.mark.parametrize("d", [3 * 16384 + 811, LONG + 811])
+def test_many_levels_many_rows(d):
     """The limits of the plan: L = 32 levels (33 thresholds, most of them crowded into a few buckets) and more rows
     than any other test, sampled and exact threshold search, adaptive and fixed p."""
     rng = np.random.default_rng(7)
-    M, d, L = 37, 3 * 16384 + 811, 32
+    M, L = 37, 32
     G = (rng.standard_normal((M, d)) * np.exp(rng.uniform(-6, 2, size=(M, 1)))).astype(np.float32)
     ladder = [3] + [10 + 37 * l + (l * l * l) // 2 for l in range(1, L)] + [d]
     assert all(a < b for a, b in zip(ladder, ladder[1:]))
@@ -339,6 +357,7 @@ def test_many_levels_many_rows():
         for shift in (0, 2):
             plan = P.Plan(P.MLMC_TOPK, M, d, P.MLMC_F32, ladder, pf)
             plan.set_sampling(shift)
+            _takes(d, lambda: P.mlmc_compress_topk(plan, g, seed=5, step=0))
             for step in range(3):
                 print(f"L=32 M={M} adaptive={pf is None} shift={shift} step={step}", flush=True)
                 msg = P.mlmc_compress_topk(plan, g, seed=5, step=step)
@@ -349,18 +368,18 @@ def test_many_levels_many_rows():
                 assert np.array_equal(out.cpu().numpy().view(np.uint32), O.aggregate_sparse(want, d, 1.0 / M).view(np.uint32))
 
 
-@pytest.mark.parametrize("M", [70, 300])
-def test_more_rows_than_a_wave_or_a_workgroup(M):
+@pytest.mark.parametrize("M,d", [(70, 16384 + 77), (300, 16384 + 77), (70, LONG + 77), (300, 4096 + 77)])
+def test_more_rows_than_a_wave_or_a_workgroup(M, d):
     """Row counts beyond 64 and beyond 256: the per-row loops that lanes or threads share (message starts, the order in
     which the message kernels take the rows, the aggregate's row table) wrap around."""
     rng = np.random.default_rng(M)
-    d = 16384 + 77
     G = (rng.standard_normal((M, d)) * np.exp(rng.uniform(-3, 3, size=(M, 1)))).astype(np.float32)
     ladder = [5, 40, 300, 2000, d // 2, d]
     L = len(ladder) - 1
     g = to_device(G)
     for pf in (None, O.geometric_p(L)):
         plan = P.Plan(P.MLMC_TOPK, M, d, P.MLMC_F32, ladder, pf)
+        _takes(d, lambda: P.mlmc_compress_topk(plan, g, seed=11, step=0))
         for step in range(2):
             print(f"rows M={M} adaptive={pf is None} step={step}", flush=True)
             msg = P.mlmc_compress_topk(plan, g, seed=11, step=step)
@@ -434,11 +453,13 @@ def test_identity_ladder_is_dense_mean():
     assert np.array_equal(out, acc * np.float32(0.25))
 
 
-def test_capacity_and_nonfinite_flags():
-    w = W.scaled(W.WORKLOADS["resnet18_topk"], d=20_000, M=2)
+@pytest.mark.parametrize("d", [20_000, LONG + 4464])
+def test_capacity_and_nonfinite_flags(d):
+    w = W.scaled(W.WORKLOADS["resnet18_topk"], d=d, M=2)
     G = W.generate(w)
     plan = _plan_for(w, O.geometric_p(w.L))
     g = to_device(G)
+    _takes(d, lambda: P.mlmc_compress_topk(plan, g, seed=0, step=0))
     small = P.SparseMessage(plan, capacity=10)
     guard = torch.full_like(small.idx, -1)
     P.mlmc_compress_topk(plan, g, seed=0, step=0, out=small)
@@ -464,10 +485,11 @@ def test_capacity_and_nonfinite_flags():
 
 
 @pytest.mark.parametrize("what", ["zeros", "few", "normal"])
-@pytest.mark.parametrize("d,dtype", [((1 << 17) + 0, P.MLMC_F32), ((1 << 17) + 1, P.MLMC_BF16), (40_000, P.MLMC_BF16)])
+@pytest.mark.parametrize("d,dtype", [((1 << 17) + 0, P.MLMC_F32), ((1 << 17) + 1, P.MLMC_F32), (LONG + 1, P.MLMC_F32), ((1 << 17) + 1, P.MLMC_BF16),
+                                      (40_000, P.MLMC_BF16)])
 def test_zones_resolved_by_one_workgroup(what, d, dtype):
     """Rows with exact histograms: zones that the ranking launch resolves alone (all of them up to 2^17 entries, those of up to 16384
-    candidates in longer rows) and zones that take the sliced passes, with one key or several at a threshold."""
+    candidates in longer rows) and zones that take the sliced passes, with one key or several at a threshold.  (Rows of 16-bit entries have no zones.)"""
     rng = np.random.default_rng(d)
     G = rng.standard_normal((3, d)).astype(np.float32)
     if what == "zeros":
