@@ -69,7 +69,7 @@ _TRACE_NAME = {"k_main2": "k_main", "k_rtn_extract": "k_bits_extract", "k_sb_cle
                "k_se_coarse": "k_hist", "k_se_map": "k_scan", "k_se_reduce": "k_se_scan", "k_se_norms": "k_sb_norms",
                "k_se_wide": "k_se_zone", "k_se_mark": "k_sb_mark", "k_se_offsets": "k_sb_offsets", "k_se_write": "k_sb_write",
                "k_rtn_prep": "k_bits_prep", "k_rtn_hist": "k_rtn_norms", "k_rtn_hmax": "k_rtn_norms", "k_rtn_hsum": "k_rtn_norms",
-               "k_c16_reduce": "k_c16_scan", "k_c16_offsets": "k_c16_scan", "k_c16_expand": "k_c16_write"}
+               "k_c16_expand": "k_c16_write"}
 
 
 def measured_traffic(workload, kernel):

@@ -136,7 +136,8 @@ mlmc_status mlmc_plan_set_staging(mlmc_plan_t *plan, int enable);
 mlmc_status mlmc_plan_set_overlap(mlmc_plan_t *plan, int enable);
 
 /* MLMC_TOPK plans: elements of a row that one workgroup of the selection read takes (a multiple of MLMC_TILE, at most
- * 2^18); 0 for other plans.  For tests and tuning: results never depend on it. */
+ * 2^18); 0 for other plans.  Plans without such a read (MLMC_BF16 rows, MLMC_F32 rows of 8192 to 65536 entries) return the number that it
+ * would have.  For tests and tuning: results never depend on it. */
 int64_t mlmc_plan_chunk(const mlmc_plan_t *plan);
 /* Tiles per row of the offset table: ceil(d / MLMC_TILE). */
 int64_t mlmc_plan_num_tiles(const mlmc_plan_t *plan);

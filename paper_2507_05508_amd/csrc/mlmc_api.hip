@@ -55,7 +55,7 @@ static const char* const k_names[K_NUM] = {
     "k_zero", "k_hist", "k_scan", "k_main", "k_fhist", "k_finish", "k_finish_rank", "redo_pass", "k_norms", "k_bits_prep", "k_msgplan", "k_filter", "k_write",
     "k_bits_smax", "k_bits_extract", "k_bits_redo", "k_agg_bits", "k_tileoff", "k_agg_sparse", "k_message_bits", "k_rtn_norms", "k_rtn_draw",
     "k_rs_hist", "k_rs_scan", "k_rs_scatter", "k_sb_norms", "k_sb_draw", "k_sb_mark", "k_sb_offsets", "k_sb_write", "k_se_count", "k_se_scan",
-    "k_se_split", "k_se_zone", "k_row_select", "k_row_write", "k_c16_hist", "k_c16_scan", "k_c16_mark", "k_c16_write"};
+    "k_se_split", "k_se_zone", "k_row_select", "k_row_write", "k_c16_hist", "k_c16_reduce", "k_c16_scan", "k_c16_mark", "k_c16_offsets", "k_c16_write"};
 struct ProfPair { int id; hipEvent_t e0, e1; };
 static std::vector<ProfPair> g_pending;
 static std::vector<ProfPair> g_free;
@@ -120,8 +120,9 @@ static void fill_topk_args(const mlmc_plan_t* pl, TopkArgs& a, const void* g, in
     a.sample_shift = pl->sample_shift;
     // Short rows are bound by the number of launches (5 to 6 us each), so what a launch saves there is less than it costs: a
     // zone of an exact histogram is one bucket, a few hundred candidates that one workgroup ranks without the two sliced
-    // passes: 4 rows of 65536, 81 -> 62 us.  Longer rows keep the sliced passes for zones with many equal keys (one workgroup would take 0.24 ms
-    // for a row of 2.6e5 that is mostly zeros, as long as the passes).
+    // passes.  compress, us, with the passes / alone: 4 rows of 4096, fixed p 50 / 47, adaptive 68 / 62; 4 of 100000 60 / 56, 86 / 80; 32 of 100000 78 / 71, 127 / 118.
+    // Longer rows keep the sliced passes for zones with many equal keys: adaptive rows with six in ten zero, 1 of 100000 161 / 161, 1 of 131072 162 / 171,
+    // 1 of 200000 190 / 218, 4 of 200000 227 / 241.
     a.alone = pl->sample_shift == 0 && pl->d <= ((int64_t)1 << 17) ? 1 : 0;
     a.staging = pl->staging;
     {
@@ -485,9 +486,10 @@ mlmc_status mlmc_plan(mlmc_plan_t** plan, int kind, int M, int64_t d, int in_dty
     // rows long enough that a second full read matters get their thresholds from a sampled histogram
     pl->sample_shift = d >= ((int64_t)1 << 23) ? 4 : d >= ((int64_t)1 << 21) ? 2 : 0;
     if (kind == MLMC_VBITS || kind == MLMC_RTN) pl->sample_shift = 0;   // the largest entry itself is needed, not its binade
-    // Small adaptive plans of several rows take the second read instead of the kernel that assembles staged lists: 4 rows of 65536 90.5 us
-    // against 96.4, 16 of 30000 99.6 / 105.9.  One or two rows leave the second read too few workgroups (2 of 200000 112.9 / 110.7, or 146.3 /
-    // 125.0 where keys repeat), and with fixed p it gains nothing (4 of 65536 67.6 / 68.0, 76.3 / 70.7 where keys repeat).
+    // Small adaptive plans of several rows take the second read instead of the kernel that assembles staged lists (fp32 rows of 8192 to 65536 entries and
+    // 16-bit rows have neither).  compress, us, second read / staged: 16 of 4096 65 / 69 (78 / 84 where keys repeat), 64 of 8000 108 / 115, 4 of 100000 80 / 79 (129 / 141).
+    // One or two rows leave the second read too few workgroups (1 of 100000 78 / 76, 125 / 119; 2 of 200000 91 / 87, 176 / 180), and with fixed p it loses
+    // where keys repeat (4 of 100000 59 / 56, 96 / 81).
     pl->staging = p_fixed == nullptr && M >= 4 && (int64_t)M * d <= ((int64_t)1 << 19) ? 0 : 1;
     // The fork and the join cost some twenty microseconds of stream operations, paid in every call, while the second read
     // has work in a call only when some row's band was not staged: worth it for many long rows (measured: -11 us per call
@@ -497,8 +499,8 @@ mlmc_status mlmc_plan(mlmc_plan_t** plan, int kind, int M, int64_t d, int in_dty
     size_t off = 0;
     pl->off_racc = off;
     off = align_up(off + sizeof(RowAcc) * (size_t)M, 256);
-    // 16-bit rows have few enough magnitudes to count them all, at any size: compress, adaptive, us, against the way of the 32-bit rows, 1 row of 16384
-    // 73 -> 35, 32 of 16385 114 -> 56, 4 of 2500000 192 -> 68, 1024 of 16384 959 -> 277, 4 of 30000001 358 -> 193; rows of one value, 4 of 2500000, 22828 -> 99.
+    // 16-bit rows have few enough magnitudes to count them all, at any size: compress, adaptive, us, against the way of the 32-bit rows, 4 rows of 1000
+    // 68 -> 31, 1 of 16384 74 -> 33, 129 of 65536 210 -> 72, 255 of 300001 513 -> 173, 1024 of 32768 1032 -> 213; nine in ten zero, 129 of 65536, 790 -> 70.
     const bool counted = kind == MLMC_TOPK && in_dtype == MLMC_BF16;
     if (kind == MLMC_TOPK && !counted) {
         pl->off_hist = off;
@@ -535,15 +537,18 @@ mlmc_status mlmc_plan(mlmc_plan_t** plan, int kind, int M, int64_t d, int in_dty
             off = align_up(off + sizeof(uint32_t) * 32768 * (size_t)M, 256);
         }
     }
-    // 32-bit rows of up to 65536 entries fit the registers of one workgroup.  (Rows of less than two tiles keep the general way, whose staging hook can
-    // be seen in what they launch; the workspace stays that of the general way, which callers may have sized pools for.)
+    // 32-bit rows of up to 65536 entries fit the registers of one workgroup.  The lower line is not one of speed: for rows of less than two tiles the staging hook is
+    // kept, which decides what a call launches.  A workgroup per row would be the faster way there too: compress, us, general way / a workgroup per row,
+    // 4 rows of 1000, fixed p 46 / 16, adaptive 61 / 23; 4 of 4096 47 / 16, 62 / 25; 64 of 8191 69 / 18, 110 / 28; 1024 of 4096 401 / 71, 865 / 107.
+    // The workspace is that of the general way and 1 KB a row, though the two kernels touch a few MB of it at most: plans of this size were that large before.
     pl->row_mode = kind == MLMC_TOPK && in_dtype == MLMC_F32 && d >= ROW_MIN && d <= ROW_MAX ? 1 : 0;
     if (pl->row_mode) {
         pl->off_row_part = off;
         off = align_up(off + sizeof(uint4) * 64 * (size_t)M, 256);
     }
     if (counted) {
-        int64_t wgs = 256 / M > 0 ? 256 / M : 1;   // one workgroup per CU in one round
+        // At most one workgroup per CU and whole slices for every row: 129 to 255 rows have one each and leave up to half the CUs idle, 257 need a second round.
+        int64_t wgs = 256 / M > 0 ? 256 / M : 1;
         if (wgs > (d + 16383) / 16384) wgs = (d + 16383) / 16384;
         pl->c16_slice = ((d + wgs - 1) / wgs + TILE - 1) / TILE * TILE;
         pl->c16_wgs = (int)((d + pl->c16_slice - 1) / pl->c16_slice);

@@ -8,7 +8,7 @@
 //   k_c16_mark, k_c16_offsets, k_c16_expand   long slices: the second read leaves the tiles' entries in lists, which become the message
 //
 // Against the way of the 32-bit rows (sampled histogram, selection read with candidate lists, ranking, message from staged lists), which these
-// rows took before, adaptive, compress + aggregate: 4 rows of 1.24e8 entries 777 -> 512 us, 32 of 1e6 289 -> 135.
+// rows took before, adaptive, compress + aggregate: 4 rows of 1.24e8 entries 817 -> 534 us, 32 of 1e6 271 -> 106.
 #include "mlmc_count16.h"
 
 namespace mlmc {
@@ -794,8 +794,8 @@ mlmc_status topk16_run(const mlmc_plan_t* pl, const TopkArgs& a, bool message, h
     const dim3 rgrid(C16_KEYS / C16_BLOCK, pl->M);
 #define MLMC_C16_REDUCE(G, PER)                                                                                          \
     do {                                                                                                                \
-        if (message && !a.c16_list) MLMC_LAUNCH(K_C16_SCAN, st, k_c16_reduce<G, PER, true><<<rgrid, C16_BLOCK * G, 0, st>>>(a)); \
-        else MLMC_LAUNCH(K_C16_SCAN, st, k_c16_reduce<G, PER, false><<<rgrid, C16_BLOCK * G, 0, st>>>(a));                \
+        if (message && !a.c16_list) MLMC_LAUNCH(K_C16_REDUCE, st, k_c16_reduce<G, PER, true><<<rgrid, C16_BLOCK * G, 0, st>>>(a)); \
+        else MLMC_LAUNCH(K_C16_REDUCE, st, k_c16_reduce<G, PER, false><<<rgrid, C16_BLOCK * G, 0, st>>>(a));              \
     } while (0)
     if (pl->c16_wgs > 64) MLMC_C16_REDUCE(8, 32);
     else if (pl->c16_wgs > 8) MLMC_C16_REDUCE(2, 32);
@@ -810,7 +810,7 @@ mlmc_status topk16_run(const mlmc_plan_t* pl, const TopkArgs& a, bool message, h
         const dim3 mgrid((unsigned)(mw < cap ? mw : cap), pl->M), egrid((unsigned)(mw < 4 * cap ? mw : 4 * cap), pl->M);
         MLMC_LAUNCH(K_C16_MARK, st, k_c16_mark<<<mgrid, MK_THREADS, 0, st>>>(a));
         const int64_t span = (pl->ntiles + 65535) / 65536 * 1024;   // at most 64 workgroups a row: what they add up in front of their tiles stays small
-        MLMC_LAUNCH(K_C16_SCAN, st, k_c16_offsets<<<dim3((unsigned)((pl->ntiles + span - 1) / span), pl->M), 1024, 0, st>>>(a, span));
+        MLMC_LAUNCH(K_C16_OFFSETS, st, k_c16_offsets<<<dim3((unsigned)((pl->ntiles + span - 1) / span), pl->M), 1024, 0, st>>>(a, span));
         MLMC_LAUNCH(K_C16_WRITE, st, k_c16_expand<<<egrid, 256, 0, st>>>(a));
     } else {
         MLMC_LAUNCH(K_C16_WRITE, st, k_c16_write<<<grid, C16_THREADS, 0, st>>>(a));
