@@ -6,12 +6,12 @@
 //
 // Such rows are bound by launches and latency: nine to twelve launches of 5 to 15 us in the way of the longer rows (sampled histogram, selection
 // read, ranking, message, each over several workgroups a row and with its own tables in memory to clear), two here.  The selection of a row of
-// 65536 takes 22 us with fixed p (load 4, first digit 6, table 1, candidates listed 6, the other digits 2, places 4) and 40 with adaptive p (sums of squares 9,
-// norms and draw 4 more); the message 6.  compress, us, before / now: 4 rows of 65536, fixed p 57 / 29, adaptive 80 / 49; 1 of 16384 53 / 20, 73 / 31;
+// 65536 takes 22 us with fixed p (load 4, first digit 5, table 1, candidates listed 6, the other digits 2, places 4) and 39 with adaptive p (sums of squares 8,
+// norms and draw 4 more); the message 6.  compress, us, the longer rows' way / this one: 4 rows of 65536, fixed p 54 / 28, adaptive 76 / 45; 1 of 16384 53 / 20, 73 / 31;
 // 64 of 32768 74 / 26, 130 / 40.  What rows of few or close values cost is LDS atomics of many lanes on one word, so zeros are in no list and in no
 // atomic, and where a row's candidates do not fit the list its counts are kept in copies.  4 rows of 65536, fixed p and adaptive, us, the longer rows' way / this
-// one before / now: three in ten zero 61 / 57 / 28, 84 / 146 / 47; nine in ten 120 / 61 / 28, 550 / 130 / 46; quarters of a normal 77 / 62 / 59, 113 / 135 / 110; all
-// within 4e-4 of one 96 / 107 / 70, 128 / 241 / 109; 30 % of one value 220 / 108 / 84, 290 / 160 / 113.
+// one before / now: three in ten zero 61 / 57 / 27, 83 / 146 / 46; nine in ten 120 / 61 / 27, 550 / 130 / 44; quarters of a normal 77 / 62 / 58, 113 / 135 / 108; all
+// within 4e-4 of one 96 / 107 / 66, 128 / 241 / 105; 30 % of one value 220 / 109 / 82, 290 / 160 / 109.
 #include <type_traits>
 
 #include "mlmc_device.h"
@@ -161,26 +161,23 @@ __global__ __launch_bounds__(RW_THREADS) void k_row_select(TopkArgs a) {
     bool crowded = false;   // uniform
     if (r.n > 0) {
         const uint32_t k0 = key_of_bits(r.b[0][0]);
-        const uint64_t there = __ballot(k0 != 0u && r.valid(0, lane) > 0);
+        const uint64_t there = __ballot(k0 != 0u);
         if (there) {
             const uint32_t b0 = (uint32_t)__builtin_amdgcn_readlane((int)(k0 >> B1_SHIFT), (int)__builtin_ctzll(there));
             crowded = __popcll(__ballot(k0 >> B1_SHIFT == b0) & there) >= 24;
         }
     }
-    auto every = [&](auto f) {   // f(key, whether to count it), all lanes
+    auto every = [&](auto f) {   // f(key), all lanes; zero past the row's end
 #pragma unroll
         for (int q = 0; q < RW_PIECES; ++q) {
             if (q >= r.n) continue;
-            const int nv = r.valid(q, lane);
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const uint32_t key = key_of_bits(r.b[q][c]);
-                f(key, c < nv && key != 0u);
-            }
+            for (int c = 0; c < 4; ++c) f(key_of_bits(r.b[q][c]));
         }
     };
-    if (crowded) every([&](uint32_t key, bool on) { count_peeled<3>(s_a, key >> B1_SHIFT, on); });
-    else every([&](uint32_t key, bool on) { if (on) atomicAdd(&s_a[key >> B1_SHIFT], 1u); });
+    static_assert(TMAX * RW_D2 >= NB1 + 64, "a word per lane that nobody reads");
+    if (__builtin_expect(crowded, 0)) every([&](uint32_t key) { count_peeled<3>(s_a, key >> B1_SHIFT, key != 0u); });
+    else every([&](uint32_t key) { atomicAdd(&s_a[key ? key >> B1_SHIFT : (uint32_t)NB1 + lane], 1u); });
     __syncthreads();
     const int na = s_na;
     // ---- first digit: thread t holds 16 buckets, descending with the thread ----
@@ -271,18 +268,17 @@ __global__ __launch_bounds__(RW_THREADS) void k_row_select(TopkArgs a) {
     // ---- second digit, of the entries that share a threshold's first one: a few per cent of the row, listed for what follows as long as there is room ----
     uint32_t* list = s_a + ns * RW_D2;
     const uint32_t room = (uint32_t)(TMAX * RW_D2 - ns * RW_D2);
-    auto fours = [&](auto with_zeros, auto f) {   // f(codes, keys, whether there is one (with_zeros: one other than zero), which piece), all lanes
+    auto fours = [&](auto with_zeros, auto f) {   // f(codes, keys, with_zeros: whether it is another than zero, which piece), all lanes; zero past the row's end
 #pragma unroll
         for (int q = 0; q < RW_PIECES; ++q) {
             if (q >= r.n) continue;
-            const int nv = r.valid(q, lane);
             uint32_t code[4], key[4];
             bool on[4];
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
                 key[c] = key_of_bits(r.b[q][c]);
                 code[c] = s_tab[key[c] >> B1_SHIFT];
-                on[c] = c < nv && (!decltype(with_zeros)::value || key[c] != 0u);
+                on[c] = !decltype(with_zeros)::value || key[c] != 0u;
             }
             f(code, key, on, q);
         }
@@ -295,7 +291,7 @@ __global__ __launch_bounds__(RW_THREADS) void k_row_select(TopkArgs a) {
 #pragma unroll
             for (int c = 0; c < 4; ++c) mine |= (uint64_t)(on[c] && (code[c] & 0x80u)) << (4 * q + c);
         };
-        if (zero_slot >= 0) fours(yes{}, mark);   // uniform
+        if (__builtin_expect(zero_slot >= 0, 0)) fours(yes{}, mark);   // uniform
         else fours(no{}, mark);
         const uint32_t c = (uint32_t)__popcll(mine), inc = wave_incl_scan(c);
         uint32_t at = 0;
@@ -327,10 +323,10 @@ __global__ __launch_bounds__(RW_THREADS) void k_row_select(TopkArgs a) {
         for (int c = 0; c < 4; ++c) w[c] = s_a[code[c] & 0x80u ? (code[c] & 0x7Fu) * RW_D2 + ((key[c] >> 8) & (RW_D2 - 1u)) : 0u];
     };
     // Where they do not fit (many equal keys, or close ones) the row is gone through again, and the list's place holds copies of the counts
-    if (listed) {
+    if (__builtin_expect(listed, 1)) {
         candidates([&](uint32_t slot, uint32_t key, bool on) {
             const uint32_t at = on ? slot * RW_D2 + ((key >> 8) & (RW_D2 - 1u)) : 0u;
-            if (clumped) count_peeled<1>(s_a, at, on);
+            if (__builtin_expect(clumped, 0)) count_peeled<1>(s_a, at, on);
             else if (on) atomicAdd(&s_a[at], 1u);
         });
         if (tid == 0 && zero_slot >= 0) atomicAdd(&s_a[zero_slot * RW_D2], s_zeros);
@@ -369,13 +365,13 @@ __global__ __launch_bounds__(RW_THREADS) void k_row_select(TopkArgs a) {
     // ---- third digit ----
     const uint32_t zero_sub = zero_slot >= 0 ? s_a[zero_slot * RW_D2] : 0u;
     const int zero_at = zero_sub >> 31 ? (int)(zero_sub & 63u) * RW_D3 : -1;
-    if (listed) {
+    if (__builtin_expect(listed, 1)) {
         if (tid == 0 && zero_at >= 0) atomicAdd(&s_b[zero_at], s_zeros);
         candidates([&](uint32_t slot, uint32_t key, bool on) {
             const uint32_t w = s_a[on ? slot * RW_D2 + ((key >> 8) & (RW_D2 - 1u)) : 0u];
             const bool want = on && (w >> 31);
             const uint32_t at = (w & 63u) * RW_D3 + (key & (RW_D3 - 1u));
-            if (clumped) count_peeled<1>(s_b, at, want);
+            if (__builtin_expect(clumped, 0)) count_peeled<1>(s_b, at, want);
             else if (want) atomicAdd(&s_b[at], 1u);
         });
     } else {
@@ -488,14 +484,14 @@ __global__ __launch_bounds__(RW_THREADS) void k_row_select(TopkArgs a) {
     auto add_square = [&](uint32_t band, uint32_t key) {
         atomicAdd(&s_sum[(255u - (key >> 23) + band) * REP_SUM + (lane & (REP_SUM - 1u))], (unsigned long long)sig_square(key));
     };
-    if (listed) {
+    if (__builtin_expect(listed, 1)) {
         auto others = [&](const uint32_t (&code)[4], const uint32_t (&key)[4], const bool (&on)[4], int) {
 #pragma unroll
             for (int c = 0; c < 4; ++c)
                 if (on[c] && !(code[c] & 0x80u)) add_square(code[c], key[c]);
         };
-        if (s_zeros) fours(yes{}, others);   // uniform
-        else fours(no{}, others);
+        if (__builtin_expect(s_zeros != 0u, 0)) fours(yes{}, others);   // uniform
+        else fours(no{}, others);                                       // (what is past the end adds nothing)
         candidates([&](uint32_t slot, uint32_t key, bool on) {
             int u = s_first[on ? slot : 0u];
             const int u1 = s_first[on ? slot + 1u : 0u];
