@@ -481,7 +481,8 @@ __global__ __launch_bounds__(256) void k_tileoff(AggSparseArgs a) {
 // where the tiles leave the CUs room a tile gets more threads, as far as a row has entries for them (agg_threads).  32 rows, 512 entries of each in a
 // tile, us with 256 / 512 / 1024 threads: 245 tiles 34.1 / 21.6 / 13.8, 489 38.3 / 26.2 / 18.6, 977 44.3 / 32.8 / 34.9; 1024 entries 40.3 / 38.6 / 23.6, 41.5 / 42.9 / 30.7,
 // 49.7 / 54.7 / 55.0; 16 rows, some 500 entries, 1954 tiles 28.5 / 32.3 / 43.2.  Of 32 entries or 128 a row's step is its barrier, which more waves make
-// longer: 32 rows, 245 tiles 13.2 / 12.4 / 12.9, 977 14.9 / 16.7 / 29.1; 256 rows, 1 tile 73.5 / 72.9 / 76.8, 245 79.4 / 79.4 / 80.2, 489 83.8 / 84.7 / 102.8.
+// longer: 256 rows, 1 tile 73.5 / 72.9 / 76.8, 245 79.4 / 79.4 / 80.2, 489 83.8 / 84.7 / 102.8; 32 rows, 245 tiles 13.2 / 12.4 / 12.9, 977 14.9 / 16.7 / 29.1; with 4 rows
+// there is nothing to lose (977 tiles 7.8 / 7.5 / 10.2), and what is drawn may be far longer than the mean (2048 entries 15.8 / 13.9 / 18.9).
 template <int NT>
 __global__ __launch_bounds__(NT) void k_agg_sparse(AggSparseArgs a) {
     // dynamic LDS, sized by the number of rows (M * 12 bytes), so that a CU holds as many workgroups as its wave
@@ -687,8 +688,11 @@ static int agg_threads(const mlmc_plan_t* pl) {
         mean = (double)pl->ladder[0];
         for (int l = 1; l <= pl->L; ++l) mean += (pl->adaptive ? 1.0 / pl->L : pl->p[l - 1]) * (double)(pl->ladder[l] - pl->ladder[l - 1]);
     }
-    if (mean < 192.0 * (double)pl->ntiles) return pl->ntiles <= 512 ? 512 : 256;
-    return pl->ntiles <= 256 ? 1024 : pl->ntiles <= 1024 ? 512 : 256;
+    const bool short_rows = mean < 192.0 * (double)pl->ntiles;
+    if (pl->ntiles <= 256) return short_rows && pl->M > 32 ? 512 : 1024;
+    if (pl->ntiles <= 512) return 512;
+    if (pl->ntiles <= 1024) return short_rows && pl->M >= 16 ? 256 : 512;
+    return 256;
 }
 
 mlmc_status agg_sparse(const mlmc_plan_t* pl, const int64_t* row_off, const uint32_t* idx, const float* val, int64_t capacity,

@@ -77,11 +77,12 @@ def test_update_argument_checks():
 
 
 @pytest.mark.parametrize("top", [1, 30])
-@pytest.mark.parametrize("tiles", [1, 255, 256, 257, 512, 513, 1023, 1024, 1025])
-def test_aggregate_by_number_of_tiles(tiles, top):
-    """The threads that share a tile depend on how many tiles there are and on how long the messages are; rows of a few entries, of some hundreds and
+@pytest.mark.parametrize("tiles,M", [(1, 9), (255, 9), (256, 9), (257, 9), (1023, 9), (1024, 9), (1025, 9), (1, 32), (1, 33), (3, 33), (512, 16), (513, 16),
+                                     (1024, 16)])
+def test_aggregate_by_number_of_tiles(tiles, M, top):
+    """The threads that share a tile depend on how many tiles and rows there are and on how long the messages are; rows of a few entries, of some hundreds and
     (top = 1) of nearly all entries of a tile, more rows than one group holds."""
-    M, d = 9, tiles * 4096 - 5
+    d = tiles * 4096 - 5
     L = 3
     rng = np.random.default_rng(tiles)
     G = rng.standard_normal((M, d), dtype=np.float32)
