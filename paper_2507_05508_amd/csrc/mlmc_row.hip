@@ -409,12 +409,13 @@ __global__ __launch_bounds__(RW_THREADS) void k_row_select(TopkArgs a) {
     if (tid == 0) ri->status = s_status;
     // ---- where the message of every stretch of four pieces begins: members by key, entries equal to a threshold that splits its equals ----
     auto places = [&](int lev) {
-        uint32_t lo[3], tau[3], inside[3];
+        uint32_t lo[3], tau[3], inside[3], nnz = 0;
         bool split[3];
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
             const int t = i == 0 ? 0 : lev - 2 + i;
-            int u = a.all_thresholds ? t : i == 0 ? 0 : lev == 1 ? i - 1 : i;   // where threshold t stands among those needed
+            const int u = a.all_thresholds ? t : i == 0 ? 0 : lev == 1 ? i - 1 : i;   // where threshold t stands among those needed
+            nnz += i == 1 ? 0u - s_need[u] : s_need[u];
             tau[i] = s_tau[u];
             inside[i] = s_rank[u];
             split[i] = s_rank[u] < s_bin[u];
@@ -464,12 +465,15 @@ __global__ __launch_bounds__(RW_THREADS) void k_row_select(TopkArgs a) {
             at.y = wave_incl_scan(c.y) - c.y;
             at.z = wave_incl_scan(c.z) - c.z;
             at.w = wave_incl_scan(c.w) - c.w;
-            const uint32_t e[3] = {at.y, at.z, at.w};
+            const uint32_t e[3] = {at.y, at.z, at.w}, here[3] = {c.y, c.z, c.w};
+            uint32_t end = at.x + c.x;
 #pragma unroll
             for (int i = 0; i < 3; ++i) {   // |in0| + |in2| - |in1|: the sets are nested
-                const uint32_t f = !split[i] ? 0u : e[i] < inside[i] ? e[i] : inside[i];
+                const uint32_t f = !split[i] ? 0u : e[i] < inside[i] ? e[i] : inside[i], g = e[i] + here[i], h = !split[i] ? 0u : g < inside[i] ? g : inside[i];
                 at.x += i == 1 ? 0u - f : f;
+                end += i == 1 ? 0u - h : h;
             }
+            if (lane == 63 && end != nnz) ri->status = s_status | (uint32_t)MLMC_DEV_INTERNAL;   // an entry too few or too many was counted
             a.row_part[(size_t)row * 64 + lane] = at;
         }
     };
