@@ -280,6 +280,13 @@ __device__ __forceinline__ void transpose8(uint32_t (&r)[8]) {
     for (int i = 0; i < 8; ++i) if (!(i & 1)) swap_bits(i, i + 1, 1, 0x55555555u);
 }
 
+// Which of a row's workgroups this one is.  Workgroups are dealt to the eight XCDs in turn; where their number is a multiple of eight, those of one XCD
+// take consecutive blocks here, so that the lines in which the words of neighbouring blocks meet (planes start at any word) are whole in one L2
+// before they leave it.
+__device__ __forceinline__ uint32_t extract_place() {
+    return (gridDim.x & 7u) == 0u ? (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3) : blockIdx.x;
+}
+
 // Writes this lane's half words of a block, plane after plane in ascending order.  The position of the next plane is one running
 // pointer for the wave (hidden from the compiler, which would otherwise keep thirty plane offsets in scalar registers
 // across the loop and spill them), the lane's offset one register.
@@ -405,7 +412,7 @@ __global__ __launch_bounds__(EX_THREADS, 4) void k_bits_extract(BitsArgs a) {
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t nblk = (a.d + EX_ELEMS - 1) / EX_ELEMS, nwhole = a.d / EX_ELEMS;
     const int64_t stride = (int64_t)gridDim.x * (EX_THREADS / 64);
-    int64_t blk = (int64_t)blockIdx.x * (EX_THREADS / 64) + wave;
+    const int64_t blk = (int64_t)extract_place() * (EX_THREADS / 64) + wave;
     const Loader ld(a.g, a.ld, a.d, row);
     const uint32_t smpmax = KIND == 1 ? 0u : row_smpmax(a, row);
     const uint32_t Es = smpmax >> 23;
@@ -477,18 +484,20 @@ __global__ __launch_bounds__(EX_THREADS, 4) void k_bits_extract(BitsArgs a) {
     }
 }
 
-// Workgroups of an extraction: a wave takes about three blocks (its loads run ahead across them), one when there are few.
-// The kinds with a row maximum begin every workgroup with a reduction over the maxima of its row, so they get half as many:
-// 2048 against 4096 workgroups at 8 rows of 1.17e7 fp32 elements: 78.6 / 81 us (fixed point), 86.8 / 90.7 us (largest entry), but
-// 91.4 / 86.4 us for the floating-point and 117 / 115 us for the Round-to-Nearest ladder; one block per wave: 227, 239, 111, 129 us.
+// Workgroups of an extraction.  Every wave of a row takes the same number of blocks, give or take the last (the loads run ahead from block to block): three,
+// or one where that leaves fewer than four workgroups per CU.  The kinds with a row maximum begin every workgroup with a reduction over the maxima of
+// its row, so they get about 2048 workgroups in all however long the rows are.  A multiple of eight per row: extract_place.
+// us, grids without that and with at most 2048 or 4096 workgroups in all / now: 4 rows of 1.24e8 bf16 entries, Round-to-Nearest, 327 / 300 and the
+// aggregate after it 267 / 249; 8 rows of 1.17e7 fp32, Round-to-Nearest 77 / 73, floating point 84.8 / 83.1, fixed point 76.7 / 74.4, largest entry 81.1 / 78.1;
+// the last two with three blocks a wave 76.9 and 82.2, 3 rows of 1.24e8 bf16 entries, fixed point, 176 as against 152.
 inline dim3 extract_grid(const mlmc_plan_t* pl) {
     const int64_t wgs = ((pl->d + EX_ELEMS - 1) / EX_ELEMS + EX_THREADS / 64 - 1) / (EX_THREADS / 64);
-    int64_t gx = (wgs + 2) / 3;
+    int64_t per = 3;
+    if ((pl->kind == MLMC_BITS || pl->kind == MLMC_VBITS) && wgs * pl->M > per * 2048) per = (wgs * pl->M + 2047) / 2048;
+    int64_t gx = (wgs + per - 1) / per;
     if (gx * pl->M < 1024) gx = wgs;
-    const int64_t total = pl->kind == MLMC_BITS || pl->kind == MLMC_VBITS ? 2048 : 4096;
-    const int64_t cap = total / pl->M > 0 ? total / pl->M : 1;
-    if (gx > cap) gx = cap;
-    return dim3((unsigned)(gx < 1 ? 1 : gx), pl->M);
+    if (gx >= 64) gx = (gx + 7) / 8 * 8;
+    return dim3((unsigned)gx, pl->M);
 }
 
 }  // namespace mlmc

@@ -329,7 +329,7 @@ __global__ __launch_bounds__(EX_THREADS, 4) void k_rtn_extract(BitsArgs a) {
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = lane_id();
     const int64_t nblk = (a.d + EX_ELEMS - 1) / EX_ELEMS, nwhole = a.d / EX_ELEMS;
     const int64_t stride = (int64_t)gridDim.x * (EX_THREADS / 64);
-    int64_t blk = (int64_t)blockIdx.x * (EX_THREADS / 64) + wave;
+    const int64_t blk = (int64_t)extract_place() * (EX_THREADS / 64) + wave;
     const Loader ld(a.g, a.ld, a.d, row);
     const uint32_t ckey = a.racc[row].smpmax_key;
     const double c = key_to_double(ckey), den = 2.0 * c;
