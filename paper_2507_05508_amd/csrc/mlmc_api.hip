@@ -556,9 +556,9 @@ mlmc_status mlmc_plan(mlmc_plan_t** plan, int kind, int M, int64_t d, int in_dty
         off = align_up(off + sizeof(uint32_t) * 32768 * (size_t)(pl->c16_wgs + 1) * M, 256);
         pl->off_c16_occ = off;
         off = align_up(off + sizeof(uint32_t) * 8 * (size_t)pl->c16_wgs * M, 256);
-        // The message read by slices (one launch) against the one by tiles (three), compress, us: 32 rows of 1000003 (slices of 126976) 102 to 108 / 92 to 117,
-        // 4 of 2500000 67 / 71 to 83; 8 of 11689512 (slices of 368640) 184 / 166, 4 of 30000001 219 / 193, 1 of 1e8 176 / 169, 4 of 1.24e8 with
-        // stretches of many scales 700 / 480.  Rows of one value, all of which may be in the message, are slower by tiles (604 / 796).
+        // The message read by slices (one launch) against the one by tiles (three), compress + aggregate, us: 32 rows of 3000001 (slices of 376832), 0.1 % outliers,
+        // 173 / 190, 8 of 11689512 (368640) 170 / 177, but heavy-tailed 167 / 155 and with fixed p 141 / 128; 4 of 30000001 215 / 215 and 214 / 194; 4 of 1.24e8 with
+        // stretches of many scales 700 / 480 (compress).  Rows of one value, all of which may be in the message, are slower by tiles (604 / 796).
         if (pl->c16_slice >= (1 << 18)) {
             pl->off_c16_list = off;
             off = align_up(off + sizeof(uint32_t) * TILE * (size_t)pl->ntiles * M, 256);

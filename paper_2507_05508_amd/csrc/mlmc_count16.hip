@@ -8,7 +8,7 @@
 //   k_c16_mark, k_c16_offsets, k_c16_expand   long slices: the second read leaves the tiles' entries in lists, which become the message
 //
 // Against the way of the 32-bit rows (sampled histogram, selection read with candidate lists, ranking, message from staged lists), which these
-// rows took before, adaptive, compress + aggregate: 4 rows of 1.24e8 entries 817 -> 534 us, 32 of 1e6 271 -> 106.
+// rows took before, adaptive, compress + aggregate: 4 rows of 1.24e8 entries 817 -> 534 us, 32 of 1e6 271 -> 93.
 #include "mlmc_count16.h"
 
 namespace mlmc {
@@ -188,19 +188,17 @@ constexpr int C16_STEP = 16 * C16_THREADS;
 constexpr int C16_WAVES = C16_THREADS / 64;
 typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ u16x2 both16(int32_t x) { const u16x2 r = {(uint16_t)x, (uint16_t)x}; return r; }
-// key in [from, from + n), per half: non-zero where it is (wraps below `from`, 0 <= n <= 2^15)
-__device__ __forceinline__ u16x2 in_range16(u16x2 key, u16x2 from, u16x2 n) { return __builtin_elementwise_sub_sat(n, (u16x2)(key - from)); }
-// bit e of the result: entry e of a lane's 16 satisfies f (non-zero halves per pair of keys), two entries per instruction
+// Per half, in its top bit (the other bits hold anything): key < bound, keys below 2^15, bounds up to it.
+__device__ __forceinline__ uint32_t below16(u16x2 key, u16x2 bound) { return __builtin_bit_cast(uint32_t, (u16x2)(key - bound)); }
+__device__ __forceinline__ uint32_t in_range16(u16x2 key, u16x2 lo, u16x2 hi) { return below16(key, hi) & ~below16(key, lo); }   // lo <= key < hi
+// bit e of the result: entry e of a lane's 16 satisfies f (top bits per pair of keys).  The top bits are pushed in from above, two entries
+// per instruction: six or seven instructions a pair (as 0 or 1 per half they were twelve, the compiler taking a halfword's minimum with 1 for a comparison).
 template <class F>
 __device__ __forceinline__ uint32_t mask16(const uint32_t (&b)[8], F f) {
-    const u16x2 one = {1, 1};
     uint32_t acc = 0;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const u16x2 r = __builtin_elementwise_min(f(__builtin_bit_cast(u16x2, b[i] & 0x7FFF7FFFu)), one);
-        acc |= __builtin_bit_cast(uint32_t, r) << (2 * i);
-    }
-    return (acc & 0x5555u) | ((acc >> 15) & 0xAAAAu);
+    for (int i = 0; i < 8; ++i) acc = (acc >> 2) | (f(__builtin_bit_cast(u16x2, b[i] & 0x7FFF7FFFu)) & 0x80008000u);
+    return ((acc >> 16) & 0xAAAAu) | ((acc >> 1) & 0x5555u);
 }
 // A lane's entries of the step that starts at entry j of the row (j: the lane's own first entry), [j, i1) of it there.
 __device__ __forceinline__ void fetch_step(const uint16_t* g, int64_t j, u32x4_b16 (&v)[2]) {
@@ -325,9 +323,9 @@ __global__ __launch_bounds__(MK_THREADS, 6) void k_c16_mark(TopkArgs a) {
         ms.lo[i] = (uint32_t)__builtin_amdgcn_readfirstlane((int)ms.lo[i]);
         ms.tau[i] = (uint32_t)__builtin_amdgcn_readfirstlane((int)ms.tau[i]);
     }
-    // candidates: keys in [f2, f2 + n2) or [f0, ...)
+    // candidates: keys in [f2, e2k) or [f0, ...)
     const int32_t lo0 = (int32_t)(ms.tau[0] < (uint32_t)C16_KEYS ? ms.tau[0] : ms.lo[0]), lo2 = (int32_t)(ms.tau[2] < (uint32_t)C16_KEYS ? ms.tau[2] : ms.lo[2]);
-    const u16x2 f2 = both16(lo2), n2 = both16((int32_t)ms.lo[1] - lo2), f0 = both16(lo0), n0 = both16(C16_KEYS - lo0);
+    const u16x2 f2 = both16(lo2), e2k = both16((int32_t)ms.lo[1]), f0 = both16(lo0);
     const bool based = lo0 < C16_KEYS;   // uniform: a base band
     const uint16_t* g = (const uint16_t*)a.g + (int64_t)row * a.ld;
     uint32_t* ent = s_ent[wave];
@@ -339,8 +337,8 @@ __global__ __launch_bounds__(MK_THREADS, 6) void k_c16_mark(TopkArgs a) {
     auto block = [&](const u32x4_b16& va, const u32x4_b16& vb, uint32_t blk, uint32_t valid) {
         const uint32_t b[8] = {va.x, va.y, va.z, va.w, vb.x, vb.y, vb.z, vb.w};
         uint32_t m;
-        if (based) m = mask16(b, [&](u16x2 k) { return (u16x2)(in_range16(k, f2, n2) | in_range16(k, f0, n0)); }) & valid;
-        else m = mask16(b, [&](u16x2 k) { return in_range16(k, f2, n2); }) & valid;
+        if (based) m = mask16(b, [&](u16x2 k) { return in_range16(k, f2, e2k) | ~below16(k, f0); }) & valid;
+        else m = mask16(b, [&](u16x2 k) { return in_range16(k, f2, e2k); }) & valid;
         if (__ballot(m != 0u) == 0ull) return;   // uniform
         const uint32_t c0 = __popc(m & 0xFFu), c1 = __popc(m >> 8);
         const uint32_t inc = wave_incl_scan(c0 | (c1 << 16));
@@ -553,16 +551,16 @@ __global__ __launch_bounds__(256) void k_c16_expand(TopkArgs a) {
     }
 }
 
-// Short slices: the message (Eq. (6)) of a slice by one workgroup.  Bound by the instructions of a step and its barrier: 32 rows of 1e6 entries 45 us.
-// A step's members are found as one 16-bit mask per lane, ranked by a scan
-// over the lanes and one LDS word per wave, and gathered in LDS ({entry's bits, offset in the step}); the next step writes them out densely, four
-// to a store.  One barrier per step, the loads of the next two steps in flight.
-// Of a threshold's equals the first few are inside.  Only in the one stretch in which they run out is that a matter of position:
-// there a step first counts them, and the one step that holds the last of them ranks them.
+// Short slices: the message (Eq. (6)) of a slice by one workgroup.  A step's members are found as one 16-bit mask per lane, ranked by a scan
+// over the lanes and one record per wave in LDS, and gathered in LDS ({entry's bits, offset in the step}); the next step writes them out densely, four
+// to a store.  One barrier per step, the loads of the next step in flight (of two or three: slower), those of the first one issued before the slice's state.
+// Of a threshold's equals the first few are inside.  Only in the one slice in which they run out is that a matter of position: there a wave's
+// record holds its equals too, from which every wave tells by itself which waves' are inside, and the one wave that holds the last of them ranks them.
+// One slice per threshold and row is such a one, and the launch ends with them: counted by lane shuffles and a second barrier, all three thresholds whether
+// split or not, 32 rows of 1e6 entries took 46 us, now 34; 8 of 5e6 52 and 37, 4 of 2.5e6 20 and 15, 8 of 65537 14 and 9.
 __global__ __launch_bounds__(C16_THREADS) void k_c16_write(TopkArgs a) {
     __shared__ __align__(16) uint32_t s_ent[2][C16_STEP];   // members of a step in index order: bits << 16 | base band by position << 15 | offset
-    __shared__ uint32_t s_tot[2][C16_WAVES];
-    __shared__ uint32_t s_eq[3][C16_WAVES];
+    __shared__ uint2 s_pub[2][C16_WAVES];          // a wave's members by key and the equals of the split thresholds, 16 bits each
     __shared__ uint32_t s_red[2 * C16_WAVES];
     __shared__ int64_t s_k[TMAX];
     __shared__ unsigned long long s_rows;
@@ -571,6 +569,14 @@ __global__ __launch_bounds__(C16_THREADS) void k_c16_write(TopkArgs a) {
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int row = blockIdx.y, slice = blockIdx.x;
     const RowInfo* ri = a.rinfo + row;
+    const int64_t i0 = (int64_t)slice * a.c16_slice, i1 = i0 + a.c16_slice < a.d ? i0 + a.c16_slice : a.d;
+    const bool last = i1 == a.d;
+    const uint16_t* g = (const uint16_t*)a.g + (int64_t)row * a.ld;
+    const uint32_t lane_off = (uint32_t)wave * 1024u + lane * 8u;   // this lane's first entry of a step; the other half is 512 further on
+    const int nfull = (int)((i1 - i0) / C16_STEP), nsteps = (int)((i1 - i0 + C16_STEP - 1) / C16_STEP);
+    const int64_t mine = i0 + lane_off;
+    u32x4_b16 buf[2], ahead[2];
+    if (nfull > 0) fetch_step(g, mine, buf);   // in flight while the slice's state is put together
     if (tid < TMAX) s_k[tid] = tid <= a.L ? a.k[tid] : 0;
     if (tid == 0) s_rows = 0ull;
     __syncthreads();
@@ -581,8 +587,6 @@ __global__ __launch_bounds__(C16_THREADS) void k_c16_write(TopkArgs a) {
         atomicAdd(&s_rows, (unsigned long long)(s_k[0] + s_k[li] - s_k[li - 1]));
     }
     static_assert(MLMC_MAX_WORKERS <= C16_THREADS, "a thread per row");
-    const int64_t i0 = (int64_t)slice * a.c16_slice, i1 = i0 + a.c16_slice < a.d ? i0 + a.c16_slice : a.d;
-    const bool last = i1 == a.d;
     C16Cuts cuts;
     uint32_t base, left_in_row = 0;
     slice_state<C16_THREADS>(a, row, slice, cuts, base, left_in_row, s_red);
@@ -606,22 +610,20 @@ __global__ __launch_bounds__(C16_THREADS) void k_c16_write(TopkArgs a) {
             if (rowstart + nnz > a.capacity) atomicOr(a.dev_status, MLMC_DEV_CAPACITY);
         }
     }
-    const uint16_t* g = (const uint16_t*)a.g + (int64_t)row * a.ld;
-    const uint32_t lane_off = (uint32_t)wave * 1024u + lane * 8u;   // this lane's first entry of a step; the other half is 512 further on
-    const int nfull = i1 > i0 ? (int)((i1 - i0) / C16_STEP) : 0, nsteps = i1 > i0 ? (int)((i1 - i0 + C16_STEP - 1) / C16_STEP) : 0;
     uint32_t* idx = a.idx + rowstart;
     float* val = a.val + rowstart;
     const int64_t room = a.capacity - rowstart;   // entries past the capacity are not written
 
     uint32_t run = base;
-    uint32_t par = 0, prev_first = 0, prev_count = 0, prev_sb = 0, prev_lo0 = 0;
+    uint32_t par = 0, prev_first = 0, prev_count = 0, prev_sb = 0;
+    const uint32_t lo0 = (uint32_t)cuts.lo[0] << 16;   // a key's place in an entry
     typedef uint32_t u32x4_out __attribute__((ext_vector_type(4), aligned(4)));
     typedef float f32x4_out __attribute__((ext_vector_type(4), aligned(4)));
-    auto value = [&](uint32_t e, uint32_t lo0) -> float {
+    auto value = [&](uint32_t e) -> float {
         const float v = __uint_as_float(e & 0xFFFF0000u);
         return (e & 0x7FFF0000u) >= lo0 || (e & 0x8000u) ? v : __fmul_rn(v, w);
     };
-    auto write_out = [&](uint32_t p, uint32_t first, uint32_t count, uint32_t sb, uint32_t lo0) {   // lo0: shifted, a key's place in an entry
+    auto write_out = [&](uint32_t p, uint32_t first, uint32_t count, uint32_t sb) {
         if ((int64_t)first + count <= room) {   // uniform
             const uint32_t quads = count / 4;
             for (uint32_t i = tid; i < quads; i += C16_THREADS) {
@@ -629,7 +631,7 @@ __global__ __launch_bounds__(C16_THREADS) void k_c16_write(TopkArgs a) {
                 u32x4_out j;
                 f32x4_out v;
                 j.x = sb + (e.x & 0x3FFFu); j.y = sb + (e.y & 0x3FFFu); j.z = sb + (e.z & 0x3FFFu); j.w = sb + (e.w & 0x3FFFu);
-                v.x = value(e.x, lo0); v.y = value(e.y, lo0); v.z = value(e.z, lo0); v.w = value(e.w, lo0);
+                v.x = value(e.x); v.y = value(e.y); v.z = value(e.z); v.w = value(e.w);
                 *(u32x4_out*)(idx + first + 4 * i) = j;
                 *(f32x4_out*)(val + first + 4 * i) = v;
             }
@@ -637,13 +639,13 @@ __global__ __launch_bounds__(C16_THREADS) void k_c16_write(TopkArgs a) {
             if (i < count) {
                 const uint32_t e = s_ent[p][i];
                 idx[first + i] = sb + (e & 0x3FFFu);
-                val[first + i] = value(e, lo0);
+                val[first + i] = value(e);
             }
         } else {
             for (uint32_t i = tid; i < count && (int64_t)first + i < room; i += C16_THREADS) {
                 const uint32_t e = s_ent[p][i];
                 idx[first + i] = sb + (e & 0x3FFFu);
-                val[first + i] = value(e, lo0);
+                val[first + i] = value(e);
             }
         }
     };
@@ -651,82 +653,68 @@ __global__ __launch_bounds__(C16_THREADS) void k_c16_write(TopkArgs a) {
         uint32_t b[8];
         words_of(v, b);
         const int64_t sb = i0 + (int64_t)s * C16_STEP;
-        C16Cuts now = cuts;                        // of this step
-        uint32_t split = 0;
-        uint32_t before_eq[3] = {0, 0, 0};         // equals in the waves before this one
-        if (cuts.cut) {   // uniform
-#pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                uint32_t c = 0;
-                if ((cuts.cut >> i) & 1u) c = __popc(mask16(b, [&](u16x2 k) { return in_range16(k, both16(cuts.tau[i]), both16(1)); }) & valid);
-                c = wave_sum(c);
-                if (lane == 0) s_eq[i][wave] = c;
-            }
-            __syncthreads();
-#pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                if (!((now.cut >> i) & 1u)) continue;
-                uint32_t all = 0;
-                for (int u = 0; u < C16_WAVES; ++u) {
-                    const uint32_t x = s_eq[i][u];
-                    before_eq[i] += u < wave ? x : 0u;
-                    all += x;
-                }
-                all = (uint32_t)__builtin_amdgcn_readfirstlane((int)all);
-                if (all > cuts.left[i]) {   // they run out here
-                    split |= 1u << i;
-                    cuts.cut &= ~(1u << i);
-                } else {
-                    cuts.left[i] -= all;
-                    now.lo[i] = cuts.tau[i];
-                }
-            }
-        }
+        // members by their key alone
+        const u16x2 from = both16(cuts.lo[2]), to = both16(cuts.lo[1]);
         uint32_t m;
-        uint32_t by_position = 0;   // base band members that now.lo[0] does not tell
-        if (split) {   // uniform
-            uint32_t in[3];
+        if (cuts.lo[0] < C16_KEYS) {   // uniform: a base band
+            const u16x2 f0 = both16(cuts.lo[0]);
+            m = mask16(b, [&](u16x2 k) { return in_range16(k, from, to) | ~below16(k, f0); }) & valid;
+        } else {
+            m = mask16(b, [&](u16x2 k) { return in_range16(k, from, to); }) & valid;
+        }
+        auto total_of = [](uint32_t c) { return (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(c), 63); };
+        // and the equals of the thresholds that are split in this slice
+        uint32_t e[3] = {0, 0, 0}, pub_x = __popc(m), pub_y = 0;
+        const uint32_t cut = cuts.cut;   // uniform
+        if (cut) {
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+                if ((cut >> i) & 1u) e[i] = mask16(b, [&](u16x2 k) { return in_range16(k, both16(cuts.tau[i]), both16(cuts.tau[i] + 1)); }) & valid;
+            pub_x |= __popc(e[0]) << 16;
+            pub_y = total_of(__popc(e[1]) | __popc(e[2]) << 16);
+        }
+        pub_x = total_of(pub_x);
+        if (lane == 0) s_pub[par][wave] = make_uint2(pub_x, pub_y);
+        __syncthreads();
+        if (prev_count) write_out(par ^ 1u, prev_first, prev_count, prev_sb);   // every wave is past its gathering of that step
+        const uint2 pub = s_pub[par][lane & (C16_WAVES - 1)];   // lane u: wave u's
+        uint32_t tot = pub.x & 0xFFFFu, by_position = 0;          // by_position: base band members that their keys do not tell
+        if (cut) {
+            // of every wave's equals those that are inside: `left` of them in the order of the waves
+            const uint32_t eq[3] = {pub.x >> 16, pub.y & 0xFFFFu, pub.y >> 16};
+            uint32_t keep[3] = {0, 0, 0};
 #pragma unroll
             for (int i = 0; i < 3; ++i) {
-                in[i] = mask16(b, [&](u16x2 k) { return in_range16(k, both16(now.lo[i]), both16(C16_KEYS - now.lo[i])); }) & valid;
-                if (!((split >> i) & 1u)) continue;
-                const uint32_t e = mask16(b, [&](u16x2 k) { return in_range16(k, both16(now.tau[i]), both16(1)); }) & valid;
-                const uint32_t c0 = __popc(e & 0xFFu), c1 = __popc(e >> 8);
-                const uint32_t inc = wave_incl_scan(c0 | (c1 << 16));
-                const uint32_t tot0 = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63) & 0xFFFFu;
-                uint32_t keep = 0, r = before_eq[i] + (inc & 0xFFFFu) - c0;
+                if (!((cut >> i) & 1u)) continue;
+                const uint32_t upto = wave_incl_scan(eq[i]), before = upto - eq[i], left = cuts.left[i];
+                const uint32_t here = before >= left ? 0u : eq[i] < left - before ? eq[i] : left - before;
+                tot += i == 1 ? 0u - here : here;
+                const uint32_t own = (uint32_t)__builtin_amdgcn_readlane((int)here, wave), all = (uint32_t)__builtin_amdgcn_readlane((int)upto, C16_WAVES - 1);
+                if (own == (uint32_t)__builtin_amdgcn_readlane((int)eq[i], wave)) {
+                    keep[i] = e[i];
+                } else if (own) {   // uniform over the wave: they run out among its own
+                    const uint32_t c0 = __popc(e[i] & 0xFFu), c1 = __popc(e[i] >> 8);
+                    const uint32_t inc = wave_incl_scan(c0 | (c1 << 16));
+                    const uint32_t tot0 = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63) & 0xFFFFu;
+                    uint32_t r = (inc & 0xFFFFu) - c0;
 #pragma unroll 1
-                for (int k = 0; k < 16; ++k) {
-                    if (k == 8) r = before_eq[i] + tot0 + (inc >> 16) - c1;
-                    if ((e >> k) & 1u) { if (r < now.left[i]) keep |= 1u << k; ++r; }
+                    for (int k = 0; k < 16; ++k) {
+                        if (k == 8) r = tot0 + (inc >> 16) - c1;
+                        if ((e[i] >> k) & 1u) { if (r < own) keep[i] |= 1u << k; ++r; }
+                    }
                 }
-                in[i] |= keep;
-                if (i == 0) by_position = keep;
+                if (all > left) cuts.cut &= ~(1u << i);   // none behind this step
+                else cuts.left[i] = left - all;
             }
-            m = in[0] | (in[2] & ~in[1]);
-        } else {
-            const u16x2 from = both16(now.lo[2]), n = both16(now.lo[1] - now.lo[2]);
-            if (now.lo[0] < C16_KEYS) {   // uniform: a base band
-                const u16x2 f0 = both16(now.lo[0]), n0 = both16(C16_KEYS - now.lo[0]);
-                m = mask16(b, [&](u16x2 k) { return (u16x2)(in_range16(k, from, n) | in_range16(k, f0, n0)); }) & valid;
-            } else {
-                m = mask16(b, [&](u16x2 k) { return in_range16(k, from, n); }) & valid;
-            }
+            by_position = keep[0];
+            m = keep[0] | ((m | keep[2]) & ~keep[1]);
         }
         const uint32_t c0 = __popc(m & 0xFFu), c1 = __popc(m >> 8);
         const uint32_t inc = wave_incl_scan(c0 | (c1 << 16));
-        const uint32_t tot = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63), tot0 = tot & 0xFFFFu, wtot = tot0 + (tot >> 16);
-        if (lane == 0) s_tot[par][wave] = wtot;
-        __syncthreads();
-        if (prev_count) write_out(par ^ 1u, prev_first, prev_count, prev_sb, prev_lo0);   // every wave is past its gathering of that step
-        uint32_t pre = 0, total = 0;
-#pragma unroll
-        for (int u = 0; u < C16_WAVES; ++u) {
-            const uint32_t x = s_tot[par][u];
-            pre += u < wave ? x : 0u;
-            total += x;
-        }
-        total = (uint32_t)__builtin_amdgcn_readfirstlane((int)total);
+        const uint32_t tot0 = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63) & 0xFFFFu;
+        const uint32_t upto = wave_incl_scan(tot);   // lane u: waves 0 .. u
+        const uint32_t wtot = (uint32_t)__builtin_amdgcn_readlane((int)tot, wave), total = (uint32_t)__builtin_amdgcn_readlane((int)upto, C16_WAVES - 1);
+        const uint32_t pre = (uint32_t)__builtin_amdgcn_readlane((int)upto, wave) - wtot;
         if ((wave & 3) == 0 && lane == 0 && sb + wave * 1024 < i1) tile_off[sb / TILE + wave / 4] = run + pre;
         if (wtot) {   // uniform
             uint32_t* out = s_ent[par];
@@ -756,34 +744,24 @@ __global__ __launch_bounds__(C16_THREADS) void k_c16_write(TopkArgs a) {
         prev_first = run;
         prev_count = total;
         prev_sb = (uint32_t)sb;
-        prev_lo0 = (uint32_t)now.lo[0] << 16;
         run += total;
         par ^= 1u;
     };
     static_assert(TILE == 4 * 1024 && C16_STEP <= 0x4000, "a tile is four waves' entries; offsets have 14 bits");
-    u32x4_b16 buf[2][2];
-    const int64_t mine = i0 + lane_off;
     int s = 0;
-    if (nfull >= 2) {
-        fetch_step(g, mine, buf[0]);
-        fetch_step(g, mine + C16_STEP, buf[1]);
-        for (; s + 4 <= nfull; s += 2) {
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                step(s + u, buf[u], 0xFFFFu);
-                fetch_step(g, mine + (int64_t)(s + u + 2) * C16_STEP, buf[u]);
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < 2; ++u) step(s + u, buf[u], 0xFFFFu);
-        s += 2;
+#pragma unroll 1
+    for (; s < nfull; ++s) {
+        fetch_step(g, mine + (int64_t)(s + 1 < nfull ? s + 1 : s) * C16_STEP, ahead);   // the last one again: a load without a condition, which the waits can count
+        step(s, buf, 0xFFFFu);
+        buf[0] = ahead[0];
+        buf[1] = ahead[1];
     }
-    for (; s < nsteps; ++s) {
-        const uint32_t valid = fetch_part(g, mine + (int64_t)s * C16_STEP, i1, buf[0]);
-        step(s, buf[0], valid);
+    if (s < nsteps) {
+        const uint32_t valid = fetch_part(g, mine + (int64_t)s * C16_STEP, i1, buf);
+        step(s, buf, valid);
     }
     __syncthreads();
-    if (prev_count) write_out(par ^ 1u, prev_first, prev_count, prev_sb, prev_lo0);
+    if (prev_count) write_out(par ^ 1u, prev_first, prev_count, prev_sb);
     if (last && tid == 0 && (int64_t)run != nnz) atomicOr(a.dev_status, MLMC_DEV_INTERNAL);
 }
 

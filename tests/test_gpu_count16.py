@@ -116,6 +116,24 @@ def test_more_than_64_slices(what, M, d):
         _check_rows(plan, msg, G, range(M), ladder, 4, step)
 
 
+@pytest.mark.parametrize("d", [4 * 16384 * 3, 4 * 16384 * 4 + 1030, 290_011])
+def test_slices_of_several_steps(d):
+    """64 rows in four slices each, of three to five steps, the last step whole, short, or ending inside a block: thresholds whose equals run out in the
+    first, a middle or the last step, several thresholds on one key, and all of a step's entries in the message."""
+    M, kinds = 64, ["normal", "few", "one", "zeros", "loud", "tiny"]
+    few = np.concatenate([_rows(k, 1, d, 11 + i) for i, k in enumerate(kinds)])
+    g = to_device(few).repeat(-(-M // len(kinds)), 1)[:M].contiguous()
+    for ladder in ([0, d // 7, d // 3 + 2, d], [d // 50, d // 50 + 1, d // 2 + 1, d - 1], [3, d // 4 + 16384, d // 4 + 20000, d // 2 - 77]):
+        plan = P.Plan(P.MLMC_TOPK, M, d, P.MLMC_BF16, ladder, None)
+        plan.ws.fill_(0xFF)
+        assert "k_c16_mark" not in launched(lambda: P.mlmc_compress_topk(plan, g, seed=6, step=0))
+        for step in range(3):
+            print(f"several steps d={d} {ladder} step={step}", flush=True)
+            msg = P.mlmc_compress_topk(plan, g, seed=6, step=step)
+            assert plan.status() == P.MLMC_DEV_NONFINITE
+            _check_rows(plan, msg, few, list(range(12)) + [M - 1], ladder, 6, step)
+
+
 def test_ties_in_more_tiles_than_a_workgroup_takes():
     """Rows of 1065 tiles, whose places two workgroups find: a threshold splits entries equal to it in the first one's tiles and in the second one's."""
     M, d = 16, 16 * (1 << 18) + 40 * 4096 + 77
