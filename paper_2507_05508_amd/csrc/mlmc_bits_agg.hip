@@ -45,6 +45,25 @@ __device__ __forceinline__ void finish_entry(float alpha, float acc, float* out,
     if (x) x[j] = __fsub_rn(x[j], __fmul_rn(eta, gt));
 }
 
+// the same for entries j .. j + 3
+__device__ __forceinline__ void finish_four(float alpha, float4 acc, float* out, float eta, float* x, int64_t j) {
+    typedef float f32x4_el __attribute__((ext_vector_type(4), aligned(4)));
+    f32x4_el gt;
+    gt.x = __fmul_rn(alpha, acc.x);
+    gt.y = __fmul_rn(alpha, acc.y);
+    gt.z = __fmul_rn(alpha, acc.z);
+    gt.w = __fmul_rn(alpha, acc.w);
+    if (out) __builtin_nontemporal_store(gt, (f32x4_el*)(out + j));
+    if (x) {
+        f32x4_el xv = *(const f32x4_el*)(x + j);
+        xv.x = __fsub_rn(xv.x, __fmul_rn(eta, gt.x));
+        xv.y = __fsub_rn(xv.y, __fmul_rn(eta, gt.y));
+        xv.z = __fsub_rn(xv.z, __fmul_rn(eta, gt.z));
+        xv.w = __fsub_rn(xv.w, __fmul_rn(eta, gt.w));
+        *(f32x4_el*)(x + j) = xv;
+    }
+}
+
 struct AggBitsArgs {
     BitsArgs b;
     const int32_t* level;
@@ -411,26 +430,11 @@ __global__ __launch_bounds__(EX_THREADS, 4) void k_agg_planes(AggBitsArgs a, con
     wave_lds_sync();
     const int64_t j0 = blk * EX_ELEMS;
     const uint32_t goff = (lane & ~7u) * 4u + ((lane & 7u) ^ ((lane >> 3) & 7u)) * 4u;   // element of this lane's first chunk
-    typedef float f32x4_el __attribute__((ext_vector_type(4), aligned(4)));
     if (j0 + EX_ELEMS <= b.d) {   // uniform
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
             const float4 s4 = *(const float4*)(buf + (64 * k + lane) * 4u);
-            const int64_t j = j0 + k * 256 + goff;
-            f32x4_el gt;
-            gt.x = __fmul_rn(a.alpha, s4.x);
-            gt.y = __fmul_rn(a.alpha, s4.y);
-            gt.z = __fmul_rn(a.alpha, s4.z);
-            gt.w = __fmul_rn(a.alpha, s4.w);
-            if (out) __builtin_nontemporal_store(gt, (f32x4_el*)(out + j));   // written once, read by the caller later
-            if (x) {
-                f32x4_el xv = *(const f32x4_el*)(x + j);
-                xv.x = __fsub_rn(xv.x, __fmul_rn(a.eta, gt.x));
-                xv.y = __fsub_rn(xv.y, __fmul_rn(a.eta, gt.y));
-                xv.z = __fsub_rn(xv.z, __fmul_rn(a.eta, gt.z));
-                xv.w = __fsub_rn(xv.w, __fmul_rn(a.eta, gt.w));
-                *(f32x4_el*)(x + j) = xv;
-            }
+            finish_four(a.alpha, s4, out, a.eta, x, j0 + k * 256 + goff);
         }
     } else {
 #pragma unroll 1
@@ -493,7 +497,7 @@ __global__ __launch_bounds__(NT) void k_agg_sparse(AggSparseArgs a) {
     uint32_t* s_len = (uint32_t*)(s_dyn_agg + TILE * sizeof(float) + (size_t)a.M * sizeof(int64_t));
     const int64_t tile = blockIdx.x;
     const int64_t base = tile * TILE;
-    for (int i = threadIdx.x; i < TILE; i += NT) s_acc[i] = 0.0f;
+    for (int i = threadIdx.x; i < TILE / 4; i += NT) ((float4*)s_acc)[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     for (int r = threadIdx.x; r < a.M; r += NT) {
         const uint32_t* to = a.tile_off + (size_t)r * (a.ntiles + 1);
         // a tile holds at most TILE entries of a row and they lie inside the row's message: an offset table that
@@ -555,9 +559,14 @@ __global__ __launch_bounds__(NT) void k_agg_sparse(AggSparseArgs a) {
             }
         }
     }
-    for (int i = threadIdx.x; i < TILE; i += NT) {
-        int64_t j = base + i;
-        if (j < a.d) finish_entry(a.alpha, s_acc[i], a.out, a.eta, a.x, j);
+    // Whole tiles 16 bytes a thread, at any alignment of the vectors (us: 8 rows of 1.17e7 17.9 / 15.6, with 0.1 % of the entries 14.5 / 12.1, 16 of 2.56e7 65 / 61, with
+    // the update 4 of 4e6 11.3 / 8.0, 4 of 1.24e8 258 / 191), but dense updates far beyond the last cache's size, which are all the launch
+    // writes, 4 bytes: 4 rows of 1.24e8 80.8 as against 84.0.
+    const bool wide = base + TILE <= a.d && (a.x || a.ntiles <= 16384);   // uniform
+    if (wide) {
+        for (int i = threadIdx.x; i < TILE / 4; i += NT) finish_four(a.alpha, ((const float4*)s_acc)[i], a.out, a.eta, a.x, base + 4 * i);
+    } else {
+        for (int i = threadIdx.x; i < TILE && base + i < a.d; i += NT) finish_entry(a.alpha, s_acc[i], a.out, a.eta, a.x, base + i);
     }
 }
 
