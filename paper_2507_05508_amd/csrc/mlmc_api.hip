@@ -449,10 +449,17 @@ mlmc_status mlmc_plan(mlmc_plan_t** plan, int kind, int M, int64_t d, int in_dty
         }
     }
     // chunking of the streaming kernels: about 2048 workgroups over all rows, but chunks of at least some 96 K
-    // elements (a workgroup of the selection read loads a 64 KB table first), whole tiles, at most 2^18 elements
-    // per workgroup (the LDS accumulators and the packed candidate offsets rely on that bound)
+    // elements (a workgroup of the selection read loads a table first), whole tiles, at most 2^18 elements
+    // per workgroup (the LDS accumulators and the packed candidate offsets rely on that bound).  Rows that would leave CUs without a chunk are cut finer, down to
+    // 32 K elements, but not into more than 64 chunks each (1 row of 8000001 in 123 chunks: 23.0 / 11.4 and 27.4 / 9.1).
+    // Selection read / message from the staged lists, us, chunks of 96 K and this way: 8 rows of 1000001, adaptive 22.8 / 24.0 and 18.2 / 14.4, fixed p 14.3 / 10.2 and
+    // 12.4 / 8.1; 8 of 300001 17.7 / 20.3 and 11.6 / 11.4; 4 of 4000001 30.4 / 29.4 and 31.4 / 22.8 (with chunks of 32 K 39.2 / 15.1).
+    int64_t least_chunk = (int64_t)M * d / 256;
+    if (least_chunk < d / 64) least_chunk = d / 64;
+    if (least_chunk < 8 * TILE) least_chunk = 8 * TILE;
+    if (least_chunk > 98304) least_chunk = 98304;
     int64_t target_per_row = 2048 / M > 0 ? 2048 / M : 1;
-    int64_t by_size = (d + 98303) / 98304;
+    int64_t by_size = (d + least_chunk - 1) / least_chunk;
     if (by_size < 4) by_size = 4;   // a short row still spreads over a few CUs
     if (target_per_row > by_size) target_per_row = by_size;
     int64_t chunk = (d + target_per_row - 1) / target_per_row;
@@ -480,7 +487,7 @@ mlmc_status mlmc_plan(mlmc_plan_t** plan, int kind, int M, int64_t d, int in_dty
     pl->chunks_per_row = (int)((d + chunk - 1) / chunk);   // <= 2^31 / 2^18 = CHUNKS_MAX
     // message offsets are kept per count chunk, a quarter of a chunk (unless that would be too many per row):
     // the second read of a row, when one is needed, then has four times as many workgroups
-    pl->csub = (pl->chunks_per_row * CSUB_MAX <= CHUNKS_MAX && chunk >= 16 * TILE) ? CSUB_MAX : 1;
+    pl->csub = (pl->chunks_per_row * CSUB_MAX <= CHUNKS_MAX && chunk >= 8 * TILE) ? CSUB_MAX : 1;
     pl->cchunk = (int)(chunk / pl->csub);
     pl->cchunks_per_row = (int)((d + pl->cchunk - 1) / pl->cchunk);
     // rows long enough that a second full read matters get their thresholds from a sampled histogram

@@ -1207,7 +1207,7 @@ __global__ __launch_bounds__(FN_THREADS, PHASE == 0 ? 8 : 4) void k_finish(TopkA
     // turns: the counters are kept in as many lane-interleaved copies (1, 2, 4 or 8) as the LDS array holds.
     const int zrep_shift = nparts * nchunks * 8 <= ZC ? 3 : nparts * nchunks * 4 <= ZC ? 2 : nparts * nchunks * 2 <= ZC ? 1 : 0;
     const uint32_t zrep_lane = lane & ((1u << zrep_shift) - 1u);
-    const uint32_t cmagic = (uint32_t)(0x100000000ull / (uint32_t)(a.cchunk >> 12)) + 1u;   // count chunk = multiple of 4096, >= 4 * 4096
+    const uint32_t cmagic = (uint32_t)(0x100000000ull / (uint32_t)(a.cchunk >> 12)) + 1u;   // count chunk = multiple of 4096, at least 2 * 4096
     auto chunk_of = [&](uint32_t j) -> uint32_t { return __umulhi(j >> 12, cmagic); };
 
     // range of the keys in the list, exponents for the part sums
@@ -2346,8 +2346,8 @@ static mlmc_status launch_select(const mlmc_plan_t* pl, const TopkArgs& a, bool 
             if (sums) MLMC_LAUNCH(km, st, k_main<VEC, true, true><<<mgrid, MAIN_THREADS, 0, st>>>(a, exact_pass));
             else MLMC_LAUNCH(km, st, k_main<VEC, false, true><<<mgrid, MAIN_THREADS, 0, st>>>(a, exact_pass));
         } else {
-            // chunks of 64 K elements or more in four count chunks: two workgroups per chunk, two per CU
-            if (pl->chunk >= 65536 && pl->csub == 4) {
+            // chunks in four count chunks (32 K elements or more): two workgroups per chunk, two per CU
+            if (pl->csub == 4) {
                 const dim3 grid2(2 * pl->chunks_per_row, pl->M);
                 if (sums) MLMC_LAUNCH(km, st, k_main2<VEC, true><<<grid2, M2_THREADS, 0, st>>>(a));
                 else MLMC_LAUNCH(km, st, k_main2<VEC, false><<<grid2, M2_THREADS, 0, st>>>(a));

@@ -507,3 +507,26 @@ def test_zones_resolved_by_one_workgroup(what, d, dtype):
         msg = P.mlmc_compress_topk(plan, g, seed=4, step=step)
         check_topk_against_oracle(plan, G, 4, step, msg, adaptive=True)
         assert plan.status() == 0
+
+
+@pytest.mark.parametrize("M,d", [(2, LONG + 1), (4, 1 << 17), (3, (1 << 18) + 32768 + 16384 + 5), (8, 300_001)])
+def test_chunks_of_32k_entries(M, d):
+    """Rows whose chunks have 32768 entries, read by two workgroups each: a last chunk with one workgroup's entries, with a few of the second's, and whole; a row of
+    one value, of few values, with everything large in the last chunk, and by either way of the message."""
+    rng = np.random.default_rng(d)
+    G = rng.standard_normal((M, d)).astype(np.float32)
+    G[0, -(d % 32768 or 32768):] *= 1000.0
+    G[1] = np.round(G[1] * 2) / 2 if M > 2 else -0.75
+    if M > 2:
+        G[2] = 0.25
+    g = to_device(G)
+    ladder = [d // 50, d // 50 + 1, d // 3, d // 2 + 7, d - 1]
+    for p in (None, O.geometric_p(4)):
+        plan = P.Plan(P.MLMC_TOPK, M, d, P.MLMC_F32, ladder, p)
+        assert plan.chunk == 32768
+        for step in range(4):
+            print(f"chunks of 32 K: {M}x{d} adaptive={p is None} step={step}", flush=True)
+            plan.set_staging(step < 2)
+            msg = P.mlmc_compress_topk(plan, g, seed=3, step=step)
+            check_topk_against_oracle(plan, G, 3, step, msg, adaptive=p is None)
+            assert plan.status() == 0
