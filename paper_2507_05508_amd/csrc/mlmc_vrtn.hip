@@ -38,9 +38,14 @@ __device__ __forceinline__ uint32_t mad_u24(uint32_t a, uint32_t b, uint32_t c) 
 // + D^2 sum n_{l-1}^2: per entry and level two products of codes below 2^15 (signs cancel in them), 24-bit multiply-adds that
 // meet in 32 bits for as many entries as fit, then in 64.  A code is the low word of |g| fl(D / 2c) + 1.5 2^52, formed with
 // the multiplier moved towards and away from zero as in k_rtn_extract; where the two differ it is the even one.  Bound
-// by instruction issue: with every code and residual in fp64 the kernel took 172 us for 8 rows of 1.17e7 at four levels, now 106
-// (the bare read: 62).  Eight entries at a time and four waves per SIMD; sixteen, or two waves, took 10 % longer.
-template <int DT, int LV>
+// by instruction issue: with every code and residual in fp64 the kernel took 172 us for 8 rows of 1.17e7 at four levels, now 100
+// (the bare read: 59).  Eight entries at a time and four waves per SIMD; sixteen, or two waves, took 10 % longer.
+// CHAIN: every width of the ladder divides the widest, so D_L / D_l is an odd integer q = 1 (mod 4) and a code is rne(n_L / q): a boundary between
+// two codes of level l is a half-integer in units of the widest level's, which n_L keeps the side of, and where the entry lies on it (a tie at both levels) the
+// even n_L lies on the side of the even n_l.  One multiply-add per code instead of two and their comparison; n_L cut is n_l cut.
+// With that and the next sixteen entries in flight 8 rows of 1.17e7 entries take 78 us (100 before, 82 with the multiply-adds alone), 4 of 4e7 133 (173), 8 of
+// 1e6 17.5 (18.4); read past the cache it is no faster and the extraction behind it 8 us slower.
+template <int DT, int LV, bool CHAIN>
 __global__ __launch_bounds__(256, LV <= 4 ? 4 : 2) void k_rtn_norms(BitsArgs a) {
     const int row = blockIdx.y;
     const uint32_t ckey = a.racc[row].smpmax_key;
@@ -53,6 +58,11 @@ __global__ __launch_bounds__(256, LV <= 4 ? 4 : 2) void k_rtn_norms(BitsArgs a) 
         const double mul = a.F[t] > 0 ? __ddiv_rn((double)((1 << a.F[t]) - 1), den) : 0.0;
         mul_in[t] = uniform_f64(__dmul_rn(mul, 1.0 - 0x1p-44));
         mul_out[t] = uniform_f64(__dmul_rn(mul, 1.0 + 0x1p-44));
+    }
+    double inv_q[LV];   // D_t / D_LV
+    if (CHAIN) {
+#pragma unroll
+        for (int t = 0; t < LV; ++t) inv_q[t] = uniform_f64(__ddiv_rn((double)((1 << a.F[t]) - 1), (double)((1 << a.F[LV]) - 1)));
     }
     unsigned long long sqr[LV + 1], prod[LV + 1];   // sum n_t^2, sum n_t n_{t-1}
 #pragma unroll
@@ -70,7 +80,7 @@ __global__ __launch_bounds__(256, LV <= 4 ? 4 : 2) void k_rtn_norms(BitsArgs a) 
                 sum += mad_u24(x[q], y[q], mad_u24(x[q + 1], y[q + 1], mad_u24(x[q + 2], y[q + 2], mul_u24(x[q + 3], y[q + 3]))));
         }
     };
-    auto batch = [&](const uint32_t* b) {
+    auto batch_each = [&](const uint32_t* b) {
         double av[8];
         uint32_t prev[8], cur[8];
 #pragma unroll
@@ -101,6 +111,43 @@ __global__ __launch_bounds__(256, LV <= 4 ? 4 : 2) void k_rtn_norms(BitsArgs a) 
 #pragma unroll
             for (int i = 0; i < 8; ++i) prev[i] = cur[i];
         }
+    };
+    auto batch_chain = [&](const uint32_t* b) {
+        double n[8];   // the widest level's codes
+        uint32_t up[8], differ = 0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const double av = (double)fabsf(__uint_as_float(b[i])), in = __fma_rn(av, mul_in[LV], 0x1.8p52);
+            up[i] = (uint32_t)__double2loint(in);
+            n[i] = __dsub_rn(in, 0x1.8p52);
+            differ |= up[i] ^ (uint32_t)__double2loint(__fma_rn(av, mul_out[LV], 0x1.8p52));
+        }
+        if (__ballot(differ != 0u) != 0ull) {   // a tie: the even one; the largest entry's code is cut
+            const uint32_t N = (1u << (a.F[LV] - 1)) - 1u;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const uint32_t out = (uint32_t)__double2loint(__fma_rn((double)fabsf(__uint_as_float(b[i])), mul_out[LV], 0x1.8p52));
+                up[i] = up[i] & 1u ? out : up[i];
+                up[i] = up[i] < N ? up[i] : N;
+                n[i] = (double)up[i];
+            }
+        }
+        dot(up, up, 2 * a.F[LV] - 2, sqr[LV]);
+#pragma unroll
+        for (int t = LV - 1; t >= 0; --t) {
+            if (t == 0 && a.F[0] == 0) continue;   // uniform: no base code
+            uint32_t low[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) low[i] = (uint32_t)__double2loint(__fma_rn(n[i], inv_q[t], 0x1.8p52));
+            dot(low, low, 2 * a.F[t] - 2, sqr[t]);
+            dot(up, low, a.F[t + 1] + a.F[t] - 2, prod[t + 1]);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) up[i] = low[i];
+        }
+    };
+    auto batch = [&](const uint32_t* b) {
+        if constexpr (CHAIN) batch_chain(b);
+        else batch_each(b);
     };
     // groups of four elements, four loads of a thread in flight
     const int64_t nq = (a.d + 3) / 4, qstride = (int64_t)gridDim.x * 256;
@@ -136,10 +183,17 @@ __global__ __launch_bounds__(256, LV <= 4 ? 4 : 2) void k_rtn_norms(BitsArgs a) 
             }
         }
     }
-    for (; whole(q); q += 4 * qstride) {
+    if (whole(q)) {
         fetch(q, b);
-        batch(b);
-        batch(b + 8);
+        for (bool more = true; more; q += 4 * qstride) {
+            more = whole(q + 4 * qstride);
+            uint32_t next[16];
+            fetch(more ? q + 4 * qstride : q, next);   // the last one again: a load without a condition
+            batch(b);
+            batch(b + 8);
+#pragma unroll
+            for (int i = 0; i < 16; ++i) b[i] = next[i];
+        }
     }
     for (; q < nq; q += 4 * qstride) {
 #pragma unroll
@@ -175,18 +229,26 @@ __global__ __launch_bounds__(256, LV <= 4 ? 4 : 2) void k_rtn_norms(BitsArgs a) 
         }
     }
 }
-template <int DT>
+template <int DT, bool CHAIN>
 static void launch_rtn_norms(int L, dim3 grid, hipStream_t st, const BitsArgs& a) {
     switch (L) {
-        case 1: k_rtn_norms<DT, 1><<<grid, 256, 0, st>>>(a); break;
-        case 2: k_rtn_norms<DT, 2><<<grid, 256, 0, st>>>(a); break;
-        case 3: k_rtn_norms<DT, 3><<<grid, 256, 0, st>>>(a); break;
-        case 4: k_rtn_norms<DT, 4><<<grid, 256, 0, st>>>(a); break;
-        case 5: k_rtn_norms<DT, 5><<<grid, 256, 0, st>>>(a); break;
-        case 6: k_rtn_norms<DT, 6><<<grid, 256, 0, st>>>(a); break;
-        case 7: k_rtn_norms<DT, 7><<<grid, 256, 0, st>>>(a); break;
-        default: k_rtn_norms<DT, 8><<<grid, 256, 0, st>>>(a); break;
+        case 1: k_rtn_norms<DT, 1, CHAIN><<<grid, 256, 0, st>>>(a); break;
+        case 2: k_rtn_norms<DT, 2, CHAIN><<<grid, 256, 0, st>>>(a); break;
+        case 3: k_rtn_norms<DT, 3, CHAIN><<<grid, 256, 0, st>>>(a); break;
+        case 4: k_rtn_norms<DT, 4, CHAIN><<<grid, 256, 0, st>>>(a); break;
+        case 5: k_rtn_norms<DT, 5, false><<<grid, 256, 0, st>>>(a); break;
+        case 6: k_rtn_norms<DT, 6, false><<<grid, 256, 0, st>>>(a); break;
+        case 7: k_rtn_norms<DT, 7, false><<<grid, 256, 0, st>>>(a); break;
+        default: k_rtn_norms<DT, 8, false><<<grid, 256, 0, st>>>(a); break;
     }
+}
+template <int DT>
+static void launch_rtn_norms(int L, dim3 grid, hipStream_t st, const BitsArgs& a) {
+    // five or more widths up to 16 that divide the widest: only 1, 2, 4, 8, 16
+    bool chain = true;
+    for (int t = 0; t < L; ++t) chain = chain && (a.F[t] == 0 || a.F[L] % a.F[t] == 0);
+    if (chain) launch_rtn_norms<DT, true>(L, grid, st, a);
+    else launch_rtn_norms<DT, false>(L, grid, st, a);
 }
 
 // 16-bit rows that are long enough: a row has at most 2^15 magnitudes, so one read that counts them (in LDS, one 32-bit atomic
