@@ -1003,20 +1003,23 @@ __device__ __forceinline__ int finish_shift(uint32_t kmin, uint32_t kmax) {
 }
 
 // The work of the finish kernels is a list of items (zone, slice) per row; the workgroups of a row take them in
-// turn.  Fills s_fill / s_rcnt (zone list lengths, region counts) and s_first (first item of every zone).
+// turn.  Fills s_fill / s_rcnt (zone list lengths, region counts), s_first (first item of every zone) and, where given, s_zone_of / s_k (the thresholds'
+// zones, the ladder): a lane per zone, region or threshold, since one thread that walks them waits for every read in turn.
 __device__ __forceinline__ int finish_items(const TopkArgs& a, const RowInfo* ri, const RowAcc* ra, bool sliced, uint32_t* s_fill,
-                                            uint32_t* s_rcnt, int32_t* s_first) {
+                                            uint32_t* s_rcnt, int32_t* s_first, int32_t* s_zone_of = nullptr, int64_t* s_k = nullptr) {
     const int tid = threadIdx.x, nz = ri->n_zones;
-    if (tid < nz) s_fill[tid] = ra->zone_fill[tid];
-    if (tid >= 64 && tid - 64 <= nz) s_rcnt[tid - 64] = ra->region_cnt[tid - 64];
-    __syncthreads();
-    if (tid == 0) {
-        int run = 0;
-        for (int z = 0; z < nz; ++z) {
-            s_first[z] = run;
-            run += !sliced ? 1 : zone_alone(a, s_fill[z]) ? 0 : finish_slices(a, s_fill[z]);
-        }
-        s_first[nz] = run;
+    static_assert(RMAX <= 64 && TMAX <= 64, "a lane each");
+    if (tid < 64) {
+        const uint32_t fill = tid < nz ? ra->zone_fill[tid] : 0u;
+        const uint32_t items = tid >= nz ? 0u : !sliced ? 1u : zone_alone(a, fill) ? 0u : (uint32_t)finish_slices(a, fill);
+        const uint32_t upto = wave_incl_scan(items);
+        if (tid < nz) s_fill[tid] = fill;
+        if (tid <= nz) s_first[tid] = (int32_t)(upto - items);
+    } else if (tid < 128) {
+        if (tid - 64 <= nz) s_rcnt[tid - 64] = ra->region_cnt[tid - 64];
+    } else if (tid < 192 && s_zone_of) {
+        const int t = tid - 128;
+        if (t <= a.L) { s_zone_of[t] = ri->thr_zone[t]; s_k[t] = a.k[t]; }
     }
     __syncthreads();
     return s_first[nz];
@@ -1165,7 +1168,9 @@ __global__ __launch_bounds__(FN_THREADS, PHASE == 0 ? 8 : 4) void k_finish(TopkA
         if (fail_bit) atomicOr(a.dev_status, MLMC_DEV_INTERNAL);
         else atomicOr((int32_t*)&ri->respec, 1);
     };
-    const int nitems = finish_items(a, ri, ra, PHASE == 0, s_fill, s_rcnt, s_first);
+    __shared__ int32_t s_zone_of[TMAX];
+    __shared__ int64_t s_k[TMAX];
+    const int nitems = finish_items(a, ri, ra, PHASE == 0, s_fill, s_rcnt, s_first, s_zone_of, s_k);
 
     auto run_item = [&](const int z, const int slice) {
     const uint32_t n = s_fill[z];
@@ -1173,30 +1178,28 @@ __global__ __launch_bounds__(FN_THREADS, PHASE == 0 ? 8 : 4) void k_finish(TopkA
     const bool alone = PHASE == 1 && (exact_pass || zone_alone(a, n));   // the sliced pass has no items for such zones
     const uint2* kl = a.cand + (size_t)row * (size_t)a.d + ri->zone_off[z];   // {bits, index}
 
-    if (tid == 0) {
-        // elements strictly above the zone: regions 0..z and zones 0..z-1
-        int64_t above = 0;
-        for (int i = 0; i <= z; ++i) above += s_rcnt[i];
-        for (int i = 0; i < z; ++i) above += s_fill[i];
-        bool ok = n <= ri->zone_cap[z];
-        int m = 0;
-        for (int t = ri->zone_t0[z]; t <= ri->zone_t1[z] && t <= L; ++t) {
-            if (ri->thr_zone[t] != z) continue;
-            const int64_t r = a.k[t] - above;
-            if (r < 1 || r > (int64_t)n) ok = false;
-            s_t[m] = t;
-            s_res[m] = (uint32_t)(r > 0 ? r : 1);
-            s_pfx[m] = 0;
-            ++m;
+    uint32_t kmin, kmax;   // range of the keys in the list
+    zone_key_range(ri, ra, z, kmin, kmax);
+    if (tid < 64) {
+        // elements strictly above the zone: regions 0..z and zones 0..z-1; lane t looks at threshold t
+        const uint32_t inc = wave_incl_scan((tid <= z ? s_rcnt[tid] : 0u) + (tid < z ? s_fill[tid] : 0u));
+        const int64_t above = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+        const bool here = tid <= L && s_zone_of[tid <= L ? tid : 0] == z;
+        const int64_t r = (here ? s_k[tid] : 0) - above;
+        const uint64_t m = __ballot(here);
+        bool ok = n <= ri->zone_cap[z] && m != 0ull && __ballot(here && (r < 1 || r > (int64_t)n)) == 0ull;
+        if (here) {
+            const uint32_t u = mbcnt(m);
+            s_t[u] = tid;
+            s_res[u] = (uint32_t)(r > 0 ? r : 1);
+            s_pfx[u] = 0;
         }
-        if (z == nzones - 1) {   // the last zone also checks that nothing was lost
-            int64_t tot = above + n + s_rcnt[z + 1];
-            if (tot != a.d) ok = false;
+        if (z == nzones - 1 && above + n + s_rcnt[z + 1] != a.d) ok = false;   // the last zone also checks that nothing was lost
+        if (tid == 0) {
+            if (!ok && slice == 0) fail();
+            s_n = __popcll(m);
+            s_ok = ok ? 1 : 0;
         }
-        if (m == 0) ok = false;
-        if (!ok && slice == 0) fail();
-        s_n = m;
-        s_ok = ok ? 1 : 0;
     }
     __syncthreads();
     if (!s_ok) return;
@@ -1211,9 +1214,7 @@ __global__ __launch_bounds__(FN_THREADS, PHASE == 0 ? 8 : 4) void k_finish(TopkA
     const uint32_t cmagic = (uint32_t)(0x100000000ull / (uint32_t)(a.cchunk >> 12)) + 1u;   // count chunk = multiple of 4096, at least 2 * 4096
     auto chunk_of = [&](uint32_t j) -> uint32_t { return __umulhi(j >> 12, cmagic); };
 
-    // range of the keys in the list, exponents for the part sums
-    uint32_t kmin, kmax;
-    zone_key_range(ri, ra, z, kmin, kmax);
+    // exponents for the part sums
     const int Elo = (int)(kmin >> 23) ? (int)(kmin >> 23) : 1;
     const int Ehi = (int)(kmax >> 23) ? (int)(kmax >> 23) : 1;
     const int span = Ehi - Elo + 1;
