@@ -90,7 +90,7 @@ __global__ __launch_bounds__(C16_BLOCK * G) void k_c16_reduce(TopkArgs a) {
 // order, are within the top k_t.
 __global__ __launch_bounds__(1024) void k_c16_scan(TopkArgs a) {
     __shared__ uint32_t s_scan[17];
-    __shared__ int64_t s_k[TMAX + 1];
+    __shared__ uint32_t s_k[TMAX + 1];   // the ladder: ranks are below 2^31
     __shared__ uint32_t s_big[TMAX][20];
     __shared__ unsigned long long s_wide[TMAX][20];
     __shared__ double s_norm[LMAX];
@@ -107,7 +107,7 @@ __global__ __launch_bounds__(1024) void k_c16_scan(TopkArgs a) {
             n[4 * i] = q.x; n[4 * i + 1] = q.y; n[4 * i + 2] = q.z; n[4 * i + 3] = q.w;
         }
     }
-    if (tid <= TMAX) s_k[tid] = tid <= L ? a.k[tid] : INT64_MAX;   // behind the last boundary: one that nothing reaches
+    if (tid <= TMAX) s_k[tid] = tid <= L ? (uint32_t)a.k[tid] : 0xFFFFFFFFu;   // behind the last boundary: one that nothing reaches
     for (int i = tid; i < TMAX * 20; i += 1024) (&s_wide[0][0])[i] = 0ull;
     if (tid == 0) s_top = 0u;
     uint32_t sum = 0;
@@ -129,31 +129,31 @@ __global__ __launch_bounds__(1024) void k_c16_scan(TopkArgs a) {
     if (tid == 0 && (int64_t)total != a.d) atomicOr(a.dev_status, MLMC_DEV_INTERNAL);
     if (tid <= L && s_k[tid] == 0) { ri->thr_tau[tid] = (uint32_t)C16_KEYS; ri->thr_jx[tid] = 0u; }
     if (sum) {
-        const int64_t r0 = before;   // rank of this thread's first entry
+        const uint32_t r0 = before;  // rank of this thread's first entry
         int t = 0;                     // the first band boundary behind rank r0: rank r0 lies in band t
-#pragma unroll
-        for (int u = 0; u < TMAX; ++u) t += s_k[u] <= r0 ? 1 : 0;
-        int64_t next = s_k[t];
+#pragma unroll 4
+        for (int u = 0; u <= L; ++u) t += s_k[u] <= r0 ? 1 : 0;
+        uint32_t next = s_k[t];
         const int E = lo_key >> 7, e1 = E ? E : 1;   // one exponent for all 32
         const int sh = 2 * (e1 - 1) + 32;
         uint64_t acc = 0;
-        if (next > r0 + (int64_t)sum) {   // all of them in one band
+        if (next > r0 + sum) {   // all of them in one band
 #pragma unroll
             for (int i = 0; i < 32; ++i) {
                 const uint32_t sig = (uint32_t)((lo_key + i) & 127) | (E ? 128u : 0u);
                 acc += (uint64_t)n[i] * (sig * sig);   // the square of the significand in units of 2^32
             }
         } else {
-            int64_t r = r0;
+            uint32_t r = r0;
 #pragma unroll
             for (int i = 31; i >= 0; --i) {
                 const uint32_t sig = (uint32_t)((lo_key + i) & 127) | (E ? 128u : 0u);
                 const uint64_t sq = sig * sig;
-                int64_t left = n[i];
+                uint32_t left = n[i];
                 while (next <= r + left) {   // boundary t lies among these entries or right behind them
-                    const int64_t take = next - r;
+                    const uint32_t take = next - r;
                     ri->thr_tau[t] = (uint32_t)(lo_key + i);
-                    ri->thr_jx[t] = n[i] - (uint32_t)(left - take);
+                    ri->thr_jx[t] = n[i] - (left - take);
                     acc += (uint64_t)take * sq;
                     if (a.all_thresholds && t >= 1) wide_add(s_wide[t], acc, sh);
                     acc = 0;
