@@ -140,8 +140,8 @@ __device__ __forceinline__ double key_to_double(uint32_t key) {
 // A lane owns the block's elements 32 l .. 32 l + 31, i.e. half a plane word of every plane, so that planes are made
 // inside a lane: bytes of four elements share a register, eight such registers are an 8 x 8 bit matrix per byte
 // column, and three exchange steps transpose it (transpose8).  That is 2.3 instructions per element for eight planes,
-// about 12 for the whole extraction, and leaves it to the memory: 8 rows of 1.17e7 fp32 elements take 79 us at two or three planes
-// (0.41 GB, 5.1 TB/s) and 86 us at the floating-point ladder's ten (0.49 GB, 5.7 TB/s; a kernel that only reads reaches 6.0).
+// about 12 for the whole extraction, and leaves it to the memory: 8 rows of 1.17e7 fp32 elements take 75 us at two or three planes
+// (0.41 GB, 5.4 TB/s) and 83 us at the floating-point ladder's ten (0.49 GB, 5.9 TB/s; without its stores the kernel takes 61 and 60).
 // A wave ballot per plane with its two lane writes took three instructions per element and plane: 94 and 175 us.
 //
 // The loads stay coalesced (a wave's load instruction covers 1 KB of consecutive elements) and are dealt to the lanes through LDS.

@@ -379,7 +379,7 @@ struct RtnPlaneCode {    // one of the (up to three) codes of a row's message
 // widened) may tie in every block: 8 rows of 1.17e7 fp32 entries, compress, 245 us, 260 with ties everywhere (1829 with a division each).
 // The codes of an element meet in one word, pushed in from its top, one instruction each (alignbit); masked and shifted into place it was two,
 // and the kernel, bound by instruction issue and short of registers, took 88 us for those rows instead of 69 (5.6 TB/s).  16-bit rows go at
-// the rate of a copy either way: 4 rows of 1.24e8, 38 planes in all, 316 us (5.0 TB/s).
+// the rate of a copy either way: 4 rows of 1.24e8, 38 planes in all, 300 us (5.3 TB/s).
 // A block's elements stay in LDS and are read once per code, so that the codes in the making are all the registers hold.
 template <int DT>
 __global__ __launch_bounds__(EX_THREADS, 4) void k_rtn_extract(BitsArgs a) {
