@@ -451,11 +451,18 @@ mlmc_status mlmc_plan(mlmc_plan_t** plan, int kind, int M, int64_t d, int in_dty
     // chunking of the streaming kernels: about 2048 workgroups over all rows, but chunks of at least some 96 K
     // elements (a workgroup of the selection read loads a table first), whole tiles, at most 2^18 elements
     // per workgroup (the LDS accumulators and the packed candidate offsets rely on that bound).  Rows that would leave CUs without a chunk are cut finer, down to
-    // 32 K elements, but not into more than 64 chunks each (1 row of 8000001 in 123 chunks: 23.0 / 11.4 and 27.4 / 9.1).
+    // 32 K elements, but not into more than about 64 chunks each: 1 row of 8000001 in 123 chunks 23.0 / 11.4 and 27.4 / 9.1 (the search below goes a quarter further at most,
+    // 1 row of 4000000 in 82).
     // Selection read / message from the staged lists, us, chunks of 96 K and this way: 8 rows of 1000001, adaptive 22.8 / 24.0 and 18.2 / 14.4, fixed p 14.3 / 10.2 and
     // 12.4 / 8.1; 8 of 300001 17.7 / 20.3 and 11.6 / 11.4; 4 of 4000001 30.4 / 29.4 and 31.4 / 22.8 (with chunks of 32 K 39.2 / 15.1).
+    // Nor finer than the counters of a ranking workgroup reach when all thresholds lie in one zone, as in rows of few values: a zone whose counters do not fit is ranked by one
+    // workgroup that reads its list again for the counts (1 row of one value, 32 levels inside it, compress, ms, 96 K / without this bound / with it: 2000001 entries
+    // 38 / 55 / 39, 4000000 79 / 111 / 79).  Where they fit, they are in fewer copies than with 96 K: 2000001
+    // entries of one value, 16 levels, 25.5 / 26.3 ms (normal ones 0.115 / 0.096).
+    const int64_t most_chunks = ZC_CAP / (CSUB_MAX * (L + 2));
     int64_t least_chunk = (int64_t)M * d / 256;
     if (least_chunk < d / 64) least_chunk = d / 64;
+    if (least_chunk < (d + most_chunks - 1) / most_chunks) least_chunk = (d + most_chunks - 1) / most_chunks;
     if (least_chunk < 8 * TILE) least_chunk = 8 * TILE;
     if (least_chunk > 98304) least_chunk = 98304;
     int64_t target_per_row = 2048 / M > 0 ? 2048 / M : 1;
@@ -476,7 +483,7 @@ mlmc_status mlmc_plan(mlmc_plan_t** plan, int kind, int M, int64_t d, int in_dty
             const int64_t cc = (c + 4 * TILE - 1) / (4 * TILE) * (4 * TILE);
             if (cc < 4 * TILE || cc > CHUNK_MAX) continue;
             const int64_t n = (d + cc - 1) / cc;
-            if (n > CHUNKS_MAX / CSUB_MAX) continue;
+            if (n > (least_chunk < 98304 ? most_chunks : CHUNKS_MAX / CSUB_MAX)) continue;
             const int64_t rounds = ((int64_t)M * n + NUM_CUS - 1) / NUM_CUS;
             const int64_t cost = rounds * (cc + 16384);   // + a workgroup's fixed part (table load, flush), in elements
             if (best_cost < 0 || cost < best_cost || (cost == best_cost && cc == chunk)) { best = cc; best_cost = cost; }

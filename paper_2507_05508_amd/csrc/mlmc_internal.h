@@ -51,6 +51,7 @@ __host__ __device__ constexpr uint32_t class_code(uint32_t group, uint32_t count
 constexpr int G_DUMMY = GMAX - 1;
 constexpr int REP_SUM = 16;             // replicas of the 64-bit group sum accumulators: slot = id * 16 + (lane & 15)
 constexpr int REP_CNT = 16;             // replicas of the 32-bit region / zone counters
+constexpr int ZC_CAP = 8192;            // counters of a ranking workgroup: (parts of the zone) x (count chunks of the row)
 constexpr int CSUB_MAX = 4;             // count chunks per chunk of the selection read
 
 constexpr int THR_NONE = -1;      // k_t == 0: nothing is within the top k_t

@@ -976,7 +976,6 @@ __device__ __forceinline__ void wave_rank_search(const uint32_t* h, uint32_t r, 
     if (!m) { bin = 0; rin = r; cnt = 0; }
 }
 
-constexpr int ZC_CAP = 8192;         // (parts of the zone) x (chunks of the row) counters
 
 // A zone's candidate list is split over up to a.fin_slices workgroups, a.fin_slice candidates or more each.
 __device__ __forceinline__ int finish_slices(const TopkArgs& a, uint32_t n) {

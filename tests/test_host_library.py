@@ -80,3 +80,13 @@ def test_plan_validation():
     tk.set_overlap(False)
     with pytest.raises(P.MlmcError):
         bits.set_overlap(True)
+
+
+@pytest.mark.parametrize("L", [16, 24, 32])
+@pytest.mark.parametrize("M,d", [(1, 2_000_001), (1, 3_000_001), (1, 4_000_000), (2, 4_000_000), (1, 4_257_475), (3, 5_800_000), (1, 131_073)])
+def test_count_chunks_fit_the_counters_of_a_ranking_workgroup(M, d, L):
+    """Chunks cut finer than 96 K entries: a zone with all thresholds of the ladder in it (a row of one value) still has a counter for each of its parts and every count
+    chunk, of which a chunk of 32768 entries or more has four; a workgroup has 8192."""
+    plan = P.Plan(P.MLMC_TOPK, M, d, P.MLMC_F32, [d * (t + 1) // (L + 2) for t in range(L + 1)], None, allocate=False)
+    per = plan.chunk // 4 if plan.chunk >= 32768 else plan.chunk
+    assert (L + 2) * -(-d // per) <= 8192
