@@ -497,6 +497,15 @@ __global__ __launch_bounds__(NT) void k_agg_sparse(AggSparseArgs a) {
     uint32_t* s_len = (uint32_t*)(s_dyn_agg + TILE * sizeof(float) + (size_t)a.M * sizeof(int64_t));
     const int64_t tile = blockIdx.x;
     const int64_t base = tile * TILE;
+    // Whole tiles leave 16 bytes a thread, at any alignment of the vectors, but not dense updates that are all the launch moves: past some 4e7 entries few short messages
+    // make it a fill, which 4 bytes a thread write faster.  us, 4 bytes / 16, out only, `per` message entries of all rows per tile: 2e7 entries, 1 or 8 rows, any per,
+    // 16.3 / 14.9 and 19.5 / 18.7; 4e7, 2 or 4 rows, per 8 to 300, 27.6 to 31 / 27.6 to 30; 1 row of 6e7, 192 39.3 / 41.1, 384 44.3 / 41.1, of 1.24e8, 75.7 / 86.2 and
+    // 84.1 / 80.4; 2 rows of 6e7, 8 to 128 39.6 / 42.6, 300 42.1 / 39.5, of 1.24e8, 384 78.5 / 81.7, 1024 120 / 112; 4 of 6e7, 8 41.2 / 42.6, 96 43.9 / 41.7, of 1.24e8, 8
+    // 77.6 / 88.1, 300 83.3 / 85.9, 1024 118 / 113; 5 of 9e7, 70 64.7 / 60.5; 8 of 1.24e8, 8 84.6 / 86.3, 64 96.8 / 86.1; 16, 8 106 / 86.  With the update 1 of 1e7
+    // 20.2 / 14.6, of 2e8 403 / 284, of 1e6 as fast.
+    const bool beyond = a.ntiles > 16384;
+    const int64_t per = a.M >= (beyond ? 5 : 4) ? 64 : beyond && a.M > 1 ? 512 : 256;
+    const bool wide = base + TILE <= a.d && (a.x || a.ntiles <= 10240 || a.M >= 8 || a.row_off[a.M] >= per * a.ntiles);   // uniform
     for (int i = threadIdx.x; i < TILE / 4; i += NT) ((float4*)s_acc)[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     for (int r = threadIdx.x; r < a.M; r += NT) {
         const uint32_t* to = a.tile_off + (size_t)r * (a.ntiles + 1);
@@ -559,14 +568,19 @@ __global__ __launch_bounds__(NT) void k_agg_sparse(AggSparseArgs a) {
             }
         }
     }
-    // Whole tiles 16 bytes a thread, at any alignment of the vectors (us: 8 rows of 1.17e7 17.9 / 15.6, with 0.1 % of the entries 14.5 / 12.1, 16 of 2.56e7 65 / 61, with
-    // the update 4 of 4e6 11.3 / 8.0, 4 of 1.24e8 258 / 191), but dense updates far beyond the last cache's size, which are all the launch
-    // writes, 4 bytes: 4 rows of 1.24e8 80.8 as against 84.0.
-    const bool wide = base + TILE <= a.d && (a.x || a.ntiles <= 16384);   // uniform
     if (wide) {
         for (int i = threadIdx.x; i < TILE / 4; i += NT) finish_four(a.alpha, ((const float4*)s_acc)[i], a.out, a.eta, a.x, base + 4 * i);
     } else {
-        for (int i = threadIdx.x; i < TILE && base + i < a.d; i += NT) finish_entry(a.alpha, s_acc[i], a.out, a.eta, a.x, base + i);
+        // Two forms of one loop: with the end of the row as its bound it is not unrolled, which a fill likes (2 rows of 1.24e8, 8 entries a tile, 76.5, unrolled 87.9), other launches
+        // do not (4 rows, 96, 86.8 and 82.7).
+        if (a.M <= 3) {   // uniform
+            for (int i = threadIdx.x; i < TILE && base + i < a.d; i += NT) finish_entry(a.alpha, s_acc[i], a.out, a.eta, a.x, base + i);
+        } else {
+            for (int i = threadIdx.x; i < TILE; i += NT) {
+                const int64_t j = base + i;
+                if (j < a.d) finish_entry(a.alpha, s_acc[i], a.out, a.eta, a.x, j);
+            }
+        }
     }
 }
 

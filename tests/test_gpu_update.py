@@ -97,3 +97,52 @@ def test_aggregate_by_number_of_tiles(tiles, M, top):
     for use_tile in (True, False):
         out = P.mlmc_aggregate(plan, msg, 1.0 / M, use_tile_off=use_tile)
         assert np.array_equal(out.cpu().numpy().view(np.uint32), want)
+
+
+@pytest.mark.parametrize("start", [1, 2, 3])
+@pytest.mark.parametrize("kind,M,d", [("topk", 3, 4096), ("topk", 9, 2 * 4096 + 1), ("topk", 2, 4095), ("stopk", 2, 3 * 4096 - 1), ("stopk", 5, 5 * 4096)])
+def test_vectors_that_start_anywhere(kind, M, d, start):
+    """The dense update and the model at every alignment that their type has: whole tiles leave 16 bytes a thread.  What lies around them stays as it is."""
+    G = np.random.default_rng(d).standard_normal((M, d)).astype(np.float32)
+    if kind == "topk":
+        plan = P.Plan(P.MLMC_TOPK, M, d, P.MLMC_F32, [d // 50, d // 10, d // 2], [0.5, 0.5])
+    else:
+        plan = P.Plan(P.MLMC_STOPK, M, d, P.MLMC_F32, [d // 7], None)
+    msg = P.mlmc_compress_topk(plan, to_device(G), seed=5, step=1)
+    off, idx, val = msg.row_off.cpu().numpy(), msg.idx.cpu().numpy().view(np.uint32), msg.val.cpu().numpy()
+    gt = O.aggregate_sparse([{"idx": idx[off[i]:off[i + 1]], "val": val[off[i]:off[i + 1]]} for i in range(M)], d, 1.0 / M)
+    x0 = np.linspace(-1, 1, d).astype(np.float32)
+    room = torch.full((2, d + 8), 7.5, dtype=torch.float32, device="cuda:0")
+    out, x = room[0, start:start + d], room[1, 4 - start:4 - start + d]
+    assert out.data_ptr() % 16 == 4 * start or d % 4
+    for update in (False, True):
+        print(f"{kind} d={d} start={start} update={update}", flush=True)
+        room.fill_(7.5)
+        x.copy_(torch.from_numpy(x0))
+        if update:
+            P.mlmc_aggregate_update(plan, msg, 1.0 / M, 0.25, x, out=out)
+        else:
+            P.mlmc_aggregate(plan, msg, 1.0 / M, out=out)
+        assert np.array_equal(out.cpu().numpy().view(np.uint32), gt.view(np.uint32))
+        assert np.array_equal(x.cpu().numpy().view(np.uint32), (O.server_update(x0, gt, 0.25) if update else x0).view(np.uint32))
+        assert bool((room[0, :start] == 7.5).all() and (room[0, start + d:] == 7.5).all())
+        assert bool((room[1, :4 - start] == 7.5).all() and (room[1, 4 - start + d:] == 7.5).all())
+
+
+@pytest.mark.parametrize("M,tiles,per", [(2, 10240, 8), (2, 10241, 254), (2, 10241, 256), (4, 10241, 60), (4, 10241, 64), (8, 10241, 8)])
+def test_width_of_the_stores_of_long_updates(M, tiles, per):
+    """Both widths of the stores at the number of tiles, rows and message entries per tile where one follows the other; the last tile is not whole."""
+    d = tiles * 4096 - 3
+    k = per * tiles // (2 * M) + 1
+    gen = torch.Generator(device="cuda").manual_seed(tiles)
+    g = torch.randn((M, d), generator=gen, device="cuda")
+    plan = P.Plan(P.MLMC_TOPK, M, d, P.MLMC_F32, [k, 2 * k, 3 * k], [0.5, 0.5])
+    print(f"aggregate M={M} tiles={tiles} per={per}", flush=True)
+    msg = P.mlmc_compress_topk(plan, g, seed=2, step=0)
+    off = msg.row_off.cpu().tolist()
+    assert per * tiles <= off[M] <= (per + 1) * tiles
+    want = torch.zeros(d, device="cuda")
+    for i in range(M):   # a row's indices are distinct: one addition per entry, in the order of the rows
+        want[msg.idx[off[i]:off[i + 1]].long()] += msg.val[off[i]:off[i + 1]]
+    out = P.mlmc_aggregate(plan, msg, 0.5, out=torch.full((d,), float("nan"), device="cuda"))
+    assert torch.equal(out.view(torch.int32), (want * 0.5).view(torch.int32))
