@@ -497,15 +497,6 @@ __global__ __launch_bounds__(NT) void k_agg_sparse(AggSparseArgs a) {
     uint32_t* s_len = (uint32_t*)(s_dyn_agg + TILE * sizeof(float) + (size_t)a.M * sizeof(int64_t));
     const int64_t tile = blockIdx.x;
     const int64_t base = tile * TILE;
-    // Whole tiles leave 16 bytes a thread, at any alignment of the vectors, but not dense updates that are all the launch moves: past some 4e7 entries few short messages
-    // make it a fill, which 4 bytes a thread write faster.  us, 4 bytes / 16, out only, `per` message entries of all rows per tile: 2e7 entries, 1 or 8 rows, any per,
-    // 16.3 / 14.9 and 19.5 / 18.7; 4e7, 2 or 4 rows, per 8 to 300, 27.6 to 31 / 27.6 to 30; 1 row of 6e7, 192 39.3 / 41.1, 384 44.3 / 41.1, of 1.24e8, 75.7 / 86.2 and
-    // 84.1 / 80.4; 2 rows of 6e7, 8 to 128 39.6 / 42.6, 300 42.1 / 39.5, of 1.24e8, 384 78.5 / 81.7, 1024 120 / 112; 4 of 6e7, 8 41.2 / 42.6, 96 43.9 / 41.7, of 1.24e8, 8
-    // 77.6 / 88.1, 300 83.3 / 85.9, 1024 118 / 113; 5 of 9e7, 70 64.7 / 60.5; 8 of 1.24e8, 8 84.6 / 86.3, 64 96.8 / 86.1; 16, 8 106 / 86.  With the update 1 of 1e7
-    // 20.2 / 14.6, of 2e8 403 / 284, of 1e6 as fast.
-    const bool beyond = a.ntiles > 16384;
-    const int64_t per = a.M >= (beyond ? 5 : 4) ? 64 : beyond && a.M > 1 ? 512 : 256;
-    const bool wide = base + TILE <= a.d && (a.x || a.ntiles <= 10240 || a.M >= 8 || a.row_off[a.M] >= per * a.ntiles);   // uniform
     for (int i = threadIdx.x; i < TILE / 4; i += NT) ((float4*)s_acc)[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     for (int r = threadIdx.x; r < a.M; r += NT) {
         const uint32_t* to = a.tile_off + (size_t)r * (a.ntiles + 1);
@@ -568,6 +559,16 @@ __global__ __launch_bounds__(NT) void k_agg_sparse(AggSparseArgs a) {
             }
         }
     }
+    // Whole tiles leave 16 bytes a thread, at any alignment of the vectors, but not dense updates that are all the launch moves: past some 4e7 entries few short messages
+    // make it a fill, which 4 bytes a thread write faster.  us, 4 bytes / 16, out only, `per` message entries of all rows per tile: 2e7 entries, 1 or 8 rows, any per,
+    // 16.3 / 14.9 and 19.5 / 18.7; 4e7, 2 or 4 rows, per 8 to 300, 27.6 to 31 / 27.6 to 30; 1 row of 6e7, 192 39.3 / 41.1, 384 44.3 / 41.1, of 1.24e8, 75.7 / 86.2 and
+    // 84.1 / 80.4; 2 rows of 6e7, 8 to 128 39.6 / 42.6, 300 42.1 / 39.5, of 1.24e8, 384 78.5 / 81.7, 1024 120 / 112; 4 of 6e7, 8 41.2 / 42.6, 96 43.9 / 41.7, of 1.24e8, 8
+    // 77.6 / 88.1, 300 83.3 / 85.9, 1024 118 / 113; 5 of 9e7, 70 64.7 / 60.5; 8 of 1.24e8, 8 84.6 / 86.3, 64 96.8 / 86.1; 16, 8 106 / 86.  With the update 1 of 1e7
+    // 20.2 / 14.6, of 2e8 403 / 284, of 1e6 as fast.
+    // Decided here: at the start of the kernel it cost 1 % at 16 rows of 2.56e7 and 256 of 131072.
+    const bool beyond = a.ntiles > 16384;
+    const int64_t per = a.M >= (beyond ? 5 : 4) ? 64 : beyond && a.M > 1 ? 512 : 256;
+    const bool wide = base + TILE <= a.d && (a.x || a.ntiles <= 10240 || a.M >= 8 || a.row_off[a.M] >= per * a.ntiles);   // uniform
     if (wide) {
         for (int i = threadIdx.x; i < TILE / 4; i += NT) finish_four(a.alpha, ((const float4*)s_acc)[i], a.out, a.eta, a.x, base + 4 * i);
     } else {
