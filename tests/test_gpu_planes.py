@@ -89,3 +89,26 @@ def test_planes_of_rows_with_non_finite_entries(kind):
             assert np.array_equal(planes[i, 0], O.pack_plane((G[i].view(np.uint32) >> 31).astype(np.uint8)))
             for b in range(F[level] - F[level - 1]):
                 assert np.array_equal(planes[i, 1 + b], O.pack_plane(((field >> b) & 1).astype(np.uint8))), (i, b)
+
+
+@pytest.mark.parametrize("kind", list(KINDS))
+@pytest.mark.parametrize("M,d", [(2, 64 * 8192), (2, 65 * 8192 - 2049), (1, 71 * 8192 + 5), (16, 199 * 8192 + 77), (16, 500 * 8192 - 5)])
+def test_planes_of_grids_rounded_up_to_the_dies(kind, M, d):
+    """Workgroups in multiples of eight, dealt by die: as many as the rows' quadruples of blocks, a few past the last one, one block or several a wave."""
+    code, ladders, *_ = KINDS[kind]
+    row = {"bits": O.compress_bits_row, "vbits": O.compress_vbits_row, "fbits": O.compress_fbits_row, "rtn": O.compress_rtn_row}[kind]
+    F = ladders[0]
+    p = O.geometric_p(len(F) - 1)
+    g = torch.randn((M, d), generator=torch.Generator(device="cuda").manual_seed(d), device="cuda") * 0.01
+    plan = P.Plan(code, M, d, P.MLMC_F32, F, p)
+    msg = P.BitsMessage(plan)
+    msg.planes.fill_(0x5555)
+    print(f"grid {kind} M={M} d={d}", flush=True)
+    P.mlmc_compress_rtn(plan, g, 4, 1, out=msg) if kind == "rtn" else P.mlmc_compress_bits(plan, g, 4, 1, out=msg)
+    assert plan.status() == 0
+    for i in sorted({0, M - 1}):
+        want = row(g[i].cpu().numpy(), F, p, 4, 1, i)
+        planes = msg.planes[i].cpu().numpy().view(np.uint64)
+        n = want["planes"].shape[0]
+        assert int(msg.level[i]) == want["level"]
+        assert np.array_equal(planes[:n], want["planes"]) and bool((planes[n:] == 0x5555).all())
