@@ -570,9 +570,11 @@ mlmc_status mlmc_plan(mlmc_plan_t** plan, int kind, int M, int64_t d, int in_dty
         off = align_up(off + sizeof(uint32_t) * 32768 * (size_t)(pl->c16_wgs + 1) * M, 256);
         pl->off_c16_occ = off;
         off = align_up(off + sizeof(uint32_t) * 8 * (size_t)pl->c16_wgs * M, 256);
-        // The message read by slices (one launch) against the one by tiles (three), compress + aggregate, us: 32 rows of 3000001 (slices of 376832), 0.1 % outliers,
-        // 173 / 190, 8 of 11689512 (368640) 170 / 177, but heavy-tailed 167 / 155 and with fixed p 141 / 128; 4 of 30000001 215 / 215 and 214 / 194; 4 of 1.24e8 with
-        // stretches of many scales 700 / 480 (compress).  Rows of one value, all of which may be in the message, are slower by tiles (604 / 796).
+        // The message read by slices (one launch) against the one by tiles (three), compress, 12 levels, us.  Rows whose stretches have scales of their own, adaptive: 32 rows of
+        // 3000001 (slices of 376832) 142 / 154, 8 of 11689512 (368640) 135 / 141, 4 of 30000001 (471040) 173 / 167, 1 of 1e8 (393216) 127 / 138, 4 of 1.24e8 (1945600) 534 / 480;
+        // with fixed p 123 / 122, 120 / 108, 145 / 135, 109 / 107, 449 / 379.  Rows of one distribution are faster by slices at these sizes too, with fixed p 123 / 129, 111 / 116,
+        // 147 / 149, 101 / 117, but 440 / 423, adaptive 152 / 180, 138 / 165, 180 / 207, 135 / 200, 568 / 698, of one value, all of which may be in the message, 433 / 632.
+        // Shorter slices: always faster (32 of 2000001 117 / 136 and 94 / 97).  So the line is where the stretches begin to gain with fixed p, not the best one for every row.
         if (pl->c16_slice >= (1 << 18)) {
             pl->off_c16_list = off;
             off = align_up(off + sizeof(uint32_t) * TILE * (size_t)pl->ntiles * M, 256);

@@ -401,7 +401,8 @@ __device__ __forceinline__ void write_block(const BitsArgs& a, const ExtractRow&
 // KIND 0: fixed-point ladder (Sec. 3.1): |g| = sig 2^(E - 150), scale s = 2^(Emax - 126), digits floor(|g| / s 2^F).
 // KIND 1: floating-point ladder (no scale).  KIND 2: fixed-point ladder of |g| / v: the row maximum was read exactly
 // beforehand (sample of every block).  Planes: sign, base field, level field (floating point: the exponent after the sign).
-// A wave takes about three blocks in turn with the next one's loads in flight; 8 KB (4 KB) of LDS per wave.
+// A wave takes its blocks in turn (extract_grid: one or three, or more in the kinds with a row maximum, 6 at 8 rows of 1.17e7, 30 at 4 of 1.24e8) with the next one's
+// loads in flight; 8 KB (4 KB) of LDS per wave.
 // BASE: the ladder has a base field (F_0 > 0).  Four waves per SIMD (128 registers).
 template <int DT, bool REDO, int KIND, bool BASE>
 __global__ __launch_bounds__(EX_THREADS, 4) void k_bits_extract(BitsArgs a) {

@@ -702,9 +702,20 @@ constexpr int MAIN_GROUP = 2048;   // elements a wave takes at a time: its eight
 // fixed interleaved shares: the waves of a SIMD are served oldest first, so with fixed shares the oldest is done when the
 // youngest still has a third of its share left and the workgroup ends at a fraction of its wave slots; with the counter
 // all waves end within one group of each other.
+// Chunks of 32 K elements are one group for each of the eight waves: nothing is left to share out and no loads run ahead of a group's own, but two workgroups to a CU
+// are still the better way (k_main / k_main2, compress, us: 32 rows of 65537, adaptive 116 / 100, fixed p 66 / 62; 64 of 131072 140 / 129, 78 / 77; 512 of 100001 677 / 642,
+// 377 / 354).
 constexpr int M2_THREADS = 512;
 constexpr int M2_WAVES = M2_THREADS / 64;
 constexpr int M2_CSUB = 2;                                   // count chunks per workgroup
+// Groups that a wave takes at most: with one piece of the ragged end they are what its private list, chunk / 8 entries, has room for.
+__host__ __device__ constexpr int m2_most_groups(int chunk) { return (chunk / 8 - 256) / MAIN_GROUP; }
+constexpr bool m2_reaches_all() {
+    for (int c = 8 * TILE; c <= CHUNK_MAX; c += 4 * TILE)
+        if (M2_WAVES * m2_most_groups(c) < c / 2 / MAIN_GROUP) return false;
+    return true;
+}
+static_assert(m2_reaches_all(), "the waves' lists have room for all of their workgroup's groups, at every chunk in four count chunks");
 constexpr int M2_TAB = 0;                                    // uint8 [NB1]
 constexpr int M2_SUM = NB1;                                  // uint64 [GMAX][REP_SUM]
 constexpr int M2_ZCUR = M2_SUM + GMAX * REP_SUM * 8;         // uint32 [64]
@@ -810,10 +821,10 @@ __global__ __launch_bounds__(M2_THREADS, 4) void k_main2(TopkArgs a) {
     {
         // Groups of MAIN_GROUP elements from the counter; a wave holds the group it works on and the next one, whose
         // loads refill the ring as those of the current one are consumed (no condition on a load of the steady-state
-        // loop, so that the waits can count them).  A wave takes at most gmax groups, which with one piece of the ragged
-        // end is what its private list has room for; together the waves have room for twice their elements.
+        // loop, so that the waits can count them).  A wave takes at most gmax groups; together the waves have room for all of them, for nearly
+        // twice as many in long chunks.
         const int ngroups = span / MAIN_GROUP;
-        const int gmax = (a.chunk / 8 - 256) / MAIN_GROUP;
+        const int gmax = m2_most_groups(a.chunk);
         int taken = 0;
         auto grab = [&]() -> int {   // uniform
             if (taken >= gmax) return -1;

@@ -40,9 +40,11 @@ __device__ __forceinline__ uint32_t mad_u24(uint32_t a, uint32_t b, uint32_t c) 
 // the multiplier moved towards and away from zero as in k_rtn_extract; where the two differ it is the even one.  Bound
 // by instruction issue: with every code and residual in fp64 the kernel took 172 us for 8 rows of 1.17e7 at four levels, now 100
 // (the bare read: 59).  Eight entries at a time and four waves per SIMD; sixteen, or two waves, took 10 % longer.
-// CHAIN: every width of the ladder divides the widest, so D_L / D_l is an odd integer q = 1 (mod 4) and a code is rne(n_L / q): a boundary between
-// two codes of level l is a half-integer in units of the widest level's, which n_L keeps the side of, and where the entry lies on it (a tie at both levels) the
-// even n_L lies on the side of the even n_l.  One multiply-add per code instead of two and their comparison; n_L cut is n_l cut.
+// CHAIN: every width of the ladder divides the widest, so D_L / D_l is an odd integer q and a code is rne(n_L / q): a boundary between
+// two codes of level l is a half-integer in units of the widest level's, which n_L keeps the side of.  Where the entry lies on it, it ties at both levels:
+// q = 1 (mod 4) for widths of two or more, so that the even n_L lies on the side of the even n_l.  Width 1 has q = 3 (mod 4) but one
+// boundary only, at the largest entry: n_L / q stays below 1/2 and all its codes are zero, as the cut ones are.  One multiply-add
+// per code instead of two and their comparison; n_L cut is n_l cut.
 // With that and the next sixteen entries in flight 8 rows of 1.17e7 entries take 78 us (100 before, 82 with the multiply-adds alone), 4 of 4e7 133 (173), 8 of
 // 1e6 17.5 (18.4); read past the cache it is no faster and the extraction behind it 8 us slower.
 template <int DT, int LV, bool CHAIN>
@@ -244,7 +246,7 @@ static void launch_rtn_norms(int L, dim3 grid, hipStream_t st, const BitsArgs& a
 }
 template <int DT>
 static void launch_rtn_norms(int L, dim3 grid, hipStream_t st, const BitsArgs& a) {
-    // five or more widths up to 16 that divide the widest: only 1, 2, 4, 8, 16
+    // with five levels or more (1, 2, 4, 8, 16 behind a base of 0; 1, 2, 3, 4, 6, 12) the way without it, whatever the widths
     bool chain = true;
     for (int t = 0; t < L; ++t) chain = chain && (a.F[t] == 0 || a.F[L] % a.F[t] == 0);
     if (chain) launch_rtn_norms<DT, true>(L, grid, st, a);
