@@ -291,6 +291,7 @@ static mlmc_status plan_stopk(mlmc_plan_t** plan, int M, int64_t d, int in_dtype
         pl->off_se_big = take(sizeof(uint64_t) * SE_WORDS * (size_t)L * M);
         pl->off_se_gsum = take(sizeof(uint64_t) * 2 * (size_t)(L + 256) * M);
         pl->off_se_nz = take(sizeof(uint32_t) * SE_NZ * (size_t)M);
+        pl->off_se_apx = take(sizeof(double) * (size_t)L * M);
         pl->off_se_end = off;
         pl->off_se_bsum = take(sizeof(uint32_t) * ((SE_BINS + 255) / 256) * (size_t)M);
         pl->off_se_map = take(sizeof(uint32_t) * 8192 * (size_t)M);
@@ -312,6 +313,9 @@ static mlmc_status plan_stopk(mlmc_plan_t** plan, int M, int64_t d, int in_dtype
         pl->off_se_list = take(sizeof(uint32_t) * (size_t)d * M);
         if (d > SE_ZBIG) pl->off_se_list2 = take(sizeof(uint32_t) * (size_t)d * M);
         pl->off_se_tie = take(sizeof(uint2) * (size_t)pl->ntiles * M);
+        pl->off_se_win = take(sizeof(uint2) * (size_t)(L + 1) * M);
+        pl->off_se_got = take(sizeof(uint2) * (size_t)M);
+        pl->off_se_cand = take(sizeof(uint32_t) * 8 * (size_t)((d + 1023) / 1024) * M);
     }
     pl->off_bitmap = off;
     off = align_up(off + sizeof(uint32_t) * (size_t)pl->bm_words * M + 16, 256);
@@ -386,6 +390,11 @@ static void fill_stopk_args(const mlmc_plan_t* pl, StopkArgs& a, const void* g, 
         a.se_list = (uint32_t*)(w + pl->off_se_list);
         a.se_list2 = (uint32_t*)(w + pl->off_se_list2);
         a.se_tie = (uint2*)(w + pl->off_se_tie);
+        a.se_apx = (double*)(w + pl->off_se_apx);
+        a.se_win = (uint2*)(w + pl->off_se_win);
+        a.se_got = (uint2*)(w + pl->off_se_got);
+        a.se_cand = (uint32_t*)(w + pl->off_se_cand);
+        a.se_cblks = (pl->d + 1023) / 1024;
     }
     a.tile_off = (uint32_t*)(w + pl->off_tileoff);
     a.norms = (double*)(w + pl->off_norms);

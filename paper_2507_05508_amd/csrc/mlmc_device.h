@@ -11,6 +11,10 @@ __device__ __forceinline__ uint32_t mbcnt(uint64_t m) {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
+// old with lane l (uniform) replaced by v (uniform); clang has the intrinsic but no builtin of this name
+__device__ int llvm_amdgcn_writelane(int v, int l, int old) __asm("llvm.amdgcn.writelane.i32");
+__device__ __forceinline__ uint32_t write_lane(uint32_t v, int l, uint32_t old) { return (uint32_t)llvm_amdgcn_writelane((int)v, l, (int)old); }
+
 // Orders LDS traffic between the lanes of one wave (no instruction beyond the waits the fences need).
 __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");

@@ -206,10 +206,12 @@ struct SRow {           // per row: the drawn segment
     int32_t level;
     float weight;
     int64_t lo, count;  // its positions in the sorted row: [lo, lo + count)
+    uint2 hi, thr_lo;   // rows that are not sorted: thresholds of its two boundaries, as in se_thr
+    int32_t few, pad_;  // 1: the second read has marked all of its entries
 };
 // The way without a sort (ladders of up to SE_LMAX levels)
 constexpr int SE_LMAX = 4096;
-constexpr int SE_BINS = 32000;          // bins of a row's exact histogram: with the coarse map they fill a CU's LDS
+constexpr int SE_BINS = 31488;          // bins of a row's exact histogram: with the coarse map, the sums and the cursors of the zones they fill a CU's LDS
 constexpr int SE_WORDS = 20;            // 32-bit words of a band's sum of squares (2^-298 units), each in a 64-bit counter
 constexpr int SE_ZBIG = 81920;          // zones of more entries are resolved by several workgroups
 constexpr int SE_NZ = 8;                // words of a row's zone counters
@@ -252,7 +254,7 @@ struct StopkArgs {
     int64_t se_slice;        // entries of such a workgroup
     uint32_t* se_coarse;     // [M][8192] sampled histogram (cleared per call)
     unsigned long long* se_big;  // [M][L][SE_WORDS] sums of squares of the bands (cleared per call)
-    uint32_t* se_map;        // [M][8192] coarse bucket -> first bin | shift << 16
+    uint32_t* se_map;        // [M][8192] coarse bucket -> shift | first bin << 16
     uint2* se_info;          // [M][SE_BINS] {lowest key, shift} of a bin
     uint32_t* se_nbins;      // [M]
     uint32_t* se_part;       // [M][se_wgs][SE_BINS] counts of a workgroup, then those of the workgroups before it
@@ -270,6 +272,11 @@ struct StopkArgs {
     uint32_t* se_bsum;       // [M][SE_BINS / 256] totals of 256 bins each
     uint32_t* se_list;       // [M][d] keys of the zones
     uint32_t* se_list2;      // [M][d] counts of the zones of se_bigz, at the places of their lists (rows longer than SE_ZBIG)
+    double* se_apx;          // [M][L] sums of squares of the bands, entries at the middle of their bins (cleared per call)
+    uint2* se_win;           // [M][L + 1] lowest and highest key of the bin that a boundary lies in
+    uint2* se_got;           // [M] lowest and highest key of the entries that the second read marks
+    uint32_t* se_cand;       // [M][se_cblks][8] a bit per four consecutive entries: one of them is marked
+    int64_t se_cblks;        // blocks of 1024 entries of a row
     uint2* se_tie;           // [M][ntiles] entries equal to the two thresholds of the drawn segment, where they are split
 };
 
@@ -318,7 +325,7 @@ struct mlmc_plan_s {
     int64_t bm_words;
     size_t off_pa, off_pb, off_counts, off_bitmap, off_tilecnt, off_clear_end, off_srow, off_bintot;
     size_t off_se_coarse, off_se_big, off_se_end, off_se_map, off_se_info, off_se_nbins, off_se_part, off_se_total, off_se_class, off_se_gtab, off_se_thr,
-        off_se_zone, off_se_nz, off_se_list, off_se_list2, off_se_tie, off_se_bsum, off_se_gsum, off_se_mid, off_se_bigz, off_se_item;   // off_se_end: end of what is cleared per call (0: the plan sorts)
+        off_se_zone, off_se_nz, off_se_list, off_se_list2, off_se_tie, off_se_bsum, off_se_gsum, off_se_mid, off_se_bigz, off_se_item, off_se_apx, off_se_win, off_se_got, off_se_cand;   // off_se_end: end of what is cleared per call (0: the plan sorts)
     int se_shift, se_wgs, se_rep, se_mids, se_bigs, se_items;
     int64_t se_slice;
     size_t off_rtn_sums, off_rtn_part, off_rtn_total;   // Round-to-Nearest plans

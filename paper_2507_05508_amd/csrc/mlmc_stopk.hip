@@ -321,6 +321,13 @@ __global__ __launch_bounds__(1024) void k_sb_draw(StopkArgs a) {
         const int64_t lo = (int64_t)(level - 1) * a.s;
         sr->lo = lo;
         sr->count = lo + a.s < a.d ? a.s : a.d - lo;
+        if (a.se_thr) {   // ladders that are not sorted: what the message kernels need of the row, in one place
+            const uint2* thr = a.se_thr + (size_t)row * (a.L + 1) + level;
+            const uint2 h = thr[-1], o = thr[0], got = a.se_got[row];
+            sr->hi = h;
+            sr->thr_lo = o;
+            sr->few = o.x >= got.x && h.x <= got.y ? 1 : 0;
+        }
         a.level[row] = level;
     }
 }
@@ -473,16 +480,19 @@ static mlmc_status launch_stopk(const mlmc_plan_t* pl, const StopkArgs& a, bool 
 //                 inside), sums of its parts
 //   k_se_wide     the same for zones of many entries (repeated keys; rows that the sample misjudged), by counts of their keys
 //   k_se_norms / k_sb_draw   Delta_l, level
-//   k_se_mark / k_se_offsets / k_se_write   third read: bitmap of the drawn segment and its message; entries equal to a
-//                 threshold whose equal keys are split are told apart by their rank in index order
-// Three reads of the rows and about 10 bytes per entry of other traffic against 4 x 24 bytes and more for the sort of pairs:
-// 8 rows of 1.17e7 fp32 entries at 1000 levels, compress + aggregate: 2788 -> 430 us.  The line at SE_LMAX levels is where the
+//   k_se_mark / k_se_offsets / k_se_write   bitmap of the drawn segment and its message; entries equal to a
+//                 threshold whose equal keys are split are told apart by their rank in index order.  The exact counts of the bins give the
+//                 norms to about 1e-4, and with them, before the second read, a key window that holds the drawn segment nearly always: that read
+//                 leaves a bit per four entries and only those are looked at, in place of a third read of the rows (73 -> 13 us, the second one 121 -> 119
+//                 with what the forecast and the marks cost it, 11)
+// Two reads of the rows and about 10 bytes per entry of other traffic against 4 x 24 bytes and more for the sort of pairs:
+// 8 rows of 1.17e7 fp32 entries at 1000 levels, compress + aggregate: 2788 -> 430 us; with the forecast and one addition per entry in the second read
+// 401 -> 341.  The line at SE_LMAX levels is where the
 // class of a bin and the list cursors of a zone per boundary still fit LDS beside the map and the sums.
 constexpr int SE_CB = 8192;             // coarse buckets: key >> SE_CSHIFT
 constexpr int SE_CSHIFT = 18;
 constexpr int SE_THREADS = 1024;
 constexpr int SE_WAVES = SE_THREADS / 64;
-constexpr uint32_t SE_ZONE = 0x8000u;   // class of a bin: sum group, or SE_ZONE | zone
 constexpr int SE_ZCAP = 2048;           // keys that a zone's workgroup puts in order in LDS
 // Zones of more entries: first counts of 2^SE_ZBITS sub-bins, then of the (at most 16) keys of every sub-bin that holds boundaries.
 // Up to SE_ZBIG entries one workgroup does both in LDS; more are taken in slices of SE_ZSLICE by many, the counts in the
@@ -490,10 +500,13 @@ constexpr int SE_ZCAP = 2048;           // keys that a zone's workgroup puts in 
 constexpr int SE_ZBITS = 14;
 constexpr uint32_t SE_ZSUB = 1u << SE_ZBITS, SE_ZSLICE = 65536;   // a slice's squares (below 2^48 each) fit a 64-bit sum
 static_assert(SE_CSHIFT - SE_ZBITS <= 4 && SE_ZBIG == (1 << SE_ZBITS) + 16 * SE_LMAX, "place of a zone's counts");
-static_assert(SE_LMAX <= 0x8000 && SE_LMAX + 256 < 0x8000, "class field");
+// Slots of k_se_split: the sums of the L + 256 groups in 2^se_rep lane-interleaved copies, behind them the cursors of the zones (fewer than L).
+constexpr int SE_SLOTS = 2 * SE_LMAX + 256;
+static_assert(SE_SLOTS < 0x10000, "class of a bin: its slot");
 
-__device__ __forceinline__ uint32_t se_bin(uint32_t entry, uint32_t key) {   // entry: of the key's coarse bucket, base | shift << 16
-    return (entry & 0xFFFFu) + ((key & ((1u << SE_CSHIFT) - 1u)) >> (entry >> 16)) + (key ? 1u : 0u);
+// entry: of the key's coarse bucket, shift | base << 16 (a shift takes the low five bits of its count as they are)
+__device__ __forceinline__ uint32_t se_bin(uint32_t entry, uint32_t key) {
+    return (entry >> 16) + ((key & ((1u << SE_CSHIFT) - 1u)) >> (entry & 31u)) + (key < 1u ? key : 1u);
 }
 
 // One more in h[b] for the active lanes that want it.  LDS atomics of many lanes on one word take a turn each (about three
@@ -600,7 +613,7 @@ __global__ __launch_bounds__(1024) void k_se_map(StopkArgs a) {
     uint32_t base = before;
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
-        const uint32_t e = base | ((uint32_t)SE_CSHIFT - kb[i]) << 16;
+        const uint32_t e = base << 16 | ((uint32_t)SE_CSHIFT - kb[i]);
         map[tid * PER + i] = e;
         base += 1u << kb[i];
     }
@@ -624,20 +637,20 @@ __global__ __launch_bounds__(SE_THREADS) void k_se_count(StopkArgs a) {
     // workgroup that makes the map took 16 us with them, 8 rows of 1.17e7 entries, 7.8 without).  A wave takes 16 buckets: small ones a lane each, large ones together.
     uint2* info = a.se_info + (size_t)row * SE_BINS;
     for (uint32_t b0 = (wave * gridDim.x + blockIdx.x) * 16u; b0 < (uint32_t)SE_CB; b0 += gridDim.x * (uint32_t)(SE_WAVES * 16)) {
-        const uint32_t e = s_map[b0 + (lane & 15u)], sh = e >> 16, n = lane < 16u ? 1u << (SE_CSHIFT - sh) : 0u;
+        const uint32_t e = s_map[b0 + (lane & 15u)], sh = e & 31u, n = lane < 16u ? 1u << (SE_CSHIFT - sh) : 0u;
         if (n <= 8u)
             for (uint32_t i = 0; i < n; ++i) {
                 const uint32_t key = ((b0 + lane) << SE_CSHIFT) + (i << sh);
-                info[1 + (e & 0xFFFFu) + i] = make_uint2(key ? key : 1u, sh);   // zeros are in bin 0: a threshold at this bin leaves them out
+                info[1 + (e >> 16) + i] = make_uint2(key ? key : 1u, sh);   // zeros are in bin 0: a threshold at this bin leaves them out
             }
         uint64_t big = __ballot(n > 8u);
         while (big) {   // uniform
             const int l = __builtin_ctzll(big);
             big &= big - 1;
-            const uint32_t eb = (uint32_t)__builtin_amdgcn_readlane((int)e, l), shb = eb >> 16, nb = 1u << (SE_CSHIFT - shb);
+            const uint32_t eb = (uint32_t)__builtin_amdgcn_readlane((int)e, l), shb = eb & 31u, nb = 1u << (SE_CSHIFT - shb);
             for (uint32_t i = lane; i < nb; i += 64) {
                 const uint32_t key = ((b0 + (uint32_t)l) << SE_CSHIFT) + (i << shb);
-                info[1 + (eb & 0xFFFFu) + i] = make_uint2(key ? key : 1u, shb);
+                info[1 + (eb >> 16) + i] = make_uint2(key ? key : 1u, shb);
             }
         }
     }
@@ -714,8 +727,10 @@ __device__ __forceinline__ int se_exp_shift(uint32_t key) {   // of the square o
 // Per 256 bins: their ranks in descending order of their keys, classes, zones, thresholds that fall on bin edges.
 __global__ __launch_bounds__(256) void k_se_scan(StopkArgs a) {
     __shared__ uint32_t s_scan[256 / 64 + 1];
-    __shared__ uint32_t s_z0, s_off0, s_many;
+    __shared__ uint32_t s_z0, s_off0, s_many, s_wide;
     __shared__ uint4 s_key[256];   // one-key bins with many boundaries: key, entries above, entries, boundaries
+    __shared__ uint4 s_win[256];   // bins with many boundaries: lowest key, shift, entries above, entries
+    __shared__ double s_apx[256];  // squares of the bins, added up by band from the workgroup's first one
     const int row = blockIdx.y, blk = blockIdx.x, tid = threadIdx.x;
     const int nbins = (int)a.se_nbins[row], nblk = (nbins + 255) / 256;
     if (blk >= nblk) return;
@@ -742,9 +757,33 @@ __global__ __launch_bounds__(256) void k_se_scan(StopkArgs a) {
         s_z0 = atomicAdd(&a.se_nz[SE_NZ * row], zones);
         s_off0 = atomicAdd(&a.se_nz[SE_NZ * row + 1], zents);
     }
-    if (tid == 0) s_many = 0;
+    if (tid == 0) s_many = s_wide = 0;
+    s_apx[tid] = 0.0;
     __syncthreads();
     uint2* thr = a.se_thr + (size_t)row * (a.L + 1);
+    // For the forecast of the drawn segment: the keys of the bin that a boundary lies in, and the squares of the bins, each entry at the middle
+    // of its bin (they choose what the second read marks, nothing else, so the order of the additions is free).
+    const uint32_t band0 = above / s;
+    uint2* win = a.se_win + (size_t)row * (a.L + 1);
+    auto apx_add = [&](uint32_t band, double e) {
+        if (band - band0 < 256u) unsafeAtomicAdd(&s_apx[band - band0], e);
+        else unsafeAtomicAdd(&a.se_apx[(size_t)row * a.L + band], e);
+    };
+    auto mid_square = [&](uint32_t lo, uint32_t shift) -> double {
+        const double v = (double)__uint_as_float(lo + ((1u << shift) >> 1));
+        return __dmul_rn(v, v);
+    };
+    auto forecast_parts = [&](uint32_t lo, uint32_t shift, uint32_t above, uint32_t n, uint32_t u0, uint32_t step) {
+        const double sq = mid_square(lo, shift);
+        const uint32_t t0 = above / s + 1u;
+        uint32_t t1 = (above + n - 1u) / s;
+        if (t1 > last_t) t1 = last_t;
+        for (uint32_t t = t0 + u0; t <= t1 + 1u; t += step) {   // the part in band t (from 1), the boundary below it
+            const uint32_t r0 = t > t0 ? (t - 1u) * s - above : 0u, r1 = t <= t1 ? t * s - above : n;
+            apx_add(t - 1u, __dmul_rn(sq, (double)(r1 - r0)));
+            if (t <= t1) win[t] = make_uint2(lo, lo + ((1u << shift) - 1u));
+        }
+    };
     // parts u0, u0 + step, ... of a key's entries: the first t s - above of them (by index) are inside boundary t
     auto key_parts = [&](uint32_t key, uint32_t above, uint32_t n, uint32_t nb, uint32_t u0, uint32_t step) {
         const uint64_t sq = sig_square(key);
@@ -758,13 +797,14 @@ __global__ __launch_bounds__(256) void k_se_scan(StopkArgs a) {
             if (u < nb) thr[t0 + u] = make_uint2(key, r1);
         }
     };
-    uint32_t code = (uint32_t)a.L + 255u;   // sums nobody reads: an empty bin, or one key with boundaries inside
+    uint32_t code = ((uint32_t)a.L + 255u) << a.se_rep;   // sums nobody reads: an empty bin, or one key with boundaries inside
     if (n && nb == 0) {
         // (255 - exponent) + band: one step at least whenever the exponent or the band changes
-        code = 255u - (in.x >> 23) + (t0 - 1u);
-        a.se_gtab[(size_t)row * (a.L + 256) + code] = (in.x >> 23) << 16 | (t0 - 1u);   // exponent, band (from 0)
+        const uint32_t group = 255u - (in.x >> 23) + (t0 - 1u);
+        a.se_gtab[(size_t)row * (a.L + 256) + group] = (in.x >> 23) << 16 | (t0 - 1u);   // exponent, band (from 0)
+        code = group << a.se_rep;
     } else if (zone) {
-        code = SE_ZONE | (s_z0 + z);   // a zone holds a boundary: fewer than L <= SE_LMAX zones
+        code = (((uint32_t)a.L + 256u) << a.se_rep) + s_z0 + z;   // a zone holds a boundary: fewer than L <= SE_LMAX zones
         SZone zr;
         zr.cum = cum;
         zr.n = n;
@@ -795,78 +835,183 @@ __global__ __launch_bounds__(256) void k_se_scan(StopkArgs a) {
         thr[0] = make_uint2(0xFFFFFFFFu, 0u);
         thr[a.L] = make_uint2(0u, SE_ALL);
     }
+    if (a.level) {   // uniform: a message follows
+        if (n && nb == 0) apx_add(t0 - 1u, __dmul_rn(mid_square(in.x, in.y), (double)n));
+        else if (nb && nb <= 32u) forecast_parts(in.x, in.y, cum, n, 0u, 1u);
+        else if (nb) s_win[atomicAdd(&s_wide, 1u)] = make_uint4(in.x, in.y, cum, n);
+        if (n && (cum + n) % s == 0u && (cum + n) / s <= last_t) win[(cum + n) / s] = make_uint2(in.x, in.x);
+        if (blk == 0 && tid == 0) {
+            win[0] = make_uint2(0xFFFFFFFFu, 0xFFFFFFFFu);
+            win[a.L] = make_uint2(0u, 0u);
+        }
+    }
     __syncthreads();
     for (uint32_t i = 0; i < s_many; ++i)   // (zeros; a row of one value has every boundary here)
         key_parts(s_key[i].x, s_key[i].y, s_key[i].z, s_key[i].w, (uint32_t)tid, 256u);
+    if (a.level) {
+        for (uint32_t i = 0; i < s_wide; ++i) forecast_parts(s_win[i].x, s_win[i].y, s_win[i].z, s_win[i].w, (uint32_t)tid, 256u);
+        __syncthreads();
+        if (s_apx[tid] > 0.0 && band0 + tid < (uint32_t)a.L) unsafeAtomicAdd(&a.se_apx[(size_t)row * a.L + band0 + tid], s_apx[tid]);
+    }
 }
 
-// Second read: sums of the regions, lists of the zones.
-constexpr int SE_SUMS_BYTES = 40960;   // sums of L + 256 groups, in 1, 2 or 4 lane-interleaved copies
-template <int DT, bool STREAM>
-__global__ __launch_bounds__(SE_THREADS) void k_se_split(StopkArgs a) {
-    __shared__ __align__(16) uint32_t s_map[SE_CB];
-    __shared__ __align__(16) uint16_t s_class[SE_BINS];
-    __shared__ uint32_t s_cur[SE_LMAX];
-    __shared__ __align__(16) unsigned long long s_sum[SE_SUMS_BYTES / 8];
-    const int row = blockIdx.y, tid = threadIdx.x;
+// The key window {lowest, highest} that holds the segment the draw will most likely take, from the squares that k_se_scan added up: the
+// levels within 2^-12 of the whole of where the drawn word falls in the running sum.  By one workgroup, which leaves it in *win.
+// What the forecast misses costs a read of the row (k_se_mark).
+constexpr int SE_PER = SE_LMAX / SE_THREADS;
+__device__ __forceinline__ void se_forecast(const StopkArgs& a, int row, double* s_w /* SE_WAVES */, int* s_t /* 2 */, uint2* win) {
+    const int tid = threadIdx.x;
     const uint32_t lane = lane_id(), wave = (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6);
-    for (int i = tid; i < SE_CB / 4; i += SE_THREADS) ((uint4*)s_map)[i] = ((const uint4*)(a.se_map + (size_t)row * SE_CB))[i];
-    for (int i = tid; i < SE_BINS / 8; i += SE_THREADS) ((uint4*)s_class)[i] = ((const uint4*)(a.se_class + (size_t)row * SE_BINS))[i];
-    for (int i = tid; i < SE_SUMS_BYTES / 8; i += SE_THREADS) s_sum[i] = 0ull;
+    const double* e = a.se_apx + (size_t)row * a.L;
+    double v[SE_PER], sum = 0.0;
+#pragma unroll
+    for (int i = 0; i < SE_PER; ++i) {
+        const int l = tid * SE_PER + i;
+        v[i] = l < a.L ? sqrt(e[l]) : 0.0;
+        sum += v[i];
+    }
+    double inc = sum;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const double u = __shfl_up(inc, o, 64);
+        if (lane >= (uint32_t)o) inc += u;
+    }
+    if (lane == 63) s_w[wave] = inc;
+    if (tid == 0) s_t[0] = s_t[1] = a.L;
+    __syncthreads();
+    double before = 0.0, total = 0.0;
+#pragma unroll
+    for (int w = 0; w < SE_WAVES; ++w) {
+        if (w == (int)wave) before = total;
+        total += s_w[w];
+    }
+    double run = before + inc - sum;
+    const double at = ((double)philox_word0(a.seed, a.step, (uint32_t)row) + 0.5) * 0x1p-32 * total, eps = total * 0x1p-12;
+    int t0 = a.L, t1 = a.L;   // first levels whose running sums pass at - eps and at + eps
+#pragma unroll
+    for (int i = SE_PER - 1; i >= 0; --i) {
+        double upto = run;
+#pragma unroll
+        for (int k = 0; k <= i; ++k) upto += v[k];
+        const int l = tid * SE_PER + i + 1;
+        if (l <= a.L && upto > at - eps) t0 = l;
+        if (l <= a.L && upto > at + eps) t1 = l;
+    }
+    if (t0 < a.L) atomicMin(&s_t[0], t0);
+    if (t1 < a.L) atomicMin(&s_t[1], t1);
+    __syncthreads();
+    if (tid == 0) {   // (a sum that is no number leaves the last level)
+        const uint2* w = a.se_win + (size_t)row * (a.L + 1);
+        *win = make_uint2(w[s_t[1]].x, w[s_t[0] - 1].y);
+    }
+    __syncthreads();
+}
+
+// Second read: sums of the regions, lists of the zones, marks of the segment that the draw will most likely take.
+struct SplitLds {
+    uint32_t map[SE_CB];                  // first: its places are offsets of the reads
+    unsigned long long slot[SE_SLOTS];
+    uint16_t cls[SE_BINS];
+    double fw[SE_WAVES];
+    int ft[2];
+    uint2 win;
+};
+static_assert(sizeof(SplitLds) <= 163840, "a CU's LDS");
+template <int DT, bool STREAM, bool MARK>
+__global__ __launch_bounds__(SE_THREADS) void k_se_split(StopkArgs a) {
+    __shared__ __align__(16) SplitLds s;
+    // Workgroups are dealt to the eight XCDs in turn: those of an XCD take slices that follow one another, so that the pieces of a zone's list that
+    // they write meet in one L2 (130 -> 127 us, 8 rows of 1.17e7 entries).
+    const uint32_t id = blockIdx.y * gridDim.x + blockIdx.x, all = gridDim.x * gridDim.y, xcd = id & 7u;
+    const uint32_t at = xcd * (all >> 3) + (xcd < (all & 7u) ? xcd : all & 7u) + (id >> 3);
+    const int row = (int)(at / gridDim.x), slice = (int)(at % gridDim.x), tid = threadIdx.x;
+    const uint32_t lane = lane_id(), wave = (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6);
+    if (MARK) se_forecast(a, row, s.fw, s.ft, &s.win);
+    for (int i = tid; i < SE_CB / 4; i += SE_THREADS) ((uint4*)s.map)[i] = ((const uint4*)(a.se_map + (size_t)row * SE_CB))[i];
+    for (int i = tid; i < SE_BINS / 8; i += SE_THREADS) ((uint4*)s.cls)[i] = ((const uint4*)(a.se_class + (size_t)row * SE_BINS))[i];
+    const int rs = a.se_rep;
+    const uint32_t groups = ((uint32_t)a.L + 256u) << rs;
+    for (uint32_t i = tid; i < groups; i += SE_THREADS) s.slot[i] = 0ull;
     {
         const int nz = (int)a.se_nz[SE_NZ * row];
-        const uint32_t* part = a.se_part + ((size_t)row * a.se_wgs + blockIdx.x) * SE_BINS;
+        const uint32_t* part = a.se_part + ((size_t)row * a.se_wgs + slice) * SE_BINS;
         const SZone* zr = a.se_zone + (size_t)row * a.L;
-        for (int z = tid; z < nz; z += SE_THREADS) s_cur[z] = zr[z].off + part[zr[z].bin];
+        for (int z = tid; z < nz; z += SE_THREADS) s.slot[groups + z] = zr[z].off + part[zr[z].bin];
         // the counts that k_se_wide adds to start at zero
         const uint32_t nbig = a.se_nz[SE_NZ * row + 3];
         for (uint32_t b = 0; b < nbig; ++b) {
             uint32_t* tab = a.se_list2 + (size_t)row * a.d + zr[a.se_bigz[(size_t)row * a.se_bigs + b]].off;
-            for (uint32_t i = blockIdx.x * SE_THREADS + tid; i <= (uint32_t)SE_ZBIG; i += gridDim.x * SE_THREADS) tab[i] = 0;
+            for (uint32_t i = slice * SE_THREADS + tid; i <= (uint32_t)SE_ZBIG; i += gridDim.x * SE_THREADS) tab[i] = 0;
         }
     }
     __syncthreads();
     RowLoader<DT, true> ld(a.g, a.ld, a.d, row);
-    const int64_t i0 = (int64_t)blockIdx.x * a.se_slice, i1 = i0 + a.se_slice < a.d ? i0 + a.se_slice : a.d;
+    const int64_t i0 = (int64_t)slice * a.se_slice, i1 = i0 + a.se_slice < a.d ? i0 + a.se_slice : a.d;
     uint32_t* list = a.se_list + (size_t)row * a.d;
-    const int rs = a.se_rep;
-    const uint32_t rlane = lane & ((1u << rs) - 1u), nobody = (uint32_t)a.L + 255u;
+    const uint32_t rlane = (lane & ((1u << rs) - 1u)) * 8u, nobody = ((uint32_t)a.L + 255u) << rs;
+    // MARK: a bit per four entries, the key of one of them is in the window (wspan stays below 2^32 - 1: keys are below 2^31, or the upper end is
+    // 2^32 - 1 and the lower one a key).
+    uint32_t wlo = 0, wspan = 0;
+    uint32_t* cand = nullptr;
+    if (MARK) {
+        wlo = (uint32_t)__builtin_amdgcn_readfirstlane((int)s.win.x);
+        wspan = (uint32_t)__builtin_amdgcn_readfirstlane((int)s.win.y) - wlo;
+        cand = a.se_cand + ((size_t)row * a.se_cblks + (size_t)(i0 >> 10) + wave) * 8 + lane;
+        if (slice == 0 && tid == 0) a.se_got[row] = s.win;
+    }
     stream_slice<DT, SE_WAVES, STREAM>(ld, i0, i1, wave, lane, [&](const uint32_t (&k)[4][4], const int (&nv)[4]) {
-        uint32_t cl[4][4], pos[4][4];
+        uint32_t cl[4][4], words = 0;
+        unsigned long long was[4][4];
 #pragma unroll
         for (int q = 0; q < 4; ++q)
 #pragma unroll
-            for (int c = 0; c < 4; ++c) cl[q][c] = s_map[k[q][c] >> SE_CSHIFT];
+            for (int c = 0; c < 4; ++c) cl[q][c] = s.map[k[q][c] >> SE_CSHIFT];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) cl[q][c] = s.cls[se_bin(cl[q][c], k[q][c])];
+        if (MARK) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                uint32_t u[4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) u[c] = c < nv[q] ? k[q][c] - wlo : 0xFFFFFFFFu;
+                const uint32_t u01 = u[0] < u[1] ? u[0] : u[1], u23 = u[2] < u[3] ? u[2] : u[3];
+                const uint64_t m = __ballot((u01 < u23 ? u01 : u23) <= wspan);
+                words = write_lane((uint32_t)m, 2 * q, words);
+                words = write_lane((uint32_t)(m >> 32), 2 * q + 1, words);
+            }
+        }
+        // One addition per entry, to its group's sum or its zone's cursor: an atomic of its own for the few zone entries is a branch, and a wait for
+        // the LDS, per entry of the lane (8 rows of 1.17e7 entries 127 us against 119; of the reads, the lookups and the marks alone 78).
 #pragma unroll
         for (int q = 0; q < 4; ++q)
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
-                cl[q][c] = s_class[se_bin(cl[q][c], k[q][c])];
                 if (c >= nv[q]) cl[q][c] = nobody;
+                const bool zone = cl[q][c] >= groups;
+                const uint32_t key = k[q][c], sig = (zone ? 1u : key >= 0x800000u ? key | 0x800000u : key) & 0xFFFFFFu;
+                was[q][c] = atomicAdd((unsigned long long*)((char*)s.slot + (cl[q][c] << 3) + (zone ? 0u : rlane)), (unsigned long long)sig * sig);
             }
-        // the places of zone entries are asked for first; they come back while the sums are added
+        // (both halves of every result are kept until all are there: a register that is free again has to be waited for before it is used)
+        asm volatile("" ::"v"(was[0][0]), "v"(was[0][1]), "v"(was[0][2]), "v"(was[0][3]), "v"(was[1][0]), "v"(was[1][1]), "v"(was[1][2]), "v"(was[1][3]),
+                     "v"(was[2][0]), "v"(was[2][1]), "v"(was[2][2]), "v"(was[2][3]), "v"(was[3][0]), "v"(was[3][1]), "v"(was[3][2]), "v"(was[3][3]));
 #pragma unroll
         for (int q = 0; q < 4; ++q)
 #pragma unroll
             for (int c = 0; c < 4; ++c)
-                if (cl[q][c] >= SE_ZONE) pos[q][c] = atomicAdd(&s_cur[cl[q][c] & (SE_ZONE - 1u)], 1u);
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-#pragma unroll
-            for (int c = 0; c < 4; ++c)
-                if (cl[q][c] < SE_ZONE) atomicAdd(&s_sum[(cl[q][c] << rs) | rlane], (unsigned long long)sig_square(k[q][c]));
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-#pragma unroll
-            for (int c = 0; c < 4; ++c)
-                if (cl[q][c] >= SE_ZONE) list[pos[q][c]] = k[q][c];
+                if (cl[q][c] >= groups) list[(uint32_t)was[q][c]] = k[q][c];
+        if (MARK) {
+            if (lane < 8) *cand = words;
+            cand += SE_WAVES * 8;
+        }
     });
     __syncthreads();
     unsigned long long* gsum = a.se_gsum + (size_t)row * (a.L + 256) * 2;
     for (int g = tid; g < a.L + 255; g += SE_THREADS) {
         unsigned long long lo = 0, hi = 0;
         for (int r = 0; r < (1 << rs); ++r) {
-            const unsigned long long v = s_sum[(g << rs) + r];
+            const unsigned long long v = s.slot[(g << rs) + r];
             lo += v & 0xFFFFFFFFull;
             hi += v >> 32;
         }
@@ -1267,13 +1412,10 @@ __global__ __launch_bounds__(64) void k_se_norms(StopkArgs a) {
 struct SegTest {
     uint32_t tau_hi, tau_lo, q_hi, q_lo;
     bool cut_hi, cut_lo, same;   // equal keys split at a boundary; both boundaries at one key
-    __device__ __forceinline__ SegTest(const StopkArgs& a, int row) {
-        const int l = a.srow[row].level;
-        const uint2* thr = a.se_thr + (size_t)row * (a.L + 1);
-        const uint2 h = thr[l - 1], o = thr[l];
-        tau_hi = h.x; q_hi = h.y; tau_lo = o.x; q_lo = o.y;
+    __device__ __forceinline__ SegTest(const SRow& r) {
+        tau_hi = r.hi.x; q_hi = r.hi.y; tau_lo = r.thr_lo.x; q_lo = r.thr_lo.y;
         same = tau_hi == tau_lo;
-        cut_hi = l > 1 && q_hi != SE_ALL;
+        cut_hi = r.level > 1 && q_hi != SE_ALL;
         cut_lo = q_lo != SE_ALL && !same;
     }
     // 0: outside, 1: member, 2: equal to tau_hi and decided by rank, 3: equal to tau_lo and decided by rank
@@ -1291,7 +1433,10 @@ struct SegTest {
     __device__ __forceinline__ uint32_t count_lo(uint32_t t, uint32_t n) const { return q_lo > t ? (q_lo - t < n ? q_lo - t : n) : 0u; }
 };
 
-// Third read: a wave takes a tile of 4096 entries; its bitmap (members, and entries that a rank decides) and its counts.
+// The drawn segment's entries: a wave takes a tile of 4096 entries; its bitmap (members, and entries that a rank decides) and its counts.
+// Where the window that the second read marked holds the segment, only the marked entries are loaded, four at a time, unless they lie in so many
+// of a tile's lines that all of it is read as quickly.
+constexpr uint32_t SE_DENSE = 128;
 template <int DT, bool STREAM>
 __global__ __launch_bounds__(256) void k_se_mark(StopkArgs a) {
     __shared__ uint32_t s_bm[4][TILE / 32];
@@ -1299,13 +1444,16 @@ __global__ __launch_bounds__(256) void k_se_mark(StopkArgs a) {
     const uint32_t lane = lane_id(), wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t tile = (int64_t)blockIdx.x * 4 + wave;
     if (tile >= a.ntiles) return;
-    const SegTest st(a, row);
+    uint32_t m = 0;   // 64 consecutive entries, a bit per four
+    if (tile * (TILE / 1024) + (lane >> 4) < a.se_cblks) m = ((const uint16_t*)(a.se_cand + ((size_t)row * a.se_cblks + tile * (TILE / 1024)) * 8))[lane];
+    const SRow sr = a.srow[row];
+    const SegTest st(sr);
     RowLoader<DT, true> ld(a.g, a.ld, a.d, row);
     ((uint2*)s_bm[wave])[lane] = make_uint2(0u, 0u);
     wave_lds_sync();
     const int64_t j0 = tile * TILE;
     uint32_t n1 = 0, n2 = 0, n3 = 0;
-    auto test = [&](const uint32_t (&b)[4], int q, int nv) {
+    auto test = [&](const uint32_t (&b)[4], int group, int nv) {   // four consecutive entries
         int kd[4];
         int any = 0;
 #pragma unroll
@@ -1322,37 +1470,52 @@ __global__ __launch_bounds__(256) void k_se_mark(StopkArgs a) {
                 n2 += kd[c] == 2;
                 n3 += kd[c] == 3;
             }
-            const uint32_t rel = (uint32_t)q * 256u + lane * 4u;
+            const uint32_t rel = (uint32_t)group * 4u;
             atomicOr(&s_bm[wave][rel >> 5], nib << (rel & 31u));
         }
     };
-    if (j0 + TILE <= a.d) {   // uniform
-        uint32_t b[16][4];
+    if (sr.few && (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan((uint32_t)__popc(m)), 63) <= SE_DENSE) {   // uniform
+        while (__ballot(m != 0)) {
+            int g[2], nv[2];
+            uint32_t b[2][4];
+            const int have = __popc(m);
 #pragma unroll
-        for (int q = 0; q < 16; ++q) {
-            if (STREAM) ld.load4_stream(j0 + q * 256 + lane * 4, b[q]);
-            else ld.load4_full(j0 + q * 256 + lane * 4, b[q]);
+            for (int u = 0; u < 2; ++u) {
+                g[u] = (int)lane * 16 + (u < have ? __builtin_ctz(m) : 0);
+                m &= m - 1;
+                nv[u] = u < have ? ld.load4(j0 + g[u] * 4, b[u]) : 0;
+            }
+#pragma unroll
+            for (int u = 0; u < 2; ++u) test(b[u], g[u], nv[u]);
         }
+    } else if (j0 + TILE <= a.d) {   // uniform
+        for (int h = 0; h < 2; ++h) {
+            uint32_t b[8][4];
 #pragma unroll
-        for (int q = 0; q < 16; ++q) test(b[q], q, 4);
+            for (int q = 0; q < 8; ++q) {
+                if (STREAM) ld.load4_stream(j0 + (h * 8 + q) * 256 + lane * 4, b[q]);
+                else ld.load4_full(j0 + (h * 8 + q) * 256 + lane * 4, b[q]);
+            }
+#pragma unroll
+            for (int q = 0; q < 8; ++q) test(b[q], (h * 8 + q) * 64 + (int)lane, 4);
+        }
     } else {
         for (int q = 0; q < 16; ++q) {
             uint32_t b[4];
             const int nv = ld.load4(j0 + q * 256 + lane * 4, b);
-            test(b, q, nv);
+            test(b, q * 64 + (int)lane, nv);
         }
     }
     wave_lds_sync();
     const int64_t w0 = tile * (TILE / 32) + lane * 2;
     uint32_t* bm = a.bitmap + (size_t)row * a.bm_words;
     if (w0 < a.bm_words) *(uint2*)(bm + w0) = ((const uint2*)s_bm[wave])[lane];   // bm_words is a multiple of 4
-    n1 = wave_sum(n1);
-    n2 = wave_sum(n2);
-    n3 = wave_sum(n3);
-    if (lane == 0) {
+    const uint32_t n12 = wave_incl_scan(n1 | n2 << 16);   // (at most 4096 each)
+    n3 = wave_incl_scan(n3);
+    if (lane == 63) {
         const size_t at = (size_t)row * a.ntiles + tile;
-        a.tile_cnt[at] = n1;
-        a.se_tie[at] = make_uint2(n2, n3);
+        a.tile_cnt[at] = n12 & 0xFFFFu;
+        a.se_tie[at] = make_uint2(n12 >> 16, n3);
     }
 }
 
@@ -1360,7 +1523,7 @@ __global__ __launch_bounds__(256) void k_se_mark(StopkArgs a) {
 __global__ __launch_bounds__(1024) void k_se_offsets(StopkArgs a) {
     __shared__ uint32_t s_scan[1024 / 64 + 1];
     const int row = blockIdx.x, tid = threadIdx.x;
-    const SegTest st(a, row);
+    const SegTest st(a.srow[row]);
     uint32_t* to = a.tile_off + (size_t)row * (a.ntiles + 1);
     const uint32_t* tc = a.tile_cnt + (size_t)row * a.ntiles;
     uint2* tie = a.se_tie + (size_t)row * a.ntiles;
@@ -1404,13 +1567,14 @@ __global__ __launch_bounds__(256) void k_se_write(StopkArgs a) {
     const int64_t tile = (int64_t)blockIdx.x * 4 + wave;
     if (tile >= a.ntiles) return;
     const uint32_t* to = a.tile_off + (size_t)row * (a.ntiles + 1);
-    if (to[tile + 1] == to[tile]) return;   // nothing of the segment in this tile
-    const SegTest st(a, row);
     const uint32_t* bm = a.bitmap + (size_t)row * a.bm_words;
-    RowLoader<DT, true> ld(a.g, a.ld, a.d, row);
-    const float w = a.srow[row].weight;
     const int64_t w0 = tile * (TILE / 32) + lane * 2;
-    uint2 m = w0 < a.bm_words ? *(const uint2*)(bm + w0) : make_uint2(0u, 0u);
+    const uint2 m = w0 < a.bm_words ? *(const uint2*)(bm + w0) : make_uint2(0u, 0u);
+    const SRow sr = a.srow[row];
+    if (to[tile + 1] == to[tile]) return;   // nothing of the segment in this tile
+    const SegTest st(sr);
+    RowLoader<DT, true> ld(a.g, a.ld, a.d, row);
+    const float w = sr.weight;
     uint64_t bits = (uint64_t)m.y << 32 | m.x;
     // f(position, fp32 bits, ordinal) for the lane's entries in order, the loads of eight of them in flight (a run of equal entries
     // fills whole lanes: one load at a time, 64 in a row)
@@ -1471,8 +1635,8 @@ __global__ __launch_bounds__(256) void k_se_write(StopkArgs a) {
 template <int DT>
 static mlmc_status launch_bins(const mlmc_plan_t* pl, const StopkArgs& a, bool message, hipStream_t st) {
     const int M = pl->M;
-    // The rows are read three times, and the message's entries once more: what the last cache (256 MB) holds is best left there.  compress, us, plain reads /
-    // past the cache, s = d / 100: 1 row of 4e6 fp32 (16 MB) 118 / 125, 8 of 5e6 (160 MB) 197 / 209, 8 of 1.1e7 bf16 (176 MB) 258 / 267, 8 of 8388608 fp32 (268 MB) 268 / 276,
+    // The rows are read twice, and the message's entries once or twice more: what the last cache (256 MB) holds is best left there.  compress, us, plain reads /
+    // past the cache, with a third read, s = d / 100: 1 row of 4e6 fp32 (16 MB) 118 / 125, 8 of 5e6 (160 MB) 197 / 209, 8 of 1.1e7 bf16 (176 MB) 258 / 267, 8 of 8388608 fp32 (268 MB) 268 / 276,
     // 8 of 9e6 (288 MB) 309 / 312 (s = d / 1000: 322 / 323), 8 of 1e7 (320 MB) 336 / 334, 8 of 2.3e7 bf16 (368 MB) 471 / 462, 8 of 11689512 fp32 (374 MB) 380 / 369.
     const bool stream = (int64_t)M * a.d * (DT == MLMC_F32 ? 4 : 2) > ((int64_t)288 << 20);
     {
@@ -1492,8 +1656,11 @@ static mlmc_status launch_bins(const mlmc_plan_t* pl, const StopkArgs& a, bool m
     else MLMC_LAUNCH(K_SE_COUNT, st, k_se_count<DT, false><<<dim3(a.se_wgs, M), SE_THREADS, 0, st>>>(a));
     MLMC_LAUNCH(K_SE_SCAN, st, k_se_reduce<<<dim3(SE_BLOCKS, M), 256, 0, st>>>(a));
     MLMC_LAUNCH(K_SE_SCAN, st, k_se_scan<<<dim3(SE_BLOCKS, M), 256, 0, st>>>(a));
-    if (stream) MLMC_LAUNCH(K_SE_SPLIT, st, k_se_split<DT, true><<<dim3(a.se_wgs, M), SE_THREADS, 0, st>>>(a));
-    else MLMC_LAUNCH(K_SE_SPLIT, st, k_se_split<DT, false><<<dim3(a.se_wgs, M), SE_THREADS, 0, st>>>(a));
+    const dim3 sgrid(a.se_wgs, M);
+    if (stream && message) MLMC_LAUNCH(K_SE_SPLIT, st, k_se_split<DT, true, true><<<sgrid, SE_THREADS, 0, st>>>(a));
+    else if (message) MLMC_LAUNCH(K_SE_SPLIT, st, k_se_split<DT, false, true><<<sgrid, SE_THREADS, 0, st>>>(a));
+    else if (stream) MLMC_LAUNCH(K_SE_SPLIT, st, k_se_split<DT, true, false><<<sgrid, SE_THREADS, 0, st>>>(a));
+    else MLMC_LAUNCH(K_SE_SPLIT, st, k_se_split<DT, false, false><<<sgrid, SE_THREADS, 0, st>>>(a));
     MLMC_LAUNCH(K_SE_ZONE, st, k_se_zone<<<dim3(a.L - 1 + (a.L + 255 + SZ_THREADS - 1) / SZ_THREADS, M), SZ_THREADS, 0, st>>>(a));
     {
         const int64_t cap = 512 / M > 0 ? 512 / M : 1;   // about two workgroups per CU: nearly always they find nothing to do

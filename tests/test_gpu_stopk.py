@@ -198,3 +198,30 @@ def test_stopk_draw_at_the_edges_of_its_stretches(L):
     G = np.stack([np.ones(L), np.zeros(L), np.r_[1e6, np.full(L - 1, 1e-6)], 1.0 + rng.random(L)]).astype(np.float32)
     print(f"stopk draw L={L}", flush=True)
     _run_and_check(G, 1, steps=(0, 1, 2, 3) if L < 1000 else (0, 1))
+
+
+@pytest.mark.parametrize("what,M,d,s", [
+    ("heavy", 16, 24_581, 50),        # one entry in a coarse bin carries most of a row: the forecast of the drawn level misses now and then
+    ("heavy", 3, 8_192, 4_096),       # two levels
+    ("loud", 2, 300_001, 300),        # the top segments lie in a few tiles, which are read whole
+    ("normal", 2, 70_001, 23_334),    # three levels: a third of every tile
+    ("normal", 4, 40_961, 41),        # a last block of one entry
+    ("nan", 2, 20_011, 20),           # sums that are no numbers
+])
+def test_stopk_forecast_of_the_drawn_segment(what, M, d, s):
+    """Messages whose entries the second read has marked, partly marked or not marked at all."""
+    rng = np.random.default_rng(d + s)
+    G = rng.standard_normal((M, d)).astype(np.float32)
+    if what == "heavy":
+        G = (np.tan(np.pi * (rng.random((M, d)) - 0.5)) ** 3).astype(np.float32)
+    elif what == "loud":
+        G[:, : d // 50] *= 1e4
+    print(f"stopk forecast {what} M={M} d={d} s={s}", flush=True)
+    if what == "nan":   # refused by the status word, and ended all the same
+        G[0, 5], G[1, 7] = np.nan, np.inf
+        plan = P.Plan(P.MLMC_STOPK, M, d, P.MLMC_F32, [s], None)
+        P.mlmc_compress_topk(plan, to_device(G), seed=1, step=1)
+        torch.cuda.synchronize()
+        assert plan.status() & P.MLMC_DEV_NONFINITE
+        return
+    _run_and_check(G, s, steps=(0, 1, 2, 3))
