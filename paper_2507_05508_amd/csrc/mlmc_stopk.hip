@@ -486,8 +486,8 @@ static mlmc_status launch_stopk(const mlmc_plan_t* pl, const StopkArgs& a, bool 
 //                 leaves a bit per four entries and only those are looked at, in place of a third read of the rows (73 -> 13 us, the second one 121 -> 119
 //                 with what the forecast and the marks cost it, 11)
 // Two reads of the rows and about 10 bytes per entry of other traffic against 4 x 24 bytes and more for the sort of pairs:
-// 8 rows of 1.17e7 fp32 entries at 1000 levels, compress + aggregate: 2788 -> 430 us; with the forecast and one addition per entry in the second read
-// 401 -> 341.  The line at SE_LMAX levels is where the
+// 8 rows of 1.17e7 fp32 entries at 1000 levels, compress + aggregate: 2788 -> 430 us; with the forecast, one addition per entry in the second read
+// and zones of one boundary ranked in one bucket 401 -> 325.  The line at SE_LMAX levels is where the
 // class of a bin and the list cursors of a zone per boundary still fit LDS beside the map and the sums.
 constexpr int SE_CB = 8192;             // coarse buckets: key >> SE_CSHIFT
 constexpr int SE_CSHIFT = 18;
@@ -1020,16 +1020,20 @@ __global__ __launch_bounds__(SE_THREADS) void k_se_split(StopkArgs a) {
     }
 }
 
-// One workgroup per zone of up to SE_ZCAP entries.  Keys of a zone differ in their low `shift` bits only.  They are put in order in
-// LDS: 256 buckets of the zone's key range, then a thread orders its bucket by insertion (a few keys); where a bucket holds many,
-// all keys by a bitonic sort, which takes three times as long.
+// One workgroup per zone of up to SE_ZCAP entries.  Keys of a zone differ in their low `shift` bits only; they are counted in 256 buckets of the zone's key range.
+// One boundary, as most zones have: it lies in one bucket, whose few keys are ranked; every other key is on one side of it by its bucket.
+// More of them, or a crowded bucket: the keys are put in order in LDS, a bucket by a thread by insertion (a few keys); where a bucket holds many,
+// all keys by a bitonic sort, which takes three times as long.  Bound by the LDS latency of those steps: 8 rows of 1.17e7 entries, 1000 levels, all in order
+// 37 us, one boundary without it 22 (of the 15 saved nearly all were insertions: reads and writes of LDS that wait for one another).
 constexpr int SZ_THREADS = 256;
 constexpr uint32_t SZ_FEW = 32;
 __global__ __launch_bounds__(SZ_THREADS) void k_se_zone(StopkArgs a) {
     __shared__ uint32_t s_k[SE_ZCAP];
     __shared__ uint32_t s_h[256];
     __shared__ uint32_t s_scan[SZ_THREADS / 64 + 1];
-    __shared__ uint32_t s_crowd;
+    __shared__ uint32_t s_crowd, s_fill;
+    __shared__ uint32_t s_cut[3];                     // the bucket of the one boundary, keys before it, in it; then the boundary's key, keys above it, and with its equals
+    __shared__ uint32_t s_sums[SZ_THREADS / 64][6];   // per wave: squares by 16 bits, above the key and of all
     const int row = blockIdx.y, tid = threadIdx.x;
     if ((int)blockIdx.x >= a.L - 1) {   // the last workgroups of a row: sums of the regions to their bands
         const int g = ((int)blockIdx.x - (a.L - 1)) * SZ_THREADS + tid;
@@ -1052,6 +1056,16 @@ __global__ __launch_bounds__(SZ_THREADS) void k_se_zone(StopkArgs a) {
     const uint32_t n = zn.n;
     if (n > (uint32_t)SE_ZCAP) return;   // k_se_wide
     const uint32_t* src = a.se_list + (size_t)row * a.d + zn.off;
+    const uint32_t s = (uint32_t)(a.s < a.d ? a.s : a.d);
+    const int esh = se_exp_shift(zn.lo);
+    // part u lies in band t0 + u (from 1)
+    auto part_from = [&](uint32_t u) -> uint32_t { return u ? (zn.t0 + u - 1u) * s - zn.cum : 0u; };
+    auto part_to = [&](uint32_t u) -> uint32_t { return u < zn.nb ? (zn.t0 + u) * s - zn.cum : n; };
+    auto part_add = [&](uint32_t u, uint64_t lo, uint64_t hi) {
+        unsigned long long* wide = a.se_big + ((size_t)row * a.L + (zn.t0 + u - 1u)) * SE_WORDS;
+        se_add(wide, lo, esh);
+        se_add(wide, hi, esh + 32);
+    };
     {
         constexpr int PER = SE_ZCAP / SZ_THREADS;
         const uint32_t dsh = zn.shift > 8u ? zn.shift - 8u : 0u;
@@ -1063,7 +1077,7 @@ __global__ __launch_bounds__(SZ_THREADS) void k_se_zone(StopkArgs a) {
             my[i] = at < n ? src[at] : 0u;   // a zone holds no zeros
         }
         s_h[tid] = 0;
-        if (tid == 0) s_crowd = 0;
+        if (tid == 0) s_crowd = s_fill = 0;
         __syncthreads();
 #pragma unroll
         for (int i = 0; i < PER; ++i)
@@ -1074,7 +1088,60 @@ __global__ __launch_bounds__(SZ_THREADS) void k_se_zone(StopkArgs a) {
         const uint32_t start = block_excl_scan<SZ_THREADS>(c, s_scan, all);
         s_h[tid] = start;
         if (c > SZ_FEW) s_crowd = 1u;
+        const uint32_t r1 = part_from(1u);   // keys inside the first boundary, 1 .. n - 1
+        if (start < r1 && r1 <= start + c) { s_cut[0] = (uint32_t)tid; s_cut[1] = start; s_cut[2] = c; }
         __syncthreads();
+        if (zn.nb == 1u && s_cut[2] <= 64u) {   // uniform
+            const uint32_t b = s_cut[0], before = s_cut[1], in = s_cut[2];
+#pragma unroll
+            for (int i = 0; i < PER; ++i)
+                if (my[i] && digit(my[i]) == b) s_k[atomicAdd(&s_fill, 1u)] = my[i];
+            __syncthreads();
+            if (wave == 0) {   // the key of rank r1 - 1
+                const uint32_t x = lane < in ? s_k[lane] : 0u;
+                uint32_t above = 0, upto = 0;
+                for (uint32_t i = 0; i < in; ++i) {
+                    const uint32_t y = (uint32_t)__builtin_amdgcn_readlane((int)x, (int)i);
+                    above += y > x;
+                    upto += y >= x;
+                }
+                if (lane < in && before + above < r1 && r1 <= before + upto) { s_cut[0] = x; s_cut[1] = before + above; s_cut[2] = before + upto; }   // equal keys agree
+            }
+            __syncthreads();
+            const uint32_t tau = s_cut[0];
+            uint32_t v[6] = {0, 0, 0, 0, 0, 0};
+#pragma unroll
+            for (int i = 0; i < PER; ++i)
+                if ((uint32_t)(i * SZ_THREADS) < n && my[i]) {
+                    const uint64_t sq = sig_square(my[i]);
+                    const uint32_t p0 = (uint32_t)sq & 0xFFFFu, p1 = (uint32_t)(sq >> 16) & 0xFFFFu, p2 = (uint32_t)(sq >> 32);   // 2048 of them: 27 bits
+                    const bool in0 = my[i] > tau;
+                    v[0] += in0 ? p0 : 0u;
+                    v[1] += in0 ? p1 : 0u;
+                    v[2] += in0 ? p2 : 0u;
+                    v[3] += p0;
+                    v[4] += p1;
+                    v[5] += p2;
+                }
+#pragma unroll
+            for (int i = 0; i < 6; ++i) {
+                v[i] = wave_incl_scan(v[i]);
+                if (lane == 63) s_sums[wave][i] = v[i];
+            }
+            __syncthreads();
+            if (tid < 2) {   // a part each
+                uint64_t t[6];
+#pragma unroll
+                for (int i = 0; i < 6; ++i) t[i] = (uint64_t)s_sums[0][i] + s_sums[1][i] + s_sums[2][i] + s_sums[3][i];
+                const uint32_t q = r1 - s_cut[1];   // equal keys inside
+                const uint64_t sq = sig_square(tau);
+                const uint64_t in0 = q * sq + t[0] + (t[1] << 16) + (t[2] << 32);             // at most 2048 squares: 59 bits
+                const uint64_t all0 = t[3] + (t[4] << 16) + (t[5] << 32);
+                part_add((uint32_t)tid, tid ? all0 - in0 : in0, 0u);
+                if (tid == 0) a.se_thr[(size_t)row * (a.L + 1) + zn.t0] = make_uint2(tau, s_cut[2] == r1 ? SE_ALL : q);
+            }
+            return;
+        }
         if (s_crowd == 0u) {   // uniform
 #pragma unroll
             for (int i = 0; i < PER; ++i)
@@ -1109,8 +1176,6 @@ __global__ __launch_bounds__(SZ_THREADS) void k_se_zone(StopkArgs a) {
             }
         }
     }
-    const uint32_t s = (uint32_t)(a.s < a.d ? a.s : a.d);
-    const int esh = se_exp_shift(zn.lo);
     for (uint32_t u = tid; u < zn.nb; u += SZ_THREADS) {
         const uint32_t r = (zn.t0 + u) * s - zn.cum;   // 1 .. n - 1 keys of the zone are inside
         const uint32_t tau = s_k[r - 1u];
@@ -1126,14 +1191,6 @@ __global__ __launch_bounds__(SZ_THREADS) void k_se_zone(StopkArgs a) {
         }
         a.se_thr[(size_t)row * (a.L + 1) + zn.t0 + u] = make_uint2(tau, q);
     }
-    // part u lies in band t0 + u (from 1)
-    auto part_from = [&](uint32_t u) -> uint32_t { return u ? (zn.t0 + u - 1u) * s - zn.cum : 0u; };
-    auto part_to = [&](uint32_t u) -> uint32_t { return u < zn.nb ? (zn.t0 + u) * s - zn.cum : n; };
-    auto part_add = [&](uint32_t u, uint64_t lo, uint64_t hi) {
-        unsigned long long* wide = a.se_big + ((size_t)row * a.L + (zn.t0 + u - 1u)) * SE_WORDS;
-        se_add(wide, lo, esh);
-        se_add(wide, hi, esh + 32);
-    };
     if (s <= 128u) {   // many short parts: a thread each (a wave needs 1.5 us to add up its lanes, whatever the part's length)
         for (uint32_t u = tid; u <= zn.nb; u += SZ_THREADS) {
             uint64_t lo = 0, hi = 0;
