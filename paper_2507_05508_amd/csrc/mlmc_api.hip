@@ -160,6 +160,7 @@ static void fill_topk_args(const mlmc_plan_t* pl, TopkArgs& a, const void* g, in
     a.c16_slice = pl->c16_slice;
     if (pl->off_c16_list) {
         a.c16_list = (uint32_t*)(w + pl->off_c16_list);
+        if (pl->off_c16_mark) a.c16_mark = (uint64_t*)(w + pl->off_c16_mark);
         a.c16_cnt = (uint4*)(w + pl->off_c16_cnt);
         a.c16_pre = (uint4*)(w + pl->off_c16_pre);
     }
@@ -585,6 +586,14 @@ mlmc_status mlmc_plan(mlmc_plan_t** plan, int kind, int M, int64_t d, int in_dty
         // 147 / 149, 101 / 117, but 440 / 423, adaptive 152 / 180, 138 / 165, 180 / 207, 135 / 200, 568 / 698, of one value, all of which may be in the message, 433 / 632.
         // Shorter slices: always faster (32 of 2000001 117 / 136 and 94 / 97).  So the line is where the stretches begin to gain with fixed p, not the best one for every row.
         if (pl->c16_slice >= (1 << 18)) {
+            // A forecast of the message (k_c16_sample) costs some 30 us and a tenth of the first read, and spares most of the second one, which below this size
+            // partly comes from the last cache.  Pass with the aggregate, 12 levels, us, without / with it, rows of many scales, adaptive: 8 of 11689512 161 / 167, 4 of 30000001
+            // 211 / 217, 1 of 1.24e8 253 / 266, 2 of 7e7 231 / 234, 32 of 4000001 227 / 215, 4 of 50000001 323 / 308, 16 of 25557032 535 / 459, 4 of 1.24e8 (16 levels) 575 / 484; rows of one
+            // distribution, fixed p: 4 of 50000001 256 / 230, 4 of 1.2e8 552 / 453.
+            if ((int64_t)M * d >= 160000000) {
+                pl->off_c16_mark = off;
+                off = align_up(off + sizeof(uint64_t) * (TILE / 512) * (size_t)pl->ntiles * M, 256);
+            }
             pl->off_c16_list = off;
             off = align_up(off + sizeof(uint32_t) * TILE * (size_t)pl->ntiles * M, 256);
             pl->off_c16_cnt = off;

@@ -1,6 +1,7 @@
 // Top-k MLMC of 16-bit rows on gfx950.  A 16-bit row has at most 2^15 magnitudes: one read that counts them gives every rank threshold,
 // every band's exact sum of squares and, slice by slice, where the message of a slice begins, so that a second read writes it.
 //
+//   k_c16_sample, k_c16_forecast   large plans: which magnitudes the message will need, from a sample
 //   k_c16_hist    first read: counts of a slice of a row in LDS, one workgroup per slice                      [mlmc_count16.h]
 //   k_c16_reduce  per magnitude: the row's total and, short slices, the entries in the slices before each slice
 //   k_c16_scan    per row: threshold keys and how many of their equals are inside, norms (Lemma 3.4), level draw
@@ -13,13 +14,228 @@
 
 namespace mlmc {
 
+// ---------------------------------------------------------------------------------------------------
+// The forecast of a row's message, so that the one read that every entry takes part in can mark what the message will need (a bit per eight entries: the
+// rows' scales differ from stretch to stretch, and most lines of a row have nothing of the drawn band) and the second read leaves out the rest.
+// k_c16_sample counts one block of 1024 entries in 32 by the upper 13 bits of the magnitudes, in up to 64 parts a row;
+// k_c16_forecast, a workgroup per row, takes thresholds and norms from the sample, draws the level as the row will (adaptive: all levels within one per cent
+// of the whole of where the drawn word falls) and leaves a window of magnitudes that holds its band and its base band, sampling errors allowed for.
+// What it misses costs a read (k_c16_mark), nothing else.  4 rows of 1.24e8 entries, 16 levels, adaptive: 10 + 19 us and 166 -> 176 for the first read,
+// the second 182 -> 56 (28 to 92 by the levels drawn, 8 of 48 rows with bands of a thirtieth or more); whole pass 575 -> 484.
+constexpr int C16_CB = 8192, C16_CSHIFT = 2;   // a sampled counter: four magnitudes
+constexpr int C16_SAMPLE = 5;
+constexpr int C16_PARTS = 64;                  // at most: one workgroup adds them up
+__global__ __launch_bounds__(512) void k_c16_sample(TopkArgs a) {
+    __shared__ __align__(16) uint32_t s_h[C16_CB];
+    __shared__ uint32_t s_occ[8];
+    const int row = blockIdx.y, tid = threadIdx.x;
+    const uint32_t lane = lane_id(), wave = (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6);
+    for (int i = tid; i < C16_CB / 4; i += 512) ((uint4*)s_h)[i] = make_uint4(0, 0, 0, 0);
+    if (tid < 8) s_occ[tid] = 0u;
+    __syncthreads();
+    const uint16_t* g = (const uint16_t*)a.g + (int64_t)row * a.ld;
+    const int64_t nblk = a.d >> 10, first = ((int64_t)1 << C16_SAMPLE) >> 1, ns = nblk > first ? ((nblk - first - 1) >> C16_SAMPLE) + 1 : 0;   // whole blocks
+    auto count = [&](uint32_t w) {
+        atomicAdd(&s_h[(w >> C16_CSHIFT) & (uint32_t)(C16_CB - 1)], 1u);
+        atomicAdd(&s_h[(w >> (16 + C16_CSHIFT)) & (uint32_t)(C16_CB - 1)], 1u);
+    };
+    constexpr int U = 4;   // blocks in flight
+    for (int64_t i = (int64_t)blockIdx.x * 8 + wave; i < ns; i += (int64_t)gridDim.x * 8 * U) {   // uniform
+        u32x4_b16 v[U][2];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t b = i + (int64_t)gridDim.x * 8 * u;
+            const uint16_t* p = g + ((((b < ns ? b : i) << C16_SAMPLE) + first) << 10) + lane * 8;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) v[u][h] = *(const u32x4_b16*)(p + 512 * h);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (i + (int64_t)gridDim.x * 8 * u >= ns) break;   // uniform
+            uint32_t other = 0;
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) other |= (v[u][h][q] ^ v[u][0][0]) | (v[u][h][q] ^ (v[u][0][0] << 16 | v[u][0][0] >> 16));
+            if ((other & 0x7FFF7FFFu) == 0u) {   // sixteen times one magnitude: rows that are mostly zero
+                atomicAdd(&s_h[(v[u][0][0] >> C16_CSHIFT) & (uint32_t)(C16_CB - 1)], 16u);
+                continue;
+            }
+#pragma unroll
+            for (int h = 0; h < 2; ++h) { count(v[u][h].x); count(v[u][h].y); count(v[u][h].z); count(v[u][h].w); }
+        }
+    }
+    __syncthreads();
+    // exponents that occur: 32 counters, eight lanes
+    uint4* part = (uint4*)(a.c16_part + ((size_t)row * (a.c16_wgs + 1) + blockIdx.x) * C16_KEYS);
+#pragma unroll
+    for (int it = 0; it < C16_CB / 4 / 512; ++it) {
+        const int i = it * 512 + tid;
+        const uint4 v = ((const uint4*)s_h)[i];
+        const uint64_t m = __ballot((v.x | v.y | v.z | v.w) != 0u);
+        const bool on = ((m >> (lane & 56u)) & 0xFFull) != 0u;
+        if (on) part[i] = v;
+        if (on && (lane & 7u) == 0u) atomicOr(&s_occ[i >> 8], 1u << ((i >> 3) & 31));
+    }
+    __syncthreads();
+    if (tid < 8) a.c16_occ[((size_t)row * a.c16_wgs + blockIdx.x) * 8 + tid] = s_occ[tid];
+}
+
+__global__ __launch_bounds__(1024) void k_c16_forecast(TopkArgs a) {
+    __shared__ __align__(16) uint32_t s_bin[C16_CB];
+    __shared__ uint32_t s_occ[C16_PARTS * 8], s_any[8];
+    __shared__ uint8_t s_exp[256];                           // the exponents that occur
+    __shared__ uint32_t s_scan[17];
+    __shared__ double s_w[16], s_above[1024];                // squares of the sampled entries above a thread's
+    __shared__ uint4 s_r[TMAX];                              // sampled ranks of the boundaries; ranks that are surely above and below them
+    __shared__ uint32_t s_hi[TMAX], s_lo[TMAX];              // magnitudes there
+    __shared__ double s_e[TMAX];                             // squares of the sampled entries above a boundary
+    const int row = blockIdx.x, tid = threadIdx.x, L = a.L, W = a.c16_wgs < C16_PARTS ? a.c16_wgs : C16_PARTS;
+    const uint32_t lane = lane_id(), wave = (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6);
+    if (tid < 8) s_any[tid] = 0u;
+    for (int i = tid; i < C16_CB / 4; i += 1024) ((uint4*)s_bin)[i] = make_uint4(0, 0, 0, 0);
+    __syncthreads();
+    for (int i = tid; i < W * 8; i += 1024) {
+        const uint32_t o = a.c16_occ[(size_t)row * a.c16_wgs * 8 + i];
+        s_occ[i] = o;
+        if (o) atomicOr(&s_any[i & 7], o);
+    }
+    __syncthreads();
+    uint32_t nexp = 0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const uint32_t o = s_any[i];
+        if (tid < 32 && ((o >> tid) & 1u)) s_exp[nexp + __popc(o & ((1u << tid) - 1u))] = (uint8_t)(32 * i + tid);
+        nexp += __popc(o);
+    }
+    __syncthreads();
+    // eight lanes an exponent of a part, eight exponents a wave, eight of these in flight
+    const uint32_t nch = (nexp + 7u) / 8u, items = nch * (uint32_t)W;
+    for (uint32_t i0 = wave; i0 < items; i0 += 16 * 8) {   // uniform
+        uint4 v[8];
+        uint32_t at[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const uint32_t i = i0 + 16u * u < items ? i0 + 16u * u : 0u, s = i / nch, j = (i - s * nch) * 8u + (lane >> 3), e = s_exp[j < nexp ? j : 0];
+            at[u] = e * 32 + (lane & 7u) * 4;
+            v[u] = make_uint4(0, 0, 0, 0);
+            if (i0 + 16u * u < items && j < nexp && ((s_occ[s * 8 + (e >> 5)] >> (e & 31)) & 1u))   // (the others are not written)
+                v[u] = *(const uint4*)(a.c16_part + ((size_t)row * (a.c16_wgs + 1) + s) * C16_KEYS + at[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            if (v[u].x) atomicAdd(&s_bin[at[u]], v[u].x);
+            if (v[u].y) atomicAdd(&s_bin[at[u] + 1], v[u].y);
+            if (v[u].z) atomicAdd(&s_bin[at[u] + 2], v[u].z);
+            if (v[u].w) atomicAdd(&s_bin[at[u] + 3], v[u].w);
+        }
+    }
+    __syncthreads();
+    const int bin0 = C16_CB - 8 * (tid + 1);   // this thread's eight counters, descending with the thread
+    uint32_t n[8], sum = 0;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const uint4 v = ((const uint4*)(s_bin + bin0))[h];
+        n[4 * h] = v.x; n[4 * h + 1] = v.y; n[4 * h + 2] = v.z; n[4 * h + 3] = v.w;
+    }
+    auto square = [](uint32_t bin) -> double {
+        const double v = (double)__uint_as_float((bin << C16_CSHIFT | 2u) << 16);
+        return v * v;
+    };
+    double en = 0.0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        if (n[i]) en += square((uint32_t)(bin0 + i)) * (double)n[i];
+        sum += n[i];
+    }
+    uint32_t total;
+    const uint32_t before = block_excl_scan<1024>(sum, s_scan, total);
+    double inc = en;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const double u = __shfl_up(inc, o, 64);
+        if (lane >= (uint32_t)o) inc += u;
+    }
+    if (lane == 63) s_w[wave] = inc;
+    {   // s_bin[p]: entries of the counters 0 .. p in descending order
+        uint32_t upto = before;
+#pragma unroll
+        for (int i = 7; i >= 0; --i) { upto += n[i]; s_bin[8 * tid + 7 - i] = upto; }   // (block_excl_scan's barriers lie behind the reads)
+    }
+    if (tid <= L) {
+        const double f = (double)total / (double)a.d;
+        const uint32_t r = (uint32_t)((double)a.k[tid] * f);
+        const float m = 5.0f * sqrtf((float)r) + 8.0f;
+        s_r[tid] = make_uint4(r, (float)r > m ? r - (uint32_t)m : 0u, r + (uint32_t)m, 0u);
+        s_hi[tid] = (uint32_t)C16_KEYS - 1u;
+        s_lo[tid] = 0u;
+    }
+    __syncthreads();
+    double e0 = 0.0, all = 0.0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) {
+        if (w == (int)wave) e0 = all;
+        all += s_w[w];
+    }
+    s_above[tid] = e0 + inc - en;
+    __syncthreads();
+    if (tid < 3 * (L + 1)) {   // a rank each: its counter by bisection
+        const int t = tid % (L + 1), what = tid / (L + 1);
+        const uint32_t r = what == 0 ? s_r[t].x : what == 1 ? s_r[t].y : s_r[t].z;
+        if (r >= total) {
+            if (what == 0) s_e[t] = all;
+        } else {
+            int lo = 0, hi = C16_CB - 1;   // the first with more than r entries up to it
+            while (lo < hi) {
+                const int mid = (lo + hi) >> 1;
+                if (s_bin[mid] > r) hi = mid;
+                else lo = mid + 1;
+            }
+            const uint32_t bin = (uint32_t)(C16_CB - 1 - lo);
+            if (what == 0) {
+                double e = s_above[lo >> 3];
+                uint32_t at = (lo >> 3) ? s_bin[(lo & ~7) - 1] : 0u;
+                for (int p = lo & ~7; p < lo; ++p) {
+                    if (s_bin[p] != at) e += square((uint32_t)(C16_CB - 1 - p)) * (double)(s_bin[p] - at);
+                    at = s_bin[p];
+                }
+                s_e[t] = r > at ? e + square(bin) * (double)(r - at) : e;
+            } else if (what == 1) {
+                if (r) s_hi[t] = bin << C16_CSHIFT | ((1u << C16_CSHIFT) - 1u);
+            } else {
+                s_lo[t] = bin << C16_CSHIFT;
+            }
+        }
+    }
+    __syncthreads();
+    if (wave == 0) {
+        const int l = (int)lane < L ? (int)lane : L - 1;
+        const double d2 = s_e[l + 1] - s_e[l];
+        const double p = level_p(a, row, d2 > 0.0 ? sqrt(d2) : 0.0, l);
+        const uint32_t x = philox_word0(a.seed, a.step, (uint32_t)row), eps = a.draw_mode == 3 ? 42949673u : 0u;
+        const int l0 = wave_draw_from_p(p, L, x > eps ? x - eps : 0u), l1 = wave_draw_from_p(p, L, x < ~eps ? x + eps : ~0u);
+        if (lane == 0) {
+            RowInfo* ri = a.rinfo + row;
+            ri->mark_lo = s_lo[l1];
+            ri->mark_hi = s_hi[l0 - 1];
+            ri->mark_base = a.k[0] > 0 ? s_lo[0] : (uint32_t)C16_KEYS;
+            ri->mark_on = s_r[l1].x - s_r[l0 - 1].x <= total / 8u ? 1 : 0;   // wider bands have entries in most lines
+        }
+    }
+}
+
 // One workgroup per (slice, row), one per CU: the counters fill its LDS.  Bound by the read.
 __global__ __launch_bounds__(C16_THREADS) void k_c16_hist(TopkArgs a) {
     __shared__ __align__(16) uint32_t s_h[C16_LDS];
     const int row = blockIdx.y;
     if (row == 0 && blockIdx.x == 0 && threadIdx.x == 0) *a.dev_status = 0;   // nothing of this launch reports through it
     const int64_t i0 = (int64_t)blockIdx.x * a.c16_slice, i1 = i0 + a.c16_slice < a.d ? i0 + a.c16_slice : a.d;
-    count16_slice((const uint16_t*)a.g + (int64_t)row * a.ld, i0, i1, s_h);
+    const uint16_t* g = (const uint16_t*)a.g + (int64_t)row * a.ld;
+    const RowInfo* ri = a.rinfo + row;
+    if (a.c16_mark && ri->mark_on)   // uniform
+        count16_slice<true>(g, i0, i1, s_h, C16Window{ri->mark_lo, ri->mark_hi - ri->mark_lo + 1u, ri->mark_base}, a.c16_mark + ((size_t)row * a.ntiles * TILE + i0) / 512);
+    else
+        count16_slice<false>(g, i0, i1, s_h, C16Window{}, nullptr);
     // Blocks of C16_BLOCK magnitudes that occur, and which those are: the values of a row have some twenty of the 256 exponents.
     __shared__ uint32_t s_occ[C16_KEYS / C16_BLOCK / 32];
     if (threadIdx.x < C16_KEYS / C16_BLOCK / 32) s_occ[threadIdx.x] = 0u;
@@ -186,8 +402,6 @@ __global__ __launch_bounds__(1024) void k_c16_scan(TopkArgs a) {
 // A step of the message kernels: C16_STEP entries, a wave takes 1024 consecutive ones in two loads, a lane 8 of either half.
 constexpr int C16_STEP = 16 * C16_THREADS;
 constexpr int C16_WAVES = C16_THREADS / 64;
-typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ u16x2 both16(int32_t x) { const u16x2 r = {(uint16_t)x, (uint16_t)x}; return r; }
 // Per half, in its top bit (the other bits hold anything): key < bound, keys below 2^15, bounds up to it.
 __device__ __forceinline__ uint32_t below16(u16x2 key, u16x2 bound) { return __builtin_bit_cast(uint32_t, (u16x2)(key - bound)); }
 __device__ __forceinline__ uint32_t in_range16(u16x2 key, u16x2 lo, u16x2 hi) { return below16(key, hi) & ~below16(key, lo); }   // lo <= key < hi
@@ -290,7 +504,7 @@ __device__ __forceinline__ void slice_state(const TopkArgs& a, int row, int s, C
 // a threshold splits them, all entries equal to it) in index order, k_c16_offsets turns the counts of the tiles into places, k_c16_expand
 // writes the message.  Waves are on their own throughout, so a row of stretches with different scales, some of which hold a hundred times as
 // many members as others, keeps no workgroup waiting: 4 rows of 1.24e8 entries in 148 stretches took 480 us with a slice per workgroup (k_c16_write),
-// and 317 with the fuller slices cut into parts after a count of 190; now 198 + 13 + 67 (1 GB at 6.3 TB/s: 158).
+// and 317 with the fuller slices cut into parts after a count of 190; this way 182 + 13 + 43, the first of them 56 where the first read has marked what is needed.
 struct C16Message {       // a row's thresholds 0, l-1, l
     uint32_t lo[3];       // keys from here on are inside whatever their position
     uint32_t tau[3];      // the key whose entries are split (C16_KEYS: none are)
@@ -385,9 +599,102 @@ __global__ __launch_bounds__(MK_THREADS, 6) void k_c16_mark(TopkArgs a) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) v[q] = __builtin_nontemporal_load((const u32x4_b16*)(g + tile * TILE + half * 2048 + q * 512 + lane * 8));
     };
-    u32x4_b16 va[4], vb[4];
     int64_t tile = (int64_t)blockIdx.x * MK_WAVES + wave;
-    if (tile < nfull) {
+    const RowInfo* ri = a.rinfo + row;
+    if (a.c16_mark && ri->mark_on && lo2 >= (int32_t)ri->mark_lo && ms.lo[1] <= ri->mark_hi + 1u && (uint32_t)lo0 >= ri->mark_base) {   // uniform
+        // The first read has marked all the candidates of the row: eight entries per mark, a lane each, in index order.
+        const uint64_t* marks = a.c16_mark + (size_t)row * a.ntiles * (TILE / 512);
+        uint16_t* place = (uint16_t*)ent;   // [2][512] the marked eights of a tile, of the next one
+        // the marks of a tile, word 2 i + h of them in lane 2 i + h
+        auto marks_at = [&](int64_t t) -> uint32_t { return ((const uint32_t*)(marks + t * 8))[lane & 15u]; };
+        // marked eights of a tile; their places, and the first 64 of them on their way
+        auto open = [&](int64_t t, uint32_t w, uint32_t par, u32x4_b16& v) -> uint32_t {
+            uint32_t c = 0;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const uint64_t m = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)w, 2 * i + 1) << 32 | (uint32_t)__builtin_amdgcn_readlane((int)w, 2 * i);
+                if (m == 0ull) continue;   // uniform
+                if ((m >> lane) & 1ull) place[par * 512u + c + mbcnt(m)] = (uint16_t)(i * 64 + (int)lane);
+                c += (uint32_t)__popcll(m);
+            }
+            wave_lds_sync();
+            v = __builtin_nontemporal_load((const u32x4_b16*)(g + t * TILE + (uint32_t)place[par * 512u + (lane < c ? lane : c - 1u)] * 8u));
+            return c;
+        };
+        for (; tile < nfull; tile += 64 * stride) {
+            // 64 of the wave's tiles at a time: a lane looks whether its tile has a mark, and settles those that have none
+            const int64_t mine = tile + (int64_t)lane * stride;
+            bool any = false;
+            if (mine < nfull) {
+                const uint4* w = (const uint4*)(marks + mine * 8);
+                uint32_t o = 0;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) { const uint4 x = w[i]; o |= x.x | x.y | x.z | x.w; }
+                any = o != 0u;
+                if (!any) cnt[mine] = make_uint4(0, 0, 0, 0);
+            }
+            uint64_t todo = __ballot(any);
+            if (todo == 0ull) continue;   // uniform
+            auto take = [&]() -> int64_t {
+                const int64_t t = tile + (int64_t)__builtin_ctzll(todo) * stride;
+                todo &= todo - 1;
+                return t;
+            };
+            u32x4_b16 v, vn = (u32x4_b16){0u, 0u, 0u, 0u};
+            int64_t t = take(), tn = t;
+            uint32_t par = 0, c = open(t, marks_at(t), 0u, v), cn = 0, wn = 0;
+            if (todo) { tn = take(); wn = marks_at(tn); }
+            while (true) {   // uniform
+                const bool more = tn != t;
+                if (more) cn = open(tn, wn, par ^ 1u, vn);
+                const int64_t ta = todo ? take() : tn;
+                if (ta != tn) wn = marks_at(ta);
+                begin(t);
+                uint32_t eq01 = 0, eq2 = 0;
+                for (uint32_t j0 = 0;; j0 += 64) {   // uniform
+                    const uint32_t b[4] = {v.x, v.y, v.z, v.w}, mine8 = place[par * 512u + (j0 + lane < c ? j0 + lane : c - 1u)];
+                    uint32_t acc = 0;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const u16x2 key = __builtin_bit_cast(u16x2, b[i] & 0x7FFF7FFFu);
+                        acc = (acc >> 2) | ((in_range16(key, f2, e2k) | ~below16(key, f0)) & 0x80008000u);
+                    }
+                    // entry e of the lane's eight: even ones from the lower halves, odd ones from the upper ones
+                    uint32_t m = j0 + lane < c ? ((acc >> 9) & 0x55u) | ((acc >> 24) & 0xAAu) : 0u;
+                    const uint32_t inc = wave_incl_scan((uint32_t)__popc(m));
+                    uint32_t at = head + inc - (uint32_t)__popc(m);
+                    while (m) {
+                        const uint32_t q = (uint32_t)__builtin_ctz(m);
+                        const uint32_t x0 = q & 2u ? b[1] : b[0], x1 = q & 2u ? b[3] : b[2], x = q & 4u ? x1 : x0;
+                        const uint32_t e = q & 1u ? x & 0xFFFF0000u : x << 16, key = e & 0x7FFF0000u;
+                        list[at] = e | (mine8 * 8u + q);
+                        eq01 += (key == t0 ? 1u : 0u) | (key == t1 ? 0x10000u : 0u);
+                        eq2 += key == t2 ? 1u : 0u;
+                        ++at;
+                        m &= m - 1u;
+                    }
+                    head += (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+                    if (j0 + 64u >= c) break;
+                    v = __builtin_nontemporal_load((const u32x4_b16*)(g + t * TILE + (uint32_t)place[par * 512u + (j0 + 64u + lane < c ? j0 + 64u + lane : c - 1u)] * 8u));
+                }
+                eq01 = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(eq01), 63);   // (at most 4096 each)
+                eq2 = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(eq2), 63);
+                e0 = eq01 & 0xFFFFu;
+                e1 = eq01 >> 16;
+                e2 = eq2;
+                end(t);
+                if (!more) break;
+                t = tn;
+                tn = ta;
+                c = cn;
+                v = vn;
+                par ^= 1u;
+                wave_lds_sync();
+            }
+        }
+        tile = nfull % stride == (int64_t)blockIdx.x * MK_WAVES + wave ? nfull : a.ntiles;
+    } else if (tile < nfull) {
+        u32x4_b16 va[4], vb[4];
         fetch(tile, 0, va);
         while (true) {   // uniform
             fetch(tile, 1, vb);
@@ -519,10 +826,16 @@ __global__ __launch_bounds__(256) void k_c16_expand(TopkArgs a) {
         uint32_t E[3] = {c.y, c.z, c.w};
         const uint32_t* list = a.c16_list + ((size_t)row * a.ntiles + tile) * TILE;
         constexpr int U = 4;
-        for (uint32_t i0 = 0; i0 < n; i0 += 64 * U) {
-            uint32_t e[U];
+        uint32_t e[U], next[U];
+        auto fetch = [&](uint32_t i0, uint32_t (&v)[U]) {
 #pragma unroll
-            for (int u = 0; u < U; ++u) { const uint32_t i = i0 + 64u * u + lane; e[u] = list[i < n ? i : n - 1u]; }
+            for (int u = 0; u < U; ++u) { const uint32_t i = i0 + 64u * u + lane; v[u] = list[i < n ? i : n - 1u]; }
+        };
+        fetch(0, next);
+        for (uint32_t i0 = 0; i0 < n; i0 += 64 * U) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) e[u] = next[u];
+            if (i0 + 64 * U < n) fetch(i0 + 64 * U, next);   // uniform; full tiles are many rounds, one after the other
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const bool on = i0 + 64u * u + lane < n;
@@ -766,8 +1079,14 @@ __global__ __launch_bounds__(C16_THREADS) void k_c16_write(TopkArgs a) {
 }
 
 // message == false: norms only.
-mlmc_status topk16_run(const mlmc_plan_t* pl, const TopkArgs& a, bool message, hipStream_t st) {
+mlmc_status topk16_run(const mlmc_plan_t* pl, const TopkArgs& args, bool message, hipStream_t st) {
+    TopkArgs a = args;
+    if (!message) a.c16_mark = nullptr;
     const dim3 grid(pl->c16_wgs, pl->M);
+    if (a.c16_mark) {
+        MLMC_LAUNCH(K_HIST, st, k_c16_sample<<<dim3(pl->c16_wgs < C16_PARTS ? pl->c16_wgs : C16_PARTS, pl->M), 512, 0, st>>>(a));
+        MLMC_LAUNCH(K_SCAN, st, k_c16_forecast<<<pl->M, 1024, 0, st>>>(a));
+    }
     MLMC_LAUNCH(K_C16_HIST, st, k_c16_hist<<<grid, C16_THREADS, 0, st>>>(a));
     const dim3 rgrid(C16_KEYS / C16_BLOCK, pl->M);
 #define MLMC_C16_REDUCE(G, PER)                                                                                          \
@@ -785,7 +1104,9 @@ mlmc_status topk16_run(const mlmc_plan_t* pl, const TopkArgs& a, bool message, h
     if (a.c16_list) {
         int64_t mw = (pl->ntiles + MK_WAVES - 1) / MK_WAVES;
         const int64_t cap = 2048 / pl->M > 0 ? 2048 / pl->M : 1;
-        const dim3 mgrid((unsigned)(mw < cap ? mw : cap), pl->M), egrid((unsigned)(mw < 4 * cap ? mw : 4 * cap), pl->M);
+        // with a forecast some rows have little to do: their workgroups make room for those of the others (4 rows of 1.24e8 entries 70 -> 56 us on average)
+        const int64_t mcap = a.c16_mark ? 4 * cap : cap;
+        const dim3 mgrid((unsigned)(mw < mcap ? mw : mcap), pl->M), egrid((unsigned)(mw < 4 * cap ? mw : 4 * cap), pl->M);
         MLMC_LAUNCH(K_C16_MARK, st, k_c16_mark<<<mgrid, MK_THREADS, 0, st>>>(a));
         const int64_t span = (pl->ntiles + 65535) / 65536 * 1024;   // at most 64 workgroups a row: what they add up in front of their tiles stays small
         MLMC_LAUNCH(K_C16_OFFSETS, st, k_c16_offsets<<<dim3((unsigned)((pl->ntiles + span - 1) / span), pl->M), 1024, 0, st>>>(a, span));

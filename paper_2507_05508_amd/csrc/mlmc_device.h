@@ -389,19 +389,19 @@ __device__ __forceinline__ int wave_draw_from_p(double p, int L, uint32_t x) {
     const uint64_t below = __ballot(lane < L && (uint64_t)x < T);   // the last level's lane is always among them
     return (int)__builtin_ctzll(below) + 1;
 }
+// Probability of level l + 1 (l < L, a lane's own; a whole wave); norm: the level's, where this call computes them.
+__device__ __forceinline__ double level_p(const TopkArgs& a, int row, double norm, int l) {
+    const int L = a.L;
+    if (a.draw_mode == 0) return a.p_fixed[l];
+    if (a.draw_mode == 1) return a.p_dev[(size_t)row * L + l];
+    const double n = a.draw_mode == 2 ? a.p_dev[(size_t)row * L + l] : norm;
+    double tot = 0.0;
+    for (int i = 0; i < L; ++i) tot = __dadd_rn(tot, lane_f64(n, i));
+    return tot == 0.0 ? __ddiv_rn(1.0, (double)L) : __ddiv_rn(n, tot);
+}
 __device__ inline int draw_row(const TopkArgs& a, int row, const double* norms_row) {   // returns the level
     const int L = a.L, lane = (int)lane_id(), l = lane < L ? lane : L - 1;
-    double p;
-    if (a.draw_mode == 0) {
-        p = a.p_fixed[l];
-    } else if (a.draw_mode == 1) {
-        p = a.p_dev[(size_t)row * L + l];
-    } else {
-        const double n = a.draw_mode == 2 ? a.p_dev[(size_t)row * L + l] : norms_row[l];
-        double tot = 0.0;
-        for (int i = 0; i < L; ++i) tot = __dadd_rn(tot, lane_f64(n, i));
-        p = tot == 0.0 ? __ddiv_rn(1.0, (double)L) : __ddiv_rn(n, tot);
-    }
+    const double p = level_p(a, row, a.draw_mode == 3 ? norms_row[l] : 0.0, l);
     const uint32_t x = philox_word0(a.seed, a.step, (uint32_t)row);
     const int level = wave_draw_from_p(p, L, x);
     const double pl = lane_f64(p, level - 1);

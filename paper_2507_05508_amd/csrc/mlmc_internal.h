@@ -88,6 +88,8 @@ struct RowInfo {
     uint32_t draw_x;
     uint32_t status;          // short rows: MLMC_DEV_* bits of the row
     uint32_t topkey;          // counted 16-bit rows: the largest magnitude
+    uint32_t mark_lo, mark_hi, mark_base;   // their forecast: magnitudes lo .. hi and from base on are marked by the first read,
+    int32_t mark_on;          // if 1
     uint32_t occ[8];          // the exponents that occur, a bit each
     uint32_t zone_top[ZMAX], zone_bot[ZMAX];   // first-digit buckets of the zone, top >= bot, both inclusive
     uint32_t zone_off[ZMAX], zone_cap[ZMAX];   // its candidate list inside the row's candidate buffer
@@ -154,6 +156,7 @@ struct TopkArgs {
     int32_t c16_wgs;         // slices per row
     int64_t c16_slice;       // entries of a slice, a multiple of TILE
     uint32_t* c16_list;      // [M][ntiles][TILE] entries that may be in the message: bits << 16 | offset in the tile (null: one workgroup per slice writes it)
+    uint64_t* c16_mark;      // [M][ntiles][8] a bit per eight entries: the message may need them (null: no forecast)
     uint4* c16_cnt;          // [M][ntiles] of every tile: its list's length, entries equal to the split keys in it
     uint4* c16_pre;          // the same with the entries equal to the split keys before it
     // level draw (Alg. 2 / Alg. 3 "Sample l"): mode 0 p_fixed, 1 dev p, 2 dev norms, 3 norms computed by this call
@@ -331,7 +334,7 @@ struct mlmc_plan_s {
     size_t off_rtn_sums, off_rtn_part, off_rtn_total;   // Round-to-Nearest plans
     int rtn_wgs;              // workgroups per row that count magnitudes (0: not counted)
     int64_t rtn_slice;
-    size_t off_c16_part, off_c16_occ, off_c16_list, off_c16_cnt, off_c16_pre;   // Top-k plans of 16-bit rows
+    size_t off_c16_part, off_c16_occ, off_c16_mark, off_c16_list, off_c16_cnt, off_c16_pre;   // Top-k plans of 16-bit rows
     int c16_wgs;              // slices per row (0: not counted)
     int64_t c16_slice;
     size_t off_row_part;

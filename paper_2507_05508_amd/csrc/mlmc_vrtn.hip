@@ -260,7 +260,7 @@ __global__ __launch_bounds__(C16_THREADS) void k_rtn_hist(BitsArgs a) {
     __shared__ __align__(16) uint32_t s_h[C16_LDS];
     const int row = blockIdx.y;
     const int64_t i0 = (int64_t)blockIdx.x * a.rtn_slice, i1 = i0 + a.rtn_slice < a.d ? i0 + a.rtn_slice : a.d;
-    count16_slice((const uint16_t*)a.g + (int64_t)row * a.ld, i0, i1, s_h);
+    count16_slice<false>((const uint16_t*)a.g + (int64_t)row * a.ld, i0, i1, s_h, C16Window{}, nullptr);
     uint4* part = (uint4*)(a.rtn_part + ((size_t)row * gridDim.x + blockIdx.x) * C16_KEYS);
     for (int i = threadIdx.x; i < C16_KEYS / 4; i += C16_THREADS) part[i] = ((const uint4*)s_h)[i];
 }

@@ -166,3 +166,37 @@ def test_entries_past_the_capacity_are_not_written(M, d):
     assert plan.status() == P.MLMC_DEV_CAPACITY
     assert torch.equal(cut.idx[:cap], whole.idx[:cap]) and torch.equal(cut.val[:cap], whole.val[:cap])
     assert bool((cut.idx[cap:] == -7).all())
+
+
+@pytest.mark.parametrize("how", ["adaptive", "fixed", "given"])
+@pytest.mark.parametrize("M,d", [(616, (1 << 18) + 4096 * 2 + 2500), (640, 1 << 18)])
+def test_forecast_marks_of_narrow_bands(M, d, how):
+    """Messages of a sixteenth of a row or less, whose entries the first read marks: rows whose sampled blocks (one of 1024 entries in 32) tell the band,
+    rows with all their large entries outside of these blocks or nearly all zero, split thresholds, bands in a few tiles; every way the level is drawn."""
+    kinds = ["normal", "few", "loud", "zeros", "normal", "tiny"]
+    few = np.concatenate([_rows(k, 1, d, 23 + i) for i, k in enumerate(kinds)])
+    block = np.arange(d) >> 10
+    few[4, (block % 32) == 16] = 0          # the sample has nothing of the row
+    few[5, 77_777] = W.f32_to_bf16_bits(np.array([3e38], np.float32))[0]   # one entry is all of the first band's norm
+    g = to_device(few).repeat(-(-M // len(kinds)), 1)[:M].contiguous()
+    picks = list(range(6)) + [M - 1]
+    for ladder in ([d >> 12, d >> 11, d >> 9, d >> 7, d >> 5], [0, 3, d // 100, d // 40]):
+        L = len(ladder) - 1
+        p = O.geometric_p(L) if how == "fixed" else None
+        plan = P.Plan(P.MLMC_TOPK, M, d, P.MLMC_BF16, ladder, p)
+        plan.ws.fill_(0xFF)
+        norms = P.mlmc_level_norms(plan, g) if how == "given" else None
+        for step in range(2):
+            print(f"marks {how} {M}x{d} {ladder} step={step}", flush=True)
+            msg = P.mlmc_compress_topk(plan, g, seed=5, step=step, p=norms, p_is_norms=norms is not None)
+            torch.cuda.synchronize()
+            assert plan.status() == P.MLMC_DEV_NONFINITE
+            off, level = msg.row_off.cpu().numpy(), msg.level.cpu().numpy()
+            assert np.array_equal(np.diff(off), [ladder[0] + ladder[l] - ladder[l - 1] for l in level])
+            for i in picks:
+                want = O.compress_topk_row(few[i % len(kinds)], ladder, p, 5, step, i)
+                assert level[i] == want["level"]
+                assert np.array_equal(u32(msg.idx[off[i]:off[i + 1]]), want["idx"]), (i, step)
+                assert np.array_equal(u32(msg.val[off[i]:off[i + 1]]), want["val"].view(np.uint32)), (i, step)
+                bounds = np.searchsorted(want["idx"], np.arange(plan.num_tiles + 1, dtype=np.int64) * P.MLMC_TILE)
+                assert np.array_equal(u32(msg.tile_off[i]), bounds.astype(np.uint32))
