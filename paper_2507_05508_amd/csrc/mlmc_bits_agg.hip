@@ -91,6 +91,106 @@ struct AggRow {          // per row, in LDS
     int32_t w, fl;       // fixed point: width of the level field; floating point: and digits of the level; codes: width of the drawn and of the previous code
 };
 
+template <int PK, bool BASE>
+__device__ __forceinline__ AggRow agg_row(const AggBitsArgs& a, int r) {
+    const BitsArgs& b = a.b;
+    const int F0 = BASE ? b.F[0] : 0;
+    int lev = a.level[r];
+    lev = lev < 1 ? 1 : (lev > b.L ? b.L : lev);
+    const double pl = b.p_fixed[lev - 1];
+    AggRow q;
+    q.c0 = 0.0f;
+    q.w = b.F[lev] - b.F[lev - 1];
+    q.fl = b.F[lev];
+    if (PK == 2) {          // c_0 = fp32(2c / D_0); the coefficient comes with the message
+        const double c = key_to_double((uint32_t)a.scale_exp[2 * r] & 0x7FFFFFFFu);
+        if (BASE) q.c0 = (float)__ddiv_rn(__dmul_rn(2.0, c), (double)((1 << F0) - 1));
+        q.cl = __uint_as_float((uint32_t)a.scale_exp[2 * r + 1]);
+        q.w = b.F[lev];                          // width of the drawn level's code
+        q.fl = lev > 1 ? b.F[lev - 1] : 0;       // width of the previous level's code when it is sent
+        q.np = F0 + q.fl + q.w;
+    } else if (PK == 1) {   // the level's weight fp32(1 / p_l)
+        q.cl = pl == 0.0 ? 0.0f : (float)__ddiv_rn(1.0, pl);
+        q.np = 9 + F0 + q.w;
+    } else {
+        if (b.vmx) {        // the scale field carries the largest entry v: c_0 = fp32(v 2^-F_0), c_l = fp32(v 2^-F_l / p_l)
+            const double vd = key_to_double((uint32_t)a.scale_exp[r] & 0x7FFFFFFFu);
+            if (BASE) q.c0 = (float)ldexp(vd, -F0);
+            q.cl = pl == 0.0 ? 0.0f : (float)__ddiv_rn(ldexp(vd, -b.F[lev]), pl);
+        } else {
+            const int e = a.scale_exp[r];
+            if (BASE) q.c0 = (float)ldexp(1.0, e - F0);
+            q.cl = pl == 0.0 ? 0.0f : (float)__ddiv_rn(ldexp(1.0, e - b.F[lev]), pl);
+        }
+        q.np = 1 + F0 + q.w;
+    }
+    return q;
+}
+
+// The same sum, a wave a word of 64 entries of every plane and an entry a lane: for rows that leave most of the chip idle with 2048 entries a wave (4 rows of 100003, fixed point: 8.4 -> 3.9 us).
+// A lane loads a plane's word, four rows at a time, whatever the rows' levels are; the words then choose the bits of the lanes' entries.
+template <int PK, bool BASE>
+__global__ __launch_bounds__(EX_THREADS) void k_agg_words(AggBitsArgs a, const uint64_t* __restrict__ planes, float* __restrict__ out, float* __restrict__ x) {
+    extern __shared__ __align__(16) unsigned char s_dyn_words[];
+    AggRow* s_row = (AggRow*)s_dyn_words;
+    const BitsArgs& b = a.b;
+    const int F0 = BASE ? b.F[0] : 0;
+    const uint32_t lane = lane_id();
+    const int64_t word = (int64_t)blockIdx.x * (EX_THREADS / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint64_t* mine = planes + (size_t)((int)lane < b.nplanes ? lane : 0u) * b.nwords + (word < b.nwords ? word : b.nwords - 1);
+    constexpr int U = 4;
+    uint64_t v[U];
+    auto fetch = [&](int r0) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = mine[(size_t)(r0 + u < b.M ? r0 + u : b.M - 1) * b.nplanes * b.nwords];
+    };
+    fetch(0);
+    for (int r = threadIdx.x; r < b.M; r += EX_THREADS) s_row[r] = agg_row<PK, BASE>(a, r);
+    __syncthreads();
+    if (word >= b.nwords) return;   // uniform
+    float acc = 0.0f;
+    for (int r0 = 0; r0 < b.M; r0 += U) {   // rows in worker order
+        uint64_t cur[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) cur[u] = v[u];
+        if (r0 + U < b.M) fetch(r0 + U);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (r0 + u >= b.M) break;   // uniform
+            const AggRow q = s_row[r0 + u];
+            const int np = __builtin_amdgcn_readfirstlane(q.np);
+            uint32_t y = 0;   // bit p: the entry's bit of plane p
+            for (int p = 0; p < np; ++p) {   // uniform
+                const uint64_t m = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(cur[u] >> 32), p) << 32 |
+                                   (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)cur[u], p);
+                y |= __builtin_amdgcn_inverse_ballot_w64(m) ? 1u << p : 0u;
+            }
+            float add;
+            if (PK == 0) {
+                const uint32_t n = y >> 1;
+                if (!BASE) add = __fmul_rn((float)n, q.cl);
+                else add = __fadd_rn(__fmul_rn((float)(n & ((1u << F0) - 1u)), q.c0), __fmul_rn((float)(n >> F0), q.cl));
+                add = __uint_as_float(__float_as_uint(add) | y << 31);
+            } else if (PK == 1) {
+                const uint32_t se = y << 31 | ((y >> 1) & 0xFFu) << 23, lev = (y >> 9 >> F0) << (23 - q.fl);
+                const float res = __fsub_rn(__uint_as_float(se | lev), __uint_as_float(se));
+                const uint32_t base = BASE ? ((y >> 9) & ((1u << F0) - 1u)) << (23 - F0) : 0u;
+                add = __fadd_rn(__uint_as_float(se | base), __fmul_rn(res, q.cl));
+            } else {
+                const int pw = q.fl > 0 ? q.fl : F0;         // level 1: the previous code is the base code
+                const int32_t D = (1 << q.w) - 1, Dp = pw > 0 ? (1 << pw) - 1 : 1;
+                const int32_t cur_n = __builtin_amdgcn_sbfe((int)y, F0 + q.fl, q.w);
+                const int32_t prev_n = pw > 0 ? __builtin_amdgcn_sbfe((int)y, q.fl > 0 ? F0 : 0, pw) : 0;
+                add = __fmul_rn((float)(int32_t)((uint32_t)cur_n * (uint32_t)Dp - (uint32_t)prev_n * (uint32_t)D), q.cl);
+                if (BASE) add = __fadd_rn(__fmul_rn((float)(int32_t)__builtin_amdgcn_sbfe((int)y, 0, F0), q.c0), add);
+            }
+            acc = __fadd_rn(acc, add);
+        }
+    }
+    const int64_t j = word * 64 + lane;
+    if (j < b.d) finish_entry(a.alpha, acc, out, a.eta, x, j);
+}
+
 // The values of w <= 24 planes, v[0] the least significant, as numbers: u[e] for the lane's 32 elements.  G: groups of eight planes.
 template <int G>
 __device__ __forceinline__ uint32_t assemble(const uint32_t (&r)[3][8], int i, int k) {
@@ -107,38 +207,7 @@ __global__ __launch_bounds__(EX_THREADS, 4) void k_agg_planes(AggBitsArgs a, con
     AggRow* s_row = (AggRow*)(s_dyn_planes + (EX_THREADS / 64) * EX_ELEMS * 4);
     const BitsArgs& b = a.b;
     const int F0 = BASE ? b.F[0] : 0;
-    for (int r = threadIdx.x; r < b.M; r += EX_THREADS) {
-        int lev = a.level[r];
-        lev = lev < 1 ? 1 : (lev > b.L ? b.L : lev);
-        const double pl = b.p_fixed[lev - 1];
-        AggRow q;
-        q.c0 = 0.0f;
-        q.w = b.F[lev] - b.F[lev - 1];
-        q.fl = b.F[lev];
-        if (PK == 2) {          // c_0 = fp32(2c / D_0); the coefficient comes with the message
-            const double c = key_to_double((uint32_t)a.scale_exp[2 * r] & 0x7FFFFFFFu);
-            if (BASE) q.c0 = (float)__ddiv_rn(__dmul_rn(2.0, c), (double)((1 << F0) - 1));
-            q.cl = __uint_as_float((uint32_t)a.scale_exp[2 * r + 1]);
-            q.w = b.F[lev];                          // width of the drawn level's code
-            q.fl = lev > 1 ? b.F[lev - 1] : 0;       // width of the previous level's code when it is sent
-            q.np = F0 + q.fl + q.w;
-        } else if (PK == 1) {   // the level's weight fp32(1 / p_l)
-            q.cl = pl == 0.0 ? 0.0f : (float)__ddiv_rn(1.0, pl);
-            q.np = 9 + F0 + q.w;
-        } else {
-            if (b.vmx) {        // the scale field carries the largest entry v: c_0 = fp32(v 2^-F_0), c_l = fp32(v 2^-F_l / p_l)
-                const double vd = key_to_double((uint32_t)a.scale_exp[r] & 0x7FFFFFFFu);
-                if (BASE) q.c0 = (float)ldexp(vd, -F0);
-                q.cl = pl == 0.0 ? 0.0f : (float)__ddiv_rn(ldexp(vd, -b.F[lev]), pl);
-            } else {
-                const int e = a.scale_exp[r];
-                if (BASE) q.c0 = (float)ldexp(1.0, e - F0);
-                q.cl = pl == 0.0 ? 0.0f : (float)__ddiv_rn(ldexp(1.0, e - b.F[lev]), pl);
-            }
-            q.np = 1 + F0 + q.w;
-        }
-        s_row[r] = q;
-    }
+    for (int r = threadIdx.x; r < b.M; r += EX_THREADS) s_row[r] = agg_row<PK, BASE>(a, r);
     __syncthreads();
     const uint32_t lane = lane_id(), wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t blk = (int64_t)blockIdx.x * (EX_THREADS / 64) + wave;
@@ -637,13 +706,22 @@ mlmc_status message_bits(const mlmc_plan_t* pl, const int32_t* level, unsigned l
 }
 
 // ---------------------------------------------------------------------------------------------------
+// By words while that many waves still find room: us, 2048 entries a wave / words: fixed point 4 rows of 100003 8.5 / 4.3, 4 of 300001 8.0 / 4.6, 8 of 300001 8.3 / 6.4, 8 of 500001
+// 7.9 / 11.4 (two words a wave); floating point (up to 32 planes) 4 of 300001 7.0 / 6.2, 8 of 300001 7.7 / 9.0, 32 of 100003 9.2 / 11.9; largest entry 4 of 300001 8.7 / 5.5.
+static bool extract_by_words(const mlmc_plan_t* pl, const BitsArgs& a) {
+    return a.sample_shift == 0 && (int64_t)pl->M * pl->d <= 3 << 19;
+}
 mlmc_status bits_compress(const mlmc_plan_t* pl, const BitsArgs& a0, hipStream_t st) {
     BitsArgs a = a0;
     if (a.flt) MLMC_LAUNCH(K_DRAW, st, k_bits_prep<<<1, 1024, 0, st>>>(a));
     const dim3 egrid = extract_grid(pl);
+    const bool words = extract_by_words(pl, a);
+    const dim3 wgrid((unsigned)((a.nwords + EW_WORDS * (EX_THREADS / 64) - 1) / (EW_WORDS * (EX_THREADS / 64))), pl->M);
 #define MLMC_EXTRACT_B(ID, DT, REDO, KIND)                                                                               \
     do {                                                                                                                \
-        if (a.F[0] == 0) MLMC_LAUNCH(ID, st, k_bits_extract<DT, REDO, KIND, false><<<egrid, EX_THREADS, 0, st>>>(a));    \
+        if (words && a.F[0] == 0) MLMC_LAUNCH(ID, st, k_bits_extract_words<DT, KIND, false><<<wgrid, EX_THREADS, 0, st>>>(a)); \
+        else if (words) MLMC_LAUNCH(ID, st, k_bits_extract_words<DT, KIND, true><<<wgrid, EX_THREADS, 0, st>>>(a));      \
+        else if (a.F[0] == 0) MLMC_LAUNCH(ID, st, k_bits_extract<DT, REDO, KIND, false><<<egrid, EX_THREADS, 0, st>>>(a));    \
         else MLMC_LAUNCH(ID, st, k_bits_extract<DT, REDO, KIND, true><<<egrid, EX_THREADS, 0, st>>>(a));                 \
     } while (0)
 #define MLMC_EXTRACT(ID, REDO, KIND)                                                                                     \
@@ -691,9 +769,16 @@ mlmc_status agg_bits(const mlmc_plan_t* pl, const BitsArgs& b, const int32_t* le
     const int64_t nblk = (b.d + EX_ELEMS - 1) / EX_ELEMS;
     const unsigned grid = (unsigned)((nblk + EX_THREADS / 64 - 1) / (EX_THREADS / 64));
     const size_t lds = (size_t)(EX_THREADS / 64) * EX_ELEMS * 4 + sizeof(AggRow) * (size_t)b.M;
+    // By words: us, 2048 entries a wave / words: fixed point 4 rows of 100003 8.4 / 3.9, 8 of 300001 9.6 / 6.2, 8 of 500001 8.7 / 7.8, 8 of 1000001 9.1 / 11.3; floating point
+    // 4 of 300001 8.2 / 7.1, 8 of 300001 11.7 / 10.7, 32 of 100003 32.6 / 18.2: the rows come one after the other either way, so their length decides.
+    const bool words = b.d <= (b.flt || b.rtn ? 1 << 18 : 1 << 19);
+    const unsigned wgrid = (unsigned)((b.nwords + EX_THREADS / 64 - 1) / (EX_THREADS / 64));
+    const size_t wlds = sizeof(AggRow) * (size_t)b.M;
 #define MLMC_AGG(PK)                                                                                                     \
     do {                                                                                                                \
-        if (b.F[0] == 0) MLMC_LAUNCH(K_AGG_BITS, st, k_agg_planes<PK, false><<<grid, EX_THREADS, lds, st>>>(a, planes, out, x)); \
+        if (words && b.F[0] == 0) MLMC_LAUNCH(K_AGG_BITS, st, k_agg_words<PK, false><<<wgrid, EX_THREADS, wlds, st>>>(a, planes, out, x)); \
+        else if (words) MLMC_LAUNCH(K_AGG_BITS, st, k_agg_words<PK, true><<<wgrid, EX_THREADS, wlds, st>>>(a, planes, out, x)); \
+        else if (b.F[0] == 0) MLMC_LAUNCH(K_AGG_BITS, st, k_agg_planes<PK, false><<<grid, EX_THREADS, lds, st>>>(a, planes, out, x)); \
         else MLMC_LAUNCH(K_AGG_BITS, st, k_agg_planes<PK, true><<<grid, EX_THREADS, lds, st>>>(a, planes, out, x));       \
     } while (0)
     if (b.rtn) MLMC_AGG(2);

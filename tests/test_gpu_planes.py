@@ -112,3 +112,21 @@ def test_planes_of_grids_rounded_up_to_the_dies(kind, M, d):
         n = want["planes"].shape[0]
         assert int(msg.level[i]) == want["level"]
         assert np.array_equal(planes[:n], want["planes"]) and bool((planes[n:] == 0x5555).all())
+
+
+@pytest.mark.parametrize("kind", list(KINDS))
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("M,d,off", [(6, 262_144, 0), (6, 262_145, 1), (3, 524_288, 1), (3, 524_289 + 2046, 3)])
+def test_planes_on_both_sides_of_the_words_limit(kind, bf16, M, d, off):
+    """The last sizes that go by words and the first ones that go by blocks of 2048 (extraction: 1572864 entries in all; aggregate: 2^18 or 2^19 a row)."""
+    rng = np.random.default_rng(d)
+    G = (rng.standard_normal((M, d)) * np.exp(rng.uniform(-6, 3, size=(M, 1)))).astype(np.float32)
+    G[:, :: 7] *= np.float32(1e-3)
+    G[0, 11] = 0.0
+    if bf16:
+        G = W.f32_to_bf16_bits(G)
+    base = to_device(G)
+    g = torch.as_strided(torch.zeros(M * (d + 11) + 8, dtype=base.dtype, device="cuda"), (M, d), (d + 11, 1), off)
+    g.copy_(base)
+    for n, F in enumerate(KINDS[kind][1][:2]):
+        _one(kind, F, G, g, n + off, 0.5, f"offset {off}")
