@@ -52,7 +52,7 @@ static mlmc_status static_scratch_of_current_device(void** out) {
 // ---- per-kernel HIP-event timing (off by default; not thread safe) ---------------------------------
 bool g_prof_on = false;
 static const char* const k_names[K_NUM] = {
-    "k_zero", "k_hist", "k_scan", "k_main", "k_fhist", "k_finish", "k_finish_rank", "redo_pass", "k_norms", "k_bits_prep", "k_msgplan", "k_filter", "k_write",
+    "k_zero", "k_hist", "k_scan", "k_main", "k_fhist", "k_finish", "k_finish_rank", "redo_pass", "k_norms", "k_bits_prep", "k_msgplan", "k_filter" /* or k_pick */, "k_write",
     "k_bits_smax", "k_bits_extract", "k_bits_redo", "k_agg_bits", "k_tileoff", "k_agg_sparse", "k_message_bits", "k_rtn_norms", "k_rtn_draw",
     "k_rs_hist", "k_rs_scan", "k_rs_scatter", "k_sb_norms", "k_sb_draw", "k_sb_mark", "k_sb_offsets", "k_sb_write", "k_se_count", "k_se_scan",
     "k_se_split", "k_se_zone", "k_row_select", "k_row_write", "k_c16_hist", "k_c16_reduce", "k_c16_scan", "k_c16_mark", "k_c16_offsets", "k_c16_write"};
@@ -150,6 +150,10 @@ static void fill_topk_args(const mlmc_plan_t* pl, TopkArgs& a, const void* g, in
     a.cand = (uint2*)(w + pl->off_cand);
     a.cand2 = (uint2*)(w + pl->off_cand2);
     a.cand_priv = (uint2*)(w + pl->off_cand_priv);
+    if (pl->off_marks) {
+        a.marks = (uint64_t*)(w + pl->off_marks);
+        a.mark_words = (int64_t)pl->chunks_per_row * pl->chunk / 256;
+    }
     a.priv_cnt = (uint32_t*)(w + pl->off_priv_cnt);
     a.chunk_base = (uint32_t*)(w + pl->off_chunk_base);
     a.row_order = (int32_t*)(w + pl->off_row_order);
@@ -630,6 +634,15 @@ mlmc_status mlmc_plan(mlmc_plan_t** plan, int kind, int M, int64_t d, int in_dty
         off = align_up(off + sizeof(int32_t) * (size_t)M, 256);
         pl->off_table8 = off;
         off = align_up(off + (size_t)NB1 * M, 256);
+        // Marks for the message (k_main2, k_pick) or its members in lists (k_filter)?  The marked entries are read again line by line, lists are written and read whatever
+        // the lines are: rows of many scales have most lines without a member, rows of one scale hardly any.  Up to here the rows are in the last cache and the second
+        // read costs little.  Pass, adaptive, us, lists / marks: many scales 8 of 300001 101 / 98, 32 of 1000001 211 / 200, 4 of 4000001 161 / 154, 4 of 8000001 207 / 198; one scale
+        // 4 of 300001 94 / 91, 8 of 1000001 114 / 114, 4 of 8000001 204 / 205, 1 of 33000001 237 / 244.  Larger: many scales 16 of 25557032 834 / 800, 8 of 11689512 334 / 307, but
+        // one scale 1047 / 1090 and 368 / 374, 4 of 6e7 723 / 762.
+        if (pl->csub == CSUB_MAX && (int64_t)M * d <= ((int64_t)1 << 25) && d <= ((int64_t)1 << 24)) {
+            pl->off_marks = off;
+            off = align_up(off + sizeof(uint64_t) * ((size_t)pl->chunks_per_row * pl->chunk / 256) * (size_t)M, 256);
+        }
     }
     pl->ws_bytes = off;
     if (workspace_bytes) *workspace_bytes = off;

@@ -81,8 +81,8 @@ struct RowInfo {
     uint32_t thr_jx[TMAX];    // entries equal to thr_tau with index below thr_jx are within the top k_t
     int32_t thr_zone[TMAX];   // zone that holds the threshold, or THR_*
     int32_t n_zones, level, respec, exact;
-    int32_t spec_level;       // level whose band the selection read staged for the message (0: none)
-    int32_t spec_ok;          // 1: the drawn level is spec_level, the message is assembled from the staged lists
+    int32_t spec_level, spec_last;   // levels whose bands the selection read staged (one) or marked for the message (spec_level 0: none)
+    int32_t spec_ok;          // 1: the drawn level is one of them
     MsgPlan msg;
     float weight;
     uint32_t draw_x;
@@ -137,6 +137,8 @@ struct TopkArgs {
     uint2* cand;             // [M][d] candidate lists of the zones: {fp32 bit pattern, index}
     uint2* cand2;            // [M][d] overflow lists: candidates of threshold bins too full to rank in LDS
     uint2* cand_priv;        // [M][chunks_per_row][16 waves][chunk / 8] staged {bits, offset in chunk << 6 | tag} as the waves met them
+    uint64_t* marks;         // [M][mark_words] a bit per four entries: the message may need one of them (plans of k_main2; null: members are staged)
+    int64_t mark_words;
     uint32_t* priv_cnt;      // [M][chunks_per_row][16] entries of every wave's private list
     uint32_t* chunk_base;    // [M][cchunks_per_row + 1] message entries of the row before every count chunk
     int32_t* row_order;      // [M] rows by descending message length: the order in which the message kernels take them
@@ -320,7 +322,7 @@ struct mlmc_plan_s {
     int staging;
     // workspace byte offsets
     size_t off_racc, off_hist, off_hist2, off_chunk_zcnt, off_zhist, off_zpacc, zero_bytes;  // [0, zero_bytes) is cleared per call
-    size_t off_rinfo, off_table, off_chunk_cnt, off_zcol, off_tileoff, off_norms, off_cand, off_cand2, off_cand_priv, off_priv_cnt, off_chunk_base, off_row_order, off_table8;
+    size_t off_rinfo, off_table, off_chunk_cnt, off_zcol, off_tileoff, off_norms, off_cand, off_cand2, off_cand_priv, off_priv_cnt, off_chunk_base, off_row_order, off_table8, off_marks;
     size_t ws_bytes;
     // s-segmented Top-k plans
     int64_t s;

@@ -27,6 +27,8 @@
 //                the row's place by message length (the two kernels below take the long rows first)
 //   k_filter     rows whose staged band is the drawn one: base band + drawn band (Eq. (6)) from the staged lists,
 //                ordered by index through a bitmap over the chunk
+//   k_pick       in plans of up to 2^25 entries in its place: the selection read marks the entries of the forecast bands (a bit per four)
+//                instead of staging them, and only the marked ones are read again
 //   k_write      the other rows: second read, a workgroup owns a chunk whose output offset is known
 #include <type_traits>
 
@@ -149,6 +151,8 @@ __global__ __launch_bounds__(1024) void k_scan(TopkArgs a, int exact_pass) {
     __shared__ int64_t s_k[TMAX];            // the ladder (indexed by loop variables below: kept out of the argument block)
     __shared__ uint16_t s_gexp[GMAX], s_gband[GMAX];
     __shared__ uint32_t s_bmin, s_bmax;      // occupied buckets of the (sampled) histogram
+    __shared__ uint32_t s_zt[ZMAX];          // first threshold of a zone | last one << 8
+    __shared__ int32_t s_lev1;               // last level of the forecast
 
     const int row = blockIdx.x, tid = threadIdx.x;
     RowInfo* ri = a.rinfo + row;
@@ -306,6 +310,7 @@ __global__ __launch_bounds__(1024) void k_scan(TopkArgs a, int exact_pass) {
             ri->zone_t1[tid] = z_t1;
             s_ztop[tid] = z_top;
             s_zbot[tid] = z_bot;
+            s_zt[tid] = (uint32_t)z_t0 | (uint32_t)z_t1 << 8;
         }
         if (tid <= nz) s_label[tid] = z_label;
         static_assert(RMAX <= 64, "a lane per region");
@@ -343,6 +348,7 @@ __global__ __launch_bounds__(1024) void k_scan(TopkArgs a, int exact_pass) {
     // midpoint), the same Philox word, the same inverse CDF.  The selection read stages the members of that band
     // so that the message can be assembled without a second read of the row; a wrong prediction only costs
     // that second read.
+    // (Rows whose entries are marked: all levels within 1.6 per cent of the whole of where the drawn word falls.)
     const int nz = s_nz;
     if (a.all_thresholds && a.draw_mode == 3) {
         for (int l = tid; l < (LMAX + 2) * 32; l += 1024) s_est[l] = 0.0f;
@@ -372,27 +378,34 @@ __global__ __launch_bounds__(1024) void k_scan(TopkArgs a, int exact_pass) {
             double tot = 0.0;
             for (int l = 0; l < L; ++l) tot += lane_f64(n, l);
             const double p = tot > 0.0 ? n / tot : 1.0 / (double)L;
-            const int lev_p = wave_draw_from_p(p, L, philox_word0(a.seed, a.step, (uint32_t)row));
-            if (tid == 0) s_lev = lev_p;
+            const uint32_t x = philox_word0(a.seed, a.step, (uint32_t)row), eps = a.marks ? 1u << 26 : 0u;
+            const int lev_c = wave_draw_from_p(p, L, x);
+            int lev_p = wave_draw_from_p(p, L, x > eps ? x - eps : 0u), lev_q = wave_draw_from_p(p, L, x < ~eps ? x + eps : ~0u);
+            if ((s_k[lev_q] - s_k[lev_p - 1]) * STAGE_MAX_BAND_INV > a.d) lev_p = lev_q = lev_c;   // wide ones one at a time
+            if (tid == 0) { s_lev = lev_p; s_lev1 = lev_q; }
         }
         __syncthreads();
     }
     if (tid == 0) {
         int sl = ((a.all_thresholds && a.draw_mode != 3) || !a.staging) ? 0 : s_lev;   // norms only: nothing to stage
+        int sl1 = a.all_thresholds ? s_lev1 : sl;
+        if (a.marks && exact_pass) sl = 0;   // the marks are those of the first attempt
         // a wide band is cheaper to collect by a second read: the staged lists of such a row would keep its few
         // workgroups busy long after the other rows are done
-        if (sl > 0 && (s_k[sl] - s_k[sl - 1]) * STAGE_MAX_BAND_INV > a.d) sl = 0;
+        if (sl > 0 && !a.marks && (s_k[sl] - s_k[sl - 1]) * STAGE_MAX_BAND_INV > a.d) sl = 0;
         ri->spec_level = sl;
+        ri->spec_last = sl1;
+        s_lev1 = sl1;
         ri->spec_ok = (sl > 0 && !(a.all_thresholds && a.draw_mode == 3)) ? 1 : 0;   // adaptive: decided after the draw
         s_lev = sl;
     }
     __syncthreads();
-    const int spec = s_lev;
+    const int spec = s_lev, spec1 = s_lev1;
 
     // class table: thread tid writes its 16 buckets (descending), 64 bytes.  The zone bounds of the current zone
     // index stay in registers; a thread's buckets share their exponent, so their group changes only with the zone
     // index and the group tables are written once per change.
-    uint32_t codes[16];
+    uint32_t codes[16], want = 0;   // want: bit per bucket, the message may need its entries
     int zi = 0;   // zones wholly above the current bucket
 #pragma unroll 4
     for (int z = 0; z < nz; ++z) zi += s_zbot[z] > (uint32_t)(NB1 - 1 - tid * 16) ? 1 : 0;
@@ -409,6 +422,8 @@ __global__ __launch_bounds__(1024) void k_scan(TopkArgs a, int exact_pass) {
         }
         if (zi < nz && b <= ztop_c) {
             codes[15 - i] = class_code((uint32_t)G_DUMMY, 64u + (uint32_t)zi, (uint32_t)zi, true);
+            const int t0 = (int)(s_zt[zi] & 0xFFu), t1 = (int)(s_zt[zi] >> 8);   // entries of bands t0 .. t1 + 1
+            want |= (!a.marks || (spec > 0 && (t0 == 0 || (t0 <= spec1 && t1 + 1 >= spec))) ? 1u : 0u) << (15 - i);   // (candidates are staged, whatever the message)
         } else {
             const uint32_t E = b >> 6;
             const int gid = (int)(255 - E) + zi;
@@ -417,7 +432,8 @@ __global__ __launch_bounds__(1024) void k_scan(TopkArgs a, int exact_pass) {
                 s_gexp[gid] = (uint16_t)(E ? E : 1);
                 s_gband[gid] = (uint16_t)lab_c;
             }
-            const bool member = spec > 0 && (lab_c == 0 || lab_c == spec);
+            const bool member = spec > 0 && (lab_c == 0 || (lab_c >= spec && lab_c <= spec1));
+            want |= (member ? 1u : 0u) << (15 - i);
             codes[15 - i] = class_code((uint32_t)gid, (uint32_t)zi, member ? TAG_MEMBER : 0u, member);
         }
     }
@@ -425,7 +441,7 @@ __global__ __launch_bounds__(1024) void k_scan(TopkArgs a, int exact_pass) {
         uint4* dst = (uint4*)(a.table + (size_t)row * NB1 + (NB1 - 16 - tid * 16));
 #pragma unroll
         for (int i = 0; i < 4; ++i) dst[i] = make_uint4(codes[4 * i], codes[4 * i + 1], codes[4 * i + 2], codes[4 * i + 3]);
-        // the same table in one byte per bucket (counter in bits 0..6, "stage" in bit 7), for the selection read that
+        // the same table in one byte per bucket (counter in bits 0..6, "mark" or "stage" in bit 7), for the selection read that
         // rebuilds the rest from the key: the sum group of a region is (255 - exponent) + region, the tag of a zone its index
         uint32_t w8[4];
 #pragma unroll
@@ -434,7 +450,7 @@ __global__ __launch_bounds__(1024) void k_scan(TopkArgs a, int exact_pass) {
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const uint32_t c = codes[4 * i + k];
-                w8[i] |= (((c >> 6) & 0x7Fu) | ((c & CODE_STAGE) ? 0x80u : 0u)) << (8 * k);
+                w8[i] |= (((c >> 6) & 0x7Fu) | ((want >> (4 * i + k)) & 1u) << 7) << (8 * k);
             }
         }
         *(uint4*)(a.table8 + (size_t)row * NB1 + (NB1 - 16 - tid * 16)) = make_uint4(w8[0], w8[1], w8[2], w8[3]);
@@ -727,7 +743,8 @@ constexpr int M2_CNT = 56 * 1024;                            // uint32 [M2_CSUB]
 constexpr int M2_END = M2_CNT + M2_CSUB * 128 * REP_CNT * 4;
 static_assert(M2_MISC_END <= M2_CNT && 2 * M2_END <= 160 * 1024 && M2_SUM % 16 == 0 && M2_ZCUR % 16 == 0, "LDS layout: two workgroups per CU");
 
-template <bool VEC, bool SUMS>
+// MARKS: a bit per four entries, the message may need one of them, in place of the members' list entries (k_pick).
+template <bool VEC, bool SUMS, bool MARKS>
 __global__ __launch_bounds__(M2_THREADS, 4) void k_main2(TopkArgs a) {
     __shared__ __align__(16) unsigned char lm[M2_END];
     uint32_t* s_cnt = (uint32_t*)(lm + M2_CNT);
@@ -777,16 +794,21 @@ __global__ __launch_bounds__(M2_THREADS, 4) void k_main2(TopkArgs a) {
     const uint32_t sum_lane = (uint32_t)M2_SUM + (lane & 15u) * 8u;
     uint32_t head = 0;
     uint32_t maxkey = 0;
+    const bool marking = MARKS && ri->spec_level > 0;   // uniform
+    // zone candidates (bit 6, past the end too); and the members of the forecast band (bit 7) where they are not marked: zones then have bit 7 of their own accord
+    constexpr uint32_t STAGED = MARKS ? 0x40u : 0x80u;
+    uint32_t* marks = (uint32_t*)(a.marks + (size_t)row * a.mark_words + (size_t)(c0 >> 8));   // of this workgroup's elements, two words per 256
 
     auto lookup = [&](const uint32_t (&b)[4], uint32_t (&code)[4]) {
 #pragma unroll
         for (int c = 0; c < 4; ++c) code[c] = lm[(b[c] >> B1_SHIFT) & (uint32_t)(NB1 - 1)];
     };
-    auto process = [&](const uint32_t (&b)[4], uint32_t (&code)[4], uint32_t rel0, uint32_t vmask, uint32_t cnt_base) {
+    // returns the lanes whose entries are marked
+    auto process = [&](const uint32_t (&b)[4], uint32_t (&code)[4], uint32_t rel0, uint32_t vmask, uint32_t cnt_base) -> uint64_t {
         uint32_t anys = 0;
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-            if (!((vmask >> c) & 1u)) code[c] = 0x7Fu;   // past the end: an unused zone's counter, the dummy group, not staged
+            if (!((vmask >> c) & 1u)) code[c] = 0x7Fu;   // past the end: an unused zone's counter, the dummy group, not marked
             const uint32_t key = key_of_bits(b[c]);
             const uint32_t cnt7 = code[c] & 0x7Fu;
             if (SUMS) {
@@ -800,18 +822,16 @@ __global__ __launch_bounds__(M2_THREADS, 4) void k_main2(TopkArgs a) {
             maxkey = key > maxkey ? key : maxkey;
             anys |= code[c];
         }
-        if (__ballot(anys & 0x80u)) {
+        if (__ballot(anys & STAGED)) {
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
-                const uint64_t m = __ballot(code[c] & 0x80u);
-                if (__builtin_amdgcn_inverse_ballot_w64(m)) {
-                    const uint32_t cnt7 = code[c] & 0x7Fu;
-                    const uint32_t tag = cnt7 >= 64u ? cnt7 & 63u : TAG_MEMBER;
-                    priv[head + mbcnt(m)] = make_uint2(b[c], ((rel0 + (uint32_t)c) << 6) | tag);
-                }
+                const uint64_t m = __ballot((code[c] & STAGED) && (!MARKS || ((vmask >> c) & 1u)));
+                if (__builtin_amdgcn_inverse_ballot_w64(m))
+                    priv[head + mbcnt(m)] = make_uint2(b[c], ((rel0 + (uint32_t)c) << 6) | (MARKS || code[c] & 0x40u ? code[c] & 63u : TAG_MEMBER));
                 head += (uint32_t)__popcll(m);
             }
         }
+        return MARKS ? __ballot(anys & 0x80u) : 0ull;
     };
 
     const int tpc = a.cchunk / TILE;   // tiles per count chunk
@@ -844,27 +864,39 @@ __global__ __launch_bounds__(M2_THREADS, 4) void k_main2(TopkArgs a) {
             while (gn >= 0) {   // uniform
                 const uint32_t cb = cnt_of(gc / (TILE / MAIN_GROUP));
                 const uint32_t rel0 = relh + (uint32_t)(gc * MAIN_GROUP) + lane * 4;
+                uint32_t words = 0;
 #pragma unroll
                 for (int q = 0; q < 8; ++q) {
 #pragma unroll
                     for (int c = 0; c < 4; ++c) cc[c] = cn[c];
                     lookup(buf[(q + 1) & 7], cn);
-                    process(buf[q], cc, rel0 + (uint32_t)(q * 256), 15u, cb);
+                    const uint64_t m = process(buf[q], cc, rel0 + (uint32_t)(q * 256), 15u, cb);
+                    if (MARKS) {
+                        words = write_lane((uint32_t)m, 2 * q, words);
+                        words = write_lane((uint32_t)(m >> 32), 2 * q + 1, words);
+                    }
                     gissue(gn, q, buf[q]);
                 }
+                if (marking && lane < 16) marks[gc * (MAIN_GROUP / 128) + lane] = words;
                 gc = gn;
                 gn = grab();
             }
             {
                 const uint32_t cb = cnt_of(gc / (TILE / MAIN_GROUP));
                 const uint32_t rel0 = relh + (uint32_t)(gc * MAIN_GROUP) + lane * 4;
+                uint32_t words = 0;
 #pragma unroll
                 for (int q = 0; q < 8; ++q) {
 #pragma unroll
                     for (int c = 0; c < 4; ++c) cc[c] = cn[c];
                     if (q < 7) lookup(buf[q + 1], cn);
-                    process(buf[q], cc, rel0 + (uint32_t)(q * 256), 15u, cb);
+                    const uint64_t m = process(buf[q], cc, rel0 + (uint32_t)(q * 256), 15u, cb);
+                    if (MARKS) {
+                        words = write_lane((uint32_t)m, 2 * q, words);
+                        words = write_lane((uint32_t)(m >> 32), 2 * q + 1, words);
+                    }
                 }
+                if (marking && lane < 16) marks[gc * (MAIN_GROUP / 128) + lane] = words;
             }
         }
         const int tbase = ngroups * MAIN_GROUP;   // up to eight pieces of 256 elements are left, the last one ragged: wave w takes piece w
@@ -875,7 +907,8 @@ __global__ __launch_bounds__(M2_THREADS, 4) void k_main2(TopkArgs a) {
 #pragma unroll
             for (int c = 0; c < 4; ++c) if (c >= nv) buf[0][c] = 0u;
             lookup(buf[0], cc);
-            process(buf[0], cc, relh + (uint32_t)pos + lane * 4, (1u << nv) - 1u, cnt_of(pos / TILE));
+            const uint64_t m = process(buf[0], cc, relh + (uint32_t)pos + lane * 4, (1u << nv) - 1u, cnt_of(pos / TILE));
+            if (marking && lane < 2) marks[pos / 128 + lane] = lane ? (uint32_t)(m >> 32) : (uint32_t)m;
         }
     }
     if (__ballot(maxkey >= 0x7F800000u) && lane == 0) atomicOr(a.dev_status, MLMC_DEV_NONFINITE);
@@ -1933,7 +1966,7 @@ __global__ __launch_bounds__(256) void k_norms(TopkArgs a) {
     if (tid < 64 && a.draw_mode == 3) {
         draw_row(a, row, s_norm);
         RowInfo* rw = a.rinfo + row;
-        if (tid == 0) rw->spec_ok = (rw->spec_level > 0 && rw->spec_level == rw->level) ? 1 : 0;
+        if (tid == 0) rw->spec_ok = (rw->spec_level > 0 && rw->spec_level <= rw->level && rw->level <= rw->spec_last) ? 1 : 0;
     }
 }
 
@@ -2332,6 +2365,150 @@ __global__ __launch_bounds__(FL_THREADS) void k_filter(TopkArgs a) {
     batched_loop<8, 64>(64u * FL_KEEP, cnt, lane, [&](uint32_t i) { return priv[i]; }, [&](uint32_t, uint2 e) { emit(e); });
 }
 
+// The same for rows whose entries the selection read has marked (k_main2: a bit per four entries of the forecast bands and of the zones that touch them):
+// only those are read again (4 rows of 8000001 entries, many scales, 12 levels: 38 us with either, but the
+// selection read 47 -> 42 without the members' list entries, and a second band can be marked where the draw is close, second reads 9 -> 4).  One workgroup per (count chunk, row), PK_SPAN elements at a time: their marks become a list of the marked fours in index order, a
+// thread takes PK_U of them in a row, and one scan over the workgroup gives the places.
+constexpr int PK_THREADS = 256;
+constexpr int PK_SPAN = 4 * TILE;    // sixteen marks a thread
+constexpr int PK_U = 2;
+static_assert(PK_SPAN / 4 / 16 == PK_THREADS, "sixteen marks a thread");
+template <bool VEC>
+__global__ __launch_bounds__(PK_THREADS) void k_pick(TopkArgs a) {
+    __shared__ uint16_t s_id[PK_SPAN / 4];
+    __shared__ uint2 s_out[PK_THREADS * PK_U * 4];
+    __shared__ uint32_t s_tot[2][PK_THREADS / 64], s_pos[PK_SPAN / TILE];
+    const int row = a.row_order[blockIdx.y], chunk_id = blockIdx.x, tid = threadIdx.x;
+    const uint32_t lane = lane_id(), wave = (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6);
+    const RowInfo* ri = a.rinfo + row;
+    const int nc = a.cchunks_per_row;
+    const int64_t c0 = (int64_t)chunk_id * a.cchunk, c1 = c0 + a.cchunk < a.d ? c0 + a.cchunk : a.d;
+    const uint16_t* marks = (const uint16_t*)(a.marks + (size_t)row * a.mark_words);   // sixteen fours each
+    auto marks_at = [&](int64_t sb) -> uint32_t { return sb + (int64_t)tid * 64 < c1 ? marks[(sb >> 6) + tid] : 0u; };
+    uint32_t ahead = marks_at(c0);   // all of it on its way before anything is looked at
+    const MsgPlan mp = ri->msg;
+    uint32_t run = a.chunk_base[(size_t)row * (nc + 1) + chunk_id];
+    const uint32_t next_base = a.chunk_base[(size_t)row * (nc + 1) + chunk_id + 1];
+    if (!ri->spec_ok) return;   // k_write reads all of the row again
+    Thr3 th;
+    // keys from lo on are inside whatever their index (k_write's signed tau plus one); "cut" marks a threshold whose equal keys are split by index
+    uint32_t lo[3];
+    bool any_cut = false;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        th.tau[i] = mp.tau[i];
+        th.jx[i] = mp.jx[i];
+        lo[i] = th.jx[i] == JX_ALL || th.tau[i] > 0x7FFFFFFFu ? th.tau[i] : th.tau[i] + 1u;
+        lo[i] = (uint32_t)__builtin_amdgcn_readfirstlane((int)lo[i]);
+        any_cut = any_cut || (th.jx[i] != 0u && th.jx[i] != JX_ALL);
+    }
+    const uint32_t width = lo[1] - lo[2];
+    const float w = mp.weight;
+    const RowLoader<MLMC_F32, VEC> ld(a.g, a.ld, a.d, row);
+    uint32_t* tile_off = a.tile_off + (size_t)row * (a.ntiles + 1);
+    uint32_t* idx = a.idx + mp.rowstart;
+    float* val = a.val + mp.rowstart;
+    const int64_t room = a.capacity - mp.rowstart;
+    uint32_t par = 0;
+    // exclusive scan over the workgroup, one barrier
+    auto scan = [&](uint32_t v, uint32_t& total) -> uint32_t {
+        const uint32_t inc = wave_incl_scan(v);
+        if (lane == 63) s_tot[par][wave] = inc;
+        __syncthreads();
+        uint32_t before = 0;
+        total = 0;
+#pragma unroll
+        for (int k = 0; k < PK_THREADS / 64; ++k) {
+            const uint32_t t = s_tot[par][k];
+            if (k < (int)wave) before += t;
+            total += t;
+        }
+        par ^= 1u;
+        return before + inc - v;
+    };
+    for (int64_t sb = c0; sb < c1; sb += PK_SPAN) {
+        uint32_t m = ahead, n;
+        if (sb + PK_SPAN < c1) ahead = marks_at(sb + PK_SPAN);   // uniform
+        uint32_t at = scan((uint32_t)__popc(m), n);   // (its barrier lies behind the last reads of s_id and s_pos)
+        if ((tid & 63) == 0) s_pos[tid >> 6] = at;    // list places of the tiles
+        for (; m; m &= m - 1u) s_id[at++] = (uint16_t)(tid * 16 + __builtin_ctz(m));
+        __syncthreads();
+        const int tiles = (int)((c1 - sb + TILE - 1) / TILE) < PK_SPAN / TILE ? (int)((c1 - sb + TILE - 1) / TILE) : PK_SPAN / TILE;
+        uint32_t b[PK_U][4], bn[PK_U][4], id[PK_U], idn[PK_U];
+        int nv[PK_U], nvn[PK_U];
+        auto fetch = [&](uint32_t i0, uint32_t (&v)[PK_U][4], uint32_t (&d4)[PK_U], int (&have)[PK_U]) {
+#pragma unroll
+            for (int u = 0; u < PK_U; ++u) {
+                const uint32_t i = i0 + tid * PK_U + u;
+                d4[u] = i < n ? s_id[i] : 0u;
+                have[u] = i < n ? ld.load4(sb + (int64_t)d4[u] * 4, v[u]) : 0;
+            }
+        };
+        fetch(0, bn, idn, nvn);
+        for (uint32_t i0 = 0; i0 < n; i0 += PK_THREADS * PK_U) {   // uniform
+#pragma unroll
+            for (int u = 0; u < PK_U; ++u) {
+                id[u] = idn[u];
+                nv[u] = nvn[u];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) b[u][c] = bn[u][c];
+            }
+            if (i0 + PK_THREADS * PK_U < n) fetch(i0 + PK_THREADS * PK_U, bn, idn, nvn);
+            uint32_t in0 = 0, mem = 0, total;   // a bit per entry
+#pragma unroll
+            for (int u = 0; u < PK_U; ++u)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const uint32_t key = key_of_bits(b[u][c]);
+                    const bool base = key >= lo[0];
+                    in0 |= (base ? 1u : 0u) << (4 * u + c);
+                    mem |= (base || key - lo[2] < width ? 1u : 0u) << (4 * u + c);
+                }
+            if (any_cut) {   // uniform
+#pragma unroll
+                for (int u = 0; u < PK_U; ++u)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        const uint32_t key = key_of_bits(b[u][c]), j = (uint32_t)sb + id[u] * 4u + (uint32_t)c, bit = 1u << (4 * u + c);
+                        const bool base = inside_top(th, 0, key, j);
+                        in0 = base ? in0 | bit : in0 & ~bit;
+                        mem = base || (inside_top(th, 2, key, j) && !inside_top(th, 1, key, j)) ? mem | bit : mem & ~bit;
+                    }
+            }
+#pragma unroll
+            for (int u = 0; u < PK_U; ++u) mem &= ~((nv[u] < 4 ? 0xFu << nv[u] & 0xFu : 0u) << (4 * u));   // what is not there
+            const uint32_t at = scan((uint32_t)__popc(mem), total);   // (its barrier lies behind the last reads of s_out)
+            {
+#pragma unroll
+                for (int u = 0; u < PK_U; ++u) {
+                    const uint32_t i = i0 + tid * PK_U + u;
+#pragma unroll
+                    for (int t = 0; t < PK_SPAN / TILE; ++t)
+                        if (i == s_pos[t] && i < n && t < tiles) tile_off[sb / TILE + t] = run + at + (uint32_t)__popc(mem & ((1u << (4 * u)) - 1u));
+                }
+            }
+            // through LDS, so that neighbouring lanes write neighbouring entries
+            uint2* o = s_out + at;
+#pragma unroll
+            for (int u = 0; u < PK_U; ++u)
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    if ((mem >> (4 * u + c)) & 1u) {
+                        const float v = __uint_as_float(b[u][c]);
+                        *o++ = make_uint2((uint32_t)sb + id[u] * 4u + (uint32_t)c, __float_as_uint((in0 >> (4 * u + c)) & 1u ? v : __fmul_rn(v, w)));
+                    }
+            __syncthreads();
+            for (uint32_t i = tid; i < total; i += PK_THREADS) {
+                const uint2 e = s_out[i];
+                if ((int64_t)run + i < room) { idx[run + i] = e.x; val[run + i] = __uint_as_float(e.y); }
+            }
+            run += total;
+        }
+        if (tid < tiles && s_pos[tid] >= n) tile_off[sb / TILE + tid] = run;   // tiles behind the last marked four
+    }
+    if (tid == 0 && run != next_base) atomicOr(a.dev_status, MLMC_DEV_INTERNAL);
+}
+
 // ---------------------------------------------------------------------------------------------------
 // host-side launchers
 template <bool VEC>
@@ -2361,8 +2538,10 @@ static mlmc_status launch_select(const mlmc_plan_t* pl, const TopkArgs& a, bool 
             // chunks in four count chunks (32 K elements or more): two workgroups per chunk, two per CU
             if (pl->csub == 4) {
                 const dim3 grid2(2 * pl->chunks_per_row, pl->M);
-                if (sums) MLMC_LAUNCH(km, st, k_main2<VEC, true><<<grid2, M2_THREADS, 0, st>>>(a));
-                else MLMC_LAUNCH(km, st, k_main2<VEC, false><<<grid2, M2_THREADS, 0, st>>>(a));
+                if (sums && a.marks) MLMC_LAUNCH(km, st, k_main2<VEC, true, true><<<grid2, M2_THREADS, 0, st>>>(a));
+                else if (a.marks) MLMC_LAUNCH(km, st, k_main2<VEC, false, true><<<grid2, M2_THREADS, 0, st>>>(a));
+                else if (sums) MLMC_LAUNCH(km, st, k_main2<VEC, true, false><<<grid2, M2_THREADS, 0, st>>>(a));
+                else MLMC_LAUNCH(km, st, k_main2<VEC, false, false><<<grid2, M2_THREADS, 0, st>>>(a));
             } else if (sums) {
                 MLMC_LAUNCH(km, st, k_main<VEC, true, false><<<mgrid, MAIN_THREADS, 0, st>>>(a, exact_pass));
             } else {
@@ -2425,7 +2604,8 @@ static mlmc_status launch_compact(const mlmc_plan_t* pl, const TopkArgs& a, hipS
         sw = pl->side_stream;
     }
     MLMC_LAUNCH(K_WRITE, sw, k_write<VEC><<<wgrid, WR_THREADS, 0, sw>>>(a));
-    if (a.staging) MLMC_LAUNCH(K_FILTER, st, k_filter<<<grid, FL_THREADS, fl_lds, st>>>(a));
+    if (a.staging && a.marks) MLMC_LAUNCH(K_FILTER, st, k_pick<VEC><<<wgrid, PK_THREADS, 0, st>>>(a));
+    else if (a.staging) MLMC_LAUNCH(K_FILTER, st, k_filter<<<grid, FL_THREADS, fl_lds, st>>>(a));
     if (fork) {
         if (hipEventRecord(pl->side_join, sw) != hipSuccess || hipStreamWaitEvent(st, pl->side_join, 0) != hipSuccess)
             return MLMC_EHIP;

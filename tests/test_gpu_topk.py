@@ -530,3 +530,44 @@ def test_chunks_of_32k_entries(M, d):
             msg = P.mlmc_compress_topk(plan, g, seed=3, step=step)
             check_topk_against_oracle(plan, G, 3, step, msg, adaptive=p is None)
             assert plan.status() == 0
+
+
+@pytest.mark.parametrize("what,M,d,pad", [
+    ("normal", 3, 65_537, 0),             # the shortest rows with marks: a workgroup's last stretch ends inside a tile
+    ("loud", 2, 300_001, 3),              # the bands lie in a few tiles, misaligned rows
+    ("few", 2, 147_456 + 4096 + 70, 0),   # thresholds that split their equals, bands of a few values
+    ("misled", 1, (1 << 21) + 777, 0),    # the sample has nothing of the row: redone, read whole
+    ("normal", 1, (1 << 22) + 16_385, 0), # sampled; a stretch of one tile and one entry
+])
+def test_message_from_marked_entries(what, M, d, pad):
+    """The message of rows whose entries the selection read marks, in bands narrow and wide, fixed p, adaptive and given norms; cut at its capacity."""
+    rng = np.random.default_rng(d + M)
+    G = rng.standard_normal((M, d)).astype(np.float32)
+    if what == "loud":
+        G[:, : d // 40] *= np.float32(1e3)
+        G[:, 11::1013] *= np.float32(1e2)
+    elif what == "few":
+        G = (np.round(G * 3) / 3).astype(np.float32)
+    elif what == "misled":
+        G[:, (np.arange(d) >> 10) % 4 == 2] = 0.0
+    g = to_device(G, ld=d + pad)
+    for ladder in ([d >> 9, d >> 7, d >> 5, d >> 3, d], [0, 40, d // 3, d - 1]):
+        L = len(ladder) - 1
+        for how in ("adaptive", "fixed", "given"):
+            p = O.geometric_p(L) if how == "fixed" else None
+            plan = P.Plan(P.MLMC_TOPK, M, d, P.MLMC_F32, ladder, p)
+            plan.ws.fill_(0xFF)
+            norms = P.mlmc_level_norms(plan, g) if how == "given" else None
+            for step in range(4 if how == "adaptive" else 2):
+                print(f"marked {what} {M}x{d}+{pad} {ladder} {how} step={step}", flush=True)
+                msg = P.mlmc_compress_topk(plan, g, seed=3, step=step, p=norms, p_is_norms=norms is not None)
+                check_topk_against_oracle(plan, G, 3, step, msg, adaptive=how == "adaptive")
+                assert plan.status() == 0
+            whole = P.mlmc_compress_topk(plan, g, seed=3, step=0, p=norms, p_is_norms=norms is not None)
+            cap = max(1, int(whole.row_off[1]) // 2)
+            cut = P.SparseMessage(plan, capacity=plan.sparse_capacity_worst, with_norms=False)
+            cut.idx.fill_(-7)
+            cut.capacity = cap
+            P.mlmc_compress_topk(plan, g, seed=3, step=0, p=norms, p_is_norms=norms is not None, out=cut)
+            assert plan.status() == P.MLMC_DEV_CAPACITY
+            assert torch.equal(cut.idx[:cap], whole.idx[:cap]) and bool((cut.idx[cap:] == -7).all())
