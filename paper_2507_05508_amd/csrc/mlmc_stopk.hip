@@ -859,15 +859,21 @@ __global__ __launch_bounds__(256) void k_se_scan(StopkArgs a) {
 // levels within 2^-12 of the whole of where the drawn word falls in the running sum.  By one workgroup, which leaves it in *win.
 // What the forecast misses costs a read of the row (k_se_mark).
 constexpr int SE_PER = SE_LMAX / SE_THREADS;
-__device__ __forceinline__ void se_forecast(const StopkArgs& a, int row, double* s_w /* SE_WAVES */, int* s_t /* 2 */, uint2* win) {
+// The squares are read before the workgroup's other tables (se_forecast_read); the caller synchronizes before it reads *win.
+__device__ __forceinline__ void se_forecast_read(const StopkArgs& a, int row, double (&e)[SE_PER]) {
+#pragma unroll
+    for (int i = 0; i < SE_PER; ++i) {
+        const int l = (int)threadIdx.x * SE_PER + i;
+        e[i] = l < a.L ? a.se_apx[(size_t)row * a.L + l] : 0.0;
+    }
+}
+__device__ __forceinline__ void se_forecast(const StopkArgs& a, int row, const double (&e)[SE_PER], double* s_w /* SE_WAVES */, int* s_t /* 2 */, uint2* win) {
     const int tid = threadIdx.x;
     const uint32_t lane = lane_id(), wave = (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6);
-    const double* e = a.se_apx + (size_t)row * a.L;
     double v[SE_PER], sum = 0.0;
 #pragma unroll
     for (int i = 0; i < SE_PER; ++i) {
-        const int l = tid * SE_PER + i;
-        v[i] = l < a.L ? sqrt(e[l]) : 0.0;
+        v[i] = sqrt(e[i]);
         sum += v[i];
     }
     double inc = sum;
@@ -904,7 +910,6 @@ __device__ __forceinline__ void se_forecast(const StopkArgs& a, int row, double*
         const uint2* w = a.se_win + (size_t)row * (a.L + 1);
         *win = make_uint2(w[s_t[1]].x, w[s_t[0] - 1].y);
     }
-    __syncthreads();
 }
 
 // Second read: sums of the regions, lists of the zones, marks of the segment that the draw will most likely take.
@@ -926,7 +931,8 @@ __global__ __launch_bounds__(SE_THREADS) void k_se_split(StopkArgs a) {
     const uint32_t at = xcd * (all >> 3) + (xcd < (all & 7u) ? xcd : all & 7u) + (id >> 3);
     const int row = (int)(at / gridDim.x), slice = (int)(at % gridDim.x), tid = threadIdx.x;
     const uint32_t lane = lane_id(), wave = (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6);
-    if (MARK) se_forecast(a, row, s.fw, s.ft, &s.win);
+    double apx[SE_PER];
+    if (MARK) se_forecast_read(a, row, apx);
     for (int i = tid; i < SE_CB / 4; i += SE_THREADS) ((uint4*)s.map)[i] = ((const uint4*)(a.se_map + (size_t)row * SE_CB))[i];
     for (int i = tid; i < SE_BINS / 8; i += SE_THREADS) ((uint4*)s.cls)[i] = ((const uint4*)(a.se_class + (size_t)row * SE_BINS))[i];
     const int rs = a.se_rep;
@@ -944,6 +950,7 @@ __global__ __launch_bounds__(SE_THREADS) void k_se_split(StopkArgs a) {
             for (uint32_t i = slice * SE_THREADS + tid; i <= (uint32_t)SE_ZBIG; i += gridDim.x * SE_THREADS) tab[i] = 0;
         }
     }
+    if (MARK) se_forecast(a, row, apx, s.fw, s.ft, &s.win);
     __syncthreads();
     RowLoader<DT, true> ld(a.g, a.ld, a.d, row);
     const int64_t i0 = (int64_t)slice * a.se_slice, i1 = i0 + a.se_slice < a.d ? i0 + a.se_slice : a.d;
@@ -1022,11 +1029,20 @@ __global__ __launch_bounds__(SE_THREADS) void k_se_split(StopkArgs a) {
 
 // One workgroup per zone of up to SE_ZCAP entries.  Keys of a zone differ in their low `shift` bits only; they are counted in 256 buckets of the zone's key range.
 // One boundary, as most zones have: it lies in one bucket, whose few keys are ranked; every other key is on one side of it by its bucket.
+// A wave ranks the keys of such a zone by itself if they are at most one per lane, as the zones of long
+// ladders and of shorter rows are: 8 rows of 300001 entries at 3001 levels 24 us, by the workgroup 46, all in order 39.
 // More of them, or a crowded bucket: the keys are put in order in LDS, a bucket by a thread by insertion (a few keys); where a bucket holds many,
 // all keys by a bitonic sort, which takes three times as long.  Bound by the LDS latency of those steps: 8 rows of 1.17e7 entries, 1000 levels, all in order
 // 37 us, one boundary without it 22 (of the 15 saved nearly all were insertions: reads and writes of LDS that wait for one another).
 constexpr int SZ_THREADS = 256;
 constexpr uint32_t SZ_FEW = 32;
+// Sum over the lanes of squares of up to 48 bits, from 16-bit parts
+__device__ __forceinline__ uint64_t wave_sum_squares(uint64_t sq) {
+    uint64_t all = 0;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) all += (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan((uint32_t)(sq >> (16 * i)) & 0xFFFFu), 63) << (16 * i);
+    return all;
+}
 __global__ __launch_bounds__(SZ_THREADS) void k_se_zone(StopkArgs a) {
     __shared__ uint32_t s_k[SE_ZCAP];
     __shared__ uint32_t s_h[256];
@@ -1066,6 +1082,24 @@ __global__ __launch_bounds__(SZ_THREADS) void k_se_zone(StopkArgs a) {
         se_add(wide, lo, esh);
         se_add(wide, hi, esh + 32);
     };
+    if (zn.nb == 1u && n <= 64u) {   // uniform
+        if (wave) return;
+        const uint32_t x = lane < n ? src[lane] : 0u, r1 = part_from(1u);
+        uint32_t above = 0, upto = 0;
+        for (uint32_t i = 0; i < n; ++i) {
+            const uint32_t y = (uint32_t)__builtin_amdgcn_readlane((int)x, (int)i);
+            above += y > x;
+            upto += y >= x;
+        }
+        const int at = __builtin_ctzll(__ballot(lane < n && above < r1 && r1 <= upto));   // one of the keys equal to that of rank r1 - 1
+        const uint32_t tau = (uint32_t)__builtin_amdgcn_readlane((int)x, at), over = (uint32_t)__builtin_amdgcn_readlane((int)above, at), with = (uint32_t)__builtin_amdgcn_readlane((int)upto, at);
+        const uint64_t sq = lane < n ? sig_square(x) : 0u;   // 64 squares: 54 bits
+        const uint32_t q = r1 - over;                        // equal keys inside
+        const uint64_t in0 = q * sig_square(tau) + wave_sum_squares(x > tau ? sq : 0u), all0 = wave_sum_squares(sq);
+        if (lane < 2) part_add(lane, lane ? all0 - in0 : in0, 0u);
+        if (lane == 0) a.se_thr[(size_t)row * (a.L + 1) + zn.t0] = make_uint2(tau, with == r1 ? SE_ALL : q);
+        return;
+    }
     {
         constexpr int PER = SE_ZCAP / SZ_THREADS;
         const uint32_t dsh = zn.shift > 8u ? zn.shift - 8u : 0u;

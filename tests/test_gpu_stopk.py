@@ -225,3 +225,20 @@ def test_stopk_forecast_of_the_drawn_segment(what, M, d, s):
         assert plan.status() & P.MLMC_DEV_NONFINITE
         return
     _run_and_check(G, s, steps=(0, 1, 2, 3))
+
+
+@pytest.mark.parametrize("M,d,s,ties", [
+    (2, 60_001, 20, False),       # zones of a few entries
+    (1, 300_001, 100, False),     # of about ten
+    (2, 600_001, 3_000, False),   # of up to 64 and more
+    (2, 60_001, 40, True),        # boundaries among equal keys
+])
+def test_stopk_zones_of_at_most_a_wave(M, d, s, ties):
+    """Zones with one boundary on both sides of one key per lane."""
+    rng = np.random.default_rng(d + s)
+    G = rng.standard_normal((M, d)).astype(np.float32)
+    if ties:   # every key some twelve times, in zones of several keys
+        G = np.repeat(G[:, : d // 12 + 1], 12, axis=1)[:, :d] * 1.0
+        G = np.ascontiguousarray(rng.permuted(G, axis=1))
+    print(f"stopk small zones M={M} d={d} s={s} ties={ties}", flush=True)
+    _run_and_check(G, s, steps=(0, 1))
