@@ -136,6 +136,8 @@ constexpr int64_t STAGE_MAX_BAND_INV = 8;   // bands wider than d / 8 are not st
 // One workgroup per row, whose sixteen waves share a CU: an instruction of all of them takes 7 ns.  Adaptive, 12 levels, 1e6 entries 20.9 us (23.8 with the band energies
 // added up in one word per band, the zones' records stored one after the other, and every thread looking for its zone from the first one on): histogram
 // 2.3, scan 2.2, zone ends 1.3, zones and list layout 3.8, band energies 4.1, predicted draw 1.9, class table 4.3.
+// MARKS: rows whose entries are marked (a.marks); the others would pay for a test of it in every bucket (14.5 against 13.9 us, 8 rows of 1.17e7, fixed p).
+template <bool MARKS>
 __global__ __launch_bounds__(1024) void k_scan(TopkArgs a, int exact_pass) {
     __shared__ __align__(16) uint32_t s_h[NB1];
     __shared__ uint32_t s_cum[NB1];          // sampled elements in buckets above b
@@ -310,7 +312,7 @@ __global__ __launch_bounds__(1024) void k_scan(TopkArgs a, int exact_pass) {
             ri->zone_t1[tid] = z_t1;
             s_ztop[tid] = z_top;
             s_zbot[tid] = z_bot;
-            s_zt[tid] = (uint32_t)z_t0 | (uint32_t)z_t1 << 8;
+            if (MARKS) s_zt[tid] = (uint32_t)z_t0 | (uint32_t)z_t1 << 8;
         }
         if (tid <= nz) s_label[tid] = z_label;
         static_assert(RMAX <= 64, "a lane per region");
@@ -378,10 +380,14 @@ __global__ __launch_bounds__(1024) void k_scan(TopkArgs a, int exact_pass) {
             double tot = 0.0;
             for (int l = 0; l < L; ++l) tot += lane_f64(n, l);
             const double p = tot > 0.0 ? n / tot : 1.0 / (double)L;
-            const uint32_t x = philox_word0(a.seed, a.step, (uint32_t)row), eps = a.marks ? 1u << 26 : 0u;
+            const uint32_t x = philox_word0(a.seed, a.step, (uint32_t)row), eps = 1u << 26;
             const int lev_c = wave_draw_from_p(p, L, x);
-            int lev_p = wave_draw_from_p(p, L, x > eps ? x - eps : 0u), lev_q = wave_draw_from_p(p, L, x < ~eps ? x + eps : ~0u);
-            if ((s_k[lev_q] - s_k[lev_p - 1]) * STAGE_MAX_BAND_INV > a.d) lev_p = lev_q = lev_c;   // wide ones one at a time
+            int lev_p = lev_c, lev_q = lev_c;
+            if (MARKS) {
+                lev_p = wave_draw_from_p(p, L, x > eps ? x - eps : 0u);
+                lev_q = wave_draw_from_p(p, L, x < ~eps ? x + eps : ~0u);
+                if ((s_k[lev_q] - s_k[lev_p - 1]) * STAGE_MAX_BAND_INV > a.d) lev_p = lev_q = lev_c;   // wide ones one at a time
+            }
             if (tid == 0) { s_lev = lev_p; s_lev1 = lev_q; }
         }
         __syncthreads();
@@ -389,10 +395,10 @@ __global__ __launch_bounds__(1024) void k_scan(TopkArgs a, int exact_pass) {
     if (tid == 0) {
         int sl = ((a.all_thresholds && a.draw_mode != 3) || !a.staging) ? 0 : s_lev;   // norms only: nothing to stage
         int sl1 = a.all_thresholds ? s_lev1 : sl;
-        if (a.marks && exact_pass) sl = 0;   // the marks are those of the first attempt
+        if (MARKS && exact_pass) sl = 0;   // the marks are those of the first attempt
         // a wide band is cheaper to collect by a second read: the staged lists of such a row would keep its few
         // workgroups busy long after the other rows are done
-        if (sl > 0 && !a.marks && (s_k[sl] - s_k[sl - 1]) * STAGE_MAX_BAND_INV > a.d) sl = 0;
+        if (sl > 0 && !MARKS && (s_k[sl] - s_k[sl - 1]) * STAGE_MAX_BAND_INV > a.d) sl = 0;
         ri->spec_level = sl;
         ri->spec_last = sl1;
         s_lev1 = sl1;
@@ -405,7 +411,7 @@ __global__ __launch_bounds__(1024) void k_scan(TopkArgs a, int exact_pass) {
     // class table: thread tid writes its 16 buckets (descending), 64 bytes.  The zone bounds of the current zone
     // index stay in registers; a thread's buckets share their exponent, so their group changes only with the zone
     // index and the group tables are written once per change.
-    uint32_t codes[16], want = 0;   // want: bit per bucket, the message may need its entries
+    uint32_t codes[16], want = 0;   // want (MARKS): bit per bucket, the message may need its entries; otherwise what is staged, CODE_STAGE
     int zi = 0;   // zones wholly above the current bucket
 #pragma unroll 4
     for (int z = 0; z < nz; ++z) zi += s_zbot[z] > (uint32_t)(NB1 - 1 - tid * 16) ? 1 : 0;
@@ -422,8 +428,10 @@ __global__ __launch_bounds__(1024) void k_scan(TopkArgs a, int exact_pass) {
         }
         if (zi < nz && b <= ztop_c) {
             codes[15 - i] = class_code((uint32_t)G_DUMMY, 64u + (uint32_t)zi, (uint32_t)zi, true);
-            const int t0 = (int)(s_zt[zi] & 0xFFu), t1 = (int)(s_zt[zi] >> 8);   // entries of bands t0 .. t1 + 1
-            want |= (!a.marks || (spec > 0 && (t0 == 0 || (t0 <= spec1 && t1 + 1 >= spec))) ? 1u : 0u) << (15 - i);   // (candidates are staged, whatever the message)
+            if (MARKS) {
+                const int t0 = (int)(s_zt[zi] & 0xFFu), t1 = (int)(s_zt[zi] >> 8);   // entries of bands t0 .. t1 + 1
+                want |= (spec > 0 && (t0 == 0 || (t0 <= spec1 && t1 + 1 >= spec)) ? 1u : 0u) << (15 - i);   // (candidates are staged, whatever the message)
+            }
         } else {
             const uint32_t E = b >> 6;
             const int gid = (int)(255 - E) + zi;
@@ -432,8 +440,8 @@ __global__ __launch_bounds__(1024) void k_scan(TopkArgs a, int exact_pass) {
                 s_gexp[gid] = (uint16_t)(E ? E : 1);
                 s_gband[gid] = (uint16_t)lab_c;
             }
-            const bool member = spec > 0 && (lab_c == 0 || (lab_c >= spec && lab_c <= spec1));
-            want |= (member ? 1u : 0u) << (15 - i);
+            const bool member = spec > 0 && (lab_c == 0 || (MARKS ? lab_c >= spec && lab_c <= spec1 : lab_c == spec));
+            if (MARKS) want |= (member ? 1u : 0u) << (15 - i);
             codes[15 - i] = class_code((uint32_t)gid, (uint32_t)zi, member ? TAG_MEMBER : 0u, member);
         }
     }
@@ -450,7 +458,7 @@ __global__ __launch_bounds__(1024) void k_scan(TopkArgs a, int exact_pass) {
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const uint32_t c = codes[4 * i + k];
-                w8[i] |= (((c >> 6) & 0x7Fu) | ((want >> (4 * i + k)) & 1u) << 7) << (8 * k);
+                w8[i] |= (((c >> 6) & 0x7Fu) | ((MARKS ? (want >> (4 * i + k)) & 1u : c & CODE_STAGE ? 1u : 0u) << 7)) << (8 * k);
             }
         }
         *(uint4*)(a.table8 + (size_t)row * NB1 + (NB1 - 16 - tid * 16)) = make_uint4(w8[0], w8[1], w8[2], w8[3]);
@@ -2530,7 +2538,8 @@ static mlmc_status launch_select(const mlmc_plan_t* pl, const TopkArgs& a, bool 
         const int kh = exact_pass ? K_REDO : K_HIST, ks = exact_pass ? K_REDO : K_SCAN;
         const int km = exact_pass ? K_REDO : K_MAIN;
         MLMC_LAUNCH(kh, st, k_hist<VEC><<<hgrid, HIST_THREADS, 0, st>>>(a, exact_pass));
-        MLMC_LAUNCH(ks, st, k_scan<<<pl->M, 1024, 0, st>>>(a, exact_pass));
+        if (a.marks) MLMC_LAUNCH(ks, st, k_scan<true><<<pl->M, 1024, 0, st>>>(a, exact_pass));
+        else MLMC_LAUNCH(ks, st, k_scan<false><<<pl->M, 1024, 0, st>>>(a, exact_pass));
         if (exact_pass) {
             if (sums) MLMC_LAUNCH(km, st, k_main<VEC, true, true><<<mgrid, MAIN_THREADS, 0, st>>>(a, exact_pass));
             else MLMC_LAUNCH(km, st, k_main<VEC, false, true><<<mgrid, MAIN_THREADS, 0, st>>>(a, exact_pass));
