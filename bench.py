@@ -45,7 +45,7 @@ def algorithmic_bytes(w, kernel, nnz_total, planes_bytes):
         return 8 * nnz_total                              # the message; its short-slice form reads the rows once more
     if kernel == "k_agg_sparse":
         return 8 * nnz_total + 4 * w.d                    # read the messages, write the dense update
-    if kernel == "k_bits_extract":
+    if kernel in ("k_bits_extract", "k_bits_extract_words"):
         return in_bytes + planes_bytes
     if kernel == "k_agg_bits":
         return planes_bytes + 4 * w.d

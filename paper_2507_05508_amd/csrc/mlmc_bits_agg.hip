@@ -706,10 +706,18 @@ mlmc_status message_bits(const mlmc_plan_t* pl, const int32_t* level, unsigned l
 }
 
 // ---------------------------------------------------------------------------------------------------
-// By words while that many waves still find room: us, 2048 entries a wave / words: fixed point 4 rows of 100003 8.5 / 4.3, 4 of 300001 8.0 / 4.6, 8 of 300001 8.3 / 6.4, 8 of 500001
-// 7.9 / 11.4 (two words a wave); floating point (up to 32 planes) 4 of 300001 7.0 / 6.2, 8 of 300001 7.7 / 9.0, 32 of 100003 9.2 / 11.9; largest entry 4 of 300001 8.7 / 5.5.
+// By words while that many waves still find room, which is up to other sizes for rows with a ragged last block, whose entries the blocks' kernel loads one by one (some 3 us),
+// and for rows of whole blocks.  compress, us, 2048 entries a wave / words (graph replay).
+// Ragged, fixed point: 4 rows of 100003 10.4 / 6.5, 128 of 12287 11.1 / 8.0 (16 bits 10.9 / 8.4), 1 of 1572863 11.2 / 7.6; largest entry 8 of 196607 11.7 / 7.4; floating point (up to
+// 32 planes) 8 of 196607 11.3 / 9.3, 600 of 2049 10.7 / 10.6 (16 bits 10.9 / 10.9).
+// Whole, fixed point: 1 of 16384 6.8 / 6.2, 4 of 262144 7.7 / 6.6, 1 of 1572864 7.8 / 7.6, 32 of 32768 7.4 / 7.2, but 32 of 49152 7.4 / 7.5, 128 of 2048 6.9 / 7.0 and of 8192 7.1 / 7.5; 16 bits 4 of 262144
+// 7.1 / 6.9, 8 of 131072 7.0 / 7.0, 4 of 393216 7.1 / 7.4, 32 of 16384 6.9 / 7.3; largest entry the same to a tenth; floating point 1 of 16384 7.0 / 7.8, 4 of 262144 7.7 / 8.5.
 static bool extract_by_words(const mlmc_plan_t* pl, const BitsArgs& a) {
-    return a.sample_shift == 0 && (int64_t)pl->M * pl->d <= 3 << 19;
+    if (a.sample_shift != 0) return false;
+    const int64_t all = (int64_t)pl->M * pl->d;
+    if (pl->d % EX_ELEMS) return all <= 3 << 19;
+    const bool f32 = pl->dtype == MLMC_F32;
+    return !a.flt && pl->M <= (f32 ? 32 : 8) && all <= (f32 && pl->M <= 8 ? 3 << 19 : 1 << 20);
 }
 mlmc_status bits_compress(const mlmc_plan_t* pl, const BitsArgs& a0, hipStream_t st) {
     BitsArgs a = a0;
@@ -719,8 +727,8 @@ mlmc_status bits_compress(const mlmc_plan_t* pl, const BitsArgs& a0, hipStream_t
     const dim3 wgrid((unsigned)((a.nwords + EW_WORDS * (EX_THREADS / 64) - 1) / (EW_WORDS * (EX_THREADS / 64))), pl->M);
 #define MLMC_EXTRACT_B(ID, DT, REDO, KIND)                                                                               \
     do {                                                                                                                \
-        if (words && a.F[0] == 0) MLMC_LAUNCH(ID, st, k_bits_extract_words<DT, KIND, false><<<wgrid, EX_THREADS, 0, st>>>(a)); \
-        else if (words) MLMC_LAUNCH(ID, st, k_bits_extract_words<DT, KIND, true><<<wgrid, EX_THREADS, 0, st>>>(a));      \
+        if (words && a.F[0] == 0) MLMC_LAUNCH(K_BITS_WORDS, st, k_bits_extract_words<DT, KIND, false><<<wgrid, EX_THREADS, 0, st>>>(a)); \
+        else if (words) MLMC_LAUNCH(K_BITS_WORDS, st, k_bits_extract_words<DT, KIND, true><<<wgrid, EX_THREADS, 0, st>>>(a));      \
         else if (a.F[0] == 0) MLMC_LAUNCH(ID, st, k_bits_extract<DT, REDO, KIND, false><<<egrid, EX_THREADS, 0, st>>>(a));    \
         else MLMC_LAUNCH(ID, st, k_bits_extract<DT, REDO, KIND, true><<<egrid, EX_THREADS, 0, st>>>(a));                 \
     } while (0)

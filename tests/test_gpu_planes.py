@@ -7,7 +7,7 @@ import torch
 import mlmc_workloads as W
 import paper_2507_05508_amd as P
 from oracle import mlmc as O
-from gpu_util import to_device
+from gpu_util import launched, to_device
 
 pytestmark = pytest.mark.gpu
 
@@ -130,3 +130,31 @@ def test_planes_on_both_sides_of_the_words_limit(kind, bf16, M, d, off):
     g.copy_(base)
     for n, F in enumerate(KINDS[kind][1][:2]):
         _one(kind, F, G, g, n + off, 0.5, f"offset {off}")
+
+
+@pytest.mark.parametrize("kind,bf16,M,d,words", [
+    ("bits", False, 6, 262_143, True), ("bits", False, 6, 262_145, False),      # ragged last blocks: 1572864 entries in all
+    ("bits", False, 8, 196_608, True), ("bits", False, 8, 198_656, False),      # whole blocks: the same for few rows,
+    ("bits", False, 16, 65_536, True), ("bits", False, 16, 67_584, False),      # 2^20 for more
+    ("bits", False, 32, 2_048, True), ("bits", False, 33, 2_048, False), ("bits", False, 33, 2_049, True),
+    ("bits", True, 8, 2_048, True), ("bits", True, 9, 2_048, False), ("bits", True, 9, 2_047, True),
+    ("vbits", False, 32, 4_096, True), ("vbits", False, 33, 4_096, False), ("vbits", True, 9, 4_096, False),
+    ("fbits", False, 1, 2_048, False), ("fbits", False, 1, 2_047, True), ("fbits", True, 6, 262_144, False),
+])
+def test_extraction_by_words_or_by_blocks(kind, bf16, M, d, words):
+    """The sizes that take either kernel, and the first and the last row's message."""
+    row = {"bits": O.compress_bits_row, "vbits": O.compress_vbits_row, "fbits": O.compress_fbits_row}[kind]
+    F = KINDS[kind][1][0]
+    p = O.geometric_p(len(F) - 1)
+    G = np.random.default_rng(d).standard_normal((M, d)).astype(np.float32)
+    if bf16:
+        G = W.f32_to_bf16_bits(G)
+    plan = P.Plan(KINDS[kind][0], M, d, P.MLMC_BF16 if bf16 else P.MLMC_F32, F, p)
+    msg, g = P.BitsMessage(plan), to_device(G)
+    print(f"extraction {kind} bf16={bf16} M={M} d={d}", flush=True)
+    names = launched(lambda: P.mlmc_compress_bits(plan, g, 4, 1, out=msg))
+    assert ("k_bits_extract_words" in names, "k_bits_extract" in names) == (words, not words)
+    for i in {0, M - 1}:
+        want = row(W.bf16_bits_to_f32(G[i]) if bf16 else G[i], F, p, 4, 1, i)
+        assert int(msg.level[i]) == want["level"]
+        assert np.array_equal(msg.planes[i].cpu().numpy().view(np.uint64)[: want["planes"].shape[0]], want["planes"])
