@@ -47,7 +47,7 @@ def algorithmic_bytes(w, kernel, nnz_total, planes_bytes):
         return 8 * nnz_total + 4 * w.d                    # read the messages, write the dense update
     if kernel in ("k_bits_extract", "k_bits_extract_words"):
         return in_bytes + planes_bytes
-    if kernel == "k_agg_bits":
+    if kernel in ("k_agg_bits", "k_agg_words"):
         return planes_bytes + 4 * w.d
     return 0
 

@@ -56,7 +56,7 @@ static const char* const k_names[K_NUM] = {
     "k_bits_smax", "k_bits_extract", "k_bits_redo", "k_agg_bits", "k_tileoff", "k_agg_sparse", "k_message_bits", "k_rtn_norms", "k_rtn_draw",
     "k_rs_hist", "k_rs_scan", "k_rs_scatter", "k_sb_norms", "k_sb_draw", "k_sb_mark", "k_sb_offsets", "k_sb_write", "k_se_count", "k_se_scan",
     "k_se_split", "k_se_zone", "k_row_select", "k_row_write", "k_c16_hist", "k_c16_reduce", "k_c16_scan", "k_c16_mark", "k_c16_offsets", "k_c16_write",
-    "k_bits_extract_words"};
+    "k_bits_extract_words", "k_agg_words"};
 struct ProfPair { int id; hipEvent_t e0, e1; };
 static std::vector<ProfPair> g_pending;
 static std::vector<ProfPair> g_free;

@@ -777,15 +777,21 @@ mlmc_status agg_bits(const mlmc_plan_t* pl, const BitsArgs& b, const int32_t* le
     const int64_t nblk = (b.d + EX_ELEMS - 1) / EX_ELEMS;
     const unsigned grid = (unsigned)((nblk + EX_THREADS / 64 - 1) / (EX_THREADS / 64));
     const size_t lds = (size_t)(EX_THREADS / 64) * EX_ELEMS * 4 + sizeof(AggRow) * (size_t)b.M;
-    // By words: us, 2048 entries a wave / words: fixed point 4 rows of 100003 8.4 / 3.9, 8 of 300001 9.6 / 6.2, 8 of 500001 8.7 / 7.8, 8 of 1000001 9.1 / 11.3; floating point
-    // 4 of 300001 8.2 / 7.1, 8 of 300001 11.7 / 10.7, 32 of 100003 32.6 / 18.2: the rows come one after the other either way, so their length decides.
-    const bool words = b.d <= (b.flt || b.rtn ? 1 << 18 : 1 << 19);
+    // By words: the rows come one after the other either way, so their length decides, and whether it leaves the blocks' kernel a ragged block (some 3 us).  us, 2048 entries a
+    // wave / words (graph replay).  Ragged, fixed point: 4 rows of 100003 7.5 / 3.6, 1 of 524287 6.5 / 4.5, 32 of 524287 24.4 / 19.6, but 8 of 1000001 9.1 / 11.3; floating point 32 of
+    // 100003 32.0 / 18.2, 1 of 262143 6.8 / 3.7, 32 of 262143 32.7 / 26.0; Round-to-Nearest (all planes of the widest message are loaded, whatever was sent) 32 of 100003 32.1 / 14.4,
+    // 1 of 262143 6.6 / 4.1, 32 of 262143 34.2 / 28.6.  Whole: fixed point 1 of 262144 3.8 / 3.4, 2 of 393216 4.4 / 4.7, 1 of 524288 3.8 / 4.3, 4 of 524288 5.5 / 5.8, 8 of 524288 7.8 / 7.7,
+    // 32 of 524288 22.2 / 19.5; floating point 1 of 262144 4.0 / 3.7, 32 30.2 / 25.9; Round-to-Nearest 1 of 196608 4.0 / 3.4, 1 of 262144 4.0 / 4.1 (equal probabilities 4 of 262144
+    // 7.3 / 7.7), 8 of 262144 10.3 / 9.4.
+    int64_t longest = b.flt || b.rtn ? 1 << 18 : 1 << 19;
+    if (b.d % EX_ELEMS == 0 && b.M < 8 && !b.flt) longest = b.rtn ? 3 << 16 : 1 << 18;
+    const bool words = b.d <= longest;
     const unsigned wgrid = (unsigned)((b.nwords + EX_THREADS / 64 - 1) / (EX_THREADS / 64));
     const size_t wlds = sizeof(AggRow) * (size_t)b.M;
 #define MLMC_AGG(PK)                                                                                                     \
     do {                                                                                                                \
-        if (words && b.F[0] == 0) MLMC_LAUNCH(K_AGG_BITS, st, k_agg_words<PK, false><<<wgrid, EX_THREADS, wlds, st>>>(a, planes, out, x)); \
-        else if (words) MLMC_LAUNCH(K_AGG_BITS, st, k_agg_words<PK, true><<<wgrid, EX_THREADS, wlds, st>>>(a, planes, out, x)); \
+        if (words && b.F[0] == 0) MLMC_LAUNCH(K_AGG_WORDS, st, k_agg_words<PK, false><<<wgrid, EX_THREADS, wlds, st>>>(a, planes, out, x)); \
+        else if (words) MLMC_LAUNCH(K_AGG_WORDS, st, k_agg_words<PK, true><<<wgrid, EX_THREADS, wlds, st>>>(a, planes, out, x)); \
         else if (b.F[0] == 0) MLMC_LAUNCH(K_AGG_BITS, st, k_agg_planes<PK, false><<<grid, EX_THREADS, lds, st>>>(a, planes, out, x)); \
         else MLMC_LAUNCH(K_AGG_BITS, st, k_agg_planes<PK, true><<<grid, EX_THREADS, lds, st>>>(a, planes, out, x));       \
     } while (0)

@@ -158,3 +158,24 @@ def test_extraction_by_words_or_by_blocks(kind, bf16, M, d, words):
         want = row(W.bf16_bits_to_f32(G[i]) if bf16 else G[i], F, p, 4, 1, i)
         assert int(msg.level[i]) == want["level"]
         assert np.array_equal(msg.planes[i].cpu().numpy().view(np.uint64)[: want["planes"].shape[0]], want["planes"])
+
+
+@pytest.mark.parametrize("kind,M,d,words", [
+    ("bits", 1, 262_144, True), ("bits", 2, 264_192, False), ("bits", 2, 264_193, True), ("bits", 8, 524_288, True),
+    ("vbits", 7, 264_192, False), ("vbits", 8, 264_192, True), ("vbits", 1, 524_289, False),
+    ("fbits", 1, 262_144, True), ("fbits", 1, 262_145, False),
+    ("rtn", 2, 196_608, True), ("rtn", 2, 198_656, False), ("rtn", 2, 198_657, True), ("rtn", 8, 262_144, True), ("rtn", 8, 262_145, False),
+])
+def test_aggregate_by_words_or_by_blocks(kind, M, d, words):
+    """The sizes that take either kernel, and the update."""
+    code, ladders, compress, aggregate = KINDS[kind]
+    F = ladders[0]
+    p = O.geometric_p(len(F) - 1)
+    G = np.random.default_rng(d).standard_normal((M, d)).astype(np.float32)
+    plan = P.Plan(code, M, d, P.MLMC_F32, F, p)
+    print(f"aggregate {kind} M={M} d={d}", flush=True)
+    msg = P.mlmc_compress_rtn(plan, to_device(G), 4, 1) if kind == "rtn" else P.mlmc_compress_bits(plan, to_device(G), 4, 1)
+    out = torch.empty(d, dtype=torch.float32, device="cuda")
+    names = launched(lambda: P.mlmc_aggregate(plan, msg, 0.5, out=out))
+    assert ("k_agg_words" in names, "k_agg_bits" in names) == (words, not words)
+    assert np.array_equal(out.cpu().numpy().view(np.uint32), aggregate(compress(G, F, p, 4, 1), F, d, 0.5).view(np.uint32))
