@@ -595,8 +595,11 @@ mlmc_status mlmc_plan(mlmc_plan_t** plan, int kind, int M, int64_t d, int in_dty
         if (pl->c16_slice >= (1 << 18)) {
             // A forecast of the message (k_c16_sample) costs some 30 us and a tenth of the first read, and spares most of the second one, which below this size
             // partly comes from the last cache.  Pass with the aggregate, 12 levels, us, without / with it, rows of many scales, adaptive: 8 of 11689512 161 / 167, 4 of 30000001
-            // 211 / 217, 1 of 1.24e8 253 / 266, 2 of 7e7 231 / 234, 32 of 4000001 227 / 215, 4 of 50000001 323 / 308, 16 of 25557032 535 / 459, 4 of 1.24e8 (16 levels) 575 / 484; rows of one
-            // distribution, fixed p: 4 of 50000001 256 / 230, 4 of 1.2e8 552 / 453.
+            // 211 / 217, 1 of 1.24e8 253 / 266, 2 of 7e7 231 / 234, 32 of 4000001 227 / 215, 4 of 50000001 293 / 267, 2 of 8e7 250 / 247, 4 of 4e7 223 / 214, 16 of 25557032 535 / 459, 4 of 1.24e8
+            // (16 levels) 575 / 484; with fixed p 2 of 8e7 203 / 191, 32 of 5000001 197 / 174.  Rows of one distribution, whose lines nearly all have a member from bands of a thirtieth on: fixed p
+            // 2 of 8e7 223 / 212, 4 of 50000001 261 / 231, 32 of 5000001 215 / 189, 4 of 1.2e8 552 / 453; adaptive, wide bands every other time, 8 of 2e7 306 / 301, 4 of 50000001 389 / 391, 32 of
+            // 5000001 334 / 322, 4 of 1.2e8 868 / 845, but 2 of 8e7 332 / 339, 4 of 4e7 299 / 303.
+            // These lose 2 % and gain 1 to 7 % with every other kind of row and draw.
             if ((int64_t)M * d >= 160000000) {
                 pl->off_c16_mark = off;
                 off = align_up(off + sizeof(uint64_t) * (TILE / 512) * (size_t)pl->ntiles * M, 256);

@@ -16,11 +16,12 @@ typedef uint32_t u32x4_b16 __attribute__((ext_vector_type(4), aligned(2)));
 // counter per lane: on one word the lanes of a wave take turns.  16-byte loads (8 entries) at any alignment, past the cache, four of a wave's in
 // flight while four are counted: bound by the read, 4 rows of 1.24e8 entries in 166 us (6.0 TB/s; with plain 8-byte loads 188).
 // MARK: (10 us more of the 166) for every 512 entries of a whole piece a 64-bit word at marks[(entry - i0) / 512], bit l: one of the eight entries from 8 l on is in win.
+// Returns how many of them the wave has marked.
 typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ u16x2 both16(int32_t x) { const u16x2 r = {(uint16_t)x, (uint16_t)x}; return r; }
 struct C16Window { uint32_t lo, span, base; };   // magnitudes lo .. lo + span - 1, and those from base on
 template <bool MARK>
-__device__ __forceinline__ void count16_slice(const uint16_t* row, int64_t i0, int64_t i1, uint32_t* s_h, const C16Window& win, uint64_t* marks) {
+__device__ __forceinline__ uint32_t count16_slice(const uint16_t* row, int64_t i0, int64_t i1, uint32_t* s_h, const C16Window& win, uint64_t* marks) {
     const int tid = threadIdx.x;
     for (int i = tid; i < C16_LDS / 4; i += C16_THREADS) ((uint4*)s_h)[i] = make_uint4(0, 0, 0, 0);
     __syncthreads();
@@ -39,6 +40,7 @@ __device__ __forceinline__ void count16_slice(const uint16_t* row, int64_t i0, i
         for (int q = 0; q < 4; ++q) b[q] = __builtin_nontemporal_load((const u32x4_b16*)(row + i0 + p * PIECE + q * 512 + lane * 8));
     };
     const u16x2 wlo = both16((int32_t)win.lo);
+    uint32_t marked = 0;
     auto use = [&](const u32x4_b16 (&b)[4], int64_t p) {
         uint32_t words = 0;
 #pragma unroll
@@ -53,6 +55,7 @@ __device__ __forceinline__ void count16_slice(const uint16_t* row, int64_t i0, i
                 }
                 const uint32_t l0 = lowest.x, l1 = lowest.y, h0 = highest.x, h1 = highest.y;
                 const uint64_t m = __ballot((l0 < l1 ? l0 : l1) < win.span || (h0 > h1 ? h0 : h1) >= win.base);
+                marked += (uint32_t)__popcll(m);
                 words = write_lane((uint32_t)m, 2 * q, words);
                 words = write_lane((uint32_t)(m >> 32), 2 * q + 1, words);
             }
@@ -85,6 +88,7 @@ __device__ __forceinline__ void count16_slice(const uint16_t* row, int64_t i0, i
         if (lane == 0) s_h[0] = z;
     }
     __syncthreads();
+    return marked;
 }
 
 }  // namespace mlmc

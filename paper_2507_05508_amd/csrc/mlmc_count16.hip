@@ -20,7 +20,7 @@ namespace mlmc {
 // k_c16_sample counts one block of 1024 entries in 32 by the upper 13 bits of the magnitudes, in up to 64 parts a row;
 // k_c16_forecast, a workgroup per row, takes thresholds and norms from the sample, draws the level as the row will (adaptive: all levels within one per cent
 // of the whole of where the drawn word falls) and leaves a window of magnitudes that holds its band and its base band, sampling errors allowed for.
-// What it misses costs a read (k_c16_mark), nothing else.  4 rows of 1.24e8 entries, 16 levels, adaptive: 10 + 19 us and 166 -> 176 for the first read,
+// What it misses costs a read (k_c16_mark), nothing else; where it would mark too much, nothing is marked.  4 rows of 1.24e8 entries, 16 levels, adaptive: 10 + 19 us and 166 -> 176 for the first read,
 // the second 182 -> 56 (28 to 92 by the levels drawn, 8 of 48 rows with bands of a thirtieth or more); whole pass 575 -> 484.
 constexpr int C16_CB = 8192, C16_CSHIFT = 2;   // a sampled counter: four magnitudes
 constexpr int C16_SAMPLE = 5;
@@ -219,7 +219,16 @@ __global__ __launch_bounds__(1024) void k_c16_forecast(TopkArgs a) {
             ri->mark_lo = s_lo[l1];
             ri->mark_hi = s_hi[l0 - 1];
             ri->mark_base = a.k[0] > 0 ? s_lo[0] : (uint32_t)C16_KEYS;
-            ri->mark_on = s_r[l1].x - s_r[l0 - 1].x <= total / 8u ? 1 : 0;   // wider bands have entries in most lines
+            // What the first read would mark: sampled entries of the window and from the base band's key on (s_bin: descending).  Entries and not ranks, because
+            // many may be equal to a boundary's key: of rows of one value, or bands that end among zeros, all (4 rows of 6e7, pass 1512 -> 1926 and 855 -> 1253 us when they
+            // were marked by their ranks), of a base band of three tenths every eight (703 -> 752).  The limit lets bands of an eighth with their margins pass; wider ones have a mark in most
+            // lines of any row.
+            auto upto = [&](uint32_t key) -> uint32_t { return key < (uint32_t)C16_KEYS ? s_bin[C16_CB - 1 - (int)(key >> C16_CSHIFT)] : 0u; };
+            auto above = [&](uint32_t key) -> uint32_t { return upto(key + (1u << C16_CSHIFT)); };
+            const uint32_t base = upto(ri->mark_base), over = above(ri->mark_hi), band = upto(ri->mark_lo);
+            const uint32_t marked = base + (band > base ? band - (over > base ? over : base) : 0u);
+            ri->mark_on = marked <= total / 32u * 5u ? 1 : 0;
+            ri->marked = 0;
         }
     }
 }
@@ -231,15 +240,21 @@ __global__ __launch_bounds__(C16_THREADS) void k_c16_hist(TopkArgs a) {
     if (row == 0 && blockIdx.x == 0 && threadIdx.x == 0) *a.dev_status = 0;   // nothing of this launch reports through it
     const int64_t i0 = (int64_t)blockIdx.x * a.c16_slice, i1 = i0 + a.c16_slice < a.d ? i0 + a.c16_slice : a.d;
     const uint16_t* g = (const uint16_t*)a.g + (int64_t)row * a.ld;
-    const RowInfo* ri = a.rinfo + row;
-    if (a.c16_mark && ri->mark_on)   // uniform
-        count16_slice<true>(g, i0, i1, s_h, C16Window{ri->mark_lo, ri->mark_hi - ri->mark_lo + 1u, ri->mark_base}, a.c16_mark + ((size_t)row * a.ntiles * TILE + i0) / 512);
+    RowInfo* ri = a.rinfo + row;
+    __shared__ uint32_t s_marked;
+    const bool marking = a.c16_mark && ri->mark_on;   // uniform
+    uint32_t marked = 0;
+    if (threadIdx.x == 0) s_marked = 0;
+    if (marking)
+        marked = count16_slice<true>(g, i0, i1, s_h, C16Window{ri->mark_lo, ri->mark_hi - ri->mark_lo + 1u, ri->mark_base}, a.c16_mark + ((size_t)row * a.ntiles * TILE + i0) / 512);
     else
         count16_slice<false>(g, i0, i1, s_h, C16Window{}, nullptr);
     // Blocks of C16_BLOCK magnitudes that occur, and which those are: the values of a row have some twenty of the 256 exponents.
     __shared__ uint32_t s_occ[C16_KEYS / C16_BLOCK / 32];
     if (threadIdx.x < C16_KEYS / C16_BLOCK / 32) s_occ[threadIdx.x] = 0u;
+    if (marking && lane_id() == 0) atomicAdd(&s_marked, marked);
     __syncthreads();
+    if (marking && threadIdx.x == 0) atomicAdd(&ri->marked, s_marked);
     uint4* part = (uint4*)(a.c16_part + ((size_t)row * (a.c16_wgs + 1) + blockIdx.x) * C16_KEYS);
     static_assert(C16_BLOCK == 128 && C16_THREADS == 1024, "half a wave per block, 32 blocks in a turn of the workgroup");
 #pragma unroll
@@ -601,8 +616,11 @@ __global__ __launch_bounds__(MK_THREADS, 6) void k_c16_mark(TopkArgs a) {
     };
     int64_t tile = (int64_t)blockIdx.x * MK_WAVES + wave;
     const RowInfo* ri = a.rinfo + row;
-    if (a.c16_mark && ri->mark_on && lo2 >= (int32_t)ri->mark_lo && ms.lo[1] <= ri->mark_hi + 1u && (uint32_t)lo0 >= ri->mark_base) {   // uniform
-        // The first read has marked all the candidates of the row: eight entries per mark, a lane each, in index order.
+    if (a.c16_mark && ri->mark_on && (int64_t)ri->marked <= a.d / 16 && lo2 >= (int32_t)ri->mark_lo && ms.lo[1] <= ri->mark_hi + 1u &&
+        (uint32_t)lo0 >= ri->mark_base) {   // uniform
+        // The first read has marked all the candidates of the row: eight entries per mark, a lane each, in index order.  At most half of the eights: taking their
+        // candidates one by one then costs less than the lines that are left out save (4 rows of 1.2e8: 40 % of the eights marked 232 us against 240 for the plain read, 61 %
+        // 268 against 248; a test per tile instead of one per row took registers and a scan per tile, 55 -> 74 with few marks).
         const uint64_t* marks = a.c16_mark + (size_t)row * a.ntiles * (TILE / 512);
         uint16_t* place = (uint16_t*)ent;   // [2][512] the marked eights of a tile, of the next one
         // the marks of a tile, word 2 i + h of them in lane 2 i + h

@@ -90,6 +90,7 @@ struct RowInfo {
     uint32_t topkey;          // counted 16-bit rows: the largest magnitude
     uint32_t mark_lo, mark_hi, mark_base;   // their forecast: magnitudes lo .. hi and from base on are marked by the first read,
     int32_t mark_on;          // if 1
+    uint32_t marked;          // eights of entries that it has marked
     uint32_t occ[8];          // the exponents that occur, a bit each
     uint32_t zone_top[ZMAX], zone_bot[ZMAX];   // first-digit buckets of the zone, top >= bot, both inclusive
     uint32_t zone_off[ZMAX], zone_cap[ZMAX];   // its candidate list inside the row's candidate buffer
