@@ -642,9 +642,12 @@ mlmc_status mlmc_plan(mlmc_plan_t** plan, int kind, int M, int64_t d, int in_dty
         off = align_up(off + (size_t)NB1 * M, 256);
         // Marks for the message (k_main2, k_pick) or its members in lists (k_filter)?  The marked entries are read again line by line, lists are written and read whatever
         // the lines are: rows of many scales have most lines without a member, rows of one scale hardly any.  Up to here the rows are in the last cache and the second
-        // read costs little.  Pass, adaptive, us, lists / marks: many scales 8 of 300001 101 / 98, 32 of 1000001 211 / 200, 4 of 4000001 161 / 154, 4 of 8000001 207 / 198; one scale
-        // 4 of 300001 94 / 91, 8 of 1000001 114 / 114, 4 of 8000001 204 / 205, 1 of 33000001 237 / 244.  Larger: many scales 16 of 25557032 834 / 800, 8 of 11689512 334 / 307, but
-        // one scale 1047 / 1090 and 368 / 374, 4 of 6e7 723 / 762.
+        // read costs little.  Pass, 12 levels, us, lists / marks, adaptive: many scales 8 of 300001 100 / 97, 32 of 1000001 220 / 197, 4 of 4000001 163 / 155, 4 of 8000001 205 / 189,
+        // 2 of 16000001 213 / 194, 1 of 16777216 169 / 166; one scale 4 of 300001 92 / 91, 8 of 1000001 114 / 115, 32 of 1000001 210 / 207, 4 of 8000001 201 / 201, 2 of 16000001 208 / 212,
+        // 1 of 16777216 178 / 183, 1 of 33000001 237 / 244.  Geometric p: many scales 32 of 1000001 131 / 127, 4 of 8000001 131 / 131, 1 of 16777216 110 / 109; one scale 4 of 300001
+        // 64 / 63, 32 of 1000001 122 / 121, 4 of 8000001 122 / 123, 1 of 16777216 110 / 111.  Equal p: many scales 32 of 1000001 187 / 164, 4 of 8000001 170 / 161, 1 of 16777216 133 / 128;
+        // one scale 32 of 1000001 163 / 160, 4 of 4000001 123 / 124, 4 of 8000001 151 / 152, 2 of 16000001 150 / 153, 1 of 16777216 125 / 129.  Larger, adaptive: many scales 16 of
+        // 25557032 834 / 800, 8 of 11689512 334 / 307, but one scale 1047 / 1090 and 368 / 374, 4 of 6e7 723 / 762.
         if (pl->csub == CSUB_MAX && (int64_t)M * d <= ((int64_t)1 << 25) && d <= ((int64_t)1 << 24)) {
             pl->off_marks = off;
             off = align_up(off + sizeof(uint64_t) * ((size_t)pl->chunks_per_row * pl->chunk / 256) * (size_t)M, 256);

@@ -131,6 +131,11 @@ __global__ __launch_bounds__(HIST_THREADS) void k_hist(TopkArgs a, int exact_pas
 constexpr double ZONE_SIGMAS = 8.0;
 constexpr double ZONE_SIGMAS_BIG = 5.0;         // samples of at least ZONE_BIG_SAMPLE elements
 constexpr int64_t ZONE_BIG_SAMPLE = 1 << 20;
+// Wide bands of several rows up to this length are marked all the same: k_write would have the one or two rows that draw such a band to itself, behind k_pick with the
+// others.  Pass, 12 levels, us, marked / read again: one distribution, equal probabilities 4 rows of 1000001 75.9 / 76.3, 8 of 3000001 144.8 / 146.0, but 8 of 4000001 163.6 / 159.6, 4 of
+// 8000001 158.0 / 153.8, 2 of 16000001 157.8 / 155.2, one row of 300001 60.5 / 60.0, of 4000001 97.1 / 95.6, of 8000001 108.1 / 106.4; many scales, adaptive 32 of 1000001 200 / 205, 4 of
+// 8000001 194 / 191.
+constexpr int64_t MARK_WIDE_ROW = (int64_t)1 << 22;
 constexpr int64_t STAGE_MAX_BAND_INV = 8;   // bands wider than d / 8 are not staged
 
 // One workgroup per row, whose sixteen waves share a CU: an instruction of all of them takes 7 ns.  Adaptive, 12 levels, 1e6 entries 20.9 us (23.8 with the band energies
@@ -398,7 +403,7 @@ __global__ __launch_bounds__(1024) void k_scan(TopkArgs a, int exact_pass) {
         if (MARKS && exact_pass) sl = 0;   // the marks are those of the first attempt
         // a wide band is cheaper to collect by a second read: the staged lists of such a row would keep its few
         // workgroups busy long after the other rows are done
-        if (sl > 0 && !MARKS && (s_k[sl] - s_k[sl - 1]) * STAGE_MAX_BAND_INV > a.d) sl = 0;
+        if (sl > 0 && (!MARKS || gridDim.x == 1 || a.d > MARK_WIDE_ROW) && (s_k[sl] - s_k[sl - 1]) * STAGE_MAX_BAND_INV > a.d) sl = 0;
         ri->spec_level = sl;
         ri->spec_last = sl1;
         s_lev1 = sl1;

@@ -1,9 +1,11 @@
 """Which rows have the entries of their message marked by an earlier read, and that the marks hold the whole message where a forecast has to hold:
 the messages of the other tests are the same with and without them."""
+import numpy as np
 import pytest
 import torch
 
 import paper_2507_05508_amd as P
+from gpu_util import check_topk_against_oracle, to_device
 
 pytestmark = pytest.mark.gpu
 
@@ -16,6 +18,12 @@ def _region(plan, nbytes, *behind):
     """Bytes of the plan's workspace that are followed by regions of the given sizes, up to its end."""
     at = plan.workspace_bytes - sum(_align(n) for n in behind) - _align(nbytes)
     return plan.ws[at:at + nbytes]
+
+
+def _marks(plan):
+    """Marks of a 32-bit plan: [M, entries / 4] bits."""
+    words = -(-plan.d // plan.chunk) * plan.chunk // 256
+    return _region(plan, 8 * words * plan.M).view(plan.M, 8 * words)
 
 
 def _marks16(plan):
@@ -39,6 +47,32 @@ def _one_hot(M, L, level):
     p = torch.zeros((M, L), dtype=torch.float64, device="cuda")
     p[:, level - 1] = 1.0
     return p
+
+
+@pytest.mark.parametrize("M,d,wide", [
+    (2, 65_537, True), (2, 1 << 22, True), (3, 300_001, True),       # several rows: bands of any width
+    (1, 65_537, False), (1, 300_001, False),                         # one row: up to an eighth of it
+    (2, (1 << 22) + 1, False),                                       # longer ones the same
+])
+def test_bands_that_are_marked(M, d, wide):
+    """Drawn bands of an eighth of a row and just above: marked, or left to the second read."""
+    G = np.random.default_rng(d).standard_normal((M, d)).astype(np.float32)
+    g = to_device(G)
+    k = d // 100
+    plan = P.Plan(P.MLMC_TOPK, M, d, P.MLMC_F32, [10, k, k + d // 8, k + d // 8 + d // 8 + 1], None)
+    for level in (1, 2, 3):
+        plan.ws.fill_(0)
+        print(f"marked bands {M}x{d} level {level}", flush=True)
+        p = _one_hot(M, 3, level)
+        msg = P.mlmc_compress_topk(plan, g, seed=3, step=0, p=p)
+        assert plan.status(informational=True) == 0
+        marks = _marks(plan)
+        if level < 3 or wide:
+            assert all(_covered(marks, msg, 4, d)) and float((marks != 0).float().mean()) > 0.01
+        else:
+            assert not bool(marks.any())
+        if d < 1 << 20:
+            check_topk_against_oracle(plan, G, 3, 0, msg, adaptive=False, p=p[0].tolist())
 
 
 def _row16(what, d):
