@@ -56,7 +56,7 @@ static const char* const k_names[K_NUM] = {
     "k_bits_smax", "k_bits_extract", "k_bits_redo", "k_agg_bits", "k_tileoff", "k_agg_sparse", "k_message_bits", "k_rtn_norms", "k_rtn_draw",
     "k_rs_hist", "k_rs_scan", "k_rs_scatter", "k_sb_norms", "k_sb_draw", "k_sb_mark", "k_sb_offsets", "k_sb_write", "k_se_count", "k_se_scan",
     "k_se_split", "k_se_zone", "k_row_select", "k_row_write", "k_c16_hist", "k_c16_reduce", "k_c16_scan", "k_c16_mark", "k_c16_offsets", "k_c16_write",
-    "k_bits_extract_words", "k_agg_words"};
+    "k_bits_extract_words", "k_agg_words", "k_scan_marks"};
 struct ProfPair { int id; hipEvent_t e0, e1; };
 static std::vector<ProfPair> g_pending;
 static std::vector<ProfPair> g_free;
@@ -151,7 +151,7 @@ static void fill_topk_args(const mlmc_plan_t* pl, TopkArgs& a, const void* g, in
     a.cand = (uint2*)(w + pl->off_cand);
     a.cand2 = (uint2*)(w + pl->off_cand2);
     a.cand_priv = (uint2*)(w + pl->off_cand_priv);
-    if (pl->off_marks) {
+    if (pl->off_marks && pl->staging) {
         a.marks = (uint64_t*)(w + pl->off_marks);
         a.mark_words = (int64_t)pl->chunks_per_row * pl->chunk / 256;
     }
@@ -721,6 +721,7 @@ mlmc_status mlmc_level_norms(const mlmc_plan_t* plan, const void* g, int64_t ld,
     fill_topk_args(plan, a, g, ld, ws, dev_status);
     a.all_thresholds = 1;
     a.draw_mode = -1;  // norms only, no draw
+    a.marks = nullptr;
     a.norms_user = norms;
     if (plan->c16_wgs) return topk16_run(plan, a, false, st);
     if (plan->row_mode) return row_topk_run(plan, a, false, st);

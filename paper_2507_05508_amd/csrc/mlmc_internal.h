@@ -292,7 +292,7 @@ enum KernelId {
     K_BITS_MAX, K_BITS_EXTRACT, K_BITS_REDO, K_AGG_BITS, K_TILEOFF, K_AGG_SPARSE, K_MSGBITS, K_RTN_NORMS, K_RTN_DRAW,
     K_RS_HIST, K_RS_SCAN, K_RS_SCATTER, K_SB_NORMS, K_SB_DRAW, K_SB_MARK, K_SB_OFFSETS, K_SB_WRITE, K_SE_COUNT, K_SE_SCAN, K_SE_SPLIT, K_SE_ZONE,
     K_ROW_SELECT, K_ROW_WRITE, K_C16_HIST, K_C16_REDUCE, K_C16_SCAN, K_C16_MARK, K_C16_OFFSETS, K_C16_WRITE,
-    K_BITS_WORDS, K_AGG_WORDS, K_NUM
+    K_BITS_WORDS, K_AGG_WORDS, K_SCAN_MARKS, K_NUM
 };
 extern bool g_prof_on;
 void prof_begin(int id, hipStream_t st);

@@ -2543,7 +2543,7 @@ static mlmc_status launch_select(const mlmc_plan_t* pl, const TopkArgs& a, bool 
         const int kh = exact_pass ? K_REDO : K_HIST, ks = exact_pass ? K_REDO : K_SCAN;
         const int km = exact_pass ? K_REDO : K_MAIN;
         MLMC_LAUNCH(kh, st, k_hist<VEC><<<hgrid, HIST_THREADS, 0, st>>>(a, exact_pass));
-        if (a.marks) MLMC_LAUNCH(ks, st, k_scan<true><<<pl->M, 1024, 0, st>>>(a, exact_pass));
+        if (a.marks) MLMC_LAUNCH(exact_pass ? K_REDO : K_SCAN_MARKS, st, k_scan<true><<<pl->M, 1024, 0, st>>>(a, exact_pass));
         else MLMC_LAUNCH(ks, st, k_scan<false><<<pl->M, 1024, 0, st>>>(a, exact_pass));
         if (exact_pass) {
             if (sums) MLMC_LAUNCH(km, st, k_main<VEC, true, true><<<mgrid, MAIN_THREADS, 0, st>>>(a, exact_pass));

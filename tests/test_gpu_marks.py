@@ -5,7 +5,7 @@ import pytest
 import torch
 
 import paper_2507_05508_amd as P
-from gpu_util import check_topk_against_oracle, to_device
+from gpu_util import check_topk_against_oracle, launched, to_device
 
 pytestmark = pytest.mark.gpu
 
@@ -73,6 +73,26 @@ def test_bands_that_are_marked(M, d, wide):
             assert not bool(marks.any())
         if d < 1 << 20:
             check_topk_against_oracle(plan, G, 3, 0, msg, adaptive=False, p=p[0].tolist())
+
+
+def test_marking_kernels_only_where_something_is_marked():
+    """Staging switched off, norms only, and plans too large for marks."""
+    g = torch.randn((4, 300_001), device="cuda")
+    for p in (None, [0.5, 0.5]):
+        plan = P.Plan(P.MLMC_TOPK, 4, 300_001, P.MLMC_F32, [100, 3000, 30_000], p)
+        call = lambda: P.mlmc_compress_topk(plan, g, seed=1, step=0)
+        names = launched(call)
+        assert "k_scan_marks" in names and "k_scan" not in names
+        plan.set_staging(False)
+        names = launched(call)
+        assert "k_scan" in names and "k_scan_marks" not in names
+        plan.set_staging(True)
+        assert "k_scan_marks" in launched(call)
+        names = launched(lambda: P.mlmc_level_norms(plan, g))
+        assert "k_scan" in names and "k_scan_marks" not in names
+    g = torch.randn((4, 100_000), device="cuda")      # adaptive plans of this size have staging off
+    plan = P.Plan(P.MLMC_TOPK, 4, 100_000, P.MLMC_F32, [100, 3000, 30_000], None)
+    assert "k_scan_marks" not in launched(lambda: P.mlmc_compress_topk(plan, g, seed=1, step=0))
 
 
 def _row16(what, d):
