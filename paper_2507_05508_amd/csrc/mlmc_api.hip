@@ -277,6 +277,13 @@ static mlmc_status plan_stopk(mlmc_plan_t** plan, int M, int64_t d, int in_dtype
     // against 110, 4 of 524289: 112 against 112, or 129 against 152 where nine in ten are zero; 8 of 8192: 106 against 102).
     const bool bins = L <= SE_LMAX && d >= 8192 && (in_dtype == MLMC_F32 || M >= 8 || (int64_t)M * d >= ((int64_t)1 << 22));
     if (bins) {
+        // The forecast of the drawn segment and the marks cost some 4 to 9 us (a sum and a window per bin, the draw in front of the second read) and spare most of the third read,
+        // which comes from the last cache in smaller plans; segments of a thirtieth of a row or more have an entry in most of its lines.  Pass, us, without / with them, one scale
+        // and many: 100 levels 8 of 16384 75 / 77 and 74 / 82, 8 of 300001 101 / 103 and 100 / 106, 8 of 1000001 119 / 120 and 120 / 123, 4 of 3000001 122 / 121 and 124 / 125, 1 of
+        // 16000001 154 / 153 and 154 / 153, 8 of 4000001 176 / 165 and 176 / 172, 8 of 11689512 368 / 330 and 361 / 325; 1000 levels 8 of 300001 128 / 131 and 119 / 125, 2 of 4000001
+        // 139 / 137 and 131 / 131, 8 of 4000001 204 / 193 and 195 / 188; 30 levels 8 of 4000001 176 / 180 and 190 / 187, 32 of 2000001 302 / 304 and 323 / 306; 10 levels 32 of 1000001
+        // 227 / 235 and 270 / 271.  16 bits, 100 levels: 32 of 300001 111 / 110 and 115 / 120, 4 of 4000001 115 / 112 and 117 / 120, 8 of 4000001 148 / 142 and 149 / 147.
+        pl->se_marks = L >= 32 && (int64_t)M * d >= ((int64_t)1 << 24) ? 1 : 0;
         pl->se_rep = L <= 1024 ? 2 : (L <= 2304 ? 1 : 0);   // (L + 256) << se_rep sums fill 40 KB of LDS
         // At least 2^19 entries of a row are sampled for the map.  Half as many as with 2^20 cost nothing where the map was the same and save their reads
         // (32 rows of 2e6 entries 296 -> 277 us, 16 of 4e6 in 16 bits 230 -> 224; 8 of 1.17e7 320 both).
@@ -403,6 +410,7 @@ static void fill_stopk_args(const mlmc_plan_t* pl, StopkArgs& a, const void* g, 
         a.se_got = (uint2*)(w + pl->off_se_got);
         a.se_cand = (uint32_t*)(w + pl->off_se_cand);
         a.se_cblks = (pl->d + 1023) / 1024;
+        a.se_marks = pl->se_marks;
     }
     a.tile_off = (uint32_t*)(w + pl->off_tileoff);
     a.norms = (double*)(w + pl->off_norms);
@@ -715,6 +723,7 @@ mlmc_status mlmc_level_norms(const mlmc_plan_t* plan, const void* g, int64_t ld,
         StopkArgs sa;
         fill_stopk_args(plan, sa, g, ld, ws, dev_status);
         sa.norms_user = norms;
+        sa.se_marks = 0;
         return stopk_run(plan, sa, false, st);
     }
     TopkArgs a;

@@ -283,6 +283,7 @@ struct StopkArgs {
     uint2* se_got;           // [M] lowest and highest key of the entries that the second read marks
     uint32_t* se_cand;       // [M][se_cblks][8] a bit per four consecutive entries: one of them is marked
     int64_t se_cblks;        // blocks of 1024 entries of a row
+    int se_marks;            // 1: a forecast of the drawn segment, whose entries the second read marks
     uint2* se_tie;           // [M][ntiles] entries equal to the two thresholds of the drawn segment, where they are split
 };
 
@@ -333,7 +334,7 @@ struct mlmc_plan_s {
     size_t off_pa, off_pb, off_counts, off_bitmap, off_tilecnt, off_clear_end, off_srow, off_bintot;
     size_t off_se_coarse, off_se_big, off_se_end, off_se_map, off_se_info, off_se_nbins, off_se_part, off_se_total, off_se_class, off_se_gtab, off_se_thr,
         off_se_zone, off_se_nz, off_se_list, off_se_list2, off_se_tie, off_se_bsum, off_se_gsum, off_se_mid, off_se_bigz, off_se_item, off_se_apx, off_se_win, off_se_got, off_se_cand;   // off_se_end: end of what is cleared per call (0: the plan sorts)
-    int se_shift, se_wgs, se_rep, se_mids, se_bigs, se_items;
+    int se_shift, se_wgs, se_rep, se_mids, se_bigs, se_items, se_marks;
     int64_t se_slice;
     size_t off_rtn_sums, off_rtn_part, off_rtn_total;   // Round-to-Nearest plans
     int rtn_wgs;              // workgroups per row that count magnitudes (0: not counted)

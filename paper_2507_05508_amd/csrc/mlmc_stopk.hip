@@ -323,7 +323,7 @@ __global__ __launch_bounds__(1024) void k_sb_draw(StopkArgs a) {
         sr->count = lo + a.s < a.d ? a.s : a.d - lo;
         if (a.se_thr) {   // ladders that are not sorted: what the message kernels need of the row, in one place
             const uint2* thr = a.se_thr + (size_t)row * (a.L + 1) + level;
-            const uint2 h = thr[-1], o = thr[0], got = a.se_got[row];
+            const uint2 h = thr[-1], o = thr[0], got = a.se_marks ? a.se_got[row] : make_uint2(~0u, 0u);
             sr->hi = h;
             sr->thr_lo = o;
             sr->few = o.x >= got.x && h.x <= got.y ? 1 : 0;
@@ -481,11 +481,11 @@ static mlmc_status launch_stopk(const mlmc_plan_t* pl, const StopkArgs& a, bool 
 //   k_se_wide     the same for zones of many entries (repeated keys; rows that the sample misjudged), by counts of their keys
 //   k_se_norms / k_sb_draw   Delta_l, level
 //   k_se_mark / k_se_offsets / k_se_write   bitmap of the drawn segment and its message; entries equal to a
-//                 threshold whose equal keys are split are told apart by their rank in index order.  The exact counts of the bins give the
-//                 norms to about 1e-4, and with them, before the second read, a key window that holds the drawn segment nearly always: that read
-//                 leaves a bit per four entries and only those are looked at, in place of a third read of the rows (73 -> 13 us, the second one 121 -> 119
-//                 with what the forecast and the marks cost it, 11)
-// Two reads of the rows and about 10 bytes per entry of other traffic against 4 x 24 bytes and more for the sort of pairs:
+//                 threshold whose equal keys are split are told apart by their rank in index order: a third read of the rows.  In large plans
+//                 (se_marks) the exact counts of the bins give the norms to about 1e-4, and with them, before the second read, a key window that holds
+//                 the drawn segment nearly always: that read leaves a bit per four entries and only those are looked at (73 -> 13 us, the second one
+//                 121 -> 119 with what the forecast and the marks cost it, 11)
+// Two reads of the rows, three in smaller plans, and about 10 bytes per entry of other traffic against 4 x 24 bytes and more for the sort of pairs:
 // 8 rows of 1.17e7 fp32 entries at 1000 levels, compress + aggregate: 2788 -> 430 us; with the forecast, one addition per entry in the second read
 // and zones of one boundary ranked in one bucket 401 -> 325.  The line at SE_LMAX levels is where the
 // class of a bin and the list cursors of a zone per boundary still fit LDS beside the map and the sums.
@@ -835,7 +835,7 @@ __global__ __launch_bounds__(256) void k_se_scan(StopkArgs a) {
         thr[0] = make_uint2(0xFFFFFFFFu, 0u);
         thr[a.L] = make_uint2(0u, SE_ALL);
     }
-    if (a.level) {   // uniform: a message follows
+    if (a.se_marks) {   // uniform
         if (n && nb == 0) apx_add(t0 - 1u, __dmul_rn(mid_square(in.x, in.y), (double)n));
         else if (nb && nb <= 32u) forecast_parts(in.x, in.y, cum, n, 0u, 1u);
         else if (nb) s_win[atomicAdd(&s_wide, 1u)] = make_uint4(in.x, in.y, cum, n);
@@ -848,7 +848,7 @@ __global__ __launch_bounds__(256) void k_se_scan(StopkArgs a) {
     __syncthreads();
     for (uint32_t i = 0; i < s_many; ++i)   // (zeros; a row of one value has every boundary here)
         key_parts(s_key[i].x, s_key[i].y, s_key[i].z, s_key[i].w, (uint32_t)tid, 256u);
-    if (a.level) {
+    if (a.se_marks) {
         for (uint32_t i = 0; i < s_wide; ++i) forecast_parts(s_win[i].x, s_win[i].y, s_win[i].z, s_win[i].w, (uint32_t)tid, 256u);
         __syncthreads();
         if (s_apx[tid] > 0.0 && band0 + tid < (uint32_t)a.L) unsafeAtomicAdd(&a.se_apx[(size_t)row * a.L + band0 + tid], s_apx[tid]);
@@ -956,8 +956,8 @@ __global__ __launch_bounds__(SE_THREADS) void k_se_split(StopkArgs a) {
     const int64_t i0 = (int64_t)slice * a.se_slice, i1 = i0 + a.se_slice < a.d ? i0 + a.se_slice : a.d;
     uint32_t* list = a.se_list + (size_t)row * a.d;
     const uint32_t rlane = (lane & ((1u << rs) - 1u)) * 8u, nobody = ((uint32_t)a.L + 255u) << rs;
-    // MARK: a bit per four entries, the key of one of them is in the window (wspan stays below 2^32 - 1: keys are below 2^31, or the upper end is
-    // 2^32 - 1 and the lower one a key).
+    // MARK: a bit per four entries, the key of one of them is in the window.  (Where one band has all of a row's norm, the window may reach from key 0 to
+    // 2^32 - 1 and takes in the entries past the row's end too: their marks load nothing.)
     uint32_t wlo = 0, wspan = 0;
     uint32_t* cand = nullptr;
     if (MARK) {
@@ -1748,8 +1748,8 @@ static mlmc_status launch_bins(const mlmc_plan_t* pl, const StopkArgs& a, bool m
     MLMC_LAUNCH(K_SE_SCAN, st, k_se_reduce<<<dim3(SE_BLOCKS, M), 256, 0, st>>>(a));
     MLMC_LAUNCH(K_SE_SCAN, st, k_se_scan<<<dim3(SE_BLOCKS, M), 256, 0, st>>>(a));
     const dim3 sgrid(a.se_wgs, M);
-    if (stream && message) MLMC_LAUNCH(K_SE_SPLIT, st, k_se_split<DT, true, true><<<sgrid, SE_THREADS, 0, st>>>(a));
-    else if (message) MLMC_LAUNCH(K_SE_SPLIT, st, k_se_split<DT, false, true><<<sgrid, SE_THREADS, 0, st>>>(a));
+    if (stream && a.se_marks) MLMC_LAUNCH(K_SE_SPLIT, st, k_se_split<DT, true, true><<<sgrid, SE_THREADS, 0, st>>>(a));
+    else if (a.se_marks) MLMC_LAUNCH(K_SE_SPLIT, st, k_se_split<DT, false, true><<<sgrid, SE_THREADS, 0, st>>>(a));
     else if (stream) MLMC_LAUNCH(K_SE_SPLIT, st, k_se_split<DT, true, false><<<sgrid, SE_THREADS, 0, st>>>(a));
     else MLMC_LAUNCH(K_SE_SPLIT, st, k_se_split<DT, false, false><<<sgrid, SE_THREADS, 0, st>>>(a));
     MLMC_LAUNCH(K_SE_ZONE, st, k_se_zone<<<dim3(a.L - 1 + (a.L + 255 + SZ_THREADS - 1) / SZ_THREADS, M), SZ_THREADS, 0, st>>>(a));

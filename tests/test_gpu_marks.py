@@ -4,8 +4,10 @@ import numpy as np
 import pytest
 import torch
 
+import mlmc_workloads as W
 import paper_2507_05508_amd as P
-from gpu_util import check_topk_against_oracle, launched, to_device
+from gpu_util import check_topk_against_oracle, launched, to_device, u32
+from oracle import mlmc as O
 
 pytestmark = pytest.mark.gpu
 
@@ -148,3 +150,78 @@ def test_forecast_marks_by_slices(what, base, band, marked, M, d):
             else:
                 assert not bool(marks.any())
         del plan, wide, msg, want
+
+
+def _few(plan):
+    """Per row, after an s-segmented Top-k call: 1 where the second read has marked the whole drawn segment."""
+    return _region(plan, 48 * plan.M, 4 * (plan.num_tiles + 1) * plan.M, 8 * plan.L * plan.M).view(torch.int32).view(plan.M, 12)[:, 10].tolist()
+
+
+@pytest.mark.parametrize("M,d,s,bf16,marks", [
+    (16, 1 << 20, 1048, False, True), (16, 1 << 20, 1 << 15, False, True), (16, 1 << 20, 1048, True, True), (2, 8_400_001, 2100, True, True),
+    (16, (1 << 20) - 1, 1048, False, False), (15, 1 << 20, 1048, True, False),       # fewer than 2^24 entries in all
+    (16, 1 << 20, 33_826, False, False), (16, 1 << 20, 1 << 19, True, False),        # 31 levels, two
+    (8, 16_384, 163, False, False), (1, 300_001, 3000, False, False),
+])
+def test_stopk_rows_that_are_marked(M, d, s, bf16, marks):
+    """The plans with a forecast, and that it holds for nearly every normal row (levels within 2^-12 of the whole of where the drawn word falls)."""
+    g = torch.randn((M, d), generator=torch.Generator(device="cuda").manual_seed(d), device="cuda")
+    plan = P.Plan(P.MLMC_STOPK, M, d, P.MLMC_BF16 if bf16 else P.MLMC_F32, [s], None)
+    g, few = g.to(torch.bfloat16) if bf16 else g, []
+    for step in range(3):
+        P.mlmc_compress_topk(plan, g, seed=1, step=step)
+        assert plan.status() == 0
+        few += _few(plan)
+    print(f"stopk marks {M}x{d} s={s} bf16={bf16}: {sum(few)} of {len(few)}", flush=True)
+    assert sum(few) >= 0.75 * len(few) if marks else few == [0] * len(few)
+
+
+@pytest.mark.parametrize("what,s,bf16", [
+    ("normal", 3001, False), ("normal", 32_769, False), ("normal", 262, True),
+    ("heavy", 3001, False),      # one entry in a coarse bin carries most of a row: the forecast misses now and then
+    ("loud", 3001, False),       # the top segments lie in a few tiles, which are read whole
+    ("few", 3001, False), ("few", 262, True),     # boundaries among equal keys
+])
+def test_stopk_messages_from_marked_entries(what, s, bf16):
+    """Rows with a last block of one entry: the message of marked, partly marked and unmarked segments against the oracle."""
+    M, d = 16, (1 << 20) + 1
+    rng = np.random.default_rng(s)
+    G = rng.standard_normal((3, d)).astype(np.float32)
+    if what == "heavy":
+        G = (np.tan(np.pi * (rng.random((3, d)) - 0.5)) ** 3).astype(np.float32)
+    elif what == "loud":
+        G[:, : d // 50] *= 1e4
+    elif what == "few":
+        G = (np.round(G * 4) / 4).astype(np.float32)
+    if bf16:
+        G = W.f32_to_bf16_bits(G)
+    g = to_device(G).repeat(6, 1)[:M].contiguous()
+    plan = P.Plan(P.MLMC_STOPK, M, d, P.MLMC_BF16 if bf16 else P.MLMC_F32, [s], None)
+    norms = [O.level_norms_row(G[i], plan.ladder)[0] for i in range(3)]
+    few = []
+    for step in range(2):
+        plan.ws.fill_(0xFF)
+        print(f"stopk marked message {what} s={s} bf16={bf16} step={step}", flush=True)
+        msg = P.mlmc_compress_topk(plan, g, seed=2, step=step)
+        assert plan.status() == 0
+        few += _few(plan)
+        off, level, got = msg.row_off.cpu().numpy(), msg.level.cpu().numpy(), msg.norms.cpu().numpy()
+        for i in range(M):
+            assert np.array_equal(got[i].view(np.uint64), np.array(norms[i % 3]).view(np.uint64))
+            assert level[i] == O.draw_level(O.adaptive_p(norms[i % 3]), 2, step, i)
+        for i in (0, 4, 11, 15):
+            want = O.compress_topk_row(G[i % 3], plan.ladder, O.adaptive_p(norms[i % 3]), 2, step, i)
+            assert np.array_equal(u32(msg.idx[off[i]:off[i + 1]]), want["idx"])
+            assert np.array_equal(u32(msg.val[off[i]:off[i + 1]]), want["val"].view(np.uint32))
+            bounds = np.searchsorted(want["idx"], np.arange(plan.num_tiles + 1, dtype=np.int64) * P.MLMC_TILE)
+            assert np.array_equal(u32(msg.tile_off[i]), bounds.astype(np.uint32))
+    assert any(few)
+
+
+def test_stopk_rows_with_nan_and_inf_end():
+    """Sums that are no numbers: refused by the status word, and ended all the same."""
+    g = torch.randn((16, 1 << 20), device="cuda")
+    g[0, 5], g[1, 7] = float("nan"), float("inf")
+    plan = P.Plan(P.MLMC_STOPK, 16, 1 << 20, P.MLMC_F32, [3001], None)
+    P.mlmc_compress_topk(plan, g, seed=1, step=1)
+    assert plan.status() & P.MLMC_DEV_NONFINITE
