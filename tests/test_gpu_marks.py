@@ -97,6 +97,19 @@ def test_marking_kernels_only_where_something_is_marked():
     assert "k_scan_marks" not in launched(lambda: P.mlmc_compress_topk(plan, g, seed=1, step=0))
 
 
+def test_adaptive_forecasts_hold():
+    """Rows of one distribution with few levels: the estimate from the whole row decides as the exact norms do, or within its margin."""
+    M, d = 8, 200_003
+    G = np.random.default_rng(1).standard_normal((M, d)).astype(np.float32)
+    g = to_device(G)
+    plan = P.Plan(P.MLMC_TOPK, M, d, P.MLMC_F32, [50, 500, 5000, 20_000], None)
+    for step in range(3):
+        plan.ws.fill_(0)
+        msg = P.mlmc_compress_topk(plan, g, seed=2, step=step)
+        assert plan.status() == 0
+        assert all(_covered(_marks(plan), msg, 4, d))
+
+
 def _row16(what, d):
     gen = torch.Generator(device="cuda").manual_seed(d)
     x = torch.randn(d, generator=gen, device="cuda")
