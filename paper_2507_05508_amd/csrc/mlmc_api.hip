@@ -339,6 +339,7 @@ static mlmc_status plan_stopk(mlmc_plan_t** plan, int M, int64_t d, int in_dtype
     pl->off_clear_end = off;
     pl->off_srow = off;
     off = align_up(off + sizeof(SRow) * (size_t)M, 256);
+    if (bins) pl->off_sseg = take(sizeof(SSeg) * (size_t)M);
     pl->off_tileoff = off;
     off = align_up(off + sizeof(uint32_t) * (size_t)(pl->ntiles + 1) * M, 256);
     pl->off_norms = off;
@@ -415,6 +416,7 @@ static void fill_stopk_args(const mlmc_plan_t* pl, StopkArgs& a, const void* g, 
     a.tile_off = (uint32_t*)(w + pl->off_tileoff);
     a.norms = (double*)(w + pl->off_norms);
     a.srow = (SRow*)(w + pl->off_srow);
+    a.sseg = (SSeg*)(w + pl->off_sseg);
     a.dev_status = dev_status;
 }
 

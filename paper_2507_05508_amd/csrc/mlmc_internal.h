@@ -208,12 +208,14 @@ struct BitsArgs {
 
 // s-segmented Top-k (uniform ladder k_l = min(s l, d), thousands of levels)
 constexpr int SLMAX = MLMC_MAX_SLEVELS;
-struct SRow {           // per row: the drawn segment
+struct SRow {           // per row: the drawn segment (one thread of k_sb_offsets and k_se_offsets adds up the counts of all rows before its own: kept short)
     int32_t level;
     float weight;
     int64_t lo, count;  // its positions in the sorted row: [lo, lo + count)
-    uint2 hi, thr_lo;   // rows that are not sorted: thresholds of its two boundaries, as in se_thr
-    int32_t few, pad_;  // 1: the second read has marked all of its entries
+};
+struct SSeg {           // the same of rows that are not sorted
+    uint2 hi, lo;       // thresholds of its two boundaries, as in se_thr
+    int32_t few, level; // few: 1 where the second read has marked all of its entries
 };
 // The way without a sort (ladders of up to SE_LMAX levels)
 constexpr int SE_LMAX = 4096;
@@ -246,6 +248,7 @@ struct StopkArgs {
     double* norms;           // [M][L]
     double* norms_user;
     SRow* srow;              // [M]
+    SSeg* sseg;              // [M]
     int32_t* level;
     int64_t* row_off;
     uint32_t* idx;
@@ -331,7 +334,7 @@ struct mlmc_plan_s {
     int64_t s;
     int nblk;
     int64_t bm_words;
-    size_t off_pa, off_pb, off_counts, off_bitmap, off_tilecnt, off_clear_end, off_srow, off_bintot;
+    size_t off_pa, off_pb, off_counts, off_bitmap, off_tilecnt, off_clear_end, off_srow, off_sseg, off_bintot;
     size_t off_se_coarse, off_se_big, off_se_end, off_se_map, off_se_info, off_se_nbins, off_se_part, off_se_total, off_se_class, off_se_gtab, off_se_thr,
         off_se_zone, off_se_nz, off_se_list, off_se_list2, off_se_tie, off_se_bsum, off_se_gsum, off_se_mid, off_se_bigz, off_se_item, off_se_apx, off_se_win, off_se_got, off_se_cand;   // off_se_end: end of what is cleared per call (0: the plan sorts)
     int se_shift, se_wgs, se_rep, se_mids, se_bigs, se_items, se_marks;

@@ -324,9 +324,7 @@ __global__ __launch_bounds__(1024) void k_sb_draw(StopkArgs a) {
         if (a.se_thr) {   // ladders that are not sorted: what the message kernels need of the row, in one place
             const uint2* thr = a.se_thr + (size_t)row * (a.L + 1) + level;
             const uint2 h = thr[-1], o = thr[0], got = a.se_marks ? a.se_got[row] : make_uint2(~0u, 0u);
-            sr->hi = h;
-            sr->thr_lo = o;
-            sr->few = o.x >= got.x && h.x <= got.y ? 1 : 0;
+            a.sseg[row] = SSeg{h, o, o.x >= got.x && h.x <= got.y ? 1 : 0, level};
         }
         a.level[row] = level;
     }
@@ -1503,8 +1501,8 @@ __global__ __launch_bounds__(64) void k_se_norms(StopkArgs a) {
 struct SegTest {
     uint32_t tau_hi, tau_lo, q_hi, q_lo;
     bool cut_hi, cut_lo, same;   // equal keys split at a boundary; both boundaries at one key
-    __device__ __forceinline__ SegTest(const SRow& r) {
-        tau_hi = r.hi.x; q_hi = r.hi.y; tau_lo = r.thr_lo.x; q_lo = r.thr_lo.y;
+    __device__ __forceinline__ SegTest(const SSeg& r) {
+        tau_hi = r.hi.x; q_hi = r.hi.y; tau_lo = r.lo.x; q_lo = r.lo.y;
         same = tau_hi == tau_lo;
         cut_hi = r.level > 1 && q_hi != SE_ALL;
         cut_lo = q_lo != SE_ALL && !same;
@@ -1537,7 +1535,7 @@ __global__ __launch_bounds__(256) void k_se_mark(StopkArgs a) {
     if (tile >= a.ntiles) return;
     uint32_t m = 0;   // 64 consecutive entries, a bit per four
     if (tile * (TILE / 1024) + (lane >> 4) < a.se_cblks) m = ((const uint16_t*)(a.se_cand + ((size_t)row * a.se_cblks + tile * (TILE / 1024)) * 8))[lane];
-    const SRow sr = a.srow[row];
+    const SSeg sr = a.sseg[row];
     const SegTest st(sr);
     RowLoader<DT, true> ld(a.g, a.ld, a.d, row);
     ((uint2*)s_bm[wave])[lane] = make_uint2(0u, 0u);
@@ -1614,7 +1612,7 @@ __global__ __launch_bounds__(256) void k_se_mark(StopkArgs a) {
 __global__ __launch_bounds__(1024) void k_se_offsets(StopkArgs a) {
     __shared__ uint32_t s_scan[1024 / 64 + 1];
     const int row = blockIdx.x, tid = threadIdx.x;
-    const SegTest st(a.srow[row]);
+    const SegTest st(a.sseg[row]);
     uint32_t* to = a.tile_off + (size_t)row * (a.ntiles + 1);
     const uint32_t* tc = a.tile_cnt + (size_t)row * a.ntiles;
     uint2* tie = a.se_tie + (size_t)row * a.ntiles;
@@ -1661,11 +1659,11 @@ __global__ __launch_bounds__(256) void k_se_write(StopkArgs a) {
     const uint32_t* bm = a.bitmap + (size_t)row * a.bm_words;
     const int64_t w0 = tile * (TILE / 32) + lane * 2;
     const uint2 m = w0 < a.bm_words ? *(const uint2*)(bm + w0) : make_uint2(0u, 0u);
-    const SRow sr = a.srow[row];
+    const SSeg sr = a.sseg[row];
+    const float w = a.srow[row].weight;
     if (to[tile + 1] == to[tile]) return;   // nothing of the segment in this tile
     const SegTest st(sr);
     RowLoader<DT, true> ld(a.g, a.ld, a.d, row);
-    const float w = sr.weight;
     uint64_t bits = (uint64_t)m.y << 32 | m.x;
     // f(position, fp32 bits, ordinal) for the lane's entries in order, the loads of eight of them in flight (a run of equal entries
     // fills whole lanes: one load at a time, 64 in a row)
