@@ -234,6 +234,8 @@ __global__ __launch_bounds__(1024) void k_c16_forecast(TopkArgs a) {
 }
 
 // One workgroup per (slice, row), one per CU: the counters fill its LDS.  Bound by the read.
+// FORECAST: rows with a forecast are marked.
+template <bool FORECAST>
 __global__ __launch_bounds__(C16_THREADS) void k_c16_hist(TopkArgs a) {
     __shared__ __align__(16) uint32_t s_h[C16_LDS];
     const int row = blockIdx.y;
@@ -242,9 +244,9 @@ __global__ __launch_bounds__(C16_THREADS) void k_c16_hist(TopkArgs a) {
     const uint16_t* g = (const uint16_t*)a.g + (int64_t)row * a.ld;
     RowInfo* ri = a.rinfo + row;
     __shared__ uint32_t s_marked;
-    const bool marking = a.c16_mark && ri->mark_on;   // uniform
+    const bool marking = FORECAST && ri->mark_on;   // uniform
     uint32_t marked = 0;
-    if (threadIdx.x == 0) s_marked = 0;
+    if (FORECAST && threadIdx.x == 0) s_marked = 0;
     if (marking)
         marked = count16_slice<true>(g, i0, i1, s_h, C16Window{ri->mark_lo, ri->mark_hi - ri->mark_lo + 1u, ri->mark_base}, a.c16_mark + ((size_t)row * a.ntiles * TILE + i0) / 512);
     else
@@ -1105,7 +1107,8 @@ mlmc_status topk16_run(const mlmc_plan_t* pl, const TopkArgs& args, bool message
         MLMC_LAUNCH(K_HIST, st, k_c16_sample<<<dim3(pl->c16_wgs < C16_PARTS ? pl->c16_wgs : C16_PARTS, pl->M), 512, 0, st>>>(a));
         MLMC_LAUNCH(K_SCAN, st, k_c16_forecast<<<pl->M, 1024, 0, st>>>(a));
     }
-    MLMC_LAUNCH(K_C16_HIST, st, k_c16_hist<<<grid, C16_THREADS, 0, st>>>(a));
+    if (a.c16_mark) MLMC_LAUNCH(K_C16_HIST, st, k_c16_hist<true><<<grid, C16_THREADS, 0, st>>>(a));
+    else MLMC_LAUNCH(K_C16_HIST, st, k_c16_hist<false><<<grid, C16_THREADS, 0, st>>>(a));
     const dim3 rgrid(C16_KEYS / C16_BLOCK, pl->M);
 #define MLMC_C16_REDUCE(G, PER)                                                                                          \
     do {                                                                                                                \
