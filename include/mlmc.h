@@ -119,9 +119,10 @@ mlmc_status mlmc_plan_set_sampling(mlmc_plan_t *plan, int shift);
  * most 2^19 elements, where a second read costs less) the read that selects the thresholds also sets aside the
  * members of the band the message will hold (Eq. (6)): the level is known before the read when p is given, and
  * predicted from the sampled histogram when p is adaptive (Alg. 3); the message is then assembled from what was set
- * aside and the rows are read once (of marked rows only the marked entries are read again).  A wrong prediction, a drawn band wider
- * than an eighth of the row (cheaper to collect by reading again; not where entries are marked), or staging switched off, makes the library read the row a second time.  Run time only,
- * never a result.
+ * aside and the rows are read once.  (Plans of up to 2^25 elements mark the entries of the band instead, and read the marked
+ * ones again.)  A wrong prediction, a drawn band wider than an eighth of the row (cheaper to collect by reading again, except
+ * from several rows of up to 2^22 elements, where it is marked), or staging switched off, makes the library read the row a
+ * second time.  Run time only, never a result.
  */
 mlmc_status mlmc_plan_set_staging(mlmc_plan_t *plan, int enable);
 
