@@ -213,9 +213,10 @@ struct SRow {           // per row: the drawn segment (one thread of k_sb_offset
     float weight;
     int64_t lo, count;  // its positions in the sorted row: [lo, lo + count)
 };
-struct SSeg {           // the same of rows that are not sorted
+struct SSeg {           // what the message kernels of rows that are not sorted need, in one place
     uint2 hi, lo;       // thresholds of its two boundaries, as in se_thr
     int32_t few, level; // few: 1 where the second read has marked all of its entries
+    float weight, pad_;
 };
 // The way without a sort (ladders of up to SE_LMAX levels)
 constexpr int SE_LMAX = 4096;

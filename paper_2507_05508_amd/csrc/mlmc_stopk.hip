@@ -321,10 +321,10 @@ __global__ __launch_bounds__(1024) void k_sb_draw(StopkArgs a) {
         const int64_t lo = (int64_t)(level - 1) * a.s;
         sr->lo = lo;
         sr->count = lo + a.s < a.d ? a.s : a.d - lo;
-        if (a.se_thr) {   // ladders that are not sorted: what the message kernels need of the row, in one place
+        if (a.se_thr) {   // ladders that are not sorted
             const uint2* thr = a.se_thr + (size_t)row * (a.L + 1) + level;
             const uint2 h = thr[-1], o = thr[0], got = a.se_marks ? a.se_got[row] : make_uint2(~0u, 0u);
-            a.sseg[row] = SSeg{h, o, o.x >= got.x && h.x <= got.y ? 1 : 0, level};
+            a.sseg[row] = SSeg{h, o, o.x >= got.x && h.x <= got.y ? 1 : 0, level, sr->weight, 0.0f};
         }
         a.level[row] = level;
     }
@@ -1660,10 +1660,10 @@ __global__ __launch_bounds__(256) void k_se_write(StopkArgs a) {
     const int64_t w0 = tile * (TILE / 32) + lane * 2;
     const uint2 m = w0 < a.bm_words ? *(const uint2*)(bm + w0) : make_uint2(0u, 0u);
     const SSeg sr = a.sseg[row];
-    const float w = a.srow[row].weight;
     if (to[tile + 1] == to[tile]) return;   // nothing of the segment in this tile
     const SegTest st(sr);
     RowLoader<DT, true> ld(a.g, a.ld, a.d, row);
+    const float w = sr.weight;
     uint64_t bits = (uint64_t)m.y << 32 | m.x;
     // f(position, fp32 bits, ordinal) for the lane's entries in order, the loads of eight of them in flight (a run of equal entries
     // fills whole lanes: one load at a time, 64 in a row)

@@ -167,7 +167,7 @@ def test_forecast_marks_by_slices(what, base, band, marked, M, d):
 
 def _few(plan):
     """Per row, after an s-segmented Top-k call: 1 where the second read has marked the whole drawn segment."""
-    return _region(plan, 24 * plan.M, 4 * (plan.num_tiles + 1) * plan.M, 8 * plan.L * plan.M).view(torch.int32).view(plan.M, 6)[:, 4].tolist()
+    return _region(plan, 32 * plan.M, 4 * (plan.num_tiles + 1) * plan.M, 8 * plan.L * plan.M).view(torch.int32).view(plan.M, 8)[:, 4].tolist()
 
 
 @pytest.mark.parametrize("M,d,s,bf16,marks", [
